@@ -759,15 +759,55 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
 }
 
 // Issues the plan: fork side streams from origin, wait on producers that ran on another
-// stream, record an event after every dispatch, join everything back into origin.
+// stream, join everything back into origin.  An event is recorded only where a wait on it follows:
+// behind a dispatch that another stream's dispatch reads from, behind the last one of every side
+// stream, and at the fork if there is a side stream.  A record is a barrier packet of its own in the
+// queue, and the next kernel starts behind it: eager forwards with a record behind every dispatch had
+// 5.4-5.8 us between kernels under the profiler.  Recording only what is waited for: 2048-token chunk
+// + 64 decodes on one stream 1172 -> 1158 us, 512 + 64 on two streams 546 -> 518 us, 340 rows of a
+// 2048-wide layer 1862 -> 1837 us.
 dyn_status run_plan(dyn_layer *L, const dyn_batch *b, const dyn_schedule *s, const WsLayout &ws,
                     const std::vector<Dispatch> &plan, hipStream_t origin, bool profile) {
-    while (L->events.size() < plan.size()) {
-        hipEvent_t ev;
-        HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-        L->events.push_back(ev);
+    // Dispatches that launch nothing take no part in the stream choreography: whoever depends
+    // on one depends on what it depended on.  Waiting and recording around them would give a
+    // captured graph forked branches without a node and the same edge several times.
+    // (Profiling, eager only, keeps them so that every dispatch has its time marks.)
+    std::vector<std::vector<int>> waits(plan.size());       // producers on other streams this dispatch waits for
+    std::vector<char> record(plan.size(), 0);
+    int last_on[(DYN_MAX_PARTITIONS + 1) * DYN_MAX_STREAMS];
+    std::fill(last_on, last_on + (DYN_MAX_PARTITIONS + 1) * DYN_MAX_STREAMS, -1);
+    bool forked = false;
+    {
+        std::vector<std::vector<int>> real_deps(plan.size());
+        for (size_t i = 0; i < plan.size(); ++i) {
+            const Dispatch &d = plan[i];
+            for (int dep : d.deps) {
+                const bool elided = plan[dep].noop && !profile;
+                for (int r : elided ? real_deps[dep] : std::vector<int>{dep})
+                    if (std::find(real_deps[i].begin(), real_deps[i].end(), r) == real_deps[i].end()) real_deps[i].push_back(r);
+            }
+            if (d.noop && !profile) continue;
+            // one wait per producer stream: a stream's events complete in order, the latest covers the rest
+            for (int dep : real_deps[i]) {
+                if (plan[dep].key() == d.key()) continue;
+                bool latest = true;
+                for (int other : real_deps[i]) latest = latest && !(plan[other].key() == plan[dep].key() && other > dep);
+                if (latest) { waits[i].push_back(dep); record[dep] = 1; }
+            }
+            last_on[d.key()] = (int)i;
+            forked = forked || d.key() != 0;
+        }
     }
-    if (!L->fork_event) HIP_TRY(hipEventCreateWithFlags(&L->fork_event, hipEventDisableTiming));
+    for (int key = 1; key < (DYN_MAX_PARTITIONS + 1) * DYN_MAX_STREAMS; ++key)
+        if (last_on[key] >= 0) record[last_on[key]] = 1;
+    if (forked) {
+        while (L->events.size() < plan.size()) {
+            hipEvent_t ev;
+            HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+            L->events.push_back(ev);
+        }
+        if (!L->fork_event) HIP_TRY(hipEventCreateWithFlags(&L->fork_event, hipEventDisableTiming));
+    }
     if (profile) {
         while (L->prof_events.size() < 1 + 4 * plan.size()) {
             hipEvent_t ev;
@@ -776,23 +816,10 @@ dyn_status run_plan(dyn_layer *L, const dyn_batch *b, const dyn_schedule *s, con
         }
         HIP_TRY(hipEventRecord(L->prof_events[0], origin));
     }
-    HIP_TRY(hipEventRecord(L->fork_event, origin));
+    if (forked) HIP_TRY(hipEventRecord(L->fork_event, origin));
     bool used[(DYN_MAX_PARTITIONS + 1) * DYN_MAX_STREAMS] = {};
-    int last_on[(DYN_MAX_PARTITIONS + 1) * DYN_MAX_STREAMS];
-    std::fill(last_on, last_on + (DYN_MAX_PARTITIONS + 1) * DYN_MAX_STREAMS, -1);
-    std::vector<hipStream_t> st_of(plan.size());
-    // Dispatches that launch nothing take no part in the stream choreography: whoever depends
-    // on one depends on what it depended on.  Waiting and recording around them would give a
-    // captured graph forked branches without a node and the same edge several times.
-    // (Profiling, eager only, keeps them so that every dispatch has its time marks.)
-    std::vector<std::vector<int>> real_deps(plan.size());
     for (size_t i = 0; i < plan.size(); ++i) {
         const Dispatch &d = plan[i];
-        for (int dep : d.deps) {
-            const bool elided = plan[dep].noop && !profile;
-            for (int r : elided ? real_deps[dep] : std::vector<int>{dep})
-                if (std::find(real_deps[i].begin(), real_deps[i].end(), r) == real_deps[i].end()) real_deps[i].push_back(r);
-        }
         if (d.noop && !profile) continue;
         const int key = d.key();
         hipStream_t st = origin;
@@ -802,14 +829,7 @@ dyn_status run_plan(dyn_layer *L, const dyn_batch *b, const dyn_schedule *s, con
             if (!used[key]) HIP_TRY(hipStreamWaitEvent(st, L->fork_event, 0));
         }
         used[key] = true;
-        st_of[i] = st;
-        // one wait per producer stream: a stream's events complete in order, the latest covers the rest
-        for (int dep : real_deps[i]) {
-            if (st_of[dep] == st) continue;
-            bool latest = true;
-            for (int other : real_deps[i]) latest = latest && !(st_of[other] == st_of[dep] && other > dep);
-            if (latest) HIP_TRY(hipStreamWaitEvent(st, L->events[dep], 0));
-        }
+        for (int dep : waits[i]) HIP_TRY(hipStreamWaitEvent(st, L->events[dep], 0));
         if (profile) {
             // the two middle events stay here unless the operator records them around its main kernel
             for (int j = 1; j <= 3; ++j) HIP_TRY(hipEventRecord(L->prof_events[j + 4 * i], st));
@@ -819,8 +839,7 @@ dyn_status run_plan(dyn_layer *L, const dyn_batch *b, const dyn_schedule *s, con
                                   mark ? L->prof_events[2 + 4 * i] : nullptr);
         if (rc != DYN_OK) return rc;
         if (profile) HIP_TRY(hipEventRecord(L->prof_events[4 + 4 * i], st));
-        HIP_TRY(hipEventRecord(L->events[i], st));
-        last_on[key] = (int)i;
+        if (record[i]) HIP_TRY(hipEventRecord(L->events[i], st));
     }
     for (int key = 1; key < (DYN_MAX_PARTITIONS + 1) * DYN_MAX_STREAMS; ++key)
         if (last_on[key] >= 0) HIP_TRY(hipStreamWaitEvent(origin, L->events[last_on[key]], 0));
