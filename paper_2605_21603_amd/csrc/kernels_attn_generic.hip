@@ -1,17 +1,258 @@
-// Paged causal attention, generic path (fp32 storage, or any shape the MFMA kernel does not
-// take), and the split-KV combine step shared by both attention kernels.
+// Paged causal attention for what the bf16, 128-wide, 16-position-page kernels do not take (fp32
+// storage, other head dims and page sizes), and the split-KV combine step shared by all attention
+// kernels.
 //
 // A token attends cached positions 0..pos of its sequence.  The key range is cut into
-// chunks of a fixed number of pages; one wave handles one (token, q head, chunk) and writes
-// an un-normalised partial (running max m, sum l, weighted values o).  The combine kernel
-// merges a token's partials in chunk order.  Chunk size is a constant of the layer, so the
-// arithmetic a row sees does not depend on the batch around it.
+// chunks of a fixed number of pages; a chunk gives an un-normalised partial (running max m, sum l,
+// weighted values o) per (token, q head).  The combine kernel merges a token's partials in chunk
+// order.  Chunk size is a constant of the layer, so the arithmetic a row sees does not depend on
+// the batch around it.
+//
+// attn_tile_kernel is the matrix-core form, for head dims 32..256 and pages of a multiple of 16
+// positions; attn_generic_kernel (one wave per (token, q head, chunk), plain loops) takes the rest.
 #include "common.h"
 #include "kernels.h"
 
 namespace dyn {
 
 constexpr int kMaxChunkTokens = 512;
+
+// A 256-thread workgroup serves one (query group, kv head, chunk): the tokens of one sequence whose
+// positions share an aligned block of 4 * (16 / G) (G = q heads per kv head), all q heads of the kv
+// head at once, so a key is fetched once per group instead of once per (token, q head).  The products are
+//   S[16 pos, 16 cols]  = K_tile Q^T    (fp32 storage: 16x16x4 fp32 MFMA; bf16: 16x16x32 bf16 MFMA)
+//   O^T[d, 16 cols]    += V_tile^T P    (16x16x4 fp32 MFMA, bf16 values widened)
+// with a column per (token, q head).  Scores, probabilities and sums stay in fp32 throughout: the
+// probabilities are operands of an fp32 product, which at 256 flop per clock and CU is still several
+// times what the cache pages arrive at.  The D layout of the first product (lane: column l % 16,
+// positions 4 (l / 16) + r) is the B layout of the second if its r-th product takes position 4 (l / 16) + r
+// as its k index l / 16, and a lane's V operand is then four consecutive positions of one head-dim row.
+// A group of one token (decode) gives each of the four waves a quarter of the chunk's positions and
+// merges the four in wave order through LDS; a group of several tokens gives each wave its own set of
+// 16 columns, and the waves walk the same positions (K and V come from the vector cache).  Which
+// of the two a token is part of depends on its sequence only, never on the schedule.
+// What bounds it: HBM latency with two tiles of 16 * TP positions in flight per wave.  Measured against
+// the one-wave-per-(token, q head, chunk) form below, launch alone: fp32, 64-wide heads, 4 tokens behind
+// 128 positions 27.7 -> 9.0 us, a 201-token prompt + 24 decodes 242 -> 34 us; bf16, 64-wide heads, 300-token prompt
+// + 40 decodes at 64..2048 1680 -> 89 us; bf16, 128-wide, 32-position pages, 13 decodes at 200..3000 301 -> 36 us.
+template <typename T, int HD, int TP>
+__global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_kernel(const T *__restrict__ qkv, const int32_t *__restrict__ seq_of_token,
+                                                        const int32_t *__restrict__ pos_of_token,
+                                                        const int32_t *__restrict__ block_table, const T *__restrict__ k_cache,
+                                                        const T *__restrict__ v_cache, T *__restrict__ out, int ld_out,
+                                                        float *__restrict__ part_o, float *__restrict__ part_ml, AttnShape sh,
+                                                        int rows) {
+    constexpr bool F32 = sizeof(T) == 4;
+    constexpr int NK = F32 ? HD / 16 : HD / 32, ND = HD / 16;      // 16-byte K operands and 16-row V operands of a lane
+    constexpr int MD = HD < 128 ? HD : 128;                        // head-dim indices merged per round
+    typedef typename std::conditional<F32, f32x4, u32x2>::type vload_t;   // four positions of V
+    __shared__ float merge_o[4][16][MD + 4];
+    __shared__ float merge_ml[4][16][2];
+    const int c = blockIdx.x % sh.max_chunks, g = (blockIdx.x / sh.max_chunks) % sh.n_kv, t = blockIdx.x / (sh.max_chunks * sh.n_kv);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15, lq = lane >> 4;
+    const int G = sh.n_q / sh.n_kv, TG = 16 / G, tg = 4 * TG;
+    const int s = seq_of_token[t], p0 = pos_of_token[t];
+    if (t > 0 && seq_of_token[t - 1] == s && pos_of_token[t - 1] / tg == p0 / tg) return;      // not the first token of its group
+    const bool in_group = lane < tg && t + lane < rows && seq_of_token[min(t + lane, rows - 1)] == s &&
+                          pos_of_token[min(t + lane, rows - 1)] / tg == p0 / tg;
+    const int n_tok = __popcll(__ballot(in_group));
+    const int n_keys = pos_of_token[t + n_tok - 1] + 1;            // keys the group's last token attends
+    const int ps = sh.page_size, ct = sh.chunk_pages * ps, j0 = c * ct;
+    if (j0 >= n_keys) return;
+    const int j1 = min(j0 + ct, n_keys);
+    const bool single = n_tok == 1;
+    const int32_t *bt = block_table + (size_t)s * sh.max_pages_per_seq;
+
+    // this lane's column: B operands of the score product, and the end of the keys it attends in this chunk
+    const int col_tok = lr / G, col_head = lr % G;
+    const int ti = single ? col_tok : wave * TG + col_tok;
+    const bool live = col_tok < TG && ti < n_tok;
+    const int tq = t + (live ? ti : 0);
+    const int col_keys = live ? pos_of_token[tq] + 1 : 0, nk = min(col_keys, j1);
+    u32x4 qf[NK];
+    const T *qp = qkv + (size_t)tq * ((sh.n_q + 2 * sh.n_kv) * HD) + (size_t)(g * G + (live ? col_head : 0)) * HD;
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+        qf[k] = *reinterpret_cast<const u32x4 *>(qp + (F32 ? k * 16 + 4 * lq : k * 32 + 8 * lq));
+        if (!live) qf[k] = u32x4{0u, 0u, 0u, 0u};
+    }
+    const float scale = 1.0f / sqrtf((float)HD);
+
+    // positions this wave walks: [w0, w1), in tiles of 16 * TP from w0 (a multiple of 16)
+    int w0 = j0, w1 = j1;
+    if (single) {
+        const int n_tile = (j1 - j0 + 16 * TP - 1) / (16 * TP), per = (n_tile + 3) / 4;
+        w0 = j0 + min(wave * per, n_tile) * 16 * TP;
+        w1 = min(j1, w0 + per * 16 * TP);
+    } else {
+        const int last = min((wave + 1) * TG, n_tok) - 1;          // the wave's last live token
+        w1 = wave * TG < n_tok ? min(j1, pos_of_token[t + last] + 1) : j0;
+    }
+    // the first key any live column of the wave must not see (single: none before w1)
+    const int free_keys = single ? w1 : (wave * TG < n_tok ? pos_of_token[t + wave * TG] + 1 : 0);
+
+    constexpr int NBUF = HD * sizeof(T) > 512 ? 1 : 2;             // register buffers: fp32 256-wide operands fit once
+    u32x4 kr[NBUF][TP][NK];
+    vload_t vr[NBUF][TP][ND];
+    auto load = [&](auto buf, int j) {                             // tile at position j; sub-tiles past the end reload the last one
+        constexpr int B = decltype(buf)::value;
+#pragma unroll
+        for (int i = 0; i < TP; ++i) {
+            const int jj = min(j + 16 * i, (w1 - 1) & ~15), lp = jj / ps, slot = jj - lp * ps;
+            const size_t pg = (size_t)bt[lp] * sh.n_kv + g;
+            const T *kp = k_cache + (pg * ps + slot + lr) * HD + (F32 ? 4 : 8) * lq;
+            const T *vp = v_cache + (pg * HD + lr) * ps + slot + 4 * lq;
+#pragma unroll
+            for (int k = 0; k < NK; ++k) kr[B][i][k] = *reinterpret_cast<const u32x4 *>(kp + k * (F32 ? 16 : 32));
+#pragma unroll
+            for (int dt = 0; dt < ND; ++dt) vr[B][i][dt] = *reinterpret_cast<const vload_t *>(vp + (size_t)dt * 16 * ps);
+        }
+    };
+    f32x4 acc[ND];
+#pragma unroll
+    for (int dt = 0; dt < ND; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m_run = -INFINITY, l_run = 0.f;
+    auto multiply = [&](auto buf, int j) {
+        constexpr int B = decltype(buf)::value;
+        f32x4 sv[TP];
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < TP; ++i) {
+            f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int k = 0; k < NK; ++k) {
+                if constexpr (F32) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        a = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kr[B][i][k][e]), __uint_as_float(qf[k][e]), a, 0, 0, 0);
+                } else {
+                    a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[B][i][k]), __builtin_bit_cast(bf16x8, qf[k]), a, 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                a[r] = j + 16 * i + 4 * lq + r < nk && j + 16 * i + 4 * lq + r < w1 ? a[r] * scale : -INFINITY;
+                mx = fmaxf(mx, a[r]);
+            }
+            sv[i] = a;
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float m_new = fmaxf(m_run, mx), m_ref = m_new == -INFINITY ? 0.f : m_new;   // a column with no key yet stays empty
+        const float alpha = expf(m_run - m_ref);
+        m_run = m_new;
+        l_run *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < ND; ++dt) acc[dt] *= alpha;
+        // Positions past the wave's last key hold stale cache bits, which must not meet their zero
+        // probabilities (0 * NaN).  A later token of the group may hold infinities or NaN of its own:
+        // where columns differ in what they see, such a tile is added position by position below.
+        const bool diagonal = j + 16 * TP > free_keys;
+#pragma unroll
+        for (int i = 0; i < TP; ++i) {
+            f32x4 p, vf[ND];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) p[r] = expf(sv[i][r] - m_ref);
+            l_run += (p[0] + p[1]) + (p[2] + p[3]);
+            const int nvalid = w1 - (j + 16 * i + 4 * lq);
+            bool odd = false;
+#pragma unroll
+            for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float v;
+                    if constexpr (F32) v = vr[B][i][dt][r];
+                    else v = __uint_as_float(r & 1 ? vr[B][i][dt][r >> 1] & 0xffff0000u : vr[B][i][dt][r >> 1] << 16);
+                    vf[dt][r] = r < nvalid ? v : 0.f;
+                    if (diagonal) odd |= !(fabsf(vf[dt][r]) < INFINITY);
+                }
+            if (__any(odd)) {
+#pragma unroll
+                for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        for (int q = 0; q < 4; ++q) {
+                            const f32x4 one = __builtin_amdgcn_mfma_f32_16x16x4f32(lq == q ? vf[dt][r] : 0.f, p[r], acc[dt], 0, 0, 0);
+                            if (j + 16 * i + 4 * q + r < nk) acc[dt] = one;
+                        }
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int dt = 0; dt < ND; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[dt][r], p[r], acc[dt], 0, 0, 0);
+            }
+        }
+    };
+    const std::integral_constant<int, 0> b0;
+    const std::integral_constant<int, NBUF - 1> b1;
+    if constexpr (NBUF == 1) {
+        for (int j = w0; j < w1; j += 16 * TP) {
+            load(b0, j);
+            multiply(b0, j);
+        }
+    } else if (w0 < w1) {
+        load(b0, w0);
+        for (int j = w0; j < w1; j += 32 * TP) {
+            load(b1, j + 16 * TP);                                 // past the end: the last tile again, all masked
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(b0, j);
+            __builtin_amdgcn_sched_barrier(0);
+            load(b0, j + 32 * TP);
+            __builtin_amdgcn_sched_barrier(0);
+            if (j + 16 * TP < w1) multiply(b1, j + 16 * TP);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    l_run += __shfl_xor(l_run, 16, 64);
+    l_run += __shfl_xor(l_run, 32, 64);
+
+    // a token whose keys fit one chunk is finished here (attn_combine_kernel leaves it alone)
+    if (single) {
+        const size_t pidx = ((size_t)t * sh.n_q + g * G) * sh.max_chunks + c;
+        const bool whole = n_keys <= ct;
+        if (lq == 0) { merge_ml[wave][lr][0] = m_run; merge_ml[wave][lr][1] = l_run; }
+        __syncthreads();
+        const float M = fmaxf(fmaxf(merge_ml[0][lr][0], merge_ml[1][lr][0]), fmaxf(merge_ml[2][lr][0], merge_ml[3][lr][0]));
+        const float mine = expf(m_run - (M == -INFINITY ? 0.f : M));
+        for (int round = 0; round < HD / MD; ++round) {
+            if (round) __syncthreads();
+#pragma unroll
+            for (int dt = 0; dt < ND; ++dt)
+                if (dt / (MD / 16) == round) *reinterpret_cast<f32x4 *>(&merge_o[wave][lr][(dt % (MD / 16)) * 16 + 4 * lq]) = acc[dt] * mine;
+            __syncthreads();
+            for (int u = threadIdx.x; u < G * MD; u += 256) {
+                const int h = u / MD, i = u % MD;
+                float Mh = -INFINITY, L = 0.f;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) Mh = fmaxf(Mh, merge_ml[w][h][0]);
+#pragma unroll
+                for (int w = 0; w < 4; ++w) L += expf(merge_ml[w][h][0] - (Mh == -INFINITY ? 0.f : Mh)) * merge_ml[w][h][1];
+                const float o = ((merge_o[0][h][i] + merge_o[1][h][i]) + merge_o[2][h][i]) + merge_o[3][h][i];
+                const int d = round * MD + i;
+                if (whole) {
+                    out[(size_t)t * ld_out + (g * G + h) * HD + d] = from_f32<T>(o * (1.0f / L));
+                } else {
+                    part_o[(pidx + (size_t)h * sh.max_chunks) * HD + d] = o;
+                    if (d == 0) { part_ml[(pidx + (size_t)h * sh.max_chunks) * 2] = Mh; part_ml[(pidx + (size_t)h * sh.max_chunks) * 2 + 1] = L; }
+                }
+            }
+        }
+    } else if (live && col_keys > j0) {                            // the chunk exists for this column's token
+        const size_t pidx = ((size_t)tq * sh.n_q + g * G + col_head) * sh.max_chunks + c;
+        if (col_keys <= ct) {
+            const float inv = 1.0f / l_run;
+            T *o = out + (size_t)tq * ld_out + (g * G + col_head) * HD + 4 * lq;
+#pragma unroll
+            for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[dt * 16 + r] = from_f32<T>(acc[dt][r] * inv);
+        } else {
+#pragma unroll
+            for (int dt = 0; dt < ND; ++dt) *reinterpret_cast<f32x4 *>(part_o + pidx * HD + dt * 16 + 4 * lq) = acc[dt];
+            if (lq == 0) { part_ml[pidx * 2] = m_run; part_ml[pidx * 2 + 1] = l_run; }
+        }
+    }
+}
 
 template <typename T>
 __global__ __launch_bounds__(64) void attn_generic_kernel(const T *__restrict__ qkv,
@@ -155,7 +396,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
                                                            const int32_t *__restrict__ pos_of_token,
                                                            const int32_t *__restrict__ ct_of_token,
                                                            T *__restrict__ out, int ld_out, AttnShape sh, int n_pairs,
-                                                           int32_t *__restrict__ counter_reset) {
+                                                           int32_t *__restrict__ counter_reset, bool one_chunk_done) {
     // the query-block kernel that ran before this one has drained its work counter: zero it for the
     // next launch that walks the same work list (the next layer of the forward)
     if (counter_reset && blockIdx.x == 0 && threadIdx.x == 0) *counter_reset = 0;
@@ -164,6 +405,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
     const int t = pair / sh.n_q;
     const int d = sh.head_dim, ct = ct_of_token ? ct_of_token[t] : sh.chunk_pages * sh.page_size;   // per-token chunk size if given
     const int all_chunks = (pos_of_token[t] + ct) / ct;     // ceil((pos + 1) / ct)
+    if (one_chunk_done && all_chunks == 1) return;          // the attention kernel wrote this token's output itself
     // beyond kMergeSegment chunks the segments kernel has merged every segment into its first chunk
     const int step = all_chunks > kMergeSegment ? kMergeSegment : 1;
     const int n_chunks = (all_chunks + step - 1) / step;
@@ -226,9 +468,10 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
     }
 }
 
-hipError_t launch_attention_combine(int dtype, bool base2, float *part_o, float *part_ml,
-                                    const int32_t *pos_of_token, const int32_t *ct_of_token, void *out, int ld_out,
-                                    const AttnShape &sh, int rows, hipStream_t s, int32_t *counter_reset) {
+static hipError_t launch_combine(int dtype, bool base2, float *part_o, float *part_ml, const int32_t *pos_of_token,
+                                 const int32_t *ct_of_token, void *out, int ld_out, const AttnShape &sh, int rows, hipStream_t s,
+                                 int32_t *counter_reset, bool one_chunk_done) {
+    if (one_chunk_done && sh.max_chunks == 1) return hipSuccess;       // no token has anything to merge
     const int n_pairs = rows * sh.n_q;
     const dim3 grid((n_pairs + 7) / 8), block(256);
     if (sh.max_chunks > kMergeSegment) {       // some token may have that many chunks: first level of the merge
@@ -240,31 +483,79 @@ hipError_t launch_attention_combine(int dtype, bool base2, float *part_o, float 
         if (e != hipSuccess) return e;
     }
     if (dtype == 0) {
-        if (base2) hipLaunchKernelGGL((attn_combine_kernel<float, true>), grid, block, 0, s, part_o, part_ml, pos_of_token, ct_of_token, (float *)out, ld_out, sh, n_pairs, counter_reset);
-        else hipLaunchKernelGGL((attn_combine_kernel<float, false>), grid, block, 0, s, part_o, part_ml, pos_of_token, ct_of_token, (float *)out, ld_out, sh, n_pairs, counter_reset);
+        if (base2) hipLaunchKernelGGL((attn_combine_kernel<float, true>), grid, block, 0, s, part_o, part_ml, pos_of_token, ct_of_token, (float *)out, ld_out, sh, n_pairs, counter_reset, one_chunk_done);
+        else hipLaunchKernelGGL((attn_combine_kernel<float, false>), grid, block, 0, s, part_o, part_ml, pos_of_token, ct_of_token, (float *)out, ld_out, sh, n_pairs, counter_reset, one_chunk_done);
     } else {
-        if (base2) hipLaunchKernelGGL((attn_combine_kernel<bf16_t, true>), grid, block, 0, s, part_o, part_ml, pos_of_token, ct_of_token, (bf16_t *)out, ld_out, sh, n_pairs, counter_reset);
-        else hipLaunchKernelGGL((attn_combine_kernel<bf16_t, false>), grid, block, 0, s, part_o, part_ml, pos_of_token, ct_of_token, (bf16_t *)out, ld_out, sh, n_pairs, counter_reset);
+        if (base2) hipLaunchKernelGGL((attn_combine_kernel<bf16_t, true>), grid, block, 0, s, part_o, part_ml, pos_of_token, ct_of_token, (bf16_t *)out, ld_out, sh, n_pairs, counter_reset, one_chunk_done);
+        else hipLaunchKernelGGL((attn_combine_kernel<bf16_t, false>), grid, block, 0, s, part_o, part_ml, pos_of_token, ct_of_token, (bf16_t *)out, ld_out, sh, n_pairs, counter_reset, one_chunk_done);
     }
     return hipGetLastError();
 }
+
+hipError_t launch_attention_combine(int dtype, bool base2, float *part_o, float *part_ml,
+                                    const int32_t *pos_of_token, const int32_t *ct_of_token, void *out, int ld_out,
+                                    const AttnShape &sh, int rows, hipStream_t s, int32_t *counter_reset) {
+    return launch_combine(dtype, base2, part_o, part_ml, pos_of_token, ct_of_token, out, ld_out, sh, rows, s, counter_reset, false);
+}
+
+namespace {
+// The matrix-core form reads K and q 16 bytes and V four positions at a time.
+bool attn_tile_supported(int dtype, const AttnShape &sh, const void *k_cache, const void *v_cache) {
+    (void)dtype;
+    const int d = sh.head_dim;
+    return (d == 32 || d == 64 || d == 128 || d == 256) && sh.page_size % 16 == 0 && sh.n_q / sh.n_kv <= 16 &&
+           (((uintptr_t)k_cache | (uintptr_t)v_cache) & 15) == 0;
+}
+
+template <typename T, int HD, int TP>
+void launch_attn_tile(dim3 grid, hipStream_t s, const void *qkv, const int32_t *seq_of_token, const int32_t *pos_of_token,
+                      const int32_t *block_table, const void *k_cache, const void *v_cache, void *out, int ld_out, float *part_o,
+                      float *part_ml, const AttnShape &sh, int rows) {
+    hipLaunchKernelGGL((attn_tile_kernel<T, HD, TP>), grid, dim3(256), 0, s, (const T *)qkv, seq_of_token, pos_of_token, block_table,
+                       (const T *)k_cache, (const T *)v_cache, (T *)out, ld_out, part_o, part_ml, sh, rows);
+}
+}  // namespace
 
 hipError_t launch_attention_generic(int dtype, const void *qkv, const int32_t *seq_of_token,
                                     const int32_t *pos_of_token, const int32_t *block_table, const void *k_cache,
                                     const void *v_cache, void *out, int ld_out, float *part_o, float *part_ml,
                                     const AttnShape &sh, int rows, hipStream_t s, hipEvent_t mid) {
     if (rows <= 0) return hipSuccess;
-    const dim3 grid((unsigned)((size_t)rows * sh.n_q * sh.max_chunks));
-    if (dtype == 0)
-        hipLaunchKernelGGL(attn_generic_kernel<float>, grid, dim3(64), 0, s, (const float *)qkv, seq_of_token,
-                           pos_of_token, block_table, (const float *)k_cache, (const float *)v_cache, part_o, part_ml, sh);
-    else
-        hipLaunchKernelGGL(attn_generic_kernel<bf16_t>, grid, dim3(64), 0, s, (const bf16_t *)qkv, seq_of_token,
-                           pos_of_token, block_table, (const bf16_t *)k_cache, (const bf16_t *)v_cache, part_o, part_ml, sh);
+    const bool tile = attn_tile_supported(dtype, sh, k_cache, v_cache);
+    if (tile) {
+        const dim3 grid((unsigned)((size_t)rows * sh.n_kv * sh.max_chunks));
+        // positions per tile: two sub-tiles of 16 where a lane's K and V operands of both fit beside the
+        // accumulators twice over, else one
+#define DYN_TILE(T, HD, TP) launch_attn_tile<T, HD, TP>(grid, s, qkv, seq_of_token, pos_of_token, block_table, k_cache, v_cache, out, ld_out, part_o, part_ml, sh, rows)
+        if (dtype == 0) {
+            switch (sh.head_dim) {
+                case 32: DYN_TILE(float, 32, 2); break;
+                case 64: DYN_TILE(float, 64, 2); break;
+                case 128: DYN_TILE(float, 128, 1); break;
+                default: DYN_TILE(float, 256, 1); break;
+            }
+        } else {
+            switch (sh.head_dim) {
+                case 32: DYN_TILE(bf16_t, 32, 2); break;
+                case 64: DYN_TILE(bf16_t, 64, 2); break;
+                case 128: DYN_TILE(bf16_t, 128, 1); break;
+                default: DYN_TILE(bf16_t, 256, 1); break;
+            }
+        }
+#undef DYN_TILE
+    } else {
+        const dim3 grid((unsigned)((size_t)rows * sh.n_q * sh.max_chunks));
+        if (dtype == 0)
+            hipLaunchKernelGGL(attn_generic_kernel<float>, grid, dim3(64), 0, s, (const float *)qkv, seq_of_token,
+                               pos_of_token, block_table, (const float *)k_cache, (const float *)v_cache, part_o, part_ml, sh);
+        else
+            hipLaunchKernelGGL(attn_generic_kernel<bf16_t>, grid, dim3(64), 0, s, (const bf16_t *)qkv, seq_of_token,
+                               pos_of_token, block_table, (const bf16_t *)k_cache, (const bf16_t *)v_cache, part_o, part_ml, sh);
+    }
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && mid) e = hipEventRecord(mid, s);
     if (e != hipSuccess) return e;
-    return launch_attention_combine(dtype, false, part_o, part_ml, pos_of_token, nullptr, out, ld_out, sh, rows, s, nullptr);
+    return launch_combine(dtype, false, part_o, part_ml, pos_of_token, nullptr, out, ld_out, sh, rows, s, nullptr, tile);
 }
 
 }  // namespace dyn

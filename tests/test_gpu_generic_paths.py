@@ -1,0 +1,112 @@
+"""GPU tests of the kernels outside the 128-wide, 16-position-page bf16 layer: the fp32 projections
+(tiles of 16, 32 and 64 rows, K slices of unequal length, widths that fill no tile) and the
+matrix-core attention for other head dims, page sizes and fp32 storage, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import GpuRun, check_against_oracle, say
+from paper_2605_21603_amd import binding as B
+from workloads import gen
+
+pytestmark = pytest.mark.gpu
+
+
+def workload(name, dtype, hidden, n_q, n_kv, hd, inter, seqs, page=16, experts=0, top_k=0, seed=40):
+    sh = gen.LayerShape(dtype, hidden, n_q, n_kv, hd, inter, n_experts=experts, top_k=top_k, page_size=page)
+    cut = seqs[0][0]
+    T = sum(q for q, _ in seqs)
+    return gen.Workload(name, sh, tuple(seqs), seed, (0, cut, T) if len(seqs) > 1 else (0, T))
+
+
+def both_schedules(w, data):
+    run = GpuRun(w, data)
+    y, k, v = run.run(B.sequential())
+    if len(w.nano_rows) > 2:
+        y1, _, _ = run.run(B.nano_schedule(w.nano_rows, chain=B.MOE_CHAIN if w.shape.n_experts else B.DENSE_CHAIN))
+        assert torch.equal(y.view(torch.uint8), y1.view(torch.uint8)), "the split schedule changed bits"
+    return y, k, v
+
+
+# rows at the edges of the 16-, 32- and 64-row tiles; hidden, inter and head widths that leave ragged K slices and column tiles
+@pytest.mark.parametrize("rows,hidden,n_q,n_kv,hd,inter", [
+    (1, 256, 4, 4, 64, 1024), (16, 68, 2, 1, 32, 100), (17, 132, 3, 1, 8, 52), (33, 36, 1, 1, 64, 260), (64, 256, 4, 2, 64, 4096),
+    (65, 260, 4, 2, 64, 8200), (130, 1024, 8, 8, 64, 5124)])
+def test_fp32_projections_at_tile_edges(rows, hidden, n_q, n_kv, hd, inter):
+    seqs = [(1, 1 + (7 * i) % 40) for i in range(rows)]
+    w = workload("f32_%d" % rows, "f32", hidden, n_q, n_kv, hd, inter, seqs)
+    data = gen.generate(w)
+    y, k, v = both_schedules(w, data)
+    # 1e-4 is the layer's fp32 bound; eight shorter chains per output stay well inside one long chain's error
+    err = check_against_oracle(w, data, y, k, v)
+    say("rows %d: %.2e" % (rows, err))
+    assert err < 2e-6
+
+
+def test_fp32_experts_with_empty_and_long_lists():
+    w = workload("f32_moe", "f32", 136, 2, 1, 32, 68, [(1, 3 + i % 9) for i in range(70)], experts=5, top_k=2)
+    data = gen.generate(w)
+    data["weights"][0]["w_router"][3] = -4.0 * data["weights"][0]["w_router"][0]
+    y, k, v = both_schedules(w, data)
+    check_against_oracle(w, data, y, k, v)
+
+
+MIX = [(23, 23), (1, 70), (1, 256), (1, 257), (40, 300), (2, 513), (1, 1)]     # chunk edges, groups that straddle aligned blocks
+
+
+@pytest.mark.parametrize("dtype,n_q,n_kv,hd,page", [
+    ("f32", 4, 4, 64, 16), ("f32", 4, 2, 32, 48), ("f32", 8, 1, 128, 16), ("f32", 2, 1, 256, 32), ("f32", 6, 2, 64, 64),
+    ("bf16", 8, 2, 64, 16), ("bf16", 4, 4, 32, 16), ("bf16", 4, 2, 128, 32), ("bf16", 16, 1, 64, 128), ("bf16", 6, 2, 64, 16),
+    ("bf16", 2, 1, 256, 64), ("bf16", 4, 1, 128, 256)])
+def test_tile_attention_head_dims_pages_and_groups(dtype, n_q, n_kv, hd, page):
+    w = workload("tile", dtype, 128, n_q, n_kv, hd, 128, MIX, page=page)
+    data = gen.generate(w)
+    md = gen.metadata(w)
+    # what a cache page holds past its sequence's last position must not be read as a value
+    for s, (_, ctx) in enumerate(w.seqs):
+        pg = int(md["block_table"][s, (ctx - 1) // page])
+        data["v_cache"][0][pg, :, :, (ctx - 1) % page + 1:] = float("nan")
+        data["k_cache"][0][pg, :, (ctx - 1) % page + 1:] = float("nan")
+    clean = dict(data, k_cache=[torch.nan_to_num(data["k_cache"][0])], v_cache=[torch.nan_to_num(data["v_cache"][0])])
+    run = GpuRun(w, data)
+    y, k, v = run.run(B.sequential())
+    y1, _, _ = run.run(B.nano_schedule(w.nano_rows))
+    assert torch.equal(y.view(torch.uint8), y1.view(torch.uint8)), "the split schedule changed bits"
+    err = check_against_oracle(w, clean, y, torch.nan_to_num(k), torch.nan_to_num(v))
+    say("%s %d/%d x %d, page %d: %.2e" % (dtype, n_q, n_kv, hd, page, err))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_a_later_tokens_nan_stays_out_of_the_earlier_tokens(dtype):
+    """Token 21 of a 40-token prompt is NaN: its key and value are NaN, tokens 0..20 must come out as without it."""
+    w = workload("nan", dtype, 128, 4, 2, 64, 128, [(40, 40), (1, 30)])
+    data = gen.generate(w)
+    y0, _, _ = GpuRun(w, data).run(B.sequential())
+    bad = dict(data, x=data["x"].clone())
+    bad["x"][21] = float("nan")
+    y1, _, _ = GpuRun(w, bad).run(B.sequential())
+    keep = list(range(21)) + [40]
+    assert torch.isfinite(y1[keep].float()).all()
+    assert torch.equal(y0[keep].view(torch.uint8), y1[keep].view(torch.uint8))
+    assert torch.isnan(y1[21:40].float()).all()
+
+
+def test_unaligned_caches_take_the_plain_loops_and_agree():
+    w = workload("unaligned", "f32", 128, 4, 2, 64, 128, MIX)
+    data = gen.generate(w)
+    run = GpuRun(w, data)
+    y0, _, _ = run.run(B.sequential())
+    step = B.DeviceStep(run.layer, data)
+    pools = []
+    for c in (step.k_cache, step.v_cache):
+        flat = torch.empty(c.numel() + 8, dtype=c.dtype, device=c.device)
+        flat[1:1 + c.numel()] = c.reshape(-1)
+        pools.append(flat)
+    step.batch.k_cache = pools[0].data_ptr() + 4
+    step.batch.v_cache = pools[1].data_ptr() + 4
+    st = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    run.layer.forward(step.batch, B.sequential(), st)
+    torch.cuda.synchronize()
+    got, ref = step.y.cpu().double().numpy(), y0.double().numpy()
+    assert np.abs(got - ref).max() / np.abs(ref).max() < 1e-5        # two fp32 attention orders
