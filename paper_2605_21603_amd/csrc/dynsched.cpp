@@ -112,8 +112,8 @@ OpCost estimate(const dyn_scheduler *s, const int32_t *ctx_len, int r0, int r1) 
                 case dyn::GEMM_WIDE:
                     compute = rounds * (3e-6 + wg_flops / (R.mfma_wide / 256));
                     break;
-                case dyn::GEMM_MANY:    // two workgroups share a CU
-                    compute = rounds * 2.0 * wg_flops / (R.mfma / 256);
+                case dyn::GEMM_MANY:    // one or two workgroups share a CU
+                    compute = rounds * (p.resident / 256) * wg_flops / (R.mfma / 256);
                     break;
                 default:
                     compute = 2.0 * std::ceil(T / 128) * 128 * n * k / R.mfma;

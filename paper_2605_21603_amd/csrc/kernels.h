@@ -43,7 +43,7 @@ bool gemm_supported(int dtype, int N, int K);
 enum { GEMM_FEW = 0, GEMM_TALL = 1, GEMM_WIDE = 2, GEMM_MANY = 3 };
 struct GemmPath {
     int kind;          // GEMM_FEW: 128 x 64|128 tiles, ring of 4; GEMM_TALL: 128 x 256|384|512, eight waves;
-                       // GEMM_WIDE: 256 x 256, eight waves; GEMM_MANY: 128 x 128|160, two workgroups per CU
+                       // GEMM_WIDE: 256 x 256, eight waves; GEMM_MANY: 128 x 128|160, two workgroups per CU, or 256 x 128, one
     int bn, mt;        // tile: W rows x X rows
     int split;         // split-K factor S(N, K)
     bool folded;       // planes accumulated one after another in registers: no plane buffer, no reduce kernel
@@ -87,6 +87,9 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
                        size_t plane_stride, int rows, int N, int K, hipStream_t s, hipEvent_t mid = nullptr,
                        const GemmEpilogue *ep = nullptr);
 
+// Many rows, split-K planes folded in registers, 256 x 128 tiles (kernels_gemm_wide.hip; launch_gemm calls it).
+hipError_t launch_gemm_fold(int grid, hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N,
+                            int K, int S, int band);
 hipError_t launch_gemm_grouped(int dtype, const void *X, int ldx, const void *W, void *Y, float *partial,
                                size_t plane_stride, const GemmGroups &gr, int max_rows, int row0, int n_rows, int N, int K,
                                hipStream_t s, hipEvent_t mid = nullptr);

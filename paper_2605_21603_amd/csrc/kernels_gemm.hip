@@ -12,8 +12,7 @@
 
 #include <algorithm>
 #include <utility>
-#include "common.h"
-#include "kernels.h"
+#include "gemm_tile.h"
 
 namespace dyn {
 
@@ -141,68 +140,27 @@ static hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const v
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ bf16 MFMA path
-// Workgroup = NW waves (4 or 8) on a BN (W rows) x MT (X rows) output tile and one K plane (or,
-// INREG, all planes in turn).  What bounds this kernel below a few hundred rows is not the matrix
-// cores and not even HBM alone but the L2 -> CU path: every byte of W must cross it once and
-// the X tile crosses it once per W tile, so both operands are fetched exactly once per
-// workgroup, with fully coalesced 128-byte row segments (8 lanes per row), by direct
-// global -> LDS loads (no registers in between) into a ring of NS stage buffers (a stage is
-// 64 k); NS - 1 stages are in flight while one is multiplied, tracked with exact vmcnt waits
-// and one barrier per stage.  A direct load places lane l's 16 bytes at l * 16 of the wave's
-// 1 KB window, so rows sit at a 128-byte pitch; bank conflicts of the MFMA-layout reads
-// (lane l: row l%16, 8 consecutive k at 8*(l/16)) are avoided by an XOR swizzle of the
-// 16-byte column with bits 1..3 of the row, applied to the global column a lane fetches.
-// Waves sit 2 (along X rows; 4 on the tall tiles) x NW/2 (along W rows) on the tile.
-// D[i][j]: i = W row (4*(l/16)+r), j = X row (l%16).  Which tile a launch uses is gemm_path's
-// decision: 128 x 64|128 with a ring of 4 for few rows, 128 x 256|384|512 for 129..512 rows,
-// 256 x 256 for many rows without planes, 128 x 128|160 with two workgroups per CU otherwise.
-//
-// INREG: one workgroup walks all S planes of its tile and adds the plane sums in registers
-// (same order, same bits as the plane buffers + gemm_reduce_kernel) - for many-row launches,
-// where there are enough tiles to fill the chip without spreading planes over workgroups and
-// the fp32 plane traffic would cost more than the weights.
-constexpr int BK = 64, ROWB = BK * 2;
-constexpr int kRotGroup = 32, kRotStep = 9;   // stage-order rotation of the bf16 kernel
+// ------------------------------------------------------------------ bf16 MFMA path (gemm_tile.h)
 constexpr int kBigBN = 128, kBigMT = 128, kBigNS = 2;   // tile and ring depth of the many-row (matrix-core-bound) regime
-
-__device__ __forceinline__ void wait_vmcnt(int n) {          // s_waitcnt vmcnt(n) only; n folds to a literal <= 63
-    // simm16: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] << 14; expcnt 7 and lgkmcnt 15 = no wait
-#define DYN_W(N) case N: __builtin_amdgcn_s_waitcnt(0x0f70 | ((N) & 15) | (((N) >> 4) << 14)); break;
-    switch (n) {
-        DYN_W(0) DYN_W(2) DYN_W(3) DYN_W(4) DYN_W(5) DYN_W(6) DYN_W(7) DYN_W(8) DYN_W(9) DYN_W(12) DYN_W(14) DYN_W(16) DYN_W(18) DYN_W(21) DYN_W(24) DYN_W(27) DYN_W(28) DYN_W(32)
-        default: __builtin_amdgcn_s_waitcnt(0x0f70); break;       // unknown count: wait for everything
-    }
-#undef DYN_W
-}
-
-// The MFMA as inline assembly, so that the many-row loop's instruction order is the one written down.
-// The compiler neither sees the instruction's latency nor orders anything around it: the caller keeps
-// dependent uses of an accumulator far apart and waits before reading it as an ordinary register.
-__device__ __forceinline__ void mfma_acc(f32x4 &c, const bf16x8 &a, const bf16x8 &b) {
-    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
-}
 
 template <int BN, int MT, bool INREG, int NS, bool GATED, int NW>
 __global__ __launch_bounds__(NW * 64, (NW == 4 && (BN + MT) * ROWB * NS <= 72 * 1024) ? 2 : 1) void gemm_bf16_kernel(
     const bf16_t *__restrict__ X, int ldx, const bf16_t *__restrict__ W, const bf16_t *__restrict__ R,
     bf16_t *__restrict__ Y, int ldy, float *__restrict__ P, size_t plane_stride, int M, int N, int K, int S,
-    GemmGroups gr) {
-    constexpr int ROWS = BN + MT;                   // rows of a stage buffer: W rows, then X rows
-    constexpr int WMW = (NW == 8 && BN < MT) ? 4 : 2;   // waves along m
-    constexpr int WNW = NW / WMW, RW = BN / WNW;     // waves along n; W rows per wave column
-    constexpr int LPS = ROWS / (NW * 8);            // direct loads per thread and stage (8 rows per wave instruction)
-    static_assert(ROWS % (NW * 8) == 0, "the stage's rows must divide among the waves' direct loads");
-    constexpr int STAGE = ROWS * ROWB;              // bytes; NS of them form the ring
-    constexpr int NA = RW / 16, NB = MT / (16 * WMW);       // 16-row operand tiles per wave
-    constexpr bool PIPE = MT >= 256;                // the hand-laid-out loop: it pays from 256-row tiles on (128-row tiles: 1-2 % slower with it)
+    int band, GemmGroups gr) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     const int m_tiles = (M + MT - 1) / MT;
-    // Workgroup ids are dealt round-robin to the 8 XCDs.  Tiles that share W rows (the
-    // m tiles of one (n tile, plane)) get ids 8 apart: same XCD, same L2, adjacent in time.
+    // Workgroup ids are dealt round-robin to the 8 XCDs.
     const int u = blockIdx.x % 8, v = blockIdx.x / 8;
-    int m_tile = v % m_tiles;
-    int ns = (v / m_tiles) * 8 + u;
+    int m_tile, ns;
+    if (band) {
+        if (!band_tile(N / BN, m_tiles, band, ns, m_tile)) return;
+    } else {
+        // Tiles that share W rows (the m tiles of one (n tile, plane)) get ids 8 apart: same XCD,
+        // same L2, adjacent in time.
+        m_tile = v % m_tiles;
+        ns = (v / m_tiles) * 8 + u;
+    }
     if (gr.n_groups) {
         // Expert-grouped launches size the grid for the largest possible group, so most tiles
         // past the first m tile are empty.  All first m tiles come first and the mostly empty
@@ -227,283 +185,15 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && (BN + MT) * ROWB * NS <= 72 * 
     } else if (ns >= (N / BN) * SG) {
         return;
     }
-    const int n_tile = ns / SG, sp = ns % SG;
-    const int Kp = K / S, kbase = INREG ? 0 : sp * Kp, n_stage = (INREG ? K : Kp) / BK;
-    const int plane_stages = Kp / BK;
-    const int n0 = n_tile * BN, m0 = m_tile * MT;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lr = lane & 15, lq = lane >> 4, wn = wave % WNW, wm = wave / WNW;
-
-    // Direct load j of this wave covers stage rows (j * NW + wave) * 8 .. + 8; lane l fetches
-    // row + l / 8, global 16-byte column (l % 8) ^ swizzle(row).
-    const bf16_t *src[LPS];
-#pragma unroll
-    for (int j = 0; j < LPS; ++j) {
-        const int row = (j * NW + wave) * 8 + (lane >> 3);
-        const int col = (lane & 7) ^ ((row >> 1) & 7);
-        if (row < BN) {
-            int n = n0 + row;
-            if (GATED) {   // stage row = wave half wn, then gate tiles, then up tiles
-                const int wn_r = row / RW, in_w = row % RW, up = in_w / (RW / 2);
-                n = n_tile * (BN / 2) + wn_r * (RW / 2) + in_w % (RW / 2) + up * (N / 2);
-            }
-            src[j] = W + (size_t)n * K + kbase + col * 8;
-        } else {
-            const int mr = min(m0 + row - BN, M - 1);
-            src[j] = X + (size_t)(list ? list[mr] / gr.x_div : mr) * ldx + kbase + col * 8;
-        }
-    }
-    // Stage order: the k stages of a plane are visited starting `rot` stages in and wrapping round,
-    // with rot a function of the n tile (groups of kRotGroup tiles share one).  Workgroups that run
-    // at the same time then read different column offsets of their 8 KB-pitched weight rows, which
-    // spreads the requests over the memory channels; tiles of one group keep reading the same X
-    // columns together, so X stays shared in L2.  The order depends on (N, K, n tile) only, never
-    // on the number of rows, so every schedule adds the same terms in the same order.
-    const int rot_group = (GATED ? n_tile * (BN / 2) / 64 : n0 / 128) / kRotGroup;   // by output column, the same for every tile shape
-    const int rot = (int)(((unsigned)rot_group * kRotStep) % (unsigned)plane_stages);
-    int iss_w = 0, iss_base = 0;                       // next stage to issue: index inside its plane, plane's first stage
-    unsigned char *iss_buf = lds;                      // the pending stage's ring buffer and k offset (issue_begin / issue_one)
-    int iss_kst = 0;
-    auto issue_begin = [&](int st) {                   // stage st goes into ring buffer st % NS; st ascends by one per call
-        iss_buf = lds + (st % NS) * STAGE;
-        iss_kst = iss_w + rot;
-        if (iss_kst >= plane_stages) iss_kst -= plane_stages;
-        iss_kst += iss_base;
-        if (++iss_w == plane_stages) { iss_w = 0; iss_base += plane_stages; }
-    };
-    auto issue_one = [&](int j) {                      // direct load j of the stage begun last
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[j] + (size_t)iss_kst * BK),
-                                         (__attribute__((address_space(3))) void *)(iss_buf + (j * NW + wave) * 8 * ROWB),
-                                         16, 0, 0);
-    };
-    auto issue = [&](int st) {                         // all direct loads of stage st
-        issue_begin(st);
-#pragma unroll
-        for (int j = 0; j < LPS; ++j) issue_one(j);
-    };
-
-    f32x4 acc[NA][NB], total[INREG ? NA : 1][INREG ? NB : 1];
-#pragma unroll
-    for (int a = 0; a < NA; ++a)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (INREG) total[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-
-    // operand read offsets inside a stage buffer (bytes), k-step 0; k-step 1 flips column bit 2
-    int a_off[NA], b_off[NB];
-#pragma unroll
-    for (int a = 0; a < NA; ++a) {
-        const int row = wn * RW + a * 16 + lr;
-        a_off[a] = row * ROWB + ((lq ^ ((row >> 1) & 7)) << 4);
-    }
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int row = BN + wm * (MT / WMW) + b * 16 + lr;
-        b_off[b] = row * ROWB + ((lq ^ ((row >> 1) & 7)) << 4);
-    }
-
-    auto fold_plane = [&](int st) {                    // a plane ends: fold its sum into the total, start from zero
-        if (INREG && (st + 1) % plane_stages == 0) {
-#pragma unroll
-            for (int a = 0; a < NA; ++a)
-#pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    total[a][b] += acc[a][b];
-                    acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-                }
-        }
-    };
-    auto wait_stage = [&](int st) {                    // stage st has landed when at most the loads of the stages issued after it are outstanding
-        const int ahead = min(NS - 2, n_stage - 1 - st);
-        if (ahead >= 4) wait_vmcnt(4 * LPS);
-        else if (ahead == 3) wait_vmcnt(3 * LPS);
-        else if (ahead == 2) wait_vmcnt(2 * LPS);
-        else if (ahead == 1) wait_vmcnt(LPS);
-        else wait_vmcnt(0);
-    };
-
-    if constexpr (PIPE) {
-        // Many rows: the matrix cores are the bound, and what keeps them waiting is everything that comes
-        // in bursts - a block of operand reads before a block of MFMAs, all of a stage's direct loads
-        // right after the barrier.  So the loop is laid out by hand, as inline assembly that the
-        // compiler neither reorders nor waits for.  A stage is four steps, (k half 0 | 1) x (first |
-        // second half of the wave's X tiles).  While the MFMAs of a step issue, the operands of the
-        // next step are read from LDS, one read every few MFMAs, across the stage boundary too; the
-        // direct loads of the stage that refills this stage's buffer are spread over the last step in
-        // the same way.  When a step begins, all that is outstanding is what the previous step read,
-        // so lgkmcnt(0) opens it (LDS reads return in order; nothing newer is in flight).  An
-        // accumulator is used once per step, so dependent MFMAs are never close.  Every accumulator
-        // still receives its k halves and stages in ascending order: the same bits as the plain loop.
-        constexpr int H0 = (NB + 1) / 2, H1 = NB - H0, TILE = 16 * ROWB;   // X tiles of the first and of the second half
-        bf16x8 a_cur[NA], a_nxt[NA], b_lo[H0], b_hi[H1];
-        // Operand tile i of a kind sits 16 rows = TILE bytes after tile 0 (the swizzle depends on the
-        // row's low four bits only), so one address per (kind, k half) and an immediate offset do.
-        const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
-        const unsigned a_adr[2] = {lds0 + (unsigned)a_off[0], lds0 + (unsigned)(a_off[0] ^ 64)};
-        const unsigned b_adr[2] = {lds0 + (unsigned)b_off[0], lds0 + (unsigned)(b_off[0] ^ 64)};
-        // The MFMAs of av x bv into accumulator columns b0 .. b0 + hb, with item(0) .. item(n_items - 1)
-        // spread evenly between them.
-        auto step = [&](const bf16x8 (&av)[NA], const auto &bv, auto b0, auto hb, auto n_items, auto &&item) {
-            constexpr int B0 = decltype(b0)::value, M = NA * decltype(hb)::value, T = decltype(n_items)::value;
-            static_for<0, M>([&](auto i) {
-                constexpr int I = decltype(i)::value;
-                mfma_acc(acc[I % NA][B0 + I / NA], av[I % NA], bv[I / NA]);
-                static_for<0, T>([&](auto k) {
-                    if constexpr (decltype(k)::value * M / T == I) item(k);
-                });
-            });
-        };
-        const std::integral_constant<int, 0> c0;
-        const std::integral_constant<int, H0> ch0;
-        const std::integral_constant<int, H1> ch1;
-        // All NS ring buffers are filled before the loop; stage st + NS is issued into the buffer of
-        // stage st once every wave has taken its last operands out of it.
-#pragma unroll
-        for (int d = 0; d < NS; ++d)
-            if (d < n_stage) issue(d);
-        {
-            const int ahead = min(NS - 1, n_stage - 1);
-            if (ahead >= 3) wait_vmcnt(3 * LPS);
-            else if (ahead == 2) wait_vmcnt(2 * LPS);
-            else if (ahead == 1) wait_vmcnt(LPS);
-            else wait_vmcnt(0);
-        }
-        __builtin_amdgcn_s_barrier();
-        static_for<0, NA>([&](auto k) { a_cur[decltype(k)::value] = lds_read16<decltype(k)::value * TILE>(a_adr[0]); });
-        static_for<0, H0>([&](auto k) { b_lo[decltype(k)::value] = lds_read16<decltype(k)::value * TILE>(b_adr[0]); });
-        for (int st = 0; st < n_stage; ++st) {
-            const unsigned so = (unsigned)(st % NS) * STAGE;
-            const unsigned a1 = a_adr[1] + so, b0 = b_adr[0] + so, b1 = b_adr[1] + so;
-            wait_lgkmcnt<0>();
-            step(a_cur, b_lo, c0, ch0, ch1, [&](auto k) {
-                constexpr int K = decltype(k)::value;
-                b_hi[K] = lds_read16<(H0 + K) * TILE>(b0);
-            });
-            wait_lgkmcnt<0>();
-            step(a_cur, b_hi, ch0, ch1, std::integral_constant<int, NA + H0>(), [&](auto k) {
-                constexpr int K = decltype(k)::value;
-                if constexpr (K < NA) a_nxt[K] = lds_read16<K * TILE>(a1);
-                else b_lo[K - NA] = lds_read16<(K - NA) * TILE>(b1);
-            });
-            wait_lgkmcnt<0>();
-            step(a_nxt, b_lo, c0, ch0, ch1, [&](auto k) {
-                constexpr int K = decltype(k)::value;
-                b_hi[K] = lds_read16<(H0 + K) * TILE>(b1);
-            });
-            wait_lgkmcnt<0>();                     // this wave has taken its last operands out of stage st's buffer
-            // One path for every stage, the last included (a second copy of the step's assembly would
-            // give each accumulator two definitions to merge at the loop's head): after the last stage
-            // the reads fetch operands nobody uses from the other ring buffer, and nothing is issued.
-            wait_stage(st + 1);
-            __builtin_amdgcn_s_barrier();          // every wave is done with the buffer and sees stage st + 1
-            const unsigned no = (unsigned)((st + 1) % NS) * STAGE;
-            const unsigned na = a_adr[0] + no, nb = b_adr[0] + no;
-            const bool refill = st + NS < n_stage;
-            if (refill) issue_begin(st + NS);
-            // reads and direct loads alternate while both last, then the rest of the longer list
-            constexpr int R = NA + H0, PAIRS = R < LPS ? R : LPS;
-            step(a_nxt, b_hi, ch0, ch1, std::integral_constant<int, R + LPS>(), [&](auto k) {
-                constexpr int K = decltype(k)::value;
-                constexpr bool is_read = K < 2 * PAIRS ? K % 2 == 0 : R > LPS;
-                constexpr int idx = K < 2 * PAIRS ? K / 2 : K - PAIRS;
-                if constexpr (is_read) {
-                    if constexpr (idx < NA) a_cur[idx] = lds_read16<idx * TILE>(na);
-                    else b_lo[idx - NA] = lds_read16<(idx - NA) * TILE>(nb);
-                } else {
-                    if (refill) issue_one(idx);
-                }
-            });
-            if (INREG && (st + 1) % plane_stages == 0) {
-                // the compiler does not know that the assembly's results arrive late: the last MFMAs
-                // must have left the pipeline before the accumulators are read as ordinary registers,
-                // and the cleared accumulators must be written before the next MFMA reads them
-                asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-                fold_plane(st);
-                asm volatile("s_nop 7" ::: "memory");
-            }
-        }
-        wait_lgkmcnt<0>();
-        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-    } else {
-#pragma unroll
-    for (int d = 0; d < NS - 1; ++d)
-        if (d < n_stage) issue(d);
-    for (int st = 0; st < n_stage; ++st) {
-        wait_stage(st);
-        // Bare barrier: __syncthreads() would add a fence that drains every outstanding load, which
-        // is exactly the prefetch.  The loads of stage st are complete (waited above) and, being
-        // direct-to-LDS, visible once complete; the reads of stage st-1 were consumed by MFMAs.
-        __builtin_amdgcn_s_barrier();
-        if (st + NS - 1 < n_stage) issue(st + NS - 1);
-        const unsigned char *buf = lds + (st % NS) * STAGE;
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            bf16x8 av[NA], bv[NB];
-#pragma unroll
-            for (int a = 0; a < NA; ++a) av[a] = *reinterpret_cast<const bf16x8 *>(buf + (a_off[a] ^ (ks << 6)));
-#pragma unroll
-            for (int b = 0; b < NB; ++b) bv[b] = *reinterpret_cast<const bf16x8 *>(buf + (b_off[b] ^ (ks << 6)));
-#pragma unroll
-            for (int a = 0; a < NA; ++a)
-#pragma unroll
-                for (int b = 0; b < NB; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[a], bv[b], acc[a][b], 0, 0, 0);
-        }
-        fold_plane(st);
-    }
-    }
-
-    if (GATED) {
-#pragma unroll
-        for (int a = 0; a < NA / 2; ++a)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int m = m0 + wm * (MT / WMW) + b * 16 + lr;
-                const int n = n_tile * (BN / 2) + wn * (RW / 2) + a * 16 + 4 * lq;
-                if (m >= M) continue;
-                const size_t orow = list ? list[m] : m;
-                const f32x4 g = acc[a][b], up = acc[a + NA / 2][b];
-                float o[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) o[r] = g[r] / (1.0f + expf(-g[r])) * up[r];
-                u32x2 ov;
-                ov[0] = (uint32_t)f2bf(o[0]) | ((uint32_t)f2bf(o[1]) << 16);
-                ov[1] = (uint32_t)f2bf(o[2]) | ((uint32_t)f2bf(o[3]) << 16);
-                *reinterpret_cast<u32x2 *>(Y + orow * ldy + n) = ov;
-            }
-        return;
-    }
-#pragma unroll
-    for (int a = 0; a < NA; ++a)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int m = m0 + wm * (MT / WMW) + b * 16 + lr;
-            const int n = n0 + wn * RW + a * 16 + 4 * lq;
-            if (m >= M) continue;
-            const size_t orow = list ? list[m] : m;
-            f32x4 o = INREG ? total[a][b] : acc[a][b];
-            if ((S == 1 || INREG) && !gr.force_planes) {
-                if (R) {
-                    const u32x2 rv = *reinterpret_cast<const u32x2 *>(R + orow * N + n);
-                    o[0] += bf2f(rv[0] & 0xffff); o[1] += bf2f(rv[0] >> 16);
-                    o[2] += bf2f(rv[1] & 0xffff); o[3] += bf2f(rv[1] >> 16);
-                }
-                u32x2 ov;
-                ov[0] = (uint32_t)f2bf(o[0]) | ((uint32_t)f2bf(o[1]) << 16);
-                ov[1] = (uint32_t)f2bf(o[2]) | ((uint32_t)f2bf(o[3]) << 16);
-                *reinterpret_cast<u32x2 *>(Y + orow * N + n) = ov;
-            } else {
-                *reinterpret_cast<f32x4 *>(P + (size_t)sp * plane_stride + orow * N + n) = o;
-            }
-        }
+    gemm_tile<BN, MT, INREG, NS, GATED, NW, (MT >= 256)>(lds, X, ldx, W, R, Y, ldy, P, plane_stride, M, N, K, S, list, gr.x_div, gr.force_planes,
+                                                         ns / SG, ns % SG, m_tile * MT);   // the hand-laid-out loop pays from 256-row tiles on
+                                                                                           // (128 x 128 tiles: 1-2 % slower with it)
 }
 
 template <int BN, int MT, bool INREG, int NS, bool GATED = false, int NW = 4>
 hipError_t launch_gemm_bf16(int grid, hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y,
                             float *partial, size_t plane_stride, int rows, int N, int K, int S, const GemmGroups &gr,
-                            int ldy = 0) {
+                            int ldy = 0, int band = 0) {
     constexpr int STAGE = (BN + MT) * ROWB;
     static_assert(NS >= 2 && NS <= 6 && NS * STAGE <= 160 * 1024, "ring does not fit in LDS");
     static bool attr_set = false;                      // above 64 KB of dynamic LDS needs an opt-in, once
@@ -515,7 +205,7 @@ hipError_t launch_gemm_bf16(int grid, hipStream_t s, const void *X, int ldx, con
     }
     hipLaunchKernelGGL((gemm_bf16_kernel<BN, MT, INREG, NS, GATED, NW>), dim3(grid), dim3(NW * 64), NS * STAGE, s,
                        (const bf16_t *)X, ldx, (const bf16_t *)W, (const bf16_t *)R, (bf16_t *)Y, ldy ? ldy : N, partial,
-                       plane_stride, rows, N, K, S, gr);
+                       plane_stride, rows, N, K, S, band, gr);
     return hipGetLastError();
 }
 
@@ -707,16 +397,19 @@ GemmPath gemm_path(int dtype, int rows, int N, int K) {
             p.resident = 256;
             return p;
         }
-        // Tile height: two workgroups fit a CU, so 512 tiles run at a time and the launch takes
-        // ceil(tiles / 512) rounds of a duration proportional to the tile height.  A taller
+        // Tile height: two 4-wave workgroups fit a CU, so 512 tiles run at a time and the launch takes
+        // ceil(tiles / 512) rounds of a duration that grows with the tile height.  A taller
         // tile that saves a round wins (2112 rows x 4096 columns: 544 tiles of 128 rows need
-        // two rounds, 448 tiles of 160 rows one).  The summation order of an output element
-        // does not depend on the tile height.
-        const long cost128 = (long)((nt * ((rows + 127) / 128) + 511) / 512) * 128;
-        const long cost160 = (long)((nt * ((rows + 159) / 160) + 511) / 512) * 160;
-        p.kind = GEMM_MANY; p.bn = 128; p.mt = cost160 < cost128 ? 160 : 128;
-        p.workgroups = nt * ((rows + p.mt - 1) / p.mt);
+        // two rounds, 448 tiles of 160 rows one).  Where planes are folded, 256 W rows x 128 X rows on
+        // eight waves with a ring of three hold the same outputs per CU as two 128 x 128 workgroups and
+        // run a round in 0.93-0.96 of their time (down at 1300 / 3000 / 4096 rows 224 / 426 / 457 -> 217 /
+        // 404 / 435 us); a round of 160-row tiles takes 1.29 of it (down at 2112 rows: 283 us, one round,
+        // against 407 us, two).  The summation order of an output element does not depend on the tile.
+        const long rounds128 = (nt * ((rows + 127) / 128) + 511) / 512, rounds160 = (nt * ((rows + 159) / 160) + 511) / 512;
+        p.kind = GEMM_MANY; p.bn = 128; p.mt = rounds160 * 129 < rounds128 * 100 ? 160 : 128;
         p.resident = 512;
+        if (p.folded && p.mt == 128 && N % 256 == 0) { p.bn = 256; p.resident = 256; }
+        p.workgroups = (N / p.bn) * ((rows + p.mt - 1) / p.mt);
         return p;
     }
     p.kind = GEMM_FEW; p.bn = 128; p.mt = rows <= 64 ? 64 : 128;
@@ -732,6 +425,13 @@ bool gemm_uses_plane_buffer(int dtype, int rows, int N, int K) {
 }
 
 namespace {
+// n tiles per band of a launch whose tiles cover the whole depth (0: n-tile order, planes spread over the
+// grid).  Eight bands an XCD's tiles of every shape here to about as many W rows as X rows (32 or 64
+// tiles run on it at a time).  4096 rows, n-tile order -> bands of 8 (4 and 16 lose 1-4 % of it): qkv 252 -> 208,
+// o 183 -> 167, down 528 -> 470, gate/up 763 -> 753 us; 3000 rows: down 449 -> 428 us; up to 2112 rows nothing changes.
+int gemm_band(const GemmPath &p) { return p.kind == GEMM_WIDE || p.kind == GEMM_MANY ? 8 : 0; }
+int gemm_band_grid(int n_tiles, int m_tiles) { return (n_tiles * m_tiles + 7) / 8 * 8; }
+
 // The operator that follows the projection, as a kernel of its own on the rows the projection wrote.
 hipError_t run_epilogue(int dtype, const GemmEpilogue &ep, void *Y, int rows, int N, hipStream_t s) {
     if (ep.kind == GemmEpilogue::NORM) return launch_rmsnorm(dtype, Y, ep.g, ep.h_out, ep.ld_h, rows, N, ep.eps, s);
@@ -773,13 +473,15 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
         rows = head;
     }
     const int S = p.split, m_tiles = (rows + p.mt - 1) / p.mt;
-    // workgroup ids are dealt to the 8 XCDs in turn: (n tile, plane) pairs are padded to a multiple of 8
-    const int grid = (((N / p.bn) * (p.folded ? 1 : S) + 7) / 8) * 8 * m_tiles;
+    // workgroup ids are dealt to the 8 XCDs in turn: tiles, or (n tile, plane) pairs, are padded to a multiple of 8
+    const int band = gemm_band(p);
+    const int grid = band ? gemm_band_grid(N / p.bn, m_tiles) : (((N / p.bn) * (p.folded ? 1 : S) + 7) / 8) * 8 * m_tiles;
 #define DYN_GEMM(BN, MT, INREG, NS, NW) \
-    launch_gemm_bf16<BN, MT, INREG, NS, false, NW>(grid, s, X, ldx, W, R, Y, partial, plane_stride, rows, N, K, S, none)
+    launch_gemm_bf16<BN, MT, INREG, NS, false, NW>(grid, s, X, ldx, W, R, Y, partial, plane_stride, rows, N, K, S, none, 0, band)
     hipError_t e;
     if (p.kind == GEMM_TALL) e = p.mt == 256 ? DYN_GEMM(128, 256, false, 3, 8) : p.mt == 384 ? DYN_GEMM(128, 384, false, 2, 8) : DYN_GEMM(128, 512, false, 2, 8);
     else if (p.kind == GEMM_WIDE) e = DYN_GEMM(256, 256, false, 2, 8);
+    else if (p.kind == GEMM_MANY && p.bn == 256) e = launch_gemm_fold(grid, s, X, ldx, W, R, Y, rows, N, K, S, band);
     else if (p.kind == GEMM_MANY && p.mt == 160) e = p.folded ? DYN_GEMM(kBigBN, 160, true, kBigNS, 4) : DYN_GEMM(kBigBN, 160, false, kBigNS, 4);
     else if (p.kind == GEMM_MANY) e = p.folded ? DYN_GEMM(kBigBN, kBigMT, true, kBigNS, 4) : DYN_GEMM(kBigBN, kBigMT, false, kBigNS, 4);
     else e = p.mt == 64 ? DYN_GEMM(128, 64, false, 4, 8) : DYN_GEMM(128, 128, false, 4, 8);
@@ -828,10 +530,10 @@ hipError_t launch_gemm_gated(const void *X, int ldx, const void *W, void *Y, int
     if (max_rows <= 0) return hipSuccess;
     hipError_t e;
 #define DYN_GATED(BN, MT, NS, NW) \
-    launch_gemm_bf16<BN, MT, false, NS, true, NW>(grid, s, X, ldx, W, nullptr, Y, nullptr, 0, max_rows, N2, K, 1, gr, ldy)
+    launch_gemm_bf16<BN, MT, false, NS, true, NW>(grid, s, X, ldx, W, nullptr, Y, nullptr, 0, max_rows, N2, K, 1, gr, ldy, band)
     if (gr.n_groups) {
         const GroupTile t = gemm_group_tile(gr, max_rows, N2);
-        const int grid = ((((N2 / t.bn) * gr.n_groups) + 7) / 8) * 8 * ((max_rows + t.mt - 1) / t.mt);
+        const int band = 0, grid = ((((N2 / t.bn) * gr.n_groups) + 7) / 8) * 8 * ((max_rows + t.mt - 1) / t.mt);
         e = t.bn == 256 ? DYN_GATED(256, 256, 2, 8) : t.mt == 256 ? DYN_GATED(128, 256, 3, 8) : t.mt == 64 ? DYN_GATED(128, 64, 4, 8) : DYN_GATED(128, 128, 4, 8);
     } else {
         const GemmPath p = gemm_path(1, max_rows, N2, K);          // split factor 1: no planes on any path
@@ -843,7 +545,8 @@ hipError_t launch_gemm_gated(const void *X, int ldx, const void *W, void *Y, int
             max_rows = head;
         }
         const int mt = p.kind == GEMM_MANY ? kBigMT : p.mt;    // the gated many-row kernel has 128-row tiles only
-        const int grid = ((N2 / p.bn + 7) / 8) * 8 * ((max_rows + mt - 1) / mt);
+        const int m_tiles = (max_rows + mt - 1) / mt, band = gemm_band(p);
+        const int grid = band ? gemm_band_grid(N2 / p.bn, m_tiles) : ((N2 / p.bn + 7) / 8) * 8 * m_tiles;
         if (p.kind == GEMM_TALL) e = p.mt == 256 ? DYN_GATED(128, 256, 3, 8) : DYN_GATED(128, 384, 2, 8);
         else if (p.kind == GEMM_WIDE) e = DYN_GATED(256, 256, 2, 8);
         else if (p.kind == GEMM_MANY) e = DYN_GATED(kBigBN, kBigMT, kBigNS, 4);

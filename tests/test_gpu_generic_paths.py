@@ -110,3 +110,13 @@ def test_unaligned_caches_take_the_plain_loops_and_agree():
     torch.cuda.synchronize()
     got, ref = step.y.cpu().double().numpy(), y0.double().numpy()
     assert np.abs(got - ref).max() / np.abs(ref).max() < 1e-5        # two fp32 attention orders
+
+
+@pytest.mark.parametrize("rows", [1025, 1281, 1500, 2049])
+def test_folded_launch_in_bands_matches_smaller_launches(rows):
+    """Rows of one many-row launch (256 x 128 tiles, planes folded, bands over the XCDs, a last band narrower than the
+    others) have the bits of the same rows cut into two launches of other tiles."""
+    w = workload("fold", "bf16", 1280, 4, 1, 128, 10240, [(1, 1 + i % 3) for i in range(rows)], seed=60)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, 200, rows))
+    data = gen.generate(w)
+    both_schedules(w, data)
