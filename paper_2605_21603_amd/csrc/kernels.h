@@ -90,6 +90,11 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
 // Many rows, split-K planes folded in registers, 256 x 128 tiles (kernels_gemm_wide.hip; launch_gemm calls it).
 hipError_t launch_gemm_fold(int grid, hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N,
                             int K, int S, int band);
+// Expert-grouped projection without planes on 256-wide tiles of a height chosen per expert (the grouped launchers
+// call it); gated: silu(gate) * up to Y, else Y, or fp32 to P with gr.force_planes.
+hipError_t launch_gemm_experts_wide(bool gated, hipStream_t s, const void *X, int ldx, const void *W, void *Y, int ldy, float *P, int N,
+                                    int K, const GemmGroups &gr);
+
 hipError_t launch_gemm_grouped(int dtype, const void *X, int ldx, const void *W, void *Y, float *partial,
                                size_t plane_stride, const GemmGroups &gr, int max_rows, int row0, int n_rows, int N, int K,
                                hipStream_t s, hipEvent_t mid = nullptr);

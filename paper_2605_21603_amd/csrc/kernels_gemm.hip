@@ -531,10 +531,12 @@ hipError_t launch_gemm_gated(const void *X, int ldx, const void *W, void *Y, int
     hipError_t e;
 #define DYN_GATED(BN, MT, NS, NW) \
     launch_gemm_bf16<BN, MT, false, NS, true, NW>(grid, s, X, ldx, W, nullptr, Y, nullptr, 0, max_rows, N2, K, 1, gr, ldy, band)
-    if (gr.n_groups) {
-        const GroupTile t = gemm_group_tile(gr, max_rows, N2);
+    const GroupTile t = gemm_group_tile(gr, max_rows, N2);
+    if (gr.n_groups && t.bn == 256) {
+        e = launch_gemm_experts_wide(true, s, X, ldx, W, Y, ldy, nullptr, N2, K, gr);
+    } else if (gr.n_groups) {
         const int band = 0, grid = ((((N2 / t.bn) * gr.n_groups) + 7) / 8) * 8 * ((max_rows + t.mt - 1) / t.mt);
-        e = t.bn == 256 ? DYN_GATED(256, 256, 2, 8) : t.mt == 256 ? DYN_GATED(128, 256, 3, 8) : t.mt == 64 ? DYN_GATED(128, 64, 4, 8) : DYN_GATED(128, 128, 4, 8);
+        e = t.mt == 256 ? DYN_GATED(128, 256, 3, 8) : t.mt == 64 ? DYN_GATED(128, 64, 4, 8) : DYN_GATED(128, 128, 4, 8);
     } else {
         const GemmPath p = gemm_path(1, max_rows, N2, K);          // split factor 1: no planes on any path
         if (p.tail_rows) {     // the last rows in a launch of their own (never a wide one: at most 256 rows)
@@ -580,7 +582,7 @@ hipError_t launch_gemm_grouped(int dtype, const void *X, int ldx, const void *W,
     const int grid = ((ns + 7) / 8) * 8 * m_tiles;
     hipError_t e;
 #define DYN_GROUPED(BN, MT, NS) launch_gemm_bf16<BN, MT, false, NS, false, 8>(grid, s, X, ldx, W, nullptr, Y, partial, plane_stride, max_rows, N, K, S, gr)
-    e = t.bn == 256 ? DYN_GROUPED(256, 256, 2) : t.mt == 256 ? DYN_GROUPED(128, 256, 3) : t.mt == 64 ? DYN_GROUPED(128, 64, 4) : DYN_GROUPED(128, 128, 4);
+    e = t.bn == 256 ? launch_gemm_experts_wide(false, s, X, ldx, W, Y, N, partial, N, K, gr) : t.mt == 256 ? DYN_GROUPED(128, 256, 3) : t.mt == 64 ? DYN_GROUPED(128, 64, 4) : DYN_GROUPED(128, 128, 4);
 #undef DYN_GROUPED
     if (e == hipSuccess && mid) e = hipEventRecord(mid, s);
     if (e != hipSuccess || S == 1 || gr.force_planes) return e;

@@ -1,5 +1,6 @@
-// Projection kernels whose tile is 256 W rows wide: the many-row launch that folds split-K planes in
-// registers.  The tile itself is gemm_tile.h's; here is which workgroup gets which.
+// Projection kernels whose tile is 256 W rows wide or chosen per expert on the device: the many-row
+// launch that folds split-K planes in registers, and the expert-grouped launches.  The tile itself is
+// gemm_tile.h's; here is which workgroup gets which.
 #include "gemm_tile.h"
 
 namespace dyn {
@@ -27,6 +28,73 @@ hipError_t launch_gemm_fold(int grid, hipStream_t s, const void *X, int ldx, con
     }
     hipLaunchKernelGGL(gemm_fold_kernel, dim3(grid), dim3(512), LDS, s, (const bf16_t *)X, ldx, (const bf16_t *)W, (const bf16_t *)R,
                        (bf16_t *)Y, rows, N, K, S, band);
+    return hipGetLastError();
+}
+
+// Expert-grouped launch with 256 W rows per tile, for some hundred rows per expert (no planes).  The host
+// knows the number of (token, expert) pairs but not how they fall on the experts; a tile height fixed
+// on the host computes up to 255 rows of padding per expert.  Here every expert's rows are cut into
+// ceil(rows / 256) equal m tiles, and a tile's height is what they need, rounded up to 64 rows: the
+// workgroup runs one of four bodies.  Tiles of the tallest bodies come first and the short ones fill the
+// end of the launch.  XCD u takes the n tiles congruent to u for all experts, an m tile's n tiles in
+// a row (they share X) and an expert's m tiles next to each other (they share W).
+// Measured against 256 x 256 tiles throughout (8 experts of a skewed router, two per token): 1100 / 1500 / 2048
+// tokens, gate/up 668 / 1006 / 1203 -> 611 / 852 / 1077 us, down 412 / 700 / 765 -> 410 / 421 / 720 us.
+constexpr int kExpertsBN = 256;
+constexpr int kExpertsLds = 160 * 1024;               // the bodies' rings: 2 x 64, 2 x 56, 3 x 48, 4 x 40 KB
+
+template <bool GATED>
+__global__ __launch_bounds__(512, 1) void gemm_experts_wide_kernel(const bf16_t *__restrict__ X, int ldx, const bf16_t *__restrict__ W,
+                                                                   bf16_t *__restrict__ Y, int ldy, float *__restrict__ P, int N, int K,
+                                                                   GemmGroups gr) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    const int u = blockIdx.x % 8, v = blockIdx.x / 8, nt = N / kExpertsBN;
+    const int n_local = (nt - u + 7) / 8;             // n tiles u, u + 8, ...
+    if (n_local <= 0) return;
+    int m = v / n_local, e = 0, units = 0, m_tile = 0, rows = 0;   // m: place of the m tile in launch order
+    const int n_tile = (v - m * n_local) * 8 + u;
+    bool found = false;
+    for (int size = 4; size >= 1 && !found; --size)   // m tiles of 64 * size rows
+        for (e = 0; e < gr.n_groups; ++e) {
+            rows = gr.counts[e];
+            const int n_m = (rows + 255) / 256;
+            if (n_m == 0) continue;
+            units = ((rows + n_m - 1) / n_m + 63) / 64;
+            if (units != size) continue;
+            if (m < n_m) { m_tile = m; found = true; break; }
+            m -= n_m;
+        }
+    if (!found) return;
+    const int32_t *list = gr.lists + (size_t)e * gr.cap;
+    const bf16_t *We = W + (size_t)e * gr.w_stride;
+    // the last m tile may hold fewer rows than it has room for, none below it is short: ceil(rows / n_m) <= 64 * units
+    const int m0 = m_tile * units * 64;
+    if (m0 >= rows) return;
+#define DYN_BODY(MT, NS) gemm_tile<kExpertsBN, MT, false, NS, GATED, 8, true>(lds, X, ldx, We, nullptr, Y, ldy, P, 0, rows, N, K, 1, list, gr.x_div, gr.force_planes, n_tile, 0, m0)
+    if (units == 4) DYN_BODY(256, 2);
+    else if (units == 3) DYN_BODY(192, 2);
+    else if (units == 2) DYN_BODY(128, 3);
+    else DYN_BODY(64, 4);
+#undef DYN_BODY
+}
+
+hipError_t launch_gemm_experts_wide(bool gated, hipStream_t s, const void *X, int ldx, const void *W, void *Y, int ldy, float *P, int N,
+                                    int K, const GemmGroups &gr) {
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void *)gemm_experts_wide_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kExpertsLds);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)gemm_experts_wide_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kExpertsLds);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    // at most one partly filled m tile per expert; workgroups past the last tile end at once
+    const int m_tiles = gr.cap / 256 + gr.n_groups, grid = (N / kExpertsBN + 7) / 8 * 8 * m_tiles;
+    if (gated)
+        hipLaunchKernelGGL(gemm_experts_wide_kernel<true>, dim3(grid), dim3(512), kExpertsLds, s, (const bf16_t *)X, ldx, (const bf16_t *)W,
+                           (bf16_t *)Y, ldy, P, N, K, gr);
+    else
+        hipLaunchKernelGGL(gemm_experts_wide_kernel<false>, dim3(grid), dim3(512), kExpertsLds, s, (const bf16_t *)X, ldx, (const bf16_t *)W,
+                           (bf16_t *)Y, ldy, P, N, K, gr);
     return hipGetLastError();
 }
 

@@ -112,6 +112,20 @@ def test_unaligned_caches_take_the_plain_loops_and_agree():
     assert np.abs(got - ref).max() / np.abs(ref).max() < 1e-5        # two fp32 attention orders
 
 
+# experts' rows around the edges of the 64-, 128-, 192- and 256-row tile bodies: popular experts with several m tiles, one without rows
+@pytest.mark.parametrize("tokens,pull", [(420, 0.0), (470, 3.0), (700, 1.0), (1100, 2.0)])
+def test_expert_tiles_follow_the_rows_each_expert_gets(tokens, pull):
+    w = workload("wide", "bf16", 512, 4, 1, 128, 512, [(1, 1 + i % 5) for i in range(tokens)], experts=4, top_k=2, seed=50 + tokens)
+    data = gen.generate(w)
+    router = data["weights"][0]["w_router"]
+    router[3] = -router[0]                                   # tokens pulled towards expert 0 never choose expert 3
+    x = data["x"].float()
+    x += pull * 512 ** 0.5 * router[0] / router[0].norm() * torch.rand(tokens, 1, generator=torch.Generator().manual_seed(1)) ** 0.5
+    data["x"] = x.to(torch.bfloat16)
+    y, k, v = both_schedules(w, data)
+    check_against_oracle(w, data, y, k, v)
+
+
 @pytest.mark.parametrize("rows", [1025, 1281, 1500, 2049])
 def test_folded_launch_in_bands_matches_smaller_launches(rows):
     """Rows of one many-row launch (256 x 128 tiles, planes folded, bands over the XCDs, a last band narrower than the
