@@ -28,13 +28,26 @@ constexpr int kMaxChunkTokens = 512;
 // positions 4 (l / 16) + r) is the B layout of the second if its r-th product takes position 4 (l / 16) + r
 // as its k index l / 16, and a lane's V operand is then four consecutive positions of one head-dim row.
 // A group of one token (decode) gives each of the four waves a quarter of the chunk's positions and
-// merges the four in wave order through LDS; a group of several tokens gives each wave its own set of
-// 16 columns, and the waves walk the same positions (K and V come from the vector cache).  Which
+// merges the four in wave order through LDS (without the quarters a decode chunk takes half as long again); a
+// group of several tokens gives each wave its own set of 16 columns, and the waves walk the same
+// positions (quarters there: a 300-token prompt + 40 decodes 67 against 51 us).  Which
 // of the two a token is part of depends on its sequence only, never on the schedule.
-// What bounds it: HBM latency with two tiles of 16 * TP positions in flight per wave.  Measured against
-// the one-wave-per-(token, q head, chunk) form below, launch alone: fp32, 64-wide heads, 4 tokens behind
-// 128 positions 27.7 -> 9.0 us, a 201-token prompt + 24 decodes 242 -> 34 us; bf16, 64-wide heads, 300-token prompt
-// + 40 decodes at 64..2048 1680 -> 89 us; bf16, 128-wide, 32-position pages, 13 decodes at 200..3000 301 -> 36 us.
+// What bounds it is latency - rows, then block table, then pages - so everything that does not wait for one
+// of these is loaded beside it, two tiles of 16 * TP positions are in flight per wave, and the block table is
+// read with scalar loads a tile ahead (a vector load of a page id waits for every page load issued before it).
+// Measured against the one-wave-per-(token, q head, chunk) form below, the attention
+// operator under events: bf16, 64-wide heads, 300-token prompt + 40 decodes at 64..2048 1690 -> 58 us; fp32, 64-wide, 201-token
+// prompt + 24 decodes 250 -> 29 us, 4 tokens behind 128 positions 34 -> 15 us; bf16, 128-wide, 32-position pages, 13
+// decodes at 200..3000 307 -> 43 us.
+// Four consecutive outputs, rounded to the storage type.
+__device__ __forceinline__ void store4(float *y, f32x4 v) { *reinterpret_cast<f32x4 *>(y) = v; }
+__device__ __forceinline__ void store4(bf16_t *y, f32x4 v) {
+    u32x2 w;
+    w[0] = (uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16);
+    w[1] = (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16);
+    *reinterpret_cast<u32x2 *>(y) = w;
+}
+
 template <typename T, int HD, int TP>
 __global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_kernel(const T *__restrict__ qkv, const int32_t *__restrict__ seq_of_token,
                                                         const int32_t *__restrict__ pos_of_token,
@@ -45,32 +58,38 @@ __global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_
     constexpr bool F32 = sizeof(T) == 4;
     constexpr int NK = F32 ? HD / 16 : HD / 32, ND = HD / 16;      // 16-byte K operands and 16-row V operands of a lane
     constexpr int MD = HD < 128 ? HD : 128;                        // head-dim indices merged per round
-    typedef typename std::conditional<F32, f32x4, u32x2>::type vload_t;   // four positions of V
     __shared__ float merge_o[4][16][MD + 4];
     __shared__ float merge_ml[4][16][2];
-    const int c = blockIdx.x % sh.max_chunks, g = (blockIdx.x / sh.max_chunks) % sh.n_kv, t = blockIdx.x / (sh.max_chunks * sh.n_kv);
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15, lq = lane >> 4;
-    const int G = sh.n_q / sh.n_kv, TG = 16 / G, tg = 4 * TG;
+    typedef typename std::conditional<F32, f32x4, u32x2>::type vload_t;   // four positions of V
+    const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
+    // (chunk, kv head, token), tokens fastest.  Only a group's first token has work, and few sequences reach the later
+    // chunks: workgroup ids, which go to the 8 XCDs in turn, are rotated inside every eight by their
+    // higher bits so that the ones with work, however regularly spaced, spread over all XCDs.
+    const unsigned wg = (blockIdx.x & ~7u) | ((blockIdx.x + (blockIdx.x >> 3) + (blockIdx.x >> 6)) & 7u);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t = (int)(wg % rows), g = (int)(wg / rows) % sh.n_kv, c = (int)(wg / rows) / sh.n_kv;
+    if (c >= sh.max_chunks) return;
+    const int G = sh.n_q / sh.n_kv, TG = 16 / G, tg = 4 * TG;      // tokens per set of columns, per group
+    const int col_tok = lr / G, col_head = lr % G;                 // this lane's column: a token of the wave's set and a q head
     const int s = seq_of_token[t], p0 = pos_of_token[t];
-    if (t > 0 && seq_of_token[t - 1] == s && pos_of_token[t - 1] / tg == p0 / tg) return;      // not the first token of its group
-    const bool in_group = lane < tg && t + lane < rows && seq_of_token[min(t + lane, rows - 1)] == s &&
-                          pos_of_token[min(t + lane, rows - 1)] / tg == p0 / tg;
-    const int n_tok = __popcll(__ballot(in_group));
-    const int n_keys = pos_of_token[t + n_tok - 1] + 1;            // keys the group's last token attends
+    const int before = t > 0 ? t - 1 : 0, s_before = seq_of_token[before], p_before = pos_of_token[before];
+    const int row = min(t + lane, rows - 1), row_seq = seq_of_token[row], row_pos = pos_of_token[row];
+    if (t > 0 && s_before == s && p_before / tg == p0 / tg) return;                            // not the first token of its group
+    const int n_tok = __popcll(__ballot(lane < tg && t + lane < rows && row_seq == s && row_pos / tg == p0 / tg));
+    const int n_keys = __builtin_amdgcn_readlane(row_pos, n_tok - 1) + 1;                      // keys the group's last token attends
     const int ps = sh.page_size, ct = sh.chunk_pages * ps, j0 = c * ct;
     if (j0 >= n_keys) return;
     const int j1 = min(j0 + ct, n_keys);
     const bool single = n_tok == 1;
     const int32_t *bt = block_table + (size_t)s * sh.max_pages_per_seq;
+    const float tiles_per_page = 16.0f / (float)ps;
 
-    // this lane's column: B operands of the score product, and the end of the keys it attends in this chunk
-    const int col_tok = lr / G, col_head = lr % G;
-    const int ti = single ? col_tok : wave * TG + col_tok;
-    const bool live = col_tok < TG && ti < n_tok;
-    const int tq = t + (live ? ti : 0);
-    const int col_keys = live ? pos_of_token[tq] + 1 : 0, nk = min(col_keys, j1);
+    const int set0 = single ? 0 : wave * TG;                       // first token of the wave's columns
+    const bool live = col_tok < TG && set0 + col_tok < n_tok;
+    const int col_pos = __shfl(row_pos, set0 + min(col_tok, TG - 1), 64);                      // every lane takes part
+    const int col_keys = live ? col_pos + 1 : 0;                   // keys the column attends
     u32x4 qf[NK];
-    const T *qp = qkv + (size_t)tq * ((sh.n_q + 2 * sh.n_kv) * HD) + (size_t)(g * G + (live ? col_head : 0)) * HD;
+    const T *qp = qkv + (size_t)(t + (live ? set0 + col_tok : 0)) * ((sh.n_q + 2 * sh.n_kv) * HD) + (size_t)(g * G + (live ? col_head : 0)) * HD;
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
         qf[k] = *reinterpret_cast<const u32x4 *>(qp + (F32 ? k * 16 + 4 * lq : k * 32 + 8 * lq));
@@ -78,28 +97,45 @@ __global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_
     }
     const float scale = 1.0f / sqrtf((float)HD);
 
-    // positions this wave walks: [w0, w1), in tiles of 16 * TP from w0 (a multiple of 16)
-    int w0 = j0, w1 = j1;
+    // positions this wave walks, [w0, w1), in tiles of 16 * TP from w0 (a multiple of 16), and where live columns
+    // begin to differ in what they see
+    int w0 = j0, w1 = j1, free_keys = j1;
     if (single) {
         const int n_tile = (j1 - j0 + 16 * TP - 1) / (16 * TP), per = (n_tile + 3) / 4;
         w0 = j0 + min(wave * per, n_tile) * 16 * TP;
-        w1 = min(j1, w0 + per * 16 * TP);
+        free_keys = w1 = min(j1, w0 + per * 16 * TP);
     } else {
-        const int last = min((wave + 1) * TG, n_tok) - 1;          // the wave's last live token
-        w1 = wave * TG < n_tok ? min(j1, pos_of_token[t + last] + 1) : j0;
+        const int last = __builtin_amdgcn_readlane(row_pos, min(set0 + TG, n_tok) - 1), first = __builtin_amdgcn_readlane(row_pos, min(set0, n_tok - 1));
+        w1 = set0 < n_tok ? min(j1, last + 1) : j0;
+        free_keys = min(w1, first + 1);
     }
-    // the first key any live column of the wave must not see (single: none before w1)
-    const int free_keys = single ? w1 : (wave * TG < n_tok ? pos_of_token[t + wave * TG] + 1 : 0);
+    const int nk = min(col_keys, w1);                              // end of the column's keys in [w0, w1)
 
     constexpr int NBUF = HD * sizeof(T) > 512 ? 1 : 2;             // register buffers: fp32 256-wide operands fit once
     u32x4 kr[NBUF][TP][NK];
     vload_t vr[NBUF][TP][ND];
-    auto load = [&](auto buf, int j) {                             // tile at position j; sub-tiles past the end reload the last one
+    // Sub-tile i of the tile at position j: its 16 positions lie in one page.  Sub-tiles past the end are the last one again.
+    auto place = [&](int j, int i, int &slot) {
+        const int at = min(j + 16 * i, (w1 - 1) & ~15);
+        const int lp = __builtin_amdgcn_readfirstlane((int)(((float)(at >> 4) + 0.5f) * tiles_per_page));   // at / ps, exact below 2^22 tiles
+        slot = at - lp * ps;
+        return lp;
+    };
+    int page[TP];                                                  // pages of the tile that is loaded next
+    auto look_up = [&](int j) {
+#pragma unroll
+        for (int i = 0; i < TP; ++i) {
+            int slot;
+            page[i] = bt[place(j, i, slot)];
+        }
+    };
+    auto load = [&](auto buf, int j) {
         constexpr int B = decltype(buf)::value;
 #pragma unroll
         for (int i = 0; i < TP; ++i) {
-            const int jj = min(j + 16 * i, (w1 - 1) & ~15), lp = jj / ps, slot = jj - lp * ps;
-            const size_t pg = (size_t)bt[lp] * sh.n_kv + g;
+            int slot;
+            place(j, i, slot);
+            const size_t pg = (size_t)page[i] * sh.n_kv + g;
             const T *kp = k_cache + (pg * ps + slot + lr) * HD + (F32 ? 4 : 8) * lq;
             const T *vp = v_cache + (pg * HD + lr) * ps + slot + 4 * lq;
 #pragma unroll
@@ -107,6 +143,7 @@ __global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_
 #pragma unroll
             for (int dt = 0; dt < ND; ++dt) vr[B][i][dt] = *reinterpret_cast<const vload_t *>(vp + (size_t)dt * 16 * ps);
         }
+        look_up(j + 16 * TP);
     };
     f32x4 acc[ND];
 #pragma unroll
@@ -114,6 +151,9 @@ __global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_
     float m_run = -INFINITY, l_run = 0.f;
     auto multiply = [&](auto buf, int j) {
         constexpr int B = decltype(buf)::value;
+        // Some live column must not see all of the tile's positions, or the chunk ends in it (wave-uniform):
+        // only then are scores and values masked.
+        const bool edge = j + 16 * TP > free_keys;
         f32x4 sv[TP];
         float mx = -INFINITY;
 #pragma unroll
@@ -129,13 +169,17 @@ __global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_
                     a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[B][i][k]), __builtin_bit_cast(bf16x8, qf[k]), a, 0, 0, 0);
                 }
             }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                a[r] = j + 16 * i + 4 * lq + r < nk && j + 16 * i + 4 * lq + r < w1 ? a[r] * scale : -INFINITY;
-                mx = fmaxf(mx, a[r]);
-            }
-            sv[i] = a;
+            sv[i] = a * scale;
         }
+        if (edge) {
+#pragma unroll
+            for (int i = 0; i < TP; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (j + 16 * i + 4 * lq + r >= nk) sv[i][r] = -INFINITY;
+        }
+#pragma unroll
+        for (int i = 0; i < TP; ++i) mx = fmaxf(mx, fmaxf(fmaxf(sv[i][0], sv[i][1]), fmaxf(sv[i][2], sv[i][3])));
         mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
         const float m_new = fmaxf(m_run, mx), m_ref = m_new == -INFINITY ? 0.f : m_new;   // a column with no key yet stays empty
@@ -144,112 +188,129 @@ __global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_
         l_run *= alpha;
 #pragma unroll
         for (int dt = 0; dt < ND; ++dt) acc[dt] *= alpha;
-        // Positions past the wave's last key hold stale cache bits, which must not meet their zero
-        // probabilities (0 * NaN).  A later token of the group may hold infinities or NaN of its own:
-        // where columns differ in what they see, such a tile is added position by position below.
-        const bool diagonal = j + 16 * TP > free_keys;
 #pragma unroll
         for (int i = 0; i < TP; ++i) {
             f32x4 p, vf[ND];
 #pragma unroll
             for (int r = 0; r < 4; ++r) p[r] = expf(sv[i][r] - m_ref);
             l_run += (p[0] + p[1]) + (p[2] + p[3]);
-            const int nvalid = w1 - (j + 16 * i + 4 * lq);
-            bool odd = false;
 #pragma unroll
             for (int dt = 0; dt < ND; ++dt)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    float v;
-                    if constexpr (F32) v = vr[B][i][dt][r];
-                    else v = __uint_as_float(r & 1 ? vr[B][i][dt][r >> 1] & 0xffff0000u : vr[B][i][dt][r >> 1] << 16);
-                    vf[dt][r] = r < nvalid ? v : 0.f;
-                    if (diagonal) odd |= !(fabsf(vf[dt][r]) < INFINITY);
+                    if constexpr (F32) vf[dt][r] = vr[B][i][dt][r];
+                    else vf[dt][r] = __uint_as_float(r & 1 ? vr[B][i][dt][r >> 1] & 0xffff0000u : vr[B][i][dt][r >> 1] << 16);
                 }
-            if (__any(odd)) {
+            if (edge) {
+                // Positions past the group's last key hold stale cache bits, which must not meet their zero
+                // probabilities (0 * NaN).  A later token of the group may hold infinities or NaN of its own: as columns
+                // differ in what they see, such values are added position by position.
+                const int nvalid = w1 - (j + 16 * i + 4 * lq);
+                bool odd = false;
 #pragma unroll
                 for (int dt = 0; dt < ND; ++dt)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        for (int q = 0; q < 4; ++q) {
-                            const f32x4 one = __builtin_amdgcn_mfma_f32_16x16x4f32(lq == q ? vf[dt][r] : 0.f, p[r], acc[dt], 0, 0, 0);
-                            if (j + 16 * i + 4 * q + r < nk) acc[dt] = one;
-                        }
-            } else {
+                    for (int r = 0; r < 4; ++r) {
+                        vf[dt][r] = r < nvalid ? vf[dt][r] : 0.f;
+                        odd |= !(fabsf(vf[dt][r]) < INFINITY);
+                    }
+                if (__any(odd)) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
+                    for (int dt = 0; dt < ND; ++dt)
 #pragma unroll
-                    for (int dt = 0; dt < ND; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[dt][r], p[r], acc[dt], 0, 0, 0);
+                        for (int r = 0; r < 4; ++r)
+                            for (int q = 0; q < 4; ++q) {
+                                const f32x4 one = __builtin_amdgcn_mfma_f32_16x16x4f32(lq == q ? vf[dt][r] : 0.f, p[r], acc[dt], 0, 0, 0);
+                                if (j + 16 * i + 4 * q + r < nk) acc[dt] = one;
+                            }
+                    continue;
+                }
             }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int dt = 0; dt < ND; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[dt][r], p[r], acc[dt], 0, 0, 0);
         }
     };
     const std::integral_constant<int, 0> b0;
     const std::integral_constant<int, NBUF - 1> b1;
-    if constexpr (NBUF == 1) {
-        for (int j = w0; j < w1; j += 16 * TP) {
-            load(b0, j);
-            multiply(b0, j);
-        }
-    } else if (w0 < w1) {
-        load(b0, w0);
-        for (int j = w0; j < w1; j += 32 * TP) {
-            load(b1, j + 16 * TP);                                 // past the end: the last tile again, all masked
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(b0, j);
-            __builtin_amdgcn_sched_barrier(0);
-            load(b0, j + 32 * TP);
-            __builtin_amdgcn_sched_barrier(0);
-            if (j + 16 * TP < w1) multiply(b1, j + 16 * TP);
-            __builtin_amdgcn_sched_barrier(0);
+    if (w0 < w1) {
+        look_up(w0);
+        if constexpr (NBUF == 1) {
+            for (int j = w0; j < w1; j += 16 * TP) {
+                load(b0, j);
+                multiply(b0, j);
+            }
+        } else {
+            load(b0, w0);
+            for (int j = w0; j < w1; j += 32 * TP) {
+                load(b1, j + 16 * TP);                             // past the end: the last sub-tile again
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(b0, j);
+                __builtin_amdgcn_sched_barrier(0);
+                load(b0, j + 32 * TP);
+                __builtin_amdgcn_sched_barrier(0);
+                if (j + 16 * TP < w1) multiply(b1, j + 16 * TP);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     }
     l_run += __shfl_xor(l_run, 16, 64);
     l_run += __shfl_xor(l_run, 32, 64);
 
-    // a token whose keys fit one chunk is finished here (attn_combine_kernel leaves it alone)
-    if (single) {
-        const size_t pidx = ((size_t)t * sh.n_q + g * G) * sh.max_chunks + c;
-        const bool whole = n_keys <= ct;
-        if (lq == 0) { merge_ml[wave][lr][0] = m_run; merge_ml[wave][lr][1] = l_run; }
-        __syncthreads();
-        const float M = fmaxf(fmaxf(merge_ml[0][lr][0], merge_ml[1][lr][0]), fmaxf(merge_ml[2][lr][0], merge_ml[3][lr][0]));
-        const float mine = expf(m_run - (M == -INFINITY ? 0.f : M));
-        for (int round = 0; round < HD / MD; ++round) {
-            if (round) __syncthreads();
-#pragma unroll
-            for (int dt = 0; dt < ND; ++dt)
-                if (dt / (MD / 16) == round) *reinterpret_cast<f32x4 *>(&merge_o[wave][lr][(dt % (MD / 16)) * 16 + 4 * lq]) = acc[dt] * mine;
-            __syncthreads();
-            for (int u = threadIdx.x; u < G * MD; u += 256) {
-                const int h = u / MD, i = u % MD;
-                float Mh = -INFINITY, L = 0.f;
-#pragma unroll
-                for (int w = 0; w < 4; ++w) Mh = fmaxf(Mh, merge_ml[w][h][0]);
-#pragma unroll
-                for (int w = 0; w < 4; ++w) L += expf(merge_ml[w][h][0] - (Mh == -INFINITY ? 0.f : Mh)) * merge_ml[w][h][1];
-                const float o = ((merge_o[0][h][i] + merge_o[1][h][i]) + merge_o[2][h][i]) + merge_o[3][h][i];
-                const int d = round * MD + i;
-                if (whole) {
-                    out[(size_t)t * ld_out + (g * G + h) * HD + d] = from_f32<T>(o * (1.0f / L));
-                } else {
-                    part_o[(pidx + (size_t)h * sh.max_chunks) * HD + d] = o;
-                    if (d == 0) { part_ml[(pidx + (size_t)h * sh.max_chunks) * 2] = Mh; part_ml[(pidx + (size_t)h * sh.max_chunks) * 2 + 1] = L; }
-                }
-            }
-        }
-    } else if (live && col_keys > j0) {                            // the chunk exists for this column's token
-        const size_t pidx = ((size_t)tq * sh.n_q + g * G + col_head) * sh.max_chunks + c;
-        if (col_keys <= ct) {
+    if (!single) {                                                 // the wave's own columns are complete
+        if (col_keys <= j0) return;                                // dead column, or its token has no key in this chunk
+        const int tq = t + set0 + col_tok, h = g * G + col_head;
+        if (col_keys <= ct) {                                      // all keys in this chunk: finished (attn_combine_kernel leaves it alone)
             const float inv = 1.0f / l_run;
-            T *o = out + (size_t)tq * ld_out + (g * G + col_head) * HD + 4 * lq;
 #pragma unroll
-            for (int dt = 0; dt < ND; ++dt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) o[dt * 16 + r] = from_f32<T>(acc[dt][r] * inv);
+            for (int dt = 0; dt < ND; ++dt) store4(out + (size_t)tq * ld_out + h * HD + dt * 16 + 4 * lq, acc[dt] * inv);
         } else {
+            const size_t pidx = ((size_t)tq * sh.n_q + h) * sh.max_chunks + c;
 #pragma unroll
             for (int dt = 0; dt < ND; ++dt) *reinterpret_cast<f32x4 *>(part_o + pidx * HD + dt * 16 + 4 * lq) = acc[dt];
             if (lq == 0) { part_ml[pidx * 2] = m_run; part_ml[pidx * 2 + 1] = l_run; }
+        }
+        return;
+    }
+    // single token: merge of the four waves, in wave order; a token whose keys fit one chunk is finished here (attn_combine_kernel leaves it alone)
+    if (lq == 0) { merge_ml[wave][lr][0] = m_run; merge_ml[wave][lr][1] = l_run; }
+    __syncthreads();
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) M = fmaxf(M, merge_ml[w][lr][0]);
+    const float mine = expf(m_run - (M == -INFINITY ? 0.f : M));
+    for (int round = 0; round < HD / MD; ++round) {
+        if (round) __syncthreads();
+#pragma unroll
+        for (int dt = 0; dt < ND; ++dt)
+            if (dt / (MD / 16) == round) *reinterpret_cast<f32x4 *>(&merge_o[wave][lr][(dt % (MD / 16)) * 16 + 4 * lq]) = acc[dt] * mine;
+        if (round == 0 && lq == 0) merge_ml[wave][lr][1] = l_run * mine;
+        __syncthreads();
+        for (int u = threadIdx.x; u < G * (MD / 4); u += 256) {
+            const int col = u / (MD / 4), i = (u % (MD / 4)) * 4, h = g * G + col;
+            f32x4 o = *reinterpret_cast<const f32x4 *>(&merge_o[0][col][i]);
+            float L = merge_ml[0][col][1];
+#pragma unroll
+            for (int w = 1; w < 4; ++w) {
+                const f32x4 x = *reinterpret_cast<const f32x4 *>(&merge_o[w][col][i]);
+                o[0] += x[0]; o[1] += x[1]; o[2] += x[2]; o[3] += x[3];
+                L += merge_ml[w][col][1];
+            }
+            const int d = round * MD + i;
+            if (n_keys <= ct) {
+                store4(out + (size_t)t * ld_out + h * HD + d, o * (1.0f / L));
+            } else {
+                const size_t pidx = ((size_t)t * sh.n_q + h) * sh.max_chunks + c;
+                *reinterpret_cast<f32x4 *>(part_o + pidx * HD + d) = o;
+                if (d == 0) {
+                    float Mh = -INFINITY;
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) Mh = fmaxf(Mh, merge_ml[w][col][0]);
+                    part_ml[pidx * 2] = Mh;
+                    part_ml[pidx * 2 + 1] = L;
+                }
+            }
         }
     }
 }
@@ -523,7 +584,7 @@ hipError_t launch_attention_generic(int dtype, const void *qkv, const int32_t *s
     if (rows <= 0) return hipSuccess;
     const bool tile = attn_tile_supported(dtype, sh, k_cache, v_cache);
     if (tile) {
-        const dim3 grid((unsigned)((size_t)rows * sh.n_kv * sh.max_chunks));
+        const dim3 grid((unsigned)(((size_t)rows * sh.n_kv * sh.max_chunks + 7) / 8 * 8));     // whole eights of workgroups
         // positions per tile: two sub-tiles of 16 where a lane's K and V operands of both fit beside the
         // accumulators twice over, else one
 #define DYN_TILE(T, HD, TP) launch_attn_tile<T, HD, TP>(grid, s, qkv, seq_of_token, pos_of_token, block_table, k_cache, v_cache, out, ld_out, part_o, part_ml, sh, rows)
