@@ -124,16 +124,18 @@ __global__ __launch_bounds__(kF32Waves * 64) void gemm_f32_kernel(const float *_
     }
 }
 
-// Tile of an fp32 launch: 16 x 16 up to 16 rows (every column group its own workgroup: the launch is one
-// latency long), 64 x 64 where such tiles give every CU a workgroup, else 32 x 32.  max_rows bounds a
-// group's rows.
+// Tile of an fp32 launch: 16 x 16 up to 16 rows or while such tiles fit the CUs at once (the launch is one
+// workgroup long, and a workgroup's products take a time of their own: 24 rows x 1536 x 1024 13.5 us against
+// 17.6 with 32 x 32, x 1024 x 4096 24 against 37), 64 x 64 where such tiles give every CU a workgroup (225 rows x
+// 8192 x 1024 64 us, 73 with 32 x 32, 114 with 16 x 16), else 32 x 32 (x 1024 x 4096 41 us; 64 x 64: 109).  max_rows
+// bounds a group's rows.
 static hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const void *R, void *Y, int max_rows, int N, int K,
                                   const GemmGroups &gr, hipStream_t s) {
     const int groups = std::max(gr.n_groups, 1);
 #define DYN_F32(MT, NT)                                                                                                          \
     hipLaunchKernelGGL((gemm_f32_kernel<MT, NT>), dim3((N + NT - 1) / NT, (max_rows + MT - 1) / MT, groups), dim3(kF32Waves * 64), 0, s, \
                        (const float *)X, ldx, (const float *)W, (const float *)R, (float *)Y, max_rows, N, K, gr)
-    if (max_rows <= 16) DYN_F32(16, 16);
+    if (max_rows <= 16 || (long)((max_rows + 15) / 16) * ((N + 15) / 16) * groups <= 256) DYN_F32(16, 16);
     else if ((long)((max_rows + 63) / 64) * ((N + 63) / 64) * groups >= 256) DYN_F32(64, 64);
     else DYN_F32(32, 32);
 #undef DYN_F32
