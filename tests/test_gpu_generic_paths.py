@@ -44,7 +44,7 @@ def test_fp32_projections_at_tile_edges(rows, hidden, n_q, n_kv, hd, inter):
 
 
 def test_fp32_experts_with_empty_and_long_lists():
-    w = workload("f32_moe", "f32", 136, 2, 1, 32, 68, [(1, 3 + i % 9) for i in range(70)], experts=5, top_k=2)
+    w = workload("f32_moe", "f32", 132, 2, 1, 32, 68, [(1, 3 + i % 9) for i in range(70)], experts=5, top_k=2)
     data = gen.generate(w)
     data["weights"][0]["w_router"][3] = -4.0 * data["weights"][0]["w_router"][0]
     y, k, v = both_schedules(w, data)
@@ -134,3 +134,14 @@ def test_folded_launch_in_bands_matches_smaller_launches(rows):
     w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, 200, rows))
     data = gen.generate(w)
     both_schedules(w, data)
+
+
+@pytest.mark.parametrize("rows", [65, 129, 300, 500])
+def test_narrow_projections_on_lower_tiles_match_smaller_launches(rows):
+    """Outputs so narrow that their (n tile, plane) pairs leave CUs idle take lower tiles; the rows keep the bits they
+    have in a 40-row launch."""
+    w = workload("narrow", "bf16", 1024, 8, 2, 128, 2048, [(1, 1 + i % 7) for i in range(rows)], seed=70)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, 40, rows))
+    data = gen.generate(w)
+    y, k, v = both_schedules(w, data)
+    check_against_oracle(w, data, y, k, v)
