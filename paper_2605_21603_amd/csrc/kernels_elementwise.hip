@@ -7,8 +7,14 @@
 
 namespace dyn {
 
+// A row has the same bits whichever kernel its launch took, so what the compiler could contract either way
+// is written out: the rotation of a pair, and (below) the sums of squares.
+__device__ __forceinline__ float rotated_lo(float a, float b, float c, float s) { return __builtin_fmaf(a, c, -(b * s)); }
+__device__ __forceinline__ float rotated_hi(float a, float b, float c, float s) { return __builtin_fmaf(b, c, a * s); }
+
 // ------------------------------------------------------------------ RMSNorm
-// One 256-thread workgroup per row.  out = x * g / sqrt(mean(x^2) + eps).
+// One 256-thread workgroup per row.  out = x * g / sqrt(mean(x^2) + eps).  With few rows the launch is
+// one workgroup's latency long, so the row and the gains are loaded together, once.
 template <typename T>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const T *__restrict__ x, const T *__restrict__ g,
                                                       T *__restrict__ out, int ld_out, int H, float eps) {
@@ -19,24 +25,38 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const T *__restrict__ x, c
     const vec_t *gr = reinterpret_cast<const vec_t *>(g);
     vec_t *orow = reinterpret_cast<vec_t *>(out + row * ld_out);
     const int nv = H / V;
-    float ss = 0.f;
-    for (int i = threadIdx.x; i < nv; i += 256) {
-        vec_t v = xr[i];
+    constexpr int KEEP = 4;                    // vectors of the row and of g a thread keeps in registers, loaded together; beyond, both are read (again)
+    vec_t kept[KEEP], gain[KEEP];
 #pragma unroll
-        for (int e = 0; e < V; ++e) { float f = to_f32<T>(v[e]); ss += f * f; }
+    for (int n = 0; n < KEEP; ++n) {
+        const int i = threadIdx.x + n * 256;
+        if (i < nv) { kept[n] = xr[i]; gain[n] = gr[i]; }
     }
+    float ss = 0.f;
+    auto square = [&](const vec_t &v) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) { const float f = to_f32<T>(v[e]); ss = __builtin_fmaf(f, f, ss); }
+    };
+#pragma unroll
+    for (int n = 0; n < KEEP; ++n)
+        if (threadIdx.x + n * 256 < nv) square(kept[n]);
+    for (int i = threadIdx.x + KEEP * 256; i < nv; i += 256) square(xr[i]);
     ss = wave_sum(ss);
     __shared__ float part[4];
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
     __syncthreads();
     const float total = ((part[0] + part[1]) + part[2]) + part[3];
     const float r = 1.0f / sqrtf(total / (float)H + eps);
-    for (int i = threadIdx.x; i < nv; i += 256) {
-        vec_t v = xr[i], gv = gr[i], o;
+    auto scaled = [&](const vec_t &v, const vec_t &gv) {
+        vec_t o;
 #pragma unroll
         for (int e = 0; e < V; ++e) o[e] = from_f32<T>(to_f32<T>(v[e]) * r * to_f32<T>(gv[e]));
-        orow[i] = o;
-    }
+        return o;
+    };
+#pragma unroll
+    for (int n = 0; n < KEEP; ++n)
+        if (threadIdx.x + n * 256 < nv) orow[threadIdx.x + n * 256] = scaled(kept[n], gain[n]);
+    for (int i = threadIdx.x + KEEP * 256; i < nv; i += 256) orow[i] = scaled(xr[i], gr[i]);
 }
 
 hipError_t launch_rmsnorm(int dtype, const void *x, const void *g, void *out, int ld_out, int rows, int H, float eps,
@@ -110,7 +130,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_norm_kernel(const float *__re
         *reinterpret_cast<vec_t *>(Y + row * H + (size_t)i * 8) = v;
         if (n < KEEP) kept[n] = v;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) { const float f = bf2f(v[e]); ss += f * f; }
+        for (int e = 0; e < 8; ++e) { const float f = bf2f(v[e]); ss = __builtin_fmaf(f, f, ss); }
     }
     ss = wave_sum(ss);
     __shared__ float part[4];
@@ -177,7 +197,7 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(T *__restrict__ qkv, const
     const float red = (float)fma(-turns, 6.283185307179586, ang);
     float s, c;
     sincosf(red, &s, &c);
-    const T lo = from_f32<T>(a * c - b * s), hi = from_f32<T>(b * c + a * s);
+    const T lo = from_f32<T>(rotated_lo(a, b, c, s)), hi = from_f32<T>(rotated_hi(a, b, c, s));
     if (hh < sh.n_q) {                                   // q head, in place
         z[i] = lo;
         z[i + half] = hi;
@@ -231,8 +251,8 @@ __global__ __launch_bounds__(256) void rope_kv_vec_kernel(T *__restrict__ qkv, c
 #pragma unroll
         for (int e = 0; e < V; ++e) {
             const float c = cs[0][i0 + e], sn = cs[1][i0 + e], fa = to_f32<T>(a[e]), fb = to_f32<T>(b[e]);
-            lo[e] = from_f32<T>(fa * c - fb * sn);
-            hi[e] = from_f32<T>(fb * c + fa * sn);
+            lo[e] = from_f32<T>(rotated_lo(fa, fb, c, sn));
+            hi[e] = from_f32<T>(rotated_hi(fa, fb, c, sn));
         }
         T *dst = hh < sh.n_q ? z : k_cache + (((size_t)page * sh.n_kv + (hh - sh.n_q)) * sh.page_size + slot) * d;
         *reinterpret_cast<vec_t *>(dst + i0) = lo;
@@ -262,20 +282,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_rope_kernel(const float *__re
     __shared__ float cs[2][128];
     const int t = blockIdx.x;
     const int d = sh.head_dim, half = d >> 1;
-    const int pos = pos_of_token[t];
-    for (int i = threadIdx.x; i < half; i += 256) {
-        const double ang = (double)pos * tab.inv_freq[i];
-        const double turns = rint(ang * 0.15915494309189535);          // 1 / (2 pi)
-        const float red = (float)fma(-turns, 6.283185307179586, ang);
-        float sn, c;
-        sincosf(red, &sn, &c);
-        cs[0][i] = c;
-        cs[1][i] = sn;
-    }
-    const int page = block_table[(size_t)seq_of_token[t] * sh.max_pages_per_seq + pos / sh.page_size];
-    const int slot = pos % sh.page_size;
-    __syncthreads();
-    const int width = (sh.n_q + 2 * sh.n_kv) * d;
+    const int width = (sh.n_q + 2 * sh.n_kv) * d, vbase = (sh.n_q + sh.n_kv) * d;
     const float *prow = P + (size_t)t * width;
     bf16_t *row = qkv + (size_t)t * width;
     auto summed = [&](int col) {                           // eight consecutive columns of the row, planes added in order, rounded
@@ -310,29 +317,54 @@ __global__ __launch_bounds__(256) void gemm_reduce_rope_kernel(const float *__re
         for (int e = 0; e < 4; ++e) { v[e] = f2bf(a[e]); v[e + 4] = f2bf(b[e]); }
         return v;
     };
-    const int per_head = half / V, n_rot = (sh.n_q + sh.n_kv) * per_head;
+    // units: rotations of eight pairs of a q or k head, then eight head-dim indices of a v head.  A thread's first
+    // unit is summed before the angles are taken: the planes arrive beside the position, its page and the sines.
+    const int per_head = half / V, n_rot = (sh.n_q + sh.n_kv) * per_head, n_units = n_rot + sh.n_kv * d / V;
     const int first = blockIdx.y * 256 + threadIdx.x, step = gridDim.y * 256;
-    for (int u = first; u < n_rot; u += step) {
-        const int hh = u / per_head, i0 = (u % per_head) * V;
-        const vec_t a = summed(hh * d + i0), b = summed(hh * d + i0 + half);
-        vec_t lo, hi;
-#pragma unroll
-        for (int e = 0; e < V; ++e) {
-            const float c = cs[0][i0 + e], sn = cs[1][i0 + e], fa = bf2f(a[e]), fb = bf2f(b[e]);
-            lo[e] = f2bf(fa * c - fb * sn);
-            hi[e] = f2bf(fb * c + fa * sn);
+    auto sum_unit = [&](int u, vec_t &a, vec_t &b) {
+        if (u < n_rot) {
+            const int col = (u / per_head) * d + (u % per_head) * V;
+            a = summed(col);
+            b = summed(col + half);
+        } else if (u < n_units) {
+            a = summed(vbase + (u - n_rot) * V);
         }
-        bf16_t *dst = hh < sh.n_q ? row + hh * d : k_cache + (((size_t)page * sh.n_kv + (hh - sh.n_q)) * sh.page_size + slot) * d;
-        *reinterpret_cast<vec_t *>(dst + i0) = lo;
-        *reinterpret_cast<vec_t *>(dst + i0 + half) = hi;
+    };
+    vec_t a, b;
+    sum_unit(first, a, b);
+    const int pos = pos_of_token[t];
+    const int page = block_table[(size_t)seq_of_token[t] * sh.max_pages_per_seq + pos / sh.page_size];
+    const int slot = pos % sh.page_size;
+    for (int i = threadIdx.x; i < half; i += 256) {
+        const double ang = (double)pos * tab.inv_freq[i];
+        const double turns = rint(ang * 0.15915494309189535);          // 1 / (2 pi)
+        const float red = (float)fma(-turns, 6.283185307179586, ang);
+        float sn, c;
+        sincosf(red, &sn, &c);
+        cs[0][i] = c;
+        cs[1][i] = sn;
     }
-    const int vbase = (sh.n_q + sh.n_kv) * d;
-    for (int u = first; u < sh.n_kv * d / V; u += step) {               // v heads -> V page [kvh][d][slot], eight head-dim indices per thread
-        const vec_t v = summed(vbase + u * V);
-        const int g = (u * V) / d, i = (u * V) % d;
-        bf16_t *vp = v_cache + (((size_t)page * sh.n_kv + g) * d + i) * sh.page_size + slot;
+    __syncthreads();
+    for (int u = first; u < n_units; u += step) {
+        if (u != first) sum_unit(u, a, b);
+        if (u < n_rot) {
+            const int hh = u / per_head, i0 = (u % per_head) * V;
+            vec_t lo, hi;
 #pragma unroll
-        for (int e = 0; e < V; ++e) vp[(size_t)e * sh.page_size] = v[e];
+            for (int e = 0; e < V; ++e) {
+                const float c = cs[0][i0 + e], sn = cs[1][i0 + e], fa = bf2f(a[e]), fb = bf2f(b[e]);
+                lo[e] = f2bf(rotated_lo(fa, fb, c, sn));
+                hi[e] = f2bf(rotated_hi(fa, fb, c, sn));
+            }
+            bf16_t *dst = hh < sh.n_q ? row + hh * d : k_cache + (((size_t)page * sh.n_kv + (hh - sh.n_q)) * sh.page_size + slot) * d;
+            *reinterpret_cast<vec_t *>(dst + i0) = lo;
+            *reinterpret_cast<vec_t *>(dst + i0 + half) = hi;
+        } else {                                                       // v head -> V page [kvh][d][slot]
+            const int g = ((u - n_rot) * V) / d, i = ((u - n_rot) * V) % d;
+            bf16_t *vp = v_cache + (((size_t)page * sh.n_kv + g) * d + i) * sh.page_size + slot;
+#pragma unroll
+            for (int e = 0; e < V; ++e) vp[(size_t)e * sh.page_size] = a[e];
+        }
     }
 }
 
@@ -342,7 +374,9 @@ hipError_t launch_reduce_rope(const float *P, size_t plane_stride, int S, void *
                               const int32_t *pos_of_token, const int32_t *block_table, void *k_cache, void *v_cache,
                               const RopeTable &tab, const AttnShape &sh, int rows, hipStream_t s) {
     if (rows <= 0) return hipSuccess;
-    const dim3 grid(rows, rows < 512 ? 4 : 1);      // as the unfused kernel: a token's units over four workgroups when tokens are few
+    // a token's units over as many workgroups as give every thread one when tokens are few
+    const int units = (sh.n_q + sh.n_kv) * (sh.head_dim / 16) + sh.n_kv * sh.head_dim / 8;
+    const dim3 grid(rows, rows < 512 ? (units + 255) / 256 : 1);
 #define DYN_RR(SC) hipLaunchKernelGGL(gemm_reduce_rope_kernel<SC>, grid, dim3(256), 0, s, P, plane_stride, S, (bf16_t *)qkv, seq_of_token, \
                                       pos_of_token, block_table, (bf16_t *)k_cache, (bf16_t *)v_cache, tab, sh)
     switch (S) {
