@@ -48,6 +48,13 @@ __device__ __forceinline__ void mfma_acc(f32x4 &c, const bf16x8 &a, const bf16x8
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
 }
 
+// n tiles per band of a launch whose tiles cover the whole depth.  Eight bring an XCD's tiles of every shape
+// here to about as many W rows as X rows (32 or 64 tiles run on it at a time).  4096 rows, n-tile order -> bands
+// of 8 (4 and 16 lose 1-4 % of it): qkv 252 -> 208, o 183 -> 167, down 528 -> 470, gate/up 763 -> 753 us; 3000 rows: down
+// 449 -> 428 us; up to 2112 rows nothing changes.
+constexpr int kBand = 8;
+inline int gemm_band_grid(int n_tiles, int m_tiles) { return (n_tiles * m_tiles + 7) / 8 * 8; }
+
 // Tile of this workgroup in a launch whose tiles cover the whole depth, in bands.  Workgroup ids are dealt
 // round-robin to the 8 XCDs; an XCD takes a contiguous eighth of the tiles in an order that walks bands of
 // `band` n tiles down all m tiles, so that what it works on at one time is about as many W rows as X rows.

@@ -89,7 +89,7 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
 
 // Many rows, split-K planes folded in registers, 256 x 128 tiles (kernels_gemm_wide.hip; launch_gemm calls it).
 hipError_t launch_gemm_fold(int grid, hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N,
-                            int K, int S, int band);
+                            int K, int S);
 // Expert-grouped projection without planes on 256-wide tiles of a height chosen per expert (the grouped launchers
 // call it); gated: silu(gate) * up to Y, else Y, or fp32 to P with gr.force_planes.
 hipError_t launch_gemm_experts_wide(bool gated, hipStream_t s, const void *X, int ldx, const void *W, void *Y, int ldy, float *P, int N,

@@ -145,18 +145,23 @@ static hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const v
 // ------------------------------------------------------------------ bf16 MFMA path (gemm_tile.h)
 constexpr int kBigBN = 128, kBigMT = 128, kBigNS = 2;   // tile and ring depth of the many-row (matrix-core-bound) regime
 
+// The tiles that only GEMM_WIDE and GEMM_MANY launches use walk their tiles in bands; the others spread planes over
+// the grid in n-tile order.  (Decided at compile time: as an argument it cost the few-row launches 2 %.)
+constexpr bool gemm_in_bands(int bn, int nw) { return bn == 256 || nw == 4; }
+
 template <int BN, int MT, bool INREG, int NS, bool GATED, int NW>
 __global__ __launch_bounds__(NW * 64, (NW == 4 && (BN + MT) * ROWB * NS <= 72 * 1024) ? 2 : 1) void gemm_bf16_kernel(
     const bf16_t *__restrict__ X, int ldx, const bf16_t *__restrict__ W, const bf16_t *__restrict__ R,
     bf16_t *__restrict__ Y, int ldy, float *__restrict__ P, size_t plane_stride, int M, int N, int K, int S,
-    int band, GemmGroups gr) {
+    GemmGroups gr) {
+    constexpr bool BANDS = gemm_in_bands(BN, NW);      // whole-depth tiles of a many-row launch
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     const int m_tiles = (M + MT - 1) / MT;
     // Workgroup ids are dealt round-robin to the 8 XCDs.
     const int u = blockIdx.x % 8, v = blockIdx.x / 8;
     int m_tile, ns;
-    if (band) {
-        if (!band_tile(N / BN, m_tiles, band, ns, m_tile)) return;
+    if (BANDS) {
+        if (!band_tile(N / BN, m_tiles, kBand, ns, m_tile)) return;
     } else {
         // Tiles that share W rows (the m tiles of one (n tile, plane)) get ids 8 apart: same XCD,
         // same L2, adjacent in time.
@@ -195,7 +200,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && (BN + MT) * ROWB * NS <= 72 * 
 template <int BN, int MT, bool INREG, int NS, bool GATED = false, int NW = 4>
 hipError_t launch_gemm_bf16(int grid, hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y,
                             float *partial, size_t plane_stride, int rows, int N, int K, int S, const GemmGroups &gr,
-                            int ldy = 0, int band = 0) {
+                            int ldy = 0) {
     constexpr int STAGE = (BN + MT) * ROWB;
     static_assert(NS >= 2 && NS <= 6 && NS * STAGE <= 160 * 1024, "ring does not fit in LDS");
     static bool attr_set = false;                      // above 64 KB of dynamic LDS needs an opt-in, once
@@ -207,7 +212,7 @@ hipError_t launch_gemm_bf16(int grid, hipStream_t s, const void *X, int ldx, con
     }
     hipLaunchKernelGGL((gemm_bf16_kernel<BN, MT, INREG, NS, GATED, NW>), dim3(grid), dim3(NW * 64), NS * STAGE, s,
                        (const bf16_t *)X, ldx, (const bf16_t *)W, (const bf16_t *)R, (bf16_t *)Y, ldy ? ldy : N, partial,
-                       plane_stride, rows, N, K, S, band, gr);
+                       plane_stride, rows, N, K, S, gr);
     return hipGetLastError();
 }
 
@@ -445,13 +450,6 @@ bool gemm_uses_plane_buffer(int dtype, int rows, int N, int K) {
 }
 
 namespace {
-// n tiles per band of a launch whose tiles cover the whole depth (0: n-tile order, planes spread over the
-// grid).  Eight bands an XCD's tiles of every shape here to about as many W rows as X rows (32 or 64
-// tiles run on it at a time).  4096 rows, n-tile order -> bands of 8 (4 and 16 lose 1-4 % of it): qkv 252 -> 208,
-// o 183 -> 167, down 528 -> 470, gate/up 763 -> 753 us; 3000 rows: down 449 -> 428 us; up to 2112 rows nothing changes.
-int gemm_band(const GemmPath &p) { return p.kind == GEMM_WIDE || p.kind == GEMM_MANY ? 8 : 0; }
-int gemm_band_grid(int n_tiles, int m_tiles) { return (n_tiles * m_tiles + 7) / 8 * 8; }
-
 // The operator that follows the projection, as a kernel of its own on the rows the projection wrote.
 hipError_t run_epilogue(int dtype, const GemmEpilogue &ep, void *Y, int rows, int N, hipStream_t s) {
     if (ep.kind == GemmEpilogue::NORM) return launch_rmsnorm(dtype, Y, ep.g, ep.h_out, ep.ld_h, rows, N, ep.eps, s);
@@ -494,14 +492,13 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
     }
     const int S = p.split, m_tiles = (rows + p.mt - 1) / p.mt;
     // workgroup ids are dealt to the 8 XCDs in turn: tiles, or (n tile, plane) pairs, are padded to a multiple of 8
-    const int band = gemm_band(p);
-    const int grid = band ? gemm_band_grid(N / p.bn, m_tiles) : (((N / p.bn) * (p.folded ? 1 : S) + 7) / 8) * 8 * m_tiles;
+    const int grid = p.kind == GEMM_WIDE || p.kind == GEMM_MANY ? gemm_band_grid(N / p.bn, m_tiles) : (((N / p.bn) * (p.folded ? 1 : S) + 7) / 8) * 8 * m_tiles;
 #define DYN_GEMM(BN, MT, INREG, NS, NW) \
-    launch_gemm_bf16<BN, MT, INREG, NS, false, NW>(grid, s, X, ldx, W, R, Y, partial, plane_stride, rows, N, K, S, none, 0, band)
+    launch_gemm_bf16<BN, MT, INREG, NS, false, NW>(grid, s, X, ldx, W, R, Y, partial, plane_stride, rows, N, K, S, none)
     hipError_t e;
     if (p.kind == GEMM_TALL) e = p.mt == 256 ? DYN_GEMM(128, 256, false, 3, 8) : p.mt == 384 ? DYN_GEMM(128, 384, false, 2, 8) : DYN_GEMM(128, 512, false, 2, 8);
     else if (p.kind == GEMM_WIDE) e = DYN_GEMM(256, 256, false, 2, 8);
-    else if (p.kind == GEMM_MANY && p.bn == 256) e = launch_gemm_fold(grid, s, X, ldx, W, R, Y, rows, N, K, S, band);
+    else if (p.kind == GEMM_MANY && p.bn == 256) e = launch_gemm_fold(grid, s, X, ldx, W, R, Y, rows, N, K, S);
     else if (p.kind == GEMM_MANY && p.mt == 160) e = p.folded ? DYN_GEMM(kBigBN, 160, true, kBigNS, 4) : DYN_GEMM(kBigBN, 160, false, kBigNS, 4);
     else if (p.kind == GEMM_MANY) e = p.folded ? DYN_GEMM(kBigBN, kBigMT, true, kBigNS, 4) : DYN_GEMM(kBigBN, kBigMT, false, kBigNS, 4);
     else e = p.mt == 64 ? DYN_GEMM(128, 64, false, 4, 8) : DYN_GEMM(128, 128, false, 4, 8);
@@ -550,12 +547,12 @@ hipError_t launch_gemm_gated(const void *X, int ldx, const void *W, void *Y, int
     if (max_rows <= 0) return hipSuccess;
     hipError_t e;
 #define DYN_GATED(BN, MT, NS, NW) \
-    launch_gemm_bf16<BN, MT, false, NS, true, NW>(grid, s, X, ldx, W, nullptr, Y, nullptr, 0, max_rows, N2, K, 1, gr, ldy, band)
+    launch_gemm_bf16<BN, MT, false, NS, true, NW>(grid, s, X, ldx, W, nullptr, Y, nullptr, 0, max_rows, N2, K, 1, gr, ldy)
     const GroupTile t = gemm_group_tile(gr, max_rows, N2);
     if (gr.n_groups && t.bn == 256) {
         e = launch_gemm_experts_wide(true, s, X, ldx, W, Y, ldy, nullptr, N2, K, gr);
     } else if (gr.n_groups) {
-        const int band = 0, grid = ((((N2 / t.bn) * gr.n_groups) + 7) / 8) * 8 * ((max_rows + t.mt - 1) / t.mt);
+        const int grid = ((((N2 / t.bn) * gr.n_groups) + 7) / 8) * 8 * ((max_rows + t.mt - 1) / t.mt);
         e = t.mt == 256 ? DYN_GATED(128, 256, 3, 8) : t.mt == 64 ? DYN_GATED(128, 64, 4, 8) : DYN_GATED(128, 128, 4, 8);
     } else {
         const GemmPath p = gemm_path(1, max_rows, N2, K);          // split factor 1: no planes on any path
@@ -567,8 +564,8 @@ hipError_t launch_gemm_gated(const void *X, int ldx, const void *W, void *Y, int
             max_rows = head;
         }
         const int mt = p.kind == GEMM_MANY ? kBigMT : p.mt;    // the gated many-row kernel has 128-row tiles only
-        const int m_tiles = (max_rows + mt - 1) / mt, band = gemm_band(p);
-        const int grid = band ? gemm_band_grid(N2 / p.bn, m_tiles) : ((N2 / p.bn + 7) / 8) * 8 * m_tiles;
+        const int m_tiles = (max_rows + mt - 1) / mt;
+        const int grid = p.kind == GEMM_WIDE || p.kind == GEMM_MANY ? gemm_band_grid(N2 / p.bn, m_tiles) : ((N2 / p.bn + 7) / 8) * 8 * m_tiles;
         if (p.kind == GEMM_TALL) e = p.mt == 256 ? DYN_GATED(128, 256, 3, 8) : DYN_GATED(128, 384, 2, 8);
         else if (p.kind == GEMM_WIDE) e = DYN_GATED(256, 256, 2, 8);
         else if (p.kind == GEMM_MANY) e = DYN_GATED(kBigBN, kBigMT, kBigNS, 4);
