@@ -53,8 +53,10 @@ using dyn::g_err;
 struct Dispatch {
     int layer, op, nano, n_nano, r0, r1, stream, partition;
     bool any_multi;          // some sequence contributes more than one token to rows r0..r1
+    bool any_single = true;  // attention: some sequence contributes exactly one
     bool noop;               // launches nothing: no rows, or the gate when the projection's epilogue applied it
     std::vector<int> deps;   // dispatches (indices into the plan) whose output rows this one reads
+    bool plan = false;          // first norm: its launch also builds the attention work lists of its rows; attention: they have been built
     bool lists_ready = false;   // MoE down projection: the gate/up dispatch of the same rows already built its expert lists
     int key() const { return partition * DYN_MAX_STREAMS + stream; }
 };
@@ -343,7 +345,9 @@ dyn_status build_plan(const dyn_layer *L, const dyn_batch *b, const dyn_schedule
     for (int l = 0; l < L->cfg.n_layers; ++l)
         for (int i = 0; i < n_slots; ++i) {
             const dyn_slot &sl = slots[i];
-            Dispatch d{l, sl.op, sl.nano, sl.n_nano, rows[sl.nano], rows[sl.nano + sl.n_nano], sl.stream, sl.partition, false, false, {}};
+            Dispatch d{};
+            d.layer = l; d.op = sl.op; d.nano = sl.nano; d.n_nano = sl.n_nano; d.r0 = rows[sl.nano]; d.r1 = rows[sl.nano + sl.n_nano];
+            d.stream = sl.stream; d.partition = sl.partition;
             // Operators that launch nothing of their own: the SiLU gate where the gate/up projection's epilogue
             // applies it; rotary + cache append, which the qkv projection's dispatch applies to the rows it
             // wrote; the second norm, applied by the o projection's dispatch; and from the second layer on
@@ -355,6 +359,12 @@ dyn_status build_plan(const dyn_layer *L, const dyn_batch *b, const dyn_schedule
                 const int s0 = (int)(std::lower_bound(q, q + b->n_seqs + 1, d.r0) - q);
                 const int s1 = (int)(std::lower_bound(q, q + b->n_seqs + 1, d.r1) - q);
                 d.any_multi = d.r1 - d.r0 > s1 - s0;
+                if (sl.op == DYN_OP_ATTN && l == 0) {
+                    d.any_single = false;
+                    for (int i = s0; i < s1 && !d.any_single; ++i) d.any_single = q[i + 1] - q[i] == 1;
+                } else if (sl.op == DYN_OP_ATTN) {
+                    d.any_single = plan[i].any_single;      // every layer dispatches the same rows
+                }
             }
             const int pos = chain_pos[sl.op];
             for (int nb = sl.nano; nb < sl.nano + sl.n_nano; ++nb) {
@@ -365,6 +375,16 @@ dyn_status build_plan(const dyn_layer *L, const dyn_batch *b, const dyn_schedule
             }
             plan.push_back(std::move(d));
         }
+    // The attention work lists depend on the rows' sequences and positions only, and every layer walks the same
+    // ones: where the first layer's norm is dispatched over exactly the rows of an attention dispatch (which
+    // follows it in its micro-batches' chain), the norm's launch builds them beside its rows.  Otherwise the
+    // first layer's attention does.
+    for (int i = 0; i < n_slots; ++i) {
+        Dispatch &d = plan[i];
+        if (d.op != DYN_OP_ATTN || d.r1 <= d.r0) continue;
+        for (int j = 0; j < n_slots; ++j)
+            if (plan[j].op == DYN_OP_NORM1 && plan[j].r0 == d.r0 && plan[j].r1 == d.r1) plan[j].plan = d.plan = true;
+    }
     // The expert lists of a dispatch depend on its rows' routing only: a down projection over
     // exactly the rows of one gate/up dispatch (which it follows in its micro-batches' chain)
     // reads that dispatch's lists instead of building its own.
@@ -631,12 +651,18 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
             sh.n_cus += __builtin_popcount(s->cu_masks[(d.partition - 1) * s->cu_mask_words + i]);
     char *kc = b->k_cache_layers ? (char *)b->k_cache_layers[d.layer] : (char *)b->k_cache + (size_t)d.layer * b->kv_layer_stride;
     char *vc = b->v_cache_layers ? (char *)b->v_cache_layers[d.layer] : (char *)b->v_cache + (size_t)d.layer * b->kv_layer_stride;
+    int32_t *const plan = (int32_t *)(base + ws.plan) + (size_t)d.r0 * (ws.max_chunks + 2) * 4;   // attention work lists of these rows
     // the dispatch's own scratch: split-K planes of `rows` rows each
     float *const planes = (float *)(base + sc.planes);
     hipError_t err = hipSuccess;
     switch (d.op) {
         case DYN_OP_NORM1:
             if (fused_into_producer(d.op, d.layer)) break;       // the previous layer's down projection wrote h
+            if (d.plan && dyn::attention_mfma_supported(c.dtype, sh)) {
+                err = dyn::launch_norm_plan(rowp(x_in, H), w.g_norm1, (void *)rowp(base + ws.h, ws.ld_h), ws.ld_h, rows, H, c.rms_eps,
+                                            b->seq_of_token + d.r0, b->pos_of_token + d.r0, plan, sh, st);
+                break;
+            }
             err = dyn::launch_rmsnorm(c.dtype, rowp(x_in, H), w.g_norm1, (void *)rowp(base + ws.h, ws.ld_h), ws.ld_h, rows, H, c.rms_eps, st);
             break;
         case DYN_OP_QKV: {
@@ -659,8 +685,8 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
             err = dyn::launch_attention(c.dtype, rowp(base + ws.qkv, NQKV), b->seq_of_token + d.r0, b->pos_of_token + d.r0,
                                         b->block_table, kc, vc, (void *)rowp(base + ws.attn, ws.ld_attn), ws.ld_attn,
                                         (float *)(base + sc.part_o), (float *)(base + sc.part_ml),
-                                        (int32_t *)(base + ws.plan) + (size_t)d.r0 * (ws.max_chunks + 2) * 4, d.any_multi, sh, rows, st, mid, pre,
-                                        d.layer > 0);   // every layer dispatches the same row ranges: layer 0 built the work lists
+                                        plan, d.any_single, d.any_multi, sh, rows, st, mid, pre,
+                                        d.plan || d.layer > 0);   // every layer dispatches the same row ranges: layer 0 built the work lists
             break;
         case DYN_OP_OPROJ: {
             dyn::GemmEpilogue ep;                                 // the second norm of the rows just written
@@ -869,7 +895,7 @@ std::vector<unsigned char> graph_key(const dyn_batch *b, const dyn_schedule *s, 
         put(b->v_cache_layers, sizeof(void *) * n_layers);
     }
     for (const Dispatch &d : plan) {
-        const int f[] = {d.layer, d.op, d.r0, d.r1, d.stream, d.partition, d.any_multi, d.noop, d.lists_ready};
+        const int f[] = {d.layer, d.op, d.r0, d.r1, d.stream, d.partition, d.any_multi, d.any_single, d.noop, d.lists_ready, d.plan};
         put(f, sizeof f);
     }
     if (s->mode == DYN_SCHED_EXPLICIT && s->n_partitions > 0) {

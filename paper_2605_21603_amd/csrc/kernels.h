@@ -125,16 +125,26 @@ hipError_t launch_rope_kv(int dtype, void *qkv, const int32_t *seq_of_token, con
                           const int32_t *block_table, void *k_cache, void *v_cache, const RopeTable &tab,
                           const AttnShape &sh, int rows, hipStream_t s);
 
+// The attention work lists inside `plan` (scratch of (4 * max_chunks + 5) * rows + 4 int32 at most): single-token
+// sequences, multi-token sequences, and the chunk size every token's partials are indexed by.
+struct AttnPlan { int32_t *single, *multi, *ct_of_token; };
+AttnPlan attn_plan_lists(int32_t *plan, const AttnShape &sh, int rows);
+bool attention_mfma_supported(int dtype, const AttnShape &sh);      // the shapes whose attention walks these lists
+hipError_t launch_attn_plan(const int32_t *seq_of_token, const int32_t *pos_of_token, int32_t *plan, const AttnShape &sh, int rows, hipStream_t s);
+// The lists of some rows and the RMSNorm of the same rows (bf16) in one launch: neither needs the other.
+hipError_t launch_norm_plan(const void *x, const void *g, void *out, int ld_out, int rows, int H, float eps, const int32_t *seq_of_token,
+                            const int32_t *pos_of_token, int32_t *plan, const AttnShape &sh, hipStream_t s);
+
 // Causal paged attention for token rows; part_o / part_ml are the split-KV partial arrays
 // ([rows, n_q, max_chunks, head_dim] and [rows, n_q, max_chunks, 2]); plan is scratch for the
-// device-built work lists (2 * (2 + 2 * rows * max_chunks) int32); any_multi: some sequence has more
-// than one token in these rows (host knowledge; enables the wide-group launch).
+// device-built work lists (AttnPlan); any_single / any_multi: some sequence has one / more
+// than one token in these rows (host knowledge; whether the decode / the prefill form is launched).
 hipError_t launch_attention(int dtype, const void *qkv, const int32_t *seq_of_token, const int32_t *pos_of_token,
                             const int32_t *block_table, const void *k_cache, const void *v_cache, void *out, int ld_out,
-                            float *part_o, float *part_ml, int32_t *plan, bool any_multi, const AttnShape &sh,
+                            float *part_o, float *part_ml, int32_t *plan, bool any_single, bool any_multi, const AttnShape &sh,
                             int rows, hipStream_t s, hipEvent_t mid = nullptr,    // mid: recorded between the chunk kernel and the combine
                             hipEvent_t pre = nullptr,   // pre: recorded after the work-list kernel, before the chunk kernel
-                            bool plan_ready = false);   // `plan` already holds the lists of these rows (built by an earlier layer's call)
+                            bool plan_ready = false);   // `plan` already holds the lists of these rows (built by the first norm's launch or an earlier layer's call)
 
 // out[rows, I] = silu(gu[:, :I]) * gu[:, I:]
 hipError_t launch_silu_mul(int dtype, const void *gu, void *out, int ld_out, int rows, int I, hipStream_t s);

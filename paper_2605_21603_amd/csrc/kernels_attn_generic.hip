@@ -529,10 +529,11 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
     }
 }
 
-static hipError_t launch_combine(int dtype, bool base2, float *part_o, float *part_ml, const int32_t *pos_of_token,
-                                 const int32_t *ct_of_token, void *out, int ld_out, const AttnShape &sh, int rows, hipStream_t s,
-                                 int32_t *counter_reset, bool one_chunk_done) {
-    if (one_chunk_done && sh.max_chunks == 1) return hipSuccess;       // no token has anything to merge
+// one_chunk_done: the attention kernels finish tokens whose keys fit one chunk themselves.
+hipError_t launch_attention_combine(int dtype, bool base2, float *part_o, float *part_ml,
+                                    const int32_t *pos_of_token, const int32_t *ct_of_token, void *out, int ld_out,
+                                    const AttnShape &sh, int rows, hipStream_t s, int32_t *counter_reset, bool one_chunk_done) {
+    if (one_chunk_done && sh.max_chunks == 1 && !counter_reset) return hipSuccess;       // no token has anything to merge
     const int n_pairs = rows * sh.n_q;
     const dim3 grid((n_pairs + 7) / 8), block(256);
     if (sh.max_chunks > kMergeSegment) {       // some token may have that many chunks: first level of the merge
@@ -551,12 +552,6 @@ static hipError_t launch_combine(int dtype, bool base2, float *part_o, float *pa
         else hipLaunchKernelGGL((attn_combine_kernel<bf16_t, false>), grid, block, 0, s, part_o, part_ml, pos_of_token, ct_of_token, (bf16_t *)out, ld_out, sh, n_pairs, counter_reset, one_chunk_done);
     }
     return hipGetLastError();
-}
-
-hipError_t launch_attention_combine(int dtype, bool base2, float *part_o, float *part_ml,
-                                    const int32_t *pos_of_token, const int32_t *ct_of_token, void *out, int ld_out,
-                                    const AttnShape &sh, int rows, hipStream_t s, int32_t *counter_reset) {
-    return launch_combine(dtype, base2, part_o, part_ml, pos_of_token, ct_of_token, out, ld_out, sh, rows, s, counter_reset, false);
 }
 
 namespace {
@@ -616,7 +611,7 @@ hipError_t launch_attention_generic(int dtype, const void *qkv, const int32_t *s
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && mid) e = hipEventRecord(mid, s);
     if (e != hipSuccess) return e;
-    return launch_combine(dtype, false, part_o, part_ml, pos_of_token, nullptr, out, ld_out, sh, rows, s, nullptr, tile);
+    return launch_attention_combine(dtype, false, part_o, part_ml, pos_of_token, nullptr, out, ld_out, sh, rows, s, nullptr, tile);
 }
 
 }  // namespace dyn

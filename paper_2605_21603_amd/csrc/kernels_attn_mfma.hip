@@ -1,6 +1,6 @@
 // Paged attention for bf16 caches, head_dim 128, 16-position pages, decode form: the layer's
-// HBM-bound operator (the paper's memory-bound "decode attention", Section 2), plus the
-// device-side work lists shared with the prefill form (kernels_attn_prefill.hip).
+// HBM-bound operator (the paper's memory-bound "decode attention", Section 2).  The work lists it shares
+// with the prefill form (kernels_attn_prefill.hip) are kernels_attn_plan.hip's.
 //
 // A wave serves one token of a single-token sequence against one chunk (up to the handle's
 // chunk size, 256 positions by default; a sequence's chunks are of equal size up to rounding) of one kv head, all q heads of that kv head's group at once, so K and V are fetched once per kv
@@ -24,167 +24,16 @@ namespace dyn {
 
 hipError_t launch_attention_combine(int dtype, bool base2, float *part_o, float *part_ml,
                                     const int32_t *pos_of_token, const int32_t *ct_of_token, void *out, int ld_out,
-                                    const AttnShape &sh, int rows, hipStream_t s, int32_t *counter_reset);
-int attn_prefill_block_tokens(const AttnShape &sh);
+                                    const AttnShape &sh, int rows, hipStream_t s, int32_t *counter_reset, bool one_chunk_done);
 hipError_t launch_attention_prefill(const void *qkv, const int32_t *seq_of_token, const int32_t *pos_of_token,
-                                    const int32_t *block_table, const void *k_cache, const void *v_cache, float *part_o,
-                                    float *part_ml, const AttnShape &sh, int32_t *plan, long max_items, int max_groups,
+                                    const int32_t *block_table, const void *k_cache, const void *v_cache, void *out, int ld_out,
+                                    float *part_o, float *part_ml, const AttnShape &sh, int32_t *plan, long max_items, int max_groups,
                                     hipStream_t s);
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int HD = 128, PS = 16, TILE_PAGES = 2;
 constexpr int kPersistentGroups = 512;   // two 4-wave workgroups for each of the 256 CUs
-
-// Work lists, built on the device from the positions (contexts differ by 8x inside a batch, so
-// a dense token x max_chunks grid would be mostly empty workgroups).  A wave serves a query
-// group: tokens of one sequence whose positions fall in the same aligned block of `tg`
-// positions, all of them against one pass over the keys.  List 0 holds the tokens that are
-// alone in their sequence this step (decode: groups of one, 4 of 16 MFMA columns live), list 1
-// the tokens of multi-token sequences (prefill chunks) in query blocks of up to tg1 tokens, against
-// chunks of prefill_chunk_positions() positions (1024 unless the block reaches past 8192 keys).
-// One entry per (group, chunk) that exists: list[0] = number of entries, entry i =
-// (first token row, chunk | tokens << 20) at list[2 + 2 i].
-// List 0 is ordered by work, largest first: its entries are bucketed by their size in quarters of
-// the largest chunk (kPlanBuckets buckets; with the default chunk of 16 pages a quarter is one
-// tile pair of four pages) and inside a bucket they stay in token order, so the eight kv heads of a chunk and the chunks
-// of a sequence remain neighbours.  The persistent decode kernel deals the list out by wave index
-// in a snake (attn_mfma_kernel): with equal-sized items first and the small ones at the end, the
-// waves' totals differ by about one percent instead of six on contexts spread over 1024..8192.
-constexpr int kPlanBuckets = 4;
-
-__global__ __launch_bounds__(1024) void attn_plan_kernel(const int32_t *__restrict__ seq_of_token,
-                                                         const int32_t *__restrict__ pos_of_token, int rows, int ct,
-                                                         int tg1, int32_t *__restrict__ plan0,
-                                                         int32_t *__restrict__ plan1, int32_t *__restrict__ ct_of_token) {
-    // One workgroup of 16 waves walks the rows 1024 at a time.  A sequence's tokens are adjacent
-    // rows with consecutive positions, so a token leads its group iff it starts its sequence or
-    // its aligned block, and the group's size comes from a bisection over the look-ahead rows.
-    // Entry offsets come from a wave scan plus one LDS step per list (per bucket of list 0).
-    constexpr int NL = kPlanBuckets + 1;                    // scanned counters: list 0's buckets, then list 1
-    __shared__ int wave_tot[NL][16];
-    __shared__ int bucket_total[kPlanBuckets];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int chunk_pages = ct / PS, bucket_pages = max(1, (chunk_pages + kPlanBuckets - 1) / kPlanBuckets);
-
-    // What token row t contributes: which list, how many entries, and for list 0 the buckets of
-    // its chunks (all but the last have the sequence's balanced chunk size, the last the rest).
-    struct Row { int which, nc, n_tok, b_full, b_last; };
-    auto classify = [&](int t) {
-        Row r{0, 0, 0, 0, 0};
-        const int s = seq_of_token[t], p = pos_of_token[t];
-        const bool prev_same = t > 0 && seq_of_token[t - 1] == s, next_same = t + 1 < rows && seq_of_token[t + 1] == s;
-        r.which = prev_same || next_same;
-        const int tg = r.which ? tg1 : 1;
-        if (!prev_same || p % tg == 0) {                     // group leader
-            const int cand = tg - p % tg;                    // positions left in the aligned block
-            // rows t .. t + n_tok - 1 belong to the sequence: the matches form a prefix of the
-            // candidates, found by bisection (a few dependent cache hits instead of tg loads)
-            int lo = 1, hi = min(cand, rows - t);            // n_tok lies in [lo, hi]
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (seq_of_token[t + mid - 1] == s) lo = mid;
-                else hi = mid - 1;
-            }
-            r.n_tok = lo;
-            const int ctw = r.which ? prefill_chunk_positions((p / tg1 + 1) * tg1) : ct;
-            r.nc = (p + r.n_tok - 1 + ctw) / ctw;            // chunks the group's last token reaches
-            if (!r.which) {                                  // the decode kernel's own chunking of this sequence
-                const int seq_pages = (p + PS) / PS;         // ceil((p + 1) / PS)
-                const int cp = (seq_pages + r.nc - 1) / r.nc, last = seq_pages - (r.nc - 1) * cp;
-                r.b_full = max(0, kPlanBuckets - (cp + bucket_pages - 1) / bucket_pages);
-                r.b_last = max(0, kPlanBuckets - (last + bucket_pages - 1) / bucket_pages);
-            }
-        }
-        return r;
-    };
-
-    // pass 1: sizes of list 0's buckets
-    if (threadIdx.x < kPlanBuckets) bucket_total[threadIdx.x] = 0;
-    __syncthreads();
-    Row first_batch{0, 0, 0, 0, 0};                          // the first 1024 rows are classified once (most batches have no more)
-    for (int t = threadIdx.x; t < rows; t += 1024) {
-        const Row r = classify(t);
-        if (t < 1024) first_batch = r;
-        if (!r.which && r.nc > 0) {
-            if (r.nc > 1) atomicAdd(&bucket_total[r.b_full], r.nc - 1);
-            atomicAdd(&bucket_total[r.b_last], 1);
-        }
-    }
-    __syncthreads();
-    int base[NL];                                             // next free entry of each bucket / of list 1
-    base[0] = 0;
-#pragma unroll
-    for (int k = 1; k < kPlanBuckets; ++k) base[k] = base[k - 1] + bucket_total[k - 1];
-    const int total0 = base[kPlanBuckets - 1] + bucket_total[kPlanBuckets - 1];
-    base[kPlanBuckets] = 0;
-
-    // pass 2: entries, in token order inside each bucket
-    for (int t0 = 0; t0 < rows; t0 += 1024) {
-        const int t = t0 + threadIdx.x;
-        Row r{0, 0, 0, 0, 0};
-        if (t < rows) {
-            r = t0 == 0 ? first_batch : classify(t);
-            const int p = pos_of_token[t];
-            ct_of_token[t] = r.which ? prefill_chunk_positions((p / tg1 + 1) * tg1) : ct;   // the chunk size this token's partials are indexed by
-        }
-        int v[NL];                                            // this thread's entries per counter
-#pragma unroll
-        for (int k = 0; k < NL; ++k) v[k] = 0;
-        if (r.which) {
-            v[kPlanBuckets] = r.nc;
-        } else if (r.nc > 0) {
-#pragma unroll
-            for (int k = 0; k < kPlanBuckets; ++k) v[k] = (k == r.b_full ? r.nc - 1 : 0) + (k == r.b_last ? 1 : 0);
-        }
-        int incl[NL];                                         // inclusive wave scans
-#pragma unroll
-        for (int k = 0; k < NL; ++k) {
-            int x = v[k];
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int u = __shfl_up(x, off, 64);
-                if (lane >= off) x += u;
-            }
-            incl[k] = x;
-            if (lane == 63) wave_tot[k][wave] = x;
-        }
-        __syncthreads();
-        int start[NL];
-#pragma unroll
-        for (int k = 0; k < NL; ++k) {
-            int pre = 0, tot = 0;
-#pragma unroll
-            for (int w = 0; w < 16; ++w) {
-                if (w < wave) pre += wave_tot[k][w];
-                tot += wave_tot[k][w];
-            }
-            start[k] = base[k] + pre + incl[k] - v[k];
-            base[k] += tot;
-        }
-        if (r.which) {
-            for (int c = 0; c < r.nc; ++c) {
-                plan1[2 + 2 * (start[kPlanBuckets] + c)] = t;
-                plan1[3 + 2 * (start[kPlanBuckets] + c)] = c | (r.n_tok << 20);
-            }
-        } else if (r.nc > 0) {
-            int at_full = 0, at_last = 0;
-#pragma unroll
-            for (int k = 0; k < kPlanBuckets; ++k) {          // select without indexing the register arrays dynamically
-                if (k == r.b_full) at_full = start[k];
-                if (k == r.b_last) at_last = start[k] + (r.b_last == r.b_full ? r.nc - 1 : 0);
-            }
-            for (int c = 0; c + 1 < r.nc; ++c) {
-                plan0[2 + 2 * (at_full + c)] = t;
-                plan0[3 + 2 * (at_full + c)] = c | (1 << 20);
-            }
-            plan0[2 + 2 * at_last] = t;
-            plan0[3 + 2 * at_last] = (r.nc - 1) | (1 << 20);
-        }
-        __syncthreads();                                      // wave_tot is reused by the next batch
-    }
-    if (threadIdx.x == 0) { plan0[0] = total0; plan1[0] = base[kPlanBuckets]; plan1[1] = 0; }   // list sizes; list 1's work counter
-}
 
 // Persistent waves: in round k wave w of the launch takes (entry, kv head) pair k * n_waves + w,
 // in odd rounds k * n_waves + (n_waves - 1 - w): a snake over a list that is ordered largest first
@@ -211,6 +60,7 @@ __global__ __launch_bounds__(256, NQG == 1 ? 2 : 1) void attn_mfma_kernel(const 
                                                            const int32_t *__restrict__ block_table,
                                                            const bf16_t *__restrict__ k_cache,
                                                            const bf16_t *__restrict__ v_cache,
+                                                           bf16_t *__restrict__ out, int ld_out,
                                                            float *__restrict__ part_o, float *__restrict__ part_ml,
                                                            AttnShape sh, const int32_t *__restrict__ plan) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -373,7 +223,17 @@ __global__ __launch_bounds__(256, NQG == 1 ? 2 : 1) void attn_mfma_kernel(const 
             float l = l_run[q];
             l += __shfl_xor(l, 16, 64);
             l += __shfl_xor(l, 32, 64);
-            if (nk_cur[q] > cur.lp_first * PS) {                 // the chunk exists for this column's token
+            if (nk_cur[q] > 0 && cur.seq_pages <= sh.chunk_pages) {   // one chunk is all: finished here, the merge leaves the token alone
+                const float inv = 1.0f / l;
+                bf16_t *y = out + (size_t)(cur.t + q * TG + col_tok) * ld_out + (g_cur * G + col_head) * HD + 4 * lq;
+#pragma unroll
+                for (int dt = 0; dt < 8; ++dt) {
+                    u32x2 w;
+                    w[0] = (uint32_t)f2bf(acc[q][dt][0] * inv) | ((uint32_t)f2bf(acc[q][dt][1] * inv) << 16);
+                    w[1] = (uint32_t)f2bf(acc[q][dt][2] * inv) | ((uint32_t)f2bf(acc[q][dt][3] * inv) << 16);
+                    *reinterpret_cast<u32x2 *>(y + dt * 16) = w;
+                }
+            } else if (nk_cur[q] > cur.lp_first * PS) {          // the chunk exists for this column's token
                 const size_t pidx =
                     ((size_t)(cur.t + q * TG + col_tok) * sh.n_q + g_cur * G + col_head) * sh.max_chunks + cur.c;
 #pragma unroll
@@ -413,21 +273,16 @@ bool attention_mfma_supported(int dtype, const AttnShape &sh) {
 
 hipError_t launch_attention(int dtype, const void *qkv, const int32_t *seq_of_token, const int32_t *pos_of_token,
                             const int32_t *block_table, const void *k_cache, const void *v_cache, void *out, int ld_out,
-                            float *part_o, float *part_ml, int32_t *plan, bool any_multi, const AttnShape &sh, int rows,
+                            float *part_o, float *part_ml, int32_t *plan, bool any_single, bool any_multi, const AttnShape &sh, int rows,
                             hipStream_t s, hipEvent_t mid, hipEvent_t pre, bool plan_ready) {
     if (rows <= 0) return hipSuccess;
     if (!attention_mfma_supported(dtype, sh))
         return launch_attention_generic(dtype, qkv, seq_of_token, pos_of_token, block_table, k_cache, v_cache, out, ld_out,
                                         part_o, part_ml, sh, rows, s, mid);
-    // two work lists per dispatch: single-token sequences, multi-token sequences
-    int32_t *plan0 = plan, *plan1 = plan + 2 + 2 * (size_t)rows * sh.max_chunks;
-    int32_t *ct_of_token = plan + 4 + 4 * (size_t)rows * sh.max_chunks;
-    // The lists depend on the rows' sequences and positions only: the first layer of a forward
-    // builds them, the others walk them again (plan_ready).
-    if (!plan_ready)
-        hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(1024), 0, s, seq_of_token, pos_of_token, rows, sh.chunk_pages * PS,
-                           attn_prefill_block_tokens(sh), plan0, plan1, ct_of_token);
-    hipError_t e = hipGetLastError();
+    // two work lists per dispatch: single-token sequences, multi-token sequences.  They depend on the rows'
+    // sequences and positions only: the first layer of a forward builds them, the others walk them again.
+    const AttnPlan lists = attn_plan_lists(plan, sh, rows);
+    hipError_t e = plan_ready ? hipSuccess : launch_attn_plan(seq_of_token, pos_of_token, plan, sh, rows, s);
     if (e == hipSuccess && pre) e = hipEventRecord(pre, s);
     if (e != hipSuccess) return e;
     const long max_items = (long)rows * sh.n_kv * sh.max_chunks;
@@ -435,16 +290,18 @@ hipError_t launch_attention(int dtype, const void *qkv, const int32_t *seq_of_to
     // wave index): two per CU of the partition the stream runs on
     const int groups = sh.n_cus > 0 && 2 * sh.n_cus < kPersistentGroups ? 2 * sh.n_cus : kPersistentGroups;
     const int grid = (int)((max_items + 3) / 4 < groups ? (max_items + 3) / 4 : groups);
-    hipLaunchKernelGGL(attn_mfma_kernel<1>, dim3(grid), dim3(256), 0, s, (const bf16_t *)qkv, seq_of_token,
-                       pos_of_token, block_table, (const bf16_t *)k_cache, (const bf16_t *)v_cache, part_o, part_ml, sh,
-                       plan0);
-    e = hipGetLastError();
+    if (any_single) {
+        hipLaunchKernelGGL(attn_mfma_kernel<1>, dim3(grid), dim3(256), 0, s, (const bf16_t *)qkv, seq_of_token,
+                           pos_of_token, block_table, (const bf16_t *)k_cache, (const bf16_t *)v_cache, (bf16_t *)out, ld_out, part_o,
+                           part_ml, sh, lists.single);
+        e = hipGetLastError();
+    }
     if (e == hipSuccess && any_multi)
-        e = launch_attention_prefill(qkv, seq_of_token, pos_of_token, block_table, k_cache, v_cache, part_o, part_ml, sh,
-                                     plan1, max_items, groups, s);
+        e = launch_attention_prefill(qkv, seq_of_token, pos_of_token, block_table, k_cache, v_cache, out, ld_out, part_o, part_ml, sh,
+                                     lists.multi, max_items, groups, s);
     if (e == hipSuccess && mid) e = hipEventRecord(mid, s);
     if (e != hipSuccess) return e;
-    return launch_attention_combine(dtype, true, part_o, part_ml, pos_of_token, ct_of_token, out, ld_out, sh, rows, s, plan1 + 1);
+    return launch_attention_combine(dtype, true, part_o, part_ml, pos_of_token, lists.ct_of_token, out, ld_out, sh, rows, s, lists.multi + 1, true);
 }
 
 }  // namespace dyn

@@ -70,6 +70,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void attn_prefill_kernel(const bf16
                                                               const int32_t *__restrict__ block_table,
                                                               const bf16_t *__restrict__ k_cache,
                                                               const bf16_t *__restrict__ v_cache,
+                                                              bf16_t *__restrict__ out, int ld_out,
                                                               float *__restrict__ part_o, float *__restrict__ part_ml,
                                                               AttnShape sh, const int32_t *__restrict__ plan, int32_t *__restrict__ counter) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -369,7 +370,17 @@ __global__ __launch_bounds__(kWaves * 64, 1) void attn_prefill_kernel(const bf16
 
 #pragma unroll
         for (int q = 0; q < kSets; ++q) {
-            if (nk[q] > lp0 * PS) {                                       // the chunk exists for this column's token
+            if (nk[q] > 0 && nk[q] <= chunk_pages * PS) {                 // one chunk is all: finished here, the merge leaves the token alone
+                const float inv = 1.0f / acc_l[q][0];
+                bf16_t *y = out + (size_t)(t0 + wave_tok0 + q * TG + col_tok) * ld_out + (g * G + col_head) * HD + 4 * lq;
+#pragma unroll
+                for (int dt = 0; dt < 8; ++dt) {
+                    u32x2 w;
+                    w[0] = (uint32_t)f2bf(acc[q][dt][0] * inv) | ((uint32_t)f2bf(acc[q][dt][1] * inv) << 16);
+                    w[1] = (uint32_t)f2bf(acc[q][dt][2] * inv) | ((uint32_t)f2bf(acc[q][dt][3] * inv) << 16);
+                    *reinterpret_cast<u32x2 *>(y + dt * 16) = w;
+                }
+            } else if (nk[q] > lp0 * PS) {                                // the chunk exists for this column's token
                 const size_t pidx =
                     ((size_t)(t0 + wave_tok0 + q * TG + col_tok) * sh.n_q + g * G + col_head) * sh.max_chunks + c;
 #pragma unroll
@@ -387,8 +398,8 @@ __global__ __launch_bounds__(kWaves * 64, 1) void attn_prefill_kernel(const bf16
 int attn_prefill_block_tokens(const AttnShape &sh) { return kWaves * kSets * (16 / (sh.n_q / sh.n_kv)); }
 
 hipError_t launch_attention_prefill(const void *qkv, const int32_t *seq_of_token, const int32_t *pos_of_token,
-                                    const int32_t *block_table, const void *k_cache, const void *v_cache, float *part_o,
-                                    float *part_ml, const AttnShape &sh, int32_t *plan, long max_items, int max_groups,
+                                    const int32_t *block_table, const void *k_cache, const void *v_cache, void *out, int ld_out,
+                                    float *part_o, float *part_ml, const AttnShape &sh, int32_t *plan, long max_items, int max_groups,
                                     hipStream_t s) {
     static_assert(kPrefillChunkPagesMax <= kWaves * 64, "one thread per page id of a chunk");
     const int lds_bytes = kRing * kTile + (kPrefillChunkPagesMax + 4) * (int)sizeof(int32_t);   // ring, page ids of a chunk, the claimed item
@@ -400,7 +411,7 @@ hipError_t launch_attention_prefill(const void *qkv, const int32_t *seq_of_token
     }
     const int grid = (int)(max_items < max_groups ? max_items : max_groups);
     hipLaunchKernelGGL(attn_prefill_kernel, dim3(grid), dim3(kWaves * 64), lds_bytes, s, (const bf16_t *)qkv, seq_of_token,
-                       pos_of_token, block_table, (const bf16_t *)k_cache, (const bf16_t *)v_cache, part_o, part_ml, sh, plan,
+                       pos_of_token, block_table, (const bf16_t *)k_cache, (const bf16_t *)v_cache, (bf16_t *)out, ld_out, part_o, part_ml, sh, plan,
                        plan + 1);
     return hipGetLastError();
 }

@@ -4,6 +4,7 @@
 // fixed by the block shape, so results do not depend on how a batch is split.
 #include "common.h"
 #include "kernels.h"
+#include "norm_row.h"
 
 namespace dyn {
 
@@ -13,50 +14,13 @@ __device__ __forceinline__ float rotated_lo(float a, float b, float c, float s) 
 __device__ __forceinline__ float rotated_hi(float a, float b, float c, float s) { return __builtin_fmaf(b, c, a * s); }
 
 // ------------------------------------------------------------------ RMSNorm
-// One 256-thread workgroup per row.  out = x * g / sqrt(mean(x^2) + eps).  With few rows the launch is
-// one workgroup's latency long, so the row and the gains are loaded together, once.
+// One 256-thread workgroup per row (norm_row.h).
 template <typename T>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const T *__restrict__ x, const T *__restrict__ g,
                                                       T *__restrict__ out, int ld_out, int H, float eps) {
-    constexpr int V = 16 / sizeof(T);
-    typedef T vec_t __attribute__((ext_vector_type(V)));
-    const size_t row = blockIdx.x;
-    const vec_t *xr = reinterpret_cast<const vec_t *>(x + row * H);
-    const vec_t *gr = reinterpret_cast<const vec_t *>(g);
-    vec_t *orow = reinterpret_cast<vec_t *>(out + row * ld_out);
-    const int nv = H / V;
-    constexpr int KEEP = 4;                    // vectors of the row and of g a thread keeps in registers, loaded together; beyond, both are read (again)
-    vec_t kept[KEEP], gain[KEEP];
-#pragma unroll
-    for (int n = 0; n < KEEP; ++n) {
-        const int i = threadIdx.x + n * 256;
-        if (i < nv) { kept[n] = xr[i]; gain[n] = gr[i]; }
-    }
-    float ss = 0.f;
-    auto square = [&](const vec_t &v) {
-#pragma unroll
-        for (int e = 0; e < V; ++e) { const float f = to_f32<T>(v[e]); ss = __builtin_fmaf(f, f, ss); }
-    };
-#pragma unroll
-    for (int n = 0; n < KEEP; ++n)
-        if (threadIdx.x + n * 256 < nv) square(kept[n]);
-    for (int i = threadIdx.x + KEEP * 256; i < nv; i += 256) square(xr[i]);
-    ss = wave_sum(ss);
     __shared__ float part[4];
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
-    __syncthreads();
-    const float total = ((part[0] + part[1]) + part[2]) + part[3];
-    const float r = 1.0f / sqrtf(total / (float)H + eps);
-    auto scaled = [&](const vec_t &v, const vec_t &gv) {
-        vec_t o;
-#pragma unroll
-        for (int e = 0; e < V; ++e) o[e] = from_f32<T>(to_f32<T>(v[e]) * r * to_f32<T>(gv[e]));
-        return o;
-    };
-#pragma unroll
-    for (int n = 0; n < KEEP; ++n)
-        if (threadIdx.x + n * 256 < nv) orow[threadIdx.x + n * 256] = scaled(kept[n], gain[n]);
-    for (int i = threadIdx.x + KEEP * 256; i < nv; i += 256) orow[i] = scaled(xr[i], gr[i]);
+    const size_t row = blockIdx.x;
+    rmsnorm_row<T>(x + row * H, g, out + row * ld_out, H, eps, threadIdx.x, part, true);
 }
 
 hipError_t launch_rmsnorm(int dtype, const void *x, const void *g, void *out, int ld_out, int rows, int H, float eps,

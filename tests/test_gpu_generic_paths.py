@@ -145,3 +145,21 @@ def test_narrow_projections_on_lower_tiles_match_smaller_launches(rows):
     data = gen.generate(w)
     y, k, v = both_schedules(w, data)
     check_against_oracle(w, data, y, k, v)
+
+
+def test_work_lists_of_more_rows_than_are_kept_in_registers():
+    """4900 rows (the lists' kernel keeps 4096 rows' classification): decodes and two prompts, one past row 4096, with the
+    bits of the same rows in smaller dispatches, whether the norm's launch builds the lists or the attention's does."""
+    seqs = [(1, 1 + (i * 7) % 600) for i in range(3900)] + [(500, 1300)] + [(1, 1 + i % 40) for i in range(200)] + [(300, 300)]
+    w = workload("rows", "bf16", 128, 2, 1, 128, 128, seqs, seed=80)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, 3900, 4400, 4900))
+    data = gen.generate(w)
+    run = GpuRun(w, data)
+    y, _, _ = run.run(B.sequential())
+    for merged in ((), (B.DYN_OP_NORM1, B.DYN_OP_QKV, B.DYN_OP_ROPE_KV)):       # lists beside each part's norm; one norm for all, lists by the attention
+        y1, _, _ = run.run(B.nano_schedule(w.nano_rows, merged_ops=merged))
+        assert torch.equal(y.view(torch.uint8), y1.view(torch.uint8))
+    sub, d2 = gen.sub_batch(w, data, [0, 77, 3899, 3900, 3950, len(seqs) - 1])
+    y2, k2, v2 = GpuRun(sub, d2).run(B.sequential())
+    assert torch.equal(y2, y[torch.as_tensor(d2["rows"])])
+    assert torch.isfinite(y.float()).all()
