@@ -342,33 +342,42 @@ __global__ __launch_bounds__(64) void attn_generic_kernel(const T *__restrict__ 
     __syncthreads();
 
     const float scale = 1.0f / sqrtf((float)d);
-    float mx = -INFINITY;
-    for (int j = j0 + lane; j < j1; j += 64) {
+    const auto score = [&](int j) {
         const T *kr = k_cache + (((size_t)bt[j / ps] * sh.n_kv + g) * ps + j % ps) * d;
         float acc = 0.f;
         for (int i = 0; i < d; ++i) acc += qs[i] * to_f32<T>(kr[i]);
-        acc *= scale;
-        sc[j - j0] = acc;
-        mx = fmaxf(mx, acc);
+        return acc * scale;
+    };
+    // A chunk may hold more positions than sc: its first kMaxChunkTokens scores are kept from the maximum's
+    // pass, those of later blocks are computed again and their values added to the partial by the lane that wrote it.
+    float mx = -INFINITY;
+    for (int j = j0 + lane; j < j1; j += 64) {
+        const float x = score(j);
+        if (j - j0 < kMaxChunkTokens) sc[j - j0] = x;
+        mx = fmaxf(mx, x);
     }
     mx = wave_max(mx);
     float sum = 0.f;
-    for (int j = j0 + lane; j < j1; j += 64) {
-        const float p = expf(sc[j - j0] - mx);
-        sc[j - j0] = p;
-        sum += p;
+    const size_t pidx = ((size_t)t * sh.n_q + h) * sh.max_chunks + c;
+    for (int b0 = j0; b0 < j1; b0 += kMaxChunkTokens) {
+        const int b1 = min(b0 + kMaxChunkTokens, j1);
+        if (b0 > j0) __syncthreads();                   // the last block's probabilities have been read
+        for (int j = b0 + lane; j < b1; j += 64) {
+            const float p = expf((b0 == j0 ? sc[j - b0] : score(j)) - mx);
+            sc[j - b0] = p;
+            sum += p;
+        }
+        __syncthreads();
+        for (int i = lane; i < d; i += 64) {
+            float acc = b0 == j0 ? 0.f : part_o[pidx * d + i];
+            for (int j = b0; j < b1; ++j) {
+                const T *vr = v_cache + (((size_t)bt[j / ps] * sh.n_kv + g) * d + i) * ps + j % ps;
+                acc += sc[j - b0] * to_f32<T>(*vr);
+            }
+            part_o[pidx * d + i] = acc;
+        }
     }
     sum = wave_sum(sum);
-    __syncthreads();
-    const size_t pidx = ((size_t)t * sh.n_q + h) * sh.max_chunks + c;
-    for (int i = lane; i < d; i += 64) {
-        float acc = 0.f;
-        for (int j = j0; j < j1; ++j) {
-            const T *vr = v_cache + (((size_t)bt[j / ps] * sh.n_kv + g) * d + i) * ps + j % ps;
-            acc += sc[j - j0] * to_f32<T>(*vr);
-        }
-        part_o[pidx * d + i] = acc;
-    }
     if (lane == 0) {
         part_ml[pidx * 2] = mx;
         part_ml[pidx * 2 + 1] = sum;

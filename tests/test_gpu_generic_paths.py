@@ -163,3 +163,15 @@ def test_work_lists_of_more_rows_than_are_kept_in_registers():
     y2, k2, v2 = GpuRun(sub, d2).run(B.sequential())
     assert torch.equal(y2, y[torch.as_tensor(d2["rows"])])
     assert torch.isfinite(y.float()).all()
+
+
+# the general attention kernel keeps 512 scores: chunks of one block, of a block and one position, of several
+@pytest.mark.parametrize("dtype,hd,page,chunk", [("f32", 16, 16, 512), ("f32", 16, 16, 1024), ("f32", 8, 24, 2040), ("bf16", 64, 24, 1032)])
+def test_general_attention_with_chunks_longer_than_its_scores(dtype, hd, page, chunk):
+    w = workload("long_chunk", dtype, 128, 2, 1, hd, 128, [(1, 512), (1, 513), (1, 1025), (3, 1500), (1, 2100), (1, 1)], page=page, seed=90)
+    data = gen.generate(w)
+    run = GpuRun(w, data, kv_chunk_positions=chunk)
+    y, k, v = run.run(B.sequential())
+    y1, _, _ = run.run(B.nano_schedule(w.nano_rows))
+    assert torch.equal(y.view(torch.uint8), y1.view(torch.uint8))
+    say("%s %d %d: %.2e" % (dtype, hd, chunk, check_against_oracle(w, data, y, k, v)))
