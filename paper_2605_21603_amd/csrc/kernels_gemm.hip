@@ -490,6 +490,12 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
         if (et != hipSuccess) return et;
         rows = head;
     }
+    if (gemm_rows16_supported(rows, p.split)) {
+        hipError_t er = launch_gemm_rows16(s, X, ldx, W, R, Y, rows, N, K, p.split);
+        if (er == hipSuccess && mid) er = hipEventRecord(mid, s);
+        if (er == hipSuccess && has_ep) er = run_epilogue(dtype, *ep, Y, rows, N, s);
+        return er;
+    }
     const int S = p.split, m_tiles = (rows + p.mt - 1) / p.mt;
     // workgroup ids are dealt to the 8 XCDs in turn: tiles, or (n tile, plane) pairs, are padded to a multiple of 8
     const int grid = p.kind == GEMM_WIDE || p.kind == GEMM_MANY ? gemm_band_grid(N / p.bn, m_tiles) : (((N / p.bn) * (p.folded ? 1 : S) + 7) / 8) * 8 * m_tiles;

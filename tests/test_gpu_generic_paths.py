@@ -175,3 +175,14 @@ def test_general_attention_with_chunks_longer_than_its_scores(dtype, hd, page, c
     y1, _, _ = run.run(B.nano_schedule(w.nano_rows))
     assert torch.equal(y.view(torch.uint8), y1.view(torch.uint8))
     say("%s %d %d: %.2e" % (dtype, hd, chunk, check_against_oracle(w, data, y, k, v)))
+
+
+# planes summed inside the workgroup up to 8 rows: 2, 4 and 8 planes of 8 (the fewest there are), 12, 15, 16 and 19 stages; loads run 8 stages ahead
+@pytest.mark.parametrize("hidden,n_q,n_kv,hd,inter", [(1024, 16, 4, 64, 3072), (2048, 16, 4, 128, 7680), (3072, 24, 8, 128, 8192), (3072, 24, 8, 128, 9728)])
+@pytest.mark.parametrize("rows", [1, 7, 8, 9])
+def test_few_rows_match_the_bits_of_larger_launches(rows, hidden, n_q, n_kv, hd, inter):
+    w = workload("few_rows", "bf16", hidden, n_q, n_kv, hd, inter, [(1, 1 + (i * 31) % 300) for i in range(21)], seed=95)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, rows, 21))
+    data = gen.generate(w)
+    y, k, v = both_schedules(w, data)
+    check_against_oracle(w, data, y, k, v)
