@@ -99,4 +99,14 @@ __host__ __device__ inline int prefill_chunk_positions(int reach) {
 }
 constexpr int kPrefillChunkPagesMax = 8192 / 16;     // in 16-position pages
 
+// What a work item does with one of its columns (a token and a q head).  nk: keys the column attends (0: a dead
+// column); the item's chunk is the `chunk` positions from `first`, a multiple of `chunk`.  The item of a
+// block's later chunk may hold tokens whose keys all lie before it (a block of 16 * (16 / G) positions, 80 at G = 3,
+// need not divide the chunk): those are some other item's to write.
+enum ColumnEnd { COLUMN_NOT_MINE, COLUMN_DONE, COLUMN_PARTIAL };
+__host__ __device__ inline ColumnEnd column_end(int nk, int first, int chunk) {
+    if (nk <= first) return COLUMN_NOT_MINE;
+    return nk <= chunk ? COLUMN_DONE : COLUMN_PARTIAL;       // one chunk is all: the item writes the output, the merge leaves the token alone
+}
+
 }  // namespace dyn

@@ -259,9 +259,10 @@ __global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_
     l_run += __shfl_xor(l_run, 32, 64);
 
     if (!single) {                                                 // the wave's own columns are complete
-        if (col_keys <= j0) return;                                // dead column, or its token has no key in this chunk
+        const ColumnEnd end = column_end(col_keys, j0, ct);
+        if (end == COLUMN_NOT_MINE) return;
         const int tq = t + set0 + col_tok, h = g * G + col_head;
-        if (col_keys <= ct) {                                      // all keys in this chunk: finished (attn_combine_kernel leaves it alone)
+        if (end == COLUMN_DONE) {
             const float inv = 1.0f / l_run;
 #pragma unroll
             for (int dt = 0; dt < ND; ++dt) store4(out + (size_t)tq * ld_out + h * HD + dt * 16 + 4 * lq, acc[dt] * inv);

@@ -370,7 +370,9 @@ __global__ __launch_bounds__(kWaves * 64, 1) void attn_prefill_kernel(const bf16
 
 #pragma unroll
         for (int q = 0; q < kSets; ++q) {
-            if (nk[q] > 0 && nk[q] <= chunk_pages * PS) {                 // one chunk is all: finished here, the merge leaves the token alone
+            const ColumnEnd end = column_end(nk[q], lp0 * PS, chunk_pages * PS);
+            if (end == COLUMN_NOT_MINE) continue;
+            if (end == COLUMN_DONE) {
                 const float inv = 1.0f / acc_l[q][0];
                 bf16_t *y = out + (size_t)(t0 + wave_tok0 + q * TG + col_tok) * ld_out + (g * G + col_head) * HD + 4 * lq;
 #pragma unroll
@@ -380,7 +382,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void attn_prefill_kernel(const bf16
                     w[1] = (uint32_t)f2bf(acc[q][dt][2] * inv) | ((uint32_t)f2bf(acc[q][dt][3] * inv) << 16);
                     *reinterpret_cast<u32x2 *>(y + dt * 16) = w;
                 }
-            } else if (nk[q] > lp0 * PS) {                                // the chunk exists for this column's token
+            } else {
                 const size_t pidx =
                     ((size_t)(t0 + wave_tok0 + q * TG + col_tok) * sh.n_q + g * G + col_head) * sh.max_chunks + c;
 #pragma unroll

@@ -1,0 +1,63 @@
+"""Which work item of the block attention kernels writes which token (no GPU).
+
+The kernels ask column_end (csrc/common.h) what an item does with each of its columns.  Here the rule is compiled for
+the host and walked over every (block, chunk) item of a prompt: a token whose keys fit one chunk has its output written
+by exactly one item, any other token has exactly one partial per chunk it reaches, and nothing else is written."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+WALK = r"""
+#include <cstdio>
+#include <vector>
+#include "common.h"
+using namespace dyn;
+// Tokens p0 .. p1 - 1 of one sequence in aligned blocks of `tg` positions; a block's chunk size is chunk_of(block),
+// its items are the chunks its last token reaches (kernels_attn_plan.hip, attn_tile_kernel).
+template <class F> static long wrong(int p0, int p1, int tg, F chunk_of) {
+    std::vector<int> done(p1, 0), partial(p1, 0), chunk(p1, 0);
+    for (int p = p0; p < p1;) {
+        const int end = p + tg - p % tg < p1 ? p + tg - p % tg : p1, ct = chunk_of((p / tg + 1) * tg);
+        for (int c = 0; c * ct < end; ++c)
+            for (int t = p; t < end; ++t) {
+                chunk[t] = ct;
+                const ColumnEnd e = column_end(t + 1, c * ct, ct);
+                done[t] += e == COLUMN_DONE;
+                partial[t] += e == COLUMN_PARTIAL;
+            }
+        p = end;
+    }
+    long bad = 0;
+    for (int t = p0; t < p1; ++t) {
+        const int chunks = (t + chunk[t]) / chunk[t];
+        bad += done[t] != (chunks == 1) || partial[t] != (chunks == 1 ? 0 : chunks);
+    }
+    return bad;
+}
+int main() {
+    long bad = 0;
+    for (int G = 1; G <= 16; ++G) {
+        const int TG = 16 / G;
+        for (int p0 : {0, 1, 959, 1000}) {
+            bad += wrong(p0, 20000, 16 * TG, [](int reach) { return prefill_chunk_positions(reach); });
+            for (int ct : {64, 240, 256, 1024}) bad += wrong(p0, 3000, 4 * TG, [ct](int) { return ct; });
+        }
+    }
+    for (int nk : {0, -1}) bad += column_end(nk, 0, 64) != COLUMN_NOT_MINE;      // dead columns
+    printf("%ld\n", bad);
+}
+"""
+
+
+def test_every_token_is_written_once_whatever_the_block_and_chunk(tmp_path):
+    if not os.path.exists(HIPCC):
+        pytest.skip("no ROCm toolchain")
+    src, exe = tmp_path / "walk.cpp", tmp_path / "walk"
+    src.write_text(WALK)
+    subprocess.check_call([HIPCC, "-x", "hip", "--cuda-host-only", "-std=c++17", "-O1", "-I" + os.path.join(ROOT, "paper_2605_21603_amd", "csrc"),
+                           str(src), "-o", str(exe)], stderr=subprocess.DEVNULL)
+    assert int(subprocess.check_output([str(exe)], text=True)) == 0

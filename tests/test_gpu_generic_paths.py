@@ -186,3 +186,13 @@ def test_few_rows_match_the_bits_of_larger_launches(rows, hidden, n_q, n_kv, hd,
     data = gen.generate(w)
     y, k, v = both_schedules(w, data)
     check_against_oracle(w, data, y, k, v)
+
+
+# query blocks of 80 (G = 3), 48 (G = 5), 32 (G = 7) and 16 (G = 11) positions: the first two do not divide a chunk of 1024,
+# so the block across position 1024 has tokens without a key in its second chunk
+@pytest.mark.parametrize("n_q,n_kv", [(3, 1), (5, 1), (6, 2), (7, 1), (11, 1)])
+def test_prompts_across_the_first_chunk_with_blocks_that_do_not_divide_it(n_q, n_kv):
+    w = workload("straddle", "bf16", 128, n_q, n_kv, 128, 128, [(1100, 1100), (1, 70), (90, 1060), (3, 1025), (2, 1024), (200, 2150), (1, 1030)], seed=97)
+    data = gen.generate(w)
+    y, k, v = both_schedules(w, data)
+    say("%d/%d: %.2e" % (n_q, n_kv, check_against_oracle(w, data, y, k, v)))
