@@ -81,7 +81,9 @@ typedef struct {
                                   schedule of a handle gives the same bits).  Small chunks give few sequences enough
                                   work items to fill the chip; large ones write fewer partials and switch items less
                                   often (32 layers at batch 256, contexts 1024..8192: 256 -> 2048 positions takes 4.5 %
-                                  off the layer; batch 128, contexts 512..4096: 1024 is 1 % faster, 2048 5 % slower) */
+                                  off the layer; batch 128, contexts 512..4096: 1024 is 1 % faster, 2048 5 % slower).
+                                  Sequences of several tokens are cut by a rule of their own (1024 positions,
+                                  more behind 8192 cached ones) whatever this says */
 } dyn_layer_config;
 
 /* One entry per layer (array of n_layers). */

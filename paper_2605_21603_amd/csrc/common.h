@@ -98,6 +98,16 @@ __host__ __device__ inline int prefill_chunk_positions(int reach) {
     return ct;
 }
 constexpr int kPrefillChunkPagesMax = 8192 / 16;     // in 16-position pages
+// The most chunks a token with at most `positions` keys can have under that rule: a chunk size below 8192 is taken up to
+// eight chunks' reach only.
+__host__ __device__ inline int prefill_max_chunks(long positions) {
+    long most = 1;
+    for (long ct = 1024; ct <= 8192; ct *= 2) {
+        const long keys = ct < 8192 && positions > 8 * ct ? 8 * ct : positions;
+        if ((keys + ct - 1) / ct > most) most = (keys + ct - 1) / ct;
+    }
+    return (int)most;
+}
 
 // What a work item does with one of its columns (a token and a q head).  nk: keys the column attends (0: a dead
 // column); the item's chunk is the `chunk` positions from `first`, a multiple of `chunk`.  The item of a

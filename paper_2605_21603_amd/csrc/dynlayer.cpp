@@ -130,7 +130,8 @@ struct Sizes {                  // bytes of each whole-batch tensor, and the row
     int ld_h, ld_attn, ld_act, max_chunks;
 };
 
-Sizes tensor_sizes(const dyn_layer *L, int T, int max_pages) {
+// prompts: the batch has, or may have, a sequence of several tokens
+Sizes tensor_sizes(const dyn_layer *L, int T, int max_pages, bool prompts) {
     const dyn_layer_config &c = L->cfg;
     const size_t e = esize(c), t = (size_t)std::max(T, 0);
     const int pairs = c.n_experts ? c.top_k : 1;
@@ -143,6 +144,11 @@ Sizes tensor_sizes(const dyn_layer *L, int T, int max_pages) {
     z.ld_attn = c.n_q_heads * c.head_dim + pad;
     z.ld_act = c.mlp_inter + pad;
     z.max_chunks = std::max(1, (std::max(max_pages, 1) + L->chunk_pages - 1) / L->chunk_pages);
+    // The bf16 prompt kernel cuts by a rule of its own, which makes more chunks than a handle's larger than 1024
+    // positions; partials and lists have one stride for all tokens.
+    const dyn::AttnShape sh{c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, max_pages, L->chunk_pages, z.max_chunks, 0};
+    if (prompts && dyn::attention_mfma_supported(c.dtype, sh))
+        z.max_chunks = std::max(z.max_chunks, dyn::attn_prefill_max_chunks((long)std::max(max_pages, 1) * c.page_size));
     z.h = t * z.ld_h * e;
     z.qkv = t * qkv_width(c) * e;
     z.attn = t * z.ld_attn * e;
@@ -205,7 +211,7 @@ ScratchBytes dispatch_scratch(const dyn_layer *L, const Sizes &z, int op, int ro
 // micro-batch) once per layer, so its dispatches' scratch adds up to at most that), nothing shared.
 size_t ws_bound(const dyn_layer *L, int T, int max_pages) {
     const dyn_layer_config &c = L->cfg;
-    const Sizes z = tensor_sizes(L, T, max_pages);
+    const Sizes z = tensor_sizes(L, T, max_pages, T > 1);
     const size_t t = (size_t)std::max(T, 0);
     const int pairs = c.n_experts ? c.top_k : 1;
     size_t total = 0;
@@ -433,7 +439,7 @@ std::vector<int> alive_until(const std::vector<Dispatch> &plan) {
 // overlapping that Section 2.1 names.
 WsLayout plan_layout(const dyn_layer *L, const dyn_batch *b, const std::vector<Dispatch> &plan, std::vector<Region> *regions_out) {
     const dyn_layer_config &c = L->cfg;
-    const Sizes z = tensor_sizes(L, b->n_tokens, b->max_pages_per_seq);
+    const Sizes z = tensor_sizes(L, b->n_tokens, b->max_pages_per_seq, b->n_tokens > b->n_seqs);
     WsLayout w{};
     w.ld_h = z.ld_h; w.ld_attn = z.ld_attn; w.ld_act = z.ld_act; w.max_chunks = z.max_chunks;
     const int P = (int)plan.size(), n_slots = P / std::max(c.n_layers, 1);
@@ -912,7 +918,7 @@ void analyse_memory(const dyn_layer *L, const dyn_batch *b, const std::vector<Di
                     dyn_memory_report *out, size_t *peak, int *peak_at) {
     const dyn_layer_config &c = L->cfg;
     const size_t e = esize(c);
-    const Sizes ws = tensor_sizes(L, b->n_tokens, b->max_pages_per_seq);
+    const Sizes ws = tensor_sizes(L, b->n_tokens, b->max_pages_per_seq, b->n_tokens > b->n_seqs);
     const int n_slots = (int)plan.size() / c.n_layers;
     const bool moe = c.n_experts > 0, gated = dyn::gemm_gated_supported(c.dtype, 2 * c.mlp_inter, c.hidden);
     const int pairs = moe ? c.top_k : 1, H = c.hidden, I = c.mlp_inter, NQKV = qkv_width(c), NQ = c.n_q_heads * c.head_dim;

@@ -18,7 +18,7 @@ struct AttnShape {
     int n_q, n_kv, head_dim, page_size;
     int max_pages_per_seq;         // block-table row length
     int chunk_pages;               // pages per split-KV chunk (a constant of the layer)
-    int max_chunks;                // chunks that fit max_pages_per_seq: stride of the partial arrays
+    int max_chunks;                // the most chunks a token of the batch can have: stride of the partial arrays
     int n_cus;                     // CUs of the stream's partition (0: whole device); sizes the persistent launch
 };
 
@@ -133,6 +133,7 @@ hipError_t launch_rope_kv(int dtype, void *qkv, const int32_t *seq_of_token, con
 struct AttnPlan { int32_t *single, *multi, *ct_of_token; };
 AttnPlan attn_plan_lists(int32_t *plan, const AttnShape &sh, int rows);
 bool attention_mfma_supported(int dtype, const AttnShape &sh);      // the shapes whose attention walks these lists
+int attn_prefill_max_chunks(long positions);      // the most chunks its prompt form cuts a token's keys into
 hipError_t launch_attn_plan(const int32_t *seq_of_token, const int32_t *pos_of_token, int32_t *plan, const AttnShape &sh, int rows, hipStream_t s);
 // The lists of some rows and the RMSNorm of the same rows (bf16) in one launch: neither needs the other.
 hipError_t launch_norm_plan(const void *x, const void *g, void *out, int ld_out, int rows, int H, float eps, const int32_t *seq_of_token,

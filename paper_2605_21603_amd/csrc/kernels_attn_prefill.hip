@@ -397,6 +397,8 @@ __global__ __launch_bounds__(kWaves * 64, 1) void attn_prefill_kernel(const bf16
     }
 }
 
+int attn_prefill_max_chunks(long positions) { return prefill_max_chunks(positions); }
+
 int attn_prefill_block_tokens(const AttnShape &sh) { return kWaves * kSets * (16 / (sh.n_q / sh.n_kv)); }
 
 hipError_t launch_attention_prefill(const void *qkv, const int32_t *seq_of_token, const int32_t *pos_of_token,

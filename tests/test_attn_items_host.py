@@ -2,7 +2,8 @@
 
 The kernels ask column_end (csrc/common.h) what an item does with each of its columns.  Here the rule is compiled for
 the host and walked over every (block, chunk) item of a prompt: a token whose keys fit one chunk has its output written
-by exactly one item, any other token has exactly one partial per chunk it reaches, and nothing else is written."""
+by exactly one item, any other token has exactly one partial per chunk it reaches, and nothing else is written.  The bound on a token's chunks that sizes the partials
+(prefill_max_chunks) is walked too."""
 import os
 import subprocess
 
@@ -45,6 +46,17 @@ int main() {
         for (int p0 : {0, 1, 959, 1000}) {
             bad += wrong(p0, 20000, 16 * TG, [](int reach) { return prefill_chunk_positions(reach); });
             for (int ct : {64, 240, 256, 1024}) bad += wrong(p0, 3000, 4 * TG, [ct](int) { return ct; });
+        }
+    }
+    // the bound that sizes partials and lists holds for every key count and block, and is met
+    for (int G : {1, 3, 4, 16}) {
+        const int tg = 16 * (16 / G);
+        int most = 1;
+        for (int n = 1; n <= 200000; ++n) {
+            const int ct = prefill_chunk_positions(((n - 1) / tg + 1) * tg);
+            if ((n + ct - 1) / ct > most) most = (n + ct - 1) / ct;
+            bad += prefill_max_chunks(n) < most;
+            if (n % 65536 == 0 || n % 65536 == 1025) bad += prefill_max_chunks(n) != most;
         }
     }
     for (int nk : {0, -1}) bad += column_end(nk, 0, 64) != COLUMN_NOT_MINE;      // dead columns

@@ -196,3 +196,15 @@ def test_prompts_across_the_first_chunk_with_blocks_that_do_not_divide_it(n_q, n
     data = gen.generate(w)
     y, k, v = both_schedules(w, data)
     say("%d/%d: %.2e" % (n_q, n_kv, check_against_oracle(w, data, y, k, v)))
+
+
+# the prompt kernel's chunks (1024 positions, 2048 behind 8192) are shorter than the handle's: 4, 5 and 3 of them for prompts here
+@pytest.mark.parametrize("chunk", [1536, 2048, 8192, 65536])
+def test_prompts_under_a_handle_with_long_chunks(chunk):
+    w = workload("long_handle_chunk", "bf16", 128, 4, 1, 128, 128, [(3100, 3100), (1, 70), (40, 4120), (1, 2049), (2, 8300), (1, 5000), (3, 1025)], seed=98)
+    data = gen.generate(w)
+    run = GpuRun(w, data, kv_chunk_positions=chunk)
+    y, k, v = run.run(B.sequential())
+    y1, _, _ = run.run(B.nano_schedule(w.nano_rows))
+    assert torch.equal(y.view(torch.uint8), y1.view(torch.uint8)), "the split schedule changed bits"
+    say("chunk %d: %.2e" % (chunk, check_against_oracle(w, data, y, k, v)))

@@ -157,3 +157,33 @@ def test_sequential_layout_of_the_prefill_decode_mix_shares_most_of_the_workspac
     split = B.nano_schedule(w.nano_rows, stagger=1)
     _, total_split = _check_layout(layer, hb, split)
     assert total < total_split < bound
+
+
+@pytest.mark.parametrize("chunk", [0, 64, 1024, 2048, 8192, 65536])
+@pytest.mark.parametrize("seqs", [[(4096, 4096), (1, 100)], [(1, 4000), (2, 8194)], [(3, 9000), (1, 30000)], [(2, 70000), (1, 131072)], [(1, 131072), (1, 5)]])
+def test_partials_and_lists_hold_every_chunk_of_every_token(seqs, chunk):
+    """The partials of a bf16, 128-wide layer have room for the most chunks any token of the batch is cut into: a
+    single token by the handle's chunk, a prompt's token by the prompt kernel's rule (1024 positions, doubled until the
+    reach of its block of 64 positions - 4 q heads per kv head here - makes at most eight, up to 8192), which a handle
+    with a chunk above 1024 positions does not bound.  The any-batch bound covers them too."""
+    sh = gen.LayerShape("bf16", 512, 4, 1, 128, 512)
+    T = sum(q for q, _ in seqs)
+    w = gen.Workload("chunks", sh, tuple(seqs), 1, (0, T))
+    fake = {n: 0x1000 for n in ("w_qkv", "w_o", "w_gate_up", "w_down", "g_norm1", "g_norm2")}
+    layer = B.DynLayer(B.make_config(sh, chunk), [fake])
+    hb = host_batch(w)
+    need = 0
+    for q, ctx in seqs:
+        for n in range(ctx - q + 1, ctx + 1):                    # keys of each of the sequence's tokens
+            ct = chunk or 256
+            if q > 1:
+                ct = 1024
+                while -(-n // 64) * 64 > 8 * ct and ct < 8192:
+                    ct *= 2
+            need = max(need, -(-n // ct))
+    by_kind = {r["kind"]: r["bytes"] for r in layer.schedule_regions(hb, B.sequential())}
+    assert by_kind["part_o"] >= T * 4 * need * 128 * 4 and by_kind["part_ml"] >= T * 4 * need * 2 * 4
+    assert by_kind["plan"] >= 4 * (2 * (2 + 2 * T * need) + T)   # two lists and a chunk size per token
+    assert layer.schedule_workspace_bytes(hb, B.sequential()) <= layer.workspace_bytes(T, -(-max(c for _, c in seqs) // 16))
+    if all(q == 1 for q, _ in seqs):                             # decodes alone: the handle's chunk and nothing more
+        assert by_kind["part_o"] == T * 4 * -(-max(c for _, c in seqs) // (chunk or 256)) * 128 * 4
