@@ -10,6 +10,8 @@
 //
 // attn_tile_kernel is the matrix-core form, for head dims 32..256 and pages of a multiple of 16
 // positions; attn_generic_kernel (one wave per (token, q head, chunk), plain loops) takes the rest.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -54,7 +56,7 @@ __global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_
                                                         const int32_t *__restrict__ block_table, const T *__restrict__ k_cache,
                                                         const T *__restrict__ v_cache, T *__restrict__ out, int ld_out,
                                                         float *__restrict__ part_o, float *__restrict__ part_ml, AttnShape sh,
-                                                        int rows) {
+                                                        int rows, int y0, int y1) {
     constexpr bool F32 = sizeof(T) == 4;
     constexpr int NK = F32 ? HD / 16 : HD / 32, ND = HD / 16;      // 16-byte K operands and 16-row V operands of a lane
     constexpr int MD = HD < 128 ? HD : 128;                        // head-dim indices merged per round
@@ -67,8 +69,9 @@ __global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_
     // higher bits so that the ones with work, however regularly spaced, spread over all XCDs.
     const unsigned wg = (blockIdx.x & ~7u) | ((blockIdx.x + (blockIdx.x >> 3) + (blockIdx.x >> 6)) & 7u);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int t = (int)(wg % rows), g = (int)(wg / rows) % sh.n_kv, c = (int)(wg / rows) / sh.n_kv;
-    if (c >= sh.max_chunks) return;
+    const int t = (int)(wg % rows), y = y0 + (int)(wg / rows);     // y: (chunk, kv head) in [y0, y1) of this launch
+    const int g = (int)((unsigned)y % (unsigned)sh.n_kv), c = (int)((unsigned)y / (unsigned)sh.n_kv);
+    if (y >= y1) return;
     const int G = sh.n_q / sh.n_kv, TG = 16 / G, tg = 4 * TG;      // tokens per set of columns, per group
     const int col_tok = lr / G, col_head = lr % G;                 // this lane's column: a token of the wave's set and a q head
     const int s = seq_of_token[t], p0 = pos_of_token[t];
@@ -573,12 +576,23 @@ bool attn_tile_supported(int dtype, const AttnShape &sh, const void *k_cache, co
            (((uintptr_t)k_cache | (uintptr_t)v_cache) & 15) == 0;
 }
 
+// A grid's threads along x are counted in 32 bits, and what does not fit wraps without an error: 1024 rows of 32 kv heads
+// under a table of 512 chunks are 2^32 threads.  Larger grids go as several launches, each a range of (chunk, kv head), or
+// of rows in the general form.
+constexpr size_t kTileGrid = (size_t)1 << 23;          // workgroups of a launch of the tile form, about
+constexpr size_t kGeneralGrid = (size_t)1 << 25;       // of the general form
+
 template <typename T, int HD, int TP>
-void launch_attn_tile(dim3 grid, hipStream_t s, const void *qkv, const int32_t *seq_of_token, const int32_t *pos_of_token,
+void launch_attn_tile(hipStream_t s, const void *qkv, const int32_t *seq_of_token, const int32_t *pos_of_token,
                       const int32_t *block_table, const void *k_cache, const void *v_cache, void *out, int ld_out, float *part_o,
                       float *part_ml, const AttnShape &sh, int rows) {
-    hipLaunchKernelGGL((attn_tile_kernel<T, HD, TP>), grid, dim3(256), 0, s, (const T *)qkv, seq_of_token, pos_of_token, block_table,
-                       (const T *)k_cache, (const T *)v_cache, (T *)out, ld_out, part_o, part_ml, sh, rows);
+    const int n_y = sh.n_kv * sh.max_chunks, step = (int)std::max<size_t>(kTileGrid / rows, 1);
+    for (int y0 = 0; y0 < n_y; y0 += std::min(step, n_y - y0)) {
+        const int y1 = y0 + std::min(step, n_y - y0);
+        hipLaunchKernelGGL((attn_tile_kernel<T, HD, TP>), dim3((unsigned)(((size_t)rows * (y1 - y0) + 7) / 8 * 8)), dim3(256), 0, s, (const T *)qkv,
+                           seq_of_token, pos_of_token, block_table, (const T *)k_cache, (const T *)v_cache, (T *)out, ld_out, part_o, part_ml, sh,
+                           rows, y0, y1);               // whole eights of workgroups
+    }
 }
 }  // namespace
 
@@ -587,12 +601,12 @@ hipError_t launch_attention_generic(int dtype, const void *qkv, const int32_t *s
                                     const void *v_cache, void *out, int ld_out, float *part_o, float *part_ml,
                                     const AttnShape &sh, int rows, hipStream_t s, hipEvent_t mid) {
     if (rows <= 0) return hipSuccess;
+    if (rows >= 1 << 24) return hipErrorInvalidConfiguration;
     const bool tile = attn_tile_supported(dtype, sh, k_cache, v_cache);
     if (tile) {
-        const dim3 grid((unsigned)(((size_t)rows * sh.n_kv * sh.max_chunks + 7) / 8 * 8));     // whole eights of workgroups
         // positions per tile: two sub-tiles of 16 where a lane's K and V operands of both fit beside the
         // accumulators twice over, else one
-#define DYN_TILE(T, HD, TP) launch_attn_tile<T, HD, TP>(grid, s, qkv, seq_of_token, pos_of_token, block_table, k_cache, v_cache, out, ld_out, part_o, part_ml, sh, rows)
+#define DYN_TILE(T, HD, TP) launch_attn_tile<T, HD, TP>(s, qkv, seq_of_token, pos_of_token, block_table, k_cache, v_cache, out, ld_out, part_o, part_ml, sh, rows)
         if (dtype == 0) {
             switch (sh.head_dim) {
                 case 32: DYN_TILE(float, 32, 2); break;
@@ -610,13 +624,19 @@ hipError_t launch_attention_generic(int dtype, const void *qkv, const int32_t *s
         }
 #undef DYN_TILE
     } else {
-        const dim3 grid((unsigned)((size_t)rows * sh.n_q * sh.max_chunks));
-        if (dtype == 0)
-            hipLaunchKernelGGL(attn_generic_kernel<float>, grid, dim3(64), 0, s, (const float *)qkv, seq_of_token,
-                               pos_of_token, block_table, (const float *)k_cache, (const float *)v_cache, part_o, part_ml, sh);
-        else
-            hipLaunchKernelGGL(attn_generic_kernel<bf16_t>, grid, dim3(64), 0, s, (const bf16_t *)qkv, seq_of_token,
-                               pos_of_token, block_table, (const bf16_t *)k_cache, (const bf16_t *)v_cache, part_o, part_ml, sh);
+        const size_t per_row = (size_t)sh.n_q * sh.max_chunks, width = (size_t)(sh.n_q + 2 * sh.n_kv) * sh.head_dim;
+        const int step = (int)std::max<size_t>(kGeneralGrid / per_row, 1);
+        if (per_row >= (size_t)1 << 26) return hipErrorInvalidConfiguration;
+        for (int r0 = 0; r0 < rows; r0 += std::min(step, rows - r0)) {
+            const dim3 grid((unsigned)(std::min(step, rows - r0) * per_row));
+            float *const po = part_o + r0 * per_row * sh.head_dim, *const pml = part_ml + r0 * per_row * 2;
+            if (dtype == 0)
+                hipLaunchKernelGGL(attn_generic_kernel<float>, grid, dim3(64), 0, s, (const float *)qkv + r0 * width, seq_of_token + r0,
+                                   pos_of_token + r0, block_table, (const float *)k_cache, (const float *)v_cache, po, pml, sh);
+            else
+                hipLaunchKernelGGL(attn_generic_kernel<bf16_t>, grid, dim3(64), 0, s, (const bf16_t *)qkv + r0 * width, seq_of_token + r0,
+                                   pos_of_token + r0, block_table, (const bf16_t *)k_cache, (const bf16_t *)v_cache, po, pml, sh);
+        }
     }
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && mid) e = hipEventRecord(mid, s);

@@ -208,3 +208,20 @@ def test_prompts_under_a_handle_with_long_chunks(chunk):
     y1, _, _ = run.run(B.nano_schedule(w.nano_rows))
     assert torch.equal(y.view(torch.uint8), y1.view(torch.uint8)), "the split schedule changed bits"
     say("chunk %d: %.2e" % (chunk, check_against_oracle(w, data, y, k, v)))
+
+
+@pytest.mark.parametrize("dtype,rows,hd,table_positions", [("bf16", 1030, 32, 131072), ("f32", 1037, 32, 131072), ("f32", 1040, 8, 524288)])
+def test_attention_under_a_table_much_wider_than_the_contexts(dtype, rows, hd, table_positions):
+    """One q head per kv head and a table so wide that the workgroups of all its chunks (256 threads each, 64 in the
+    general form of the 8-wide heads) are more than 2^32 threads: several launches, in the tile form each with
+    workgroups past its last row at 1037 rows.  The same bits as under a table as wide as the longest context, and
+    as in smaller dispatches."""
+    w = workload("wide_table", dtype, 128, 32, 32, hd, 128, [(40, 40)] + [(1, 1 + (7 * i) % 300) for i in range(rows - 42)] + [(1, 1500), (1, 3000)], seed=99)
+    data = gen.generate(w)
+    y0, k0, v0 = both_schedules(w, data)
+    check_against_oracle(w, data, y0, k0, v0)
+    table = np.zeros((data["block_table"].shape[0], table_positions // 16), dtype=np.int32)
+    table[:, :data["block_table"].shape[1]] = data["block_table"]
+    y, k, v = both_schedules(w, dict(data, block_table=table))
+    for a, b in ((y, y0), (k, k0), (v, v0)):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
