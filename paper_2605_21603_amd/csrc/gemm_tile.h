@@ -48,6 +48,17 @@ __device__ __forceinline__ void mfma_acc(f32x4 &c, const bf16x8 &a, const bf16x8
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
 }
 
+// Waits for the assembly LDS reads into a and b.  A read whose result nobody uses still writes its registers when it
+// arrives: they are operands behind the wait, so that none is given to a value (a store's address) before.
+template <int NA, int NB>
+__device__ __forceinline__ void drain(bf16x8 (&a)[NA], bf16x8 (&b)[NB]) {
+    wait_lgkmcnt<0>();
+#pragma unroll
+    for (int i = 0; i < NA; ++i) asm volatile("" : "+v"(a[i]));
+#pragma unroll
+    for (int i = 0; i < NB; ++i) asm volatile("" : "+v"(b[i]));
+}
+
 // n tiles per band of a launch whose tiles cover the whole depth.  Eight bring an XCD's tiles of every shape
 // here to about as many W rows as X rows (32 or 64 tiles run on it at a time).  4096 rows, n-tile order -> bands
 // of 8 (4 and 16 lose 1-4 % of it): qkv 252 -> 208, o 183 -> 167, down 528 -> 470, gate/up 763 -> 753 us; 3000 rows: down
@@ -280,7 +291,7 @@ __device__ __forceinline__ void gemm_tile(unsigned char *lds, const bf16_t *__re
                 asm volatile("s_nop 7" ::: "memory");
             }
         }
-        wait_lgkmcnt<0>();
+        drain(a_cur, b_lo);                        // what the last stage read for a next one
         asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
     } else {
 #pragma unroll

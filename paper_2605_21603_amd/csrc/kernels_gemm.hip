@@ -292,7 +292,7 @@ __global__ __launch_bounds__(512) void mfma_loop_probe_kernel(const unsigned cha
             if constexpr (I % 4 == 3) fb[0][I / 4] = lds_read16<16384 + (I / 4) * 2048>(sn);
         });
     }
-    wait_lgkmcnt<0>();
+    drain(fa[0], fb[0]);
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
     float v = 0.f;
 #pragma unroll

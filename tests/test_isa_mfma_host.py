@@ -145,3 +145,75 @@ def test_the_replay_convicts_a_reader_that_comes_too_early():
     # and the way back to a loop's head
     loop = [".LBB0_1:"] + asm(read) + nop(15) + [product, "\ts_cbranch_scc1 .LBB0_1", "\ts_endpgm"]
     assert product_read_hazards(loop) != []
+
+
+def touched_in_flight(body):
+    """Instructions that name a register of an assembly LDS read before a wait has retired it, over all paths, behind
+    the loops that issue such reads as well as in them: a read nobody uses still writes its register when it arrives.
+    In state: LDS operations issued since the read (LDS operations retire in order; scalar loads may overtake them
+    and retire nothing)."""
+    items = parse(body)
+    at = {lab: i for i, (lab, _, _) in enumerate(items) if lab}
+    entry, work, found = {0: {}}, [0], set()
+
+    def join(i, state):
+        have = entry.get(i)
+        if have is None:
+            entry[i] = dict(state)
+            work.append(i)
+            return
+        new = {r: min(n, have.get(r, n)) for r, n in state.items()}
+        if any(have.get(r) != n for r, n in new.items()):
+            have.update(new)
+            work.append(i)
+
+    while work:
+        i = work.pop()
+        state, first = dict(entry[i]), True
+        while i < len(items):
+            label, s, asm = items[i]
+            if label:
+                if not first:
+                    join(i, state)
+                    break
+                i, first = i + 1, False
+                continue
+            first = False
+            op, _, rest = s.partition(" ")
+            if op == "s_waitcnt":
+                m = re.search(r"lgkmcnt\((\d+)\)", rest)
+                if m:
+                    state = {r: n for r, n in state.items() if n < int(m.group(1))}
+            else:
+                if registers(rest) & set(state):
+                    found.add((i, s))
+                if op.startswith("ds_"):
+                    state = {r: n + 1 for r, n in state.items()}
+                    if asm and op.startswith("ds_read"):
+                        state.update({r: 0 for r in registers(rest.partition(",")[0])})
+                if op.startswith("s_cbranch") or op == "s_branch":
+                    join(at[rest.strip()], state)
+                if op in ("s_branch", "s_endpgm"):
+                    break
+            i += 1
+    return [s for _, s in sorted(found)]
+
+
+@pytest.mark.parametrize("source", ["kernels_attn_prefill.hip", "kernels_gemm.hip", "kernels_gemm_wide.hip"])
+def test_no_register_is_touched_while_a_read_into_it_is_in_flight(tmp_path, source):
+    checked = 0
+    for name, body in kernels(compile_to_isa(tmp_path, source)):
+        if any("ASMSTART" in a and "ds_read" in b for a, b in zip(body, body[1:])):
+            assert not touched_in_flight(body), (name, touched_in_flight(body)[:5])
+            checked += 1
+    assert checked >= 1
+
+
+def test_the_flight_replay_convicts_a_register_reused_before_its_wait():
+    asm = lambda s: ["\t;;#ASMSTART", s, "\t;;#ASMEND"]
+    head = [".LBB0_1:", "\ts_waitcnt lgkmcnt(0)"] + asm("\tds_read_b128 v[0:3], v40") + asm("\tds_read_b128 v[4:7], v40 offset:0x800") + ["\ts_cbranch_scc1 .LBB0_1"]
+    assert touched_in_flight(head + ["\tv_add_u32_e32 v1, s0, v50", "\ts_waitcnt lgkmcnt(0)"]) != []         # an address where data will land
+    assert touched_in_flight(head + ["\ts_waitcnt lgkmcnt(0)", "\tv_add_u32_e32 v1, s0, v50"]) == []
+    assert touched_in_flight(head + ["\ts_waitcnt lgkmcnt(1)", "\tv_add_u32_e32 v1, s0, v50"]) == []         # the first read has retired
+    assert touched_in_flight(head + ["\ts_waitcnt lgkmcnt(1)", "\tv_add_u32_e32 v5, s0, v50"]) != []
+    assert touched_in_flight(head + ["\ts_load_dword s4, s[2:3], 0x0", "\ts_waitcnt lgkmcnt(2)", "\tv_add_u32_e32 v1, s0, v50"]) != []
