@@ -59,6 +59,22 @@ __device__ __forceinline__ void drain(bf16x8 (&a)[NA], bf16x8 (&b)[NB]) {
     for (int i = 0; i < NB; ++i) asm volatile("" : "+v"(b[i]));
 }
 
+// Makes every accumulator an operand here: an ordinary instruction on one stays on its side of this and of the assembly
+// around it (across a bare wait the compiler may move it).
+template <int NA, int NB>
+__device__ __forceinline__ void pin(f32x4 (&acc)[NA][NB]) {
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) asm volatile("" : "+v"(acc[a][b]));
+}
+// Waits until the assembly products into acc have left the matrix core.
+template <int NA, int NB>
+__device__ __forceinline__ void settle(f32x4 (&acc)[NA][NB]) {
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    pin(acc);
+}
+
 // n tiles per band of a launch whose tiles cover the whole depth.  Eight bring an XCD's tiles of every shape
 // here to about as many W rows as X rows (32 or 64 tiles run on it at a time).  4096 rows, n-tile order -> bands
 // of 8 (4 and 16 lose 1-4 % of it): qkv 252 -> 208, o 183 -> 167, down 528 -> 470, gate/up 763 -> 753 us; 3000 rows: down
@@ -286,13 +302,14 @@ __device__ __forceinline__ void gemm_tile(unsigned char *lds, const bf16_t *__re
                 // the compiler does not know that the assembly's results arrive late: the last MFMAs
                 // must have left the pipeline before the accumulators are read as ordinary registers,
                 // and the cleared accumulators must be written before the next MFMA reads them
-                asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+                settle(acc);
                 fold_plane(st);
+                pin(acc);
                 asm volatile("s_nop 7" ::: "memory");
             }
         }
         drain(a_cur, b_lo);                        // what the last stage read for a next one
-        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+        settle(acc);
     } else {
 #pragma unroll
     for (int d = 0; d < NS - 1; ++d)

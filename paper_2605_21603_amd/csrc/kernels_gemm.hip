@@ -260,10 +260,10 @@ __global__ __launch_bounds__(512) void mfma_loop_probe_kernel(const unsigned cha
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gsrc + ((st * 8 + j) & 31) * 8192),
                                          (__attribute__((address_space(3))) void *)(lds + (st & 1) * STAGE + (j * 8 + wave) * 1024), 16, 0, 0);
     };
-    f32x4 acc[32];
+    f32x4 acc[1][32];
     bf16x8 fa[2][4], fb[2][8];
 #pragma unroll
-    for (int i = 0; i < 32; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < 32; ++i) acc[0][i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int j = 0; j < 8; ++j) load(0, j);
     wait_vmcnt(0);
@@ -276,7 +276,7 @@ __global__ __launch_bounds__(512) void mfma_loop_probe_kernel(const unsigned cha
         wait_lgkmcnt<0>();
         static_for<0, 32>([&](auto i) {
             constexpr int I = decltype(i)::value;
-            mfma_acc(acc[I], fa[0][I & 3], fb[0][I >> 2]);
+            mfma_acc(acc[0][I], fa[0][I & 3], fb[0][I >> 2]);
             if constexpr (I % 8 == 1 && I / 8 < 4) fa[1][I / 8] = lds_read16<(I / 8) * 2048>(so1);
             if constexpr (I % 4 == 3) fb[1][I / 4] = lds_read16<16384 + (I / 4) * 2048>(so1);
             if constexpr (I % 4 == 2) load(st + 1, I / 4);
@@ -287,16 +287,16 @@ __global__ __launch_bounds__(512) void mfma_loop_probe_kernel(const unsigned cha
         __builtin_amdgcn_s_barrier();
         static_for<0, 32>([&](auto i) {
             constexpr int I = decltype(i)::value;
-            mfma_acc(acc[I], fa[1][I & 3], fb[1][I >> 2]);
+            mfma_acc(acc[0][I], fa[1][I & 3], fb[1][I >> 2]);
             if constexpr (I % 8 == 1 && I / 8 < 4) fa[0][I / 8] = lds_read16<(I / 8) * 2048>(sn);
             if constexpr (I % 4 == 3) fb[0][I / 4] = lds_read16<16384 + (I / 4) * 2048>(sn);
         });
     }
     drain(fa[0], fb[0]);
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    settle(acc);
     float v = 0.f;
 #pragma unroll
-    for (int i = 0; i < 32; ++i) v += acc[i][0] + acc[i][1] + acc[i][2] + acc[i][3];
+    for (int i = 0; i < 32; ++i) v += acc[0][i][0] + acc[0][i][1] + acc[0][i][2] + acc[0][i][3];
     sink[(size_t)blockIdx.x * 512 + tid] = v;        // keeps the products alive
 }
 

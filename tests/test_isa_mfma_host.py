@@ -8,7 +8,8 @@ reads or overwrites a product's register must come at least WAIT_STATES later if
 assembly.  Exempt are the accumulator of a following product, which the hardware forwards, and the destination of an LDS
 read, whose data arrive long after.  Only the s_nop that the source itself writes count: what else stands
 between in today's build the compiler may move.  The mask that separates the two on some paths is the compiler's
-instruction, and a register it has written is no product's any more."""
+instruction, and a register it has written is no product's any more.  A product written as assembly must not
+follow a vector instruction that writes one of its operands within OPERAND_STATES instructions."""
 import re
 
 import pytest
@@ -17,6 +18,8 @@ from test_isa_host import compile_to_isa, registers
 # A 16x16x32 bf16 product is at most an 8-pass instruction: the ISA's table asks 11 wait states before a vector
 # instruction touches its result, one more than that covers this generation's longer pipeline.
 WAIT_STATES = 12
+# and a product that reads what a vector instruction wrote needs two (the compiler sees to its own)
+OPERAND_STATES = 2
 
 
 def parse(body):
@@ -69,11 +72,19 @@ def product_read_hazards(body):
             for r in sources:
                 if r in state and state[r][0] < WAIT_STATES and (asm or state[r][1]):
                     found.add((i, s))
+            if asm and op.startswith("v_mfma") and any(("w", r) in state for r in registers(rest)):
+                found.add((i, s))
             n = states_of(s, asm)
-            state = {r: (t + n, a) for r, (t, a) in state.items() if t + n < WAIT_STATES and r not in own}
-            if op.startswith("v_mfma"):
-                for r in own:
+            products = {r: (t + n, a) for r, (t, a) in state.items() if isinstance(r, int) and t + n < WAIT_STATES and r not in own}
+            m = max(n, states_of(s, True) if op == "s_nop" else 1)                   # any instruction is a state here
+            state = {k: (t + m, a) for k, (t, a) in state.items() if not isinstance(k, int) and t + m < OPERAND_STATES}
+            state.update(products)
+            for r in own:
+                if op.startswith("v_mfma"):
                     state[r] = (0, asm)
+                    state.pop(("w", r), None)
+                elif op.startswith("v_"):
+                    state["w", r] = (0, asm)
             if op.startswith("s_cbranch") or op == "s_branch":
                 target = at[rest.strip()]
                 merge(entry, target, state, work)
@@ -115,7 +126,7 @@ def kernels(lines):
         yield lines[i].split(":")[0], body[:stop[0]] if stop else body
 
 
-@pytest.mark.parametrize("source", ["kernels_attn_prefill.hip"])
+@pytest.mark.parametrize("source", ["kernels_attn_prefill.hip", "kernels_gemm.hip", "kernels_gemm_wide.hip"])
 def test_nothing_reads_a_product_before_it_has_left_the_matrix_core(tmp_path, source):
     checked = 0
     for name, body in kernels(compile_to_isa(tmp_path, source)):
@@ -139,6 +150,11 @@ def test_the_replay_convicts_a_reader_that_comes_too_early():
     assert product_read_hazards([product, "\tv_cndmask_b32_e32 v0, v30, v0, vcc"] + asm(read)) == []          # a masked value
     assert product_read_hazards(asm(product) + ["\tv_add_f32_e32 v20, v0, v21"]) != []
     assert product_read_hazards(asm(product) + asm(product)) == []                   # accumulation is forwarded
+    write = "\tv_mov_b32_e32 v1, 0"
+    assert product_read_hazards([write] + asm(product)) != []
+    assert product_read_hazards([write] + nop(0) + asm(product)) != []
+    assert product_read_hazards([write] + nop(1) + asm(product)) == []
+    assert product_read_hazards([write, product]) == []                             # the compiler's own
     # the distance of the shorter way round a branch counts
     skip = [product, "\ts_cbranch_scc1 .LBB0_2"] + nop(15) + [".LBB0_2:"] + asm(read)
     assert product_read_hazards(skip) != []
