@@ -32,20 +32,24 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # HBM bytes per launch of the attention kernel, read with rocprofv3 counters (FETCH_SIZE and
 # WRITE_SIZE in runs of their own, scaled by a 1 GiB copy probe).  Counters cannot be read
 # from inside this process, so the figure of the committed counter summary is repeated here,
-# together with the hash of the kernel's source it was measured on: if the source has changed
-# since, the figure is withheld (traffic = null) instead of going stale silently.
-ATTN_SOURCE = os.path.join(ROOT, "paper_2605_21603_amd", "csrc", "kernels_attn_mfma.hip")
+# together with one hash of the sources it was measured on - the kernel, and the work lists whose order
+# decides which wave walks what: if one has changed since, the figure is withheld (traffic = null)
+# instead of going stale silently.
+ATTN_SOURCE = tuple(os.path.join(ROOT, "paper_2605_21603_amd", "csrc", f) for f in ("kernels_attn_mfma.hip", "kernels_attn_plan.hip"))
 ROCPROF_TRAFFIC = {
-    "c2": {"bytes": 1273019187 + 21839462, "source_sha256_16": "a507ddf900053cde", "kv_chunk_positions": 256,
+    "c2": {"bytes": 1273019187 + 21839462, "source_sha256_16": "fb4e40fae84d189f", "kv_chunk_positions": 256,
            "source": "profiles/c2_sequential_attn_mfma_kernel.md (FETCH_SIZE 621,591.4 x 2.0 KiB + WRITE_SIZE 21,327.6 KiB)"},
-    "c5": {"bytes": 5050555802 + 22979789, "source_sha256_16": "a507ddf900053cde", "kv_chunk_positions": 1024,
+    "c5": {"bytes": 5050555802 + 22979789, "source_sha256_16": "fb4e40fae84d189f", "kv_chunk_positions": 1024,
            "source": "profiles/c5_sequential_32_layer_decode.md (FETCH_SIZE 2,466,091.7 x 2.0 KiB + WRITE_SIZE 22,441.2 KiB)"},
 }
 
 
-def source_hash(path):
-    with open(path, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+def source_hash(paths):
+    h = hashlib.sha256()
+    for path in paths:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def log(msg):

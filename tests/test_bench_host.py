@@ -45,6 +45,20 @@ def test_committed_counter_figures_belong_to_the_attention_kernel_as_it_is():
         assert 1.0 <= t["bytes"] / bench.attention_bytes(gen.config(wl)) < 1.06
 
 
+def test_the_counter_guard_covers_the_kernel_and_its_work_lists(tmp_path):
+    names = [os.path.basename(p) for p in bench.ATTN_SOURCE]
+    assert sorted(names) == ["kernels_attn_mfma.hip", "kernels_attn_plan.hip"]
+    hashes = {bench.source_hash(bench.ATTN_SOURCE)}
+    for changed in names:
+        copies = []
+        for p in bench.ATTN_SOURCE:
+            copy = tmp_path / os.path.basename(p)
+            copy.write_bytes(open(p, "rb").read() + (b"\n" if os.path.basename(p) == changed else b""))
+            copies.append(str(copy))
+        hashes.add(bench.source_hash(copies))
+    assert len(hashes) == 3
+
+
 def test_more_than_one_gpu_is_refused_with_a_message():
     p = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], stdout=subprocess.PIPE, stderr=subprocess.PIPE,
                        text=True, timeout=120)
