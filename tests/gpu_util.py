@@ -1,5 +1,6 @@
 """Helpers shared by the GPU tests: run a generated step through the C-ABI library and
 compare with the oracle."""
+import ctypes
 import sys
 
 import numpy as np
@@ -15,6 +16,20 @@ TOL = {"f32": 1e-4, "bf16": 2e-2}
 def say(msg):
     print(msg, flush=True)
     sys.stdout.flush()
+
+
+class _GemmPath(ctypes.Structure):          # dyn::GemmPath (csrc/kernels.h)
+    _fields_ = [(n, ctypes.c_int) for n in ("kind", "bn", "mt", "split")] + [("folded", ctypes.c_bool)] + \
+               [(n, ctypes.c_int) for n in ("workgroups", "resident", "tail_rows")]
+
+
+def gemm_path(rows, N, K):
+    """The tile, planes and form the library takes for a bf16 projection: what a test is for, it asserts."""
+    p = _GemmPath()
+    f = B.lib()._ZN3dyn9gemm_pathEiiii           # the struct is returned through a pointer passed first
+    f.argtypes, f.restype = [ctypes.c_void_p] + [ctypes.c_int] * 4, None
+    f(ctypes.byref(p), 1, rows, N, K)
+    return p
 
 
 def row_rel_err(got: np.ndarray, ref: np.ndarray) -> float:

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import GpuRun, check_against_oracle, say
+from gpu_util import GpuRun, check_against_oracle, gemm_path, say
 from paper_2605_21603_amd import binding as B
 from workloads import gen
 
@@ -126,20 +126,33 @@ def test_expert_tiles_follow_the_rows_each_expert_gets(tokens, pull):
     check_against_oracle(w, data, y, k, v)
 
 
-@pytest.mark.parametrize("rows", [1025, 1281, 1500, 2049])
-def test_folded_launch_in_bands_matches_smaller_launches(rows):
-    """Rows of one many-row launch (256 x 128 tiles, planes folded, bands over the XCDs, a last band narrower than the
-    others) have the bits of the same rows cut into two launches of other tiles."""
-    w = workload("fold", "bf16", 1280, 4, 1, 128, 10240, [(1, 1 + i % 3) for i in range(rows)], seed=60)
+# gate/up of 5376 columns: 21 n tiles of 256, bands of 8, 8 and 5 (42 tiles of 128 beside 160 rows: five of 8, one of 2), the
+# last m tile with 57, 1, 92 and 1 rows; 20480 columns: ten whole bands of 256-wide tiles, and twenty beside 160 rows
+@pytest.mark.parametrize("hidden,inter,rows,bn", [(1024, 2688, 825, 256), (1024, 2688, 1025, 256), (1024, 2688, 1500, 256), (1024, 2688, 1537, 128),
+                                                  (1024, 2688, 2049, 256), (1280, 10240, 1025, 256), (1280, 10240, 1281, 128)])
+def test_folded_launch_in_bands_matches_smaller_launches(hidden, inter, rows, bn):
+    """Rows of one many-row launch (planes folded, bands over the XCDs, the last band narrower than the others where
+    the width is no multiple of it) have the bits of the same rows cut into launches of other tiles, and a
+    sample of them, computed alone, is the oracle's."""
+    p, few = gemm_path(rows, 2 * inter, hidden), gemm_path(40, 2 * inter, hidden)
+    assert p.folded and p.split > 1 and p.bn == bn and p.mt == (128 if bn == 256 else 160) and not few.folded
+    assert (2 * inter // bn) % 8 == {(5376, 256): 5, (5376, 128): 2}.get((2 * inter, bn), 0)
+    w = workload("fold", "bf16", hidden, 4, 1, 128, inter, [(1, 1 + i % 3) for i in range(rows)], seed=60)
     w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, 200, rows))
     data = gen.generate(w)
-    both_schedules(w, data)
+    y, _, _ = both_schedules(w, data)
+    sample = list(range(0, rows, max(rows // 31, 1)))[:31] + [rows - 2, rows - 1]
+    sub, d2 = gen.extract_sequences(w, data, sample)
+    y2, k2, v2 = GpuRun(sub, d2).run(B.sequential())
+    assert torch.equal(y2, y[torch.as_tensor(d2["rows"])])
+    check_against_oracle(sub, d2, y2, k2, v2)
 
 
 @pytest.mark.parametrize("rows", [65, 129, 300, 500])
 def test_narrow_projections_on_lower_tiles_match_smaller_launches(rows):
     """Outputs so narrow that their (n tile, plane) pairs leave CUs idle take lower tiles; the rows keep the bits they
     have in a 40-row launch."""
+    assert all(gemm_path(rows, N, K).kind == 0 and gemm_path(rows, N, K).split > 1 for N, K in ((1536, 1024), (1024, 1024), (4096, 1024), (1024, 2048)))
     w = workload("narrow", "bf16", 1024, 8, 2, 128, 2048, [(1, 1 + i % 7) for i in range(rows)], seed=70)
     w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, 40, rows))
     data = gen.generate(w)
@@ -181,6 +194,7 @@ def test_general_attention_with_chunks_longer_than_its_scores(dtype, hd, page, c
 @pytest.mark.parametrize("hidden,n_q,n_kv,hd,inter", [(1024, 16, 4, 64, 3072), (2048, 16, 4, 128, 7680), (3072, 24, 8, 128, 8192), (3072, 24, 8, 128, 9728)])
 @pytest.mark.parametrize("rows", [1, 7, 8, 9])
 def test_few_rows_match_the_bits_of_larger_launches(rows, hidden, n_q, n_kv, hd, inter):
+    assert all(gemm_path(rows, N, K).split in (2, 4, 8) for N, K in (((n_q + 2 * n_kv) * hd, hidden), (hidden, n_q * hd), (hidden, inter)))
     w = workload("few_rows", "bf16", hidden, n_q, n_kv, hd, inter, [(1, 1 + (i * 31) % 300) for i in range(21)], seed=95)
     w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, rows, 21))
     data = gen.generate(w)
