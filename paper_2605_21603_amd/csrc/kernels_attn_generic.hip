@@ -569,8 +569,7 @@ hipError_t launch_attention_combine(int dtype, bool base2, float *part_o, float 
 
 namespace {
 // The matrix-core form reads K and q 16 bytes and V four positions at a time.
-bool attn_tile_supported(int dtype, const AttnShape &sh, const void *k_cache, const void *v_cache) {
-    (void)dtype;
+bool attn_tile_supported(const AttnShape &sh, const void *k_cache, const void *v_cache) {
     const int d = sh.head_dim;
     return (d == 32 || d == 64 || d == 128 || d == 256) && sh.page_size % 16 == 0 && sh.n_q / sh.n_kv <= 16 &&
            (((uintptr_t)k_cache | (uintptr_t)v_cache) & 15) == 0;
@@ -602,7 +601,7 @@ hipError_t launch_attention_generic(int dtype, const void *qkv, const int32_t *s
                                     const AttnShape &sh, int rows, hipStream_t s, hipEvent_t mid) {
     if (rows <= 0) return hipSuccess;
     if (rows >= 1 << 24) return hipErrorInvalidConfiguration;
-    const bool tile = attn_tile_supported(dtype, sh, k_cache, v_cache);
+    const bool tile = attn_tile_supported(sh, k_cache, v_cache);
     if (tile) {
         // positions per tile: two sub-tiles of 16 where a lane's K and V operands of both fit beside the
         // accumulators twice over, else one
