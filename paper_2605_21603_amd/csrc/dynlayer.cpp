@@ -1022,7 +1022,7 @@ dyn_status check_config(const dyn_layer_config *c) {
                           {2 * c->mlp_inter, c->hidden}, {c->hidden, c->mlp_inter}};
     for (auto &p : nk)
         if (!dyn::gemm_supported(c->dtype, p[0], p[1]))
-            return fail(DYN_ERR_UNSUPPORTED, "projection %d x %d: bf16 needs widths that are multiples of 128 and depths that are multiples of 256", p[0], p[1]);
+            return fail(DYN_ERR_UNSUPPORTED, "projection %d x %d: bf16 needs widths that are multiples of 128 and depths that are multiples of 64", p[0], p[1]);
     if (c->n_experts > 16) return fail(DYN_ERR_UNSUPPORTED, "at most 16 experts");
     if (c->kv_chunk_positions != 0 && (c->kv_chunk_positions < 64 || c->kv_chunk_positions > 65536 || c->kv_chunk_positions % c->page_size))
         return fail(DYN_ERR_INVALID_ARG, "kv_chunk_positions = %d: 0, or a multiple of page_size in 64..65536", c->kv_chunk_positions);

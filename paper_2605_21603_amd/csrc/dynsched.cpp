@@ -58,7 +58,8 @@ void reset_recording(dyn_scheduler *s, int k) {
 //                             a CU working at 1/256 of 0.95 PFLOP/s (1.25 with 256 x 256 tiles);
 //                             planes that are not folded in registers are read back at 5 TB/s
 //   decode attention          K/V stream at about 5.0 TB/s
-//   prefill attention         about 0.45 PFLOP/s
+//   prefill attention         about 0.45 PFLOP/s (up to 0.94 since its waves work in two groups; not fitted again:
+//                             the order it leads to costs at most 2.3 % against the better one on 36 mixes)
 //   element-wise operators    about 2 TB/s
 //   a dependent kernel in a replayed graph costs about 2 us before it does anything; the
 //   split-K reduce, the split-KV merge and the work-list kernel add their own launches.

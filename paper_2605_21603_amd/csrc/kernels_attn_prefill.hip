@@ -2,20 +2,20 @@
 // compute-bound form of the layer's attention (the paper's compute-bound operator class,
 // Section 2), bf16 caches, head_dim 128, 16-position pages.
 //
-// An 8-wave workgroup serves one query block - up to 8 * 8 tokens of one sequence whose
-// positions fall in one aligned block - against one chunk of cached positions (1024, more behind
-// a long prefix: prefill_chunk_positions) of one kv head.  K and V tiles of 32 positions (two pages, 16 KB) go from global memory
-// straight into an LDS ring with direct loads, once per workgroup, and all eight waves read
-// their MFMA operands from there: a key is fetched once per 64 query tokens and q-head
+// An 8-wave workgroup serves one query block - up to 16 * (16 / G) tokens (64 with G = 4 q heads per kv
+// head) of one sequence whose positions fall in one aligned block - against one chunk of cached positions (1024, more behind
+// a long prefix: prefill_chunk_positions) of one kv head.  K and V tiles of 64 positions (four pages each, 32 KB together) go from
+// global memory straight into an LDS ring with direct loads, once per workgroup, and all eight waves read
+// their MFMA operands from there: a key is fetched once per query block and q-head
 // group, and the waves hold no K/V staging registers.  A wave owns two sets of 16 columns
 // (64 accumulator registers): everything fits the 256 vector registers of a wave at two
 // waves per SIMD, so one wave's softmax overlaps another's matrix products and no operand
 // ever sits in an accumulation register it has to be copied out of.
-//   S[32 pos, 32 cols]  = K_tile[32, 128] Q^T[128, 32]       (16 x mfma 16x16x32 per wave)
-//   O^T[128, 32 cols]  += V_tile^T[128, 32] P[32, 32]        (16 x mfma 16x16x32 per wave)
+//   S[64 pos, 32 cols]  = K_tile[64, 128] Q^T[128, 32]       (32 x mfma 16x16x32 per wave)
+//   O^T[128, 32 cols]  += V_tile^T[128, 64] P[64, 32]        (32 x mfma 16x16x32 per wave)
 // A column is (token, q head of the kv head's group); the D layout of the first product
 // (lane: column l % 16, positions 4 (l / 16) + r of a page) is the B layout of the second
-// with the k index running over (page 0: 4 positions, page 1: 4 positions), and V's
+// with the k index running over (one page: 4 positions, the next: 4 positions), and V's
 // position-fastest page layout makes the matching A operand two 8-byte LDS reads.
 // K rows are 256 bytes, so their 16-byte columns are XOR-swizzled with the row on the way in
 // (the direct load's source address is permuted, its LDS destination cannot be).

@@ -534,7 +534,8 @@ namespace {
 // holds every row once).  Few rows per expert stream the weights through 128-row tiles; from about
 // 100 rows a second 128-row tile per expert would move its weights into LDS again, so the tile
 // grows with the rows: one 256-row tall tile up to about 200 rows, 256 x 256 tiles beyond (eight
-// experts' gate/up at 512 / 1024 / 2048 tokens: 593 / 989 / 1847 us with 128-row tiles).  The
+// experts' gate/up at 512 / 1024 / 2048 tokens: 593 / 989 / 1847 us with 128-row tiles).  Both lines were drawn with
+// 256-row tiles of one height; gemm_experts_wide_kernel, which fits the height to each expert, was not timed below 200.  The
 // grid still covers max_rows per group; tiles past a group's count exit at once.
 struct GroupTile { int bn, mt; };
 GroupTile gemm_group_tile(const GemmGroups &gr, int max_rows, int N) {
