@@ -368,6 +368,22 @@ int gemm_tall_rows(int rows, int S, int N, int K) {
     return (rows + 383) / 384 <= (rows + 511) / 512 ? 384 : 512;
 }
 
+// 256 x 128 tiles for folded planes (kernels_gemm_wide.hip), from the number of 128 x 128 tiles.  They hold the same outputs
+// per CU as two 128 x 128 workgroups and run a full round in 0.93-1.0 of the pair's time; but where the last round leaves
+// a CU one 128 x 128 workgroup, that one runs alone and ends sooner, and a 256-wide tile does not.  They win where K is long
+// or cut into many planes.  Contraction alone, 128 x 128 -> 256 x 128, over 9 layer widths and 50 row counts of 513..4096:
+//   K >= 12288, last round at least half filled: -4 to +11 %, +1.5 % on average (4096 rows x 4096 x 14336 449 -> 435 us, 1600
+//     rows 236 -> 213)
+//   8 planes and more, whole bands, and one round more than half filled or whole rounds: -1.5 to +7.8 % (4096 rows x 4096 x
+//     4096 164 -> 157 us, 1450 rows 78 -> 75)
+//   the rest: -15 to +3 % (1664 rows x 6144 x 4096 115 -> 130 us, 4096 x 2560 x 1536 56 -> 64, 3000 x 13824 x 2560 235 -> 260)
+bool fold_tiles(int tiles, int S, int N, int K) {
+    if (N % 256) return false;
+    const int last = tiles % 512;                // 0: whole rounds
+    if (K >= 12288) return tiles > 256 && (last == 0 || last >= 256);
+    return S >= 8 && K >= 4096 && N % (256 * kBand) == 0 && (last == 0 || last >= 496 || (tiles < 512 && last > 256));
+}
+
 }  // namespace
 
 GemmPath gemm_path(int dtype, int rows, int N, int K) {
@@ -427,15 +443,11 @@ GemmPath gemm_path(int dtype, int rows, int N, int K) {
         // Tile height: two 4-wave workgroups fit a CU, so 512 tiles run at a time and the launch takes
         // ceil(tiles / 512) rounds of a duration that grows with the tile height.  A taller
         // tile that saves a round wins (2112 rows x 4096 columns: 544 tiles of 128 rows need
-        // two rounds, 448 tiles of 160 rows one).  Where planes are folded, 256 W rows x 128 X rows on
-        // eight waves with a ring of three hold the same outputs per CU as two 128 x 128 workgroups and
-        // run a round in 0.93-0.96 of their time (down at 1300 / 3000 / 4096 rows 224 / 426 / 457 -> 217 /
-        // 404 / 435 us); a round of 160-row tiles takes 1.29 of it (down at 2112 rows: 283 us, one round,
-        // against 407 us, two).  The summation order of an output element does not depend on the tile.
+        // two rounds, 448 tiles of 160 rows one).  The summation order of an output element does not depend on the tile.
         const long rounds128 = (nt * ((rows + 127) / 128) + 511) / 512, rounds160 = (nt * ((rows + 159) / 160) + 511) / 512;
         p.kind = GEMM_MANY; p.bn = 128; p.mt = rounds160 * 129 < rounds128 * 100 ? 160 : 128;
         p.resident = 512;
-        if (p.folded && p.mt == 128 && N % 256 == 0) { p.bn = 256; p.resident = 256; }
+        if (p.folded && p.mt == 128 && fold_tiles(nt * ((rows + 127) / 128), S, N, K)) { p.bn = 256; p.resident = 256; }
         p.workgroups = (N / p.bn) * ((rows + p.mt - 1) / p.mt);
         return p;
     }

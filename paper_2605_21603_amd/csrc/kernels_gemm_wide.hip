@@ -7,7 +7,7 @@ namespace dyn {
 
 // 256 W rows x 128 X rows, planes folded in registers, a ring of three stages (144 KB): the same outputs
 // per CU as two 128 x 128 workgroups with a quarter less operand traffic into LDS and two stages
-// in flight instead of one, on the hand-laid-out loop.  Bands as in gemm_bf16_kernel.  (Measured: gemm_path.)
+// in flight instead of one, on the hand-laid-out loop.  Bands as in gemm_bf16_kernel.  (Where they pay, measured: fold_tiles.)
 __global__ __launch_bounds__(512, 1) void gemm_fold_kernel(const bf16_t *__restrict__ X, int ldx, const bf16_t *__restrict__ W,
                                                            const bf16_t *__restrict__ R, bf16_t *__restrict__ Y, int M, int N, int K,
                                                            int S) {

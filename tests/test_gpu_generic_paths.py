@@ -126,17 +126,21 @@ def test_expert_tiles_follow_the_rows_each_expert_gets(tokens, pull):
     check_against_oracle(w, data, y, k, v)
 
 
-# gate/up of 5376 columns: 21 n tiles of 256, bands of 8, 8 and 5 (42 tiles of 128 beside 160 rows: five of 8, one of 2), the
-# last m tile with 57, 1, 92 and 1 rows; 20480 columns: ten whole bands of 256-wide tiles, and twenty beside 160 rows
-@pytest.mark.parametrize("hidden,inter,rows,bn", [(1024, 2688, 825, 256), (1024, 2688, 1025, 256), (1024, 2688, 1500, 256), (1024, 2688, 1537, 128),
-                                                  (1024, 2688, 2049, 256), (1280, 10240, 1025, 256), (1280, 10240, 1281, 128)])
-def test_folded_launch_in_bands_matches_smaller_launches(hidden, inter, rows, bn):
+# The projection of N columns and depth K: 42 n tiles of 128 (bands of eight, the last of two) with 57, 1, 92 and 97 rows in
+# the last m tile; 160 of 128, whole bands; 9 n tiles of 256 (bands of eight and one) with 1 and 57 rows in the last m tile;
+# 8 of 256, one whole band
+@pytest.mark.parametrize("hidden,inter,rows,N,K,bn,mt", [
+    (1024, 2688, 825, 5376, 1024, 128, 128), (1024, 2688, 1025, 5376, 1024, 128, 128), (1024, 2688, 1500, 5376, 1024, 128, 128),
+    (1024, 2688, 1537, 5376, 1024, 128, 160), (1280, 10240, 1281, 20480, 1280, 128, 160), (2304, 12288, 1793, 2304, 12288, 256, 128),
+    (2304, 12288, 1977, 2304, 12288, 256, 128), (4096, 1024, 2100, 2048, 4096, 256, 128)])
+def test_folded_launch_in_bands_matches_smaller_launches(hidden, inter, rows, N, K, bn, mt):
     """Rows of one many-row launch (planes folded, bands over the XCDs, the last band narrower than the others where
     the width is no multiple of it) have the bits of the same rows cut into launches of other tiles, and a
     sample of them, computed alone, is the oracle's."""
-    p, few = gemm_path(rows, 2 * inter, hidden), gemm_path(40, 2 * inter, hidden)
-    assert p.folded and p.split > 1 and p.bn == bn and p.mt == (128 if bn == 256 else 160) and not few.folded
-    assert (2 * inter // bn) % 8 == {(5376, 256): 5, (5376, 128): 2}.get((2 * inter, bn), 0)
+    assert (N, K) in ((2 * inter, hidden), (hidden, inter))
+    p, few = gemm_path(rows, N, K), gemm_path(40, N, K)
+    assert p.folded and p.split > 1 and (p.bn, p.mt) == (bn, mt) and not few.folded
+    assert (N // bn) % 8 == {5376: 2, 2304: 1}.get(N, 0)
     w = workload("fold", "bf16", hidden, 4, 1, 128, inter, [(1, 1 + i % 3) for i in range(rows)], seed=60)
     w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, 200, rows))
     data = gen.generate(w)
