@@ -88,7 +88,7 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
                        const GemmEpilogue *ep = nullptr);
 
 // A few rows (at most 8), planes summed in the workgroup (kernels_gemm_rows.hip; launch_gemm calls it).
-bool gemm_rows16_supported(int rows, int S);
+bool gemm_rows16_supported(int rows, int N, int K, int S);
 hipError_t launch_gemm_rows16(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int S);
 // Many rows, split-K planes folded in registers, 256 x 128 tiles (kernels_gemm_wide.hip; launch_gemm calls it).
 hipError_t launch_gemm_fold(int grid, hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N,

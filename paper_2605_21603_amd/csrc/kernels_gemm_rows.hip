@@ -70,12 +70,23 @@ __global__ __launch_bounds__(64 * S) void gemm_rows16_kernel(const bf16_t *__res
     *reinterpret_cast<uint2 *>(Y + at) = ov;
 }
 
-// The kernel takes 16 rows, but every workgroup reads all of X for its 16 W rows, so what it costs grows with the rows
-// (4096-wide layer, down projection: 1 row 21.6 + 4.1 us of the launch that sums planes -> 23.6, 13 rows 22.0 + 4.2 -> 29.3).
-// Whole step, 128-row tiles with planes against this: 2 / 4 / 6 / 8 / 10 / 13 rows 137.3 / 136.4 / 137.0 / 139.0 / 140.0 / 156.2
-// -> 130.3 / 132.1 / 133.8 / 137.1 / 139.1 / 157.8 us; a 2048-wide layer's 1 / 4 / 8 / 14 rows 73.3 / 74.3 / 74.6 / 77.7 -> 68.3 /
-// 70.7 / 72.9 / 76.8 us.  Past 8 rows the difference is within two runs of one side.
-bool gemm_rows16_supported(int rows, int S) { return rows <= 8 && (S == 2 || S == 4 || S == 8); }
+// Where the kernel is taken.  Every workgroup reads all of X for its 16 W rows, so what it saves shrinks with the rows, and
+// with workgroups that are more than the CUs but do not fill them twice.  Microseconds saved by one projection inside a step
+// of one layer / of three (whose weights leave the caches in between), 14 layer widths:
+//   at most 256 workgroups, 2 or 4 planes: 1, 4, 8 rows x 2560 x 6912 2.7/3.6, 4.3/2.5, 2.9/2.1, x 3072 x 3072 2.3/3.2, 1.8/2.7, 1.8/2.0,
+//     x 4096 x 11008 4.8/4.5, 5.6/5.4, 4.1/5.0, the least x 2048 x 2048 0/1.6, 0.7/1.2, 0.3/0.9
+//   at most 256, 8 planes: 1, 4, 6, 8 rows x 4096 x 4096 1.9/1.7, 1.2/2.2, 1.7/2.1, 1.8/1.4, x 4096 x 14336 1.8/1.7, 1.1/0.2, 1.5/0, 0.2/-1.5,
+//     x 3072 x 8192 1.5/1.1, 0.5/-0.1, 0.6/0, -0.3/-1.5, x 2048 x 5632 2.0/1.2, 0.8/0.2, 1.6/-0.8, 0.8/-1.2
+//   257 to 511: 1, 2, 4 rows x 6144 x 4096 2.7/-0.5, 2.5/-0.5, 0.2/-1.7, x 5120 x 5120 3.4/1.5, 0.6/2.0, 0.5/0.1, x 5120 x 3072 -0.2/-0.1, -0.1/0,
+//     -1.2/-0.9, x 4608 x 3584 -0.6/-0.6, -1.6/-1.6, -1.4/-1.1; with long K x 5120 x 13824 0.5/-1.1, -2.0/-1.6, -3.7/-3.5
+//   512 and more: three layers, 1, 5, 8 rows x 8192 x 8192 3.2, 2.8, 3.0, x 10240 x 8192 12, 11, 10, x 8192 x 28672 4.5, 2.3, -7.2, x 8192 x 6144
+//     1.3, 0.1, -1.5; with 2 planes x 12288 x 4096 -0.3, 0, -1.4
+bool gemm_rows16_supported(int rows, int N, int K, int S) {
+    if (rows > 8 || (S != 2 && S != 4 && S != 8)) return false;
+    const int wg = N / 16;
+    if (wg <= 256) return S < 8 || rows <= 6 || (long)rows * K <= 8L * N;
+    return wg < 512 ? rows <= 2 && K < 2 * N : S > 2 && rows <= 5;
+}
 
 hipError_t launch_gemm_rows16(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int S) {
 #define DYN_ROWS(SC) hipLaunchKernelGGL(gemm_rows16_kernel<SC>, dim3(N / 16), dim3(64 * SC), 0, s, (const bf16_t *)X, ldx, (const bf16_t *)W, \

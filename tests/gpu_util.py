@@ -32,6 +32,11 @@ def gemm_path(rows, N, K):
     return p
 
 
+def planes_in_workgroup(rows, N, K):
+    """Whether the library sums a bf16 projection's planes inside the workgroup."""
+    return B.lib()._ZN3dyn21gemm_rows16_supportedEiiii(rows, N, K, gemm_path(rows, N, K).split) & 0xff != 0
+
+
 def row_rel_err(got: np.ndarray, ref: np.ndarray) -> float:
     """max over rows of max_i |got - ref| / max_i |ref| (element-wise relative error is
     meaningless next to zeros)."""
