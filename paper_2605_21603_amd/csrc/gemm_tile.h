@@ -79,7 +79,16 @@ __device__ __forceinline__ void settle(f32x4 (&acc)[NA][NB]) {
 // here to about as many W rows as X rows (32 or 64 tiles run on it at a time).  4096 rows, n-tile order -> bands
 // of 8 (4 and 16 lose 1-4 % of it): qkv 252 -> 208, o 183 -> 167, down 528 -> 470, gate/up 763 -> 753 us; 3000 rows: down
 // 449 -> 428 us; up to 2112 rows nothing changes.
+// A weight matrix of more than 256 MiB does not stay in the last-level cache between two passes over it, and a band
+// whose m tiles do not all run at once makes them: there n-tile order is the better one up to 2400 rows, and at every number
+// of rows beyond 512 MiB (bands -> n-tile order: 1800 rows x 8192 x 28672 906 -> 805 us, 850 x 27648 x 5120 278 -> 264, 3000 x 57344
+// x 8192 2340 -> 2295; against it 2400 x 32768 x 6144 773 -> 787; past the line 4096 x 32768 x 6144 1222 -> 1275, 3600 x 8192 x
+// 28672 1677 -> 1850).
 constexpr int kBand = 8;
+__device__ __forceinline__ int gemm_band(int rows, int N, int K) {
+    const size_t w = (size_t)N * K;
+    return (w > (size_t)1 << 27 && rows <= 2400) || w > (size_t)1 << 28 ? 1 : kBand;
+}
 inline int gemm_band_grid(int n_tiles, int m_tiles) { return (n_tiles * m_tiles + 7) / 8 * 8; }
 
 // Tile of this workgroup in a launch whose tiles cover the whole depth, in bands.  Workgroup ids are dealt

@@ -162,7 +162,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && (BN + MT) * ROWB * NS <= 72 * 
     const int u = blockIdx.x % 8, v = blockIdx.x / 8;
     int m_tile, ns;
     if (BANDS) {
-        if (!band_tile(N / BN, m_tiles, kBand, ns, m_tile)) return;
+        if (!band_tile(N / BN, m_tiles, gemm_band(M, N, K), ns, m_tile)) return;
     } else {
         // Tiles that share W rows (the m tiles of one (n tile, plane)) get ids 8 apart: same XCD,
         // same L2, adjacent in time.

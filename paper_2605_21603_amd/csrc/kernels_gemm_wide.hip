@@ -13,7 +13,7 @@ __global__ __launch_bounds__(512, 1) void gemm_fold_kernel(const bf16_t *__restr
                                                            int S) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     int n_tile, m_tile;
-    if (!band_tile(N / 256, (M + 127) / 128, kBand, n_tile, m_tile)) return;
+    if (!band_tile(N / 256, (M + 127) / 128, gemm_band(M, N, K), n_tile, m_tile)) return;
     gemm_tile<256, 128, true, 3, false, 8, true>(lds, X, ldx, W, R, Y, N, nullptr, 0, M, N, K, S, nullptr, 1, false, n_tile, 0, m_tile * 128);
 }
 

@@ -152,6 +152,22 @@ def test_folded_launch_in_bands_matches_smaller_launches(hidden, inter, rows, N,
     check_against_oracle(sub, d2, y2, k2, v2)
 
 
+def test_projections_of_very_large_weights_walk_n_tiles_in_order():
+    """Weights of more than 256 MiB (gate/up 33280 x 8192, down 8192 x 16640): bands of one n tile, on 256 x 256 and on
+    128 x 160 tiles.  The bits of the rows in smaller launches, and the oracle's values on a sample."""
+    rows, hidden, inter = 1100, 8192, 16640
+    p, q = gemm_path(rows, 2 * inter, hidden), gemm_path(rows, hidden, inter)
+    assert hidden * inter > 1 << 27 and (p.bn, p.mt, p.kind) == (256, 256, 2) and (q.bn, q.mt, q.kind) == (128, 160, 3)
+    w = workload("big", "bf16", hidden, 4, 1, 128, inter, [(1, 1 + i % 3) for i in range(rows)], seed=61)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, 200, rows))
+    data = gen.generate(w, device="cuda:0")
+    y, _, _ = both_schedules(w, data)
+    sub, d2 = gen.extract_sequences(w, data, [0, 255, 256, 511, 700, rows - 1])
+    y2, k2, v2 = GpuRun(sub, d2).run(B.sequential())
+    assert torch.equal(y2, y[torch.as_tensor(d2["rows"])])
+    check_against_oracle(sub, d2, y2, k2, v2)
+
+
 @pytest.mark.parametrize("rows", [65, 129, 300, 500])
 def test_narrow_projections_on_lower_tiles_match_smaller_launches(rows):
     """Outputs so narrow that their (n tile, plane) pairs leave CUs idle take lower tiles; the rows keep the bits they
