@@ -17,6 +17,8 @@
 // percent.  Softmax is online per tile of two pages in the exp2 domain with the running
 // max shared by the four lanes of a head; the partial (m, l, o) of the chunk goes to the
 // split-KV arrays and attn_combine_kernel merges chunks in order.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -35,7 +37,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 constexpr int HD = 128, PS = 16, TILE_PAGES = 2;
 constexpr int kPersistentGroups = 512;   // two 4-wave workgroups for each of the 256 CUs
 
-// Persistent waves: in round k wave w of the launch takes (entry, kv head) pair k * n_waves + w,
+// Persistent waves: in round k wave w of the launch (numbered by gw below) takes (entry, kv head) pair k * n_waves + w,
 // in odd rounds k * n_waves + (n_waves - 1 - w): a snake over a list that is ordered largest first
 // (attn_plan_kernel), so a wave that drew the largest item of one round draws the smallest of the next.
 // A pair is walked two tiles (four pages) at a time through two register buffers, and when a
@@ -71,7 +73,12 @@ __global__ __launch_bounds__(256, NQG == 1 ? 2 : 1) void attn_mfma_kernel(const 
     const int col_tok = lr / G, col_head = lr % G;   // MFMA column lr of set q = (token q * TG + col_tok, q head col_head)
     const float sscale = 1.4426950408889634f / sqrtf((float)HD);   // log2(e) / sqrt(d)
 
-    const int gw = blockIdx.x * 4 + wave;
+    // With few rounds the waves that have work are dealt over the workgroups first: what a CU gets from memory is bounded
+    // per CU, and four items side by side on one take twice as long as on four (one token behind 2900 positions, 96
+    // items: 19.4 -> 9 us; 13 tokens behind 3000, 1248 items: 39 -> 30; 40 behind 2000, 2.5 rounds: 66 -> 63).  From
+    // four rounds on all of memory is busy either way, and a chunk's kv heads stay side by side (200 tokens up to 8000
+    // positions: 604 us, dealt over the workgroups 608).
+    const int gw = n_items < 4 * n_waves ? wave * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x * 4 + wave;
     int round = 0;
     auto item_at = [&](int k) { return k * n_waves + ((k & 1) ? n_waves - 1 - gw : gw); };
     int item = item_at(0);
@@ -289,7 +296,7 @@ hipError_t launch_attention(int dtype, const void *qkv, const int32_t *seq_of_to
     // every workgroup of a persistent launch has to be resident at once (the work is dealt out by
     // wave index): two per CU of the partition the stream runs on
     const int groups = sh.n_cus > 0 && 2 * sh.n_cus < kPersistentGroups ? 2 * sh.n_cus : kPersistentGroups;
-    const int grid = (int)((max_items + 3) / 4 < groups ? (max_items + 3) / 4 : groups);
+    const int grid = (int)std::min<long>(max_items, groups);        // a workgroup per item while they are few
     if (any_single) {
         hipLaunchKernelGGL(attn_mfma_kernel<1>, dim3(grid), dim3(256), 0, s, (const bf16_t *)qkv, seq_of_token,
                            pos_of_token, block_table, (const bf16_t *)k_cache, (const bf16_t *)v_cache, (bf16_t *)out, ld_out, part_o,
