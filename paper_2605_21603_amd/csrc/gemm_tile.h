@@ -112,7 +112,7 @@ template <int BN, int MT, bool INREG, int NS, bool GATED, int NW, bool PIPE>
 __device__ __forceinline__ void gemm_tile(unsigned char *lds, const bf16_t *__restrict__ X, int ldx, const bf16_t *__restrict__ W,
                                           const bf16_t *__restrict__ R, bf16_t *__restrict__ Y, int ldy, float *__restrict__ P,
                                           size_t plane_stride, int M, int N, int K, int S, const int32_t *list, int x_div,
-                                          bool planes_only, int n_tile, int sp, int m0) {
+                                          bool planes_only, int n_tile, int sp, int m0, int expert = 0) {
     constexpr int ROWS = BN + MT;                   // rows of a stage buffer: W rows, then X rows
     constexpr int WMW = (NW == 8 && BN < MT) ? 4 : 2;   // waves along m
     constexpr int WNW = NW / WMW, RW = BN / WNW;     // waves along n; W rows per wave column
@@ -150,9 +150,12 @@ __device__ __forceinline__ void gemm_tile(unsigned char *lds, const bf16_t *__re
     // at the same time then read different column offsets of their 8 KB-pitched weight rows, which
     // spreads the requests over the memory channels; tiles of one group keep reading the same X
     // columns together, so X stays shared in L2.  The order depends on (N, K, n tile) only, never
-    // on the number of rows, so every schedule adds the same terms in the same order.
+    // on the number of rows, so every schedule adds the same terms in the same order.  Experts rotate one
+    // against the next: a down projection's 32 n tiles are one group, and all 256 workgroups of eight experts'
+    // read the same columns of rows 28 KB apart (8 experts x 4096 x 14336, two of them per token: 4, 32, 128 tokens 142 -> 128,
+    // 180 -> 169, 187 -> 175 us; 256 tokens 194 -> 192; gate/up, seven groups of n tiles, the same within 1 %).
     const int rot_group = (GATED ? n_tile * (BN / 2) / 64 : n0 / 128) / kRotGroup;   // by output column, the same for every tile shape
-    const int rot = (int)(((unsigned)rot_group * kRotStep) % (unsigned)plane_stages);
+    const int rot = (int)((unsigned)(rot_group + expert) * kRotStep % (unsigned)plane_stages);
     int iss_w = 0, iss_base = 0;                       // next stage to issue: index inside its plane, plane's first stage
     unsigned char *iss_buf = lds;                      // the pending stage's ring buffer and k offset (issue_begin / issue_one)
     int iss_kst = 0;

@@ -181,21 +181,22 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && (BN + MT) * ROWB * NS <= 72 * 
         ns = blockIdx.x % per_m;
     }
     const int32_t *list = nullptr;
+    int expert = 0;
     const int SG = INREG ? 1 : S;                      // planes spread over the grid
     if (grouped) {                                     // (expert, n tile, plane); rows come from the expert's list
         const int per_group = (N / BN) * SG;
         if (ns >= per_group * gr.n_groups) return;
-        const int e = ns / per_group;
-        ns -= e * per_group;
-        M = gr.counts[e];
+        expert = ns / per_group;
+        ns -= expert * per_group;
+        M = gr.counts[expert];
         if (m_tile * MT >= M) return;
-        list = gr.lists + (size_t)e * gr.cap;
-        W += (size_t)e * gr.w_stride;
+        list = gr.lists + (size_t)expert * gr.cap;
+        W += (size_t)expert * gr.w_stride;
     } else if (ns >= (N / BN) * SG) {
         return;
     }
     gemm_tile<BN, MT, INREG, NS, GATED, NW, (MT >= 256)>(lds, X, ldx, W, R, Y, ldy, P, plane_stride, M, N, K, S, list, gr.x_div, gr.force_planes,
-                                                         ns / SG, ns % SG, m_tile * MT);   // the hand-laid-out loop pays from 256-row tiles on
+                                                         ns / SG, ns % SG, m_tile * MT, expert);   // the hand-laid-out loop pays from 256-row tiles on
                                                                                            // (128 x 128 tiles: 1-2 % slower with it)
 }
 

@@ -70,7 +70,7 @@ __global__ __launch_bounds__(512, 1) void gemm_experts_wide_kernel(const bf16_t 
     // the last m tile may hold fewer rows than it has room for, none below it is short: ceil(rows / n_m) <= 64 * units
     const int m0 = m_tile * units * 64;
     if (m0 >= rows) return;
-#define DYN_BODY(MT, NS) gemm_tile<kExpertsBN, MT, false, NS, GATED, 8, true>(lds, X, ldx, We, nullptr, Y, ldy, P, 0, rows, N, K, 1, list, gr.x_div, gr.force_planes, n_tile, 0, m0)
+#define DYN_BODY(MT, NS) gemm_tile<kExpertsBN, MT, false, NS, GATED, 8, true>(lds, X, ldx, We, nullptr, Y, ldy, P, 0, rows, N, K, 1, list, gr.x_div, gr.force_planes, n_tile, 0, m0, e)
     if (units == 4) DYN_BODY(256, 2);
     else if (units == 3) DYN_BODY(192, 2);
     else if (units == 2) DYN_BODY(128, 3);
