@@ -23,24 +23,27 @@ constexpr int kMaxChunkTokens = 512;
 // positions share an aligned block of 4 * (16 / G) (G = q heads per kv head), all q heads of the kv
 // head at once, so a key is fetched once per group instead of once per (token, q head).  The products are
 //   S[16 pos, 16 cols]  = K_tile Q^T    (fp32 storage: 16x16x4 fp32 MFMA; bf16: 16x16x32 bf16 MFMA)
-//   O^T[d, 16 cols]    += V_tile^T P    (16x16x4 fp32 MFMA, bf16 values widened)
-// with a column per (token, q head).  Scores, probabilities and sums stay in fp32 throughout: the
-// probabilities are operands of an fp32 product, which at 256 flop per clock and CU is still several
-// times what the cache pages arrive at.  The D layout of the first product (lane: column l % 16,
-// positions 4 (l / 16) + r) is the B layout of the second if its r-th product takes position 4 (l / 16) + r
-// as its k index l / 16, and a lane's V operand is then four consecutive positions of one head-dim row.
+//   O^T[d, 16 cols]    += V_tile^T P    (fp32 storage: 16x16x4 fp32 MFMA; bf16: three 16x16x16 bf16 MFMAs)
+// with a column per (token, q head).  Scores, probabilities and sums keep 24 bits throughout: beside bf16 values a
+// probability goes in as the three bf16 numbers it is the sum of.  The D layout of the first product (lane: column l % 16,
+// positions 4 (l / 16) + r) is the B layout of the second (fp32: if its r-th product takes position 4 (l / 16) + r
+// as its k index l / 16), and a lane's V operand is then four consecutive positions of one head-dim row.
 // A group of one token (decode) gives each of the four waves a quarter of the chunk's positions and
 // merges the four in wave order through LDS (without the quarters a decode chunk takes half as long again); a
 // group of several tokens gives each wave its own set of 16 columns, and the waves walk the same
 // positions (quarters there: a 300-token prompt + 40 decodes 67 against 51 us).  Which
 // of the two a token is part of depends on its sequence only, never on the schedule.
-// What bounds it is latency - rows, then block table, then pages - so everything that does not wait for one
-// of these is loaded beside it, two tiles of 16 * TP positions are in flight per wave, and the block table is
-// read with scalar loads a tile ahead (a vector load of a page id waits for every page load issued before it).
-// Measured against the one-wave-per-(token, q head, chunk) form below, the attention
-// operator under events: bf16, 64-wide heads, 300-token prompt + 40 decodes at 64..2048 1690 -> 58 us; fp32, 64-wide, 201-token
-// prompt + 24 decodes 250 -> 29 us, 4 tokens behind 128 positions 34 -> 15 us; bf16, 128-wide, 32-position pages, 13
-// decodes at 200..3000 307 -> 43 us.
+// What bounds it is latency - rows, then block table, then pages - and the instructions around a chunk's few tiles
+// (with every page in L2 40 decodes of 64-wide heads take 34.6 of 35.5 us), so everything that does not wait for one
+// of these is loaded beside it, two tiles of 16 * TP positions are in flight per wave, the block table is
+// read with scalar loads a tile ahead (a vector load of a page id waits for every page load issued before it), and
+// nothing is divided (TileRule).  The items that exist are a fraction of the (chunk, kv head, token) grid over the
+// block table's width - one in twelve for a prompt beside decodes - and a workgroup without one still takes a place and two
+// loads' latency, so from 512 workgroups on they are counted in the kernel and dealt out (TileList).  The operator under events,
+// dense grid -> dealt out -> without divisions, in the exp2 domain -> V by bf16 products: bf16, 64-wide heads, 300-token
+// prompt + 40 decodes at 64..2048 55 -> 37.5 -> 35 -> 32.7 us, 40 decodes alone 35.5 -> 35 -> 33 -> 30.3; bf16, 128-wide,
+// 32-position pages, 13 decodes at 200..3000 43 -> 35 -> 33.4 -> 32.7, at 3000 each (no empty workgroups) 47.3 -> 50.8 -> 49.2
+// -> 47.1; fp32, 64-wide, 201-token prompt + 24 decodes 31.4 -> 25.6 -> 25.1.
 // Four consecutive outputs, rounded to the storage type.
 __device__ __forceinline__ void store4(float *y, f32x4 v) { *reinterpret_cast<f32x4 *>(y) = v; }
 __device__ __forceinline__ void store4(bf16_t *y, f32x4 v) {
@@ -50,38 +53,94 @@ __device__ __forceinline__ void store4(bf16_t *y, f32x4 v) {
     *reinterpret_cast<u32x2 *>(y) = w;
 }
 
+// Sizes that every item divides by, with their reciprocals (a division is some 35 vector instructions, and with ten of them
+// per item an item was more arithmetic around its keys than on them).
+struct TileRule {
+    double per_block, per_chunk, per_kv;
+    int G, TG, block, chunk, g_mul;                                // q heads per kv head, tokens per set of columns, positions per block and per chunk
+};
+// a / b for 0 <= a < 2^31 and per_b = 1 / b: a + 1/2 is at least 1 / (2 b) away from a multiple of b, the product's error below a / b 2^-51.
+__device__ __forceinline__ int quotient(int a, double per_b) { return (int)(((double)a + 0.5) * per_b); }
+
+// What a workgroup serves: a query group's last token row, its chunk and kv head.
+struct TileItem { int t_last, c, g, seq, pos, row_seq, row_pos; };   // + that row's sequence and position; lane l's: the l-th row before it
+
+// The n-th of the items that exist, in token order (a group's chunks in a row, kv heads fastest), for up to kListRows
+// rows: every thread counts the chunks of the groups that end in its kListRows / 256 rows.
+constexpr int kListRows = 1024, kRowsPerThread = kListRows / 256;
+struct TileList {
+    int upto[kRowsPerThread], before, total;                       // chunks up to and with each of the thread's rows, before its first, of all rows
+
+    __device__ __forceinline__ void build(const int32_t *__restrict__ seq_of_token, const int32_t *__restrict__ pos_of_token, int rows,
+                                          const TileRule &rule, int *scratch) {
+        const int r0 = threadIdx.x * kRowsPerThread;
+        int seq[kRowsPerThread + 1], pos[kRowsPerThread + 1];
+#pragma unroll
+        for (int i = 0; i <= kRowsPerThread; ++i) {
+            const int r = min(r0 + i, rows - 1);
+            seq[i] = seq_of_token[r];
+            pos[i] = pos_of_token[r];
+        }
+        int n = 0;
+#pragma unroll
+        for (int i = 0; i < kRowsPerThread; ++i) {
+            const bool ends = r0 + i + 1 >= rows || seq[i + 1] != seq[i] || quotient(pos[i + 1], rule.per_block) != quotient(pos[i], rule.per_block);
+            if (r0 + i < rows && ends) n += quotient(pos[i], rule.per_chunk) + 1;
+            upto[i] = n;
+        }
+        int incl = n;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int x = __shfl_up(incl, off, 64);
+            if ((int)(threadIdx.x & 63) >= off) incl += x;
+        }
+        if ((threadIdx.x & 63) == 63) scratch[threadIdx.x >> 6] = incl;
+        __syncthreads();
+        before = incl - n;
+        total = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            if (w < (int)(threadIdx.x >> 6)) before += scratch[w];
+            total += scratch[w];
+        }
+    }
+    // The thread that counted item n says which it is; every thread of the workgroup calls this.
+    // `scratch`: two words that the previous call did not use.
+    __device__ __forceinline__ void find(int n, int n_kv, const TileRule &rule, int *scratch, int &t_last, int &c, int &g) const {
+        const int entry = quotient(n, rule.per_kv), mine = entry - before;
+        if (mine >= 0 && mine < upto[kRowsPerThread - 1]) {
+            int i = 0, base = 0;
+#pragma unroll
+            for (int k = 0; k + 1 < kRowsPerThread; ++k)
+                if (mine >= upto[k]) { i = k + 1; base = upto[k]; }
+            scratch[0] = threadIdx.x * kRowsPerThread + i;
+            scratch[1] = mine - base;
+        }
+        __syncthreads();
+        t_last = __builtin_amdgcn_readfirstlane(scratch[0]);
+        c = __builtin_amdgcn_readfirstlane(scratch[1]);
+        g = n - entry * n_kv;
+    }
+};
+
 template <typename T, int HD, int TP>
-__global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_kernel(const T *__restrict__ qkv, const int32_t *__restrict__ seq_of_token,
-                                                        const int32_t *__restrict__ pos_of_token,
-                                                        const int32_t *__restrict__ block_table, const T *__restrict__ k_cache,
-                                                        const T *__restrict__ v_cache, T *__restrict__ out, int ld_out,
-                                                        float *__restrict__ part_o, float *__restrict__ part_ml, AttnShape sh,
-                                                        int rows, int y0, int y1) {
+__device__ __forceinline__ void attn_tile(const T *__restrict__ qkv, const int32_t *__restrict__ block_table, const T *__restrict__ k_cache,
+                                          const T *__restrict__ v_cache, T *__restrict__ out, int ld_out, float *__restrict__ part_o,
+                                          float *__restrict__ part_ml, const AttnShape &sh, const TileRule &rule, const TileItem &item,
+                                          float (*merge_o)[16][(HD < 128 ? HD : 128) + 4], float (*merge_ml)[16][2]) {
     constexpr bool F32 = sizeof(T) == 4;
     constexpr int NK = F32 ? HD / 16 : HD / 32, ND = HD / 16;      // 16-byte K operands and 16-row V operands of a lane
     constexpr int MD = HD < 128 ? HD : 128;                        // head-dim indices merged per round
-    __shared__ float merge_o[4][16][MD + 4];
-    __shared__ float merge_ml[4][16][2];
     typedef typename std::conditional<F32, f32x4, u32x2>::type vload_t;   // four positions of V
     const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
-    // (chunk, kv head, token), tokens fastest.  Only a group's first token has work, and few sequences reach the later
-    // chunks: workgroup ids, which go to the 8 XCDs in turn, are rotated inside every eight by their
-    // higher bits so that the ones with work, however regularly spaced, spread over all XCDs.
-    const unsigned wg = (blockIdx.x & ~7u) | ((blockIdx.x + (blockIdx.x >> 3) + (blockIdx.x >> 6)) & 7u);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int t = (int)(wg % rows), y = y0 + (int)(wg / rows);     // y: (chunk, kv head) in [y0, y1) of this launch
-    const int g = (int)((unsigned)y % (unsigned)sh.n_kv), c = (int)((unsigned)y / (unsigned)sh.n_kv);
-    if (y >= y1) return;
-    const int G = sh.n_q / sh.n_kv, TG = 16 / G, tg = 4 * TG;      // tokens per set of columns, per group
-    const int col_tok = lr / G, col_head = lr % G;                 // this lane's column: a token of the wave's set and a q head
-    const int s = seq_of_token[t], p0 = pos_of_token[t];
-    const int before = t > 0 ? t - 1 : 0, s_before = seq_of_token[before], p_before = pos_of_token[before];
-    const int row = min(t + lane, rows - 1), row_seq = seq_of_token[row], row_pos = pos_of_token[row];
-    if (t > 0 && s_before == s && p_before / tg == p0 / tg) return;                            // not the first token of its group
-    const int n_tok = __popcll(__ballot(lane < tg && t + lane < rows && row_seq == s && row_pos / tg == p0 / tg));
-    const int n_keys = __builtin_amdgcn_readlane(row_pos, n_tok - 1) + 1;                      // keys the group's last token attends
-    const int ps = sh.page_size, ct = sh.chunk_pages * ps, j0 = c * ct;
-    if (j0 >= n_keys) return;
+    const int g = item.g, c = item.c;
+    const int G = rule.G, TG = rule.TG, tg = rule.block;           // tokens per set of columns, per group
+    const int col_tok = (lr * rule.g_mul) >> 16, col_head = lr - col_tok * G;   // this lane's column: a token of the wave's set and a q head
+    const int s = item.seq, p_last = item.pos, row_seq = item.row_seq, row_pos = item.row_pos;
+    const int n_tok = __popcll(__ballot(lane < tg && lane <= item.t_last && row_seq == s && quotient(row_pos, rule.per_block) == quotient(p_last, rule.per_block)));
+    const int t = item.t_last - n_tok + 1, n_keys = p_last + 1;    // the group's first token; keys its last token attends
+    const int ps = sh.page_size, ct = rule.chunk, j0 = c * ct;
     const int j1 = min(j0 + ct, n_keys);
     const bool single = n_tok == 1;
     const int32_t *bt = block_table + (size_t)s * sh.max_pages_per_seq;
@@ -89,7 +148,7 @@ __global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_
 
     const int set0 = single ? 0 : wave * TG;                       // first token of the wave's columns
     const bool live = col_tok < TG && set0 + col_tok < n_tok;
-    const int col_pos = __shfl(row_pos, set0 + min(col_tok, TG - 1), 64);                      // every lane takes part
+    const int col_pos = __shfl(row_pos, max(n_tok - 1 - set0 - min(col_tok, TG - 1), 0), 64);   // every lane takes part
     const int col_keys = live ? col_pos + 1 : 0;                   // keys the column attends
     u32x4 qf[NK];
     const T *qp = qkv + (size_t)(t + (live ? set0 + col_tok : 0)) * ((sh.n_q + 2 * sh.n_kv) * HD) + (size_t)(g * G + (live ? col_head : 0)) * HD;
@@ -98,7 +157,9 @@ __global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_
         qf[k] = *reinterpret_cast<const u32x4 *>(qp + (F32 ? k * 16 + 4 * lq : k * 32 + 8 * lq));
         if (!live) qf[k] = u32x4{0u, 0u, 0u, 0u};
     }
-    const float scale = 1.0f / sqrtf((float)HD);
+    // Scores in the exp2 domain where storage is bf16 (the running maximum of a partial too: the merge is told), in the natural one in fp32.
+    const float scale = (F32 ? 1.0f : 1.4426950408889634f) / sqrtf((float)HD);
+    auto exp_of = [](float x) { return F32 ? expf(x) : __builtin_amdgcn_exp2f(x); };
 
     // positions this wave walks, [w0, w1), in tiles of 16 * TP from w0 (a multiple of 16), and where live columns
     // begin to differ in what they see
@@ -108,7 +169,7 @@ __global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_
         w0 = j0 + min(wave * per, n_tile) * 16 * TP;
         free_keys = w1 = min(j1, w0 + per * 16 * TP);
     } else {
-        const int last = __builtin_amdgcn_readlane(row_pos, min(set0 + TG, n_tok) - 1), first = __builtin_amdgcn_readlane(row_pos, min(set0, n_tok - 1));
+        const int last = __builtin_amdgcn_readlane(row_pos, n_tok - min(set0 + TG, n_tok)), first = __builtin_amdgcn_readlane(row_pos, max(n_tok - 1 - set0, 0));
         w1 = set0 < n_tok ? min(j1, last + 1) : j0;
         free_keys = min(w1, first + 1);
     }
@@ -186,53 +247,107 @@ __global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_
         mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
         const float m_new = fmaxf(m_run, mx), m_ref = m_new == -INFINITY ? 0.f : m_new;   // a column with no key yet stays empty
-        const float alpha = expf(m_run - m_ref);
+        const float alpha = exp_of(m_run - m_ref);
         m_run = m_new;
         l_run *= alpha;
 #pragma unroll
         for (int dt = 0; dt < ND; ++dt) acc[dt] *= alpha;
+        f32x4 p[TP];
 #pragma unroll
         for (int i = 0; i < TP; ++i) {
-            f32x4 p, vf[ND];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) p[r] = expf(sv[i][r] - m_ref);
-            l_run += (p[0] + p[1]) + (p[2] + p[3]);
+            for (int r = 0; r < 4; ++r) p[i][r] = exp_of(sv[i][r] - m_ref);
+            l_run += (p[i][0] + p[i][1]) + (p[i][2] + p[i][3]);
+        }
+        // Edge tiles.  Positions past the group's last key hold stale cache bits, which must not meet their zero
+        // probabilities (0 * NaN).  A later token of the group may hold infinities or NaN of its own: as columns
+        // differ in what they see, such values are added position by position.
+        bool odd[TP];
+#pragma unroll
+        for (int i = 0; i < TP; ++i) {
+            odd[i] = false;
+            if (edge) {
+                const int nvalid = w1 - (j + 16 * i + 4 * lq);
+#pragma unroll
+                for (int dt = 0; dt < ND; ++dt) {
+                    if constexpr (F32) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            vr[B][i][dt][r] = r < nvalid ? vr[B][i][dt][r] : 0.f;
+                            odd[i] |= !(fabsf(vr[B][i][dt][r]) < INFINITY);
+                        }
+                    } else {
+                        u32x2 &v = vr[B][i][dt];
+                        v[0] &= (nvalid > 0 ? 0x0000ffffu : 0u) | (nvalid > 1 ? 0xffff0000u : 0u);
+                        v[1] &= (nvalid > 2 ? 0x0000ffffu : 0u) | (nvalid > 3 ? 0xffff0000u : 0u);
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) odd[i] |= (v[h] & 0x7f800000u) == 0x7f800000u || (v[h] & 0x7f80u) == 0x7f80u;
+                    }
+                }
+                odd[i] = __any(odd[i]);
+            }
+        }
+        auto by_position = [&](auto sub) {
+            constexpr int i = decltype(sub)::value;
 #pragma unroll
             for (int dt = 0; dt < ND; ++dt)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    if constexpr (F32) vf[dt][r] = vr[B][i][dt][r];
-                    else vf[dt][r] = __uint_as_float(r & 1 ? vr[B][i][dt][r >> 1] & 0xffff0000u : vr[B][i][dt][r >> 1] << 16);
-                }
-            if (edge) {
-                // Positions past the group's last key hold stale cache bits, which must not meet their zero
-                // probabilities (0 * NaN).  A later token of the group may hold infinities or NaN of its own: as columns
-                // differ in what they see, such values are added position by position.
-                const int nvalid = w1 - (j + 16 * i + 4 * lq);
-                bool odd = false;
-#pragma unroll
-                for (int dt = 0; dt < ND; ++dt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        vf[dt][r] = r < nvalid ? vf[dt][r] : 0.f;
-                        odd |= !(fabsf(vf[dt][r]) < INFINITY);
+                    float v;
+                    if constexpr (F32) v = vr[B][i][dt][r];
+                    else v = __uint_as_float(r & 1 ? vr[B][i][dt][r >> 1] & 0xffff0000u : vr[B][i][dt][r >> 1] << 16);
+#pragma unroll 1
+                    for (int q = 0; q < 4; ++q) {          // a loop: this is rare, and code in the way costs instruction fetches
+                        const f32x4 one = __builtin_amdgcn_mfma_f32_16x16x4f32(lq == q ? v : 0.f, p[i][r], acc[dt], 0, 0, 0);
+                        if (j + 16 * i + 4 * q + r < nk) acc[dt] = one;
                     }
-                if (__any(odd)) {
+                }
+        };
+        if constexpr (F32) {
+            static_for<0, TP>([&](auto sub) {
+                constexpr int i = decltype(sub)::value;
+                if (odd[i]) { by_position(sub); return; }
 #pragma unroll
-                    for (int dt = 0; dt < ND; ++dt)
+                for (int r = 0; r < 4; ++r)
 #pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            for (int q = 0; q < 4; ++q) {
-                                const f32x4 one = __builtin_amdgcn_mfma_f32_16x16x4f32(lq == q ? vf[dt][r] : 0.f, p[r], acc[dt], 0, 0, 0);
-                                if (j + 16 * i + 4 * q + r < nk) acc[dt] = one;
-                            }
-                    continue;
+                    for (int dt = 0; dt < ND; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[B][i][dt][r], p[i][r], acc[dt], 0, 0, 0);
+            });
+        } else {
+            // A probability is the sum of three bf16 numbers, exactly (8 bits of its 24 each, by truncation), and its
+            // products with a bf16 value are exact: three bf16 products stand for one in fp32 at 48 cycles instead of 128.
+            // (An infinite value gives NaN where a part is zero; the layer's output row is NaN behind either.)
+            u32x2 part[3][TP];
+#pragma unroll
+            for (int i = 0; i < TP; ++i) {
+                uint32_t w[3][4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    w[0][r] = __float_as_uint(p[i][r]) & 0xffff0000u;
+                    const float rest = p[i][r] - __uint_as_float(w[0][r]);
+                    w[1][r] = __float_as_uint(rest) & 0xffff0000u;
+                    w[2][r] = __float_as_uint(rest - __uint_as_float(w[1][r]));
+                }
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    part[k][i][0] = (w[k][0] >> 16) | (w[k][1] & 0xffff0000u);
+                    part[k][i][1] = (w[k][2] >> 16) | (w[k][3] & 0xffff0000u);
                 }
             }
+            bool any_odd = false;
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
+            for (int i = 0; i < TP; ++i) any_odd |= odd[i];
+            if (any_odd) {
+                static_for<0, TP>([&](auto sub) { by_position(sub); });
+            } else {
+                static_for<0, TP>([&](auto sub) {
+                    constexpr int i = decltype(sub)::value;
 #pragma unroll
-                for (int dt = 0; dt < ND; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[dt][r], p[r], acc[dt], 0, 0, 0);
+                    for (int k = 2; k >= 0; --k)
+#pragma unroll
+                        for (int dt = 0; dt < ND; ++dt)
+                            acc[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, vr[B][i][dt]), __builtin_bit_cast(s16x4, part[k][i]), acc[dt], 0, 0, 0);
+                });
+            }
         }
     };
     const std::integral_constant<int, 0> b0;
@@ -283,7 +398,7 @@ __global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_
     float M = -INFINITY;
 #pragma unroll
     for (int w = 0; w < 4; ++w) M = fmaxf(M, merge_ml[w][lr][0]);
-    const float mine = expf(m_run - (M == -INFINITY ? 0.f : M));
+    const float mine = exp_of(m_run - (M == -INFINITY ? 0.f : M));
     for (int round = 0; round < HD / MD; ++round) {
         if (round) __syncthreads();
 #pragma unroll
@@ -316,6 +431,63 @@ __global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_
                 }
             }
         }
+    }
+}
+
+// LIST: the workgroups walk the items that exist, dealt in turn; else one workgroup per (chunk, kv head, token) of the
+// dense grid, of which only a group's last token and the chunks it reaches have work.
+template <typename T, int HD, int TP, bool LIST>
+__global__ __launch_bounds__(256, HD * sizeof(T) <= 256 ? 2 : 1) void attn_tile_kernel(const T *__restrict__ qkv, const int32_t *__restrict__ seq_of_token,
+                                                        const int32_t *__restrict__ pos_of_token,
+                                                        const int32_t *__restrict__ block_table, const T *__restrict__ k_cache,
+                                                        const T *__restrict__ v_cache, T *__restrict__ out, int ld_out,
+                                                        float *__restrict__ part_o, float *__restrict__ part_ml, AttnShape sh,
+                                                        TileRule rule, int rows, int y0, int y1) {
+    __shared__ float merge_o[4][16][(HD < 128 ? HD : 128) + 4];
+    __shared__ float merge_ml[4][16][2];
+    auto item_of = [&](int t_last, int c, int g) {
+        const int row = max(t_last - (int)(threadIdx.x & 63), 0);
+        return TileItem{t_last, c, g, seq_of_token[t_last], pos_of_token[t_last], seq_of_token[row], pos_of_token[row]};
+    };
+    auto serve = [&](const TileItem &item) {
+        attn_tile<T, HD, TP>(qkv, block_table, k_cache, v_cache, out, ld_out, part_o, part_ml, sh, rule, item, merge_o, merge_ml);
+    };
+    if constexpr (LIST) {
+        __shared__ int scratch[8];
+        TileList list;
+        list.build(seq_of_token, pos_of_token, rows, rule, scratch);
+        const int n_items = list.total * sh.n_kv;
+        int n = blockIdx.x, t_last, c, g, turn = 0;
+        if (n >= n_items) return;
+        auto next = [&]() {                                        // item n; its rows' loads are in flight while the one before is served
+            turn ^= 2;
+            list.find(n, sh.n_kv, rule, scratch + 4 + turn, t_last, c, g);
+            return item_of(t_last, c, g);
+        };
+        TileItem cur = next();
+        while (true) {
+            n += gridDim.x;
+            const bool more = n < n_items;
+            TileItem nxt = cur;
+            if (more) nxt = next();
+            serve(cur);
+            if (!more) break;
+            __syncthreads();                                       // the merge arrays are free again
+            cur = nxt;
+        }
+    } else {
+        // (chunk, kv head, token), tokens fastest.  Few sequences reach the later chunks: workgroup ids, which go to
+        // the 8 XCDs in turn, are rotated inside every eight by their higher bits so that the ones with
+        // work, however regularly spaced, spread over all XCDs.
+        const unsigned wg = (blockIdx.x & ~7u) | ((blockIdx.x + (blockIdx.x >> 3) + (blockIdx.x >> 6)) & 7u);
+        const int t = (int)(wg % rows), y = y0 + (int)(wg / rows);     // y: (chunk, kv head) in [y0, y1) of this launch
+        const int g = (int)((unsigned)y % (unsigned)sh.n_kv), c = (int)((unsigned)y / (unsigned)sh.n_kv);
+        if (y >= y1) return;
+        const int after = min(t + 1, rows - 1), s_after = seq_of_token[after], p_after = pos_of_token[after];
+        const TileItem item = item_of(t, c, g);
+        if (after > t && s_after == item.seq && quotient(p_after, rule.per_block) == quotient(item.pos, rule.per_block)) return;   // not the last token of its group
+        if (c * rule.chunk > item.pos) return;
+        serve(item);
     }
 }
 
@@ -581,17 +753,34 @@ bool attn_tile_supported(const AttnShape &sh, const void *k_cache, const void *v
 constexpr size_t kTileGrid = (size_t)1 << 23;          // workgroups of a launch of the tile form, about
 constexpr size_t kGeneralGrid = (size_t)1 << 25;       // of the general form
 
+// Up to kListGrid workgroups the dense grid is resident at once and its items start a scan earlier (4 tokens behind 128
+// positions: 14.8 us either way, one workgroup per CU).  Beyond, as many workgroups as are resident walk the list: two per CU with
+// 256-byte rows (at 1024 workgroups 13 decodes of 200..3000 positions 39.8 us, at 512 34.8), else four (300 + 40 tokens: 512 / 768 / 1024 /
+// 2048 workgroups 41.6 / 39.1 / 36.9 / 38.2).
+constexpr size_t kListGrid = 512;
+
+
 template <typename T, int HD, int TP>
 void launch_attn_tile(hipStream_t s, const void *qkv, const int32_t *seq_of_token, const int32_t *pos_of_token,
                       const int32_t *block_table, const void *k_cache, const void *v_cache, void *out, int ld_out, float *part_o,
                       float *part_ml, const AttnShape &sh, int rows) {
-    const int n_y = sh.n_kv * sh.max_chunks, step = (int)std::max<size_t>(kTileGrid / rows, 1);
+    const int n_y = sh.n_kv * sh.max_chunks;
+    const size_t dense = (size_t)rows * n_y;
+    const int G = sh.n_q / sh.n_kv, block = 4 * (16 / G), chunk = sh.chunk_pages * sh.page_size;
+    const TileRule rule{1.0 / block, 1.0 / chunk, 1.0 / sh.n_kv, G, 16 / G, block, chunk, 65536 / G + 1};
+#define DYN_TILE_LAUNCH(LIST, GRID, Y0, Y1)                                                                                              \
+    hipLaunchKernelGGL((attn_tile_kernel<T, HD, TP, LIST>), dim3(GRID), dim3(256), 0, s, (const T *)qkv, seq_of_token, pos_of_token,     \
+                       block_table, (const T *)k_cache, (const T *)v_cache, (T *)out, ld_out, part_o, part_ml, sh, rule, rows, Y0, Y1)
+    if (rows <= kListRows && dense > kListGrid) {
+        DYN_TILE_LAUNCH(true, (unsigned)std::min<size_t>(dense, HD * sizeof(T) >= 256 ? 512 : 1024), 0, n_y);
+        return;
+    }
+    const int step = (int)std::max<size_t>(kTileGrid / rows, 1);
     for (int y0 = 0; y0 < n_y; y0 += std::min(step, n_y - y0)) {
         const int y1 = y0 + std::min(step, n_y - y0);
-        hipLaunchKernelGGL((attn_tile_kernel<T, HD, TP>), dim3((unsigned)(((size_t)rows * (y1 - y0) + 7) / 8 * 8)), dim3(256), 0, s, (const T *)qkv,
-                           seq_of_token, pos_of_token, block_table, (const T *)k_cache, (const T *)v_cache, (T *)out, ld_out, part_o, part_ml, sh,
-                           rows, y0, y1);               // whole eights of workgroups
+        DYN_TILE_LAUNCH(false, (unsigned)(((size_t)rows * (y1 - y0) + 7) / 8 * 8), y0, y1);               // whole eights of workgroups
     }
+#undef DYN_TILE_LAUNCH
 }
 }  // namespace
 
@@ -640,7 +829,7 @@ hipError_t launch_attention_generic(int dtype, const void *qkv, const int32_t *s
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && mid) e = hipEventRecord(mid, s);
     if (e != hipSuccess) return e;
-    return launch_attention_combine(dtype, false, part_o, part_ml, pos_of_token, nullptr, out, ld_out, sh, rows, s, nullptr, tile);
+    return launch_attention_combine(dtype, tile && dtype == 1, part_o, part_ml, pos_of_token, nullptr, out, ld_out, sh, rows, s, nullptr, tile);
 }
 
 }  // namespace dyn

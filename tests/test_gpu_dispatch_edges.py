@@ -19,3 +19,19 @@ def test_decode_items_reach_every_token_and_head(n_kv, tokens):
     data = gen.generate(w)
     y, k, v = both_schedules(w, data)
     say("%d items: %.2e" % (n_kv * tokens, check_against_oracle(w, data, y, k, v)))
+
+
+# Attention for other shapes lists its items from 512 workgroups of the dense grid up to 1024 rows: sequentially the first
+# batch has 1030 rows (dense) and its second micro-batch 1024 (listed); the others are listed whole and dense or listed in
+# parts.  Groups that end in every place of a thread's four rows, sequences of one and several tokens in turn.
+@pytest.mark.parametrize("dtype,n_q,n_kv,hd,page,seqs", [
+    ("bf16", 4, 2, 64, 16, [(6, 30)] + [(1, 1 + (11 * i) % 300) for i in range(1024)]),
+    ("bf16", 6, 2, 64, 16, [(301, 700)] + [(1 + i % 3, 40 + 13 * i) for i in range(60)]),
+    ("bf16", 8, 1, 128, 32, [(1, 5000)] + [(1, 1 + 97 * i) for i in range(31)] + [(2, 513)]),
+    ("f32", 4, 4, 32, 48, [(1, 1)] + [(5 + i % 13, 20 + 31 * i) for i in range(40)]),
+    ("bf16", 2, 1, 256, 64, [(17, 17), (1, 9000), (40, 257), (1, 256), (1, 512), (1, 513), (500, 600)])])
+def test_tile_attention_lists_every_item_once(dtype, n_q, n_kv, hd, page, seqs):
+    w = workload("list", dtype, 128, n_q, n_kv, hd, 128, seqs, page=page, seed=70 + n_q)
+    data = gen.generate(w)
+    y, k, v = both_schedules(w, data)
+    say("%d rows: %.2e" % (w.n_tokens, check_against_oracle(w, data, y, k, v)))
