@@ -87,6 +87,9 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
                        size_t plane_stride, int rows, int N, int K, hipStream_t s, hipEvent_t mid = nullptr,
                        const GemmEpilogue *ep = nullptr);
 
+// fp32 projection, plain or expert-grouped (kernels_gemm_f32.hip; launch_gemm and launch_gemm_grouped call it); max_rows bounds a group's rows.
+hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const void *R, void *Y, int max_rows, int N, int K, const GemmGroups &gr,
+                           hipStream_t s);
 // A few rows (at most 8), planes summed in the workgroup (kernels_gemm_rows.hip; launch_gemm calls it).
 bool gemm_rows16_supported(int rows, int N, int K, int S);
 hipError_t launch_gemm_rows16(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int S);

@@ -16,132 +16,6 @@
 
 namespace dyn {
 
-// ------------------------------------------------------------------ fp32 path
-// Eight waves share one MT (X rows) x NT (W rows) output tile; each multiplies its own eighth of K
-// (kF32Waves slices of whole 16-deep units) with 16x16x4 fp32 MFMAs and the eight sums are added in
-// wave order through LDS, then the residual: every output is eight fp32 chains in ascending k, cut by
-// K alone, so its bits do not depend on the tile or on how many rows are in flight.
-// Operands go from memory straight into MFMA layout: a lane loads four consecutive k of its row (16
-// rows x 64 bytes per instruction) and element e of the four is the operand of product e, whose k
-// index l / 16 then stands for k 4 (l / 16) + e in both matrices.
-// What bounds it: with few rows the latency of one pass over a K slice, which is why the slices are
-// short and a slice's loads are all issued ahead of its products; with many rows the fp32 matrix rate
-// (256 flop per clock and CU: an output tile of 64 x 64 asks for 16 bytes per clock and CU of the
-// vector cache, a 16 x 16 one for 64).  Launch alone, against 64 x 64 tiles of fp32 FMAs staged through
-// LDS 16 k at a time by one chain per output: 4 rows x 768 x 256 27.7 -> 3.2 us, 4 x 256 x 1024
-// 96 -> 5.1 us; 225 rows x 1536 x 1024 141 -> 19, x 8192 x 1024 149 -> 60, x 1024 x 4096 513 -> 34 us.
-constexpr int kF32Waves = 8;
-typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));       // weights, residual, output: any float alignment
-
-template <int MT, int NT>
-__global__ __launch_bounds__(kF32Waves * 64) void gemm_f32_kernel(const float *__restrict__ X, int ldx, const float *__restrict__ W,
-                                                                  const float *__restrict__ R, float *__restrict__ Y, int M, int N,
-                                                                  int K, GemmGroups gr) {
-    constexpr int NA = NT / 16, NB = MT / 16, UNR = (NA + NB) <= 4 ? 4 : 2;  // units of 16 k loaded ahead of their products
-    constexpr int SUB = NA * NB < 4 ? NA * NB : 4;                           // 16 x 16 sub-tiles reduced per LDS round
-    __shared__ f32x4 part[kF32Waves][SUB][64];
-    const int32_t *list = nullptr;
-    if (gr.n_groups) {                                 // blockIdx.z = expert: its rows come from a list
-        M = gr.counts[blockIdx.z];
-        list = gr.lists + (size_t)blockIdx.z * gr.cap;
-        W += (size_t)blockIdx.z * gr.w_stride;
-    }
-    const int m0 = blockIdx.y * MT;
-    if (m0 >= M) return;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15, lq = lane >> 4;
-    const int n0 = blockIdx.x * NT;
-    const float *wp[NA], *xp[NB];                      // rows past the end read the last one; what they give is not stored
-#pragma unroll
-    for (int a = 0; a < NA; ++a) wp[a] = W + (size_t)min(n0 + a * 16 + lr, N - 1) * K + 4 * lq;
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int m = min(m0 + b * 16 + lr, M - 1);
-        xp[b] = X + (size_t)(list ? list[m] / gr.x_div : m) * ldx + 4 * lq;
-    }
-    f32x4 acc[NA][NB];
-#pragma unroll
-    for (int a = 0; a < NA; ++a)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int units = (K + 15) / 16, u0 = units * wave / kF32Waves, u1 = units * (wave + 1) / kF32Waves;
-    const int full = K / 16;                           // whole units; the last one of a K that is no multiple of 16 is read guarded
-    auto multiply = [&](const f32x4 (&wv)[NA], const f32x4 (&xv)[NB]) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int a = 0; a < NA; ++a)
-#pragma unroll
-                for (int b = 0; b < NB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[a][e], xv[b][e], acc[a][b], 0, 0, 0);
-    };
-    int u = u0;
-    const int u1f = min(u1, full);
-    for (; u + UNR <= u1f; u += UNR) {
-        f32x4 wv[UNR][NA], xv[UNR][NB];
-#pragma unroll
-        for (int i = 0; i < UNR; ++i) {
-#pragma unroll
-            for (int a = 0; a < NA; ++a) wv[i][a] = *reinterpret_cast<const f32x4_u *>(wp[a] + (size_t)(u + i) * 16);
-#pragma unroll
-            for (int b = 0; b < NB; ++b) xv[i][b] = *reinterpret_cast<const f32x4_u *>(xp[b] + (size_t)(u + i) * 16);
-        }
-#pragma unroll
-        for (int i = 0; i < UNR; ++i) multiply(wv[i], xv[i]);
-    }
-    for (; u < u1; ++u) {
-        f32x4 wv[NA], xv[NB];
-        const bool in = u < full || u * 16 + 4 * lq < K;            // K is a multiple of 4
-#pragma unroll
-        for (int a = 0; a < NA; ++a) wv[a] = in ? (f32x4) * reinterpret_cast<const f32x4_u *>(wp[a] + (size_t)u * 16) : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int b = 0; b < NB; ++b) xv[b] = in ? (f32x4) * reinterpret_cast<const f32x4_u *>(xp[b] + (size_t)u * 16) : f32x4{0.f, 0.f, 0.f, 0.f};
-        multiply(wv, xv);
-    }
-    // D: lane l holds W rows 4 (l / 16) + r of X row l % 16.  Sub-tiles are reduced SUB at a time, a wave to a sub-tile.
-#pragma unroll
-    for (int s0 = 0; s0 < NA * NB; s0 += SUB) {
-        if (s0) __syncthreads();
-#pragma unroll
-        for (int i = 0; i < SUB; ++i) part[wave][i][lane] = acc[(s0 + i) / NB][(s0 + i) % NB];
-        __syncthreads();
-        if (wave < SUB) {
-            const int a = (s0 + wave) / NB, b = (s0 + wave) % NB;
-            f32x4 o = part[0][wave][lane];
-#pragma unroll
-            for (int w = 1; w < kF32Waves; ++w) { const f32x4 p = part[w][wave][lane]; o[0] += p[0]; o[1] += p[1]; o[2] += p[2]; o[3] += p[3]; }
-            const int m = m0 + b * 16 + lr, n = n0 + a * 16 + 4 * lq;
-            if (m < M && n < N) {
-                const size_t at = (size_t)(list ? list[m] : m) * N + n;
-                if (n + 4 <= N) {
-                    if (R) { const f32x4_u rv = *reinterpret_cast<const f32x4_u *>(R + at); o[0] += rv[0]; o[1] += rv[1]; o[2] += rv[2]; o[3] += rv[3]; }
-                    *reinterpret_cast<f32x4_u *>(Y + at) = o;
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (n + r < N) Y[at + r] = o[r] + (R ? R[at + r] : 0.f);
-                }
-            }
-        }
-    }
-}
-
-// Tile of an fp32 launch: 16 x 16 up to 16 rows or while such tiles fit the CUs at once (the launch is one
-// workgroup long, and a workgroup's products take a time of their own: 24 rows x 1536 x 1024 13.5 us against
-// 17.6 with 32 x 32, x 1024 x 4096 24 against 37), 64 x 64 where such tiles give every CU a workgroup (225 rows x
-// 8192 x 1024 64 us, 73 with 32 x 32, 114 with 16 x 16), else 32 x 32 (x 1024 x 4096 41 us; 64 x 64: 109).  max_rows
-// bounds a group's rows.
-static hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const void *R, void *Y, int max_rows, int N, int K,
-                                  const GemmGroups &gr, hipStream_t s) {
-    const int groups = std::max(gr.n_groups, 1);
-#define DYN_F32(MT, NT)                                                                                                          \
-    hipLaunchKernelGGL((gemm_f32_kernel<MT, NT>), dim3((N + NT - 1) / NT, (max_rows + MT - 1) / MT, groups), dim3(kF32Waves * 64), 0, s, \
-                       (const float *)X, ldx, (const float *)W, (const float *)R, (float *)Y, max_rows, N, K, gr)
-    if (max_rows <= 16 || (long)((max_rows + 15) / 16) * ((N + 15) / 16) * groups <= 256) DYN_F32(16, 16);
-    else if ((long)((max_rows + 63) / 64) * ((N + 63) / 64) * groups >= 256) DYN_F32(64, 64);
-    else DYN_F32(32, 32);
-#undef DYN_F32
-    return hipGetLastError();
-}
-
 // ------------------------------------------------------------------ bf16 MFMA path (gemm_tile.h)
 constexpr int kBigBN = 128, kBigMT = 128, kBigNS = 2;   // tile and ring depth of the many-row (matrix-core-bound) regime
 

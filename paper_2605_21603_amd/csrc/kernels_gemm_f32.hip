@@ -1,0 +1,355 @@
+// fp32 projections on fp32 MFMAs (launch_gemm and launch_gemm_grouped call launch_gemm_f32).
+//
+// K is cut into eight chains (kF32Chains slices of whole 16-deep units); each is accumulated by 16x16x4 fp32 MFMAs from
+// zero, and the eight sums are added one after the other, then the residual: an output's order of terms follows
+// from its column, N and K (and whether experts share the launch) alone, so its bits do not depend on the tile or on how
+// many rows are in flight.
+// Where K is a multiple of 512 and N of 4 a chain is whole blocks of 64 k (256 bytes of a row).  Product (r, e) of a block,
+// r and e = 0..3, takes k = 16 c + 4 r + e as its k index c; the blocks of a chain are walked from one that turns with the
+// chain and with the group of 64 columns, and the first chain added turns with that group too: rows lie a power of two
+// apart, and what runs at the same time would otherwise read one channel of the second-level cache.
+#include <algorithm>
+
+#include "gemm_tile.h"
+
+namespace dyn {
+
+constexpr int kF32Chains = 8, kF32Block = 64;
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));       // weights, residual, output: any float alignment
+
+__device__ __forceinline__ int f32_block(int i, int chain, int n0, int blocks) {     // the i-th block of a chain
+    const int at = i + (chain + n0 / 64 * 3) % blocks;
+    return at < blocks ? at : at - blocks;
+}
+__device__ __forceinline__ int f32_chain(int i, int n0) { return (i + n0 / 64) % kF32Chains; }     // the i-th chain to add
+
+// Four outputs of a row from column n on: + residual, stored.
+__device__ __forceinline__ void f32_store(f32x4 o, size_t at, int n, int N, const float *__restrict__ R, float *__restrict__ Y) {
+    if (n + 4 <= N) {
+        if (R) { const f32x4_u rv = *reinterpret_cast<const f32x4_u *>(R + at); o[0] += rv[0]; o[1] += rv[1]; o[2] += rv[2]; o[3] += rv[3]; }
+        *reinterpret_cast<f32x4_u *>(Y + at) = o;
+    } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (n + r < N) Y[at + r] = o[r] + (R ? R[at + r] : 0.f);
+    }
+}
+
+// The eight waves' sums of a tile meet in LDS, SUB sub-tiles of 16 x 16 at a time, a wave to a sub-tile.  D: lane l holds W rows
+// 4 (l / 16) + r of X row l % 16.  list: output rows (null: m itself).
+template <int NA, int NB, bool TURN>
+__device__ __forceinline__ void f32_finish(f32x4 (*part)[NA * NB < 4 ? NA * NB : 4][64], const f32x4 (&acc)[NA][NB], int m0, int n0, int M, int N,
+                                           const int32_t *list, const float *__restrict__ R, float *__restrict__ Y) {
+    constexpr int SUB = NA * NB < 4 ? NA * NB : 4;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15, lq = lane >> 4;
+#pragma unroll
+    for (int s0 = 0; s0 < NA * NB; s0 += SUB) {
+        if (s0) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < SUB; ++i) part[wave][i][lane] = acc[(s0 + i) / NB][(s0 + i) % NB];
+        __syncthreads();
+        if (wave < SUB) {
+            const int a = (s0 + wave) / NB, b = (s0 + wave) % NB;
+            f32x4 o = part[TURN ? f32_chain(0, n0) : 0][wave][lane];
+#pragma unroll
+            for (int w = 1; w < kF32Chains; ++w) { const f32x4 p = part[TURN ? f32_chain(w, n0) : w][wave][lane]; o[0] += p[0]; o[1] += p[1]; o[2] += p[2]; o[3] += p[3]; }
+            const int m = m0 + b * 16 + lr, n = n0 + a * 16 + 4 * lq;
+            if (m < M && n < N) f32_store(o, (size_t)(list ? list[m] : m) * N + n, n, N, R, Y);
+        }
+    }
+}
+
+// Any shape: eight waves share one MT (X rows) x NT (W rows) output tile, a wave per chain.
+// Operands go from memory straight into MFMA layout: a lane loads four consecutive k of its row (16
+// rows x 64 bytes per instruction) and element e of the four is the operand of product e, whose k
+// index l / 16 then stands for k 4 (l / 16) + e in both matrices.  Launch alone, against 64 x 64 tiles of fp32 FMAs staged
+// through LDS 16 k at a time by one chain per output: 4 rows x 768 x 256 27.7 -> 3.2 us, 4 x 256 x 1024 96 -> 5.1 us.
+template <int MT, int NT>
+__global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_kernel(const float *__restrict__ X, int ldx, const float *__restrict__ W,
+                                                                  const float *__restrict__ R, float *__restrict__ Y, int M, int N,
+                                                                  int K, GemmGroups gr) {
+    constexpr int NA = NT / 16, NB = MT / 16, UNR = (NA + NB) <= 4 ? 4 : 2;  // units of 16 k loaded ahead of their products
+    __shared__ f32x4 part[kF32Chains][NA * NB < 4 ? NA * NB : 4][64];
+    const int32_t *list = nullptr;
+    if (gr.n_groups) {                                 // blockIdx.z = expert: its rows come from a list
+        M = gr.counts[blockIdx.z];
+        list = gr.lists + (size_t)blockIdx.z * gr.cap;
+        W += (size_t)blockIdx.z * gr.w_stride;
+    }
+    const int m0 = blockIdx.y * MT;
+    if (m0 >= M) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15, lq = lane >> 4;
+    const int n0 = blockIdx.x * NT;
+    const float *wp[NA], *xp[NB];                      // rows past the end read the last one; what they give is not stored
+#pragma unroll
+    for (int a = 0; a < NA; ++a) wp[a] = W + (size_t)min(n0 + a * 16 + lr, N - 1) * K + 4 * lq;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int m = min(m0 + b * 16 + lr, M - 1);
+        xp[b] = X + (size_t)(list ? list[m] / gr.x_div : m) * ldx + 4 * lq;
+    }
+    f32x4 acc[NA][NB];
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int units = (K + 15) / 16, u0 = units * wave / kF32Chains, u1 = units * (wave + 1) / kF32Chains;
+    const int full = K / 16;                           // whole units; the last one of a K that is no multiple of 16 is read guarded
+    auto multiply = [&](const f32x4 (&wv)[NA], const f32x4 (&xv)[NB]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int a = 0; a < NA; ++a)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[a][e], xv[b][e], acc[a][b], 0, 0, 0);
+    };
+    int u = u0;
+    const int u1f = min(u1, full);
+    for (; u + UNR <= u1f; u += UNR) {
+        f32x4 wv[UNR][NA], xv[UNR][NB];
+#pragma unroll
+        for (int i = 0; i < UNR; ++i) {
+#pragma unroll
+            for (int a = 0; a < NA; ++a) wv[i][a] = *reinterpret_cast<const f32x4_u *>(wp[a] + (size_t)(u + i) * 16);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) xv[i][b] = *reinterpret_cast<const f32x4_u *>(xp[b] + (size_t)(u + i) * 16);
+        }
+#pragma unroll
+        for (int i = 0; i < UNR; ++i) multiply(wv[i], xv[i]);
+    }
+    for (; u < u1; ++u) {
+        f32x4 wv[NA], xv[NB];
+        const bool in = u < full || u * 16 + 4 * lq < K;            // K is a multiple of 4
+#pragma unroll
+        for (int a = 0; a < NA; ++a) wv[a] = in ? (f32x4) * reinterpret_cast<const f32x4_u *>(wp[a] + (size_t)u * 16) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int b = 0; b < NB; ++b) xv[b] = in ? (f32x4) * reinterpret_cast<const f32x4_u *>(xp[b] + (size_t)u * 16) : f32x4{0.f, 0.f, 0.f, 0.f};
+        multiply(wv, xv);
+    }
+    f32_finish<NA, NB, false>(part, acc, m0, n0, M, N, list, R, Y);
+}
+
+// Four adjacent lanes trade with four registers: register j of lane x of every quad becomes register x of lane j.
+__device__ __forceinline__ void quad_transpose(f32x4 (&v)[4]) {
+    const bool x0 = threadIdx.x & 1, x1 = threadIdx.x & 2;
+#define DYN_TRADE(A, B, CTRL, UP)                                                                         \
+    _Pragma("unroll") for (int e = 0; e < 4; ++e) {                                                       \
+        const int a = __float_as_int(v[A][e]), b = __float_as_int(v[B][e]);                               \
+        const int an = __builtin_amdgcn_mov_dpp(a, CTRL, 0xf, 0xf, true), bn = __builtin_amdgcn_mov_dpp(b, CTRL, 0xf, 0xf, true); \
+        v[A][e] = __int_as_float(UP ? bn : a);                                                            \
+        v[B][e] = __int_as_float(UP ? b : an);                                                            \
+    }
+    DYN_TRADE(0, 1, 0xb1, x0)                              // quad_perm 1, 0, 3, 2
+    DYN_TRADE(2, 3, 0xb1, x0)
+    DYN_TRADE(0, 2, 0x4e, x1)                              // quad_perm 2, 3, 0, 1
+    DYN_TRADE(1, 3, 0x4e, x1)
+#undef DYN_TRADE
+}
+
+// Whole blocks, few rows or few tiles: as above, but a quad of lanes loads 64 adjacent bytes and trades them.  Load j of a
+// block's four covers rows 4 q + j, q = 0..3, 256 bytes each; in MFMA layout a quarter wave names 16 rows and the
+// load takes 65 cycles of the vector cache, this way 17.  16 x 16 tiles keep two blocks in flight (24 rows x 1024 x 4096
+// 15.9 -> 11.0 us, 100 rows 30.7 -> 19.2); with 32 x 32 that costs the second workgroup of a CU (225 rows x 1024 x 4096 31.6 -> 28.8
+// us, 30.3 with two).  Trading takes 64 vector instructions an operand: what is one short block long gains nothing
+// (4 rows x 1024 x 1024 4.6 -> 5.1 us, x 8192 x 1024 8.0 -> 8.9, x 1024 x 4096 12.0 -> 10.8).
+template <int MT, int NT>
+__global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_quads_kernel(const float *__restrict__ X, int ldx, const float *__restrict__ W,
+                                                                        const float *__restrict__ R, float *__restrict__ Y, int M, int N, int K) {
+    constexpr int NA = NT / 16, NB = MT / 16, NBUF = NA + NB <= 2 ? 2 : 1;
+    __shared__ f32x4 part[kF32Chains][NA * NB < 4 ? NA * NB : 4][64];
+    const int m0 = blockIdx.y * MT, n0 = blockIdx.x * NT;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), row4 = (lane >> 2 & 3) * 4, col = (lane >> 4) * 16 + (lane & 3) * 4;
+    const float *const Wt = W + (size_t)n0 * K, *const Xt = X + (size_t)m0 * ldx;
+    size_t wo[NA], xo[NB][4];                              // rows past the end read the last ones; what they give is not stored
+#pragma unroll
+    for (int a = 0; a < NA; ++a) wo[a] = (size_t)min(a * 16 + row4, N - 4 - n0) * K + col;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) xo[b][j] = (size_t)min(b * 16 + row4 + j, M - 1 - m0) * ldx + col;
+    f32x4 acc[NA][NB];
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int blocks = K / (kF32Block * kF32Chains);
+    f32x4 wv[NBUF][NA][4], xv[NBUF][NB][4];
+    auto load = [&](auto buf, int i) {
+        constexpr int B = decltype(buf)::value;
+        const int at = (wave * blocks + f32_block(i, wave, n0, blocks)) * kF32Block;
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) wv[B][a][j] = *reinterpret_cast<const f32x4_u *>(Wt + (size_t)j * K + at + wo[a]);
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) xv[B][b][j] = *reinterpret_cast<const f32x4_u *>(Xt + at + xo[b][j]);
+    };
+    auto multiply = [&](auto buf) {
+        constexpr int B = decltype(buf)::value;
+#pragma unroll
+        for (int a = 0; a < NA; ++a) quad_transpose(wv[B][a]);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) quad_transpose(xv[B][b]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int a = 0; a < NA; ++a)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[B][a][r][e], xv[B][b][r][e], acc[a][b], 0, 0, 0);
+    };
+    const std::integral_constant<int, 0> b0;
+    const std::integral_constant<int, NBUF - 1> b1;
+    if constexpr (NBUF == 1) {
+        for (int i = 0; i < blocks; ++i) {
+            load(b0, i);
+            multiply(b0);
+        }
+    } else {                                               // a pass always loads: behind a load that may not have been issued the compiler waits for all
+        load(b0, 0);
+        int i = 0;
+        for (; i + 2 < blocks; i += 2) {
+            load(b1, i + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(b0);
+            __builtin_amdgcn_sched_barrier(0);
+            load(b0, i + 2);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(b1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (i + 1 < blocks) {
+            load(b1, i + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(b0);
+            multiply(b1);
+        } else {
+            multiply(b0);
+        }
+    }
+    f32_finish<NA, NB, true>(part, acc, m0, n0, M, N, nullptr, R, Y);
+}
+
+// Whole blocks, many tiles: 64 x 64, four waves of 32 x 32 that share stages of one block (256-byte rows, direct loads of
+// one row per quarter wave, two stages) and walk the chains one after the other, each chain's sum added to the
+// total in registers.  Two workgroups per CU, bound by the matrix rate and the first stage's latency: 100 / 225 / 300 rows x 8192 x
+// 1024 31 / 56.5 / 79 us with 64 x 64 tiles loaded straight into MFMA layout (eight waves, 16 rows a quarter wave) -> 24.5 /
+// 41.2 / 60.5.  The 16-byte columns are swizzled with the row: lanes of 16 rows read 16
+// different bank groups.
+constexpr int kF32TileLds = 2 * 128 * 256;
+__global__ __launch_bounds__(256, 2) void gemm_f32_tiles_kernel(const float *__restrict__ X, int ldx, const float *__restrict__ W,
+                                                                const float *__restrict__ R, float *__restrict__ Y, int M, int N, int K) {
+    constexpr int T = 64, LOADS = 2 * T / 4 / 4, STAGE = 2 * T * 256;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15, lq = lane >> 4;
+    const int wn = wave & 1, wm = wave >> 1;
+    const int blocks = K / (kF32Block * kF32Chains), n_stage = kF32Chains * blocks;
+    const float *src[LOADS];
+#pragma unroll
+    for (int j = 0; j < LOADS; ++j) {
+        const int row = (j * 4 + wave) * 4 + (lane >> 4), col = ((lane ^ row) & 15) * 4;
+        src[j] = row < T ? W + (size_t)min(n0 + row, N - 1) * K + col : X + (size_t)min(m0 + row - T, M - 1) * ldx + col;
+    }
+    int at_chain = 0, at_block = 0;                        // next stage to issue
+    auto issue = [&](int st) {
+        const int chain = f32_chain(at_chain, n0), k = (chain * blocks + f32_block(at_block, chain, n0, blocks)) * kF32Block;
+        if (++at_block == blocks) { at_block = 0; ++at_chain; }
+#pragma unroll
+        for (int j = 0; j < LOADS; ++j)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[j] + k),
+                                             (__attribute__((address_space(3))) void *)(lds + (st & 1) * STAGE + (j * 4 + wave) * 1024), 16, 0, 0);
+    };
+    f32x4 acc[2][2], total[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    issue(0);
+    int left = blocks;                                     // stages left of the chain
+    bool first = true;
+    for (int st = 0; st < n_stage; ++st) {
+        wait_vmcnt(0);
+        // Bare barrier: every wave sees stage st and has its operands of the one before in registers.
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (st + 1 < n_stage) issue(st + 1);
+        const unsigned char *buf = lds + (st & 1) * STAGE;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            f32x4 wv[2], xv[2];
+#pragma unroll
+            for (int a = 0; a < 2; ++a) { const int row = wn * 32 + a * 16 + lr; wv[a] = *reinterpret_cast<const f32x4 *>(buf + row * 256 + (((lq * 4 + r) ^ lr) << 4)); }
+#pragma unroll
+            for (int b = 0; b < 2; ++b) { const int row = T + wm * 32 + b * 16 + lr; xv[b] = *reinterpret_cast<const f32x4 *>(buf + row * 256 + (((lq * 4 + r) ^ lr) << 4)); }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[a][e], xv[b][e], acc[a][b], 0, 0, 0);
+        }
+        if (--left == 0) {                                 // the chain ends
+            left = blocks;
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    if (first) total[a][b] = acc[a][b];
+                    else { total[a][b][0] += acc[a][b][0]; total[a][b][1] += acc[a][b][1]; total[a][b][2] += acc[a][b][2]; total[a][b][3] += acc[a][b][3]; }
+                    acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+            first = false;
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int m = m0 + wm * 32 + b * 16 + lr, n = n0 + wn * 32 + a * 16 + 4 * lq;
+            if (m < M && n < N) f32_store(total[a][b], (size_t)m * N + n, n, N, R, Y);
+        }
+}
+
+// Tile of an fp32 launch.  16 x 16 up to 16 rows or 512 tiles, two a CU: the launch is as long as a workgroup, and a workgroup's
+// products take a time of their own (whole blocks, 32 x 32 -> 16 x 16: 48 rows x 1536 x 1024, 288 tiles, 8.7 -> 7.0 us; 100 x 1024 x 4096,
+// 448 tiles, 27.9 -> 19.2; past the line 160 x 1024 x 4096, 640 tiles, 28.4 -> 28.7, 24 x 8192 x 1024, 1024 tiles, 13.2 -> 15.5).  64 x 64
+// where such tiles are about a CU's each: 192 of them (225 rows x 8192 x 1024, 512 tiles: 41 us; 225 x 1536 x 1024, 96 tiles: 23.5 us, with
+// 32 x 32 17.1).  Else 32 x 32.  Other depths and widths, and experts, take the form for any shape.
+hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const void *R, void *Y, int max_rows, int N, int K,
+                           const GemmGroups &gr, hipStream_t s) {
+    const int groups = std::max(gr.n_groups, 1);
+    auto tiles = [&](int t) { return (long)((max_rows + t - 1) / t) * ((N + t - 1) / t) * groups; };
+    const bool whole = !gr.n_groups && K % (kF32Block * kF32Chains) == 0 && N % 4 == 0;
+    const bool few = max_rows <= 16 || tiles(16) <= (whole ? 512 : 256);
+#define DYN_F32(KERNEL, T, THREADS, LDS, ...)                                                                                    \
+    hipLaunchKernelGGL(KERNEL, dim3((N + T - 1) / T, (max_rows + T - 1) / T, groups), dim3(THREADS), LDS, s, (const float *)X, ldx, \
+                       (const float *)W, (const float *)R, (float *)Y, max_rows, N, K, ##__VA_ARGS__)
+    if (whole) {
+        const bool aligned = ldx % 4 == 0 && (((uintptr_t)X | (uintptr_t)W) & 15) == 0;      // the direct loads' 16 bytes
+        if (few) {
+            DYN_F32((gemm_f32_quads_kernel<16, 16>), 16, kF32Chains * 64, 0);
+        } else if (aligned && tiles(64) >= 192) {
+            static bool attr_set = false;                  // 64 KB of dynamic LDS: opted in, once
+            if (!attr_set) {
+                const hipError_t e = hipFuncSetAttribute((const void *)gemm_f32_tiles_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kF32TileLds);
+                if (e != hipSuccess) return e;
+                attr_set = true;
+            }
+            DYN_F32(gemm_f32_tiles_kernel, 64, 256, kF32TileLds);
+        } else {
+            DYN_F32((gemm_f32_quads_kernel<32, 32>), 32, kF32Chains * 64, 0);
+        }
+        return hipGetLastError();
+    }
+    if (few) DYN_F32((gemm_f32_kernel<16, 16>), 16, kF32Chains * 64, 0, gr);
+    else if (tiles(64) >= 256) DYN_F32((gemm_f32_kernel<64, 64>), 64, kF32Chains * 64, 0, gr);
+    else DYN_F32((gemm_f32_kernel<32, 32>), 32, kF32Chains * 64, 0, gr);
+#undef DYN_F32
+    return hipGetLastError();
+}
+
+}  // namespace dyn

@@ -35,3 +35,36 @@ def test_tile_attention_lists_every_item_once(dtype, n_q, n_kv, hd, page, seqs):
     data = gen.generate(w)
     y, k, v = both_schedules(w, data)
     say("%d rows: %.2e" % (w.n_tokens, check_against_oracle(w, data, y, k, v)))
+
+
+# fp32 projections of whole 64-deep blocks: 16 x 16, 32 x 32 and 64 x 64 tiles and their edges, one and several blocks a chain
+# (depths 512, 1024, 2048 and 4608; odd and even counts), widths that fill no 64-, 32- or 16-wide tile; 1030 and 516 are depths of
+# the other form.  The second micro-batch takes other tiles than the whole.
+@pytest.mark.parametrize("rows,hidden,n_q,n_kv,hd,inter", [
+    (3, 512, 4, 2, 64, 1024), (17, 512, 3, 1, 16, 1536), (47, 1024, 4, 2, 64, 2048), (150, 1024, 8, 4, 64, 4608), (65, 2048, 8, 2, 64, 4100),
+    (129, 512, 8, 8, 64, 8196), (200, 512, 2, 1, 64, 6148)])
+def test_fp32_projections_of_whole_blocks(rows, hidden, n_q, n_kv, hd, inter):
+    head = rows // 3
+    seqs = ([(head, head)] if head else []) + [(1, 1 + (7 * i) % 40) for i in range(rows - head)]
+    w = workload("f32_blocks", "f32", hidden, n_q, n_kv, hd, inter, seqs, seed=80 + rows)
+    data = gen.generate(w)
+    y, k, v = both_schedules(w, data)
+    err = check_against_oracle(w, data, y, k, v)
+    say("rows %d: %.2e" % (rows, err))
+    assert err < 2e-6                                        # eight chains of K / 8 terms: as in the test of the other tiles
+
+
+def test_fp32_projections_take_weights_at_any_float():
+    """Weights that start 4 bytes off a 16-byte line take loads of single rows where 64 x 64 tiles copy 16 bytes: the same bits."""
+    w = workload("f32_off", "f32", 512, 8, 8, 64, 8192, [(200, 200)], seed=90)
+    data = gen.generate(w)
+    run = GpuRun(w, data)
+    y0, _, _ = run.run(B.sequential())
+    for n in ("w_qkv", "w_o", "w_gate_up", "w_down"):
+        t = run.weights[0][n]
+        flat = torch.empty(t.numel() + 4, dtype=t.dtype, device=t.device)
+        flat[1:1 + t.numel()] = t.reshape(-1)
+        run.weights[0][n] = flat[1:1 + t.numel()].view(t.shape)
+    run.layer = B.DynLayer(B.make_config(w.shape, 0), run.weights)
+    y1, _, _ = run.run(B.sequential())
+    assert torch.equal(y0, y1)
