@@ -90,8 +90,9 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
 // fp32 projection, plain or expert-grouped (kernels_gemm_f32.hip; launch_gemm and launch_gemm_grouped call it); max_rows bounds a group's rows.
 hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const void *R, void *Y, int max_rows, int N, int K, const GemmGroups &gr,
                            hipStream_t s);
-// A few rows (at most 8), planes summed in the workgroup (kernels_gemm_rows.hip; launch_gemm calls it).
-bool gemm_rows16_supported(int rows, int N, int K, int S);
+// A few rows (at most 16), planes summed in the workgroup (kernels_gemm_rows.hip; launch_gemm calls it).
+bool gemm_rows16_supported(int rows, int N, int K, int S);            // with 8 X rows a stage
+bool gemm_rows16_wide_supported(int rows, int N, int K, int S);       // with 16
 hipError_t launch_gemm_rows16(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int S);
 // Many rows, split-K planes folded in registers, 256 x 128 tiles (kernels_gemm_wide.hip; launch_gemm calls it).
 hipError_t launch_gemm_fold(int grid, hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N,

@@ -380,7 +380,7 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
         if (et != hipSuccess) return et;
         rows = head;
     }
-    if (gemm_rows16_supported(rows, N, K, p.split)) {
+    if (gemm_rows16_supported(rows, N, K, p.split) || gemm_rows16_wide_supported(rows, N, K, p.split)) {
         hipError_t er = launch_gemm_rows16(s, X, ldx, W, R, Y, rows, N, K, p.split);
         if (er == hipSuccess && mid) er = hipEventRecord(mid, s);
         if (er == hipSuccess && has_ep) er = run_epilogue(dtype, *ep, Y, rows, N, s);

@@ -1,4 +1,4 @@
-// bf16 projections with planes for a few rows: the planes summed inside the workgroup.
+// bf16 projections with planes for up to 16 rows: the planes summed inside the workgroup.
 #include <hip/hip_runtime.h>
 
 #include "gemm_tile.h"
@@ -6,52 +6,77 @@
 
 namespace dyn {
 
-// A workgroup owns 16 W rows over the whole depth, wave p plane p of the S; a lane loads its MFMA operands straight into
-// registers, kDeep stages ahead, and the planes meet in LDS.  Bound by the weight stream; what it saves is the planes'
-// way through memory and the launch that sums them.  The stages of a plane are walked in the rotated order of
-// the other tiles and the planes are added in plane order: the same bits.
-constexpr int kDeep = 8;
+// A workgroup owns 16 W rows over the whole depth, wave p plane p of the S, and the planes meet in LDS.  Bound by the weight
+// stream; what it saves is the planes' way through memory and the launch that sums them.  The stages of a plane are walked in
+// the rotated order of the other tiles and the planes are added in plane order: the same bits.
+// W and X go into a ring of the wave's own by direct loads of whole 128-byte lines, and come out in MFMA layout: loaded straight
+// into that layout a quarter wave names 16 rows, which costs 65 cycles of the vector cache an instruction against 17, and at 8
+// rows X's loads and W's together took longer than W's way from memory.  No barrier in the loop, kDeep stages on their way
+// (64 KB a CU with 8 planes; 5: no change).  Launch alone, straight -> by LDS, weights from HBM / from the last-level cache:
+// 6144 x 4096 1 row 12.6/11.2 -> 11.2/7.4 us, 13 rows (planes summed by a launch of their own before) 13.5/11.9 -> 12.6/8.0;
+// 4096 x 4096 8.0/6.5 -> 8.0/4.7, 12.5/9.4 -> 8.5/5.0; 4096 x 14336 23.7/19.4 -> 23.1/18.0, 25.7/21.6 -> 24.4/18.9.
+constexpr int kDeep = 4;
 
-template <int S>
+template <int S, int XR>
 __global__ __launch_bounds__(64 * S) void gemm_rows16_kernel(const bf16_t *__restrict__ X, int ldx, const bf16_t *__restrict__ W,
                                                              const bf16_t *__restrict__ R, bf16_t *__restrict__ Y, int rows,
                                                              int N, int K) {
-    __shared__ f32x4 planes[S][64];
+    constexpr int LOADS = 2 + XR / 8, STAGE = LOADS * 1024;   // 16 W rows, XR (8 or 16) X rows of 64 k
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];      // a ring of kDeep stages for every wave; in the end the planes' sums
+    f32x4(*const planes)[64] = reinterpret_cast<f32x4(*)[64]>(lds);
     const int lane = threadIdx.x & 63, sp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15, lq = lane >> 4;
-    const int n0 = blockIdx.x * 16, Kp = K / S, n_stage = Kp / 64;
+    const int n0 = blockIdx.x * 16, Kp = K / S, n_stage = Kp / BK;
     const int rot = (int)(((unsigned)(n0 / 128 / kRotGroup) * kRotStep) % (unsigned)n_stage);
-    const bf16_t *w = W + (size_t)(n0 + lr) * K + sp * Kp + lq * 8, *x = X + (size_t)min(lr, rows - 1) * ldx + sp * Kp + lq * 8;
-    bf16x8 a[kDeep][2], b[kDeep][2];
+    const bf16_t *src[LOADS];                              // 8 rows of a stage by 8 lanes each, the 16-byte columns swizzled with the row
+#pragma unroll
+    for (int j = 0; j < LOADS; ++j) {
+        const int row = (j & 1) * 8 + (lane >> 3), col = sp * Kp + ((lane & 7) ^ (row >> 1 & 7)) * 8;
+        src[j] = j < 2 ? W + (size_t)(n0 + row) * K + col : X + (size_t)min(row, rows - 1) * ldx + col;
+    }
+    unsigned char *const ring = lds + sp * kDeep * STAGE;
+    const unsigned ring0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)ring;
+    const unsigned adr = ring0 + lr * ROWB + ((lq ^ (lr >> 1 & 7)) << 4);
+    const unsigned x_adr = ring0 + 16 * ROWB + (lr % XR) * ROWB + ((lq ^ ((lr % XR) >> 1 & 7)) << 4);      // columns 8..15 of 8 rows: not stored
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto load = [&](int d, int st) {
-        const int k = (st + rot < n_stage ? st + rot : st + rot - n_stage) * 64;
+    int kst = rot;                                         // next stage to issue
+    auto issue = [&](int slot) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            a[d][h] = *reinterpret_cast<const bf16x8 *>(w + k + h * 32);
-            b[d][h] = *reinterpret_cast<const bf16x8 *>(x + k + h * 32);
-        }
+        for (int j = 0; j < LOADS; ++j)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[j] + (size_t)kst * BK),
+                                             (__attribute__((address_space(3))) void *)(ring + slot * STAGE + j * 1024), 16, 0, 0);
+        if (++kst == n_stage) kst = 0;
     };
-    auto multiply = [&](int d) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[d][h], b[d][h], acc, 0, 0, 0);
+    auto multiply = [&](auto slot) {                       // a ring is its wave's own: no barrier
+        constexpr int AT = decltype(slot)::value * STAGE;
+        bf16x8 a0 = lds_read16<AT>(adr), a1 = lds_read16<AT>(adr ^ 64u), b0 = lds_read16<AT>(x_adr), b1 = lds_read16<AT>(x_adr ^ 64u);
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a0), "+v"(a1), "+v"(b0), "+v"(b1) : : "memory");
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b0, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b1, acc, 0, 0, 0);
     };
 #pragma unroll
-    for (int d = 0; d < kDeep; ++d)
-        if (d < n_stage) load(d, d);
+    for (int d = 0; d < kDeep; ++d) issue(d);              // a plane has at least 8 stages
     int st = 0;
     for (; st + 2 * kDeep <= n_stage; st += kDeep)
-#pragma unroll
-        for (int d = 0; d < kDeep; ++d) {
+        static_for<0, kDeep>([&](auto d) {
+            wait_vmcnt((kDeep - 1) * LOADS);                   // the oldest stage has landed
             multiply(d);
-            load(d, st + d + kDeep);
-        }
-    for (; st < n_stage; st += kDeep)
-#pragma unroll
-        for (int d = 0; d < kDeep; ++d)
-            if (st + d < n_stage) {
-                multiply(d);
-                if (st + d + kDeep < n_stage) load(d, st + d + kDeep);
+            issue(decltype(d)::value);
+        });
+    const int left = n_stage - st - kDeep;                 // stages still to issue, less than a ring
+    static_for<0, 2 * kDeep - 1>([&](auto d) {
+        constexpr int D = decltype(d)::value;
+        if (D < left + kDeep) {
+            if (D < left) {
+                wait_vmcnt((kDeep - 1) * LOADS);
+                multiply(std::integral_constant<int, D % kDeep>());
+                issue(D % kDeep);
+            } else {
+                if (D == left) wait_vmcnt(0);
+                multiply(std::integral_constant<int, D % kDeep>());
             }
+        }
+    });
+    __syncthreads();                                       // the rings are free
     planes[sp][lane] = acc;
     __syncthreads();
     if (sp != 0 || lr >= rows) return;
@@ -70,8 +95,8 @@ __global__ __launch_bounds__(64 * S) void gemm_rows16_kernel(const bf16_t *__res
     *reinterpret_cast<uint2 *>(Y + at) = ov;
 }
 
-// Where the kernel is taken.  Every workgroup reads all of X for its 16 W rows, so what it saves shrinks with the rows, and
-// with workgroups that are more than the CUs but do not fill them twice.  Microseconds saved by one projection inside a step
+// Where the kernel is taken with 8 X rows a stage.  The line was drawn with loads straight into MFMA layout, when every row of
+// X cost (microseconds saved by one projection inside a step
 // of one layer / of three (whose weights leave the caches in between), 14 layer widths:
 //   at most 256 workgroups, 2 or 4 planes: 1, 4, 8 rows x 2560 x 6912 2.7/3.6, 4.3/2.5, 2.9/2.1, x 3072 x 3072 2.3/3.2, 1.8/2.7, 1.8/2.0,
 //     x 4096 x 11008 4.8/4.5, 5.6/5.4, 4.1/5.0, the least x 2048 x 2048 0/1.6, 0.7/1.2, 0.3/0.9
@@ -88,12 +113,45 @@ bool gemm_rows16_supported(int rows, int N, int K, int S) {
     return wg < 512 ? rows <= 2 && K < 2 * N : S > 2 && rows <= 5;
 }
 
+// Where the kernel is taken with 16 X rows a stage: the rest up to 16 rows.  Every workgroup reads all of X for its 16 W rows, so
+// with workgroups that are more than the CUs but do not fill them twice the CUs with two set the pace, and two planes of a large
+// matrix do not save what that costs.  A layer's step, planes summed by a launch of their own beyond the line above -> in the
+// workgroup throughout, us a layer:
+//   at most 256 workgroups, or 512 and more: 4096 wide, 14336 MLP, 9 / 13 / 16 rows 117.0 / 119.0 / 117.6 -> 112.5 / 114.3 / 117.2; 3072 x 8192
+//     83.3 / 83.8 / 84.6 -> 75.9 / 79.3 / 83.2; 2048 x 5632 65.1 / 66.0 / 66.4 -> 56.3 / 57.7 / 58.9; 3584 x 18944 140.3 / 141.6 / 142.1 -> 136.4 / 139.0
+//     / 142.6; 8192 x 28672 359 / 355 / 361 -> 339 / 345 / 351; two planes of 16384 x 2048 (2048 wide, 64-wide heads) 66.7 / 67.5 / 68.9 -> 60.7 / 62.0 / 64.5
+//   257 to 511: 5120 x 13824 1 / 4 / 8 / 13 rows 156.8 / 160.5 / 164.0 / 168.6 -> 155.7 / 158.0 / 164.9 / 175.6; 6144 x 16384 209.7 / 214.2 / 215.6 /
+//     217.9 -> 208.4 / 212.8 / 217.0 / 223.6; two planes of 15360 x 5120, in the first of these from 13 rows on: 168.6 -> 173.4
+bool gemm_rows16_wide_supported(int rows, int N, int K, int S) {
+    if (S != 2 && S != 4 && S != 8) return false;
+    const int wg = N / 16;
+    const bool all = wg <= 256 || (wg >= 512 && (S > 2 || (size_t)N * K <= (size_t)48 << 20));
+    return rows <= (all ? 16 : 6);
+}
+
 hipError_t launch_gemm_rows16(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int S) {
-#define DYN_ROWS(SC) hipLaunchKernelGGL(gemm_rows16_kernel<SC>, dim3(N / 16), dim3(64 * SC), 0, s, (const bf16_t *)X, ldx, (const bf16_t *)W, \
-                                        (const bf16_t *)R, (bf16_t *)Y, rows, N, K)
-    if (S == 8) DYN_ROWS(8);
-    else if (S == 4) DYN_ROWS(4);
-    else DYN_ROWS(2);
+    static_assert(8 * kDeep * 4096 <= 160 * 1024, "eight planes' rings do not fit in LDS");
+#define DYN_ROWS(SC, XR)                                                                                                    \
+    do {                                                                                                                    \
+        constexpr int LDS = SC * kDeep * (2 + XR / 8) * 1024;                                                               \
+        static bool attr_set = false;                                                                                       \
+        if (!attr_set) {                                                                                                    \
+            const hipError_t e = hipFuncSetAttribute((const void *)gemm_rows16_kernel<SC, XR>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS); \
+            if (e != hipSuccess) return e;                                                                                  \
+            attr_set = true;                                                                                                \
+        }                                                                                                                   \
+        hipLaunchKernelGGL((gemm_rows16_kernel<SC, XR>), dim3(N / 16), dim3(64 * SC), LDS, s, (const bf16_t *)X, ldx, (const bf16_t *)W, \
+                           (const bf16_t *)R, (bf16_t *)Y, rows, N, K);                                                     \
+    } while (0)
+    if (gemm_rows16_supported(rows, N, K, S)) {            // at most 8 rows
+        if (S == 8) DYN_ROWS(8, 8);
+        else if (S == 4) DYN_ROWS(4, 8);
+        else DYN_ROWS(2, 8);
+    } else {
+        if (S == 8) DYN_ROWS(8, 16);
+        else if (S == 4) DYN_ROWS(4, 16);
+        else DYN_ROWS(2, 16);
+    }
 #undef DYN_ROWS
     return hipGetLastError();
 }

@@ -3,7 +3,7 @@ same rows in other launches."""
 import pytest
 import torch
 
-from gpu_util import GpuRun, check_against_oracle, say
+from gpu_util import GpuRun, check_against_oracle, gemm_path, say
 from paper_2605_21603_amd import binding as B
 from test_gpu_generic_paths import both_schedules, workload
 from workloads import gen
@@ -68,3 +68,21 @@ def test_fp32_projections_take_weights_at_any_float():
     run.layer = B.DynLayer(B.make_config(w.shape, 0), run.weights)
     y1, _, _ = run.run(B.sequential())
     assert torch.equal(y0, y1)
+
+
+# planes summed inside the workgroup with 16 X rows a stage: 2, 4 and 8 planes of 8, 12, 15, 16, 19 and 28 stages (four on their
+# way), up to the last row it is taken for (16; 6 with 257..511 workgroups; two planes of a wide gate/up projection), against the bits of 21 and
+# of the remaining rows in other launches
+@pytest.mark.parametrize("hidden,n_q,n_kv,hd,inter,rows,reached", [
+    (1024, 16, 4, 64, 3072, 9, 3), (1024, 16, 4, 64, 3072, 16, 3), (2048, 16, 4, 128, 7680, 13, 4), (2048, 16, 4, 128, 7680, 16, 4),
+    (3072, 24, 8, 128, 8192, 6, 4), (3072, 24, 8, 128, 8192, 7, 3), (3072, 24, 8, 128, 9728, 15, 2), (4096, 32, 1, 128, 14336, 16, 2),
+    (2048, 32, 8, 64, 8192, 11, 3)])
+def test_up_to_16_rows_match_the_bits_of_larger_launches(hidden, n_q, n_kv, hd, inter, rows, reached):
+    wide = B.lib()._ZN3dyn26gemm_rows16_wide_supportedEiiii
+    shapes = (((n_q + 2 * n_kv) * hd, hidden), (hidden, n_q * hd), (hidden, inter), (2 * inter, hidden))
+    assert sum(wide(rows, N, K, gemm_path(rows, N, K).split) & 0xff != 0 for N, K in shapes) == reached
+    w = workload("up_to_16", "bf16", hidden, n_q, n_kv, hd, inter, [(1, 1 + (i * 31) % 300) for i in range(21)], seed=96)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, rows, 21))
+    data = gen.generate(w)
+    y, k, v = both_schedules(w, data)
+    check_against_oracle(w, data, y, k, v)
