@@ -57,6 +57,7 @@ struct Dispatch {
     bool noop;               // launches nothing: no rows, or the gate when the projection's epilogue applied it
     std::vector<int> deps;   // dispatches (indices into the plan) whose output rows this one reads
     bool plan = false;          // first norm: its launch also builds the attention work lists of its rows; attention: they have been built
+    bool gated = false;         // gate/up and SiLU: the gate is applied by the gate/up dispatch (plan_gated)
     bool lists_ready = false;   // MoE down projection: the gate/up dispatch of the same rows already built its expert lists
     int key() const { return partition * DYN_MAX_STREAMS + stream; }
 };
@@ -154,7 +155,7 @@ Sizes tensor_sizes(const dyn_layer *L, int T, int max_pages, bool prompts) {
     z.attn = t * z.ld_attn * e;
     z.x2 = t * c.hidden * e;
     // the [gate | up] intermediate exists only when the SiLU gate is not applied in the projection's epilogue
-    z.gu = dyn::gemm_gated_supported(c.dtype, 2 * c.mlp_inter, c.hidden) ? 0 : t * pairs * 2 * c.mlp_inter * e;
+    z.gu = dyn::gemm_gated_supported(c.dtype, 2 * c.mlp_inter, c.hidden, c.n_experts > 0) ? 0 : t * pairs * 2 * c.mlp_inter * e;
     z.act = t * pairs * z.ld_act * e;
     z.xa = c.n_layers > 1 ? t * c.hidden * e : 0;
     z.xb = c.n_layers > 2 ? t * c.hidden * e : 0;
@@ -173,7 +174,7 @@ ScratchBytes dispatch_scratch(const dyn_layer *L, const Sizes &z, int op, int ro
     if (rows <= 0) return k;
     const size_t r = (size_t)rows;
     const int H = c.hidden, I = c.mlp_inter, NQKV = qkv_width(c), NQ = c.n_q_heads * c.head_dim;
-    const bool moe = c.n_experts > 0, gated = dyn::gemm_gated_supported(c.dtype, 2 * I, H);
+    const bool moe = c.n_experts > 0;
     auto planes = [&](int N, int K) {
         return dyn::gemm_uses_plane_buffer(c.dtype, rows, N, K) ? (size_t)dyn::gemm_split_k(c.dtype, N, K) * r * N * sizeof(float) : 0;
     };
@@ -188,8 +189,8 @@ ScratchBytes dispatch_scratch(const dyn_layer *L, const Sizes &z, int op, int ro
             if (moe) {
                 k.lists = r * c.top_k * 2 * c.n_experts * sizeof(int32_t);   // E counts + E lists of up to rows * top_k pairs
                 const int S = dyn::gemm_split_k(c.dtype, 2 * I, H, c.n_experts);
-                if (!gated && S > 1) k.planes = (size_t)S * r * c.top_k * 2 * I * sizeof(float);
-            } else if (!gated) {
+                if (S > 1 && !dyn::gemm_gated_supported(c.dtype, 2 * I, H, true)) k.planes = (size_t)S * r * c.top_k * 2 * I * sizeof(float);
+            } else {
                 k.planes = planes(2 * I, H);
             }
             break;
@@ -248,6 +249,17 @@ const char *op_name(int op) {
 // ready-operator rule covers them) and launch nothing.
 bool fused_into_producer(int op, int layer) {
     return op == DYN_OP_ROPE_KV || op == DYN_OP_NORM2 || (op == DYN_OP_NORM1 && layer > 0);
+}
+
+// Whether the gate/up dispatches of a plan apply the SiLU gate themselves, so that no [gate | up] tensor exists: in
+// the projection's epilogue where it has one, and where planes are summed by a launch of their own in that
+// launch - if that is so for every micro-batch; one that folds its planes in registers stores gate and up.
+bool plan_gated(const dyn_layer_config &c, const std::vector<Dispatch> &plan) {
+    if (dyn::gemm_gated_supported(c.dtype, 2 * c.mlp_inter, c.hidden, c.n_experts > 0)) return true;
+    if (c.n_experts || !dyn::reduce_gate_supported(c.dtype, c.mlp_inter)) return false;
+    for (const Dispatch &d : plan)
+        if (d.op == DYN_OP_GATE_UP && d.r1 > d.r0 && !dyn::gemm_uses_plane_buffer(c.dtype, d.r1 - d.r0, 2 * c.mlp_inter, c.hidden)) return false;
+    return true;
 }
 
 // Checks of an explicit schedule that need no batch: counts in range, arrays present, masks not empty.
@@ -354,12 +366,11 @@ dyn_status build_plan(const dyn_layer *L, const dyn_batch *b, const dyn_schedule
             Dispatch d{};
             d.layer = l; d.op = sl.op; d.nano = sl.nano; d.n_nano = sl.n_nano; d.r0 = rows[sl.nano]; d.r1 = rows[sl.nano + sl.n_nano];
             d.stream = sl.stream; d.partition = sl.partition;
-            // Operators that launch nothing of their own: the SiLU gate where the gate/up projection's epilogue
-            // applies it; rotary + cache append, which the qkv projection's dispatch applies to the rows it
+            // Operators that launch nothing of their own: the SiLU gate where the gate/up projection's dispatch
+            // applies it (below); rotary + cache append, which the qkv projection's dispatch applies to the rows it
             // wrote; the second norm, applied by the o projection's dispatch; and from the second layer on
             // the first norm, applied by the previous layer's down projection (fused_into_producer).
-            d.noop = d.r1 <= d.r0 || (sl.op == DYN_OP_SILU && dyn::gemm_gated_supported(L->cfg.dtype, 2 * L->cfg.mlp_inter, L->cfg.hidden)) ||
-                     fused_into_producer(sl.op, l);
+            d.noop = d.r1 <= d.r0 || fused_into_producer(sl.op, l);
             {   // sequences inside [r0, r1): cut points are sequence boundaries
                 const int32_t *q = b->q_start_host;
                 const int s0 = (int)(std::lower_bound(q, q + b->n_seqs + 1, d.r0) - q);
@@ -380,6 +391,11 @@ dyn_status build_plan(const dyn_layer *L, const dyn_batch *b, const dyn_schedule
                 if (dep >= 0 && std::find(d.deps.begin(), d.deps.end(), dep) == d.deps.end()) d.deps.push_back(dep);
             }
             plan.push_back(std::move(d));
+        }
+    if (plan_gated(L->cfg, plan))
+        for (Dispatch &d : plan) {
+            d.gated = d.op == DYN_OP_GATE_UP || d.op == DYN_OP_SILU;
+            if (d.op == DYN_OP_SILU) d.noop = true;
         }
     // The attention work lists depend on the rows' sequences and positions only, and every layer walks the same
     // ones: where the first layer's norm is dispatched over exactly the rows of an attention dispatch (which
@@ -446,7 +462,7 @@ WsLayout plan_layout(const dyn_layer *L, const dyn_batch *b, const std::vector<D
     w.slot.assign((size_t)std::max(n_slots, 0), SlotScratch{});
     if (P == 0 || n_slots == 0) return w;
     const std::vector<int> until = alive_until(plan);
-    const bool moe = c.n_experts > 0, gated = dyn::gemm_gated_supported(c.dtype, 2 * c.mlp_inter, c.hidden);
+    const bool moe = c.n_experts > 0, gated = plan_gated(c, plan);
 
     bool single_stream = true;
     {
@@ -721,8 +737,8 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
                 err = dyn::launch_expert_lists((const int32_t *)(base + ws.sel), n_pairs, pair0, c.n_experts, n_pairs, counts, lists, st);
                 if (err != hipSuccess) break;
                 dyn::GemmGroups gr{counts, lists, n_pairs, c.top_k, c.n_experts, (size_t)2 * I * H, 0};
-                if (dyn::gemm_gated_supported(c.dtype, 2 * I, H)) {   // SiLU gate in the epilogue: DYN_OP_SILU has nothing left to do
-                    err = dyn::launch_gemm_gated(base + ws.h, ws.ld_h, w.w_gate_up, base + ws.act, ws.ld_act, gr, rows, 2 * I, H, st, mid);
+                if (d.gated) {                                    // SiLU gate in the epilogue: DYN_OP_SILU has nothing left to do
+                    err = dyn::launch_gemm_gated(c.dtype, base + ws.h, ws.ld_h, w.w_gate_up, base + ws.act, ws.ld_act, gr, rows, 2 * I, H, st, mid);
                     break;
                 }
                 // the grouped kernels index planes by pair id: the dispatch's planes start at its first pair
@@ -731,16 +747,26 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
                                                n_pairs, 2 * I, H, st, mid);
                 break;
             }
-            if (dyn::gemm_gated_supported(c.dtype, 2 * I, H)) {       // SiLU gate in the epilogue: DYN_OP_SILU has nothing left to do
-                err = dyn::launch_gemm_gated(rowp(base + ws.h, ws.ld_h), ws.ld_h, w.w_gate_up, (void *)rowp(base + ws.act, ws.ld_act),
-                                             ws.ld_act, dyn::GemmGroups{}, rows, 2 * I, H, st, mid);
+            if (d.gated) {                                        // DYN_OP_SILU has nothing left to do
+                void *const act = (void *)rowp(base + ws.act, ws.ld_act);
+                if (dyn::gemm_uses_plane_buffer(c.dtype, rows, 2 * I, H)) {     // a launch that needs no planes after all leaves gate and up there
+                    dyn::GemmEpilogue ep;
+                    ep.kind = dyn::GemmEpilogue::GATE;
+                    ep.h_out = act;
+                    ep.ld_h = ws.ld_act;
+                    err = dyn::launch_gemm(c.dtype, rowp(base + ws.h, ws.ld_h), ws.ld_h, w.w_gate_up, nullptr, planes, planes, (size_t)rows * 2 * I,
+                                           rows, 2 * I, H, st, mid, &ep);
+                } else {
+                    err = dyn::launch_gemm_gated(c.dtype, rowp(base + ws.h, ws.ld_h), ws.ld_h, w.w_gate_up, act, ws.ld_act, dyn::GemmGroups{}, rows,
+                                                 2 * I, H, st, mid);
+                }
                 break;
             }
             err = dyn::launch_gemm(c.dtype, rowp(base + ws.h, ws.ld_h), ws.ld_h, w.w_gate_up, nullptr, (void *)rowp(base + ws.gu, 2 * I),
                                    planes, (size_t)rows * 2 * I, rows, 2 * I, H, st, mid);
             break;
         case DYN_OP_SILU:
-            if (dyn::gemm_gated_supported(c.dtype, 2 * I, H)) break;   // done in the gate/up projection's epilogue
+            if (d.gated) break;                                   // done by the gate/up projection's dispatch
             if (c.n_experts) {
                 const size_t pair0 = (size_t)d.r0 * c.top_k;
                 err = dyn::launch_silu_mul(c.dtype, base + ws.gu + pair0 * 2 * I * e, base + ws.act + pair0 * ws.ld_act * e,
@@ -920,7 +946,7 @@ void analyse_memory(const dyn_layer *L, const dyn_batch *b, const std::vector<Di
     const size_t e = esize(c);
     const Sizes ws = tensor_sizes(L, b->n_tokens, b->max_pages_per_seq, b->n_tokens > b->n_seqs);
     const int n_slots = (int)plan.size() / c.n_layers;
-    const bool moe = c.n_experts > 0, gated = dyn::gemm_gated_supported(c.dtype, 2 * c.mlp_inter, c.hidden);
+    const bool moe = c.n_experts > 0, gated = plan_gated(c, plan);
     const int pairs = moe ? c.top_k : 1, H = c.hidden, I = c.mlp_inter, NQKV = qkv_width(c), NQ = c.n_q_heads * c.head_dim;
     int slot_of[DYN_N_OPS][DYN_MAX_NANO];
     for (auto &r : slot_of) std::fill(r, r + DYN_MAX_NANO, -1);
@@ -983,7 +1009,7 @@ void analyse_memory(const dyn_layer *L, const dyn_batch *b, const std::vector<Di
             case DYN_OP_GATE_UP:
                 scratch[i] = moe ? lists + (gated ? 0 : (size_t)dyn::gemm_split_k(c.dtype, 2 * I, H, c.n_experts) > 1
                                                             ? (size_t)dyn::gemm_split_k(c.dtype, 2 * I, H, c.n_experts) * r * pairs * 2 * I * sizeof(float) : 0)
-                                 : (gated ? 0 : planes(2 * I, H));
+                                 : planes(2 * I, H);
                 break;
             case DYN_OP_DOWN:
                 scratch[i] = moe ? lists + (size_t)dyn::gemm_split_k(c.dtype, H, I, c.n_experts) * r * c.top_k * H * sizeof(float) : planes(H, I);

@@ -67,8 +67,10 @@ hipError_t launch_rmsnorm(int dtype, const void *x, const void *g, void *out, in
 // applies it (one pass over the planes); otherwise the operator's own kernel runs on the rows the
 // projection wrote.  Either way every element sees the same arithmetic in the same order.
 struct GemmEpilogue {
-    enum { NONE = 0, NORM = 1, ROPE = 2 } kind = NONE;
+    enum { NONE = 0, NORM = 1, ROPE = 2, GATE = 3 } kind = NONE;
     // NORM: h_out[row] = RMSNorm(Y[row]) * g, row pitch ld_h
+    // GATE: h_out[row] = silu(first half of Y[row]) * second half, row pitch ld_h; Y is written only where no planes are, and may lie
+    // on the plane buffer
     const void *g = nullptr;
     void *h_out = nullptr;
     int ld_h = 0;
@@ -90,6 +92,8 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
 // fp32 projection, plain or expert-grouped (kernels_gemm_f32.hip; launch_gemm and launch_gemm_grouped call it); max_rows bounds a group's rows.
 hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const void *R, void *Y, int max_rows, int N, int K, const GemmGroups &gr,
                            hipStream_t s);
+bool gemm_f32_gated_supported(int N2, int K);
+hipError_t launch_gemm_f32_gated(const void *X, int ldx, const void *W, void *Y, int ldy, int rows, int N2, int K, hipStream_t s);
 // A few rows (at most 16), planes summed in the workgroup (kernels_gemm_rows.hip; launch_gemm calls it).
 bool gemm_rows16_supported(int rows, int N, int K, int S);            // with 8 X rows a stage
 bool gemm_rows16_wide_supported(int rows, int N, int K, int S);       // with 16
@@ -106,11 +110,11 @@ hipError_t launch_gemm_grouped(int dtype, const void *X, int ldx, const void *W,
                                size_t plane_stride, const GemmGroups &gr, int max_rows, int row0, int n_rows, int N, int K,
                                hipStream_t s, hipEvent_t mid = nullptr);
 
-// Gate/up projection with the SiLU gate applied in the epilogue (bf16, split factor 1 only):
+// Gate/up projection with the SiLU gate applied in the epilogue (bf16: split factor 1 only; fp32: not expert-grouped):
 // Y[row, N2/2] = silu(X Wg^T) * (X Wu^T), row pitch ldy.  gr.n_groups = 0: plain, pointers offset to
 // the dispatch's first row, max_rows rows.  Grouped: as launch_gemm_grouped.
-bool gemm_gated_supported(int dtype, int N2, int K);
-hipError_t launch_gemm_gated(const void *X, int ldx, const void *W, void *Y, int ldy, const GemmGroups &gr, int max_rows,
+bool gemm_gated_supported(int dtype, int N2, int K, bool experts);
+hipError_t launch_gemm_gated(int dtype, const void *X, int ldx, const void *W, void *Y, int ldy, const GemmGroups &gr, int max_rows,
                              int N2, int K, hipStream_t s, hipEvent_t mid = nullptr);
 
 // MoE router for token rows: logits = h W_r^T in fp32, top_k largest (ties to the lower index),
@@ -154,6 +158,9 @@ hipError_t launch_attention(int dtype, const void *qkv, const int32_t *seq_of_to
                             hipEvent_t pre = nullptr,   // pre: recorded after the work-list kernel, before the chunk kernel
                             bool plan_ready = false);   // `plan` already holds the lists of these rows (built by the first norm's launch or an earlier layer's call)
 
+// The same from a gate/up projection's split-K planes ([rows, 2 I] each): summed in plane order, rounded to bf16, gated.
+bool reduce_gate_supported(int dtype, int I);
+hipError_t launch_reduce_gate(const float *P, size_t plane_stride, int S, void *out, int ld_out, int rows, int I, hipStream_t s);
 // out[rows, I] = silu(gu[:, :I]) * gu[:, I:]
 hipError_t launch_silu_mul(int dtype, const void *gu, void *out, int ld_out, int rows, int I, hipStream_t s);
 

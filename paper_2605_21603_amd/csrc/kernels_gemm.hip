@@ -345,13 +345,14 @@ hipError_t run_epilogue(int dtype, const GemmEpilogue &ep, void *Y, int rows, in
     if (ep.kind == GemmEpilogue::NORM) return launch_rmsnorm(dtype, Y, ep.g, ep.h_out, ep.ld_h, rows, N, ep.eps, s);
     if (ep.kind == GemmEpilogue::ROPE)
         return launch_rope_kv(dtype, Y, ep.seq_of_token, ep.pos_of_token, ep.block_table, ep.k_cache, ep.v_cache, *ep.rope, *ep.shape, rows, s);
+    if (ep.kind == GemmEpilogue::GATE) return launch_silu_mul(dtype, Y, ep.h_out, ep.ld_h, rows, N / 2, s);
     return hipSuccess;
 }
 
 GemmEpilogue epilogue_at(const GemmEpilogue &ep, int dtype, int row, int N) {      // the same epilogue for rows starting `row` rows in
     GemmEpilogue e = ep;
     const size_t es = dtype == 0 ? 4 : 2;
-    if (e.kind == GemmEpilogue::NORM) e.h_out = (char *)e.h_out + (size_t)row * e.ld_h * es;
+    if (e.kind == GemmEpilogue::NORM || e.kind == GemmEpilogue::GATE) e.h_out = (char *)e.h_out + (size_t)row * e.ld_h * es;
     if (e.kind == GemmEpilogue::ROPE) { e.seq_of_token += row; e.pos_of_token += row; }
     (void)N;
     return e;
@@ -408,6 +409,7 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
     if (has_ep && ep->kind == GemmEpilogue::ROPE && !R && reduce_rope_supported(dtype, *ep->shape))
         return launch_reduce_rope(partial, plane_stride, S, Y, ep->seq_of_token, ep->pos_of_token, ep->block_table, ep->k_cache,
                                   ep->v_cache, *ep->rope, *ep->shape, rows, s);
+    if (has_ep && ep->kind == GemmEpilogue::GATE) return launch_reduce_gate(partial, plane_stride, S, ep->h_out, ep->ld_h, rows, N / 2, s);
     const size_t n_vec = (size_t)rows * N / 4;
     const int blocks = (int)((n_vec + 255) / 256 < 2048 ? (n_vec + 255) / 256 : 2048);
     hipLaunchKernelGGL(gemm_reduce_kernel, dim3(blocks), dim3(256), 0, s, partial, plane_stride, (const bf16_t *)R,
@@ -435,14 +437,20 @@ GroupTile gemm_group_tile(const GemmGroups &gr, int max_rows, int N) {
 }
 }  // namespace
 
-bool gemm_gated_supported(int dtype, int N2, int K) { return dtype == 1 && gemm_split_k(dtype, N2, K) == 1; }
+bool gemm_gated_supported(int dtype, int N2, int K, bool experts) {
+    return dtype == 1 ? gemm_split_k(dtype, N2, K) == 1 : !experts && gemm_f32_gated_supported(N2, K);
+}
 
 // act[rows or listed rows, N2/2] = silu(X Wg^T) * (X Wu^T) with W = [gate rows; up rows] ([N2, K]),
 // output row pitch ldy.  Plain (gr.n_groups = 0: X, Y offset to the dispatch) or expert-grouped.
-hipError_t launch_gemm_gated(const void *X, int ldx, const void *W, void *Y, int ldy, const GemmGroups &gr, int max_rows,
+hipError_t launch_gemm_gated(int dtype, const void *X, int ldx, const void *W, void *Y, int ldy, const GemmGroups &gr, int max_rows,
                              int N2, int K, hipStream_t s, hipEvent_t mid) {
     if (max_rows <= 0) return hipSuccess;
     hipError_t e;
+    if (dtype == 0) {
+        e = launch_gemm_f32_gated(X, ldx, W, Y, ldy, max_rows, N2, K, s);
+        return e == hipSuccess && mid ? hipEventRecord(mid, s) : e;
+    }
 #define DYN_GATED(BN, MT, NS, NW) \
     launch_gemm_bf16<BN, MT, false, NS, true, NW>(grid, s, X, ldx, W, nullptr, Y, nullptr, 0, max_rows, N2, K, 1, gr, ldy)
     const GroupTile t = gemm_group_tile(gr, max_rows, N2);
@@ -455,7 +463,7 @@ hipError_t launch_gemm_gated(const void *X, int ldx, const void *W, void *Y, int
         const GemmPath p = gemm_path(1, max_rows, N2, K);          // split factor 1: no planes on any path
         if (p.tail_rows) {     // the last rows in a launch of their own (never a wide one: at most 256 rows)
             const int head = max_rows - p.tail_rows;
-            e = launch_gemm_gated((const bf16_t *)X + (size_t)head * ldx, ldx, W, (bf16_t *)Y + (size_t)head * ldy, ldy, gr,
+            e = launch_gemm_gated(dtype, (const bf16_t *)X + (size_t)head * ldx, ldx, W, (bf16_t *)Y + (size_t)head * ldy, ldy, gr,
                                   p.tail_rows, N2, K, s, nullptr);
             if (e != hipSuccess) return e;
             max_rows = head;

@@ -35,13 +35,39 @@ __device__ __forceinline__ void f32_store(f32x4 o, size_t at, int n, int N, cons
     }
 }
 
-// The eight waves' sums of a tile meet in LDS, SUB sub-tiles of 16 x 16 at a time, a wave to a sub-tile.  D: lane l holds W rows
-// 4 (l / 16) + r of X row l % 16.  list: output rows (null: m itself).
-template <int NA, int NB, bool TURN>
+// silu(g) * u
+__device__ __forceinline__ f32x4 f32_gate(f32x4 g, f32x4 u) {
+    f32x4 o;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) o[r] = g[r] / (1.0f + expf(-g[r])) * u[r];
+    return o;
+}
+
+// The eight waves' sums of a tile meet in LDS, SUB sub-tiles of 16 x 16 at a time, a wave to a sub-tile (GATED: to a pair, gate columns in
+// a = 0 and the up columns beside them in a = 1).  D: lane l holds W rows 4 (l / 16) + r of X row l % 16.  list: output rows (null: m itself).
+template <int NA, int NB, bool TURN, bool GATED = false>
 __device__ __forceinline__ void f32_finish(f32x4 (*part)[NA * NB < 4 ? NA * NB : 4][64], const f32x4 (&acc)[NA][NB], int m0, int n0, int M, int N,
-                                           const int32_t *list, const float *__restrict__ R, float *__restrict__ Y) {
+                                           const int32_t *list, const float *__restrict__ R, float *__restrict__ Y, int ldy = 0) {
     constexpr int SUB = NA * NB < 4 ? NA * NB : 4;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15, lq = lane >> 4;
+    if constexpr (GATED) {
+        static_assert(NA == 2 && SUB == NA * NB, "one pair of sub-tiles per 16 rows of X");
+#pragma unroll
+        for (int i = 0; i < SUB; ++i) part[wave][i][lane] = acc[i / NB][i % NB];
+        __syncthreads();
+        if (wave < NB) {
+            f32x4 g = part[f32_chain(0, n0)][wave][lane], u = part[f32_chain(0, n0)][NB + wave][lane];
+#pragma unroll
+            for (int w = 1; w < kF32Chains; ++w) {
+                const f32x4 p = part[f32_chain(w, n0)][wave][lane], q = part[f32_chain(w, n0)][NB + wave][lane];
+                g[0] += p[0]; g[1] += p[1]; g[2] += p[2]; g[3] += p[3];
+                u[0] += q[0]; u[1] += q[1]; u[2] += q[2]; u[3] += q[3];
+            }
+            const int m = m0 + wave * 16 + lr;
+            if (m < M) *reinterpret_cast<f32x4_u *>(Y + (size_t)m * ldy + n0 + 4 * lq) = f32_gate(g, u);
+        }
+        return;
+    }
 #pragma unroll
     for (int s0 = 0; s0 < NA * NB; s0 += SUB) {
         if (s0) __syncthreads();
@@ -152,17 +178,18 @@ __device__ __forceinline__ void quad_transpose(f32x4 (&v)[4]) {
 // 15.9 -> 11.0 us, 100 rows 30.7 -> 19.2); with 32 x 32 that costs the second workgroup of a CU (225 rows x 1024 x 4096 31.6 -> 28.8
 // us, 30.3 with two).  Trading takes 64 vector instructions an operand: what is one short block long gains nothing
 // (4 rows x 1024 x 1024 4.6 -> 5.1 us, x 8192 x 1024 8.0 -> 8.9, x 1024 x 4096 12.0 -> 10.8).
-template <int MT, int NT>
+// GATED: the NT rows are NT / 2 gate columns from n0 on and the N / 2 rows later up columns beside them; Y (pitch ldy) = silu(gate) * up.
+template <int MT, int NT, bool GATED = false>
 __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_quads_kernel(const float *__restrict__ X, int ldx, const float *__restrict__ W,
-                                                                        const float *__restrict__ R, float *__restrict__ Y, int M, int N, int K) {
-    constexpr int NA = NT / 16, NB = MT / 16, NBUF = NA + NB <= 2 ? 2 : 1;
+                                                                        const float *__restrict__ R, float *__restrict__ Y, int M, int N, int K, int ldy) {
+    constexpr int NA = NT / 16, NB = MT / 16, NBUF = NA + NB <= 3 ? 2 : 1;
     __shared__ f32x4 part[kF32Chains][NA * NB < 4 ? NA * NB : 4][64];
-    const int m0 = blockIdx.y * MT, n0 = blockIdx.x * NT;
+    const int m0 = blockIdx.y * MT, n0 = blockIdx.x * (GATED ? NT / 2 : NT);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), row4 = (lane >> 2 & 3) * 4, col = (lane >> 4) * 16 + (lane & 3) * 4;
     const float *const Wt = W + (size_t)n0 * K, *const Xt = X + (size_t)m0 * ldx;
     size_t wo[NA], xo[NB][4];                              // rows past the end read the last ones; what they give is not stored
 #pragma unroll
-    for (int a = 0; a < NA; ++a) wo[a] = (size_t)min(a * 16 + row4, N - 4 - n0) * K + col;
+    for (int a = 0; a < NA; ++a) wo[a] = (size_t)(GATED ? a * (N / 2) + row4 : min(a * 16 + row4, N - 4 - n0)) * K + col;
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -230,7 +257,7 @@ __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_quads_kernel(const f
             multiply(b0);
         }
     }
-    f32_finish<NA, NB, true>(part, acc, m0, n0, M, N, nullptr, R, Y);
+    f32_finish<NA, NB, true, GATED>(part, acc, m0, n0, M, N, nullptr, R, Y, ldy);
 }
 
 // Whole blocks, many tiles: 64 x 64, four waves of 32 x 32 that share stages of one block (256-byte rows, direct loads of
@@ -239,12 +266,14 @@ __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_quads_kernel(const f
 // 1024 31 / 56.5 / 79 us with 64 x 64 tiles loaded straight into MFMA layout (eight waves, 16 rows a quarter wave) -> 24.5 /
 // 41.2 / 60.5.  The 16-byte columns are swizzled with the row: lanes of 16 rows read 16
 // different bank groups.
+// GATED: of every 32 W rows of the tile the first 16 are gate columns and the other 16 the up columns beside them.
 constexpr int kF32TileLds = 2 * 128 * 256;
+template <bool GATED>
 __global__ __launch_bounds__(256, 2) void gemm_f32_tiles_kernel(const float *__restrict__ X, int ldx, const float *__restrict__ W,
-                                                                const float *__restrict__ R, float *__restrict__ Y, int M, int N, int K) {
+                                                                const float *__restrict__ R, float *__restrict__ Y, int M, int N, int K, int ldy) {
     constexpr int T = 64, LOADS = 2 * T / 4 / 4, STAGE = 2 * T * 256;
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
-    const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
+    const int m0 = blockIdx.y * T, n0 = blockIdx.x * (GATED ? T / 2 : T);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15, lq = lane >> 4;
     const int wn = wave & 1, wm = wave >> 1;
     const int blocks = K / (kF32Block * kF32Chains), n_stage = kF32Chains * blocks;
@@ -252,7 +281,8 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_tiles_kernel(const float *__r
 #pragma unroll
     for (int j = 0; j < LOADS; ++j) {
         const int row = (j * 4 + wave) * 4 + (lane >> 4), col = ((lane ^ row) & 15) * 4;
-        src[j] = row < T ? W + (size_t)min(n0 + row, N - 1) * K + col : X + (size_t)min(m0 + row - T, M - 1) * ldx + col;
+        const int n = GATED ? n0 + (row >> 5) * 16 + (row & 15) + (row & 16 ? N / 2 : 0) : min(n0 + row, N - 1);
+        src[j] = row < T ? W + (size_t)n * K + col : X + (size_t)min(m0 + row - T, M - 1) * ldx + col;
     }
     int at_chain = 0, at_block = 0;                        // next stage to issue
     auto issue = [&](int st) {
@@ -305,6 +335,14 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_tiles_kernel(const float *__r
             first = false;
         }
     }
+    if constexpr (GATED) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int m = m0 + wm * 32 + b * 16 + lr;
+            if (m < M) *reinterpret_cast<f32x4_u *>(Y + (size_t)m * ldy + n0 + wn * 16 + 4 * lq) = f32_gate(total[0][b], total[1][b]);
+        }
+        return;
+    }
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -319,37 +357,60 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_tiles_kernel(const float *__r
 // 448 tiles, 27.9 -> 19.2; past the line 160 x 1024 x 4096, 640 tiles, 28.4 -> 28.7, 24 x 8192 x 1024, 1024 tiles, 13.2 -> 15.5).  64 x 64
 // where such tiles are about a CU's each: 192 of them (225 rows x 8192 x 1024, 512 tiles: 41 us; 225 x 1536 x 1024, 96 tiles: 23.5 us, with
 // 32 x 32 17.1).  Else 32 x 32.  Other depths and widths, and experts, take the form for any shape.
+//
+// The gated form takes the same tiles over all 2 I columns; its 16-row tile is 16 gate and 16 up columns wide.  It exists for whole
+// blocks and I a multiple of 32; the launch it saves and the [gate | up] rows' way through memory are 5.8 us of a step of 225 rows (1024
+// wide, 4096 MLP: 136.9 -> 131.1 us).
+namespace {
+template <bool GATED>
+hipError_t launch_f32_tiles(const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int ldy, hipStream_t s) {
+    static bool attr_set = false;                      // 64 KB of dynamic LDS: opted in, once
+    if (!attr_set) {
+        const hipError_t e = hipFuncSetAttribute((const void *)gemm_f32_tiles_kernel<GATED>, hipFuncAttributeMaxDynamicSharedMemorySize, kF32TileLds);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(gemm_f32_tiles_kernel<GATED>, dim3((N + 63) / 64, (rows + 63) / 64), dim3(256), kF32TileLds, s, (const float *)X, ldx,
+                       (const float *)W, (const float *)R, (float *)Y, rows, N, K, ldy);
+    return hipGetLastError();
+}
+
+template <int MT, int NT, bool GATED>
+hipError_t launch_f32_quads(const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int ldy, hipStream_t s) {
+    hipLaunchKernelGGL((gemm_f32_quads_kernel<MT, NT, GATED>), dim3((N + NT - 1) / NT, (rows + MT - 1) / MT), dim3(kF32Chains * 64), 0, s,
+                       (const float *)X, ldx, (const float *)W, (const float *)R, (float *)Y, rows, N, K, ldy);
+    return hipGetLastError();
+}
+
+template <bool GATED>
+hipError_t launch_f32_whole(const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int ldy, hipStream_t s) {
+    auto tiles = [&](int t) { return (long)((rows + t - 1) / t) * ((N + t - 1) / t); };
+    const bool aligned = ldx % 4 == 0 && (((uintptr_t)X | (uintptr_t)W) & 15) == 0;      // the direct loads' 16 bytes
+    if (rows <= 16 || tiles(16) <= 512) return launch_f32_quads<16, GATED ? 32 : 16, GATED>(X, ldx, W, R, Y, rows, N, K, ldy, s);
+    if (aligned && tiles(64) >= 192) return launch_f32_tiles<GATED>(X, ldx, W, R, Y, rows, N, K, ldy, s);
+    return launch_f32_quads<32, 32, GATED>(X, ldx, W, R, Y, rows, N, K, ldy, s);
+}
+}  // namespace
+
 hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const void *R, void *Y, int max_rows, int N, int K,
                            const GemmGroups &gr, hipStream_t s) {
+    if (!gr.n_groups && K % (kF32Block * kF32Chains) == 0 && N % 4 == 0) return launch_f32_whole<false>(X, ldx, W, R, Y, max_rows, N, K, N, s);
     const int groups = std::max(gr.n_groups, 1);
     auto tiles = [&](int t) { return (long)((max_rows + t - 1) / t) * ((N + t - 1) / t) * groups; };
-    const bool whole = !gr.n_groups && K % (kF32Block * kF32Chains) == 0 && N % 4 == 0;
-    const bool few = max_rows <= 16 || tiles(16) <= (whole ? 512 : 256);
-#define DYN_F32(KERNEL, T, THREADS, LDS, ...)                                                                                    \
-    hipLaunchKernelGGL(KERNEL, dim3((N + T - 1) / T, (max_rows + T - 1) / T, groups), dim3(THREADS), LDS, s, (const float *)X, ldx, \
-                       (const float *)W, (const float *)R, (float *)Y, max_rows, N, K, ##__VA_ARGS__)
-    if (whole) {
-        const bool aligned = ldx % 4 == 0 && (((uintptr_t)X | (uintptr_t)W) & 15) == 0;      // the direct loads' 16 bytes
-        if (few) {
-            DYN_F32((gemm_f32_quads_kernel<16, 16>), 16, kF32Chains * 64, 0);
-        } else if (aligned && tiles(64) >= 192) {
-            static bool attr_set = false;                  // 64 KB of dynamic LDS: opted in, once
-            if (!attr_set) {
-                const hipError_t e = hipFuncSetAttribute((const void *)gemm_f32_tiles_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kF32TileLds);
-                if (e != hipSuccess) return e;
-                attr_set = true;
-            }
-            DYN_F32(gemm_f32_tiles_kernel, 64, 256, kF32TileLds);
-        } else {
-            DYN_F32((gemm_f32_quads_kernel<32, 32>), 32, kF32Chains * 64, 0);
-        }
-        return hipGetLastError();
-    }
-    if (few) DYN_F32((gemm_f32_kernel<16, 16>), 16, kF32Chains * 64, 0, gr);
-    else if (tiles(64) >= 256) DYN_F32((gemm_f32_kernel<64, 64>), 64, kF32Chains * 64, 0, gr);
-    else DYN_F32((gemm_f32_kernel<32, 32>), 32, kF32Chains * 64, 0, gr);
+#define DYN_F32(T)                                                                                                                                \
+    hipLaunchKernelGGL((gemm_f32_kernel<T, T>), dim3((N + T - 1) / T, (max_rows + T - 1) / T, groups), dim3(kF32Chains * 64), 0, s, (const float *)X, \
+                       ldx, (const float *)W, (const float *)R, (float *)Y, max_rows, N, K, gr)
+    if (max_rows <= 16 || tiles(16) <= 256) DYN_F32(16);
+    else if (tiles(64) >= 256) DYN_F32(64);
+    else DYN_F32(32);
 #undef DYN_F32
     return hipGetLastError();
+}
+
+bool gemm_f32_gated_supported(int N2, int K) { return K % (kF32Block * kF32Chains) == 0 && N2 % 64 == 0; }
+
+hipError_t launch_gemm_f32_gated(const void *X, int ldx, const void *W, void *Y, int ldy, int rows, int N2, int K, hipStream_t s) {
+    return launch_f32_whole<true>(X, ldx, W, nullptr, Y, rows, N2, K, ldy, s);
 }
 
 }  // namespace dyn

@@ -86,3 +86,21 @@ def test_up_to_16_rows_match_the_bits_of_larger_launches(hidden, n_q, n_kv, hd, 
     data = gen.generate(w)
     y, k, v = both_schedules(w, data)
     check_against_oracle(w, data, y, k, v)
+
+
+# The gate applied by the launch that sums a gate/up projection's planes (or, up to 16 rows, reading what the rows' kernel left in the
+# plane buffer) gives the bits of the gate as a launch of its own, which stays where a micro-batch folds its planes in registers:
+# 2 and 4 planes (4 from a depth of 2048 on), parts of a batch on either side of the folded path.
+@pytest.mark.parametrize("hidden,inter,cuts,folded", [
+    (1024, 2048, (0, 700, 1300), (True, False, False)), (1024, 2048, (0, 9, 1300), (True, False, True)), (1024, 1984, (0, 5, 21), (False, False, False)),
+    (2048, 2048, (0, 17, 150), (False, False, False)), (2048, 2048, (0, 300, 1300), (True, False, True))])
+def test_gate_with_the_planes_sum_matches_the_gate_alone(hidden, inter, cuts, folded):
+    uses = B.lib()._ZN3dyn22gemm_uses_plane_bufferEiiii
+    rows = (cuts[-1], cuts[1], cuts[2] - cuts[1])
+    assert tuple(not uses(1, r, 2 * inter, hidden) & 0xff for r in rows) == folded
+    seqs = [(1, 1 + (i * 17) % 90) for i in range(cuts[1])] + [(rows[2], rows[2])]
+    w = workload("gate", "bf16", hidden, 4, 2, 64, inter, seqs, seed=100 + rows[0])
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, cuts)
+    data = gen.generate(w)
+    y, k, v = both_schedules(w, data)                        # the whole batch and its parts: the same bits
+    say("%d rows: %.2e" % (rows[0], check_against_oracle(w, data, y, k, v)))
