@@ -97,7 +97,9 @@ hipError_t launch_gemm_f32_gated(const void *X, int ldx, const void *W, void *Y,
 // A few rows (at most 16), planes summed in the workgroup (kernels_gemm_rows.hip; launch_gemm calls it).
 bool gemm_rows16_supported(int rows, int N, int K, int S);            // with 8 X rows a stage
 bool gemm_rows16_wide_supported(int rows, int N, int K, int S);       // with 16
-hipError_t launch_gemm_rows16(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int S);
+bool gemm_rows16_rope_supported(const AttnShape &sh);                 // with rotary + cache append in the same launch
+hipError_t launch_gemm_rows16(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int S,
+                              const GemmEpilogue *rope);
 // Many rows, split-K planes folded in registers, 256 x 128 tiles (kernels_gemm_wide.hip; launch_gemm calls it).
 hipError_t launch_gemm_fold(int grid, hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N,
                             int K, int S);

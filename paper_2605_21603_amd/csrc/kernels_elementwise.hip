@@ -5,13 +5,9 @@
 #include "common.h"
 #include "kernels.h"
 #include "norm_row.h"
+#include "rotary.h"
 
 namespace dyn {
-
-// A row has the same bits whichever kernel its launch took, so what the compiler could contract either way
-// is written out: the rotation of a pair, and (below) the sums of squares.
-__device__ __forceinline__ float rotated_lo(float a, float b, float c, float s) { return __builtin_fmaf(a, c, -(b * s)); }
-__device__ __forceinline__ float rotated_hi(float a, float b, float c, float s) { return __builtin_fmaf(b, c, a * s); }
 
 // ------------------------------------------------------------------ RMSNorm
 // One 256-thread workgroup per row (norm_row.h).
@@ -156,11 +152,8 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(T *__restrict__ qkv, const
         vp[(size_t)(i + half) * sh.page_size] = z[i + half];
         return;
     }
-    const double ang = (double)pos * tab.inv_freq[i];
-    const double turns = rint(ang * 0.15915494309189535);              // 1 / (2 pi)
-    const float red = (float)fma(-turns, 6.283185307179586, ang);
     float s, c;
-    sincosf(red, &s, &c);
+    rotary_angle(pos, tab.inv_freq[i], s, c);
     const T lo = from_f32<T>(rotated_lo(a, b, c, s)), hi = from_f32<T>(rotated_hi(a, b, c, s));
     if (hh < sh.n_q) {                                   // q head, in place
         z[i] = lo;
@@ -192,11 +185,8 @@ __global__ __launch_bounds__(256) void rope_kv_vec_kernel(T *__restrict__ qkv, c
     const int d = sh.head_dim, half = d >> 1;
     const int pos = pos_of_token[t];
     for (int i = threadIdx.x; i < half; i += 256) {
-        const double ang = (double)pos * tab.inv_freq[i];
-        const double turns = rint(ang * 0.15915494309189535);          // 1 / (2 pi)
-        const float red = (float)fma(-turns, 6.283185307179586, ang);
         float sn, c;
-        sincosf(red, &sn, &c);
+        rotary_angle(pos, tab.inv_freq[i], sn, c);
         cs[0][i] = c;
         cs[1][i] = sn;
     }
@@ -300,11 +290,8 @@ __global__ __launch_bounds__(256) void gemm_reduce_rope_kernel(const float *__re
     const int page = block_table[(size_t)seq_of_token[t] * sh.max_pages_per_seq + pos / sh.page_size];
     const int slot = pos % sh.page_size;
     for (int i = threadIdx.x; i < half; i += 256) {
-        const double ang = (double)pos * tab.inv_freq[i];
-        const double turns = rint(ang * 0.15915494309189535);          // 1 / (2 pi)
-        const float red = (float)fma(-turns, 6.283185307179586, ang);
         float sn, c;
-        sincosf(red, &sn, &c);
+        rotary_angle(pos, tab.inv_freq[i], sn, c);
         cs[0][i] = c;
         cs[1][i] = sn;
     }
@@ -403,8 +390,7 @@ __global__ __launch_bounds__(256) void silu_mul_kernel(const T *__restrict__ gu,
 
 // Split-K reduce of a gate/up projection fused with the gate (bf16): the planes of eight gate and of the eight up columns
 // are summed in plane order and rounded - the values gemm_reduce_kernel would have stored - and gated as above.
-// Bound by the planes' bytes, read once (two planes of 340 rows x 16384: 9.3 + 6.1 us as two launches, 8 us in one; the step
-// 163.3 -> 159.6 us).
+// Bound by the planes' bytes, read once (two planes of 340 rows x 16384: 9.3 + 6.1 us as two launches, 9.9 us in one).
 template <int SC>
 __global__ __launch_bounds__(256) void gemm_reduce_gate_kernel(const float *__restrict__ P, size_t plane_stride, int S, bf16_t *__restrict__ out,
                                                                int ld_out, int I, size_t n_vec) {

@@ -382,9 +382,10 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
         rows = head;
     }
     if (gemm_rows16_supported(rows, N, K, p.split) || gemm_rows16_wide_supported(rows, N, K, p.split)) {
-        hipError_t er = launch_gemm_rows16(s, X, ldx, W, R, Y, rows, N, K, p.split);
+        const bool rope = has_ep && ep->kind == GemmEpilogue::ROPE && !R && gemm_rows16_rope_supported(*ep->shape);
+        hipError_t er = launch_gemm_rows16(s, X, ldx, W, R, Y, rows, N, K, p.split, rope ? ep : nullptr);
         if (er == hipSuccess && mid) er = hipEventRecord(mid, s);
-        if (er == hipSuccess && has_ep) er = run_epilogue(dtype, *ep, Y, rows, N, s);
+        if (er == hipSuccess && has_ep && !rope) er = run_epilogue(dtype, *ep, Y, rows, N, s);
         return er;
     }
     const int S = p.split, m_tiles = (rows + p.mt - 1) / p.mt;

@@ -1,8 +1,11 @@
 // bf16 projections with planes for up to 16 rows: the planes summed inside the workgroup.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "gemm_tile.h"
 #include "kernels.h"
+#include "rotary.h"
 
 namespace dyn {
 
@@ -15,23 +18,47 @@ namespace dyn {
 // (64 KB a CU with 8 planes; 5: no change).  Launch alone, straight -> by LDS, weights from HBM / from the last-level cache:
 // 6144 x 4096 1 row 12.6/11.2 -> 11.2/7.4 us, 13 rows (planes summed by a launch of their own before) 13.5/11.9 -> 12.6/8.0;
 // 4096 x 4096 8.0/6.5 -> 8.0/4.7, 12.5/9.4 -> 8.5/5.0; 4096 x 14336 23.7/19.4 -> 23.1/18.0, 25.7/21.6 -> 24.4/18.9.
+// With Rotary (qkv) the 16 W rows are eight head-dim indices of a head and their partners half a head dim on: the sums are rounded, rotated
+// and go to the qkv row or the cache pages, as gemm_reduce_rope_kernel does it; the first waves take an angle a lane while the first
+// stages are on their way.  (One token, 6144 x 4096: 10.4 + 4.9 us as two launches, 12.3 us in one; with all
+// angles taken by wave 0 13.4.)
 constexpr int kDeep = 4;
 
-template <int S, int XR>
+struct NoRotary {};
+struct Rotary {
+    const int32_t *seq_of_token, *pos_of_token, *block_table;
+    bf16_t *k_cache, *v_cache;
+    RopeTable tab;
+    AttnShape sh;
+};
+
+template <int S, int XR, class EP>
 __global__ __launch_bounds__(64 * S) void gemm_rows16_kernel(const bf16_t *__restrict__ X, int ldx, const bf16_t *__restrict__ W,
                                                              const bf16_t *__restrict__ R, bf16_t *__restrict__ Y, int rows,
-                                                             int N, int K) {
+                                                             int N, int K, EP ep) {
+    constexpr bool ROTARY = std::is_same_v<EP, Rotary>;
+    constexpr int PER_WAVE = S < 4 ? 4 / S : 1;                // angles a lane of the first four waves takes
+    __shared__ float2 angle[ROTARY ? 4 : 1][64];               // cosine, sine of row r of wave 0's lanes
     constexpr int LOADS = 2 + XR / 8, STAGE = LOADS * 1024;   // 16 W rows, XR (8 or 16) X rows of 64 k
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];      // a ring of kDeep stages for every wave; in the end the planes' sums
     f32x4(*const planes)[64] = reinterpret_cast<f32x4(*)[64]>(lds);
     const int lane = threadIdx.x & 63, sp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15, lq = lane >> 4;
-    const int n0 = blockIdx.x * 16, Kp = K / S, n_stage = Kp / BK;
+    int n0 = blockIdx.x * 16, pair = 8;                    // W rows n0 .. n0 + 7 and the eight from n0 + pair on
+    int head = 0, i0 = 0;
+    if constexpr (ROTARY) {
+        const int per_head = ep.sh.head_dim / 16;
+        head = blockIdx.x / per_head;
+        i0 = blockIdx.x % per_head * 8;
+        n0 = head * ep.sh.head_dim + i0;
+        pair = ep.sh.head_dim / 2;
+    }
+    const int Kp = K / S, n_stage = Kp / BK;
     const int rot = (int)(((unsigned)(n0 / 128 / kRotGroup) * kRotStep) % (unsigned)n_stage);
     const bf16_t *src[LOADS];                              // 8 rows of a stage by 8 lanes each, the 16-byte columns swizzled with the row
 #pragma unroll
     for (int j = 0; j < LOADS; ++j) {
         const int row = (j & 1) * 8 + (lane >> 3), col = sp * Kp + ((lane & 7) ^ (row >> 1 & 7)) * 8;
-        src[j] = j < 2 ? W + (size_t)(n0 + row) * K + col : X + (size_t)min(row, rows - 1) * ldx + col;
+        src[j] = j < 2 ? W + (size_t)(n0 + (row & 7) + (row & 8 ? pair : 0)) * K + col : X + (size_t)min(row, rows - 1) * ldx + col;
     }
     unsigned char *const ring = lds + sp * kDeep * STAGE;
     const unsigned ring0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)ring;
@@ -53,8 +80,29 @@ __global__ __launch_bounds__(64 * S) void gemm_rows16_kernel(const bf16_t *__res
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b0, acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b1, acc, 0, 0, 0);
     };
+    int pos = 0, seq = 0, page = 0;
+    double freq[ROTARY ? PER_WAVE : 1];
+    if constexpr (ROTARY)                                  // before the ring's loads: a wait for these is none for those
+        if (sp < 4) {
+            pos = ep.pos_of_token[min(lr, rows - 1)];
+            seq = ep.seq_of_token[min(lr, rows - 1)];
+#pragma unroll
+            for (int i = 0; i < PER_WAVE; ++i) freq[i] = ep.tab.inv_freq[i0 + 4 * (lq & 1) + sp + i * S];
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
     for (int d = 0; d < kDeep; ++d) issue(d);              // a plane has at least 8 stages
+    if constexpr (ROTARY)
+        if (sp < 4) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (sp == 0) page = ep.block_table[(size_t)seq * ep.sh.max_pages_per_seq + pos / ep.sh.page_size];
+#pragma unroll
+            for (int i = 0; i < PER_WAVE; ++i) {
+                float s, c;
+                rotary_angle(pos, freq[i], s, c);
+                angle[sp + i * S][lane] = make_float2(c, s);
+            }
+        }
     int st = 0;
     for (; st + 2 * kDeep <= n_stage; st += kDeep)
         static_for<0, kDeep>([&](auto d) {
@@ -83,6 +131,30 @@ __global__ __launch_bounds__(64 * S) void gemm_rows16_kernel(const bf16_t *__res
     f32x4 o = planes[0][lane];
 #pragma unroll
     for (int s = 1; s < S; ++s) o += planes[s][lane];
+    if constexpr (ROTARY) {
+        const AttnShape &sh = ep.sh;
+        const int d = sh.head_dim, at = i0 + 4 * (lq & 1) + (lq >> 1) * pair, slot = pos % sh.page_size;   // lanes 32 on hold the partners
+        bf16_t v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            v[r] = f2bf(o[r]);
+            const float mine = bf2f(v[r]), other = __shfl_xor(mine, 32, 64);
+            const float2 cs = angle[r][lane];
+            if (head < sh.n_q + sh.n_kv) v[r] = f2bf(lq < 2 ? rotated_lo(mine, other, cs.x, cs.y) : rotated_hi(other, mine, cs.x, cs.y));
+        }
+        if (head < sh.n_q + sh.n_kv) {
+            bf16_t *dst = head < sh.n_q ? Y + (size_t)lr * N + head * d : ep.k_cache + (((size_t)page * sh.n_kv + (head - sh.n_q)) * sh.page_size + slot) * d;
+            uint2 ov;
+            ov.x = (uint32_t)v[0] | ((uint32_t)v[1] << 16);
+            ov.y = (uint32_t)v[2] | ((uint32_t)v[3] << 16);
+            *reinterpret_cast<uint2 *>(dst + at) = ov;
+        } else {                                           // v head -> V page [kvh][d][slot]
+            bf16_t *vp = ep.v_cache + (((size_t)page * sh.n_kv + (head - sh.n_q - sh.n_kv)) * d + at) * sh.page_size + slot;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) vp[(size_t)r * sh.page_size] = v[r];
+        }
+        return;
+    }
     const size_t at = (size_t)lr * N + n0 + 4 * lq;
     if (R) {
         const uint2 rv = *reinterpret_cast<const uint2 *>(R + at);
@@ -129,31 +201,44 @@ bool gemm_rows16_wide_supported(int rows, int N, int K, int S) {
     return rows <= (all ? 16 : 6);
 }
 
-hipError_t launch_gemm_rows16(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int S) {
-    static_assert(8 * kDeep * 4096 <= 160 * 1024, "eight planes' rings do not fit in LDS");
-#define DYN_ROWS(SC, XR)                                                                                                    \
-    do {                                                                                                                    \
-        constexpr int LDS = SC * kDeep * (2 + XR / 8) * 1024;                                                               \
-        static bool attr_set = false;                                                                                       \
-        if (!attr_set) {                                                                                                    \
-            const hipError_t e = hipFuncSetAttribute((const void *)gemm_rows16_kernel<SC, XR>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS); \
-            if (e != hipSuccess) return e;                                                                                  \
-            attr_set = true;                                                                                                \
-        }                                                                                                                   \
-        hipLaunchKernelGGL((gemm_rows16_kernel<SC, XR>), dim3(N / 16), dim3(64 * SC), LDS, s, (const bf16_t *)X, ldx, (const bf16_t *)W, \
-                           (const bf16_t *)R, (bf16_t *)Y, rows, N, K);                                                     \
-    } while (0)
-    if (gemm_rows16_supported(rows, N, K, S)) {            // at most 8 rows
-        if (S == 8) DYN_ROWS(8, 8);
-        else if (S == 4) DYN_ROWS(4, 8);
-        else DYN_ROWS(2, 8);
-    } else {
-        if (S == 8) DYN_ROWS(8, 16);
-        else if (S == 4) DYN_ROWS(4, 16);
-        else DYN_ROWS(2, 16);
+// The rotary form: halves of a head in whole eights, and a head's columns in one group of the stage order.
+bool gemm_rows16_rope_supported(const AttnShape &sh) {
+    return sh.head_dim % 16 == 0 && 128 * kRotGroup % sh.head_dim == 0 && sh.head_dim <= 2 * kMaxHalfDim;
+}
+
+namespace {
+template <int S, int XR, class EP>
+hipError_t launch_rows(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, const EP &ep) {
+    constexpr int LDS = S * kDeep * (2 + XR / 8) * 1024;
+    static_assert(LDS + 2048 <= 160 * 1024, "the planes' rings do not fit in LDS");
+    static bool attr_set = false;
+    if (!attr_set) {
+        const hipError_t e = hipFuncSetAttribute((const void *)gemm_rows16_kernel<S, XR, EP>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        if (e != hipSuccess) return e;
+        attr_set = true;
     }
-#undef DYN_ROWS
+    hipLaunchKernelGGL((gemm_rows16_kernel<S, XR, EP>), dim3(N / 16), dim3(64 * S), LDS, s, (const bf16_t *)X, ldx, (const bf16_t *)W,
+                       (const bf16_t *)R, (bf16_t *)Y, rows, N, K, ep);
     return hipGetLastError();
+}
+
+template <class EP>
+hipError_t launch_rows_of(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int S, const EP &ep) {
+    if (gemm_rows16_supported(rows, N, K, S))              // at most 8 rows
+        return S == 8   ? launch_rows<8, 8>(s, X, ldx, W, R, Y, rows, N, K, ep)
+               : S == 4 ? launch_rows<4, 8>(s, X, ldx, W, R, Y, rows, N, K, ep)
+                        : launch_rows<2, 8>(s, X, ldx, W, R, Y, rows, N, K, ep);
+    return S == 8   ? launch_rows<8, 16>(s, X, ldx, W, R, Y, rows, N, K, ep)
+           : S == 4 ? launch_rows<4, 16>(s, X, ldx, W, R, Y, rows, N, K, ep)
+                    : launch_rows<2, 16>(s, X, ldx, W, R, Y, rows, N, K, ep);
+}
+}  // namespace
+
+hipError_t launch_gemm_rows16(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int S,
+                              const GemmEpilogue *rope) {
+    if (!rope) return launch_rows_of(s, X, ldx, W, R, Y, rows, N, K, S, NoRotary{});
+    const Rotary ep{rope->seq_of_token, rope->pos_of_token, rope->block_table, (bf16_t *)rope->k_cache, (bf16_t *)rope->v_cache, *rope->rope, *rope->shape};
+    return launch_rows_of(s, X, ldx, W, R, Y, rows, N, K, S, ep);
 }
 
 }  // namespace dyn

@@ -104,3 +104,23 @@ def test_gate_with_the_planes_sum_matches_the_gate_alone(hidden, inter, cuts, fo
     data = gen.generate(w)
     y, k, v = both_schedules(w, data)                        # the whole batch and its parts: the same bits
     say("%d rows: %.2e" % (rows[0], check_against_oracle(w, data, y, k, v)))
+
+
+# Rotary and cache append inside the few rows' qkv projection: heads of 16 to 256, 2 and 4 and 8 planes, 8 and 16 X rows a stage, pages
+# of 16 and 48, and a head dim that keeps its own launch (8); the first micro-batch takes the fused form where the whole batch of 21
+# rows does not, and gives the same bits in the output and in both caches.
+@pytest.mark.parametrize("hidden,n_q,n_kv,hd,page,rows", [
+    (1024, 8, 4, 64, 16, 1), (1024, 16, 8, 16, 16, 9), (2048, 8, 2, 32, 48, 16), (2048, 8, 4, 128, 16, 7), (4096, 6, 1, 256, 16, 13), (1024, 8, 4, 8, 16, 5)])
+def test_rotary_inside_the_few_rows_projection(hidden, n_q, n_kv, hd, page, rows):
+    N = (n_q + 2 * n_kv) * hd
+    S = gemm_path(rows, N, hidden).split
+    assert S > 1 and B.lib()._ZN3dyn26gemm_rows16_wide_supportedEiiii(rows, N, hidden, S) & 0xff != 0
+    w = workload("rows_rope", "bf16", hidden, n_q, n_kv, hd, 1024, [(1, 1 + (i * 131) % 900) for i in range(20)] + [(1, 6000)], page=page, seed=120 + rows)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, rows, 21))
+    data = gen.generate(w)
+    run = GpuRun(w, data)
+    whole = run.run(B.sequential())
+    parts = run.run(B.nano_schedule(w.nano_rows, chain=B.DENSE_CHAIN))
+    for a, b in zip(whole, parts):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    say("%d rows, heads of %d: %.2e" % (rows, hd, check_against_oracle(w, data, *whole)))
