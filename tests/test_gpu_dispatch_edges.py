@@ -124,3 +124,19 @@ def test_rotary_inside_the_few_rows_projection(hidden, n_q, n_kv, hd, page, rows
     for a, b in zip(whole, parts):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
     say("%d rows, heads of %d: %.2e" % (rows, hd, check_against_oracle(w, data, *whole)))
+
+
+# Expert tiles of at most 64, 128, 192 and 256 rows where an XCD's tiles run at once (4, 16 and 24 n tiles of 256), and of 256 with an expert's
+# rows in unequal tiles where they do not (56 n tiles; the second micro-batch has other tiles): no row twice, none left out.
+@pytest.mark.parametrize("inter,tokens,pull", [(512, 1000, 1.0), (2048, 600, 0.0), (2048, 1050, 1.5), (3072, 1200, 1.0), (7168, 450, 0.0), (7168, 900, 2.0)])
+def test_expert_tiles_in_one_round_and_in_several(inter, tokens, pull):
+    w = workload("rounds", "bf16", 256, 2, 1, 128, inter, [(1, 1 + i % 5) for i in range(tokens)], experts=4, top_k=2, seed=140 + tokens)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, tokens // 9, tokens))
+    data = gen.generate(w)
+    router = data["weights"][0]["w_router"]
+    router[2] = -router[0]                                   # tokens pulled towards expert 0 never choose expert 2
+    x = data["x"].float()
+    x += pull * 256 ** 0.5 * router[0] / router[0].norm() * torch.rand(tokens, 1, generator=torch.Generator().manual_seed(2)) ** 0.5
+    data["x"] = x.to(torch.bfloat16)
+    y, k, v = both_schedules(w, data)
+    say("%d tokens: %.2e" % (tokens, check_against_oracle(w, data, y, k, v)))
