@@ -93,6 +93,8 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
 hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const void *R, void *Y, int max_rows, int N, int K, const GemmGroups &gr,
                            hipStream_t s);
 bool gemm_f32_gated_supported(int N2, int K);
+bool gemm_f32_rope_supported(const void *X, int ldx, const void *W, int rows, int N, int K, const AttnShape &sh);   // rotary + cache append in the same launch
+hipError_t launch_gemm_f32_rope(const void *X, int ldx, const void *W, void *Y, int rows, int N, int K, const GemmEpilogue &rope, hipStream_t s);
 hipError_t launch_gemm_f32_gated(const void *X, int ldx, const void *W, void *Y, int ldy, int rows, int N2, int K, hipStream_t s);
 // A few rows (at most 16), planes summed in the workgroup (kernels_gemm_rows.hip; launch_gemm calls it).
 bool gemm_rows16_supported(int rows, int N, int K, int S);            // with 8 X rows a stage

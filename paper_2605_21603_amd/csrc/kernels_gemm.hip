@@ -365,9 +365,10 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
     const GemmGroups none{};
     const bool has_ep = ep && ep->kind != GemmEpilogue::NONE;
     if (dtype == 0) {
-        hipError_t e0 = launch_gemm_f32(X, ldx, W, R, Y, rows, N, K, none, s);
+        const bool rope = has_ep && ep->kind == GemmEpilogue::ROPE && !R && gemm_f32_rope_supported(X, ldx, W, rows, N, K, *ep->shape);
+        hipError_t e0 = rope ? launch_gemm_f32_rope(X, ldx, W, Y, rows, N, K, *ep, s) : launch_gemm_f32(X, ldx, W, R, Y, rows, N, K, none, s);
         if (e0 == hipSuccess && mid) e0 = hipEventRecord(mid, s);
-        if (e0 == hipSuccess && has_ep) e0 = run_epilogue(dtype, *ep, Y, rows, N, s);
+        if (e0 == hipSuccess && has_ep && !rope) e0 = run_epilogue(dtype, *ep, Y, rows, N, s);
         return e0;
     }
     const GemmPath p = gemm_path(dtype, rows, N, K);

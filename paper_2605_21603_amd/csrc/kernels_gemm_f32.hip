@@ -9,8 +9,10 @@
 // chain and with the group of 64 columns, and the first chain added turns with that group too: rows lie a power of two
 // apart, and what runs at the same time would otherwise read one channel of the second-level cache.
 #include <algorithm>
+#include <type_traits>
 
 #include "gemm_tile.h"
+#include "rotary.h"
 
 namespace dyn {
 
@@ -35,6 +37,44 @@ __device__ __forceinline__ void f32_store(f32x4 o, size_t at, int n, int N, cons
     }
 }
 
+// What a tile of 32 W rows does when its first 16 (a = 0) and its other 16 (a = 1) are partners: nothing, gate columns and the up
+// columns beside them, or head-dim indices and the ones half a head dim on, rotated and appended to the cache as
+// rope_kv_vec_kernel does it.
+struct F32Plain { static constexpr bool PAIRS = false, ROTARY = false; };
+struct F32Gated { static constexpr bool PAIRS = true, ROTARY = false; int ldy; };
+struct F32Rotary {
+    static constexpr bool PAIRS = true, ROTARY = true;
+    const int32_t *seq_of_token, *pos_of_token, *block_table;
+    float *k_cache, *v_cache;
+    RopeTable tab;
+    AttnShape sh;
+};
+// First W row of a tile, and how far on its partners lie.
+template <class EP>
+__device__ __forceinline__ int f32_column(const EP &ep, int nt, int N, int &partner) {
+    if constexpr (EP::ROTARY) {
+        const int d = ep.sh.head_dim, per_head = d / 32;
+        partner = d / 2;
+        return (int)blockIdx.x / per_head * d + (int)blockIdx.x % per_head * 16;
+    }
+    partner = N / 2;
+    return blockIdx.x * (EP::PAIRS ? nt / 2 : nt);
+}
+// Rotary: a wave takes one angle a lane, angle r of the 16 rows b = wave % NB, before its operands are multiplied, and looks the page up.
+template <int NB>
+struct F32Angles { float2 at[NB][4][64]; };
+template <int NB>
+__device__ __forceinline__ void f32_angles(F32Angles<NB> &angles, const F32Rotary &ep, int m0, int n0, int M, int &pos, int &page) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), b = wave % NB, r = wave / NB;
+    const int m = min(m0 + b * 16 + (lane & 15), M - 1);
+    pos = ep.pos_of_token[m];
+    page = ep.block_table[(size_t)ep.seq_of_token[m] * ep.sh.max_pages_per_seq + pos / ep.sh.page_size];
+    if (r >= 4) return;
+    float s, c;
+    rotary_angle(pos, ep.tab.inv_freq[n0 % ep.sh.head_dim + 4 * (lane >> 4) + r], s, c);
+    angles.at[b][r][lane] = make_float2(c, s);
+}
+
 // silu(g) * u
 __device__ __forceinline__ f32x4 f32_gate(f32x4 g, f32x4 u) {
     f32x4 o;
@@ -43,28 +83,53 @@ __device__ __forceinline__ f32x4 f32_gate(f32x4 g, f32x4 u) {
     return o;
 }
 
-// The eight waves' sums of a tile meet in LDS, SUB sub-tiles of 16 x 16 at a time, a wave to a sub-tile (GATED: to a pair, gate columns in
-// a = 0 and the up columns beside them in a = 1).  D: lane l holds W rows 4 (l / 16) + r of X row l % 16.  list: output rows (null: m itself).
-template <int NA, int NB, bool TURN, bool GATED = false>
+// The eight waves' sums of a tile meet in LDS, SUB sub-tiles of 16 x 16 at a time, a wave to a sub-tile or to a pair of partners.
+// D: lane l holds W rows 4 (l / 16) + r of X row l % 16.  list: output rows (null: m itself).
+template <int NA, int NB, bool TURN, class EP>
 __device__ __forceinline__ void f32_finish(f32x4 (*part)[NA * NB < 4 ? NA * NB : 4][64], const f32x4 (&acc)[NA][NB], int m0, int n0, int M, int N,
-                                           const int32_t *list, const float *__restrict__ R, float *__restrict__ Y, int ldy = 0) {
+                                           const int32_t *list, const float *__restrict__ R, float *__restrict__ Y, const EP &ep,
+                                           const F32Angles<NB> *angles, int pos, int page) {
     constexpr int SUB = NA * NB < 4 ? NA * NB : 4;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15, lq = lane >> 4;
-    if constexpr (GATED) {
+    if constexpr (EP::PAIRS) {
         static_assert(NA == 2 && SUB == NA * NB, "one pair of sub-tiles per 16 rows of X");
 #pragma unroll
         for (int i = 0; i < SUB; ++i) part[wave][i][lane] = acc[i / NB][i % NB];
         __syncthreads();
-        if (wave < NB) {
-            f32x4 g = part[f32_chain(0, n0)][wave][lane], u = part[f32_chain(0, n0)][NB + wave][lane];
+        if (wave >= NB) return;
+        f32x4 g = part[TURN ? f32_chain(0, n0) : 0][wave][lane], u = part[TURN ? f32_chain(0, n0) : 0][NB + wave][lane];
 #pragma unroll
-            for (int w = 1; w < kF32Chains; ++w) {
-                const f32x4 p = part[f32_chain(w, n0)][wave][lane], q = part[f32_chain(w, n0)][NB + wave][lane];
-                g[0] += p[0]; g[1] += p[1]; g[2] += p[2]; g[3] += p[3];
-                u[0] += q[0]; u[1] += q[1]; u[2] += q[2]; u[3] += q[3];
+        for (int w = 1; w < kF32Chains; ++w) {
+            const f32x4 p = part[TURN ? f32_chain(w, n0) : w][wave][lane], q = part[TURN ? f32_chain(w, n0) : w][NB + wave][lane];
+            g[0] += p[0]; g[1] += p[1]; g[2] += p[2]; g[3] += p[3];
+            u[0] += q[0]; u[1] += q[1]; u[2] += q[2]; u[3] += q[3];
+        }
+        const int m = m0 + wave * 16 + lr;
+        if (m >= M) return;
+        if constexpr (EP::ROTARY) {
+            const AttnShape &sh = ep.sh;
+            const int d = sh.head_dim, head = n0 / d, i = n0 % d + 4 * lq, slot = pos % sh.page_size;
+            if (head >= sh.n_q + sh.n_kv) {                // v head -> V page [kvh][d][slot]
+                float *vp = ep.v_cache + (((size_t)page * sh.n_kv + (head - sh.n_q - sh.n_kv)) * d + i) * sh.page_size + slot;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    vp[(size_t)r * sh.page_size] = g[r];
+                    vp[(size_t)(r + d / 2) * sh.page_size] = u[r];
+                }
+                return;
             }
-            const int m = m0 + wave * 16 + lr;
-            if (m < M) *reinterpret_cast<f32x4_u *>(Y + (size_t)m * ldy + n0 + 4 * lq) = f32_gate(g, u);
+            f32x4 lo, hi;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float2 cs = angles->at[wave][r][lane];
+                lo[r] = rotated_lo(g[r], u[r], cs.x, cs.y);
+                hi[r] = rotated_hi(g[r], u[r], cs.x, cs.y);
+            }
+            float *dst = head < sh.n_q ? Y + (size_t)m * N + head * d : ep.k_cache + (((size_t)page * sh.n_kv + (head - sh.n_q)) * sh.page_size + slot) * d;
+            *reinterpret_cast<f32x4_u *>(dst + i) = lo;
+            *reinterpret_cast<f32x4_u *>(dst + i + d / 2) = hi;
+        } else {
+            *reinterpret_cast<f32x4_u *>(Y + (size_t)m * ep.ldy + n0 + 4 * lq) = f32_gate(g, u);
         }
         return;
     }
@@ -90,12 +155,13 @@ __device__ __forceinline__ void f32_finish(f32x4 (*part)[NA * NB < 4 ? NA * NB :
 // rows x 64 bytes per instruction) and element e of the four is the operand of product e, whose k
 // index l / 16 then stands for k 4 (l / 16) + e in both matrices.  Launch alone, against 64 x 64 tiles of fp32 FMAs staged
 // through LDS 16 k at a time by one chain per output: 4 rows x 768 x 256 27.7 -> 3.2 us, 4 x 256 x 1024 96 -> 5.1 us.
-template <int MT, int NT>
+template <int MT, int NT, class EP>
 __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_kernel(const float *__restrict__ X, int ldx, const float *__restrict__ W,
                                                                   const float *__restrict__ R, float *__restrict__ Y, int M, int N,
-                                                                  int K, GemmGroups gr) {
+                                                                  int K, GemmGroups gr, EP ep) {
     constexpr int NA = NT / 16, NB = MT / 16, UNR = (NA + NB) <= 4 ? 4 : 2;  // units of 16 k loaded ahead of their products
     __shared__ f32x4 part[kF32Chains][NA * NB < 4 ? NA * NB : 4][64];
+    __shared__ F32Angles<EP::ROTARY ? NB : 1> angles;
     const int32_t *list = nullptr;
     if (gr.n_groups) {                                 // blockIdx.z = expert: its rows come from a list
         M = gr.counts[blockIdx.z];
@@ -105,10 +171,11 @@ __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_kernel(const float *
     const int m0 = blockIdx.y * MT;
     if (m0 >= M) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15, lq = lane >> 4;
-    const int n0 = blockIdx.x * NT;
+    int partner, pos = 0, page = 0;
+    const int n0 = f32_column(ep, NT, N, partner);
     const float *wp[NA], *xp[NB];                      // rows past the end read the last one; what they give is not stored
 #pragma unroll
-    for (int a = 0; a < NA; ++a) wp[a] = W + (size_t)min(n0 + a * 16 + lr, N - 1) * K + 4 * lq;
+    for (int a = 0; a < NA; ++a) wp[a] = W + (size_t)(EP::PAIRS ? n0 + a * partner + lr : min(n0 + a * 16 + lr, N - 1)) * K + 4 * lq;
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         const int m = min(m0 + b * 16 + lr, M - 1);
@@ -129,6 +196,7 @@ __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_kernel(const float *
 #pragma unroll
                 for (int b = 0; b < NB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[a][e], xv[b][e], acc[a][b], 0, 0, 0);
     };
+    if constexpr (EP::ROTARY) f32_angles(angles, ep, m0, n0, M, pos, page);
     int u = u0;
     const int u1f = min(u1, full);
     for (; u + UNR <= u1f; u += UNR) {
@@ -152,7 +220,7 @@ __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_kernel(const float *
         for (int b = 0; b < NB; ++b) xv[b] = in ? (f32x4) * reinterpret_cast<const f32x4_u *>(xp[b] + (size_t)u * 16) : f32x4{0.f, 0.f, 0.f, 0.f};
         multiply(wv, xv);
     }
-    f32_finish<NA, NB, false>(part, acc, m0, n0, M, N, list, R, Y);
+    f32_finish<NA, NB, false>(part, acc, m0, n0, M, N, list, R, Y, ep, EP::ROTARY ? (const F32Angles<NB> *)&angles : nullptr, pos, page);
 }
 
 // Four adjacent lanes trade with four registers: register j of lane x of every quad becomes register x of lane j.
@@ -178,18 +246,19 @@ __device__ __forceinline__ void quad_transpose(f32x4 (&v)[4]) {
 // 15.9 -> 11.0 us, 100 rows 30.7 -> 19.2); with 32 x 32 that costs the second workgroup of a CU (225 rows x 1024 x 4096 31.6 -> 28.8
 // us, 30.3 with two).  Trading takes 64 vector instructions an operand: what is one short block long gains nothing
 // (4 rows x 1024 x 1024 4.6 -> 5.1 us, x 8192 x 1024 8.0 -> 8.9, x 1024 x 4096 12.0 -> 10.8).
-// GATED: the NT rows are NT / 2 gate columns from n0 on and the N / 2 rows later up columns beside them; Y (pitch ldy) = silu(gate) * up.
-template <int MT, int NT, bool GATED = false>
+template <int MT, int NT, class EP>
 __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_quads_kernel(const float *__restrict__ X, int ldx, const float *__restrict__ W,
-                                                                        const float *__restrict__ R, float *__restrict__ Y, int M, int N, int K, int ldy) {
+                                                                        const float *__restrict__ R, float *__restrict__ Y, int M, int N, int K, EP ep) {
     constexpr int NA = NT / 16, NB = MT / 16, NBUF = NA + NB <= 3 ? 2 : 1;
     __shared__ f32x4 part[kF32Chains][NA * NB < 4 ? NA * NB : 4][64];
-    const int m0 = blockIdx.y * MT, n0 = blockIdx.x * (GATED ? NT / 2 : NT);
+    __shared__ F32Angles<EP::ROTARY ? NB : 1> angles;
+    int partner, pos = 0, page = 0;
+    const int m0 = blockIdx.y * MT, n0 = f32_column(ep, NT, N, partner);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), row4 = (lane >> 2 & 3) * 4, col = (lane >> 4) * 16 + (lane & 3) * 4;
     const float *const Wt = W + (size_t)n0 * K, *const Xt = X + (size_t)m0 * ldx;
     size_t wo[NA], xo[NB][4];                              // rows past the end read the last ones; what they give is not stored
 #pragma unroll
-    for (int a = 0; a < NA; ++a) wo[a] = (size_t)(GATED ? a * (N / 2) + row4 : min(a * 16 + row4, N - 4 - n0)) * K + col;
+    for (int a = 0; a < NA; ++a) wo[a] = (size_t)(EP::PAIRS ? a * partner + row4 : min(a * 16 + row4, N - 4 - n0)) * K + col;
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -231,12 +300,14 @@ __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_quads_kernel(const f
     const std::integral_constant<int, 0> b0;
     const std::integral_constant<int, NBUF - 1> b1;
     if constexpr (NBUF == 1) {
+        if constexpr (EP::ROTARY) f32_angles(angles, ep, m0, n0, M, pos, page);
         for (int i = 0; i < blocks; ++i) {
             load(b0, i);
             multiply(b0);
         }
     } else {                                               // a pass always loads: behind a load that may not have been issued the compiler waits for all
         load(b0, 0);
+        if constexpr (EP::ROTARY) f32_angles(angles, ep, m0, n0, M, pos, page);
         int i = 0;
         for (; i + 2 < blocks; i += 2) {
             load(b1, i + 1);
@@ -257,7 +328,7 @@ __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_quads_kernel(const f
             multiply(b0);
         }
     }
-    f32_finish<NA, NB, true, GATED>(part, acc, m0, n0, M, N, nullptr, R, Y, ldy);
+    f32_finish<NA, NB, true>(part, acc, m0, n0, M, N, nullptr, R, Y, ep, EP::ROTARY ? (const F32Angles<NB> *)&angles : nullptr, pos, page);
 }
 
 // Whole blocks, many tiles: 64 x 64, four waves of 32 x 32 that share stages of one block (256-byte rows, direct loads of
@@ -375,42 +446,68 @@ hipError_t launch_f32_tiles(const void *X, int ldx, const void *W, const void *R
     return hipGetLastError();
 }
 
-template <int MT, int NT, bool GATED>
-hipError_t launch_f32_quads(const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int ldy, hipStream_t s) {
-    hipLaunchKernelGGL((gemm_f32_quads_kernel<MT, NT, GATED>), dim3((N + NT - 1) / NT, (rows + MT - 1) / MT), dim3(kF32Chains * 64), 0, s,
-                       (const float *)X, ldx, (const float *)W, (const float *)R, (float *)Y, rows, N, K, ldy);
+template <int MT, int NT, class EP>
+hipError_t launch_f32_quads(const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, const EP &ep, hipStream_t s) {
+    hipLaunchKernelGGL((gemm_f32_quads_kernel<MT, NT, EP>), dim3((N + NT - 1) / NT, (rows + MT - 1) / MT), dim3(kF32Chains * 64), 0, s,
+                       (const float *)X, ldx, (const float *)W, (const float *)R, (float *)Y, rows, N, K, ep);
     return hipGetLastError();
 }
 
-template <bool GATED>
-hipError_t launch_f32_whole(const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int ldy, hipStream_t s) {
-    auto tiles = [&](int t) { return (long)((rows + t - 1) / t) * ((N + t - 1) / t); };
-    const bool aligned = ldx % 4 == 0 && (((uintptr_t)X | (uintptr_t)W) & 15) == 0;      // the direct loads' 16 bytes
-    if (rows <= 16 || tiles(16) <= 512) return launch_f32_quads<16, GATED ? 32 : 16, GATED>(X, ldx, W, R, Y, rows, N, K, ldy, s);
-    if (aligned && tiles(64) >= 192) return launch_f32_tiles<GATED>(X, ldx, W, R, Y, rows, N, K, ldy, s);
-    return launch_f32_quads<32, 32, GATED>(X, ldx, W, R, Y, rows, N, K, ldy, s);
+long f32_tiles(int rows, int N, int t) { return (long)((rows + t - 1) / t) * ((N + t - 1) / t); }
+bool f32_whole(int N, int K) { return K % (kF32Block * kF32Chains) == 0 && N % 4 == 0; }
+bool f32_few(int rows, int N, bool whole, int groups = 1) { return rows <= 16 || f32_tiles(rows, N, 16) * groups <= (whole ? 512 : 256); }
+bool f32_direct(const void *X, int ldx, const void *W, int rows, int N) {      // 64 x 64 tiles; the direct loads take 16 bytes
+    return ldx % 4 == 0 && (((uintptr_t)X | (uintptr_t)W) & 15) == 0 && f32_tiles(rows, N, 64) >= 192;
+}
+
+int f32_pitch(const F32Plain &, int N) { return N; }
+int f32_pitch(const F32Gated &ep, int) { return ep.ldy; }
+
+template <class EP>
+hipError_t launch_f32_whole(const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, const EP &ep, hipStream_t s) {
+    if (f32_few(rows, N, true)) return launch_f32_quads<16, EP::PAIRS ? 32 : 16>(X, ldx, W, R, Y, rows, N, K, ep, s);
+    if constexpr (!EP::ROTARY)
+        if (f32_direct(X, ldx, W, rows, N)) return launch_f32_tiles<EP::PAIRS>(X, ldx, W, R, Y, rows, N, K, f32_pitch(ep, N), s);
+    return launch_f32_quads<32, 32>(X, ldx, W, R, Y, rows, N, K, ep, s);
+}
+
+template <int MT, int NT, class EP>
+hipError_t launch_f32_any(const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, const GemmGroups &gr, const EP &ep,
+                          hipStream_t s) {
+    hipLaunchKernelGGL((gemm_f32_kernel<MT, NT, EP>), dim3((N + NT - 1) / NT, (rows + MT - 1) / MT, std::max(gr.n_groups, 1)), dim3(kF32Chains * 64), 0, s,
+                       (const float *)X, ldx, (const float *)W, (const float *)R, (float *)Y, rows, N, K, gr, ep);
+    return hipGetLastError();
 }
 }  // namespace
 
+// The rotary form: tiles of 16 + 16 columns for few rows or few tiles at any depth, and 32 x 32 of whole blocks, where a
+// head's halves have to lie in one group of 64 columns.  225 rows x 1536 x 1024 17.8 + 4.9 us as two launches, 19.3 in one; 4 rows x 768 x
+// 256 3.3 + 2.7 -> 4.4 (steps 131.1 -> 128.5, 40.5 -> 39.2 us).
 hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const void *R, void *Y, int max_rows, int N, int K,
                            const GemmGroups &gr, hipStream_t s) {
-    if (!gr.n_groups && K % (kF32Block * kF32Chains) == 0 && N % 4 == 0) return launch_f32_whole<false>(X, ldx, W, R, Y, max_rows, N, K, N, s);
+    if (!gr.n_groups && f32_whole(N, K)) return launch_f32_whole(X, ldx, W, R, Y, max_rows, N, K, F32Plain{}, s);
     const int groups = std::max(gr.n_groups, 1);
-    auto tiles = [&](int t) { return (long)((max_rows + t - 1) / t) * ((N + t - 1) / t) * groups; };
-#define DYN_F32(T)                                                                                                                                \
-    hipLaunchKernelGGL((gemm_f32_kernel<T, T>), dim3((N + T - 1) / T, (max_rows + T - 1) / T, groups), dim3(kF32Chains * 64), 0, s, (const float *)X, \
-                       ldx, (const float *)W, (const float *)R, (float *)Y, max_rows, N, K, gr)
-    if (max_rows <= 16 || tiles(16) <= 256) DYN_F32(16);
-    else if (tiles(64) >= 256) DYN_F32(64);
-    else DYN_F32(32);
-#undef DYN_F32
-    return hipGetLastError();
+    if (f32_few(max_rows, N, false, groups)) return launch_f32_any<16, 16>(X, ldx, W, R, Y, max_rows, N, K, gr, F32Plain{}, s);
+    if (f32_tiles(max_rows, N, 64) * groups >= 256) return launch_f32_any<64, 64>(X, ldx, W, R, Y, max_rows, N, K, gr, F32Plain{}, s);
+    return launch_f32_any<32, 32>(X, ldx, W, R, Y, max_rows, N, K, gr, F32Plain{}, s);
 }
 
-bool gemm_f32_gated_supported(int N2, int K) { return K % (kF32Block * kF32Chains) == 0 && N2 % 64 == 0; }
+bool gemm_f32_gated_supported(int N2, int K) { return f32_whole(N2, K) && N2 % 64 == 0; }
 
 hipError_t launch_gemm_f32_gated(const void *X, int ldx, const void *W, void *Y, int ldy, int rows, int N2, int K, hipStream_t s) {
-    return launch_f32_whole<true>(X, ldx, W, nullptr, Y, rows, N2, K, ldy, s);
+    return launch_f32_whole(X, ldx, W, nullptr, Y, rows, N2, K, F32Gated{ldy}, s);
+}
+
+bool gemm_f32_rope_supported(const void *X, int ldx, const void *W, int rows, int N, int K, const AttnShape &sh) {
+    if (sh.head_dim % 32 || sh.head_dim > 2 * kMaxHalfDim) return false;
+    if (!f32_whole(N, K)) return f32_few(rows, N, false);
+    return 64 % sh.head_dim == 0 && (f32_few(rows, N, true) || !f32_direct(X, ldx, W, rows, N));
+}
+
+hipError_t launch_gemm_f32_rope(const void *X, int ldx, const void *W, void *Y, int rows, int N, int K, const GemmEpilogue &rope, hipStream_t s) {
+    const F32Rotary ep{rope.seq_of_token, rope.pos_of_token, rope.block_table, (float *)rope.k_cache, (float *)rope.v_cache, *rope.rope, *rope.shape};
+    if (f32_whole(N, K)) return launch_f32_whole(X, ldx, W, nullptr, Y, rows, N, K, ep, s);
+    return launch_f32_any<16, 32>(X, ldx, W, nullptr, Y, rows, N, K, GemmGroups{}, ep, s);
 }
 
 }  // namespace dyn

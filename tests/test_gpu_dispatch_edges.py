@@ -140,3 +140,24 @@ def test_expert_tiles_in_one_round_and_in_several(inter, tokens, pull):
     data["x"] = x.to(torch.bfloat16)
     y, k, v = both_schedules(w, data)
     say("%d tokens: %.2e" % (tokens, check_against_oracle(w, data, y, k, v)))
+
+
+# The same inside the fp32 projection: tiles of any depth (256, 68) and of whole blocks (512, 1024), 16 and 32 rows high, heads of 32, 64 and
+# 256, pages of 16 and 48.  Where the batch or one of its parts keeps the launch of its own - more rows (the first two, whose whole batch
+# takes 64 x 64 tiles and tiles of any depth), heads of 128 and 16 - it is the same bits.
+@pytest.mark.parametrize("hidden,n_q,n_kv,hd,page,rows,cut", [
+    (512, 32, 8, 64, 16, 260, 15), (256, 64, 32, 64, 16, 40, 16), (256, 4, 4, 64, 48, 9, 4), (68, 6, 1, 256, 16, 21, 1), (1024, 16, 4, 64, 16, 230, 47),
+    (1024, 18, 6, 32, 48, 150, 100), (512, 4, 2, 128, 16, 21, 9), (512, 6, 1, 16, 16, 21, 9)])
+def test_rotary_inside_the_fp32_projection(hidden, n_q, n_kv, hd, page, rows, cut):
+    seqs = [(1, 1 + (i * 31) % 200) for i in range(cut)] + [(rows - cut, rows + 90)]
+    w = workload("f32_rope", "f32", hidden, n_q, n_kv, hd, 256, seqs, page=page, seed=160 + rows)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, cut, rows))
+    data = gen.generate(w)
+    run = GpuRun(w, data)
+    whole = run.run(B.sequential())
+    parts = run.run(B.nano_schedule(w.nano_rows, chain=B.DENSE_CHAIN))
+    for a, b in zip(whole, parts):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    err = check_against_oracle(w, data, *whole)
+    say("%d rows, heads of %d: %.2e" % (rows, hd, err))
+    assert err < 2e-6                                        # as the fp32 projections' own tests
