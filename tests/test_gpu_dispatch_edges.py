@@ -161,3 +161,22 @@ def test_rotary_inside_the_fp32_projection(hidden, n_q, n_kv, hd, page, rows, cu
     err = check_against_oracle(w, data, *whole)
     say("%d rows, heads of %d: %.2e" % (rows, hd, err))
     assert err < 2e-6                                        # as the fp32 projections' own tests
+
+
+# From 512 rows on the v heads of 16 rows are appended together: prompts behind 0, 16, 7 and 33 positions (whole runs and runs across
+# pages), single tokens between them, a last group of 3 rows, pages of 16, 32 and 8; both caches against the bits of parts
+# below 512 rows.
+@pytest.mark.parametrize("dtype,hidden,n_q,n_kv,hd,page", [("bf16", 1024, 8, 2, 128, 16), ("bf16", 512, 4, 4, 64, 32), ("f32", 128, 4, 2, 64, 16), ("bf16", 256, 2, 1, 32, 8)])
+def test_v_of_16_rows_is_appended_whole(dtype, hidden, n_q, n_kv, hd, page):
+    seqs = [(300, 300), (1, 77), (1, 16), (100, 116), (1, 1), (48, 55), (64, 97), (16, 16), (20, 53)]
+    T = sum(q for q, _ in seqs)
+    assert T > 512 and T % 16
+    w = workload("v16", dtype, hidden, n_q, n_kv, hd, 512, seqs, page=page, seed=180)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, 301, T))
+    data = gen.generate(w)
+    run = GpuRun(w, data)
+    whole = run.run(B.sequential())
+    parts = run.run(B.nano_schedule(w.nano_rows, chain=B.DENSE_CHAIN))
+    for a, b in zip(whole, parts):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    say("%d rows: %.2e" % (T, check_against_oracle(w, data, *whole)))
