@@ -114,35 +114,84 @@ hipError_t launch_route(int dtype, const void *h, int ldh, const float *w_router
     return hipGetLastError();
 }
 
-// One wave per expert scans the dispatch's pairs in ascending order and appends its own, 512 pairs loaded at a
-// time (one after the other, 2240 pairs were 35 load latencies: 13 us).
-__global__ void expert_lists_kernel(const int32_t *__restrict__ sel, int n_pairs, int pair_base, int cap,
-                                    int32_t *__restrict__ counts, int32_t *__restrict__ lists) {
+// Up to 512 pairs: one wave per expert loads them all at a time and appends its own in ascending order.
+constexpr int kScanAhead = 8, kScanPairs = 64 * kScanAhead;
+__global__ void expert_lists_scan_kernel(const int32_t *__restrict__ sel, int n_pairs, int pair_base, int cap, int32_t *__restrict__ counts,
+                                         int32_t *__restrict__ lists) {
     const int e = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    constexpr int AHEAD = 8;
-    int count = 0;
-    for (int base = 0; base < n_pairs; base += 64 * AHEAD) {
-        int chosen[AHEAD];
+    int count = 0, chosen[kScanAhead];
 #pragma unroll
-        for (int i = 0; i < AHEAD; ++i) {
-            const int p = base + i * 64 + lane;
-            chosen[i] = p < n_pairs ? sel[pair_base + p] : -1;
-        }
+    for (int i = 0; i < kScanAhead; ++i) chosen[i] = i * 64 + lane < n_pairs ? sel[pair_base + i * 64 + lane] : -1;
 #pragma unroll
-        for (int i = 0; i < AHEAD; ++i) {
-            const bool mine = chosen[i] == e;
-            const unsigned long long mask = __ballot(mine);
-            if (mine) lists[(size_t)e * cap + count + __popcll(mask & ((1ull << lane) - 1ull))] = pair_base + base + i * 64 + lane;
-            count += __popcll(mask);
-        }
+    for (int i = 0; i < kScanAhead; ++i) {
+        const bool mine = chosen[i] == e;
+        const unsigned long long mask = __ballot(mine);
+        if (mine) lists[(size_t)e * cap + count + __popcll(mask & ((1ull << lane) - 1ull))] = pair_base + i * 64 + lane;
+        count += __popcll(mask);
     }
     if (lane == 0) counts[e] = count;
+}
+
+// More pairs: sixteen waves take consecutive parts of the dispatch's pairs; each counts its part's pairs per expert, the counts of the waves before it
+// are its offsets, and every expert's pairs land in ascending order.  Bound by the latency of one load, two barriers and a ballot
+// per expert and 64 pairs, twice: 2240 pairs of 8 experts 13.2 us by a wave per expert that scans all of them, 7.6 this way; 512 pairs
+// 5.1 and 7.0.
+constexpr int kListWaves = 16, kListAhead = 8;             // 64-pair steps of a wave kept in registers between count and store
+__global__ __launch_bounds__(kListWaves * 64) void expert_lists_kernel(const int32_t *__restrict__ sel, int n_pairs, int pair_base, int E, int cap,
+                                                                       int32_t *__restrict__ counts, int32_t *__restrict__ lists) {
+    __shared__ int count[kListWaves][kMaxExperts], before[kMaxExperts];     // this pass's, by wave; those of the passes before
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (threadIdx.x < kMaxExperts) before[threadIdx.x] = 0;
+    constexpr int PASS = kListWaves * 64 * kListAhead;
+    for (int base = 0; base < n_pairs; base += PASS) {
+        const int steps = (min(PASS, n_pairs - base) + kListWaves * 64 - 1) / (kListWaves * 64), first = base + wave * steps * 64;
+        int chosen[kListAhead];
+#pragma unroll
+        for (int i = 0; i < kListAhead; ++i) {
+            const int p = first + i * 64 + lane;
+            chosen[i] = i < steps && p < n_pairs ? sel[pair_base + p] : -1;
+        }
+        for (int e = 0; e < E; ++e) {
+            int c = 0;
+#pragma unroll
+            for (int i = 0; i < kListAhead; ++i)
+                if (i < steps) c += __popcll(__ballot(chosen[i] == e));
+            if (lane == 0) count[wave][e] = c;
+        }
+        __syncthreads();
+        int at_lane = 0, total = 0;                        // lane e: where this wave's pairs of expert e start; all of this pass's
+        if (lane < E) {
+            at_lane = before[lane];
+#pragma unroll
+            for (int w = 0; w < kListWaves; ++w) {
+                const int c = count[w][lane];
+                at_lane += w < wave ? c : 0;
+                total += c;
+            }
+        }
+        for (int e = 0; e < E; ++e) {
+            int at = __builtin_amdgcn_readlane(at_lane, e);
+#pragma unroll
+            for (int i = 0; i < kListAhead; ++i) {
+                if (i >= steps) break;
+                const bool mine = chosen[i] == e;
+                const unsigned long long mask = __ballot(mine);
+                if (mine) lists[(size_t)e * cap + at + __popcll(mask & ((1ull << lane) - 1ull))] = pair_base + first + i * 64 + lane;
+                at += __popcll(mask);
+            }
+        }
+        __syncthreads();                                   // every wave has read the counts and what came before
+        if (wave == 0 && lane < E) before[lane] += total;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < E) counts[threadIdx.x] = before[threadIdx.x];
 }
 
 hipError_t launch_expert_lists(const int32_t *sel, int n_pairs, int pair_base, int E, int cap, int32_t *counts,
                                int32_t *lists, hipStream_t s) {
     if (n_pairs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(expert_lists_kernel, dim3(1), dim3(64 * E), 0, s, sel, n_pairs, pair_base, cap, counts, lists);
+    if (n_pairs <= kScanPairs) hipLaunchKernelGGL(expert_lists_scan_kernel, dim3(1), dim3(64 * E), 0, s, sel, n_pairs, pair_base, cap, counts, lists);
+    else hipLaunchKernelGGL(expert_lists_kernel, dim3(1), dim3(kListWaves * 64), 0, s, sel, n_pairs, pair_base, E, cap, counts, lists);
     return hipGetLastError();
 }
 

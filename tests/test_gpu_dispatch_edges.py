@@ -180,3 +180,13 @@ def test_v_of_16_rows_is_appended_whole(dtype, hidden, n_q, n_kv, hd, page):
     for a, b in zip(whole, parts):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
     say("%d rows: %.2e" % (T, check_against_oracle(w, data, *whole)))
+
+
+# Expert lists by sixteen waves: 1 pair, a wave's 64 and one more, whole and ragged steps of 1024, and more than the 8192 pairs of one pass.
+@pytest.mark.parametrize("tokens,experts,top_k", [(1, 3, 1), (64, 16, 1), (65, 5, 1), (512, 8, 2), (513, 16, 2), (4300, 4, 2)])
+def test_expert_lists_hold_every_pair_in_order(tokens, experts, top_k):
+    seqs = [(tokens - 1, tokens - 1), (1, 9)] if tokens > 1 else [(1, 9)]
+    w = workload("lists", "bf16", 128, 1, 1, 128, 128, seqs, experts=experts, top_k=top_k, seed=200 + tokens)
+    data = gen.generate(w)
+    y, k, v = both_schedules(w, data)
+    say("%d pairs, %d experts: %.2e" % (tokens * top_k, experts, check_against_oracle(w, data, y, k, v)))
