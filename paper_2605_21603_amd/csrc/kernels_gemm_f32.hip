@@ -492,7 +492,8 @@ hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const void *R,
     return launch_f32_any<32, 32>(X, ldx, W, R, Y, max_rows, N, K, gr, F32Plain{}, s);
 }
 
-bool gemm_f32_gated_supported(int N2, int K) { return f32_whole(N2, K) && N2 % 64 == 0; }
+// (From I = 64 on: a narrower activation's padded rows are longer than [gate | up] rows, and a plan's workspace would grow.)
+bool gemm_f32_gated_supported(int N2, int K) { return f32_whole(N2, K) && N2 % 64 == 0 && N2 >= 128; }
 
 hipError_t launch_gemm_f32_gated(const void *X, int ldx, const void *W, void *Y, int ldy, int rows, int N2, int K, hipStream_t s) {
     return launch_f32_whole(X, ldx, W, nullptr, Y, rows, N2, K, F32Gated{ldy}, s);
