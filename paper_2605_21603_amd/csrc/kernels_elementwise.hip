@@ -182,7 +182,7 @@ __device__ __forceinline__ void append_v16(const T *__restrict__ qkv, const int3
                                            const int32_t *__restrict__ block_table, T *__restrict__ v_cache, const AttnShape &sh, int t0, int c, int rows) {
     constexpr int V = 16 / sizeof(T);
     typedef T vec_t __attribute__((ext_vector_type(V)));
-    __shared__ int page_of[16], slot_of[16], seq_at[16];
+    __shared__ int page_of[16], slot_of[16], one_run;
     const int n = min(16, rows - t0), d = sh.head_dim, width = (sh.n_q + 2 * sh.n_kv) * d;
     const bool mine = c < sh.n_kv * d;
     const T *const v0 = qkv + (size_t)t0 * width + (size_t)(sh.n_q + sh.n_kv) * d + (mine ? c : 0);
@@ -191,14 +191,16 @@ __device__ __forceinline__ void append_v16(const T *__restrict__ qkv, const int3
     for (int k = 0; k < 16; ++k) v[k] = v0[(size_t)min(k, n - 1) * width];
     if ((int)threadIdx.x < n) {
         const int pos = pos_of_token[t0 + threadIdx.x], seq = seq_of_token[t0 + threadIdx.x];
-        seq_at[threadIdx.x] = seq;
+        const bool next = seq == __builtin_amdgcn_readfirstlane(seq) && pos - (int)threadIdx.x == __builtin_amdgcn_readfirstlane(pos);
+        const unsigned long long follow = __ballot(next);
+        if (threadIdx.x == 0) one_run = follow == 0xffffull;
         slot_of[threadIdx.x] = pos % sh.page_size;
         page_of[threadIdx.x] = block_table[(size_t)seq * sh.max_pages_per_seq + pos / sh.page_size];
     }
     __syncthreads();
     if (!mine) return;
-    // a sequence's rows are adjacent and its positions consecutive; 16 positions from a multiple of 16 share a page of whole 16s
-    const bool run = n == 16 && seq_at[0] == seq_at[15] && slot_of[0] % 16 == 0 && sh.page_size % 16 == 0 && ((uintptr_t)v_cache & 15) == 0;
+    // 16 consecutive positions of one sequence from a multiple of 16 share a page of whole 16s
+    const bool run = one_run && slot_of[0] % 16 == 0 && sh.page_size % 16 == 0 && ((uintptr_t)v_cache & 15) == 0;
     const int g = c / d, i = c % d;
     if (run) {
         T *vp = v_cache + (((size_t)page_of[0] * sh.n_kv + g) * d + i) * sh.page_size + slot_of[0];
