@@ -54,6 +54,7 @@ struct Dispatch {
     int layer, op, nano, n_nano, r0, r1, stream, partition;
     bool any_multi;          // some sequence contributes more than one token to rows r0..r1
     bool any_single = true;  // attention: some sequence contributes exactly one
+    int long_rows = 0;       // qkv: rows of sequences that contribute 16 tokens and more
     bool noop;               // launches nothing: no rows, or the gate when the projection's epilogue applied it
     std::vector<int> deps;   // dispatches (indices into the plan) whose output rows this one reads
     bool plan = false;          // first norm: its launch also builds the attention work lists of its rows; attention: they have been built
@@ -381,6 +382,10 @@ dyn_status build_plan(const dyn_layer *L, const dyn_batch *b, const dyn_schedule
                     for (int i = s0; i < s1 && !d.any_single; ++i) d.any_single = q[i + 1] - q[i] == 1;
                 } else if (sl.op == DYN_OP_ATTN) {
                     d.any_single = plan[i].any_single;      // every layer dispatches the same rows
+                } else if (sl.op == DYN_OP_QKV && l == 0) {
+                    for (int i = s0; i < s1; ++i) d.long_rows += q[i + 1] - q[i] >= 16 ? q[i + 1] - q[i] : 0;
+                } else if (sl.op == DYN_OP_QKV) {
+                    d.long_rows = plan[i].long_rows;
                 }
             }
             const int pos = chain_pos[sl.op];
@@ -697,6 +702,7 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
             ep.v_cache = vc;
             ep.rope = &L->rope;
             ep.shape = &sh;
+            ep.long_rows = d.long_rows;
             err = dyn::launch_gemm(c.dtype, rowp(base + ws.h, ws.ld_h), ws.ld_h, w.w_qkv, nullptr, (void *)rowp(base + ws.qkv, NQKV),
                                    planes, (size_t)rows * NQKV, rows, NQKV, H, st, mid, &ep);
             break;

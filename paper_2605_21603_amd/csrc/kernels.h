@@ -80,6 +80,7 @@ struct GemmEpilogue {
     void *k_cache = nullptr, *v_cache = nullptr;
     const RopeTable *rope = nullptr;
     const AttnShape *shape = nullptr;
+    int long_rows = 0;       // of the rows, those of sequences with 16 tokens and more among them
 };
 
 // Y[rows,N] = X[rows,K] W[N,K]^T (+ R[rows,N]); ldx = elements between rows of X (>= K).  partial: fp32 scratch for split-K planes,
@@ -138,7 +139,7 @@ hipError_t launch_moe_combine(int dtype, const float *planes, size_t plane_strid
 // Rotary on the q and k heads of qkv rows (in place for q) and cache append of k', v.
 hipError_t launch_rope_kv(int dtype, void *qkv, const int32_t *seq_of_token, const int32_t *pos_of_token,
                           const int32_t *block_table, void *k_cache, void *v_cache, const RopeTable &tab,
-                          const AttnShape &sh, int rows, hipStream_t s);
+                          const AttnShape &sh, int rows, int long_rows, hipStream_t s);
 
 // The attention work lists inside `plan` (scratch of (4 * max_chunks + 5) * rows + 4 int32 at most): single-token
 // sequences, multi-token sequences, and the chunk size every token's partials are indexed by.

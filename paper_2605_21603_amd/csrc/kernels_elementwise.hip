@@ -172,53 +172,57 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(T *__restrict__ qkv, const
 // per head) into LDS; then a thread rotates V pair indices of one head with 16-byte loads and
 // stores (q in place, k into its cache page), and the v heads are scattered into the
 // position-fastest V page element by element.  Same arithmetic per element as the scalar form.
-// Many rows (ROWS16): 256 columns of the v heads of 16 adjacent rows are a workgroup's of their own, a column a thread.  Where the rows
-// are one sequence's from a multiple of 16 on, which is every prompt whose cached part fills its pages, a column's 16 positions
-// are adjacent in the page and leave as whole 16-byte stores: a token alone stores two bytes to each of its columns' 32.
-// (Rows of 32 + 16 heads of 128, bf16: 1120 14.2 -> 10.2, 2112 22.3 -> 14.3, 4096 33.7 -> 20.0 us; with four columns a thread, 1120 rows
-// took 18 us: the rows that are no run store 64 times, one behind the other.)
+// Many rows (RUNS): 16 rows of one sequence at consecutive positions from a multiple of 16 on - a run, wherever in the launch
+// it starts - share a page of whole 16s, where a column's 16 positions are adjacent and leave as whole 16-byte stores, 256
+// columns a workgroup, a column a thread.  A row of no run is its own workgroup's, two bytes to each of its columns' 32.
+// A prompt is runs but for its ends whatever row and position it starts at (launch, 32 + 16 heads of 128, bf16, a workgroup per row -> by
+// runs: 2048 rows 17.4 -> 12.9 us, behind 1001 positions 17.6 -> 14.2, behind three single tokens' rows 18.5 -> 13.4, prompts of 511 + 1000 +
+// 600 19.2 -> 14.8; fp32, 16 + 8 heads of 64: 2048 behind 1001 8.9 -> 7.0).
+struct RunWindow {                             // of rows base .. base + 30, one a lane
+    int row, pos, seq;
+    bool in;
+    __device__ __forceinline__ RunWindow(const int32_t *__restrict__ seq_of_token, const int32_t *__restrict__ pos_of_token, int base, int rows) {
+        const int lane = threadIdx.x & 63;
+        row = base + lane;
+        in = lane < 31 && row >= 0 && row < rows;
+        pos = pos_of_token[in ? row : 0];
+        seq = seq_of_token[in ? row : 0];
+    }
+    // Which of the first 16 rows a run starts at, a bit each: at most one.  Every lane of the wave takes part.
+    __device__ __forceinline__ unsigned starts() const {
+        const int lane = threadIdx.x & 63, seq_before = __shfl_up(seq, 1, 64), pos_before = __shfl_up(pos, 1, 64);
+        const unsigned long long follows = __ballot(lane > 0 && in && row > 0 && seq == seq_before && pos == pos_before + 1);
+        return (unsigned)__ballot(lane < 16 && in && pos % 16 == 0 && (follows >> (lane + 1) & 0x7fff) == 0x7fff);
+    }
+};
+
+// The run that starts in rows t0 .. t0 + 15, column c of the v heads.
 template <typename T>
-__device__ __forceinline__ void append_v16(const T *__restrict__ qkv, const int32_t *__restrict__ seq_of_token, const int32_t *__restrict__ pos_of_token,
-                                           const int32_t *__restrict__ block_table, T *__restrict__ v_cache, const AttnShape &sh, int t0, int c, int rows) {
+__device__ __forceinline__ void append_v_run(const T *__restrict__ qkv, const int32_t *__restrict__ seq_of_token, const int32_t *__restrict__ pos_of_token,
+                                             const int32_t *__restrict__ block_table, T *__restrict__ v_cache, const AttnShape &sh, int t0, int c, int rows) {
     constexpr int V = 16 / sizeof(T);
     typedef T vec_t __attribute__((ext_vector_type(V)));
-    __shared__ int page_of[16], slot_of[16], one_run;
-    const int n = min(16, rows - t0), d = sh.head_dim, width = (sh.n_q + 2 * sh.n_kv) * d;
-    const bool mine = c < sh.n_kv * d;
-    const T *const v0 = qkv + (size_t)t0 * width + (size_t)(sh.n_q + sh.n_kv) * d + (mine ? c : 0);
+    const RunWindow window(seq_of_token, pos_of_token, t0, rows);
+    const unsigned starts = window.starts();
+    if (!starts || c >= sh.n_kv * sh.head_dim) return;
+    const int first = __builtin_ctz(starts), d = sh.head_dim, width = (sh.n_q + 2 * sh.n_kv) * d, g = c / d, i = c % d;
+    const int pos = __builtin_amdgcn_readlane(window.pos, first), seq = __builtin_amdgcn_readlane(window.seq, first);
+    const T *const v0 = qkv + (size_t)(t0 + first) * width + (size_t)(sh.n_q + sh.n_kv) * d + c;
     T v[16];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = v0[(size_t)min(k, n - 1) * width];
-    if ((int)threadIdx.x < n) {
-        const int pos = pos_of_token[t0 + threadIdx.x], seq = seq_of_token[t0 + threadIdx.x];
-        const bool next = seq == __builtin_amdgcn_readfirstlane(seq) && pos - (int)threadIdx.x == __builtin_amdgcn_readfirstlane(pos);
-        const unsigned long long follow = __ballot(next);
-        if (threadIdx.x == 0) one_run = follow == 0xffffull;
-        slot_of[threadIdx.x] = pos % sh.page_size;
-        page_of[threadIdx.x] = block_table[(size_t)seq * sh.max_pages_per_seq + pos / sh.page_size];
-    }
-    __syncthreads();
-    if (!mine) return;
-    // 16 consecutive positions of one sequence from a multiple of 16 share a page of whole 16s
-    const bool run = one_run && slot_of[0] % 16 == 0 && sh.page_size % 16 == 0 && ((uintptr_t)v_cache & 15) == 0;
-    const int g = c / d, i = c % d;
-    if (run) {
-        T *vp = v_cache + (((size_t)page_of[0] * sh.n_kv + g) * d + i) * sh.page_size + slot_of[0];
+    for (int k = 0; k < 16; ++k) v[k] = v0[(size_t)k * width];
+    const int page = block_table[(size_t)seq * sh.max_pages_per_seq + pos / sh.page_size];
+    T *const vp = v_cache + (((size_t)page * sh.n_kv + g) * d + i) * sh.page_size + pos % sh.page_size;
 #pragma unroll
-        for (int k = 0; k < 16; k += V) {
-            vec_t o;
+    for (int k = 0; k < 16; k += V) {
+        vec_t o;
 #pragma unroll
-            for (int j = 0; j < V; ++j) o[j] = v[k + j];
-            *reinterpret_cast<vec_t *>(vp + k) = o;
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < 16; ++k)
-            if (k < n) v_cache[(((size_t)page_of[k] * sh.n_kv + g) * d + i) * sh.page_size + slot_of[k]] = v[k];
+        for (int j = 0; j < V; ++j) o[j] = v[k + j];
+        *reinterpret_cast<vec_t *>(vp + k) = o;
     }
 }
 
-template <typename T, bool ROWS16>
+template <typename T, bool RUNS, int AHEAD>
 __global__ __launch_bounds__(256) void rope_kv_vec_kernel(T *__restrict__ qkv, const int32_t *__restrict__ seq_of_token,
                                                           const int32_t *__restrict__ pos_of_token,
                                                           const int32_t *__restrict__ block_table,
@@ -227,21 +231,20 @@ __global__ __launch_bounds__(256) void rope_kv_vec_kernel(T *__restrict__ qkv, c
     constexpr int V = 16 / sizeof(T);
     typedef T vec_t __attribute__((ext_vector_type(V)));
     __shared__ float cs[2][128];                          // cos, sin of the token's angles (head_dim <= 256)
-    const int v_across = (sh.n_kv * sh.head_dim + 255) / 256, v_groups = ROWS16 ? (rows + 15) / 16 * v_across : 0;
-    if (ROWS16 && (int)blockIdx.x < v_groups) {
-        append_v16<T>(qkv, seq_of_token, pos_of_token, block_table, v_cache, sh, (int)blockIdx.x / v_across * 16,
-                      (int)blockIdx.x % v_across * 256 + (int)threadIdx.x, rows);
+    const int v_across = (sh.n_kv * sh.head_dim + 255) / 256, v_groups = RUNS ? (rows + 15) / 16 * v_across : 0;
+    if (RUNS && (int)blockIdx.x < v_groups) {
+        append_v_run<T>(qkv, seq_of_token, pos_of_token, block_table, v_cache, sh, (int)blockIdx.x / v_across * 16,
+                        (int)blockIdx.x % v_across * 256 + (int)threadIdx.x, rows);
         return;
     }
     const int t = blockIdx.x - v_groups;
     const int d = sh.head_dim, half = d >> 1;
     T *row = qkv + (size_t)t * ((sh.n_q + 2 * sh.n_kv) * d);
     const int per_head = half / V, n_rot = (sh.n_q + sh.n_kv) * per_head;
-    // a token's units are dealt over gridDim.y workgroups (few tokens: more workgroups than tokens); a thread's first two are loaded
-    // ahead of the position, the angles and the barrier behind them
+    // a token's units are dealt over gridDim.y workgroups (few tokens: more workgroups than tokens); a thread's first AHEAD are
+    // loaded ahead of the position, the angles and the barrier behind them
     const int first = blockIdx.y * 256 + threadIdx.x, step = gridDim.y * 256;
-    constexpr int AHEAD = 2;
-    vec_t a[AHEAD], b[AHEAD];
+    vec_t a[AHEAD > 0 ? AHEAD : 1], b[AHEAD > 0 ? AHEAD : 1];
     auto load = [&](int u, vec_t &lo, vec_t &hi) {
         const T *z = row + u / per_head * d + u % per_head * V;
         lo = *reinterpret_cast<const vec_t *>(z);
@@ -250,6 +253,7 @@ __global__ __launch_bounds__(256) void rope_kv_vec_kernel(T *__restrict__ qkv, c
 #pragma unroll
     for (int j = 0; j < AHEAD; ++j)
         if (first + j * step < n_rot) load(first + j * step, a[j], b[j]);
+    const RunWindow window(seq_of_token, pos_of_token, RUNS ? t - 15 : t, rows);      // a run that holds row t starts in its first 16
     const int pos = pos_of_token[t];
     for (int i = threadIdx.x; i < half; i += 256) {
         float sn, c;
@@ -280,7 +284,7 @@ __global__ __launch_bounds__(256) void rope_kv_vec_kernel(T *__restrict__ qkv, c
         load(u, a[0], b[0]);
         rotate(u, a[0], b[0]);
     }
-    if (ROWS16) return;
+    if (RUNS && window.starts()) return;
     const T *vrow = row + (sh.n_q + sh.n_kv) * d;
     for (int u = first; u < sh.n_kv * d; u += step) {                   // v heads -> V page [kvh][d][slot]
         const int g = u / d, i = u % d;
@@ -411,19 +415,24 @@ hipError_t launch_reduce_rope(const float *P, size_t plane_stride, int S, void *
 
 hipError_t launch_rope_kv(int dtype, void *qkv, const int32_t *seq_of_token, const int32_t *pos_of_token,
                           const int32_t *block_table, void *k_cache, void *v_cache, const RopeTable &tab,
-                          const AttnShape &sh, int rows, hipStream_t s) {
+                          const AttnShape &sh, int rows, int long_rows, hipStream_t s) {
     if (rows <= 0) return hipSuccess;
     const int vec = dtype == 0 ? 4 : 8;
     if ((sh.head_dim / 2) % vec == 0 && sh.head_dim <= 256) {
-        // from 512 rows on there are workgroups enough with one per row
-#define DYN_ROPE(T, ROWS16, GRID)                                                                                                        \
-    hipLaunchKernelGGL((rope_kv_vec_kernel<T, ROWS16>), GRID, dim3(256), 0, s, (T *)qkv, seq_of_token, pos_of_token, block_table, (T *)k_cache, \
+        // From 512 rows on there are workgroups enough with one per row.  The v heads go by runs where pages hold whole ones and a
+        // quarter of the rows may belong to some: looking for runs where there are none costs up to a microsecond (1100 single tokens: bf16
+        // 20.2 us by rows, 21.1 by runs, fp32 8.9, 9.2), and a row in a run saves 2 ns.  By rows nothing is loaded ahead (two units: 21.2, 9.3).
+        const bool runs = long_rows >= rows / 4 && sh.page_size % 16 == 0 && ((uintptr_t)v_cache & 15) == 0;
+        const int run_groups = (rows + 15) / 16 * ((sh.n_kv * sh.head_dim + 255) / 256);
+#define DYN_ROPE(T, RUNS, AHEAD, GRID)                                                                                                          \
+    hipLaunchKernelGGL((rope_kv_vec_kernel<T, RUNS, AHEAD>), GRID, dim3(256), 0, s, (T *)qkv, seq_of_token, pos_of_token, block_table, (T *)k_cache, \
                        (T *)v_cache, tab, sh, rows)
-        const dim3 few(rows, 4), many(rows + (rows + 15) / 16 * ((sh.n_kv * sh.head_dim + 255) / 256));
-        if (dtype == 0) {
-            if (rows < 512) DYN_ROPE(float, false, few); else DYN_ROPE(float, true, many);
+        if (rows >= 512 && runs) {
+            if (dtype == 0) DYN_ROPE(float, true, 2, dim3(rows + run_groups)); else DYN_ROPE(bf16_t, true, 2, dim3(rows + run_groups));
+        } else if (rows >= 512) {
+            if (dtype == 0) DYN_ROPE(float, false, 0, dim3(rows)); else DYN_ROPE(bf16_t, false, 0, dim3(rows));
         } else {
-            if (rows < 512) DYN_ROPE(bf16_t, false, few); else DYN_ROPE(bf16_t, true, many);
+            if (dtype == 0) DYN_ROPE(float, false, 2, dim3(rows, 4)); else DYN_ROPE(bf16_t, false, 2, dim3(rows, 4));
         }
 #undef DYN_ROPE
         return hipGetLastError();

@@ -344,7 +344,8 @@ namespace {
 hipError_t run_epilogue(int dtype, const GemmEpilogue &ep, void *Y, int rows, int N, hipStream_t s) {
     if (ep.kind == GemmEpilogue::NORM) return launch_rmsnorm(dtype, Y, ep.g, ep.h_out, ep.ld_h, rows, N, ep.eps, s);
     if (ep.kind == GemmEpilogue::ROPE)
-        return launch_rope_kv(dtype, Y, ep.seq_of_token, ep.pos_of_token, ep.block_table, ep.k_cache, ep.v_cache, *ep.rope, *ep.shape, rows, s);
+        return launch_rope_kv(dtype, Y, ep.seq_of_token, ep.pos_of_token, ep.block_table, ep.k_cache, ep.v_cache, *ep.rope, *ep.shape, rows,
+                              ep.long_rows, s);
     if (ep.kind == GemmEpilogue::GATE) return launch_silu_mul(dtype, Y, ep.h_out, ep.ld_h, rows, N / 2, s);
     return hipSuccess;
 }

@@ -182,6 +182,50 @@ def test_v_of_16_rows_is_appended_whole(dtype, hidden, n_q, n_kv, hd, page):
     say("%d rows: %.2e" % (T, check_against_oracle(w, data, *whole)))
 
 
+def rows_in_runs(seqs):
+    """Rows that belong to 16 rows of one sequence at consecutive positions from a multiple of 16 on."""
+    return sum(max(0, c // 16 - (c - q + 15) // 16) * 16 for q, c in seqs)
+
+
+# The runs themselves: a cached prefix that fills its pages or not (runs at slot 0 and at slot 16 of a later page), prompts that
+# start on a row that is a multiple of 16 or behind single tokens, sequences that are one run, a run and a rest on either side, or
+# just none; pages that hold no whole run.  Parts below 512 rows append row by row: the same bits.
+@pytest.mark.parametrize("dtype,page,seqs,runs", [
+    ("bf16", 16, [(320, 368), (208, 208)], 528), ("bf16", 32, [(320, 368), (208, 1209)], 512), ("bf16", 64, [(1, 77)] * 3 + [(320, 361), (200, 200)], 496),
+    ("f32", 16, [(1, 9)] + [(15 + i % 18, 15 + i % 18 + (7 * i) % 40) for i in range(24)], None), ("f32", 48, [(1, 5)] * 7 + [(16, 32), (17, 32), (31, 47), (30, 45), (500, 517)], 544),
+    ("bf16", 24, [(500, 500), (33, 70)], 0), ("f32", 16, [(1, 1 + i % 50) for i in range(400)] + [(140, 150)], 128)])
+def test_v_runs_start_anywhere(dtype, page, seqs, runs):
+    T = sum(q for q, _ in seqs)
+    assert T >= 512 and (runs is None or (rows_in_runs(seqs) if page % 16 == 0 else 0) == runs)
+    w = workload("v_runs", dtype, 256, 4, 2, 64, 512, seqs, page=page, seed=190 + T)
+    cut = next(sum(q for q, _ in seqs[:i]) for i in range(len(seqs), 0, -1) if sum(q for q, _ in seqs[:i]) < 512)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, cut, T))
+    data = gen.generate(w)
+    run = GpuRun(w, data)
+    whole = run.run(B.sequential())
+    parts = run.run(B.nano_schedule(w.nano_rows, chain=B.DENSE_CHAIN))
+    for a, b in zip(whole, parts):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    say("%d rows: %.2e" % (T, check_against_oracle(w, data, *whole)))
+
+
+def test_v_cache_off_a_16_byte_line_is_appended_row_by_row():
+    w = workload("v_off", "f32", 128, 4, 2, 64, 256, [(500, 500), (30, 60)], seed=199)
+    data = gen.generate(w)
+    run = GpuRun(w, data)
+    whole = run.run(B.sequential())
+    step = B.DeviceStep(run.layer, data)
+    flat = torch.empty(step.v_cache.numel() + 4, dtype=step.v_cache.dtype, device="cuda:0")
+    off = flat[1:1 + step.v_cache.numel()].view(step.v_cache.shape)
+    off.copy_(step.v_cache)
+    step.batch.v_cache = off.data_ptr()
+    st = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    run.layer.forward(step.batch, B.sequential(), st)
+    st.synchronize()
+    assert torch.equal(off.cpu(), whole[2]) and torch.equal(step.k_cache.cpu(), whole[1])
+
+
 # Expert lists by sixteen waves: 1 pair, a wave's 64 and one more, whole and ragged steps of 1024, and more than the 8192 pairs of one pass.
 @pytest.mark.parametrize("tokens,experts,top_k", [(1, 3, 1), (64, 16, 1), (65, 5, 1), (512, 8, 2), (513, 16, 2), (4300, 4, 2)])
 def test_expert_lists_hold_every_pair_in_order(tokens, experts, top_k):
