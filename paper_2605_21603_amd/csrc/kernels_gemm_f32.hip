@@ -244,9 +244,12 @@ __device__ __forceinline__ void quad_transpose(f32x4 (&v)[4]) {
 // block's four covers rows 4 q + j, q = 0..3, 256 bytes each; in MFMA layout a quarter wave names 16 rows and the
 // load takes 65 cycles of the vector cache, this way 17.  16 x 16 tiles keep two blocks in flight (24 rows x 1024 x 4096
 // 15.9 -> 11.0 us, 100 rows 30.7 -> 19.2); with 32 x 32 that costs the second workgroup of a CU (225 rows x 1024 x 4096 31.6 -> 28.8
-// us, 30.3 with two).  Trading takes 64 vector instructions an operand: what is one short block long gains nothing
-// (4 rows x 1024 x 1024 4.6 -> 5.1 us, x 8192 x 1024 8.0 -> 8.9, x 1024 x 4096 12.0 -> 10.8).
-template <int MT, int NT, class EP>
+// us, 30.3 with two).  Trading takes 64 vector instructions an operand.  Up to 8 rows X is loaded straight into MFMA layout instead (XQUADS
+// false): the lanes of rows past the last one name its lines again, so a load costs what its few rows do (1 / 4 rows: 8192 x 1024, gated 11.9 /
+// 12.7 -> 11.9 / 11.9 us, 1024 x 4096 11.2 / 11.0 -> 9.7 / 9.8, 16384 x 2048, gated 28.2 / 28.4 -> 23.4 / 24.2, 2048 x 8192 20.2 / 20.4 ->
+// 17.1 / 18.3; steps of 2048 wide, 8192 MLP, 1 / 8 / 16 rows 92.7 / 98.2 / 99.2 -> 84.5 / 92.1 / 99.0: at 16 rows either way, so the line is
+// where half the rows are there).
+template <int MT, int NT, bool XQUADS, class EP>
 __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_quads_kernel(const float *__restrict__ X, int ldx, const float *__restrict__ W,
                                                                         const float *__restrict__ R, float *__restrict__ Y, int M, int N, int K, EP ep) {
     constexpr int NA = NT / 16, NB = MT / 16, NBUF = NA + NB <= 3 ? 2 : 1;
@@ -262,7 +265,7 @@ __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_quads_kernel(const f
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) xo[b][j] = (size_t)min(b * 16 + row4 + j, M - 1 - m0) * ldx + col;
+        for (int j = 0; j < 4; ++j) xo[b][j] = XQUADS ? (size_t)min(b * 16 + row4 + j, M - 1 - m0) * ldx + col : (size_t)min(b * 16 + (lane & 15), M - 1 - m0) * ldx + (lane >> 4) * 16 + 4 * j;
     f32x4 acc[NA][NB];
 #pragma unroll
     for (int a = 0; a < NA; ++a)
@@ -286,8 +289,10 @@ __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_quads_kernel(const f
         constexpr int B = decltype(buf)::value;
 #pragma unroll
         for (int a = 0; a < NA; ++a) quad_transpose(wv[B][a]);
+        if constexpr (XQUADS) {
 #pragma unroll
-        for (int b = 0; b < NB; ++b) quad_transpose(xv[B][b]);
+            for (int b = 0; b < NB; ++b) quad_transpose(xv[B][b]);
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -448,8 +453,16 @@ hipError_t launch_f32_tiles(const void *X, int ldx, const void *W, const void *R
 
 template <int MT, int NT, class EP>
 hipError_t launch_f32_quads(const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, const EP &ep, hipStream_t s) {
-    hipLaunchKernelGGL((gemm_f32_quads_kernel<MT, NT, EP>), dim3((N + NT - 1) / NT, (rows + MT - 1) / MT), dim3(kF32Chains * 64), 0, s,
-                       (const float *)X, ldx, (const float *)W, (const float *)R, (float *)Y, rows, N, K, ep);
+#define DYN_QUADS(XQUADS)                                                                                                                 \
+    hipLaunchKernelGGL((gemm_f32_quads_kernel<MT, NT, XQUADS, EP>), dim3((N + NT - 1) / NT, (rows + MT - 1) / MT), dim3(kF32Chains * 64), 0, s, \
+                       (const float *)X, ldx, (const float *)W, (const float *)R, (float *)Y, rows, N, K, ep)
+    if constexpr (MT == 16)
+        if (rows <= 8) {
+            DYN_QUADS(false);
+            return hipGetLastError();
+        }
+    DYN_QUADS(true);
+#undef DYN_QUADS
     return hipGetLastError();
 }
 

@@ -182,6 +182,24 @@ def test_v_of_16_rows_is_appended_whole(dtype, hidden, n_q, n_kv, hd, page):
     say("%d rows: %.2e" % (T, check_against_oracle(w, data, *whole)))
 
 
+# Up to 8 rows of whole 64-deep blocks X is loaded straight into MFMA layout, from 9 on by quads that trade: parts of 8 rows and fewer
+# beside a whole batch of 9 to 16, plain, gated and rotary forms, one and several blocks a chain: the same bits.
+@pytest.mark.parametrize("hidden,n_q,n_kv,hd,inter,cut,rows", [
+    (512, 8, 2, 64, 1024, 1, 9), (1024, 16, 4, 64, 2048, 8, 9), (2048, 4, 2, 128, 1536, 8, 16), (1536, 8, 4, 32, 4608, 3, 11)])
+def test_fp32_x_of_few_rows_goes_straight(hidden, n_q, n_kv, hd, inter, cut, rows):
+    w = workload("f32_x", "f32", hidden, n_q, n_kv, hd, inter, [(1, 1 + (i * 37) % 120) for i in range(rows)], seed=170 + rows)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, cut, rows))
+    data = gen.generate(w)
+    run = GpuRun(w, data)
+    whole = run.run(B.sequential())
+    parts = run.run(B.nano_schedule(w.nano_rows, chain=B.DENSE_CHAIN))
+    for a, b in zip(whole, parts):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    err = check_against_oracle(w, data, *whole)
+    say("%d + %d rows: %.2e" % (cut, rows - cut, err))
+    assert err < 2e-6                                        # as the fp32 projections' own tests
+
+
 def rows_in_runs(seqs):
     """Rows that belong to 16 rows of one sequence at consecutive positions from a multiple of 16 on."""
     return sum(max(0, c // 16 - (c - q + 15) // 16) * 16 for q, c in seqs)
