@@ -129,6 +129,7 @@ hipError_t launch_route(int dtype, const void *h, int ldh, const float *w_router
 
 // Per-expert lists of (token, rank) pairs p = t * top_k + j in ascending p, for the rows of one
 // dispatch: counts[E], lists[E, cap].  pair_base = first pair id of the dispatch.
+bool expert_lists_scan(int n_pairs, int E);      // by a wave per expert, else by sixteen waves
 hipError_t launch_expert_lists(const int32_t *sel, int n_pairs, int pair_base, int E, int cap, int32_t *counts,
                                int32_t *lists, hipStream_t s);
 

@@ -2,6 +2,8 @@
 // weighted combine.  Every token's routing and output depend on that token alone, and every
 // sum has a fixed order (experts by router rank, split-K planes ascending), so results do
 // not depend on how the batch is cut.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -114,28 +116,33 @@ hipError_t launch_route(int dtype, const void *h, int ldh, const float *w_router
     return hipGetLastError();
 }
 
-// Up to 512 pairs: one wave per expert loads them all at a time and appends its own in ascending order.
-constexpr int kScanAhead = 8, kScanPairs = 64 * kScanAhead;
+// One wave per expert scans the dispatch's pairs, 512 loaded at a time, and appends its own in ascending order.
 __global__ void expert_lists_scan_kernel(const int32_t *__restrict__ sel, int n_pairs, int pair_base, int cap, int32_t *__restrict__ counts,
                                          int32_t *__restrict__ lists) {
     const int e = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int count = 0, chosen[kScanAhead];
+    constexpr int AHEAD = 8;
+    int count = 0;
+    for (int base = 0; base < n_pairs; base += 64 * AHEAD) {
+        int chosen[AHEAD];
 #pragma unroll
-    for (int i = 0; i < kScanAhead; ++i) chosen[i] = i * 64 + lane < n_pairs ? sel[pair_base + i * 64 + lane] : -1;
+        for (int i = 0; i < AHEAD; ++i) {
+            const int p = base + i * 64 + lane;
+            chosen[i] = p < n_pairs ? sel[pair_base + p] : -1;
+        }
 #pragma unroll
-    for (int i = 0; i < kScanAhead; ++i) {
-        const bool mine = chosen[i] == e;
-        const unsigned long long mask = __ballot(mine);
-        if (mine) lists[(size_t)e * cap + count + __popcll(mask & ((1ull << lane) - 1ull))] = pair_base + i * 64 + lane;
-        count += __popcll(mask);
+        for (int i = 0; i < AHEAD; ++i) {
+            const bool mine = chosen[i] == e;
+            const unsigned long long mask = __ballot(mine);
+            if (mine) lists[(size_t)e * cap + count + __popcll(mask & ((1ull << lane) - 1ull))] = pair_base + base + i * 64 + lane;
+            count += __popcll(mask);
+        }
     }
     if (lane == 0) counts[e] = count;
 }
 
 // More pairs: sixteen waves take consecutive parts of the dispatch's pairs; each counts its part's pairs per expert, the counts of the waves before it
 // are its offsets, and every expert's pairs land in ascending order.  Bound by the latency of one load, two barriers and a ballot
-// per expert and 64 pairs, twice: 2240 pairs of 8 experts 13.2 us by a wave per expert that scans all of them, 7.6 this way; 512 pairs
-// 5.1 and 7.0.
+// per expert and 64 pairs, twice.
 constexpr int kListWaves = 16, kListAhead = 8;             // 64-pair steps of a wave kept in registers between count and store
 __global__ __launch_bounds__(kListWaves * 64) void expert_lists_kernel(const int32_t *__restrict__ sel, int n_pairs, int pair_base, int E, int cap,
                                                                        int32_t *__restrict__ counts, int32_t *__restrict__ lists) {
@@ -187,10 +194,16 @@ __global__ __launch_bounds__(kListWaves * 64) void expert_lists_kernel(const int
     if ((int)threadIdx.x < E) counts[threadIdx.x] = before[threadIdx.x];
 }
 
+// The scan takes the time of its steps of 512 pairs, each a load's latency, the sixteen waves that of their ballots, which are as many
+// as there are experts (launches inside a layer's steps, scan / sixteen waves, us: 4 experts 520 pairs 3.9 / 3.7, 800 4.6 / 3.8; 8
+// experts 700 4.0 / 4.8, 900 4.9 / 5.0, 1000 7.2 / 4.9, 1536 9.7 / 5.6; 16 experts 1040 7.2 / 7.8, 1200 6.4 / 8.0, 1600 8.7 / 8.7, 2048 10.0 /
+// 8.8, 3072 15.5 / 10.6).
+bool expert_lists_scan(int n_pairs, int E) { return n_pairs <= std::max(512, 100 * E); }
+
 hipError_t launch_expert_lists(const int32_t *sel, int n_pairs, int pair_base, int E, int cap, int32_t *counts,
                                int32_t *lists, hipStream_t s) {
     if (n_pairs <= 0) return hipSuccess;
-    if (n_pairs <= kScanPairs) hipLaunchKernelGGL(expert_lists_scan_kernel, dim3(1), dim3(64 * E), 0, s, sel, n_pairs, pair_base, cap, counts, lists);
+    if (expert_lists_scan(n_pairs, E)) hipLaunchKernelGGL(expert_lists_scan_kernel, dim3(1), dim3(64 * E), 0, s, sel, n_pairs, pair_base, cap, counts, lists);
     else hipLaunchKernelGGL(expert_lists_kernel, dim3(1), dim3(kListWaves * 64), 0, s, sel, n_pairs, pair_base, E, cap, counts, lists);
     return hipGetLastError();
 }

@@ -1,5 +1,7 @@
 """GPU tests at the edges of dispatch rules: sizes on both sides of a line, against the oracle and against the
 same rows in other launches."""
+import ctypes
+
 import pytest
 import torch
 
@@ -244,7 +246,7 @@ def test_v_cache_off_a_16_byte_line_is_appended_row_by_row():
     assert torch.equal(off.cpu(), whole[2]) and torch.equal(step.k_cache.cpu(), whole[1])
 
 
-# Expert lists by sixteen waves: 1 pair, a wave's 64 and one more, whole and ragged steps of 1024, and more than the 8192 pairs of one pass.
+# Layers over lists of 1 pair, a wave's 64 and one more and 1026 of 16 experts (scanned), 1024 of 8 and more than the 8192 pairs of one pass (by sixteen waves).
 @pytest.mark.parametrize("tokens,experts,top_k", [(1, 3, 1), (64, 16, 1), (65, 5, 1), (512, 8, 2), (513, 16, 2), (4300, 4, 2)])
 def test_expert_lists_hold_every_pair_in_order(tokens, experts, top_k):
     seqs = [(tokens - 1, tokens - 1), (1, 9)] if tokens > 1 else [(1, 9)]
@@ -252,3 +254,28 @@ def test_expert_lists_hold_every_pair_in_order(tokens, experts, top_k):
     data = gen.generate(w)
     y, k, v = both_schedules(w, data)
     say("%d pairs, %d experts: %.2e" % (tokens * top_k, experts, check_against_oracle(w, data, y, k, v)))
+
+
+# The lists themselves, read back: both sides of the line between the scan and the sixteen waves (512 pairs; 100 an expert from 6 experts on),
+# steps of 512 and of 1024 pairs and one more or less, waves without a pair, several passes, pairs that begin past 0, an expert nobody chose.
+@pytest.mark.parametrize("experts,n_pairs,scan", [
+    (3, 1, 1), (8, 64, 1), (4, 512, 1), (4, 513, 0), (1, 960, 0), (2, 1024, 0), (2, 1025, 0), (8, 800, 1), (8, 801, 0), (16, 513, 1), (16, 1600, 1),
+    (16, 1601, 0), (5, 2048, 0), (8, 8192, 0), (8, 8193, 0), (16, 16390, 0)])
+def test_expert_lists_read_back(experts, n_pairs, scan):
+    lib = B.lib()
+    assert lib._ZN3dyn17expert_lists_scanEii(n_pairs, experts) & 0xff == scan
+    f = lib._ZN3dyn19launch_expert_listsEPKiiiiiPiS2_P12ihipStream_t
+    f.argtypes, f.restype = [ctypes.c_void_p] + [ctypes.c_int] * 4 + [ctypes.c_void_p] * 3, ctypes.c_int
+    base, cap = 37, n_pairs + 5
+    sel = torch.randint(0, experts, (base + n_pairs,), dtype=torch.int32, generator=torch.Generator().manual_seed(n_pairs))
+    if experts > 2:
+        sel[sel == 1] = 0
+    d_sel, counts, lists = sel.cuda(), torch.full((experts,), -1, dtype=torch.int32, device="cuda:0"), torch.full((experts, cap), -1, dtype=torch.int32, device="cuda:0")
+    st = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    assert f(d_sel.data_ptr(), n_pairs, base, experts, cap, counts.data_ptr(), lists.data_ptr(), st.cuda_stream) == 0
+    st.synchronize()
+    for e in range(experts):
+        want = (sel[base:] == e).nonzero().flatten().int() + base
+        assert counts[e].item() == len(want)
+        assert torch.equal(lists[e, :len(want)].cpu(), want) and (lists[e, len(want):] == -1).all()
