@@ -704,7 +704,7 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
             ep.shape = &sh;
             ep.long_rows = d.long_rows;
             err = dyn::launch_gemm(c.dtype, rowp(base + ws.h, ws.ld_h), ws.ld_h, w.w_qkv, nullptr, (void *)rowp(base + ws.qkv, NQKV),
-                                   planes, (size_t)rows * NQKV, rows, NQKV, H, st, mid, &ep);
+                                   planes, (size_t)rows * NQKV, rows, NQKV, H, st, mid, &ep, sh.n_cus);
             break;
         }
         case DYN_OP_ROPE_KV:
@@ -724,7 +724,7 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
             ep.ld_h = ws.ld_h;
             ep.eps = c.rms_eps;
             err = dyn::launch_gemm(c.dtype, rowp(base + ws.attn, ws.ld_attn), ws.ld_attn, w.w_o, rowp(x_in, H), (void *)rowp(base + ws.x2, H),
-                                   planes, (size_t)rows * H, rows, H, NQ, st, mid, &ep);
+                                   planes, (size_t)rows * H, rows, H, NQ, st, mid, &ep, sh.n_cus);
             break;
         }
         case DYN_OP_NORM2:
@@ -761,7 +761,7 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
                     ep.h_out = act;
                     ep.ld_h = ws.ld_act;
                     err = dyn::launch_gemm(c.dtype, rowp(base + ws.h, ws.ld_h), ws.ld_h, w.w_gate_up, nullptr, planes, planes, (size_t)rows * 2 * I,
-                                           rows, 2 * I, H, st, mid, &ep);
+                                           rows, 2 * I, H, st, mid, &ep, sh.n_cus);
                 } else {
                     err = dyn::launch_gemm_gated(c.dtype, rowp(base + ws.h, ws.ld_h), ws.ld_h, w.w_gate_up, act, ws.ld_act, dyn::GemmGroups{}, rows,
                                                  2 * I, H, st, mid);
@@ -769,7 +769,7 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
                 break;
             }
             err = dyn::launch_gemm(c.dtype, rowp(base + ws.h, ws.ld_h), ws.ld_h, w.w_gate_up, nullptr, (void *)rowp(base + ws.gu, 2 * I),
-                                   planes, (size_t)rows * 2 * I, rows, 2 * I, H, st, mid);
+                                   planes, (size_t)rows * 2 * I, rows, 2 * I, H, st, mid, nullptr, sh.n_cus);
             break;
         case DYN_OP_SILU:
             if (d.gated) break;                                   // done by the gate/up projection's dispatch
@@ -812,7 +812,7 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
                 ep.eps = c.rms_eps;
             }
             err = dyn::launch_gemm(c.dtype, rowp(base + ws.act, ws.ld_act), ws.ld_act, w.w_down, rowp(base + ws.x2, H), (void *)rowp(x_out, H),
-                                   planes, (size_t)rows * H, rows, H, I, st, mid, &ep);
+                                   planes, (size_t)rows * H, rows, H, I, st, mid, &ep, sh.n_cus);
             break;
         }
         default:

@@ -86,9 +86,10 @@ struct GemmEpilogue {
 // Y[rows,N] = X[rows,K] W[N,K]^T (+ R[rows,N]); ldx = elements between rows of X (>= K).  partial: fp32 scratch for split-K planes,
 // plane p at partial + p * plane_stride (elements); unused when the split factor is 1.
 // If mid is not NULL it is recorded after the contraction kernel, before the split-K reduce.
+// n_cus: compute units of the partition the stream runs on, 0: all.
 hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const void *R, void *Y, float *partial,
                        size_t plane_stride, int rows, int N, int K, hipStream_t s, hipEvent_t mid = nullptr,
-                       const GemmEpilogue *ep = nullptr);
+                       const GemmEpilogue *ep = nullptr, int n_cus = 0);
 
 // fp32 projection, plain or expert-grouped (kernels_gemm_f32.hip; launch_gemm and launch_gemm_grouped call it); max_rows bounds a group's rows.
 hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const void *R, void *Y, int max_rows, int N, int K, const GemmGroups &gr,
@@ -98,8 +99,9 @@ bool gemm_f32_rope_supported(const void *X, int ldx, const void *W, int rows, in
 hipError_t launch_gemm_f32_rope(const void *X, int ldx, const void *W, void *Y, int rows, int N, int K, const GemmEpilogue &rope, hipStream_t s);
 hipError_t launch_gemm_f32_gated(const void *X, int ldx, const void *W, void *Y, int ldy, int rows, int N2, int K, hipStream_t s);
 // A few rows (at most 16), planes summed in the workgroup (kernels_gemm_rows.hip; launch_gemm calls it).
-bool gemm_rows16_supported(int rows, int N, int K, int S);            // with 8 X rows a stage
-bool gemm_rows16_wide_supported(int rows, int N, int K, int S);       // with 16
+bool gemm_rows16_wide_supported(int rows, int N, int K, int S);       // on the whole chip
+bool gemm_rows16_supported(int rows, int N, int K, int S);            // on any number of CUs
+bool gemm_rows16_taken(int rows, int N, int K, int S, int n_cus, bool norm);   // n_cus: of the partition, 0: all; norm: an RMSNorm follows
 bool gemm_rows16_rope_supported(const AttnShape &sh);                 // with rotary + cache append in the same launch
 hipError_t launch_gemm_rows16(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int S,
                               const GemmEpilogue *rope);

@@ -361,7 +361,7 @@ GemmEpilogue epilogue_at(const GemmEpilogue &ep, int dtype, int row, int N) {   
 }  // namespace
 
 hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const void *R, void *Y, float *partial,
-                       size_t plane_stride, int rows, int N, int K, hipStream_t s, hipEvent_t mid, const GemmEpilogue *ep) {
+                       size_t plane_stride, int rows, int N, int K, hipStream_t s, hipEvent_t mid, const GemmEpilogue *ep, int n_cus) {
     if (rows <= 0) return hipSuccess;
     const GemmGroups none{};
     const bool has_ep = ep && ep->kind != GemmEpilogue::NONE;
@@ -379,11 +379,11 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
         if (has_ep) tail_ep = epilogue_at(*ep, dtype, head, N);
         hipError_t et = launch_gemm(dtype, (const bf16_t *)X + (size_t)head * ldx, ldx, W, R ? (const bf16_t *)R + (size_t)head * N : nullptr,
                                     (bf16_t *)Y + (size_t)head * N, partial ? partial + (size_t)head * N : nullptr, plane_stride,
-                                    p.tail_rows, N, K, s, nullptr, has_ep ? &tail_ep : nullptr);
+                                    p.tail_rows, N, K, s, nullptr, has_ep ? &tail_ep : nullptr, n_cus);
         if (et != hipSuccess) return et;
         rows = head;
     }
-    if (gemm_rows16_supported(rows, N, K, p.split) || gemm_rows16_wide_supported(rows, N, K, p.split)) {
+    if (gemm_rows16_taken(rows, N, K, p.split, n_cus, has_ep && ep->kind == GemmEpilogue::NORM)) {
         const bool rope = has_ep && ep->kind == GemmEpilogue::ROPE && !R && gemm_rows16_rope_supported(*ep->shape);
         hipError_t er = launch_gemm_rows16(s, X, ldx, W, R, Y, rows, N, K, p.split, rope ? ep : nullptr);
         if (er == hipSuccess && mid) er = hipEventRecord(mid, s);

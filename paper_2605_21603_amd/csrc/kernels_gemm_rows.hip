@@ -167,17 +167,26 @@ __global__ __launch_bounds__(64 * S) void gemm_rows16_kernel(const bf16_t *__res
     *reinterpret_cast<uint2 *>(Y + at) = ov;
 }
 
-// Where the kernel is taken with 8 X rows a stage.  The line was drawn with loads straight into MFMA layout, when every row of
-// X cost (microseconds saved by one projection inside a step
-// of one layer / of three (whose weights leave the caches in between), 14 layer widths:
-//   at most 256 workgroups, 2 or 4 planes: 1, 4, 8 rows x 2560 x 6912 2.7/3.6, 4.3/2.5, 2.9/2.1, x 3072 x 3072 2.3/3.2, 1.8/2.7, 1.8/2.0,
-//     x 4096 x 11008 4.8/4.5, 5.6/5.4, 4.1/5.0, the least x 2048 x 2048 0/1.6, 0.7/1.2, 0.3/0.9
-//   at most 256, 8 planes: 1, 4, 6, 8 rows x 4096 x 4096 1.9/1.7, 1.2/2.2, 1.7/2.1, 1.8/1.4, x 4096 x 14336 1.8/1.7, 1.1/0.2, 1.5/0, 0.2/-1.5,
-//     x 3072 x 8192 1.5/1.1, 0.5/-0.1, 0.6/0, -0.3/-1.5, x 2048 x 5632 2.0/1.2, 0.8/0.2, 1.6/-0.8, 0.8/-1.2
-//   257 to 511: 1, 2, 4 rows x 6144 x 4096 2.7/-0.5, 2.5/-0.5, 0.2/-1.7, x 5120 x 5120 3.4/1.5, 0.6/2.0, 0.5/0.1, x 5120 x 3072 -0.2/-0.1, -0.1/0,
-//     -1.2/-0.9, x 4608 x 3584 -0.6/-0.6, -1.6/-1.6, -1.4/-1.1; with long K x 5120 x 13824 0.5/-1.1, -2.0/-1.6, -3.7/-3.5
-//   512 and more: three layers, 1, 5, 8 rows x 8192 x 8192 3.2, 2.8, 3.0, x 10240 x 8192 12, 11, 10, x 8192 x 28672 4.5, 2.3, -7.2, x 8192 x 6144
-//     1.3, 0.1, -1.5; with 2 planes x 12288 x 4096 -0.3, 0, -1.4
+// Where the kernel is taken on the whole chip.  Every workgroup reads all of X for its 16 W rows, so
+// with workgroups that are more than the CUs but do not fill them twice the CUs with two set the pace, and two planes of a large
+// matrix do not save what that costs.  A layer's step, planes summed by a launch of their own -> in the
+// workgroup, us a layer:
+//   at most 256 workgroups, or 512 and more: 4096 wide, 14336 MLP, 9 / 13 / 16 rows 117.0 / 119.0 / 117.6 -> 112.5 / 114.3 / 117.2; 3072 x 8192
+//     83.3 / 83.8 / 84.6 -> 75.9 / 79.3 / 83.2; 2048 x 5632 65.1 / 66.0 / 66.4 -> 56.3 / 57.7 / 58.9; 3584 x 18944 140.3 / 141.6 / 142.1 -> 136.4 / 139.0
+//     / 142.6; 8192 x 28672 359 / 355 / 361 -> 339 / 345 / 351; two planes of 16384 x 2048 (2048 wide, 64-wide heads) 66.7 / 67.5 / 68.9 -> 60.7 / 62.0 / 64.5
+//   257 to 511: 5120 x 13824 1 / 4 / 8 / 13 rows 156.8 / 160.5 / 164.0 / 168.6 -> 155.7 / 158.0 / 164.9 / 175.6; 6144 x 16384 209.7 / 214.2 / 215.6 /
+//     217.9 -> 208.4 / 212.8 / 217.0 / 223.6; two planes of 15360 x 5120, in the first of these from 13 rows on: 168.6 -> 173.4
+// The limit of 6 rows was drawn before the rotary form, which saves a launch more; with it, planes -> workgroup at 7 / 9 / 13 / 16 rows: 4096 wide (qkv
+// 6144 x 4096) 124.6 / 125.6 / 129.5 / 130.8 -> 119.0 / 119.8 / 124.7 / 127.1, 5120 x 13824 158.7 / 159.7 / 163.0 / 164.2 -> 149.9 / 153.6 / 160.8 / 164.7,
+// 6144 x 16384 214.8 / 216.0 / 220.3 / 222.0 -> 214.9 / 219.4 / 226.7 / 231.2.
+bool gemm_rows16_wide_supported(int rows, int N, int K, int S) {
+    if (S != 2 && S != 4 && S != 8) return false;
+    const int wg = N / 16;
+    const bool all = wg <= 256 || (wg >= 512 && (S > 2 || (size_t)N * K <= (size_t)48 << 20));
+    return rows <= (all ? 16 : 6);
+}
+
+// Where it is taken on any number of CUs: the shapes with the fewest X bytes beside their weights.  (A part of the above.)
 bool gemm_rows16_supported(int rows, int N, int K, int S) {
     if (rows > 8 || (S != 2 && S != 4 && S != 8)) return false;
     const int wg = N / 16;
@@ -185,20 +194,20 @@ bool gemm_rows16_supported(int rows, int N, int K, int S) {
     return wg < 512 ? rows <= 2 && K < 2 * N : S > 2 && rows <= 5;
 }
 
-// Where the kernel is taken with 16 X rows a stage: the rest up to 16 rows.  Every workgroup reads all of X for its 16 W rows, so
-// with workgroups that are more than the CUs but do not fill them twice the CUs with two set the pace, and two planes of a large
-// matrix do not save what that costs.  A layer's step, planes summed by a launch of their own beyond the line above -> in the
-// workgroup throughout, us a layer:
-//   at most 256 workgroups, or 512 and more: 4096 wide, 14336 MLP, 9 / 13 / 16 rows 117.0 / 119.0 / 117.6 -> 112.5 / 114.3 / 117.2; 3072 x 8192
-//     83.3 / 83.8 / 84.6 -> 75.9 / 79.3 / 83.2; 2048 x 5632 65.1 / 66.0 / 66.4 -> 56.3 / 57.7 / 58.9; 3584 x 18944 140.3 / 141.6 / 142.1 -> 136.4 / 139.0
-//     / 142.6; 8192 x 28672 359 / 355 / 361 -> 339 / 345 / 351; two planes of 16384 x 2048 (2048 wide, 64-wide heads) 66.7 / 67.5 / 68.9 -> 60.7 / 62.0 / 64.5
-//   257 to 511: 5120 x 13824 1 / 4 / 8 / 13 rows 156.8 / 160.5 / 164.0 / 168.6 -> 155.7 / 158.0 / 164.9 / 175.6; 6144 x 16384 209.7 / 214.2 / 215.6 /
-//     217.9 -> 208.4 / 212.8 / 217.0 / 223.6; two planes of 15360 x 5120, in the first of these from 13 rows on: 168.6 -> 173.4
-bool gemm_rows16_wide_supported(int rows, int N, int K, int S) {
-    if (S != 2 && S != 4 && S != 8) return false;
-    const int wg = N / 16;
-    const bool all = wg <= 256 || (wg >= 512 && (S > 2 || (size_t)N * K <= (size_t)48 << 20));
-    return rows <= (all ? 16 : 6);
+// On a partition what a CU gets from its cache bounds the launch rather than memory, and 16 X rows beside 16 W rows are as much again as the
+// weights.  The operator, planes summed by a launch of their own -> in the workgroup, us on 64 / 128 / 192 CUs:
+//   up to 4 rows: 1 row x 6144 x 4096 43/36/30 -> 37/29/28, x 4096 x 14336 71/51/52 -> 67/48/49, x 8192 x 28672 192/120/122 -> 180/114/101, 4 rows
+//     193/121/122 -> 201/124/106
+//   8 rows, K < 2 N: x 8192 x 8192 83/61/63 -> 84/60/55; longer: x 3072 x 8192 46/39/33 -> 38/33/29, x 4096 x 14336 73/52/52 -> 79/54/53, x 8192 x 28672
+//     196/122/124 -> 227/139/116
+//   16 rows: x 3584 x 2560 31/27/27 -> 28/23/23, x 3072 x 8192 46/40/34 -> 42/35/30, x 16384 x 3072 (gate/up) 64/46/45 -> 59/44/42, x 4096 x 14336
+//     74/53/53 -> 92/61/60, x 10240 x 8192 92/68/60 -> 115/72/63; where a norm follows, which the launch that sums planes applies too:
+//     x 3072 x 3072 36/31/31 -> 34/31/29, x 3584 x 3584 39/33/33 -> 42/35/34, x 4096 x 4096 45/36/37 -> 49/37/38
+bool gemm_rows16_taken(int rows, int N, int K, int S, int n_cus, bool norm) {
+    if (!gemm_rows16_wide_supported(rows, N, K, S)) return false;
+    if (n_cus <= 0 || n_cus >= 256 || rows <= 4 || gemm_rows16_supported(rows, N, K, S)) return true;
+    if (rows <= 8 && K < 2 * N) return true;
+    return (size_t)N * K <= (size_t)(rows > 8 && norm ? 10 : 48) << 20;
 }
 
 // The rotary form: halves of a head in whole eights, and a head's columns in one group of the stage order.
@@ -224,7 +233,9 @@ hipError_t launch_rows(hipStream_t s, const void *X, int ldx, const void *W, con
 
 template <class EP>
 hipError_t launch_rows_of(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int S, const EP &ep) {
-    if (gemm_rows16_supported(rows, N, K, S))              // at most 8 rows
+    // 8 X rows a stage wherever they are enough: 16 for 6 rows cost 0 to 1 % of a layer's step (5120 wide 141.6 -> 142.5 us a layer), on 64
+    // CUs more, with fewer workgroups a CU (2 rows of 3072 wide 111.4 -> 115.8, of 2048 wide 94 -> 103)
+    if (rows <= 8)
         return S == 8   ? launch_rows<8, 8>(s, X, ldx, W, R, Y, rows, N, K, ep)
                : S == 4 ? launch_rows<4, 8>(s, X, ldx, W, R, Y, rows, N, K, ep)
                         : launch_rows<2, 8>(s, X, ldx, W, R, Y, rows, N, K, ep);

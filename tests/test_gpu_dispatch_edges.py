@@ -90,6 +90,27 @@ def test_up_to_16_rows_match_the_bits_of_larger_launches(hidden, n_q, n_kv, hd, 
     check_against_oracle(w, data, y, k, v)
 
 
+# The same kernel on a partition of the CUs, which large projections of 5 rows and more and those that a norm follows leave earlier than on the whole
+# chip: both forms give the whole chip's bits.
+@pytest.mark.parametrize("hidden,inter,rows,on_all,on_part", [
+    (4096, 14336, 16, 0b110, 0b000), (4096, 14336, 8, 0b110, 0b010), (4096, 14336, 4, 0b111, 0b111), (3072, 8192, 16, 0b111, 0b111), (3584, 4096, 9, 0b110, 0b100)])
+def test_few_rows_on_a_partition(hidden, inter, rows, on_all, on_part):
+    taken = B.lib()._ZN3dyn17gemm_rows16_takenEiiiiib
+    shapes = ((hidden + 1024, hidden, False), (hidden, hidden, True), (hidden, inter, False))       # qkv, o (its norm follows), down
+
+    def forms(n_cus):
+        return sum((taken(rows, N, K, gemm_path(rows, N, K).split, n_cus, norm) & 0xff != 0) << i for i, (N, K, norm) in enumerate(shapes))
+    assert forms(0) == forms(256) == on_all and forms(64) == forms(192) == on_part
+    w = workload("part_rows", "bf16", hidden, hidden // 128, 4, 128, inter, [(1, 1 + (i * 31) % 300) for i in range(rows)], seed=97)
+    data = gen.generate(w)
+    run = GpuRun(w, data)
+    whole = run.run(B.sequential())
+    for mask in (0xff, 0xffffff):
+        part = run.run(B.nano_schedule([0, rows], chain=B.DENSE_CHAIN, partitions=[1], cu_masks=[[mask] * 8]))
+        for a, b in zip(whole, part):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
 # The gate applied by the launch that sums a gate/up projection's planes (or, up to 16 rows, reading what the rows' kernel left in the
 # plane buffer) gives the bits of the gate as a launch of its own, which stays where a micro-batch folds its planes in registers:
 # 2 and 4 planes (4 from a depth of 2048 on), parts of a batch on either side of the folded path.
