@@ -107,12 +107,12 @@ __device__ __forceinline__ bool band_tile(int nt, int m_tiles, int band, int &n_
 
 // The tile of W rows [n_tile * BN, + BN) and X rows [m0, m0 + MT) (below M) over plane sp of S (INREG: all
 // planes in turn).  list: X and output rows are list[row] (the X row list[row] / x_div) instead of row.
-// planes_only: the plane's fp32 sums go to P whatever S is.  lds: NS * (BN + MT) * ROWB bytes, 1024-byte aligned.
+// planes_only: the plane's fp32 sums go to P whatever S is.  expert: whose weights W are (0: not grouped).  lds: NS * (BN + MT) * ROWB bytes, 1024-byte aligned.
 template <int BN, int MT, bool INREG, int NS, bool GATED, int NW, bool PIPE>
 __device__ __forceinline__ void gemm_tile(unsigned char *lds, const bf16_t *__restrict__ X, int ldx, const bf16_t *__restrict__ W,
                                           const bf16_t *__restrict__ R, bf16_t *__restrict__ Y, int ldy, float *__restrict__ P,
                                           size_t plane_stride, int M, int N, int K, int S, const int32_t *list, int x_div,
-                                          bool planes_only, int n_tile, int sp, int m0, int expert = 0) {
+                                          bool planes_only, int n_tile, int sp, int m0, int expert) {
     constexpr int ROWS = BN + MT;                   // rows of a stage buffer: W rows, then X rows
     constexpr int WMW = (NW == 8 && BN < MT) ? 4 : 2;   // waves along m
     constexpr int WNW = NW / WMW, RW = BN / WNW;     // waves along n; W rows per wave column
@@ -149,7 +149,7 @@ __device__ __forceinline__ void gemm_tile(unsigned char *lds, const bf16_t *__re
     // with rot a function of the n tile (groups of kRotGroup tiles share one).  Workgroups that run
     // at the same time then read different column offsets of their 8 KB-pitched weight rows, which
     // spreads the requests over the memory channels; tiles of one group keep reading the same X
-    // columns together, so X stays shared in L2.  The order depends on (N, K, n tile) only, never
+    // columns together, so X stays shared in L2.  The order depends on (N, K, n tile, expert) only, never
     // on the number of rows, so every schedule adds the same terms in the same order.  Experts rotate one
     // against the next: a down projection's 32 n tiles are one group, and all 256 workgroups of eight experts'
     // read the same columns of rows 28 KB apart (8 experts x 4096 x 14336, two of them per token: 4, 32, 128 tokens 142 -> 128,

@@ -16,7 +16,7 @@ __global__ __launch_bounds__(512, 1) void gemm_fold_kernel(const bf16_t *__restr
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     int n_tile, m_tile;
     if (!band_tile(N / 256, (M + 127) / 128, gemm_band(M, N, K), n_tile, m_tile)) return;
-    gemm_tile<256, 128, true, 3, false, 8, true>(lds, X, ldx, W, R, Y, N, nullptr, 0, M, N, K, S, nullptr, 1, false, n_tile, 0, m_tile * 128);
+    gemm_tile<256, 128, true, 3, false, 8, true>(lds, X, ldx, W, R, Y, N, nullptr, 0, M, N, K, S, nullptr, 1, false, n_tile, 0, m_tile * 128, 0);
 }
 
 hipError_t launch_gemm_fold(int grid, hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N,
