@@ -155,7 +155,8 @@ Sizes tensor_sizes(const dyn_layer *L, int T, int max_pages, bool prompts) {
     z.qkv = t * qkv_width(c) * e;
     z.attn = t * z.ld_attn * e;
     z.x2 = t * c.hidden * e;
-    // the [gate | up] intermediate exists only when the SiLU gate is not applied in the projection's epilogue
+    // The [gate | up] intermediate: none where the SiLU gate is applied in the projection's epilogue for any number of rows; else an
+    // upper bound, which a plan whose planes' sums apply the gate leaves unused (plan_gated).
     z.gu = dyn::gemm_gated_supported(c.dtype, 2 * c.mlp_inter, c.hidden, c.n_experts > 0) ? 0 : t * pairs * 2 * c.mlp_inter * e;
     z.act = t * pairs * z.ld_act * e;
     z.xa = c.n_layers > 1 ? t * c.hidden * e : 0;

@@ -493,9 +493,6 @@ hipError_t launch_f32_any(const void *X, int ldx, const void *W, const void *R, 
 }
 }  // namespace
 
-// The rotary form: tiles of 16 + 16 columns for few rows or few tiles at any depth, and 32 x 32 of whole blocks, where a
-// head's halves have to lie in one group of 64 columns.  225 rows x 1536 x 1024 17.8 + 4.9 us as two launches, 19.3 in one; 4 rows x 768 x
-// 256 3.3 + 2.7 -> 4.4 (steps 131.1 -> 128.5, 40.5 -> 39.2 us).
 hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const void *R, void *Y, int max_rows, int N, int K,
                            const GemmGroups &gr, hipStream_t s) {
     if (!gr.n_groups && f32_whole(N, K)) return launch_f32_whole(X, ldx, W, R, Y, max_rows, N, K, F32Plain{}, s);
@@ -512,6 +509,9 @@ hipError_t launch_gemm_f32_gated(const void *X, int ldx, const void *W, void *Y,
     return launch_f32_whole(X, ldx, W, nullptr, Y, rows, N2, K, F32Gated{ldy}, s);
 }
 
+// The rotary form: tiles of 16 + 16 columns for few rows or few tiles at any depth, and 32 x 32 of whole blocks, where a
+// head's halves have to lie in one group of 64 columns.  225 rows x 1536 x 1024 17.8 + 4.9 us as two launches, 19.3 in one; 4 rows x 768 x
+// 256 3.3 + 2.7 -> 4.4 (steps 131.1 -> 128.5, 40.5 -> 39.2 us).
 bool gemm_f32_rope_supported(const void *X, int ldx, const void *W, int rows, int N, int K, const AttnShape &sh) {
     if (sh.head_dim % 32 || sh.head_dim > 2 * kMaxHalfDim) return false;
     if (!f32_whole(N, K)) return f32_few(rows, N, false);
