@@ -39,6 +39,22 @@ def test_tile_attention_lists_every_item_once(dtype, n_q, n_kv, hd, page, seqs):
     say("%d rows: %.2e" % (w.n_tokens, check_against_oracle(w, data, y, k, v)))
 
 
+# An infinity among the cached values, in a tile that every column sees whole: its sequence's output rows are NaN (the norm behind the
+# attention makes them so, whether the attention gave an infinity or NaN), every other row keeps its bits.
+@pytest.mark.parametrize("dtype,hd,page", [("bf16", 64, 16), ("bf16", 128, 32), ("f32", 64, 16)])
+def test_an_infinite_cached_value_stays_in_its_sequence(dtype, hd, page):
+    w = workload("inf", dtype, 256, 4, 2, hd, 128, [(40, 300), (1, 200), (1, 500), (20, 90), (1, 40)], page=page, seed=78)
+    data = gen.generate(w)
+    clean, _, _ = both_schedules(w, data)
+    rows = torch.arange(w.n_tokens)
+    hit = (rows < 40) | (rows == 41)
+    for s in (0, 2):
+        data["v_cache"][0][data["block_table"][s, 100 // page], 1, 5, 100 % page] = float("inf")
+    y, _, _ = both_schedules(w, data)
+    assert torch.isnan(y[hit].float()).all()
+    assert torch.equal(y[~hit], clean[~hit]) and torch.isfinite(clean.float()).all()
+
+
 # fp32 projections of whole 64-deep blocks: 16 x 16, 32 x 32 and 64 x 64 tiles and their edges, one and several blocks a chain
 # (depths 512, 1024, 2048 and 4608; odd and even counts), widths that fill no 64-, 32- or 16-wide tile; 1030 and 516 are depths of
 # the other form.  The second micro-batch takes other tiles than the whole.
