@@ -33,7 +33,7 @@ def gemm_path(rows, N, K):
 
 
 def planes_in_workgroup(rows, N, K):
-    """Whether the library sums a bf16 projection's planes inside the workgroup."""
+    """Whether the library sums a bf16 projection's planes inside the workgroup on any number of CUs (on all of them it does for more shapes)."""
     return B.lib()._ZN3dyn21gemm_rows16_supportedEiiii(rows, N, K, gemm_path(rows, N, K).split) & 0xff != 0
 
 

@@ -88,7 +88,7 @@ def test_fp32_projections_take_weights_at_any_float():
     assert torch.equal(y0, y1)
 
 
-# planes summed inside the workgroup with 16 X rows a stage: 2, 4 and 8 planes of 8, 12, 15, 16, 19 and 28 stages (four on their
+# planes summed inside the workgroup with 16 X rows a stage (6 and 7 rows: 8): 2, 4 and 8 planes of 8, 12, 15, 16, 19 and 28 stages (four on their
 # way), up to the last row it is taken for (16; 6 with 257..511 workgroups; two planes of a wide gate/up projection), against the bits of 21 and
 # of the remaining rows in other launches
 @pytest.mark.parametrize("hidden,n_q,n_kv,hd,inter,rows,reached", [

@@ -210,8 +210,8 @@ def test_general_attention_with_chunks_longer_than_its_scores(dtype, hd, page, c
     say("%s %d %d: %.2e" % (dtype, hd, chunk, check_against_oracle(w, data, y, k, v)))
 
 
-# planes summed inside the workgroup (8 rows at most): 2, 4 and 8 planes of 8 (the fewest there are), 12, 15, 16 and 19 stages; loads
-# run 8 stages ahead.  Of the three projections some leave the kernel earlier: 8 long planes behind 6 rows, 320 workgroups behind 2
+# planes summed inside the workgroup with 8 X rows a stage (9 rows: 16): 2, 4 and 8 planes of 8 (the fewest there are), 12, 15, 16 and 19 stages.
+# `reached` counts the projections of the three that take it on any number of CUs: 8 long planes up to 6 rows, 320 workgroups up to 2
 @pytest.mark.parametrize("hidden,n_q,n_kv,hd,inter,rows,reached", [
     (1024, 16, 4, 64, 3072, 1, 3), (1024, 16, 4, 64, 3072, 7, 3), (1024, 16, 4, 64, 3072, 8, 3), (1024, 16, 4, 64, 3072, 9, 0),
     (2048, 16, 4, 128, 7680, 1, 3), (2048, 16, 4, 128, 7680, 6, 3), (2048, 16, 4, 128, 7680, 7, 2), (3072, 24, 8, 128, 8192, 2, 3),
