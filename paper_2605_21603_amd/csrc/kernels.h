@@ -112,6 +112,9 @@ hipError_t launch_gemm_fold(int grid, hipStream_t s, const void *X, int ldx, con
 // call it); gated: silu(gate) * up to Y, else Y, or fp32 to P with gr.force_planes.
 hipError_t launch_gemm_experts_wide(bool gated, hipStream_t s, const void *X, int ldx, const void *W, void *Y, int ldy, float *P, int N,
                                     int K, const GemmGroups &gr);
+// The same on 128-wide tiles, with or without planes (plane p of S at P + p * plane_stride where there are several or gr.force_planes).
+hipError_t launch_gemm_experts(bool gated, hipStream_t s, const void *X, int ldx, const void *W, void *Y, int ldy, float *P, size_t plane_stride,
+                               int max_rows, int N, int K, int S, const GemmGroups &gr);
 
 hipError_t launch_gemm_grouped(int dtype, const void *X, int ldx, const void *W, void *Y, float *partial,
                                size_t plane_stride, const GemmGroups &gr, int max_rows, int row0, int n_rows, int N, int K,

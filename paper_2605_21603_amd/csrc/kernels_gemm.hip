@@ -21,14 +21,13 @@ constexpr int kBigBN = 128, kBigMT = 128, kBigNS = 2;   // tile and ring depth o
 
 // The tiles that only GEMM_WIDE and GEMM_MANY launches use walk their tiles in bands; the others spread planes over
 // the grid in n-tile order.  (Decided at compile time: as an argument it cost one token's step under 1 %, 128 rows' nothing
-// that could be measured.)  Expert-grouped launches use none of the banded tiles.
+// that could be measured.)
 constexpr bool gemm_in_bands(int bn, int nw) { return bn == 256 || nw == 4; }
 
 template <int BN, int MT, bool INREG, int NS, bool GATED, int NW>
 __global__ __launch_bounds__(NW * 64, (NW == 4 && (BN + MT) * ROWB * NS <= 72 * 1024) ? 2 : 1) void gemm_bf16_kernel(
     const bf16_t *__restrict__ X, int ldx, const bf16_t *__restrict__ W, const bf16_t *__restrict__ R,
-    bf16_t *__restrict__ Y, int ldy, float *__restrict__ P, size_t plane_stride, int M, int N, int K, int S,
-    GemmGroups gr) {
+    bf16_t *__restrict__ Y, int ldy, float *__restrict__ P, size_t plane_stride, int M, int N, int K, int S) {
     constexpr bool BANDS = gemm_in_bands(BN, NW);      // whole-depth tiles of a many-row launch
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     const int m_tiles = (M + MT - 1) / MT;
@@ -43,41 +42,16 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && (BN + MT) * ROWB * NS <= 72 * 
         m_tile = v % m_tiles;
         ns = (v / m_tiles) * 8 + u;
     }
-    const bool grouped = !BANDS && gr.n_groups;
-    if (grouped) {
-        // Expert-grouped launches size the grid for the largest possible group, so most tiles
-        // past the first m tile are empty.  All first m tiles come first and the mostly empty
-        // ones trail the launch (interleaved, every second workgroup was an empty one that
-        // still had to wait for a free 128 KB LDS slot, and the launch took twice as long);
-        // an m tile keeps the XCD of its n tile.
-        const int per_m = gridDim.x / m_tiles;         // a multiple of 8
-        m_tile = blockIdx.x / per_m;
-        ns = blockIdx.x % per_m;
-    }
-    const int32_t *list = nullptr;
-    int expert = 0;
     const int SG = INREG ? 1 : S;                      // planes spread over the grid
-    if (grouped) {                                     // (expert, n tile, plane); rows come from the expert's list
-        const int per_group = (N / BN) * SG;
-        if (ns >= per_group * gr.n_groups) return;
-        expert = ns / per_group;
-        ns -= expert * per_group;
-        M = gr.counts[expert];
-        if (m_tile * MT >= M) return;
-        list = gr.lists + (size_t)expert * gr.cap;
-        W += (size_t)expert * gr.w_stride;
-    } else if (ns >= (N / BN) * SG) {
-        return;
-    }
-    gemm_tile<BN, MT, INREG, NS, GATED, NW, (MT >= 256)>(lds, X, ldx, W, R, Y, ldy, P, plane_stride, M, N, K, S, list, gr.x_div, gr.force_planes,
-                                                         ns / SG, ns % SG, m_tile * MT, expert);   // the hand-laid-out loop pays from 256-row tiles on
+    if (!BANDS && ns >= (N / BN) * SG) return;
+    gemm_tile<BN, MT, INREG, NS, GATED, NW, (MT >= 256)>(lds, X, ldx, W, R, Y, ldy, P, plane_stride, M, N, K, S, nullptr, 1, false,
+                                                         ns / SG, ns % SG, m_tile * MT, 0);   // the hand-laid-out loop pays from 256-row tiles on
                                                                                            // (128 x 128 tiles: 1-2 % slower with it)
 }
 
 template <int BN, int MT, bool INREG, int NS, bool GATED = false, int NW = 4>
 hipError_t launch_gemm_bf16(int grid, hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y,
-                            float *partial, size_t plane_stride, int rows, int N, int K, int S, const GemmGroups &gr,
-                            int ldy = 0) {
+                            float *partial, size_t plane_stride, int rows, int N, int K, int S, int ldy = 0) {
     constexpr int STAGE = (BN + MT) * ROWB;
     static_assert(NS >= 2 && NS <= 6 && NS * STAGE <= 160 * 1024, "ring does not fit in LDS");
     static bool attr_set = false;                      // above 64 KB of dynamic LDS needs an opt-in, once
@@ -89,7 +63,7 @@ hipError_t launch_gemm_bf16(int grid, hipStream_t s, const void *X, int ldx, con
     }
     hipLaunchKernelGGL((gemm_bf16_kernel<BN, MT, INREG, NS, GATED, NW>), dim3(grid), dim3(NW * 64), NS * STAGE, s,
                        (const bf16_t *)X, ldx, (const bf16_t *)W, (const bf16_t *)R, (bf16_t *)Y, ldy ? ldy : N, partial,
-                       plane_stride, rows, N, K, S, gr);
+                       plane_stride, rows, N, K, S);
     return hipGetLastError();
 }
 
@@ -394,7 +368,7 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
     // workgroup ids are dealt to the 8 XCDs in turn: tiles, or (n tile, plane) pairs, are padded to a multiple of 8
     const int grid = p.kind == GEMM_WIDE || p.kind == GEMM_MANY ? gemm_band_grid(N / p.bn, m_tiles) : (((N / p.bn) * (p.folded ? 1 : S) + 7) / 8) * 8 * m_tiles;
 #define DYN_GEMM(BN, MT, INREG, NS, NW) \
-    launch_gemm_bf16<BN, MT, INREG, NS, false, NW>(grid, s, X, ldx, W, R, Y, partial, plane_stride, rows, N, K, S, none)
+    launch_gemm_bf16<BN, MT, INREG, NS, false, NW>(grid, s, X, ldx, W, R, Y, partial, plane_stride, rows, N, K, S)
     hipError_t e;
     if (p.kind == GEMM_TALL) e = p.mt == 256 ? DYN_GEMM(128, 256, false, 3, 8) : p.mt == 384 ? DYN_GEMM(128, 384, false, 2, 8) : DYN_GEMM(128, 512, false, 2, 8);
     else if (p.kind == GEMM_WIDE) e = DYN_GEMM(256, 256, false, 2, 8);
@@ -423,21 +397,10 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
 }
 
 namespace {
-// Tile of an expert-grouped launch, from the average number of rows per group (the lists' capacity
-// holds every row once).  Few rows per expert stream the weights through 128-row tiles; from about
-// 100 rows a second 128-row tile per expert would move its weights into LDS again, so the tile
-// grows with the rows: one 256-row tall tile up to about 200 rows, 256 x 256 tiles beyond (eight
-// experts' gate/up at 512 / 1024 / 2048 tokens: 593 / 989 / 1847 us with 128-row tiles).  Both lines were drawn with
-// 256-row tiles of one height; gemm_experts_wide_kernel, which fits the height to each expert, was not timed below 200.  The
-// grid still covers max_rows per group; tiles past a group's count exit at once.
-struct GroupTile { int bn, mt; };
-GroupTile gemm_group_tile(const GemmGroups &gr, int max_rows, int N) {
-    if (max_rows <= 64) return {128, 64};
-    const int avg = gr.cap / (gr.n_groups > 0 ? gr.n_groups : 1);
-    if (avg <= 100 || max_rows <= 128) return {128, 128};
-    if (avg <= 200 || N % 256) return {128, 256};
-    return {256, 256};
-}
+// Whether an expert-grouped launch is on 256-wide tiles, from the average number of rows per group (the lists' capacity holds every row
+// once).  To about 200 rows per expert the weight stream is the bound; beyond, a 256 x 256 tile's half the operand bytes per FLOP are
+// (eight experts' gate/up at 1024 / 2048 tokens: 989 / 1847 us with 128-row tiles, 751 / 1231).  The 256-wide tile has no planes.
+bool gemm_experts_on_wide(const GemmGroups &gr, int N, int S) { return S == 1 && N % 256 == 0 && gr.cap / std::max(gr.n_groups, 1) > 200; }
 }  // namespace
 
 bool gemm_gated_supported(int dtype, int N2, int K, bool experts) {
@@ -455,13 +418,10 @@ hipError_t launch_gemm_gated(int dtype, const void *X, int ldx, const void *W, v
         return e == hipSuccess && mid ? hipEventRecord(mid, s) : e;
     }
 #define DYN_GATED(BN, MT, NS, NW) \
-    launch_gemm_bf16<BN, MT, false, NS, true, NW>(grid, s, X, ldx, W, nullptr, Y, nullptr, 0, max_rows, N2, K, 1, gr, ldy)
-    const GroupTile t = gemm_group_tile(gr, max_rows, N2);
-    if (gr.n_groups && t.bn == 256) {
-        e = launch_gemm_experts_wide(true, s, X, ldx, W, Y, ldy, nullptr, N2, K, gr);
-    } else if (gr.n_groups) {
-        const int grid = ((((N2 / t.bn) * gr.n_groups) + 7) / 8) * 8 * ((max_rows + t.mt - 1) / t.mt);
-        e = t.mt == 256 ? DYN_GATED(128, 256, 3, 8) : t.mt == 64 ? DYN_GATED(128, 64, 4, 8) : DYN_GATED(128, 128, 4, 8);
+    launch_gemm_bf16<BN, MT, false, NS, true, NW>(grid, s, X, ldx, W, nullptr, Y, nullptr, 0, max_rows, N2, K, 1, ldy)
+    if (gr.n_groups) {
+        e = gemm_experts_on_wide(gr, N2, 1) ? launch_gemm_experts_wide(true, s, X, ldx, W, Y, ldy, nullptr, N2, K, gr)
+                                            : launch_gemm_experts(true, s, X, ldx, W, Y, ldy, nullptr, 0, max_rows, N2, K, 1, gr);
     } else {
         const GemmPath p = gemm_path(1, max_rows, N2, K);          // split factor 1: no planes on any path
         if (p.tail_rows) {     // the last rows in a launch of their own (never a wide one: at most 256 rows)
@@ -500,15 +460,8 @@ hipError_t launch_gemm_grouped(int dtype, const void *X, int ldx, const void *W,
         return e0;
     }
     const int S = gemm_split_k(dtype, N, K, gr.n_groups);
-    GroupTile t = gemm_group_tile(gr, max_rows, N);
-    if (S > 1 && t.bn == 256) t = {128, 256};          // the 256 x 256 tile has no planes
-    const int m_tiles = (max_rows + t.mt - 1) / t.mt;
-    const int ns = (N / t.bn) * S * gr.n_groups;
-    const int grid = ((ns + 7) / 8) * 8 * m_tiles;
-    hipError_t e;
-#define DYN_GROUPED(BN, MT, NS) launch_gemm_bf16<BN, MT, false, NS, false, 8>(grid, s, X, ldx, W, nullptr, Y, partial, plane_stride, max_rows, N, K, S, gr)
-    e = t.bn == 256 ? launch_gemm_experts_wide(false, s, X, ldx, W, Y, N, partial, N, K, gr) : t.mt == 256 ? DYN_GROUPED(128, 256, 3) : t.mt == 64 ? DYN_GROUPED(128, 64, 4) : DYN_GROUPED(128, 128, 4);
-#undef DYN_GROUPED
+    hipError_t e = gemm_experts_on_wide(gr, N, S) ? launch_gemm_experts_wide(false, s, X, ldx, W, Y, N, partial, N, K, gr)
+                                                  : launch_gemm_experts(false, s, X, ldx, W, Y, N, partial, plane_stride, max_rows, N, K, S, gr);
     if (e == hipSuccess && mid) e = hipEventRecord(mid, s);
     if (e != hipSuccess || S == 1 || gr.force_planes) return e;
     // output rows row0 .. row0 + n_rows - 1 are exactly the rows the groups wrote

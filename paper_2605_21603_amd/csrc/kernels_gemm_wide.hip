@@ -49,6 +49,27 @@ hipError_t launch_gemm_fold(int grid, hipStream_t s, const void *X, int ldx, con
 constexpr int kExpertsBN = 256, kXcdCus = 32;
 constexpr int kExpertsLds = 160 * 1024;               // the bodies' rings: 2 x 64, 2 x 56, 3 x 48, 4 x 40 KB
 
+// The m tile at place `m` of the launch order: an expert's rows are cut into as few m tiles of at most `top` 64s as hold them, the experts
+// with the tallest tiles first.  even: an expert's tiles alike, else heights that add up to its rows.  units 0: no tile.  counts: the experts'
+// rows, one a lane.  (A lane works its own expert out and counts the tiles before it; expert by expert in scalar code, with a division
+// each, a workgroup began 2 us later.)
+struct ExpertTile { int units, expert, rows, m0; };
+__device__ __forceinline__ ExpertTile expert_tile(int counts, int n_experts, int m, int top, bool even) {
+    const int lane = threadIdx.x & 63, all = (counts + 63) / 64, n_m = (all + top - 1) / top, each = max(n_m, 1);
+    const int low = even ? ((counts + each - 1) / each + 63) / 64 : all / each, taller = even ? 0 : all - low * each;   // the first `taller` m tiles are 64 rows taller
+    const int size = low + (taller > 0);
+    int start = 0;                                     // m tiles before this expert's
+    for (int e = 0; e < n_experts; ++e) {
+        const int n = __builtin_amdgcn_readlane(n_m, e), sz = __builtin_amdgcn_readlane(size, e);
+        start += sz > size || (sz == size && e < lane) ? n : 0;
+    }
+    const unsigned long long mine = __ballot(m >= start && m < start + n_m);
+    if (!mine) return ExpertTile{0, 0, 0, 0};
+    const int e = __builtin_ctzll(mine), at = m - __builtin_amdgcn_readlane(start, e), rows = __builtin_amdgcn_readlane(counts, e);
+    const int lo = __builtin_amdgcn_readlane(low, e), ta = __builtin_amdgcn_readlane(taller, e), m0 = 64 * (at * lo + min(at, ta));
+    return ExpertTile{m0 < rows ? lo + (at < ta) : 0, e, rows, m0};   // equal tiles of whole 64s may leave the last one empty
+}
+
 template <bool GATED>
 __global__ __launch_bounds__(512, 1) void gemm_experts_wide_kernel(const bf16_t *__restrict__ X, int ldx, const bf16_t *__restrict__ W,
                                                                    bf16_t *__restrict__ Y, int ldy, float *__restrict__ P, int N, int K,
@@ -68,31 +89,16 @@ __global__ __launch_bounds__(512, 1) void gemm_experts_wide_kernel(const bf16_t 
     const int fit = kXcdCus / n_local;
     const int top = n1 <= fit ? 1 : n2 <= fit ? 2 : n3 <= fit ? 3 : 4;
     const bool once = n4 <= fit;                       // one round: as long as its tallest tile, which equal tiles keep low and in step on W
-    int m = v / n_local, e = 0, units = 0, rows = 0, m0 = 0;   // m: place of the m tile in launch order
+    int m = v / n_local;                               // place of the m tile in launch order
     const int n_tile = (v - m * n_local) * 8 + u;
-    bool found = false;
-    for (int size = top; size >= 1 && !found; --size)   // m tiles of 64 * size rows
-        for (e = 0; e < gr.n_groups; ++e) {
-            rows = __builtin_amdgcn_readlane(counts, e);
-            const int all = (rows + 63) / 64, n_m = (all + top - 1) / top;
-            if (n_m == 0) continue;
-            const int low = once ? ((rows + n_m - 1) / n_m + 63) / 64 : all / n_m, taller = once ? 0 : all - low * n_m;   // the first `taller` m tiles are 64 rows taller
-            if (size != low + (taller > 0)) continue;
-            if (m < n_m) {
-                units = low + (m < taller);
-                m0 = 64 * (m * low + min(m, taller));
-                found = true;
-                break;
-            }
-            m -= n_m;
-        }
-    if (!found || m0 >= rows) return;                  // equal tiles of whole 64s may leave the last one empty
-    const int32_t *list = gr.lists + (size_t)e * gr.cap;
-    const bf16_t *We = W + (size_t)e * gr.w_stride;
-#define DYN_BODY(MT, NS) gemm_tile<kExpertsBN, MT, false, NS, GATED, 8, true>(lds, X, ldx, We, nullptr, Y, ldy, P, 0, rows, N, K, 1, list, gr.x_div, gr.force_planes, n_tile, 0, m0, e)
-    if (units == 4) DYN_BODY(256, 2);
-    else if (units == 3) DYN_BODY(192, 2);
-    else if (units == 2) DYN_BODY(128, 3);
+    const ExpertTile t = expert_tile(counts, gr.n_groups, m, top, once);
+    if (!t.units) return;
+    const int32_t *list = gr.lists + (size_t)t.expert * gr.cap;
+    const bf16_t *We = W + (size_t)t.expert * gr.w_stride;
+#define DYN_BODY(MT, NS) gemm_tile<kExpertsBN, MT, false, NS, GATED, 8, true>(lds, X, ldx, We, nullptr, Y, ldy, P, 0, t.rows, N, K, 1, list, gr.x_div, gr.force_planes, n_tile, 0, t.m0, t.expert)
+    if (t.units == 4) DYN_BODY(256, 2);
+    else if (t.units == 3) DYN_BODY(192, 2);
+    else if (t.units == 2) DYN_BODY(128, 3);
     else DYN_BODY(64, 4);
 #undef DYN_BODY
 }
@@ -115,6 +121,66 @@ hipError_t launch_gemm_experts_wide(bool gated, hipStream_t s, const void *X, in
         hipLaunchKernelGGL(gemm_experts_wide_kernel<false>, dim3(grid), dim3(512), kExpertsLds, s, (const bf16_t *)X, ldx, (const bf16_t *)W,
                            (bf16_t *)Y, ldy, P, N, K, gr);
     return hipGetLastError();
+}
+
+// Expert-grouped launch on 128-wide tiles, with or without planes: up to some 200 rows per expert, where the weight stream is the
+// bound.  What stands beside a stage's 128 W rows in LDS are the X rows of the tile, and an expert of 40 rows on a 128-row tile brings in
+// 88 copies of its last row: the tile's height follows the expert's own count here too (64 to 256 rows, as above), and an
+// expert's weights are read once up to 256 rows.  Tallest tiles first, an expert's tiles together; workgroups that share W rows lie a
+// multiple of 8 apart (one XCD).  One height for the launch (64, 128 or 256 rows by the average) -> by the count, steps of 8 experts of 4096 x
+// 14336, two per token: 100 / 200 / 256 / 300 tokens 655 / 752 / 862 / 965 -> 644 / 744 / 855 / 865 us, prompts of 72 / 312 / 512 / 712 rows 609 / 836 /
+// 969 / 1206 -> 596 / 740 / 843 / 1049 us; 64 tokens and fewer are on 64-row tiles either way.
+// FEW: no expert has more than 64 rows, one tile each.
+constexpr int kExpertsRowsLds = 160 * 1024;           // the bodies' rings: 3 x 48, 4 x 40, 4 x 32, 4 x 24 KB; FEW: the last, one workgroup per CU (two, with rings of three: 1 token's down projection 84 -> 102 us)
+
+template <bool GATED, bool FEW>
+__global__ __launch_bounds__(512, 1) void gemm_experts_kernel(const bf16_t *__restrict__ X, int ldx, const bf16_t *__restrict__ W,
+                                                              bf16_t *__restrict__ Y, int ldy, float *__restrict__ P, size_t plane_stride,
+                                                              int N, int K, int S, GemmGroups gr) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    const int pairs = N / 128 * S, per_m = (pairs + 7) / 8 * 8;      // (n tile, plane) pairs of an m tile
+    const int m = blockIdx.x / per_m, ns = blockIdx.x - m * per_m;
+    if (ns >= pairs) return;
+    ExpertTile t{1, m, FEW ? gr.counts[m] : 0, 0};
+    if constexpr (!FEW) t = expert_tile((int)(threadIdx.x & 63) < gr.n_groups ? gr.counts[threadIdx.x & 63] : 0, gr.n_groups, m, 4, false);
+    if (!t.units || !t.rows) return;
+    const int32_t *list = gr.lists + (size_t)t.expert * gr.cap;
+    const bf16_t *We = W + (size_t)t.expert * gr.w_stride;
+#define DYN_BODY(MT, NS) gemm_tile<128, MT, false, NS, GATED, 8, (MT >= 256)>(lds, X, ldx, We, nullptr, Y, ldy, P, plane_stride, t.rows, N, K, S, list, gr.x_div, gr.force_planes, ns / S, ns % S, t.m0, t.expert)
+    if constexpr (FEW) DYN_BODY(64, 4);
+    else if (t.units == 4) DYN_BODY(256, 3);
+    else if (t.units == 3) DYN_BODY(192, 4);
+    else if (t.units == 2) DYN_BODY(128, 4);
+    else DYN_BODY(64, 4);
+#undef DYN_BODY
+}
+
+namespace {
+template <bool GATED, bool FEW>
+hipError_t launch_experts(hipStream_t s, const void *X, int ldx, const void *W, void *Y, int ldy, float *P, size_t plane_stride, int N, int K, int S,
+                          const GemmGroups &gr) {
+    constexpr int LDS = FEW ? 4 * (128 + 64) * ROWB : kExpertsRowsLds;
+    static bool attr_set = false;
+    if (!attr_set) {
+        const hipError_t e = hipFuncSetAttribute((const void *)gemm_experts_kernel<GATED, FEW>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    const int m_tiles = FEW ? gr.n_groups : gr.cap / 256 + gr.n_groups;   // at most one m tile of fewer than 256 rows per expert beyond whole ones
+    const int grid = (N / 128 * S + 7) / 8 * 8 * m_tiles;
+    hipLaunchKernelGGL((gemm_experts_kernel<GATED, FEW>), dim3(grid), dim3(512), LDS, s, (const bf16_t *)X, ldx, (const bf16_t *)W, (bf16_t *)Y, ldy, P,
+                       plane_stride, N, K, S, gr);
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_gemm_experts(bool gated, hipStream_t s, const void *X, int ldx, const void *W, void *Y, int ldy, float *P, size_t plane_stride,
+                               int max_rows, int N, int K, int S, const GemmGroups &gr) {
+    if (max_rows <= 64)
+        return gated ? launch_experts<true, true>(s, X, ldx, W, Y, ldy, P, plane_stride, N, K, S, gr)
+                     : launch_experts<false, true>(s, X, ldx, W, Y, ldy, P, plane_stride, N, K, S, gr);
+    return gated ? launch_experts<true, false>(s, X, ldx, W, Y, ldy, P, plane_stride, N, K, S, gr)
+                 : launch_experts<false, false>(s, X, ldx, W, Y, ldy, P, plane_stride, N, K, S, gr);
 }
 
 }  // namespace dyn

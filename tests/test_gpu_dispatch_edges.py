@@ -181,6 +181,22 @@ def test_expert_tiles_in_one_round_and_in_several(inter, tokens, pull):
     say("%d tokens: %.2e" % (tokens, check_against_oracle(w, data, y, k, v)))
 
 
+# Up to 200 rows per expert on average: 128-wide tiles of 64 to 256 rows by the expert's own count, without planes (512 deep) and with (1024), an
+# expert of several tiles, one without rows; 64 tokens, and the smaller micro-batches, on 64-row tiles throughout.
+@pytest.mark.parametrize("hidden,tokens,pull", [(512, 64, 0.0), (512, 130, 3.0), (512, 260, 1.0), (1024, 66, 0.0), (1024, 390, 2.0), (1024, 399, 0.5)])
+def test_expert_tiles_of_few_rows_follow_the_counts(hidden, tokens, pull):
+    w = workload("counts", "bf16", hidden, 4, 1, 128, 512, [(1, 1 + i % 5) for i in range(tokens)], experts=4, top_k=2, seed=90 + tokens)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, tokens // 3, tokens))
+    data = gen.generate(w)
+    router = data["weights"][0]["w_router"]
+    router[2] = -router[0]                                   # tokens pulled towards expert 0 never choose expert 2
+    x = data["x"].float()
+    x += pull * hidden ** 0.5 * router[0] / router[0].norm() * torch.rand(tokens, 1, generator=torch.Generator().manual_seed(3)) ** 0.5
+    data["x"] = x.to(torch.bfloat16)
+    y, k, v = both_schedules(w, data)
+    say("%d tokens: %.2e" % (tokens, check_against_oracle(w, data, y, k, v)))
+
+
 # The same inside the fp32 projection: tiles of any depth (256, 68) and of whole blocks (512, 1024), 16 and 32 rows high, heads of 32, 64 and
 # 256, pages of 16 and 48.  Where the batch or one of its parts keeps the launch of its own - more rows (the first two, whose whole batch
 # takes 64 x 64 tiles and tiles of any depth), heads of 128 and 16 - it is the same bits.

@@ -24,15 +24,16 @@ def hand_laid_loops(body):
 
 @pytest.mark.parametrize("kernel,tiles", [("gemm_fold_kernel", [(256, 128)]),
                                           ("gemm_experts_wide_kernelILb0E", [(256, 256), (256, 192), (256, 128), (256, 64)]),
-                                          ("gemm_experts_wide_kernelILb1E", [(256, 256), (256, 192), (256, 128), (256, 64)])])
+                                          ("gemm_experts_wide_kernelILb1E", [(256, 256), (256, 192), (256, 128), (256, 64)]),
+                                          ("gemm_experts_kernelILb0ELb0E", [(128, 256)]), ("gemm_experts_kernelILb1ELb0E", [(128, 256)])])
 def test_wide_loops_touch_no_operand_before_its_wait(lines, kernel, tiles):
     starts = [i for i, l in enumerate(lines) if l.startswith("_ZN3dyn") and l.split(";")[0].strip().endswith(":")]
     at = next(i for i in starts if kernel in lines[i])
     body = lines[at:min([s for s in starts if s > at] + [len(lines)])]
     loops = hand_laid_loops(body)
     want = Counter()
-    for bn, mt in tiles:                                  # eight waves, two along the X rows
-        na, nb = bn // 4 // 16, mt // 32
+    for bn, mt in tiles:                                  # eight waves, two along the X rows; four on a tile taller than wide
+        na, nb = (bn // 4 // 16, mt // 32) if bn >= mt else (bn // 2 // 16, mt // 64)
         want[(2 * na * nb, 2 * (na + nb))] += 1
     got = Counter()
     for loop in loops:
