@@ -37,10 +37,10 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # instead of going stale silently.
 ATTN_SOURCE = tuple(os.path.join(ROOT, "paper_2605_21603_amd", "csrc", f) for f in ("kernels_attn_mfma.hip", "kernels_attn_plan.hip"))
 ROCPROF_TRAFFIC = {
-    "c2": {"bytes": 1273026970 + 21841408, "source_sha256_16": "4bd466c26c87f3b4", "kv_chunk_positions": 256,
-           "source": "profiles/c2_sequential_attn_mfma_kernel.md (FETCH_SIZE 621,595.2 x 2.0 KiB + WRITE_SIZE 21,329.5 KiB)"},
-    "c5": {"bytes": 5050574848 + 22979994, "source_sha256_16": "4bd466c26c87f3b4", "kv_chunk_positions": 1024,
-           "source": "profiles/c5_sequential_32_layer_decode.md (FETCH_SIZE 2,466,101.0 x 2.0 KiB + WRITE_SIZE 22,441.4 KiB)"},
+    "c2": {"bytes": 1272979866 + 20712858, "source_sha256_16": "38f4af673607fc3f", "kv_chunk_positions": 256,
+           "source": "profiles/c2_sequential_attn_mfma_kernel.md (FETCH_SIZE 621,572.2 x 2.0 KiB + WRITE_SIZE 20,227.4 KiB)"},
+    "c5": {"bytes": 5050603725 + 21981798, "source_sha256_16": "38f4af673607fc3f", "kv_chunk_positions": 1024,
+           "source": "profiles/c5_sequential_32_layer_decode.md (FETCH_SIZE 2,466,115.1 x 2.0 KiB + WRITE_SIZE 21,466.6 KiB)"},
 }
 
 

@@ -98,6 +98,17 @@ __host__ __device__ inline int prefill_chunk_positions(int reach) {
     return ct;
 }
 constexpr int kPrefillChunkPagesMax = 8192 / 16;     // in 16-position pages
+// The same for a block of a long prompt: its sequence has about `rows` tokens in this step with about `mean_keys` keys each, in blocks
+// of `tg`, for n_kv kv heads.  Such a prompt has work for all 256 CUs from its query blocks alone, and what a finer cut costs is a
+// partial set written and read back per chunk and token: chunks double (to 8192) while one is at most half of what a CU
+// gets.  4096 tokens behind 8192 positions,
+// chunks of 2048 -> 8192: merge 88 -> 33 us with the merge's own form, a step 2482 -> 2435; 4096 alone, 1024 -> 2048: chunk kernel 205 -> 188 us.
+__host__ __device__ inline int prefill_run_chunk_positions(int reach, int tg, int n_kv, int rows, int mean_keys) {
+    int ct = prefill_chunk_positions(reach);
+    const long long cu = (long long)n_kv * rows * mean_keys / (256 * tg);
+    while (ct < 8192 && ct < reach && 4 * ct <= cu) ct *= 2;
+    return ct;
+}
 // The most chunks a token with at most `positions` keys can have under that rule: a chunk size below 8192 is taken up to
 // eight chunks' reach only.
 __host__ __device__ inline int prefill_max_chunks(long positions) {

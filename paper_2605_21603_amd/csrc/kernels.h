@@ -18,9 +18,15 @@ struct AttnShape {
     int n_q, n_kv, head_dim, page_size;
     int max_pages_per_seq;         // block-table row length
     int chunk_pages;               // pages per split-KV chunk (a constant of the layer)
-    int max_chunks;                // the most chunks a token of the batch can have: stride of the partial arrays
+    int max_chunks;                // the most chunks a token of the batch can have
     int n_cus;                     // CUs of the stream's partition (0: whole device); sizes the persistent launch
+    int rows;                      // rows of the dispatch
 };
+
+// Where chunk c of a row's q head lies in the split-KV partial arrays, chunk by chunk: what a dispatch's tokens use is one piece of
+// memory.  (With a token's chunks side by side, room for the most any token can have between one token and the next, the
+// partials of 4096 prompt tokens behind 8192 positions lay 24 KB apart over 3.2 GB.)
+__host__ __device__ inline size_t part_index(const AttnShape &sh, int row, int head, int c) { return ((size_t)c * sh.rows + row) * sh.n_q + head; }
 
 // Expert grouping of a projection (all fields zero: plain GEMM).  Group e has counts[e] rows;
 // row i of the group reads X row lists[e * cap + i] / x_div and writes output row
@@ -159,7 +165,7 @@ hipError_t launch_norm_plan(const void *x, const void *g, void *out, int ld_out,
                             const int32_t *pos_of_token, int32_t *plan, const AttnShape &sh, hipStream_t s);
 
 // Causal paged attention for token rows; part_o / part_ml are the split-KV partial arrays
-// ([rows, n_q, max_chunks, head_dim] and [rows, n_q, max_chunks, 2]); plan is scratch for the
+// ([max_chunks, rows, n_q, head_dim] and [max_chunks, rows, n_q, 2]); plan is scratch for the
 // device-built work lists (AttnPlan); any_single / any_multi: some sequence has one / more
 // than one token in these rows (host knowledge; whether the decode / the prefill form is launched).
 hipError_t launch_attention(int dtype, const void *qkv, const int32_t *seq_of_token, const int32_t *pos_of_token,

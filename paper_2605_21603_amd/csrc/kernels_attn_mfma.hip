@@ -29,7 +29,7 @@ hipError_t launch_attention_combine(int dtype, bool base2, float *part_o, float 
                                     const AttnShape &sh, int rows, hipStream_t s, int32_t *counter_reset, bool one_chunk_done);
 hipError_t launch_attention_prefill(const void *qkv, const int32_t *seq_of_token, const int32_t *pos_of_token,
                                     const int32_t *block_table, const void *k_cache, const void *v_cache, void *out, int ld_out,
-                                    float *part_o, float *part_ml, const AttnShape &sh, int32_t *plan, long max_items, int max_groups,
+                                    float *part_o, float *part_ml, const AttnShape &sh, int32_t *plan, const int32_t *ct_of_token, long max_items, int max_groups,
                                     hipStream_t s);
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -241,8 +241,7 @@ __global__ __launch_bounds__(256, NQG == 1 ? 2 : 1) void attn_mfma_kernel(const 
                     *reinterpret_cast<u32x2 *>(y + dt * 16) = w;
                 }
             } else if (nk_cur[q] > cur.lp_first * PS) {          // the chunk exists for this column's token
-                const size_t pidx =
-                    ((size_t)(cur.t + q * TG + col_tok) * sh.n_q + g_cur * G + col_head) * sh.max_chunks + cur.c;
+                const size_t pidx = part_index(sh, cur.t + q * TG + col_tok, g_cur * G + col_head, cur.c);
 #pragma unroll
                 for (int dt = 0; dt < 8; ++dt)
                     *reinterpret_cast<f32x4 *>(part_o + pidx * HD + dt * 16 + 4 * lq) = acc[q][dt];
@@ -305,7 +304,7 @@ hipError_t launch_attention(int dtype, const void *qkv, const int32_t *seq_of_to
     }
     if (e == hipSuccess && any_multi)
         e = launch_attention_prefill(qkv, seq_of_token, pos_of_token, block_table, k_cache, v_cache, out, ld_out, part_o, part_ml, sh,
-                                     lists.multi, max_items, groups, s);
+                                     lists.multi, lists.ct_of_token, max_items, groups, s);
     if (e == hipSuccess && mid) e = hipEventRecord(mid, s);
     if (e != hipSuccess) return e;
     return launch_attention_combine(dtype, true, part_o, part_ml, pos_of_token, lists.ct_of_token, out, ld_out, sh, rows, s, lists.multi + 1, true);

@@ -4,7 +4,7 @@
 //
 // An 8-wave workgroup serves one query block - up to 16 * (16 / G) tokens (64 with G = 4 q heads per kv
 // head) of one sequence whose positions fall in one aligned block - against one chunk of cached positions (1024, more behind
-// a long prefix: prefill_chunk_positions) of one kv head.  K and V tiles of 64 positions (four pages each, 32 KB together) go from
+// a long prefix or for a long prompt: prompt_chunk) of one kv head.  K and V tiles of 64 positions (four pages each, 32 KB together) go from
 // global memory straight into an LDS ring with direct loads, once per workgroup, and all eight waves read
 // their MFMA operands from there: a key is fetched once per query block and q-head
 // group, and the waves hold no K/V staging registers.  A wave owns two sets of 16 columns
@@ -72,7 +72,8 @@ __global__ __launch_bounds__(kWaves * 64, 1) void attn_prefill_kernel(const bf16
                                                               const bf16_t *__restrict__ v_cache,
                                                               bf16_t *__restrict__ out, int ld_out,
                                                               float *__restrict__ part_o, float *__restrict__ part_ml,
-                                                              AttnShape sh, const int32_t *__restrict__ plan, int32_t *__restrict__ counter) {
+                                                              AttnShape sh, const int32_t *__restrict__ plan, int32_t *__restrict__ counter,
+                                                              const int32_t *__restrict__ ct_of_token) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     int32_t *pid = reinterpret_cast<int32_t *>(lds + kRing * kTile);      // physical pages of the chunk
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -103,8 +104,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void attn_prefill_kernel(const bf16
         const int c = packed & 0xfffff, n_tok = packed >> 20;
         const int n_keys = pos_of_token[t0 + n_tok - 1] + 1;             // keys the block's last token attends
         const int seq_pages = (n_keys + PS - 1) / PS;
-        const int block_tokens = kWaves * kSets * TG;                     // the aligned position block this item's tokens share
-        const int chunk_pages = prefill_chunk_positions((pos_of_token[t0] / block_tokens + 1) * block_tokens) / PS;
+        const int chunk_pages = ct_of_token[t0] / PS;                     // the same for all tokens of an aligned position block
         const int lp0 = c * chunk_pages;
         const int n_pg = min(chunk_pages, seq_pages - lp0);
         const int n_tile = (n_pg + kTP - 1) / kTP;
@@ -388,8 +388,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void attn_prefill_kernel(const bf16
                     *reinterpret_cast<u32x2 *>(y + dt * 16) = w;
                 }
             } else {
-                const size_t pidx =
-                    ((size_t)(t0 + wave_tok0 + q * TG + col_tok) * sh.n_q + g * G + col_head) * sh.max_chunks + c;
+                const size_t pidx = part_index(sh, t0 + wave_tok0 + q * TG + col_tok, g * G + col_head, c);
 #pragma unroll
                 for (int dt = 0; dt < 8; ++dt)
                     *reinterpret_cast<f32x4 *>(part_o + pidx * HD + dt * 16 + 4 * lq) = acc[q][dt];
@@ -408,7 +407,7 @@ int attn_prefill_block_tokens(const AttnShape &sh) { return kWaves * kSets * (16
 
 hipError_t launch_attention_prefill(const void *qkv, const int32_t *seq_of_token, const int32_t *pos_of_token,
                                     const int32_t *block_table, const void *k_cache, const void *v_cache, void *out, int ld_out,
-                                    float *part_o, float *part_ml, const AttnShape &sh, int32_t *plan, long max_items, int max_groups,
+                                    float *part_o, float *part_ml, const AttnShape &sh, int32_t *plan, const int32_t *ct_of_token, long max_items, int max_groups,
                                     hipStream_t s) {
     static_assert(kPrefillChunkPagesMax <= kWaves * 64, "one thread per page id of a chunk");
     const int lds_bytes = kRing * kTile + (kPrefillChunkPagesMax + 4) * (int)sizeof(int32_t);   // ring, page ids of a chunk, the claimed item
@@ -421,7 +420,7 @@ hipError_t launch_attention_prefill(const void *qkv, const int32_t *seq_of_token
     const int grid = (int)(max_items < max_groups ? max_items : max_groups);
     hipLaunchKernelGGL(attn_prefill_kernel, dim3(grid), dim3(kWaves * 64), lds_bytes, s, (const bf16_t *)qkv, seq_of_token,
                        pos_of_token, block_table, (const bf16_t *)k_cache, (const bf16_t *)v_cache, (bf16_t *)out, ld_out, part_o, part_ml, sh, plan,
-                       plan + 1);
+                       plan + 1, ct_of_token);
     return hipGetLastError();
 }
 

@@ -45,6 +45,7 @@ int main() {
         const int TG = 16 / G;
         for (int p0 : {0, 1, 959, 1000}) {
             bad += wrong(p0, 20000, 16 * TG, [](int reach) { return prefill_chunk_positions(reach); });
+            for (int rows : {1024, 5120}) bad += wrong(p0, 20000, 16 * TG, [=](int reach) { return prefill_run_chunk_positions(reach, 16 * TG, 8, rows, reach); });
             for (int ct : {64, 240, 256, 1024}) bad += wrong(p0, 3000, 4 * TG, [ct](int) { return ct; });
         }
     }

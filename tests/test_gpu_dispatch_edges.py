@@ -5,7 +5,7 @@ import ctypes
 import pytest
 import torch
 
-from gpu_util import GpuRun, check_against_oracle, gemm_path, say
+from gpu_util import GpuRun, as_f64, check_against_oracle, gemm_path, row_rel_err, say
 from paper_2605_21603_amd import binding as B
 from test_gpu_generic_paths import both_schedules, workload
 from workloads import gen
@@ -195,6 +195,36 @@ def test_expert_tiles_of_few_rows_follow_the_counts(hidden, tokens, pull):
     data["x"] = x.to(torch.bfloat16)
     y, k, v = both_schedules(w, data)
     say("%d tokens: %.2e" % (tokens, check_against_oracle(w, data, y, k, v)))
+
+
+# A long prompt's chunks grow with its rows, here from 1024 (2048) to 2048 and 4096 positions: with other sequences around it, in
+# another micro-batch than theirs, the same bits; the rows of its end as a step of their own, which keeps the shorter chunks, agree to bf16 rounding.
+@pytest.mark.parametrize("prompt,cached", [(4200, 100), (4097, 5003)])
+def test_long_prompts_take_longer_chunks(prompt, cached):
+    seqs = [(prompt, cached + prompt), (1, 77), (33, 40)]
+    w = workload("long", "bf16", 128, 32, 8, 128, 128, seqs, seed=prompt)
+    data = gen.generate(w)
+    y, k, v = both_schedules(w, data)
+    y, end = y[:prompt], 1000
+    w_end = workload("end", "bf16", 128, 32, 8, 128, 128, [(end, cached + prompt)])
+    rows = slice(prompt - end, prompt)
+    part = dict(data, x=data["x"][rows].contiguous(), k_cache=list(k), v_cache=list(v), seq_of_token=data["seq_of_token"][rows],
+                pos_of_token=data["pos_of_token"][rows], block_table=data["block_table"][:1], q_start=[0, end], ctx_len=data["ctx_len"][:1])
+    y_end = GpuRun(w_end, part).run(B.sequential())[0]
+    assert row_rel_err(as_f64(y_end), as_f64(y[-end:])) < 2e-2         # TOL of a bf16 layer
+    assert not torch.equal(y_end, y[-end:])                           # the cuts differ
+
+
+# The merge's forms: one and two chunks four groups of eight heads at a time, up to eight, more, and more than 64 in two levels; head counts that
+# leave groups of eight part-filled, dims of one and two loads a lane.
+@pytest.mark.parametrize("dtype,n_q,n_kv,hd", [("bf16", 12, 3, 128), ("bf16", 40, 8, 64), ("f32", 3, 1, 64), ("f32", 2, 2, 256), ("bf16", 36, 12, 32)])
+def test_merge_of_every_number_of_chunks(dtype, n_q, n_kv, hd):
+    seqs = [(1, c) for c in (1, 64, 65, 128, 129, 512, 513, 1100, 4096, 4200)] + [(70, 100), (2, 300)]
+    w = workload("merge", dtype, 128, n_q, n_kv, hd, 128, seqs, seed=n_q)
+    data = gen.generate(w)
+    run = GpuRun(w, data, kv_chunk_positions=64)
+    y, k, v = run.run(B.sequential())
+    say("%d heads of %d: %.2e" % (n_q, hd, check_against_oracle(w, data, y, k, v)))
 
 
 # The same inside the fp32 projection: tiles of any depth (256, 68) and of whole blocks (512, 1024), 16 and 32 rows high, heads of 32, 64 and
