@@ -59,6 +59,7 @@ struct Dispatch {
     std::vector<int> deps;   // dispatches (indices into the plan) whose output rows this one reads
     bool plan = false;          // first norm: its launch also builds the attention work lists of its rows; attention: they have been built
     bool gated = false;         // gate/up and SiLU: the gate is applied by the gate/up dispatch (plan_gated)
+    bool norm_in = false;       // qkv and gate/up: the norm before them is applied by the projection itself; first norm, o and down projection: so they leave it out (plan_norm_in)
     bool lists_ready = false;   // MoE down projection: the gate/up dispatch of the same rows already built its expert lists
     int key() const { return partition * DYN_MAX_STREAMS + stream; }
 };
@@ -258,10 +259,32 @@ bool fused_into_producer(int op, int layer) {
 // launch - if that is so for every micro-batch; one that folds its planes in registers stores gate and up.
 bool plan_gated(const dyn_layer_config &c, const std::vector<Dispatch> &plan) {
     if (dyn::gemm_gated_supported(c.dtype, 2 * c.mlp_inter, c.hidden, c.n_experts > 0)) return true;
-    if (c.n_experts || !dyn::reduce_gate_supported(c.dtype, c.mlp_inter)) return false;
-    for (const Dispatch &d : plan)
-        if (d.op == DYN_OP_GATE_UP && d.r1 > d.r0 && !dyn::gemm_uses_plane_buffer(c.dtype, d.r1 - d.r0, 2 * c.mlp_inter, c.hidden)) return false;
+    if (c.n_experts || (c.dtype != DYN_F32 && !dyn::reduce_gate_supported(c.dtype, c.mlp_inter))) return false;
+    for (const Dispatch &d : plan) {
+        const int rows = d.r1 - d.r0;
+        if (d.op != DYN_OP_GATE_UP || rows <= 0) continue;
+        if (c.dtype == DYN_F32 ? !dyn::gemm_f32_gated_rows_supported(rows, 2 * c.mlp_inter, c.hidden)
+                               : !dyn::gemm_uses_plane_buffer(c.dtype, rows, 2 * c.mlp_inter, c.hidden)) return false;
+    }
     return true;
+}
+
+// Whether every dispatch of `op` (qkv, gate/up) applies the norm before it itself, so that none is launched or fused into what
+// comes before; `gated` as plan_gated says.
+bool plan_norm_in(const dyn_layer_config &c, const std::vector<Dispatch> &plan, int op, bool gated) {
+    if (c.n_experts || c.dtype != DYN_F32 || (op == DYN_OP_GATE_UP && !gated)) return false;
+    const dyn::AttnShape sh{c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, 1, 1, 1, 0, 0};
+    for (const Dispatch &d : plan) {
+        const int rows = d.r1 - d.r0, N = op == DYN_OP_QKV ? qkv_width(c) : 2 * c.mlp_inter;
+        if (d.op != op || rows <= 0) continue;
+        if (!dyn::gemm_norm_in_supported(c.dtype, rows, N, c.hidden)) return false;
+        if (op == DYN_OP_QKV && !dyn::gemm_f32_rope_supported(nullptr, c.hidden, nullptr, rows, N, c.hidden, sh)) return false;
+    }
+    return true;
+}
+
+bool norm_in(const std::vector<Dispatch> &plan, int op) {         // what build_plan found
+    return std::any_of(plan.begin(), plan.end(), [op](const Dispatch &d) { return d.op == op && d.norm_in; });
 }
 
 // Checks of an explicit schedule that need no batch: counts in range, arrays present, masks not empty.
@@ -403,6 +426,11 @@ dyn_status build_plan(const dyn_layer *L, const dyn_batch *b, const dyn_schedule
             d.gated = d.op == DYN_OP_GATE_UP || d.op == DYN_OP_SILU;
             if (d.op == DYN_OP_SILU) d.noop = true;
         }
+    const bool norm1_in = plan_norm_in(L->cfg, plan, DYN_OP_QKV, false), norm2_in = plan_norm_in(L->cfg, plan, DYN_OP_GATE_UP, plan_gated(L->cfg, plan));
+    for (Dispatch &d : plan) {
+        d.norm_in = d.op == DYN_OP_NORM1 || d.op == DYN_OP_QKV || d.op == DYN_OP_DOWN ? norm1_in : (d.op == DYN_OP_OPROJ || d.op == DYN_OP_GATE_UP) && norm2_in;
+        if (d.op == DYN_OP_NORM1 && norm1_in) d.noop = true;
+    }
     // The attention work lists depend on the rows' sequences and positions only, and every layer walks the same
     // ones: where the first layer's norm is dispatched over exactly the rows of an attention dispatch (which
     // follows it in its micro-batches' chain), the norm's launch builds them beside its rows.  Otherwise the
@@ -469,6 +497,7 @@ WsLayout plan_layout(const dyn_layer *L, const dyn_batch *b, const std::vector<D
     if (P == 0 || n_slots == 0) return w;
     const std::vector<int> until = alive_until(plan);
     const bool moe = c.n_experts > 0, gated = plan_gated(c, plan);
+    const bool norm1 = !norm_in(plan, DYN_OP_QKV), norm2 = !norm_in(plan, DYN_OP_GATE_UP);
 
     bool single_stream = true;
     {
@@ -503,9 +532,9 @@ WsLayout plan_layout(const dyn_layer *L, const dyn_batch *b, const std::vector<D
     // norm's, written by the o projection's dispatch, read by the router and gate/up
     struct TensorDef { int kind; size_t bytes; int producer, last_consumer; bool present; int producer_layer_offset; };
     const TensorDef defs[] = {
-        {DYN_REGION_H, z.h, DYN_OP_NORM1, DYN_OP_QKV, true, 0},
-        {DYN_REGION_H, z.h, DYN_OP_DOWN, DYN_OP_QKV, c.n_layers > 1, -1},
-        {DYN_REGION_H, z.h, DYN_OP_OPROJ, DYN_OP_GATE_UP, true, 0},
+        {DYN_REGION_H, z.h, DYN_OP_NORM1, DYN_OP_QKV, norm1, 0},
+        {DYN_REGION_H, z.h, DYN_OP_DOWN, DYN_OP_QKV, norm1 && c.n_layers > 1, -1},
+        {DYN_REGION_H, z.h, DYN_OP_OPROJ, DYN_OP_GATE_UP, norm2, 0},
         {DYN_REGION_QKV, z.qkv, DYN_OP_QKV, DYN_OP_ATTN, true, 0},
         {DYN_REGION_ATTN, z.attn, DYN_OP_ATTN, DYN_OP_OPROJ, true, 0},
         {DYN_REGION_X2, z.x2, DYN_OP_OPROJ, DYN_OP_DOWN, true, 0},
@@ -685,7 +714,7 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
     hipError_t err = hipSuccess;
     switch (d.op) {
         case DYN_OP_NORM1:
-            if (fused_into_producer(d.op, d.layer)) break;       // the previous layer's down projection wrote h
+            if (d.norm_in || fused_into_producer(d.op, d.layer)) break;       // the qkv projection normalises; the previous layer's down projection wrote h
             if (d.plan && dyn::attention_mfma_supported(c.dtype, sh)) {
                 err = dyn::launch_norm_plan(rowp(x_in, H), w.g_norm1, (void *)rowp(base + ws.h, ws.ld_h), ws.ld_h, rows, H, c.rms_eps,
                                             b->seq_of_token + d.r0, b->pos_of_token + d.r0, plan, sh, st);
@@ -704,8 +733,9 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
             ep.rope = &L->rope;
             ep.shape = &sh;
             ep.long_rows = d.long_rows;
-            err = dyn::launch_gemm(c.dtype, rowp(base + ws.h, ws.ld_h), ws.ld_h, w.w_qkv, nullptr, (void *)rowp(base + ws.qkv, NQKV),
-                                   planes, (size_t)rows * NQKV, rows, NQKV, H, st, mid, &ep, sh.n_cus);
+            err = dyn::launch_gemm(c.dtype, d.norm_in ? rowp(x_in, H) : rowp(base + ws.h, ws.ld_h), d.norm_in ? H : ws.ld_h, w.w_qkv, nullptr,
+                                   (void *)rowp(base + ws.qkv, NQKV), planes, (size_t)rows * NQKV, rows, NQKV, H, st, mid, &ep, sh.n_cus,
+                                   dyn::GemmNorm{d.norm_in ? w.g_norm1 : nullptr, c.rms_eps});
             break;
         }
         case DYN_OP_ROPE_KV:
@@ -719,7 +749,7 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
             break;
         case DYN_OP_OPROJ: {
             dyn::GemmEpilogue ep;                                 // the second norm of the rows just written
-            ep.kind = dyn::GemmEpilogue::NORM;
+            if (!d.norm_in) ep.kind = dyn::GemmEpilogue::NORM;
             ep.g = w.g_norm2;
             ep.h_out = (void *)rowp(base + ws.h, ws.ld_h);
             ep.ld_h = ws.ld_h;
@@ -764,8 +794,9 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
                     err = dyn::launch_gemm(c.dtype, rowp(base + ws.h, ws.ld_h), ws.ld_h, w.w_gate_up, nullptr, planes, planes, (size_t)rows * 2 * I,
                                            rows, 2 * I, H, st, mid, &ep, sh.n_cus);
                 } else {
-                    err = dyn::launch_gemm_gated(c.dtype, rowp(base + ws.h, ws.ld_h), ws.ld_h, w.w_gate_up, act, ws.ld_act, dyn::GemmGroups{}, rows,
-                                                 2 * I, H, st, mid);
+                    err = dyn::launch_gemm_gated(c.dtype, d.norm_in ? rowp(base + ws.x2, H) : rowp(base + ws.h, ws.ld_h), d.norm_in ? H : ws.ld_h,
+                                                 w.w_gate_up, act, ws.ld_act, dyn::GemmGroups{}, rows, 2 * I, H, st, mid,
+                                                 dyn::GemmNorm{d.norm_in ? w.g_norm2 : nullptr, c.rms_eps});
                 }
                 break;
             }
@@ -805,7 +836,7 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
                 break;
             }
             dyn::GemmEpilogue ep;                                 // the next layer's first norm of the rows just written
-            if (d.layer + 1 < nl) {
+            if (d.layer + 1 < nl && !d.norm_in) {
                 ep.kind = dyn::GemmEpilogue::NORM;
                 ep.g = L->w[d.layer + 1].g_norm1;
                 ep.h_out = (void *)rowp(base + ws.h, ws.ld_h);
@@ -934,7 +965,7 @@ std::vector<unsigned char> graph_key(const dyn_batch *b, const dyn_schedule *s, 
         put(b->v_cache_layers, sizeof(void *) * n_layers);
     }
     for (const Dispatch &d : plan) {
-        const int f[] = {d.layer, d.op, d.r0, d.r1, d.stream, d.partition, d.any_multi, d.any_single, d.noop, d.lists_ready, d.plan};
+        const int f[] = {d.layer, d.op, d.r0, d.r1, d.stream, d.partition, d.any_multi, d.any_single, d.noop, d.lists_ready, d.plan, d.gated, d.norm_in};
         put(f, sizeof f);
     }
     if (s->mode == DYN_SCHED_EXPLICIT && s->n_partitions > 0) {
@@ -953,7 +984,10 @@ void analyse_memory(const dyn_layer *L, const dyn_batch *b, const std::vector<Di
     const size_t e = esize(c);
     const Sizes ws = tensor_sizes(L, b->n_tokens, b->max_pages_per_seq, b->n_tokens > b->n_seqs);
     const int n_slots = (int)plan.size() / c.n_layers;
-    const bool moe = c.n_experts > 0, gated = plan_gated(c, plan);
+    // (fp32 steps of so few rows that their projections normalise and gate at any depth hold less than this counts: the report is of what
+    // the operators exchange with any number of rows.)
+    const bool moe = c.n_experts > 0;
+    const bool gated = c.dtype == DYN_F32 ? dyn::gemm_gated_supported(c.dtype, 2 * c.mlp_inter, c.hidden, moe) : plan_gated(c, plan);
     const int pairs = moe ? c.top_k : 1, H = c.hidden, I = c.mlp_inter, NQKV = qkv_width(c), NQ = c.n_q_heads * c.head_dim;
     int slot_of[DYN_N_OPS][DYN_MAX_NANO];
     for (auto &r : slot_of) std::fill(r, r + DYN_MAX_NANO, -1);

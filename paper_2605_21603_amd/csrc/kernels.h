@@ -89,21 +89,28 @@ struct GemmEpilogue {
     int long_rows = 0;       // of the rows, those of sequences with 16 tokens and more among them
 };
 
+// The RMSNorm before a projection, applied to the X rows by the projection itself (g null: none); same bits as launch_rmsnorm's rows.
+struct GemmNorm { const void *g = nullptr; float eps = 0.f; };
+bool gemm_norm_in_supported(int dtype, int rows, int N, int K);
+
 // Y[rows,N] = X[rows,K] W[N,K]^T (+ R[rows,N]); ldx = elements between rows of X (>= K).  partial: fp32 scratch for split-K planes,
 // plane p at partial + p * plane_stride (elements); unused when the split factor is 1.
 // If mid is not NULL it is recorded after the contraction kernel, before the split-K reduce.
 // n_cus: compute units of the partition the stream runs on, 0: all.
 hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const void *R, void *Y, float *partial,
                        size_t plane_stride, int rows, int N, int K, hipStream_t s, hipEvent_t mid = nullptr,
-                       const GemmEpilogue *ep = nullptr, int n_cus = 0);
+                       const GemmEpilogue *ep = nullptr, int n_cus = 0, const GemmNorm &norm = GemmNorm{});
 
 // fp32 projection, plain or expert-grouped (kernels_gemm_f32.hip; launch_gemm and launch_gemm_grouped call it); max_rows bounds a group's rows.
 hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const void *R, void *Y, int max_rows, int N, int K, const GemmGroups &gr,
                            hipStream_t s);
 bool gemm_f32_gated_supported(int N2, int K);
 bool gemm_f32_rope_supported(const void *X, int ldx, const void *W, int rows, int N, int K, const AttnShape &sh);   // rotary + cache append in the same launch
-hipError_t launch_gemm_f32_rope(const void *X, int ldx, const void *W, void *Y, int rows, int N, int K, const GemmEpilogue &rope, hipStream_t s);
-hipError_t launch_gemm_f32_gated(const void *X, int ldx, const void *W, void *Y, int ldy, int rows, int N2, int K, hipStream_t s);
+hipError_t launch_gemm_f32_rope(const void *X, int ldx, const void *W, void *Y, int rows, int N, int K, const GemmNorm &norm, const GemmEpilogue &rope,
+                                hipStream_t s);
+bool gemm_f32_gated_rows_supported(int rows, int N2, int K);         // with that many rows, or any
+bool gemm_f32_norm_supported(int rows, int N, int K);                // with rotary or gate, the norm of X in the same launch
+hipError_t launch_gemm_f32_gated(const void *X, int ldx, const void *W, void *Y, int ldy, int rows, int N2, int K, const GemmNorm &norm, hipStream_t s);
 // A few rows (at most 16), planes summed in the workgroup (kernels_gemm_rows.hip; launch_gemm calls it).
 bool gemm_rows16_wide_supported(int rows, int N, int K, int S);       // on the whole chip
 bool gemm_rows16_supported(int rows, int N, int K, int S);            // on any number of CUs
@@ -131,7 +138,7 @@ hipError_t launch_gemm_grouped(int dtype, const void *X, int ldx, const void *W,
 // the dispatch's first row, max_rows rows.  Grouped: as launch_gemm_grouped.
 bool gemm_gated_supported(int dtype, int N2, int K, bool experts);
 hipError_t launch_gemm_gated(int dtype, const void *X, int ldx, const void *W, void *Y, int ldy, const GemmGroups &gr, int max_rows,
-                             int N2, int K, hipStream_t s, hipEvent_t mid = nullptr);
+                             int N2, int K, hipStream_t s, hipEvent_t mid = nullptr, const GemmNorm &norm = GemmNorm{});
 
 // MoE router for token rows: logits = h W_r^T in fp32, top_k largest (ties to the lower index),
 // softmax over the selected logits.  sel / wgt are [rows, top_k], largest logit first.

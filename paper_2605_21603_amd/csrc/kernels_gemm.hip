@@ -335,13 +335,14 @@ GemmEpilogue epilogue_at(const GemmEpilogue &ep, int dtype, int row, int N) {   
 }  // namespace
 
 hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const void *R, void *Y, float *partial,
-                       size_t plane_stride, int rows, int N, int K, hipStream_t s, hipEvent_t mid, const GemmEpilogue *ep, int n_cus) {
+                       size_t plane_stride, int rows, int N, int K, hipStream_t s, hipEvent_t mid, const GemmEpilogue *ep, int n_cus,
+                       const GemmNorm &norm) {
     if (rows <= 0) return hipSuccess;
     const GemmGroups none{};
     const bool has_ep = ep && ep->kind != GemmEpilogue::NONE;
     if (dtype == 0) {
         const bool rope = has_ep && ep->kind == GemmEpilogue::ROPE && !R && gemm_f32_rope_supported(X, ldx, W, rows, N, K, *ep->shape);
-        hipError_t e0 = rope ? launch_gemm_f32_rope(X, ldx, W, Y, rows, N, K, *ep, s) : launch_gemm_f32(X, ldx, W, R, Y, rows, N, K, none, s);
+        hipError_t e0 = rope ? launch_gemm_f32_rope(X, ldx, W, Y, rows, N, K, norm, *ep, s) : launch_gemm_f32(X, ldx, W, R, Y, rows, N, K, none, s);
         if (e0 == hipSuccess && mid) e0 = hipEventRecord(mid, s);
         if (e0 == hipSuccess && has_ep && !rope) e0 = run_epilogue(dtype, *ep, Y, rows, N, s);
         return e0;
@@ -403,6 +404,8 @@ namespace {
 bool gemm_experts_on_wide(const GemmGroups &gr, int N, int S) { return S == 1 && N % 256 == 0 && gr.cap / std::max(gr.n_groups, 1) > 200; }
 }  // namespace
 
+bool gemm_norm_in_supported(int dtype, int rows, int N, int K) { return dtype == 0 && gemm_f32_norm_supported(rows, N, K); }
+
 bool gemm_gated_supported(int dtype, int N2, int K, bool experts) {
     return dtype == 1 ? gemm_split_k(dtype, N2, K) == 1 : !experts && gemm_f32_gated_supported(N2, K);
 }
@@ -410,11 +413,11 @@ bool gemm_gated_supported(int dtype, int N2, int K, bool experts) {
 // act[rows or listed rows, N2/2] = silu(X Wg^T) * (X Wu^T) with W = [gate rows; up rows] ([N2, K]),
 // output row pitch ldy.  Plain (gr.n_groups = 0: X, Y offset to the dispatch) or expert-grouped.
 hipError_t launch_gemm_gated(int dtype, const void *X, int ldx, const void *W, void *Y, int ldy, const GemmGroups &gr, int max_rows,
-                             int N2, int K, hipStream_t s, hipEvent_t mid) {
+                             int N2, int K, hipStream_t s, hipEvent_t mid, const GemmNorm &norm) {
     if (max_rows <= 0) return hipSuccess;
     hipError_t e;
     if (dtype == 0) {
-        e = launch_gemm_f32_gated(X, ldx, W, Y, ldy, max_rows, N2, K, s);
+        e = launch_gemm_f32_gated(X, ldx, W, Y, ldy, max_rows, N2, K, norm, s);
         return e == hipSuccess && mid ? hipEventRecord(mid, s) : e;
     }
 #define DYN_GATED(BN, MT, NS, NW) \

@@ -75,6 +75,44 @@ __device__ __forceinline__ void f32_angles(F32Angles<NB> &angles, const F32Rotar
     angles.at[b][r][lane] = make_float2(c, s);
 }
 
+// NORM: X rows are normalised as they are loaded, x * r * g with rmsnorm_row's r, where the launch has one workgroup row or few: a norm's
+// own launch is as long as reading one row twice, and every workgroup reads the rows anyway.
+struct F32Norm { const float *g; float eps; };
+
+// The rows' sums of squares as rmsnorm_row takes them, a row to each half of the workgroup, P of them at a time; then r of row `row` of the tile.
+template <int P>
+__device__ __forceinline__ void f32_squares(float (*part)[4], const float *__restrict__ X, int ldx, int m0, int M, int K) {
+    const int half = threadIdx.x >> 8, tid = threadIdx.x & 255;
+    float ss[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) ss[p] = 0.f;
+    for (int i = tid; i < K / 4; i += 256) {
+        f32x4 v[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) v[p] = *reinterpret_cast<const f32x4_u *>(X + (size_t)min(m0 + 2 * p + half, M - 1) * ldx + 4 * i);
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ss[p] = __builtin_fmaf(v[p][e], v[p][e], ss[p]);
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        ss[p] = wave_sum(ss[p]);
+        if ((tid & 63) == 0) part[2 * p + half][tid >> 6] = ss[p];
+    }
+}
+__device__ __forceinline__ void f32_row_squares(float (*part)[4], const float *__restrict__ X, int ldx, int m0, int M, int K) {
+    const int rows = M - m0;
+    if (rows <= 4) f32_squares<2>(part, X, ldx, m0, M, K);
+    else if (rows <= 8) f32_squares<4>(part, X, ldx, m0, M, K);
+    else f32_squares<8>(part, X, ldx, m0, M, K);
+    __syncthreads();
+}
+__device__ __forceinline__ float f32_row_scale(const float (*part)[4], int row, int K, float eps) {
+    const float total = ((part[row][0] + part[row][1]) + part[row][2]) + part[row][3];
+    return 1.0f / sqrtf(total / (float)K + eps);
+}
+
 // silu(g) * u
 __device__ __forceinline__ f32x4 f32_gate(f32x4 g, f32x4 u) {
     f32x4 o;
@@ -155,10 +193,12 @@ __device__ __forceinline__ void f32_finish(f32x4 (*part)[NA * NB < 4 ? NA * NB :
 // rows x 64 bytes per instruction) and element e of the four is the operand of product e, whose k
 // index l / 16 then stands for k 4 (l / 16) + e in both matrices.  Launch alone, against 64 x 64 tiles of fp32 FMAs staged
 // through LDS 16 k at a time by one chain per output: 4 rows x 768 x 256 27.7 -> 3.2 us, 4 x 256 x 1024 96 -> 5.1 us.
-template <int MT, int NT, class EP>
+template <int MT, int NT, bool NORM, class EP>
 __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_kernel(const float *__restrict__ X, int ldx, const float *__restrict__ W,
                                                                   const float *__restrict__ R, float *__restrict__ Y, int M, int N,
-                                                                  int K, GemmGroups gr, EP ep) {
+                                                                  int K, GemmGroups gr, F32Norm norm, EP ep) {
+    static_assert(!NORM || MT == 16, "a lane has one X row");
+    __shared__ float squares[NORM ? 16 : 1][4];
     constexpr int NA = NT / 16, NB = MT / 16, UNR = (NA + NB) <= 4 ? 4 : 2;  // units of 16 k loaded ahead of their products
     __shared__ f32x4 part[kF32Chains][NA * NB < 4 ? NA * NB : 4][64];
     __shared__ F32Angles<EP::ROTARY ? NB : 1> angles;
@@ -196,21 +236,53 @@ __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_kernel(const float *
 #pragma unroll
                 for (int b = 0; b < NB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[a][e], xv[b][e], acc[a][b], 0, 0, 0);
     };
-    if constexpr (EP::ROTARY) f32_angles(angles, ep, m0, n0, M, pos, page);
     int u = u0;
     const int u1f = min(u1, full);
-    for (; u + UNR <= u1f; u += UNR) {
-        f32x4 wv[UNR][NA], xv[UNR][NB];
+    if constexpr (NORM) {                              // K is a multiple of 256: a chain has an even number of units, two at a time here
+        f32x4 wv[2][NA], xv[2][NB], gv[2];
+        auto load = [&](int at) {
 #pragma unroll
-        for (int i = 0; i < UNR; ++i) {
+            for (int i = 0; i < 2; ++i) {
+#pragma unroll
+                for (int a = 0; a < NA; ++a) wv[i][a] = *reinterpret_cast<const f32x4_u *>(wp[a] + (size_t)(at + i) * 16);
+                xv[i][0] = *reinterpret_cast<const f32x4_u *>(xp[0] + (size_t)(at + i) * 16);
+                gv[i] = *reinterpret_cast<const f32x4_u *>(norm.g + (at + i) * 16 + 4 * lq);
+            }
+        };
+        load(u);                                       // on its way while the sums of squares are taken
+        if constexpr (EP::ROTARY) f32_angles(angles, ep, m0, n0, M, pos, page);
+        f32_row_squares(squares, X, ldx, m0, M, K);
+        const float r = f32_row_scale(squares, min(lr, M - 1 - m0), K, norm.eps);
+        while (true) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) xv[i][0][e] = xv[i][0][e] * r * gv[i][e];
+                multiply(wv[i], xv[i]);
+            }
+            u += 2;
+            if (u >= u1) break;
+            load(u);
+        }
+    } else if constexpr (EP::ROTARY) {
+        f32_angles(angles, ep, m0, n0, M, pos, page);
+    }
+    auto batch = [&](auto n) {                         // n units, their loads together
+        constexpr int U = decltype(n)::value;
+        f32x4 wv[U][NA], xv[U][NB];
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
 #pragma unroll
             for (int a = 0; a < NA; ++a) wv[i][a] = *reinterpret_cast<const f32x4_u *>(wp[a] + (size_t)(u + i) * 16);
 #pragma unroll
             for (int b = 0; b < NB; ++b) xv[i][b] = *reinterpret_cast<const f32x4_u *>(xp[b] + (size_t)(u + i) * 16);
         }
 #pragma unroll
-        for (int i = 0; i < UNR; ++i) multiply(wv[i], xv[i]);
-    }
+        for (int i = 0; i < U; ++i) multiply(wv[i], xv[i]);
+        u += U;
+    };
+    while (u + UNR <= u1f) batch(std::integral_constant<int, UNR>());
+    if (UNR > 2 && u + 2 <= u1f) batch(std::integral_constant<int, 2>());
     for (; u < u1; ++u) {
         f32x4 wv[NA], xv[NB];
         const bool in = u < full || u * 16 + 4 * lq < K;            // K is a multiple of 4
@@ -249,9 +321,12 @@ __device__ __forceinline__ void quad_transpose(f32x4 (&v)[4]) {
 // 12.7 -> 11.9 / 11.9 us, 1024 x 4096 11.2 / 11.0 -> 9.7 / 9.8, 16384 x 2048, gated 28.2 / 28.4 -> 23.4 / 24.2, 2048 x 8192 20.2 / 20.4 ->
 // 17.1 / 18.3; steps of 2048 wide, 8192 MLP, 1 / 8 / 16 rows 92.7 / 98.2 / 99.2 -> 84.5 / 92.1 / 99.0: at 16 rows either way, so the line is
 // where half the rows are there).
-template <int MT, int NT, bool XQUADS, class EP>
+template <int MT, int NT, bool XQUADS, bool NORM, class EP>
 __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_quads_kernel(const float *__restrict__ X, int ldx, const float *__restrict__ W,
-                                                                        const float *__restrict__ R, float *__restrict__ Y, int M, int N, int K, EP ep) {
+                                                                        const float *__restrict__ R, float *__restrict__ Y, int M, int N, int K,
+                                                                        F32Norm norm, EP ep) {
+    static_assert(!NORM || MT == 16, "a tile of few rows");
+    __shared__ float squares[NORM ? 16 : 1][4];
     constexpr int NA = NT / 16, NB = MT / 16, NBUF = NA + NB <= 3 ? 2 : 1;
     __shared__ f32x4 part[kF32Chains][NA * NB < 4 ? NA * NB : 4][64];
     __shared__ F32Angles<EP::ROTARY ? NB : 1> angles;
@@ -272,7 +347,8 @@ __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_quads_kernel(const f
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int blocks = K / (kF32Block * kF32Chains);
-    f32x4 wv[NBUF][NA][4], xv[NBUF][NB][4];
+    f32x4 wv[NBUF][NA][4], xv[NBUF][NB][4], gv[NORM ? NBUF : 1][XQUADS ? 1 : 4];
+    float scale[XQUADS ? 4 : 1];                           // of the rows of this lane's X loads
     auto load = [&](auto buf, int i) {
         constexpr int B = decltype(buf)::value;
         const int at = (wave * blocks + f32_block(i, wave, n0, blocks)) * kF32Block;
@@ -284,9 +360,19 @@ __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_quads_kernel(const f
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int j = 0; j < 4; ++j) xv[B][b][j] = *reinterpret_cast<const f32x4_u *>(Xt + at + xo[b][j]);
+        if constexpr (NORM) {
+#pragma unroll
+            for (int j = 0; j < (XQUADS ? 1 : 4); ++j) gv[B][j] = *reinterpret_cast<const f32x4_u *>(norm.g + at + (XQUADS ? col : (lane >> 4) * 16 + 4 * j));
+        }
     };
     auto multiply = [&](auto buf) {
         constexpr int B = decltype(buf)::value;
+        if constexpr (NORM) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) xv[B][0][j][e] = xv[B][0][j][e] * scale[XQUADS ? j : 0] * gv[B][XQUADS ? 0 : j][e];
+        }
 #pragma unroll
         for (int a = 0; a < NA; ++a) quad_transpose(wv[B][a]);
         if constexpr (XQUADS) {
@@ -313,6 +399,11 @@ __global__ __launch_bounds__(kF32Chains * 64) void gemm_f32_quads_kernel(const f
     } else {                                               // a pass always loads: behind a load that may not have been issued the compiler waits for all
         load(b0, 0);
         if constexpr (EP::ROTARY) f32_angles(angles, ep, m0, n0, M, pos, page);
+        if constexpr (NORM) {                              // while the first block is on its way
+            f32_row_squares(squares, X, ldx, m0, M, K);
+#pragma unroll
+            for (int j = 0; j < (XQUADS ? 4 : 1); ++j) scale[j] = f32_row_scale(squares, min(XQUADS ? row4 + j : (lane & 15), M - 1 - m0), K, norm.eps);
+        }
         int i = 0;
         for (; i + 2 < blocks; i += 2) {
             load(b1, i + 1);
@@ -434,7 +525,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_tiles_kernel(const float *__r
 // where such tiles are about a CU's each: 192 of them (225 rows x 8192 x 1024, 512 tiles: 41 us; 225 x 1536 x 1024, 96 tiles: 23.5 us, with
 // 32 x 32 17.1).  Else 32 x 32.  Other depths and widths, and experts, take the form for any shape.
 //
-// The gated form takes the same tiles over all 2 I columns; its 16-row tile is 16 gate and 16 up columns wide.  It exists for whole
+// The gated form takes the same tiles over all 2 I columns; its 16-row tile is 16 gate and 16 up columns wide.  It exists for any number of rows for whole
 // blocks and I a multiple of 32; the launch it saves and the [gate | up] rows' way through memory are 5.8 us of a step of 225 rows (1024
 // wide, 4096 MLP: 136.9 -> 131.1 us).
 namespace {
@@ -452,16 +543,24 @@ hipError_t launch_f32_tiles(const void *X, int ldx, const void *W, const void *R
 }
 
 template <int MT, int NT, class EP>
-hipError_t launch_f32_quads(const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, const EP &ep, hipStream_t s) {
-#define DYN_QUADS(XQUADS)                                                                                                                 \
-    hipLaunchKernelGGL((gemm_f32_quads_kernel<MT, NT, XQUADS, EP>), dim3((N + NT - 1) / NT, (rows + MT - 1) / MT), dim3(kF32Chains * 64), 0, s, \
-                       (const float *)X, ldx, (const float *)W, (const float *)R, (float *)Y, rows, N, K, ep)
-    if constexpr (MT == 16)
+hipError_t launch_f32_quads(const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, const F32Norm &norm, const EP &ep,
+                            hipStream_t s) {
+#define DYN_QUADS(XQUADS, NORM)                                                                                                                 \
+    hipLaunchKernelGGL((gemm_f32_quads_kernel<MT, NT, XQUADS, NORM, EP>), dim3((N + NT - 1) / NT, (rows + MT - 1) / MT), dim3(kF32Chains * 64), 0, s, \
+                       (const float *)X, ldx, (const float *)W, (const float *)R, (float *)Y, rows, N, K, norm, ep)
+    if constexpr (MT == 16) {
+        if constexpr (EP::PAIRS)
+            if (norm.g) {
+                if (rows <= 8) DYN_QUADS(false, true);
+                else DYN_QUADS(true, true);
+                return hipGetLastError();
+            }
         if (rows <= 8) {
-            DYN_QUADS(false);
+            DYN_QUADS(false, false);
             return hipGetLastError();
         }
-    DYN_QUADS(true);
+    }
+    DYN_QUADS(true, false);
 #undef DYN_QUADS
     return hipGetLastError();
 }
@@ -477,25 +576,34 @@ int f32_pitch(const F32Plain &, int N) { return N; }
 int f32_pitch(const F32Gated &ep, int) { return ep.ldy; }
 
 template <class EP>
-hipError_t launch_f32_whole(const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, const EP &ep, hipStream_t s) {
-    if (f32_few(rows, N, true)) return launch_f32_quads<16, EP::PAIRS ? 32 : 16>(X, ldx, W, R, Y, rows, N, K, ep, s);
+hipError_t launch_f32_whole(const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, const F32Norm &norm, const EP &ep,
+                            hipStream_t s) {
+    if (f32_few(rows, N, true)) return launch_f32_quads<16, EP::PAIRS ? 32 : 16>(X, ldx, W, R, Y, rows, N, K, norm, ep, s);
     if constexpr (!EP::ROTARY)
         if (f32_direct(X, ldx, W, rows, N)) return launch_f32_tiles<EP::PAIRS>(X, ldx, W, R, Y, rows, N, K, f32_pitch(ep, N), s);
-    return launch_f32_quads<32, 32>(X, ldx, W, R, Y, rows, N, K, ep, s);
+    return launch_f32_quads<32, 32>(X, ldx, W, R, Y, rows, N, K, norm, ep, s);
 }
 
 template <int MT, int NT, class EP>
 hipError_t launch_f32_any(const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, const GemmGroups &gr, const EP &ep,
-                          hipStream_t s) {
-    hipLaunchKernelGGL((gemm_f32_kernel<MT, NT, EP>), dim3((N + NT - 1) / NT, (rows + MT - 1) / MT, std::max(gr.n_groups, 1)), dim3(kF32Chains * 64), 0, s,
-                       (const float *)X, ldx, (const float *)W, (const float *)R, (float *)Y, rows, N, K, gr, ep);
+                          hipStream_t s, const F32Norm &norm = F32Norm{nullptr, 0.f}) {
+#define DYN_ANY(NORM)                                                                                                                                  \
+    hipLaunchKernelGGL((gemm_f32_kernel<MT, NT, NORM, EP>), dim3((N + NT - 1) / NT, (rows + MT - 1) / MT, std::max(gr.n_groups, 1)), dim3(kF32Chains * 64), \
+                       0, s, (const float *)X, ldx, (const float *)W, (const float *)R, (float *)Y, rows, N, K, gr, norm, ep)
+    if constexpr (MT == 16 && EP::PAIRS)
+        if (norm.g) {
+            DYN_ANY(true);
+            return hipGetLastError();
+        }
+    DYN_ANY(false);
+#undef DYN_ANY
     return hipGetLastError();
 }
 }  // namespace
 
 hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const void *R, void *Y, int max_rows, int N, int K,
                            const GemmGroups &gr, hipStream_t s) {
-    if (!gr.n_groups && f32_whole(N, K)) return launch_f32_whole(X, ldx, W, R, Y, max_rows, N, K, F32Plain{}, s);
+    if (!gr.n_groups && f32_whole(N, K)) return launch_f32_whole(X, ldx, W, R, Y, max_rows, N, K, F32Norm{nullptr, 0.f}, F32Plain{}, s);
     const int groups = std::max(gr.n_groups, 1);
     if (f32_few(max_rows, N, false, groups)) return launch_f32_any<16, 16>(X, ldx, W, R, Y, max_rows, N, K, gr, F32Plain{}, s);
     if (f32_tiles(max_rows, N, 64) * groups >= 256) return launch_f32_any<64, 64>(X, ldx, W, R, Y, max_rows, N, K, gr, F32Plain{}, s);
@@ -505,8 +613,23 @@ hipError_t launch_gemm_f32(const void *X, int ldx, const void *W, const void *R,
 // (From I = 64 on: a narrower activation's padded rows are longer than [gate | up] rows, and a plan's workspace would grow.)
 bool gemm_f32_gated_supported(int N2, int K) { return f32_whole(N2, K) && N2 % 64 == 0 && N2 >= 128; }
 
-hipError_t launch_gemm_f32_gated(const void *X, int ldx, const void *W, void *Y, int ldy, int rows, int N2, int K, hipStream_t s) {
-    return launch_f32_whole(X, ldx, W, nullptr, Y, rows, N2, K, F32Gated{ldy}, s);
+// Other depths: tiles of 16 + 16 columns, few rows or few tiles (a step of 256 wide, 4 / 32 rows 39.4 / 45.9 -> 37.8 / 43.7 us; 768 wide, 8 rows 60.2 -> 56.6).
+bool gemm_f32_gated_rows_supported(int rows, int N2, int K) {
+    return gemm_f32_gated_supported(N2, K) || (N2 % 64 == 0 && N2 >= 128 && !f32_whole(N2, K) && f32_few(rows, N2, false));
+}
+
+// The norm in the same launch: rows of up to 1024, 8192 elements of X in all, the step with norms of their own -> in the projections: 256 wide 1 / 8 /
+// 16 / 32 rows 36.1 / 42.3 / 43.4 / 43.8 -> 32.7 / 38.8 / 41.4 / 41.8 us; 512 wide 1 / 8 / 16 rows 41.1 / 47.4 / 48.6 -> 37.8 / 44.7 / 47.8; 1024
+// wide 1 / 4 / 8 rows 47.3 / 49.0 / 49.9 -> 45.3 / 46.8 / 49.3.  Beyond, a workgroup's own pass over X is longer than the launch: 512 wide 24
+// rows 48.4 -> 48.6, 1024 wide 16 rows 52.2 -> 54.4, 2048 wide 1 / 8 rows 84.6 / 91.5 -> 87.3 / 97.3, 4096 wide 8 rows 163 -> 166.
+bool gemm_f32_norm_supported(int rows, int N, int K) {
+    return K % 256 == 0 && K <= 1024 && (long)rows * K <= 8192 && f32_few(rows, N, f32_whole(N, K));
+}
+
+hipError_t launch_gemm_f32_gated(const void *X, int ldx, const void *W, void *Y, int ldy, int rows, int N2, int K, const GemmNorm &norm, hipStream_t s) {
+    const F32Norm nm{(const float *)norm.g, norm.eps};
+    if (f32_whole(N2, K)) return launch_f32_whole(X, ldx, W, nullptr, Y, rows, N2, K, nm, F32Gated{ldy}, s);
+    return launch_f32_any<16, 32>(X, ldx, W, nullptr, Y, rows, N2, K, GemmGroups{}, F32Gated{ldy}, s, nm);
 }
 
 // The rotary form: tiles of 16 + 16 columns for few rows or few tiles at any depth, and 32 x 32 of whole blocks, where a
@@ -518,10 +641,12 @@ bool gemm_f32_rope_supported(const void *X, int ldx, const void *W, int rows, in
     return 64 % sh.head_dim == 0 && (f32_few(rows, N, true) || !f32_direct(X, ldx, W, rows, N));
 }
 
-hipError_t launch_gemm_f32_rope(const void *X, int ldx, const void *W, void *Y, int rows, int N, int K, const GemmEpilogue &rope, hipStream_t s) {
+hipError_t launch_gemm_f32_rope(const void *X, int ldx, const void *W, void *Y, int rows, int N, int K, const GemmNorm &norm, const GemmEpilogue &rope,
+                                hipStream_t s) {
+    const F32Norm nm{(const float *)norm.g, norm.eps};
     const F32Rotary ep{rope.seq_of_token, rope.pos_of_token, rope.block_table, (float *)rope.k_cache, (float *)rope.v_cache, *rope.rope, *rope.shape};
-    if (f32_whole(N, K)) return launch_f32_whole(X, ldx, W, nullptr, Y, rows, N, K, ep, s);
-    return launch_f32_any<16, 32>(X, ldx, W, nullptr, Y, rows, N, K, GemmGroups{}, ep, s);
+    if (f32_whole(N, K)) return launch_f32_whole(X, ldx, W, nullptr, Y, rows, N, K, nm, ep, s);
+    return launch_f32_any<16, 32>(X, ldx, W, nullptr, Y, rows, N, K, GemmGroups{}, ep, s, nm);
 }
 
 }  // namespace dyn

@@ -227,6 +227,22 @@ def test_merge_of_every_number_of_chunks(dtype, n_q, n_kv, hd):
     say("%d heads of %d: %.2e" % (n_q, hd, check_against_oracle(w, data, y, k, v)))
 
 
+# fp32 steps whose projections normalise their rows themselves (256 wide to 32 rows, 768 to 10, 1024 to 8) and gate at any depth, in turn with
+# ones that do not (a micro-batch or the batch past the line, 2048 wide): the same bits, over two layers.
+@pytest.mark.parametrize("hidden,n_q,n_kv,hd,inter,cut,rows", [
+    (256, 4, 4, 64, 1024, 3, 4), (256, 4, 2, 64, 160, 32, 65), (256, 2, 2, 64, 96, 17, 32), (768, 12, 12, 64, 3072, 10, 21), (1024, 16, 4, 64, 512, 8, 17),
+    (1024, 8, 2, 128, 64, 1, 8), (512, 8, 8, 32, 1024, 9, 16), (2048, 4, 4, 64, 64, 1, 3), (260, 4, 4, 64, 128, 2, 9)])
+def test_fp32_norm_and_gate_inside_the_projections(hidden, n_q, n_kv, hd, inter, cut, rows):
+    sh = gen.LayerShape("f32", hidden, n_q, n_kv, hd, inter, n_layers=2)
+    w = gen.Workload("norm_in", sh, tuple((1, 1 + (7 * i) % 50) for i in range(rows)), 300 + rows, (0, cut, rows))
+    data = gen.generate(w)
+    data["x"] = data["x"] * torch.logspace(-3, 3, rows)[:, None]
+    y, k, v = both_schedules(w, data)
+    err = check_against_oracle(w, data, y, k, v)
+    say("%d rows of %d: %.2e" % (rows, hidden, err))
+    assert err < 5e-6                                        # two layers of what one layer's test allows
+
+
 # The same inside the fp32 projection: tiles of any depth (256, 68) and of whole blocks (512, 1024), 16 and 32 rows high, heads of 32, 64 and
 # 256, pages of 16 and 48.  Where the batch or one of its parts keeps the launch of its own - more rows (the first two, whose whole batch
 # takes 64 x 64 tiles and tiles of any depth), heads of 128 and 16 - it is the same bits.
