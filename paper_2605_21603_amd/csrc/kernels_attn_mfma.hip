@@ -19,6 +19,7 @@
 // split-KV arrays and attn_combine_kernel merges chunks in order.
 #include <algorithm>
 
+#include "attn_prefill.h"
 #include "common.h"
 #include "kernels.h"
 
@@ -55,8 +56,9 @@ struct AttnItem {
     const int32_t *bt;                // block-table row of the group's sequence
 };
 
-template <int NQG>
-__global__ __launch_bounds__(256, NQG == 1 ? 2 : 1) void attn_mfma_kernel(const bf16_t *__restrict__ qkv,
+// block: the workgroup's place among the n_blocks of WAVES waves that walk the list.
+template <int NQG, int WAVES>
+__device__ __forceinline__ void attn_decode_items(const bf16_t *__restrict__ qkv,
                                                            const int32_t *__restrict__ seq_of_token,
                                                            const int32_t *__restrict__ pos_of_token,
                                                            const int32_t *__restrict__ block_table,
@@ -64,10 +66,10 @@ __global__ __launch_bounds__(256, NQG == 1 ? 2 : 1) void attn_mfma_kernel(const 
                                                            const bf16_t *__restrict__ v_cache,
                                                            bf16_t *__restrict__ out, int ld_out,
                                                            float *__restrict__ part_o, float *__restrict__ part_ml,
-                                                           AttnShape sh, const int32_t *__restrict__ plan) {
+                                                           AttnShape sh, const int32_t *__restrict__ plan, int block, int n_blocks) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_items = plan[0] * sh.n_kv;
-    const int n_waves = gridDim.x * 4;
+    const int n_waves = n_blocks * WAVES;
     const int G = sh.n_q / sh.n_kv, TG = 16 / G;
     const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
     const int col_tok = lr / G, col_head = lr % G;   // MFMA column lr of set q = (token q * TG + col_tok, q head col_head)
@@ -78,7 +80,7 @@ __global__ __launch_bounds__(256, NQG == 1 ? 2 : 1) void attn_mfma_kernel(const 
     // items: 19.4 -> 9 us; 13 tokens behind 3000, 1248 items: 39 -> 30; 40 behind 2000, 2.5 rounds: 66 -> 63).  From
     // four rounds on all of memory is busy either way, and a chunk's kv heads stay side by side (200 tokens up to 8000
     // positions: 604 us, dealt over the workgroups 608).
-    const int gw = n_items < 4 * n_waves ? wave * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x * 4 + wave;
+    const int gw = n_items < 4 * n_waves ? wave * n_blocks + block : block * WAVES + wave;
     int round = 0;
     auto item_at = [&](int k) { return k * n_waves + ((k & 1) ? n_waves - 1 - gw : gw); };
     int item = item_at(0);
@@ -268,6 +270,56 @@ __global__ __launch_bounds__(256, NQG == 1 ? 2 : 1) void attn_mfma_kernel(const 
 #undef DYN_ATTN_COMPUTE
 }
 
+template <int NQG>
+__global__ __launch_bounds__(256, NQG == 1 ? 2 : 1) void attn_mfma_kernel(const bf16_t *__restrict__ qkv, const int32_t *__restrict__ seq_of_token,
+                                                           const int32_t *__restrict__ pos_of_token, const int32_t *__restrict__ block_table,
+                                                           const bf16_t *__restrict__ k_cache, const bf16_t *__restrict__ v_cache,
+                                                           bf16_t *__restrict__ out, int ld_out, float *__restrict__ part_o,
+                                                           float *__restrict__ part_ml, AttnShape sh, const int32_t *__restrict__ plan) {
+    attn_decode_items<NQG, 4>(qkv, seq_of_token, pos_of_token, block_table, k_cache, v_cache, out, ld_out, part_o, part_ml, sh, plan, blockIdx.x, gridDim.x);
+}
+
+// Workgroups of a mixed launch that start on query blocks.  The share that would finish both lists together if each CU had its part of memory's
+// rate: memory is busy with fewer, so the decode list ends first, and its workgroups take query blocks after it; the other way round
+// there is no way back (2048 prompt tokens beside 128 decodes behind 4000 positions, half of the CUs on query blocks: a step of 1414 us as two
+// launches 1525).  Costs in us of one CU: a position of a decode item 512 bytes at 19.5 GB/s, a query block's tile of 64 positions 6 beside
+// decodes; the first, the middle and the last query block stand for all.  The share is rounded to whole rounds of query blocks, which are long beside the
+// launch (2048 tokens beside 64 decodes, 384 of them, on 88 / 112 / 128 workgroups: 154 / 172 / 148 us); up to a quarter of the workgroups each
+// takes one.
+__device__ __forceinline__ int mixed_prompt_groups(const int32_t *__restrict__ plan, const int32_t *__restrict__ plan_multi,
+                                                   const int32_t *__restrict__ pos_of_token, const int32_t *__restrict__ ct_of_token, const AttnShape &sh,
+                                                   int groups) {
+    const int entries = plan_multi[0];
+    auto tiles = [&](int e) {
+        const int t = plan_multi[2 + 2 * e], packed = plan_multi[3 + 2 * e], ct = ct_of_token[t];
+        return (min(ct, pos_of_token[t] + (packed >> 20) - (packed & 0xfffff) * ct) + 63) / 64;
+    };
+    const float prompts = 1.5f * (tiles(0) + 2 * tiles(entries / 2) + tiles(entries - 1)) * entries, decodes = 0.026f * PS * sh.chunk_pages * plan[0];
+    const int items = entries * sh.n_kv;
+    const float share = max(groups * prompts / (prompts + decodes), 1.0f);
+    const int rounds = items <= groups / 4 ? 1 : max((int)(items / share + 0.5f), 1);
+    return max(min(((items + rounds - 1) / rounds + 7) / 8 * 8, groups - 8), min(8, groups / 2));
+}
+
+// Decodes and prompts of one dispatch in one launch, a workgroup per CU: the first (an equal share of every XCD's) claim query blocks, the others
+// walk the decode list and then claim query blocks too.  Decodes wait for memory and prompts for the matrix cores: one behind the
+// other, each leaves what the other needs idle.  Two launches -> one: 2048 prompt tokens + 64 decodes behind 2048 positions 117 + 67 -> 151 us; steps
+// of 60 + 30, 512 + 64, 1000 + 128 and 2500 + 100 tokens 198 / 542 / 858 / 1487 -> 186 / 521 / 821 / 1444 us, 4096 + 64 2052 -> 2056.
+__global__ __launch_bounds__(prefill::kWaves * 64, 1) void attn_mixed_kernel(const bf16_t *__restrict__ qkv, const int32_t *__restrict__ seq_of_token,
+                                                           const int32_t *__restrict__ pos_of_token, const int32_t *__restrict__ block_table,
+                                                           const bf16_t *__restrict__ k_cache, const bf16_t *__restrict__ v_cache,
+                                                           bf16_t *__restrict__ out, int ld_out, float *__restrict__ part_o,
+                                                           float *__restrict__ part_ml, AttnShape sh, const int32_t *__restrict__ plan,
+                                                           const int32_t *__restrict__ plan_multi, int32_t *__restrict__ counter,
+                                                           const int32_t *__restrict__ ct_of_token) {
+    const int prompts = mixed_prompt_groups(plan, plan_multi, pos_of_token, ct_of_token, sh, gridDim.x);
+    if ((int)blockIdx.x >= prompts)
+        attn_decode_items<1, prefill::kWaves>(qkv, seq_of_token, pos_of_token, block_table, k_cache, v_cache, out, ld_out, part_o, part_ml, sh, plan,
+                                              (int)blockIdx.x - prompts, (int)gridDim.x - prompts);
+    prefill::attn_prefill_items(qkv, seq_of_token, pos_of_token, block_table, k_cache, v_cache, out, ld_out, part_o, part_ml, sh, plan_multi, counter,
+                                ct_of_token);
+}
+
 hipError_t launch_attention_generic(int dtype, const void *qkv, const int32_t *seq_of_token,
                                     const int32_t *pos_of_token, const int32_t *block_table, const void *k_cache,
                                     const void *v_cache, void *out, int ld_out, float *part_o, float *part_ml,
@@ -296,15 +348,26 @@ hipError_t launch_attention(int dtype, const void *qkv, const int32_t *seq_of_to
     // wave index): two per CU of the partition the stream runs on
     const int groups = sh.n_cus > 0 && 2 * sh.n_cus < kPersistentGroups ? 2 * sh.n_cus : kPersistentGroups;
     const int grid = (int)std::min<long>(max_items, groups);        // a workgroup per item while they are few
-    if (any_single) {
+    if (any_single && any_multi) {
+        static bool attr_set = false;
+        if (!attr_set) {
+            e = hipFuncSetAttribute((const void *)attn_mixed_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, prefill::lds_bytes());
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+        hipLaunchKernelGGL(attn_mixed_kernel, dim3(groups / 2), dim3(prefill::kWaves * 64), prefill::lds_bytes(), s, (const bf16_t *)qkv, seq_of_token, pos_of_token,
+                           block_table, (const bf16_t *)k_cache, (const bf16_t *)v_cache, (bf16_t *)out, ld_out, part_o, part_ml, sh, lists.single, lists.multi,
+                           lists.multi + 1, lists.ct_of_token);
+        e = hipGetLastError();
+    } else if (any_single) {
         hipLaunchKernelGGL(attn_mfma_kernel<1>, dim3(grid), dim3(256), 0, s, (const bf16_t *)qkv, seq_of_token,
                            pos_of_token, block_table, (const bf16_t *)k_cache, (const bf16_t *)v_cache, (bf16_t *)out, ld_out, part_o,
                            part_ml, sh, lists.single);
         e = hipGetLastError();
-    }
-    if (e == hipSuccess && any_multi)
+    } else if (any_multi) {
         e = launch_attention_prefill(qkv, seq_of_token, pos_of_token, block_table, k_cache, v_cache, out, ld_out, part_o, part_ml, sh,
                                      lists.multi, lists.ct_of_token, max_items, groups, s);
+    }
     if (e == hipSuccess && mid) e = hipEventRecord(mid, s);
     if (e != hipSuccess) return e;
     return launch_attention_combine(dtype, true, part_o, part_ml, pos_of_token, lists.ct_of_token, out, ld_out, sh, rows, s, lists.multi + 1, true);

@@ -243,6 +243,20 @@ def test_fp32_norm_and_gate_inside_the_projections(hidden, n_q, n_kv, hd, inter,
     assert err < 5e-6                                        # two layers of what one layer's test allows
 
 
+# Decodes beside a prompt in one launch: one query block and one decode, more blocks than half of the workgroups and few, decodes of no
+# round and of several; the prompt and the decodes as micro-batches of their own are launches of their own, with the same bits; on a partition of 64 CUs too.
+@pytest.mark.parametrize("n_q,n_kv,prompt,cached,n_decode,ctx", [
+    (1, 1, 2, 0, 1, 1), (4, 1, 33, 7, 130, 700), (32, 8, 300, 600, 3, 2000), (12, 12, 700, 0, 40, 300), (16, 16, 1500, 0, 9, 4000), (3, 1, 81, 1000, 300, 64)])
+def test_decodes_beside_a_prompt(n_q, n_kv, prompt, cached, n_decode, ctx):
+    seqs = [(prompt, prompt + cached)] + [(1, 1 + (ctx - 1) * (n_decode - i) // n_decode) for i in range(n_decode)]
+    w = workload("mixed", "bf16", 128, n_q, n_kv, 128, 128, seqs, seed=prompt)
+    data = gen.generate(w)
+    y, k, v = both_schedules(w, data)
+    y_part, _, _ = GpuRun(w, data).run(B.nano_schedule([0, w.nano_rows[-1]], chain=B.DENSE_CHAIN, partitions=[1], cu_masks=[[0xff] * 8]))
+    assert torch.equal(y.view(torch.uint8), y_part.view(torch.uint8))
+    say("%d + %d: %.2e" % (prompt, n_decode, check_against_oracle(w, data, y, k, v)))
+
+
 # The same inside the fp32 projection: tiles of any depth (256, 68) and of whole blocks (512, 1024), 16 and 32 rows high, heads of 32, 64 and
 # 256, pages of 16 and 48.  Where the batch or one of its parts keeps the launch of its own - more rows (the first two, whose whole batch
 # takes 64 x 64 tiles and tiles of any depth), heads of 128 and 16 - it is the same bits.
