@@ -180,8 +180,13 @@ int gemm_split_k(int dtype, int N, int K, int groups) {
 }
 
 namespace {
-bool gemm_many_rows(int rows, int N) {      // enough 128 x 128 tiles for the many-row regime
-    return N % kBigBN == 0 && (N / kBigBN) * ((rows + kBigMT - 1) / kBigMT) >= 256;
+// Enough 128 x 128 tiles for the many-row regime.  One row of them is not many rows, however wide: to 1.5 rounds of the few-row form's
+// workgroups its deeper ring wins, beyond two many-row workgroups a CU do (layers' steps, many -> few, 1 / 16 / 64 / 128 rows: 256 tiles, 6144 wide,
+// 220 / 240 / 285 / 353 -> 185 / 202 / 255 / 332 us; 296, 3584 wide, 148 / 163 / 195 / 239 -> 141 / 155 / 195 / 238; 448, 8192 wide, 336 / 376 / 443 / 537
+// -> 343 / 383 / 449 / 540).
+bool gemm_many_rows(int rows, int N) {
+    const int nt = N / kBigBN;
+    return N % kBigBN == 0 && nt * ((rows + kBigMT - 1) / kBigMT) >= 256 && (rows > kBigMT || nt >= 384);
 }
 
 // 256 x 256 tiles, eight waves of 64 x 128 each: half the operand bytes moved into LDS per FLOP

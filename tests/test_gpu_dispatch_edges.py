@@ -257,6 +257,17 @@ def test_decodes_beside_a_prompt(n_q, n_kv, prompt, cached, n_decode, ctx):
     say("%d + %d: %.2e" % (prompt, n_decode, check_against_oracle(w, data, y, k, v)))
 
 
+# A wide gate/up projection (256 and 383 tiles) of up to 128 rows on the few-row form gives the many-row form's bits (129 rows and more).
+@pytest.mark.parametrize("inter,few", [(16384, 1), (24512, 128)])
+def test_wide_projections_of_few_rows(inter, few):
+    assert [gemm_path(r, 2 * inter, 256).kind for r in (1, 128)] == [0, 0] and gemm_path(400, 2 * inter, 256).kind != 0     # GEMM_FEW
+    w = workload("wide_few", "bf16", 256, 2, 1, 128, inter, [(1, 1 + i % 7) for i in range(few + 400)], seed=inter)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, few, few + 400))
+    data = gen.generate(w)
+    y, k, v = both_schedules(w, data)
+    say("%d columns: %.2e" % (2 * inter, check_against_oracle(w, data, y, k, v)))
+
+
 # The same inside the fp32 projection: tiles of any depth (256, 68) and of whole blocks (512, 1024), 16 and 32 rows high, heads of 32, 64 and
 # 256, pages of 16 and 48.  Where the batch or one of its parts keeps the launch of its own - more rows (the first two, whose whole batch
 # takes 64 x 64 tiles and tiles of any depth), heads of 128 and 16 - it is the same bits.
