@@ -91,13 +91,13 @@ __device__ __forceinline__ int gemm_band(int rows, int N, int K) {
 }
 inline int gemm_band_grid(int n_tiles, int m_tiles) { return (n_tiles * m_tiles + 7) / 8 * 8; }
 
-// Tile of this workgroup in a launch whose tiles cover the whole depth, in bands.  Workgroup ids are dealt
+// Tile of workgroup `block` in a launch whose tiles cover the whole depth, in bands.  Workgroup ids are dealt
 // round-robin to the 8 XCDs; an XCD takes a contiguous eighth of the tiles in an order that walks bands of
 // `band` n tiles down all m tiles, so that what it works on at one time is about as many W rows as X rows.
 // (In n-tile order the 32 CUs of an XCD hold two or four n tiles and every m tile: each XCD then reads all
 // of X, eight times the matrix in all.)  False: no tile.
-__device__ __forceinline__ bool band_tile(int nt, int m_tiles, int band, int &n_tile, int &m_tile) {
-    const int v = blockIdx.x / 8, total = nt * m_tiles, chunk = (total + 7) / 8, idx = (int)(blockIdx.x % 8) * chunk + v;
+__device__ __forceinline__ bool band_tile(int block, int nt, int m_tiles, int band, int &n_tile, int &m_tile) {
+    const int v = block / 8, total = nt * m_tiles, chunk = (total + 7) / 8, idx = block % 8 * chunk + v;
     if (v >= chunk || idx >= total) return false;
     const int b = idx / (band * m_tiles), r = idx - b * band * m_tiles, width = min(band, nt - b * band);
     m_tile = r / width;

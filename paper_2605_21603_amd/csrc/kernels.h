@@ -121,6 +121,12 @@ hipError_t launch_gemm_rows16(hipStream_t s, const void *X, int ldx, const void 
 // Many rows, split-K planes folded in registers, 256 x 128 tiles (kernels_gemm_wide.hip; launch_gemm calls it).
 hipError_t launch_gemm_fold(int grid, hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N,
                             int K, int S);
+// The same rows without planes, on 256-wide tiles of several heights: tiles[i] m tiles of 64 (i + 1) rows.  wide_cut: the heights for a launch, if they
+// beat `now` (in rounds of 256 x 256 tiles); rows x N has to be GEMM_WIDE's.
+struct WideCut { int tiles[4]; };
+bool wide_cut(int rows, int N, float now, WideCut *out);
+hipError_t launch_gemm_cut(bool gated, hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int ldy, int rows, int N, int K,
+                           const WideCut &cut);
 // Expert-grouped projection without planes on 256-wide tiles of a height chosen per expert (the grouped launchers
 // call it); gated: silu(gate) * up to Y, else Y, or fp32 to P with gr.force_planes.
 hipError_t launch_gemm_experts_wide(bool gated, hipStream_t s, const void *X, int ldx, const void *W, void *Y, int ldy, float *P, int N,

@@ -35,7 +35,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && (BN + MT) * ROWB * NS <= 72 * 
     const int u = blockIdx.x % 8, v = blockIdx.x / 8;
     int m_tile, ns;
     if (BANDS) {
-        if (!band_tile(N / BN, m_tiles, gemm_band(M, N, K), ns, m_tile)) return;
+        if (!band_tile(blockIdx.x, N / BN, m_tiles, gemm_band(M, N, K), ns, m_tile)) return;
     } else {
         // Tiles that share W rows (the m tiles of one (n tile, plane)) get ids 8 apart: same XCD,
         // same L2, adjacent in time.
@@ -312,6 +312,16 @@ GemmPath gemm_path(int dtype, int rows, int N, int K) {
     return p;
 }
 
+namespace {
+// A GEMM_WIDE launch on tiles of several heights, where that is the faster way; else p as it is: rounds of 256 tiles, and the last rows' launch
+// at what it takes beside a round (gate/up of 28672 columns, 64 / 128 / 256 rows: 48 / 60 / 76 us, a round 122).
+bool gemm_cut(const GemmPath &p, int rows, int N, WideCut *cut) {
+    if (p.kind != GEMM_WIDE) return false;
+    const float tail = p.tail_rows == 0 ? 0.f : p.tail_rows <= 64 ? 0.40f : p.tail_rows <= 128 ? 0.49f : 0.62f;
+    return wide_cut(rows, N, (p.workgroups + 255) / 256 + tail, cut);
+}
+}  // namespace
+
 bool gemm_uses_plane_buffer(int dtype, int rows, int N, int K) {
     if (dtype == 0 || rows <= 0) return false;
     const GemmPath p = gemm_path(dtype, rows, N, K);
@@ -353,6 +363,13 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
         return e0;
     }
     const GemmPath p = gemm_path(dtype, rows, N, K);
+    WideCut cut;
+    if (gemm_cut(p, rows, N, &cut)) {
+        hipError_t ec = launch_gemm_cut(false, s, X, ldx, W, R, Y, N, rows, N, K, cut);
+        if (ec == hipSuccess && mid) ec = hipEventRecord(mid, s);
+        if (ec == hipSuccess && has_ep) ec = run_epilogue(dtype, *ep, Y, rows, N, s);
+        return ec;
+    }
     if (p.tail_rows) {         // the last rows in a launch of their own (own tiles, own planes and reduce)
         const int head = rows - p.tail_rows;
         GemmEpilogue tail_ep;
@@ -432,6 +449,11 @@ hipError_t launch_gemm_gated(int dtype, const void *X, int ldx, const void *W, v
                                             : launch_gemm_experts(true, s, X, ldx, W, Y, ldy, nullptr, 0, max_rows, N2, K, 1, gr);
     } else {
         const GemmPath p = gemm_path(1, max_rows, N2, K);          // split factor 1: no planes on any path
+        WideCut cut;
+        if (gemm_cut(p, max_rows, N2, &cut)) {
+            e = launch_gemm_cut(true, s, X, ldx, W, nullptr, Y, ldy, max_rows, N2, K, cut);
+            return e == hipSuccess && mid ? hipEventRecord(mid, s) : e;
+        }
         if (p.tail_rows) {     // the last rows in a launch of their own (never a wide one: at most 256 rows)
             const int head = max_rows - p.tail_rows;
             e = launch_gemm_gated(dtype, (const bf16_t *)X + (size_t)head * ldx, ldx, W, (bf16_t *)Y + (size_t)head * ldy, ldy, gr,

@@ -15,7 +15,7 @@ __global__ __launch_bounds__(512, 1) void gemm_fold_kernel(const bf16_t *__restr
                                                            int S) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     int n_tile, m_tile;
-    if (!band_tile(N / 256, (M + 127) / 128, gemm_band(M, N, K), n_tile, m_tile)) return;
+    if (!band_tile(blockIdx.x, N / 256, (M + 127) / 128, gemm_band(M, N, K), n_tile, m_tile)) return;
     gemm_tile<256, 128, true, 3, false, 8, true>(lds, X, ldx, W, R, Y, N, nullptr, 0, M, N, K, S, nullptr, 1, false, n_tile, 0, m_tile * 128, 0);
 }
 
@@ -181,6 +181,101 @@ hipError_t launch_gemm_experts(bool gated, hipStream_t s, const void *X, int ldx
                      : launch_experts<false, true>(s, X, ldx, W, Y, ldy, P, plane_stride, N, K, S, gr);
     return gated ? launch_experts<true, false>(s, X, ldx, W, Y, ldy, P, plane_stride, N, K, S, gr)
                  : launch_experts<false, false>(s, X, ldx, W, Y, ldy, P, plane_stride, N, K, S, gr);
+}
+
+// Many rows without planes on 256-wide tiles of several heights, tallest first.  256 of them run at a time and a launch of one height is a whole number
+// of rounds; heights that add up to the rows let every CU's share be about the same (wide_cut).  Each height's tiles in bands.
+template <bool GATED>
+__global__ __launch_bounds__(512, 1) void gemm_cut_kernel(const bf16_t *__restrict__ X, int ldx, const bf16_t *__restrict__ W, const bf16_t *__restrict__ R,
+                                                          bf16_t *__restrict__ Y, int ldy, int M, int N, int K, WideCut cut) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    const int nt = N / 256;
+    int block = blockIdx.x, size = 4, row0 = 0;
+    for (; size >= 1; --size) {
+        const int grid = (nt * cut.tiles[size - 1] + 7) / 8 * 8;
+        if (block < grid) break;
+        block -= grid;
+        row0 += cut.tiles[size - 1] * 64 * size;
+    }
+    int n_tile, m_tile;
+    if (size < 1 || !band_tile(block, nt, cut.tiles[size - 1], gemm_band(M, N, K), n_tile, m_tile)) return;
+    const int m0 = row0 + m_tile * 64 * size;
+    if (m0 >= M) return;
+#define DYN_BODY(MT, NS) gemm_tile<256, MT, false, NS, GATED, 8, true>(lds, X, ldx, W, R, Y, ldy, nullptr, 0, M, N, K, 1, nullptr, 1, false, n_tile, 0, m0, 0)
+    if (size == 4) DYN_BODY(256, 2);
+    else if (size == 3) DYN_BODY(192, 2);
+    else if (size == 2) DYN_BODY(128, 3);
+    else DYN_BODY(64, 4);
+#undef DYN_BODY
+}
+
+hipError_t launch_gemm_cut(bool gated, hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int ldy, int rows, int N, int K,
+                           const WideCut &cut) {
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void *)gemm_cut_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kExpertsLds);
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)gemm_cut_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kExpertsLds);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    int grid = 0;
+    for (int n : cut.tiles) grid += gemm_band_grid(N / 256, n);
+    if (gated)
+        hipLaunchKernelGGL(gemm_cut_kernel<true>, dim3(grid), dim3(512), kExpertsLds, s, (const bf16_t *)X, ldx, (const bf16_t *)W, (const bf16_t *)R, (bf16_t *)Y,
+                           ldy, rows, N, K, cut);
+    else
+        hipLaunchKernelGGL(gemm_cut_kernel<false>, dim3(grid), dim3(512), kExpertsLds, s, (const bf16_t *)X, ldx, (const bf16_t *)W, (const bf16_t *)R, (bf16_t *)Y,
+                           ldy, rows, N, K, cut);
+    return hipGetLastError();
+}
+
+// Longest of the 256 CUs' shares when n[i] tiles of cost[i], costs falling, each go to the CU that is free first.
+namespace {
+float longest_share(const int *n, const float *cost, int kinds) {
+    struct Level { float load; int cus; } lv[64];          // CUs by load
+    int levels = 1;
+    lv[0] = {0.f, 256};
+    for (int k = 0; k < kinds; ++k)
+        for (int left = n[k]; left > 0;) {
+            int low = 0;
+            for (int i = 1; i < levels; ++i)
+                if (lv[i].load < lv[low].load) low = i;
+            const int take = std::min(left, lv[low].cus);
+            left -= take;
+            const float load = lv[low].load + cost[k];
+            lv[low].cus -= take;
+            if (lv[low].cus == 0) lv[low] = lv[--levels];
+            int same = 0;
+            while (same < levels && lv[same].load != load) ++same;
+            if (same < levels) lv[same].cus += take;
+            else if (levels < 64) lv[levels++] = {load, take};
+            else return 1e30f;
+        }
+    float most = 0.f;
+    for (int i = 0; i < levels; ++i) most = std::max(most, lv[i].load);
+    return most;
+}
+}  // namespace
+
+// The heights with the shortest longest share, tallest tiles first: 192-, 128- and 64-row tiles take 0.80, 0.60 and 0.40 of a 256-row one.  From two
+// rounds on and where 4.5 % are to be had: a height's tiles walk all of W once more.  28672 columns 4096 deep, one height (and the last rows' launch) ->
+// heights of their own, 800 / 1100 / 1300 / 1700 / 2112 rows 232 / 291 / 334 / 407 / 460 -> 207 / 264 / 301 / 386 / 439 us, steps 546 / 665 / 747 / 888 / 1048 -> 524 /
+// 642 / 731 / 869 / 1023; outside the lines 600 rows 186 -> 198, 3000 rows 623 -> 626.
+bool wide_cut(int rows, int N, float now, WideCut *out) {
+    static const float cost[4] = {1.0f, 0.80f, 0.60f, 0.40f};             // 256, 192, 128, 64 rows
+    const int nt = N / 256, units = (rows + 63) / 64;
+    if (now < 2.0f) return false;
+    float best = now * 0.955f;
+    bool found = false;
+    for (int n3 = 0; n3 <= std::min(units / 3, 6); ++n3)
+        for (int n2 = 0; n2 <= std::min((units - 3 * n3) / 2, 3); ++n2) {
+            const int n1 = (units - 3 * n3 - 2 * n2) % 4, n4 = (units - 3 * n3 - 2 * n2) / 4;
+            if (n1 > 1) continue;
+            const int n[4] = {n4 * nt, n3 * nt, n2 * nt, n1 * nt};
+            const float t = longest_share(n, cost, 4);
+            if (t < best) { best = t; *out = WideCut{{n1, n2, n3, n4}}; found = true; }
+        }
+    return found;
 }
 
 }  // namespace dyn

@@ -268,6 +268,22 @@ def test_wide_projections_of_few_rows(inter, few):
     say("%d columns: %.2e" % (2 * inter, check_against_oracle(w, data, y, k, v)))
 
 
+# Gate/up launches cut into tiles of several heights (four 192-row m tiles and one of 64 for 800 rows, ..): every row once, with the bits of the
+# smaller launches' tiles; widths whose n tiles fill the bands and do not.
+@pytest.mark.parametrize("inter,rows,cut", [(14336, 800, 300), (14336, 1061, 40), (14336, 1300, 700), (14080, 1700, 500), (14336, 2112, 64)])
+def test_many_rows_on_tiles_of_several_heights(inter, rows, cut):
+    tiles, f = (ctypes.c_int * 4)(), B.lib()._ZN3dyn8wide_cutEiifPNS_7WideCutE
+    f.argtypes, f.restype = [ctypes.c_int, ctypes.c_int, ctypes.c_float, ctypes.c_void_p], ctypes.c_bool
+    p = gemm_path(rows, 2 * inter, 256)
+    assert p.kind == 2 and f(rows, 2 * inter, (p.workgroups + 255) // 256 + (0.4 if p.tail_rows else 0.0), tiles)      # GEMM_WIDE
+    assert 0 <= 64 * sum((i + 1) * n for i, n in enumerate(tiles)) - rows < 64
+    w = workload("heights", "bf16", 256, 2, 1, 128, inter, [(1, 1 + i % 5) for i in range(rows)], seed=rows)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, cut, rows))
+    data = gen.generate(w)
+    y, k, v = both_schedules(w, data)
+    say("%d rows, %s: %.2e" % (rows, list(tiles), check_against_oracle(w, data, y, k, v)))
+
+
 # The same inside the fp32 projection: tiles of any depth (256, 68) and of whole blocks (512, 1024), 16 and 32 rows high, heads of 32, 64 and
 # 256, pages of 16 and 48.  Where the batch or one of its parts keeps the launch of its own - more rows (the first two, whose whole batch
 # takes 64 x 64 tiles and tiles of any depth), heads of 128 and 16 - it is the same bits.

@@ -25,6 +25,8 @@ def hand_laid_loops(body):
 @pytest.mark.parametrize("kernel,tiles", [("gemm_fold_kernel", [(256, 128)]),
                                           ("gemm_experts_wide_kernelILb0E", [(256, 256), (256, 192), (256, 128), (256, 64)]),
                                           ("gemm_experts_wide_kernelILb1E", [(256, 256), (256, 192), (256, 128), (256, 64)]),
+                                          ("gemm_cut_kernelILb0E", [(256, 256), (256, 192), (256, 128), (256, 64)]),
+                                          ("gemm_cut_kernelILb1E", [(256, 256), (256, 192), (256, 128), (256, 64)]),
                                           ("gemm_experts_kernelILb0ELb0E", [(128, 256)]), ("gemm_experts_kernelILb1ELb0E", [(128, 256)])])
 def test_wide_loops_touch_no_operand_before_its_wait(lines, kernel, tiles):
     starts = [i for i, l in enumerate(lines) if l.startswith("_ZN3dyn") and l.split(";")[0].strip().endswith(":")]
