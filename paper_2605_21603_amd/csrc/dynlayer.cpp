@@ -796,7 +796,7 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
                 } else {
                     err = dyn::launch_gemm_gated(c.dtype, d.norm_in ? rowp(base + ws.x2, H) : rowp(base + ws.h, ws.ld_h), d.norm_in ? H : ws.ld_h,
                                                  w.w_gate_up, act, ws.ld_act, dyn::GemmGroups{}, rows, 2 * I, H, st, mid,
-                                                 dyn::GemmNorm{d.norm_in ? w.g_norm2 : nullptr, c.rms_eps});
+                                                 dyn::GemmNorm{d.norm_in ? w.g_norm2 : nullptr, c.rms_eps}, sh.n_cus);
                 }
                 break;
             }

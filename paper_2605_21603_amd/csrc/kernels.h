@@ -127,6 +127,12 @@ struct WideCut { int tiles[4]; };
 bool wide_cut(int rows, int N, float now, WideCut *out);
 hipError_t launch_gemm_cut(bool gated, hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int ldy, int rows, int N, int K,
                            const WideCut &cut);
+// Planes folded in registers, 128-wide tiles of several heights: tiles[i] m tiles of 96 + 32 i rows.  fold_cut: the heights for a launch, if they beat
+// p's one.
+struct FoldCut { int tiles[3]; };
+bool fold_cut(const GemmPath &p, int rows, int N, FoldCut *out);
+hipError_t launch_gemm_fold_cut(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int S,
+                                const FoldCut &cut);
 // Expert-grouped projection without planes on 256-wide tiles of a height chosen per expert (the grouped launchers
 // call it); gated: silu(gate) * up to Y, else Y, or fp32 to P with gr.force_planes.
 hipError_t launch_gemm_experts_wide(bool gated, hipStream_t s, const void *X, int ldx, const void *W, void *Y, int ldy, float *P, int N,
@@ -144,7 +150,7 @@ hipError_t launch_gemm_grouped(int dtype, const void *X, int ldx, const void *W,
 // the dispatch's first row, max_rows rows.  Grouped: as launch_gemm_grouped.
 bool gemm_gated_supported(int dtype, int N2, int K, bool experts);
 hipError_t launch_gemm_gated(int dtype, const void *X, int ldx, const void *W, void *Y, int ldy, const GemmGroups &gr, int max_rows,
-                             int N2, int K, hipStream_t s, hipEvent_t mid = nullptr, const GemmNorm &norm = GemmNorm{});
+                             int N2, int K, hipStream_t s, hipEvent_t mid = nullptr, const GemmNorm &norm = GemmNorm{}, int n_cus = 0);
 
 // MoE router for token rows: logits = h W_r^T in fp32, top_k largest (ties to the lower index),
 // softmax over the selected logits.  sel / wgt are [rows, top_k], largest logit first.

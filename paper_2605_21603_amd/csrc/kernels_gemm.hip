@@ -315,8 +315,8 @@ GemmPath gemm_path(int dtype, int rows, int N, int K) {
 namespace {
 // A GEMM_WIDE launch on tiles of several heights, where that is the faster way; else p as it is: rounds of 256 tiles, and the last rows' launch
 // at what it takes beside a round (gate/up of 28672 columns, 64 / 128 / 256 rows: 48 / 60 / 76 us, a round 122).
-bool gemm_cut(const GemmPath &p, int rows, int N, WideCut *cut) {
-    if (p.kind != GEMM_WIDE) return false;
+bool gemm_cut(const GemmPath &p, int rows, int N, int n_cus, WideCut *cut) {
+    if (p.kind != GEMM_WIDE || (n_cus > 0 && n_cus < 256)) return false;      // (shares of 256 CUs)
     const float tail = p.tail_rows == 0 ? 0.f : p.tail_rows <= 64 ? 0.40f : p.tail_rows <= 128 ? 0.49f : 0.62f;
     return wide_cut(rows, N, (p.workgroups + 255) / 256 + tail, cut);
 }
@@ -364,7 +364,7 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
     }
     const GemmPath p = gemm_path(dtype, rows, N, K);
     WideCut cut;
-    if (gemm_cut(p, rows, N, &cut)) {
+    if (gemm_cut(p, rows, N, n_cus, &cut)) {
         hipError_t ec = launch_gemm_cut(false, s, X, ldx, W, R, Y, N, rows, N, K, cut);
         if (ec == hipSuccess && mid) ec = hipEventRecord(mid, s);
         if (ec == hipSuccess && has_ep) ec = run_epilogue(dtype, *ep, Y, rows, N, s);
@@ -393,7 +393,9 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
 #define DYN_GEMM(BN, MT, INREG, NS, NW) \
     launch_gemm_bf16<BN, MT, INREG, NS, false, NW>(grid, s, X, ldx, W, R, Y, partial, plane_stride, rows, N, K, S)
     hipError_t e;
-    if (p.kind == GEMM_TALL) e = p.mt == 256 ? DYN_GEMM(128, 256, false, 3, 8) : p.mt == 384 ? DYN_GEMM(128, 384, false, 2, 8) : DYN_GEMM(128, 512, false, 2, 8);
+    FoldCut fold;
+    if ((n_cus <= 0 || n_cus >= 256) && fold_cut(p, rows, N, &fold)) e = launch_gemm_fold_cut(s, X, ldx, W, R, Y, rows, N, K, S, fold);
+    else if (p.kind == GEMM_TALL) e = p.mt == 256 ? DYN_GEMM(128, 256, false, 3, 8) : p.mt == 384 ? DYN_GEMM(128, 384, false, 2, 8) : DYN_GEMM(128, 512, false, 2, 8);
     else if (p.kind == GEMM_WIDE) e = DYN_GEMM(256, 256, false, 2, 8);
     else if (p.kind == GEMM_MANY && p.bn == 256) e = launch_gemm_fold(grid, s, X, ldx, W, R, Y, rows, N, K, S);
     else if (p.kind == GEMM_MANY && p.mt == 160) e = p.folded ? DYN_GEMM(kBigBN, 160, true, kBigNS, 4) : DYN_GEMM(kBigBN, 160, false, kBigNS, 4);
@@ -435,7 +437,7 @@ bool gemm_gated_supported(int dtype, int N2, int K, bool experts) {
 // act[rows or listed rows, N2/2] = silu(X Wg^T) * (X Wu^T) with W = [gate rows; up rows] ([N2, K]),
 // output row pitch ldy.  Plain (gr.n_groups = 0: X, Y offset to the dispatch) or expert-grouped.
 hipError_t launch_gemm_gated(int dtype, const void *X, int ldx, const void *W, void *Y, int ldy, const GemmGroups &gr, int max_rows,
-                             int N2, int K, hipStream_t s, hipEvent_t mid, const GemmNorm &norm) {
+                             int N2, int K, hipStream_t s, hipEvent_t mid, const GemmNorm &norm, int n_cus) {
     if (max_rows <= 0) return hipSuccess;
     hipError_t e;
     if (dtype == 0) {
@@ -450,14 +452,14 @@ hipError_t launch_gemm_gated(int dtype, const void *X, int ldx, const void *W, v
     } else {
         const GemmPath p = gemm_path(1, max_rows, N2, K);          // split factor 1: no planes on any path
         WideCut cut;
-        if (gemm_cut(p, max_rows, N2, &cut)) {
+        if (gemm_cut(p, max_rows, N2, n_cus, &cut)) {
             e = launch_gemm_cut(true, s, X, ldx, W, nullptr, Y, ldy, max_rows, N2, K, cut);
             return e == hipSuccess && mid ? hipEventRecord(mid, s) : e;
         }
         if (p.tail_rows) {     // the last rows in a launch of their own (never a wide one: at most 256 rows)
             const int head = max_rows - p.tail_rows;
             e = launch_gemm_gated(dtype, (const bf16_t *)X + (size_t)head * ldx, ldx, W, (bf16_t *)Y + (size_t)head * ldy, ldy, gr,
-                                  p.tail_rows, N2, K, s, nullptr);
+                                  p.tail_rows, N2, K, s, nullptr, norm, n_cus);
             if (e != hipSuccess) return e;
             max_rows = head;
         }

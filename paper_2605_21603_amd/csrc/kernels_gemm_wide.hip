@@ -231,10 +231,11 @@ hipError_t launch_gemm_cut(bool gated, hipStream_t s, const void *X, int ldx, co
 
 // Longest of the 256 CUs' shares when n[i] tiles of cost[i], costs falling, each go to the CU that is free first.
 namespace {
-float longest_share(const int *n, const float *cost, int kinds) {
-    struct Level { float load; int cus; } lv[64];          // CUs by load
+// odd: what a CU's last tile takes longer for being alone there, in parts of its cost, where two run side by side.
+float longest_share(const int *n, const float *cost, int kinds, float odd = 0.f) {
+    struct Level { float load, last; int cus; bool alone; } lv[64];          // CUs by load
     int levels = 1;
-    lv[0] = {0.f, 256};
+    lv[0] = {0.f, 0.f, 256, false};
     for (int k = 0; k < kinds; ++k)
         for (int left = n[k]; left > 0;) {
             int low = 0;
@@ -242,17 +243,17 @@ float longest_share(const int *n, const float *cost, int kinds) {
                 if (lv[i].load < lv[low].load) low = i;
             const int take = std::min(left, lv[low].cus);
             left -= take;
-            const float load = lv[low].load + cost[k];
+            const Level next{lv[low].load + cost[k], cost[k], take, !lv[low].alone};
             lv[low].cus -= take;
             if (lv[low].cus == 0) lv[low] = lv[--levels];
             int same = 0;
-            while (same < levels && lv[same].load != load) ++same;
+            while (same < levels && !(lv[same].load == next.load && lv[same].alone == next.alone)) ++same;
             if (same < levels) lv[same].cus += take;
-            else if (levels < 64) lv[levels++] = {load, take};
+            else if (levels < 64) lv[levels++] = next;
             else return 1e30f;
         }
     float most = 0.f;
-    for (int i = 0; i < levels; ++i) most = std::max(most, lv[i].load);
+    for (int i = 0; i < levels; ++i) most = std::max(most, lv[i].load + (lv[i].alone ? odd * lv[i].last : 0.f));
     return most;
 }
 }  // namespace
@@ -275,6 +276,74 @@ bool wide_cut(int rows, int N, float now, WideCut *out) {
             const float t = longest_share(n, cost, 4);
             if (t < best) { best = t; *out = WideCut{{n1, n2, n3, n4}}; found = true; }
         }
+    return found;
+}
+
+// The same for planes folded in registers: 128-wide tiles of 160, 128 and 96 rows, four waves, two workgroups per CU.
+__global__ __launch_bounds__(256, 2) void gemm_fold_cut_kernel(const bf16_t *__restrict__ X, int ldx, const bf16_t *__restrict__ W, const bf16_t *__restrict__ R,
+                                                               bf16_t *__restrict__ Y, int M, int N, int K, int S, FoldCut cut) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    const int nt = N / 128;
+    int block = blockIdx.x, size = 5, row0 = 0;            // in 32 rows
+    for (; size >= 3; --size) {
+        const int grid = (nt * cut.tiles[size - 3] + 7) / 8 * 8;
+        if (block < grid) break;
+        block -= grid;
+        row0 += cut.tiles[size - 3] * 32 * size;
+    }
+    int n_tile, m_tile;
+    if (size < 3 || !band_tile(block, nt, cut.tiles[size - 3], gemm_band(M, N, K), n_tile, m_tile)) return;
+    const int m0 = row0 + m_tile * 32 * size;
+    if (m0 >= M) return;
+#define DYN_BODY(MT) gemm_tile<128, MT, true, 2, false, 4, false>(lds, X, ldx, W, R, Y, N, nullptr, 0, M, N, K, S, nullptr, 1, false, n_tile, 0, m0, 0)
+    if (size == 5) DYN_BODY(160);
+    else if (size == 4) DYN_BODY(128);
+    else DYN_BODY(96);
+#undef DYN_BODY
+}
+
+hipError_t launch_gemm_fold_cut(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int S,
+                                const FoldCut &cut) {
+    constexpr int LDS = 2 * (128 + 160) * ROWB;
+    static bool attr_set = false;
+    if (!attr_set) {
+        const hipError_t e = hipFuncSetAttribute((const void *)gemm_fold_cut_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    int grid = 0;
+    for (int n : cut.tiles) grid += gemm_band_grid(N / 128, n);
+    hipLaunchKernelGGL(gemm_fold_cut_kernel, dim3(grid), dim3(256), LDS, s, (const bf16_t *)X, ldx, (const bf16_t *)W, (const bf16_t *)R, (bf16_t *)Y, rows, N, K,
+                       S, cut);
+    return hipGetLastError();
+}
+
+// m tiles of one height or two neighbouring ones, as many as give the shortest longest share.  In rounds of two 128-row tiles a CU: 160-, 128- and 96-row
+// tiles take 0.60, 0.50 and 0.43 (a pair's 99 / 83 / 71 us at 4096 x 4096), a CU's odd one 0.6 of its own more, a round of 256 x 128 tiles 0.975.
+// One height -> two, 1100 / 1300 / 1700 / 2112 / 2700 rows: qkv (6144 x 4096) 78 / 86 / 131 / 140 / 161 -> 70 / 76 / 121 / 125 / 141 us, o (4096 x 4096) 78 / 74 / 81 /
+// 98 / 141 -> 67 / 70 / 74 / 87 / 132, down (4096 x 14336) from 1300 rows 220 / 241 / 290 / 425 -> 213 / 225 / 249 / 412; 1900 and 4096 rows, which fill whole
+// rounds, 241 -> 247 and 469 -> 475 with two: left as they are.
+bool fold_cut(const GemmPath &p, int rows, int N, FoldCut *out) {
+    static const float cost[3] = {0.60f, 0.50f, 0.43f};
+    if (p.kind != GEMM_MANY || !p.folded) return false;
+    const int nt = N / 128, units = (rows + 31) / 32;
+    float best;
+    if (p.bn == 256) {
+        best = 0.975f * ((p.workgroups + 255) / 256);
+    } else {
+        const int n[3] = {p.mt == 160 ? p.workgroups : 0, p.mt == 128 ? p.workgroups : 0, 0};
+        best = longest_share(n, cost, 3, 0.6f);
+    }
+    best *= 0.97f;
+    bool found = false;
+    for (int k = (units + 4) / 5; k <= (units + 2) / 3; ++k) {
+        const FoldCut c = units <= 3 * k   ? FoldCut{{k, 0, 0}}
+                          : units <= 4 * k ? FoldCut{{4 * k - units, units - 3 * k, 0}}
+                                           : FoldCut{{0, 5 * k - units, units - 4 * k}};
+        const int n[3] = {c.tiles[2] * nt, c.tiles[1] * nt, c.tiles[0] * nt};
+        const float t = longest_share(n, cost, 3, 0.6f);
+        if (t < best) { best = t; *out = c; found = true; }
+    }
     return found;
 }
 

@@ -284,6 +284,30 @@ def test_many_rows_on_tiles_of_several_heights(inter, rows, cut):
     say("%d rows, %s: %.2e" % (rows, list(tiles), check_against_oracle(w, data, y, k, v)))
 
 
+# Folded planes on tiles of two heights (96 + 128, 128 + 160 and 96 rows alone): the heights hold the rows, every row once, the bits of the launches of fewer rows;
+# the same on a partition of 64 CUs, which keeps one height.
+@pytest.mark.parametrize("hidden,inter,rows,cut,N", [(2048, 2048, 1700, 500, 3072), (2048, 2048, 2112, 700, 3072), (2048, 5120, 2620, 17, 2048), (4096, 4096, 1500, 900, 4096)])
+def test_folded_planes_on_tiles_of_two_heights(hidden, inter, rows, cut, N):
+    lib, tiles = B.lib(), (ctypes.c_int * 3)()
+    f = lib._ZN3dyn8fold_cutERKNS_8GemmPathEiiPNS_7FoldCutE
+    f.argtypes, f.restype = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_void_p], ctypes.c_bool
+    taken = []
+    for n, k in ((hidden + 1024, hidden), (hidden, hidden), (hidden, inter)):
+        p = gemm_path(rows, n, k)
+        if f(ctypes.byref(p), rows, n, tiles):
+            taken.append(n)
+            assert p.folded and 0 <= 32 * sum((3 + i) * t for i, t in enumerate(tiles)) - rows < 96
+    assert N in taken
+    w = workload("two_heights", "bf16", hidden, hidden // 128, 4, 128, inter, [(1, 1 + i % 5) for i in range(rows)], seed=rows)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, cut, rows))
+    data = gen.generate(w)
+    run = GpuRun(w, data)
+    y, k, v = run.run(B.sequential())
+    for sched in (B.nano_schedule(w.nano_rows, chain=B.DENSE_CHAIN), B.nano_schedule([0, rows], chain=B.DENSE_CHAIN, partitions=[1], cu_masks=[[0xff] * 8])):
+        assert torch.equal(y.view(torch.uint8), run.run(sched)[0].view(torch.uint8))
+    say("%d rows: %.2e" % (rows, check_against_oracle(w, data, y, k, v)))
+
+
 # The same inside the fp32 projection: tiles of any depth (256, 68) and of whole blocks (512, 1024), 16 and 32 rows high, heads of 32, 64 and
 # 256, pages of 16 and 48.  Where the batch or one of its parts keeps the launch of its own - more rows (the first two, whose whole batch
 # takes 64 x 64 tiles and tiles of any depth), heads of 128 and 16 - it is the same bits.
