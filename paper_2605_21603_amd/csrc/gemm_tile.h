@@ -31,6 +31,10 @@ namespace dyn {
 constexpr int BK = 64, ROWB = BK * 2;
 constexpr int kRotGroup = 32, kRotStep = 9;   // stage-order rotation of the bf16 kernel
 
+// Rotation group of the tile at W row n0 of N.  The second half of a wide output counts from its own start: gate and up columns
+// that belong together are then summed alike, and a tile may hold both (gemm_gate_fold_kernel).
+__device__ __forceinline__ int rot_group_of(int n0, int N) { return (N >= 8192 && N % 512 == 0 && n0 >= N / 2 ? n0 - N / 2 : n0) / 128 / kRotGroup; }
+
 __device__ __forceinline__ void wait_vmcnt(int n) {          // s_waitcnt vmcnt(n) only; n folds to a literal <= 63
     // simm16: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] << 14; expcnt 7 and lgkmcnt 15 = no wait
 #define DYN_W(N) case N: __builtin_amdgcn_s_waitcnt(0x0f70 | ((N) & 15) | (((N) >> 4) << 14)); break;
@@ -154,7 +158,7 @@ __device__ __forceinline__ void gemm_tile(unsigned char *lds, const bf16_t *__re
     // against the next: a down projection's 32 n tiles are one group, and all 256 workgroups of eight experts'
     // read the same columns of rows 28 KB apart (8 experts x 4096 x 14336, two of them per token: 4, 32, 128 tokens 142 -> 128,
     // 180 -> 169, 187 -> 175 us; 256 tokens 194 -> 192; gate/up, seven groups of n tiles, the same within 1 %).
-    const int rot_group = (GATED ? n_tile * (BN / 2) / 64 : n0 / 128) / kRotGroup;   // by output column, the same for every tile shape
+    const int rot_group = !GATED ? rot_group_of(n0, N) : n_tile * (BN / 2) / (INREG ? 128 : 64) / kRotGroup;   // by output column, the same for every tile shape
     const int rot = (int)((unsigned)(rot_group + expert) * kRotStep % (unsigned)plane_stages);
     int iss_w = 0, iss_base = 0;                       // next stage to issue: index inside its plane, plane's first stage
     unsigned char *iss_buf = lds;                      // the pending stage's ring buffer and k offset (issue_begin / issue_one)
@@ -360,7 +364,16 @@ __device__ __forceinline__ void gemm_tile(unsigned char *lds, const bf16_t *__re
                 const int n = n_tile * (BN / 2) + wn * (RW / 2) + a * 16 + 4 * lq;
                 if (m >= M) continue;
                 const size_t orow = list ? list[m] : m;
-                const f32x4 g = acc[a][b], up = acc[a + NA / 2][b];
+                f32x4 g, up;
+                if constexpr (INREG) {                 // rounded as the rows of [gate | up] that the planes' sums would store
+                    g = total[a][b];
+                    up = total[a + NA / 2][b];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) { g[r] = bf2f(f2bf(g[r])); up[r] = bf2f(f2bf(up[r])); }
+                } else {
+                    g = acc[a][b];
+                    up = acc[a + NA / 2][b];
+                }
                 float o[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) o[r] = g[r] / (1.0f + expf(-g[r])) * up[r];

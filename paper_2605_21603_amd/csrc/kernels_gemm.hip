@@ -449,6 +449,8 @@ hipError_t launch_gemm_gated(int dtype, const void *X, int ldx, const void *W, v
     if (gr.n_groups) {
         e = gemm_experts_on_wide(gr, N2, 1) ? launch_gemm_experts_wide(true, s, X, ldx, W, Y, ldy, nullptr, N2, K, gr)
                                             : launch_gemm_experts(true, s, X, ldx, W, Y, ldy, nullptr, 0, max_rows, N2, K, 1, gr);
+    } else if (gemm_split_k(1, N2, K) > 1) {
+        e = launch_gemm_gate_fold(s, X, ldx, W, Y, ldy, max_rows, N2, K);
     } else {
         const GemmPath p = gemm_path(1, max_rows, N2, K);          // split factor 1: no planes on any path
         WideCut cut;

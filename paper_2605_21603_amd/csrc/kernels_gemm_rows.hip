@@ -53,7 +53,7 @@ __global__ __launch_bounds__(64 * S) void gemm_rows16_kernel(const bf16_t *__res
         pair = ep.sh.head_dim / 2;
     }
     const int Kp = K / S, n_stage = Kp / BK;
-    const int rot = (int)(((unsigned)(n0 / 128 / kRotGroup) * kRotStep) % (unsigned)n_stage);
+    const int rot = (int)(((unsigned)rot_group_of(n0, N) * kRotStep) % (unsigned)n_stage);
     const bf16_t *src[LOADS];                              // 8 rows of a stage by 8 lanes each, the 16-byte columns swizzled with the row
 #pragma unroll
     for (int j = 0; j < LOADS; ++j) {

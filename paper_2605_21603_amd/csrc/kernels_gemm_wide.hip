@@ -347,4 +347,51 @@ bool fold_cut(const GemmPath &p, int rows, int N, FoldCut *out) {
     return found;
 }
 
+// Gate/up with planes, some hundred rows: 64 gate and the matching 64 up columns a workgroup, planes folded in registers and gated, where
+// tiles of one height fill the chip once.  What it saves over planes spread over workgroups is their way through memory and the launch that sums
+// them (340 rows x 16384 x 2048, two planes: 34.9 + 10.1 us -> 38).  On the hand-laid-out loop from 128 rows a tile (0.5 % of a step).
+template <int MT, int NS>
+__global__ __launch_bounds__(512, 1) void gemm_gate_fold_kernel(const bf16_t *__restrict__ X, int ldx, const bf16_t *__restrict__ W, bf16_t *__restrict__ Y,
+                                                                int ldy, int M, int N, int K, int S) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    const int m_tiles = (M + MT - 1) / MT, u = blockIdx.x % 8, v = blockIdx.x / 8;      // m tiles that share W rows on one XCD
+    const int n_tile = v / m_tiles * 8 + u;
+    if (n_tile >= N / 128) return;
+    gemm_tile<128, MT, true, NS, true, 8, (MT >= 128)>(lds, X, ldx, W, nullptr, Y, ldy, nullptr, 0, M, N, K, S, nullptr, 1, false, n_tile, 0,
+                                                       v % m_tiles * MT, 0);
+}
+
+// Its tile height for a launch, 0: not taken.  Above 128 rows, while one round of tiles of up to 256 rows holds them; steps, planes over workgroups -> folded:
+// 2048 wide, 64-wide heads 130 / 200 / 250 / 340 / 480 rows 94 / 99 / 103 / 150 / 154 -> 90 / 93 / 97 / 143 / 142 us; 2560 wide 130 / 300 / 500 rows 104 / 139 / 172 ->
+// 97 / 135 / 163; 1024 wide 130 / 300 / 500 rows 60 / 82 / 89 -> 54 / 73 / 78.
+int gate_fold_rows(int rows, int N2, int K) {
+    if (gemm_split_k(1, N2, K) == 1 || N2 < 8192 || N2 % 512 || rows <= 128 || rows > 512) return 0;
+    const int nt = N2 / 128, m_tiles = 256 / nt;           // m tiles of one round
+    if (m_tiles < 1) return 0;
+    const int mt = ((rows + m_tiles - 1) / m_tiles + 63) / 64 * 64;
+    return mt <= 256 ? mt : 0;
+}
+
+hipError_t launch_gemm_gate_fold(hipStream_t s, const void *X, int ldx, const void *W, void *Y, int ldy, int rows, int N2, int K) {
+    const int mt = gate_fold_rows(rows, N2, K), S = gemm_split_k(1, N2, K), grid = (N2 / 128 + 7) / 8 * 8 * ((rows + mt - 1) / mt);
+#define DYN_GATE_FOLD(MT, NS)                                                                                                                          \
+    {                                                                                                                                                  \
+        constexpr int LDS = NS * (128 + MT) * ROWB;                                                                                                    \
+        static bool attr_set = false;                                                                                                                  \
+        if (!attr_set) {                                                                                                                               \
+            const hipError_t e = hipFuncSetAttribute((const void *)gemm_gate_fold_kernel<MT, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);    \
+            if (e != hipSuccess) return e;                                                                                                             \
+            attr_set = true;                                                                                                                           \
+        }                                                                                                                                              \
+        hipLaunchKernelGGL((gemm_gate_fold_kernel<MT, NS>), dim3(grid), dim3(512), LDS, s, (const bf16_t *)X, ldx, (const bf16_t *)W, (bf16_t *)Y, ldy, \
+                           rows, N2, K, S);                                                                                                            \
+    }
+    if (mt == 256) DYN_GATE_FOLD(256, 3)
+    else if (mt == 192) DYN_GATE_FOLD(192, 3)
+    else if (mt == 128) DYN_GATE_FOLD(128, 4)
+    else DYN_GATE_FOLD(64, 4)
+#undef DYN_GATE_FOLD
+    return hipGetLastError();
+}
+
 }  // namespace dyn

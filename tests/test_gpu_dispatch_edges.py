@@ -308,6 +308,21 @@ def test_folded_planes_on_tiles_of_two_heights(hidden, inter, rows, cut, N):
     say("%d rows: %.2e" % (rows, check_against_oracle(w, data, y, k, v)))
 
 
+# Gate/up whose planes are folded and gated in one launch (129 to 512 rows; tiles of 64, 128, 192 and 256 rows, with 64 and 108 n tiles): the bits of planes
+# summed by a launch (up to 128 rows), in the workgroup (up to 16) and of the many-row form with a gate of its own (513 rows and more).
+@pytest.mark.parametrize("hidden,inter,rows,cut,tile", [(1024, 4096, 145, 16, 64), (1024, 4096, 385, 128, 128), (1024, 4096, 700, 400, 128), (2560, 6912, 300, 90, 192),
+                                                        (2560, 6912, 513, 512, 256)])
+def test_gate_with_planes_folded(hidden, inter, rows, cut, tile):
+    taken = B.lib()._ZN3dyn14gate_fold_rowsEiii
+    assert gemm_path(300, 2 * inter, hidden).split > 1 and taken(128, 2 * inter, hidden) == taken(513, 2 * inter, hidden) == 0
+    assert tile in [taken(r, 2 * inter, hidden) for r in (cut, rows - cut, rows)]
+    w = workload("gate_fold", "bf16", hidden, hidden // 128, 4, 128, inter, [(1, 1 + i % 5) for i in range(rows)], seed=rows)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, cut, rows))
+    data = gen.generate(w)
+    y, k, v = both_schedules(w, data)
+    say("%d rows: %.2e" % (rows, check_against_oracle(w, data, y, k, v)))
+
+
 # The same inside the fp32 projection: tiles of any depth (256, 68) and of whole blocks (512, 1024), 16 and 32 rows high, heads of 32, 64 and
 # 256, pages of 16 and 48.  Where the batch or one of its parts keeps the launch of its own - more rows (the first two, whose whole batch
 # takes 64 x 64 tiles and tiles of any depth), heads of 128 and 16 - it is the same bits.
