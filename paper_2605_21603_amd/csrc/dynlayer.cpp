@@ -60,6 +60,7 @@ struct Dispatch {
     bool plan = false;          // first norm: its launch also builds the attention work lists of its rows; attention: they have been built
     bool gated = false;         // gate/up and SiLU: the gate is applied by the gate/up dispatch (plan_gated)
     bool norm_in = false;       // qkv and gate/up: the norm before them is applied by the projection itself; first norm, o and down projection: so they leave it out (plan_norm_in)
+    bool route_in = false;      // o projection: the launch that writes the second norm's rows routes them; route: so it launches nothing (set_route_in)
     bool lists_ready = false;   // MoE down projection: the gate/up dispatch of the same rows already built its expert lists
     int key() const { return partition * DYN_MAX_STREAMS + stream; }
 };
@@ -283,6 +284,19 @@ bool plan_norm_in(const dyn_layer_config &c, const std::vector<Dispatch> &plan, 
     return true;
 }
 
+// The router of a bf16 layer of up to 8 experts runs behind the second norm in the o projection's dispatch, up to 512 rows in the norm's launch,
+// and a route dispatch launches nothing.  (More experts' router elements do not fit a thread's registers beside the norm's.)
+bool route_in(const std::vector<Dispatch> &plan) {
+    return std::any_of(plan.begin(), plan.end(), [](const Dispatch &d) { return d.op == DYN_OP_OPROJ && d.route_in; });
+}
+void set_route_in(std::vector<Dispatch> &plan, bool in) {
+    for (Dispatch &d : plan) {
+        if (d.op != DYN_OP_OPROJ && d.op != DYN_OP_ROUTE) continue;
+        d.route_in = in;
+        if (d.op == DYN_OP_ROUTE) d.noop = in || d.r1 <= d.r0;
+    }
+}
+
 bool norm_in(const std::vector<Dispatch> &plan, int op) {         // what build_plan found
     return std::any_of(plan.begin(), plan.end(), [op](const Dispatch &d) { return d.op == op && d.norm_in; });
 }
@@ -431,6 +445,7 @@ dyn_status build_plan(const dyn_layer *L, const dyn_batch *b, const dyn_schedule
         d.norm_in = d.op == DYN_OP_NORM1 || d.op == DYN_OP_QKV || d.op == DYN_OP_DOWN ? norm1_in : (d.op == DYN_OP_OPROJ || d.op == DYN_OP_GATE_UP) && norm2_in;
         if (d.op == DYN_OP_NORM1 && norm1_in) d.noop = true;
     }
+    if (L->cfg.dtype == DYN_BF16 && L->cfg.n_experts > 0 && L->cfg.n_experts <= 8) set_route_in(plan, true);
     // The attention work lists depend on the rows' sequences and positions only, and every layer walks the same
     // ones: where the first layer's norm is dispatched over exactly the rows of an attention dispatch (which
     // follows it in its micro-batches' chain), the norm's launch builds them beside its rows.  Otherwise the
@@ -540,7 +555,7 @@ WsLayout plan_layout(const dyn_layer *L, const dyn_batch *b, const std::vector<D
         {DYN_REGION_X2, z.x2, DYN_OP_OPROJ, DYN_OP_DOWN, true, 0},
         {DYN_REGION_GU, z.gu, DYN_OP_GATE_UP, DYN_OP_SILU, !gated, 0},
         {DYN_REGION_ACT, z.act, gated ? DYN_OP_GATE_UP : DYN_OP_SILU, DYN_OP_DOWN, true, 0},
-        {DYN_REGION_ROUTING, align_up(z.sel) + z.wgt, DYN_OP_ROUTE, DYN_OP_DOWN, moe, 0},
+        {DYN_REGION_ROUTING, align_up(z.sel) + z.wgt, route_in(plan) ? DYN_OP_OPROJ : DYN_OP_ROUTE, DYN_OP_DOWN, moe, 0},
     };
     int region_of_kind[DYN_REGION_KINDS];
     std::fill(region_of_kind, region_of_kind + DYN_REGION_KINDS, -1);
@@ -643,6 +658,15 @@ WsLayout plan_layout(const dyn_layer *L, const dyn_batch *b, const std::vector<D
     }
     if (regions_out) *regions_out = std::move(regions);
     return w;
+}
+
+// The layout for a workspace of `bytes`.  A router in the norm's launch writes its result one operator earlier, beside the o projection's
+// planes, which can move the peak by the few hundred bytes of that result: where only they are missing, the router stays a launch of its own.
+WsLayout fit_layout(const dyn_layer *L, const dyn_batch *b, std::vector<Dispatch> &plan, size_t bytes) {
+    const WsLayout w = plan_layout(L, b, plan, nullptr);
+    if (w.total <= bytes || !route_in(plan)) return w;
+    set_route_in(plan, false);
+    return plan_layout(L, b, plan, nullptr);
 }
 
 void destroy_graph_entry(GraphEntry &g) {
@@ -754,6 +778,9 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
             ep.h_out = (void *)rowp(base + ws.h, ws.ld_h);
             ep.ld_h = ws.ld_h;
             ep.eps = c.rms_eps;
+            if (d.route_in)
+                ep.route = dyn::GemmRoute{w.w_router, (int32_t *)(base + ws.sel) + (size_t)d.r0 * c.top_k, (float *)(base + ws.wgt) + (size_t)d.r0 * c.top_k,
+                                          c.n_experts, c.top_k};
             err = dyn::launch_gemm(c.dtype, rowp(base + ws.attn, ws.ld_attn), ws.ld_attn, w.w_o, rowp(x_in, H), (void *)rowp(base + ws.x2, H),
                                    planes, (size_t)rows * H, rows, H, NQ, st, mid, &ep, sh.n_cus);
             break;
@@ -761,6 +788,7 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
         case DYN_OP_NORM2:
             break;                                                // applied by the o projection's dispatch
         case DYN_OP_ROUTE:
+            if (d.route_in) break;                                // done by the o projection's dispatch
             err = dyn::launch_route(c.dtype, rowp(base + ws.h, ws.ld_h), ws.ld_h, w.w_router,
                                     (int32_t *)(base + ws.sel) + (size_t)d.r0 * c.top_k,
                                     (float *)(base + ws.wgt) + (size_t)d.r0 * c.top_k, rows, H, c.n_experts, c.top_k, st);
@@ -965,7 +993,7 @@ std::vector<unsigned char> graph_key(const dyn_batch *b, const dyn_schedule *s, 
         put(b->v_cache_layers, sizeof(void *) * n_layers);
     }
     for (const Dispatch &d : plan) {
-        const int f[] = {d.layer, d.op, d.r0, d.r1, d.stream, d.partition, d.any_multi, d.any_single, d.noop, d.lists_ready, d.plan, d.gated, d.norm_in};
+        const int f[] = {d.layer, d.op, d.r0, d.r1, d.stream, d.partition, d.any_multi, d.any_single, d.noop, d.lists_ready, d.plan, d.gated, d.norm_in, d.route_in};
         put(f, sizeof f);
     }
     if (s->mode == DYN_SCHED_EXPLICIT && s->n_partitions > 0) {
@@ -1004,7 +1032,7 @@ void analyse_memory(const dyn_layer *L, const dyn_batch *b, const std::vector<Di
         {DYN_OP_ATTN, {DYN_OP_OPROJ, -1}, ws.ld_attn * e, false, true, false},
         {DYN_OP_OPROJ, {DYN_OP_DOWN, -1}, H * e, false, true, false},                         // x2: the residual of the MLP
         {DYN_OP_OPROJ, {moe ? DYN_OP_ROUTE : DYN_OP_GATE_UP, moe ? DYN_OP_GATE_UP : -1}, ws.ld_h * e, false, true, false},   // second norm
-        {DYN_OP_ROUTE, {DYN_OP_GATE_UP, DYN_OP_DOWN}, (size_t)c.top_k * 8, false, moe, false},   // selected experts and their weights
+        {route_in(plan) ? DYN_OP_OPROJ : DYN_OP_ROUTE, {DYN_OP_GATE_UP, DYN_OP_DOWN}, (size_t)c.top_k * 8, false, moe, false},   // selected experts and their weights
         {DYN_OP_GATE_UP, {DYN_OP_SILU, -1}, (size_t)pairs * 2 * I * e, false, !gated, false},
         {gated ? DYN_OP_GATE_UP : DYN_OP_SILU, {DYN_OP_DOWN, -1}, (size_t)pairs * ws.ld_act * e, false, true, false},
     };
@@ -1246,7 +1274,7 @@ dyn_status dyn_layer_forward(dyn_layer *L, const dyn_batch *b, const dyn_schedul
     if (rc != DYN_OK) return rc;
     if (b->n_tokens == 0) return DYN_OK;
     if ((rc = check_batch_tensors(L, b)) != DYN_OK) return rc;
-    const WsLayout ws = plan_layout(L, b, plan, nullptr);
+    const WsLayout ws = fit_layout(L, b, plan, b->workspace_bytes);
     if (!b->workspace || ((uintptr_t)b->workspace & 255)) return fail(DYN_ERR_WORKSPACE, "workspace missing or not 256-byte aligned");
     if (b->workspace_bytes < ws.total)
         return fail(DYN_ERR_WORKSPACE, "workspace has %zu bytes, this schedule needs %zu", b->workspace_bytes, ws.total);
@@ -1390,7 +1418,7 @@ dyn_status dyn_layer_forward_noalloc(dyn_layer *L, const dyn_batch *b, void *hip
     if (rc != DYN_OK) return rc;
     if (b->n_tokens == 0) return DYN_OK;
     if ((rc = check_batch_tensors(L, b)) != DYN_OK) return rc;
-    const WsLayout ws = plan_layout(L, b, plan, nullptr);
+    const WsLayout ws = fit_layout(L, b, plan, kScratchBytes);
     if (ws.total > kScratchBytes)
         return fail(DYN_ERR_WORKSPACE, "this batch needs %zu bytes of workspace, the static scratch array holds %zu: use dyn_layer_forward with a workspace of the caller's",
                     ws.total, kScratchBytes);

@@ -63,8 +63,9 @@ GemmPath gemm_path(int dtype, int rows, int N, int K);
 bool gemm_uses_plane_buffer(int dtype, int rows, int N, int K);
 
 // ld_out: elements between output rows (>= H).
+struct GemmRoute;
 hipError_t launch_rmsnorm(int dtype, const void *x, const void *g, void *out, int ld_out, int rows, int H, float eps,
-                          hipStream_t s);
+                          hipStream_t s, const GemmRoute *route = nullptr);
 
 // What follows a projection on the same token rows and is applied by the same launch sequence,
 // so that its input never makes a round trip through a kernel of its own: the RMSNorm of the
@@ -72,6 +73,9 @@ hipError_t launch_rmsnorm(int dtype, const void *x, const void *g, void *out, in
 // projection).  Where the projection's split-K planes are summed by a reduce kernel, that kernel
 // applies it (one pass over the planes); otherwise the operator's own kernel runs on the rows the
 // projection wrote.  Either way every element sees the same arithmetic in the same order.
+// The router of the rows that a norm writes (bf16, at most 8 experts), applied behind the norm, by its launch where rows are few: as launch_route, sel and wgt at the first row.  w_router null: none.
+struct GemmRoute { const float *w_router = nullptr; int32_t *sel = nullptr; float *wgt = nullptr; int E = 0, top_k = 0; };
+
 struct GemmEpilogue {
     enum { NONE = 0, NORM = 1, ROPE = 2, GATE = 3 } kind = NONE;
     // NORM: h_out[row] = RMSNorm(Y[row]) * g, row pitch ld_h
@@ -81,6 +85,7 @@ struct GemmEpilogue {
     void *h_out = nullptr;
     int ld_h = 0;
     float eps = 0.f;
+    GemmRoute route;         // NORM: the router of the normalised rows
     // ROPE: rotary on the q and k heads of the Y rows (q in place), k' and v appended to the cache
     const int32_t *seq_of_token = nullptr, *pos_of_token = nullptr, *block_table = nullptr;
     void *k_cache = nullptr, *v_cache = nullptr;
@@ -205,7 +210,7 @@ hipError_t launch_silu_mul(int dtype, const void *gu, void *out, int ld_out, int
 
 // The split-K reduce of a projection fused with what follows it (bf16; used by launch_gemm).
 hipError_t launch_reduce_norm(const float *P, size_t plane_stride, int S, const void *R, void *Y, const void *g, void *out,
-                              int ld_out, int rows, int H, float eps, hipStream_t s);
+                              int ld_out, int rows, int H, float eps, hipStream_t s, const GemmRoute *route = nullptr);
 bool reduce_rope_supported(int dtype, const AttnShape &sh);
 hipError_t launch_reduce_rope(const float *P, size_t plane_stride, int S, void *qkv, const int32_t *seq_of_token,
                               const int32_t *pos_of_token, const int32_t *block_table, void *k_cache, void *v_cache,

@@ -6,6 +6,7 @@
 #include "kernels.h"
 #include "norm_row.h"
 #include "rotary.h"
+#include "route_row.h"
 
 namespace dyn {
 
@@ -19,9 +20,37 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const T *__restrict__ x, c
     rmsnorm_row<T>(x + row * H, g, out + row * ld_out, H, eps, threadIdx.x, part, true);
 }
 
+// The same with the router behind it: a launch of its own reads the row again, and the router's weights behind the norm rather than beside it.
+// Latency bounds it: one row, the router's elements from the L2, two sums over the workgroup, one thread's choice.  (Hidden 4096, 8 experts, one
+// row: norm 4.6 + router 11.7 -> 8.8 us, the step 238.7 -> 233.1; 256 rows with 8 planes 10.2 + 12.3 -> 16.0 us, the step 861 -> 859.)
+__global__ __launch_bounds__(256) void rmsnorm_route_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ g, bf16_t *__restrict__ out,
+                                                            int ld_out, int H, float eps, GemmRoute route) {
+    __shared__ float part[4], slices[4][kMaxExperts];
+    const size_t row = blockIdx.x;
+    RowRouter<8> router(route, H);
+    router.load();
+    rmsnorm_row<bf16_t, RowRouter<8> &>(x + row * H, g, out + row * ld_out, H, eps, threadIdx.x, part, true, router);
+    route_choose<8>(router.acc, slices, route.E, route.top_k, route.sel + row * route.top_k, route.wgt + row * route.top_k);
+}
+
+// Rows up to which the router joins the norm: the router's elements in registers leave a CU two such workgroups, and more rows than these take
+// hold at once take longer than two launches (1120 rows: 6.8 + 13.0 us apart, 21.4 together).
+constexpr int kNormRouteRows = 512;
+static hipError_t route_rows(const GemmRoute &to, const void *h, int ld_h, int rows, int H, hipStream_t s) {
+    return launch_route(1, h, ld_h, to.w_router, to.sel, to.wgt, rows, H, to.E, to.top_k, s);
+}
+
 hipError_t launch_rmsnorm(int dtype, const void *x, const void *g, void *out, int ld_out, int rows, int H, float eps,
-                          hipStream_t s) {
+                          hipStream_t s, const GemmRoute *route) {
     if (rows <= 0) return hipSuccess;
+    if (route && route->w_router && rows > kNormRouteRows) {
+        const hipError_t e = launch_rmsnorm(dtype, x, g, out, ld_out, rows, H, eps, s);
+        return e == hipSuccess ? route_rows(*route, out, ld_out, rows, H, s) : e;
+    }
+    if (route && route->w_router) {
+        hipLaunchKernelGGL(rmsnorm_route_kernel, dim3(rows), dim3(256), 0, s, (const bf16_t *)x, (const bf16_t *)g, (bf16_t *)out, ld_out, H, eps, *route);
+        return hipGetLastError();
+    }
     if (dtype == 0)
         hipLaunchKernelGGL(rmsnorm_kernel<float>, dim3(rows), dim3(256), 0, s, (const float *)x, (const float *)g,
                            (float *)out, ld_out, H, eps);
@@ -39,12 +68,14 @@ hipError_t launch_rmsnorm(int dtype, const void *x, const void *g, void *out, in
 // (SC = the split factor as a compile-time constant, so that a row's plane loads are all issued
 // before the first is added - one workgroup per row has nothing else to hide their latency with;
 // 0 = any factor, loop.)
-template <int SC>
+// ROUTE: the router behind the norm, as rmsnorm_route_kernel applies it.
+template <int SC, bool ROUTE>
 __global__ __launch_bounds__(256) void gemm_reduce_norm_kernel(const float *__restrict__ P, size_t plane_stride, int S,
                                                                const bf16_t *__restrict__ R, bf16_t *__restrict__ Y,
                                                                const bf16_t *__restrict__ g, bf16_t *__restrict__ out,
-                                                               int ld_out, int H, float eps) {
+                                                               int ld_out, int H, float eps, GemmRoute route) {
     typedef bf16_t vec_t __attribute__((ext_vector_type(8)));
+    RowRouter<ROUTE ? 8 : 1> router(route, H);
     constexpr int KEEP = 4;                                 // vectors a thread keeps in registers (H <= 8192); beyond, Y is read back
     const size_t row = blockIdx.x;
     const int nv = H / 8;
@@ -92,6 +123,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_norm_kernel(const float *__re
 #pragma unroll
         for (int e = 0; e < 8; ++e) { const float f = bf2f(v[e]); ss = __builtin_fmaf(f, f, ss); }
     }
+    if constexpr (ROUTE) router.load();                     // beside the row's sum
     ss = wave_sum(ss);
     __shared__ float part[4];
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
@@ -107,14 +139,25 @@ __global__ __launch_bounds__(256) void gemm_reduce_norm_kernel(const float *__re
 #pragma unroll
         for (int e = 0; e < 8; ++e) o[e] = f2bf(bf2f(v[e]) * r * bf2f(gv[e]));
         *reinterpret_cast<vec_t *>(out + row * ld_out + (size_t)i * 8) = o;
+        if constexpr (ROUTE) router(i, o);
+    }
+    if constexpr (ROUTE) {
+        __shared__ float slices[4][kMaxExperts];
+        route_choose<8>(router.acc, slices, route.E, route.top_k, route.sel + row * route.top_k, route.wgt + row * route.top_k);
     }
 }
 
 hipError_t launch_reduce_norm(const float *P, size_t plane_stride, int S, const void *R, void *Y, const void *g, void *out,
-                              int ld_out, int rows, int H, float eps, hipStream_t s) {
+                              int ld_out, int rows, int H, float eps, hipStream_t s, const GemmRoute *route) {
     if (rows <= 0) return hipSuccess;
-#define DYN_RN(SC) hipLaunchKernelGGL(gemm_reduce_norm_kernel<SC>, dim3(rows), dim3(256), 0, s, P, plane_stride, S, (const bf16_t *)R, \
-                                      (bf16_t *)Y, (const bf16_t *)g, (bf16_t *)out, ld_out, H, eps)
+    if (route && route->w_router && rows > kNormRouteRows) {
+        const hipError_t e = launch_reduce_norm(P, plane_stride, S, R, Y, g, out, ld_out, rows, H, eps, s);
+        return e == hipSuccess ? route_rows(*route, out, ld_out, rows, H, s) : e;
+    }
+    const GemmRoute none, &to = route ? *route : none;
+#define DYN_RN_OF(SC, ROUTE) hipLaunchKernelGGL((gemm_reduce_norm_kernel<SC, ROUTE>), dim3(rows), dim3(256), 0, s, P, plane_stride, S, (const bf16_t *)R, \
+                                                (bf16_t *)Y, (const bf16_t *)g, (bf16_t *)out, ld_out, H, eps, to)
+#define DYN_RN(SC) if (to.w_router) DYN_RN_OF(SC, true); else DYN_RN_OF(SC, false)
     switch (S) {
         case 2: DYN_RN(2); break;
         case 4: DYN_RN(4); break;
@@ -122,6 +165,7 @@ hipError_t launch_reduce_norm(const float *P, size_t plane_stride, int S, const 
         default: DYN_RN(0); break;
     }
 #undef DYN_RN
+#undef DYN_RN_OF
     return hipGetLastError();
 }
 

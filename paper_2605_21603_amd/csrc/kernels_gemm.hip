@@ -331,7 +331,7 @@ bool gemm_uses_plane_buffer(int dtype, int rows, int N, int K) {
 namespace {
 // The operator that follows the projection, as a kernel of its own on the rows the projection wrote.
 hipError_t run_epilogue(int dtype, const GemmEpilogue &ep, void *Y, int rows, int N, hipStream_t s) {
-    if (ep.kind == GemmEpilogue::NORM) return launch_rmsnorm(dtype, Y, ep.g, ep.h_out, ep.ld_h, rows, N, ep.eps, s);
+    if (ep.kind == GemmEpilogue::NORM) return launch_rmsnorm(dtype, Y, ep.g, ep.h_out, ep.ld_h, rows, N, ep.eps, s, &ep.route);
     if (ep.kind == GemmEpilogue::ROPE)
         return launch_rope_kv(dtype, Y, ep.seq_of_token, ep.pos_of_token, ep.block_table, ep.k_cache, ep.v_cache, *ep.rope, *ep.shape, rows,
                               ep.long_rows, s);
@@ -343,6 +343,7 @@ GemmEpilogue epilogue_at(const GemmEpilogue &ep, int dtype, int row, int N) {   
     GemmEpilogue e = ep;
     const size_t es = dtype == 0 ? 4 : 2;
     if (e.kind == GemmEpilogue::NORM || e.kind == GemmEpilogue::GATE) e.h_out = (char *)e.h_out + (size_t)row * e.ld_h * es;
+    if (e.route.w_router) { e.route.sel += (size_t)row * e.route.top_k; e.route.wgt += (size_t)row * e.route.top_k; }
     if (e.kind == GemmEpilogue::ROPE) { e.seq_of_token += row; e.pos_of_token += row; }
     (void)N;
     return e;
@@ -407,7 +408,7 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
     if (S == 1 || p.folded) return has_ep ? run_epilogue(dtype, *ep, Y, rows, N, s) : hipSuccess;
     // the planes are summed in plane order, with the residual; where an operator follows on the same rows, by its fused form
     if (has_ep && ep->kind == GemmEpilogue::NORM && N % 8 == 0)
-        return launch_reduce_norm(partial, plane_stride, S, R, Y, ep->g, ep->h_out, ep->ld_h, rows, N, ep->eps, s);
+        return launch_reduce_norm(partial, plane_stride, S, R, Y, ep->g, ep->h_out, ep->ld_h, rows, N, ep->eps, s, &ep->route);
     if (has_ep && ep->kind == GemmEpilogue::ROPE && !R && reduce_rope_supported(dtype, *ep->shape))
         return launch_reduce_rope(partial, plane_stride, S, Y, ep->seq_of_token, ep->pos_of_token, ep->block_table, ep->k_cache,
                                   ep->v_cache, *ep->rope, *ep->shape, rows, s);

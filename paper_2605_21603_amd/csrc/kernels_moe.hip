@@ -6,48 +6,21 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "route_row.h"
 
 namespace dyn {
-
-constexpr int kMaxExperts = 16;
-
-// One 256-thread workgroup per token.  Every thread takes contiguous 8-element pieces of the
-// row, multiplies them with the same pieces of all E router rows (all loads of a piece are
-// independent, so they are in flight together), a butterfly and a fixed-order LDS step add the
-// slices, thread 0 picks the top_k largest logits (ties to the lower index) and normalises
-// exp(logit - max) over the picked ones.  EM experts at most (a power of two): the butterfly halves
-// the experts a lane carries at each of its first steps - lanes that differ in a step's bit keep
-// different halves - so 8 experts take 10 shuffles and not 48; every sum pairs the same lanes as a
-// butterfly per expert, with the same bits.
-// (Operator with its lists under events: 256 tokens 25.9 -> 22.6 us, 1120 tokens 30.3 -> 24.5 us.)
-template <int N>
-__device__ __forceinline__ float halving_sum(const float (&v)[N], int off, int lane) {     // N: experts left, off: the step's lane distance
-    if constexpr (N == 1) {
-        float x = v[0];
-        for (; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-        return x;
-    } else {
-        const bool up = lane & off;
-        float keep[N / 2];
-#pragma unroll
-        for (int e = 0; e < N / 2; ++e) {
-            const float give = up ? v[e] : v[e + N / 2], mine = up ? v[e + N / 2] : v[e];
-            keep[e] = mine + __shfl_xor(give, off, 64);
-        }
-        return halving_sum<N / 2>(keep, off >> 1, lane);
-    }
-}
 
 template <typename T, int EM>
 __global__ __launch_bounds__(256) void route_kernel(const T *__restrict__ h, int ldh, const float *__restrict__ w_router,
                                                     int32_t *__restrict__ sel, float *__restrict__ wgt, int rows,
                                                     int H, int E, int top_k) {
-    const int t = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ float part[4][kMaxExperts];
+    const int t = blockIdx.x;
     float acc[EM];
 #pragma unroll
     for (int e = 0; e < EM; ++e) acc[e] = 0.f;
     for (int k0 = threadIdx.x * 8; k0 < H; k0 += 256 * 8) {
-        const bool whole = k0 + 8 <= H;       // fp32 rows may end in a half piece (H is a multiple of 4)
+        const bool whole = k0 + 8 <= H;
         float x[8];
         if constexpr (sizeof(T) == 2) {       // one 16-byte load (rows and k0 are 16-byte aligned)
             const u32x4 raw = *reinterpret_cast<const u32x4 *>(h + (size_t)t * ldh + k0);
@@ -60,47 +33,11 @@ __global__ __launch_bounds__(256) void route_kernel(const T *__restrict__ h, int
 #pragma unroll
             for (int i = 0; i < 8; ++i) x[i] = i < 4 || whole ? to_f32<T>(h[(size_t)t * ldh + k0 + i]) : 0.f;
         }
-#pragma unroll
-        for (int e = 0; e < EM; ++e)
-            if (e < E) {
-                const f32x4 w0 = *reinterpret_cast<const f32x4 *>(w_router + (size_t)e * H + k0);
-                const f32x4 w1 = whole ? *reinterpret_cast<const f32x4 *>(w_router + (size_t)e * H + k0 + 4) : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[e] = fmaf(x[i], w0[i], acc[e]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[e] = fmaf(x[4 + i], w1[i], acc[e]);
-            }
+        RouterPiece<EM> p;
+        load_piece(p, w_router, H, E, k0);
+        add_piece(acc, p, x, E);
     }
-    __shared__ float part[4][kMaxExperts];
-    {
-        const float v = halving_sum<EM>(acc, 32, lane);
-        // lane bits 5, 4, .. (one per halving) name the expert, high bit first: the lanes below them all hold its sum
-        constexpr int PER = 64 / EM;
-        if (lane % PER == 0) part[wave][lane / PER] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    float logit[EM];
-#pragma unroll
-    for (int e = 0; e < EM; ++e) logit[e] = ((part[0][e] + part[1][e]) + part[2][e]) + part[3][e];
-    // No array is indexed with a run-time value here: that would move it from registers to scratch
-    // memory, and this single thread's dependent accesses to it were most of the kernel's time.
-    unsigned used = 0;
-    float mx = 0.f, denom = 0.f;
-    for (int j = 0; j < top_k; ++j) {
-        int best = -1;
-        float best_val = 0.f;
-#pragma unroll
-        for (int e = 0; e < EM; ++e)
-            if (e < E && !((used >> e) & 1u) && (best < 0 || logit[e] > best_val)) { best = e; best_val = logit[e]; }
-        used |= 1u << best;
-        if (j == 0) mx = best_val;            // picks come in descending order: the first is the maximum
-        const float ex = expf(best_val - mx);
-        denom += ex;
-        sel[(size_t)t * top_k + j] = best;
-        wgt[(size_t)t * top_k + j] = ex;
-    }
-    for (int j = 0; j < top_k; ++j) wgt[(size_t)t * top_k + j] = wgt[(size_t)t * top_k + j] / denom;
+    route_choose(acc, part, E, top_k, sel + (size_t)t * top_k, wgt + (size_t)t * top_k);
 }
 
 hipError_t launch_route(int dtype, const void *h, int ldh, const float *w_router, int32_t *sel, float *wgt, int rows,

@@ -6,10 +6,11 @@ namespace dyn {
 
 // out = x * g / sqrt(mean(x^2) + eps); tid: 0..255 within the row's threads, part: 4 floats of LDS of their own.
 // The row and the gains are loaded together, once: with few rows the launch is one workgroup's latency
-// long.  Every thread of the workgroup calls this (it synchronises); live = false computes nothing.
-template <typename T>
+// long.  Every thread of the workgroup calls this (it synchronises); live = false computes nothing.  each(i, o) is given the vectors stored.
+struct NoVector { template <typename V> __device__ __forceinline__ void operator()(int, const V &) const {} };
+template <typename T, typename F = NoVector>
 __device__ __forceinline__ void rmsnorm_row(const T *__restrict__ x, const T *__restrict__ g, T *__restrict__ out, int H, float eps, int tid,
-                                            float *part, bool live) {
+                                            float *part, bool live, F &&each = F()) {
     constexpr int V = 16 / sizeof(T);
     typedef T vec_t __attribute__((ext_vector_type(V)));
     const vec_t *xr = reinterpret_cast<const vec_t *>(x), *gr = reinterpret_cast<const vec_t *>(g);
@@ -44,8 +45,16 @@ __device__ __forceinline__ void rmsnorm_row(const T *__restrict__ x, const T *__
     };
 #pragma unroll
     for (int n = 0; n < KEEP; ++n)
-        if (tid + n * 256 < nv) orow[tid + n * 256] = scaled(kept[n], gain[n]);
-    for (int i = tid + KEEP * 256; i < nv; i += 256) orow[i] = scaled(xr[i], gr[i]);
+        if (tid + n * 256 < nv) {
+            const vec_t o = scaled(kept[n], gain[n]);
+            orow[tid + n * 256] = o;
+            each(tid + n * 256, o);
+        }
+    for (int i = tid + KEEP * 256; i < nv; i += 256) {
+        const vec_t o = scaled(xr[i], gr[i]);
+        orow[i] = o;
+        each(i, o);
+    }
 }
 
 }  // namespace dyn

@@ -197,6 +197,28 @@ def test_expert_tiles_of_few_rows_follow_the_counts(hidden, tokens, pull):
     say("%d tokens: %.2e" % (tokens, check_against_oracle(w, data, y, k, v)))
 
 
+# The router in the launch of the second norm, with planes and without: rows of less than one vector per thread, of three and of five, all experts
+# but one chosen, counts of experts that are no power of two, 16 experts (a launch of its own).  A workspace a byte too small for that (`apart`) gives the
+# router its own launch, with the same bits.
+@pytest.mark.parametrize("hidden,experts,top_k,rows,apart", [
+    (512, 8, 1, 4, True), (512, 8, 1, 130, False), (4608, 3, 2, 21, False), (8320, 5, 3, 2, False), (8320, 8, 7, 40, False), (256, 8, 2, 600, False), (4096, 16, 2, 30, False)])
+def test_router_inside_the_second_norm(hidden, experts, top_k, rows, apart):
+    inter = 1024 if hidden == 512 else 128
+    w = workload("route", "bf16", hidden, 8, 2, 128, inter, [(1, 1 + i % 5) for i in range(rows)], experts=experts, top_k=top_k, seed=40 + rows)
+    w = gen.Workload(w.name, w.shape, w.seqs, w.seed, (0, (rows + 2) // 3, rows))
+    data = gen.generate(w)
+    y, k, v = both_schedules(w, data)
+    if apart:
+        run = GpuRun(w, data)
+        one_stream = B.nano_schedule(w.nano_rows, chain=B.MOE_CHAIN, streams=[0, 0])
+        step = B.DeviceStep(run.layer, data, sched=one_stream)
+        step.batch.workspace_bytes -= 1
+        run.layer.forward(step.batch, one_stream, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        assert torch.equal(step.y.cpu().view(torch.uint8), y.view(torch.uint8))
+    say("%d rows of %d: %.2e" % (rows, hidden, check_against_oracle(w, data, y, k, v)))
+
+
 # A long prompt's chunks grow with its rows, here from 1024 (2048) to 2048 and 4096 positions: with other sequences around it, in
 # another micro-batch than theirs, the same bits; the rows of its end as a step of their own, which keeps the shorter chunks, agree to bf16 rounding.
 @pytest.mark.parametrize("prompt,cached", [(4200, 100), (4097, 5003)])
