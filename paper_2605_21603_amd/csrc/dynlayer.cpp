@@ -150,7 +150,7 @@ Sizes tensor_sizes(const dyn_layer *L, int T, int max_pages, bool prompts) {
     z.max_chunks = std::max(1, (std::max(max_pages, 1) + L->chunk_pages - 1) / L->chunk_pages);
     // The bf16 prompt kernel cuts by a rule of its own, which makes more chunks than a handle's larger than 1024
     // positions; partials and lists have one stride for all tokens.
-    const dyn::AttnShape sh{c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, max_pages, L->chunk_pages, z.max_chunks, 0, 0};
+    const dyn::AttnShape sh{c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, max_pages, L->chunk_pages, z.max_chunks, 0};
     if (prompts && dyn::attention_mfma_supported(c.dtype, sh))
         z.max_chunks = std::max(z.max_chunks, dyn::attn_prefill_max_chunks((long)std::max(max_pages, 1) * c.page_size));
     z.h = t * z.ld_h * e;
@@ -274,7 +274,7 @@ bool plan_gated(const dyn_layer_config &c, const std::vector<Dispatch> &plan) {
 // comes before; `gated` as plan_gated says.
 bool plan_norm_in(const dyn_layer_config &c, const std::vector<Dispatch> &plan, int op, bool gated) {
     if (c.n_experts || c.dtype != DYN_F32 || (op == DYN_OP_GATE_UP && !gated)) return false;
-    const dyn::AttnShape sh{c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, 1, 1, 1, 0, 0};
+    const dyn::AttnShape sh{c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, 1, 1, 1, 0};
     for (const Dispatch &d : plan) {
         const int rows = d.r1 - d.r0, N = op == DYN_OP_QKV ? qkv_width(c) : 2 * c.mlp_inter;
         if (d.op != op || rows <= 0) continue;
@@ -726,7 +726,7 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
     const char *x_in = d.layer == 0 ? (const char *)b->x : (d.layer % 2 ? base + ws.xa : base + ws.xb);
     char *x_out = d.layer == nl - 1 ? (char *)b->y : (d.layer % 2 ? base + ws.xb : base + ws.xa);
     auto rowp = [&](const char *p, int width) { return p + (size_t)d.r0 * width * e; };
-    dyn::AttnShape sh{c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, b->max_pages_per_seq, L->chunk_pages, ws.max_chunks, 0, rows};
+    dyn::AttnShape sh{c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, b->max_pages_per_seq, L->chunk_pages, ws.max_chunks, 0};
     if (d.partition > 0 && s->mode == DYN_SCHED_EXPLICIT)
         for (int i = 0; i < s->cu_mask_words; ++i)
             sh.n_cus += __builtin_popcount(s->cu_masks[(d.partition - 1) * s->cu_mask_words + i]);

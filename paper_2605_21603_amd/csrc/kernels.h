@@ -20,13 +20,12 @@ struct AttnShape {
     int chunk_pages;               // pages per split-KV chunk (a constant of the layer)
     int max_chunks;                // the most chunks a token of the batch can have
     int n_cus;                     // CUs of the stream's partition (0: whole device); sizes the persistent launch
-    int rows;                      // rows of the dispatch
 };
 
-// Where chunk c of a row's q head lies in the split-KV partial arrays, chunk by chunk: what a dispatch's tokens use is one piece of
-// memory.  (With a token's chunks side by side, room for the most any token can have between one token and the next, the
-// partials of 4096 prompt tokens behind 8192 positions lay 24 KB apart over 3.2 GB.)
-__host__ __device__ inline size_t part_index(const AttnShape &sh, int row, int head, int c) { return ((size_t)c * sh.rows + row) * sh.n_q + head; }
+// Where chunk c of a row's q head lies in the split-KV partial arrays: a token's chunks behind one another, the heads of one side by side, so
+// what is written at one time - a few tokens' chunks - is one piece of memory.  (Chunk by chunk over all rows, a token's chunks lay a
+// whole number of MiB apart: 256 tokens of up to 32 chunks, attention 861 us where this takes 856, three layers' step 3198 -> 3176.)
+__host__ __device__ inline size_t part_index(const AttnShape &sh, int row, int head, int c) { return ((size_t)row * sh.max_chunks + c) * sh.n_q + head; }
 
 // Expert grouping of a projection (all fields zero: plain GEMM).  Group e has counts[e] rows;
 // row i of the group reads X row lists[e * cap + i] / x_div and writes output row

@@ -586,8 +586,9 @@ __global__ __launch_bounds__(256) void attn_combine_segments_kernel(float *__res
     if (n_chunks <= kMergeSegment || c0 >= n_chunks) return;
     const int n = min(kMergeSegment, n_chunks - c0);
     const size_t next = part_index(sh, 0, 0, 1);           // from a chunk to the one behind it
-    float *ml = part_ml + (c0 * next + pair) * 2;
-    float *po = part_o + (c0 * next + pair) * d;
+    const size_t at = part_index(sh, t, pair % sh.n_q, c0);
+    float *ml = part_ml + at * 2;
+    float *po = part_o + at * d;
     float M = -INFINITY;
     for (int c = sub; c < n; c += 32) M = fmaxf(M, ml[c * next * 2]);
 #pragma unroll
@@ -901,7 +902,7 @@ hipError_t launch_attention_generic(int dtype, const void *qkv, const int32_t *s
         if (per_row >= (size_t)1 << 26) return hipErrorInvalidConfiguration;
         for (int r0 = 0; r0 < rows; r0 += std::min(step, rows - r0)) {
             const dim3 grid((unsigned)(std::min(step, rows - r0) * per_row));
-            float *const po = part_o + (size_t)r0 * sh.n_q * sh.head_dim, *const pml = part_ml + (size_t)r0 * sh.n_q * 2;
+            float *const po = part_o + part_index(sh, r0, 0, 0) * sh.head_dim, *const pml = part_ml + part_index(sh, r0, 0, 0) * 2;
             if (dtype == 0)
                 hipLaunchKernelGGL(attn_generic_kernel<float>, grid, dim3(64), 0, s, (const float *)qkv + r0 * width, seq_of_token + r0,
                                    pos_of_token + r0, block_table, (const float *)k_cache, (const float *)v_cache, po, pml, sh);
