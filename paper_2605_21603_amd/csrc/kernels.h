@@ -24,7 +24,7 @@ struct AttnShape {
 
 // Where chunk c of a row's q head lies in the split-KV partial arrays: a token's chunks behind one another, the heads of one side by side, so
 // what is written at one time - a few tokens' chunks - is one piece of memory.  (Chunk by chunk over all rows, a token's chunks lay a
-// whole number of MiB apart: 256 tokens of up to 32 chunks, attention 861 us where this takes 856, three layers' step 3198 -> 3176.)
+// whole number of MiB apart: 256 tokens of up to 32 chunks, attention 861 us where this takes 858, three layers' step 3198 -> 3176.)
 __host__ __device__ inline size_t part_index(const AttnShape &sh, int row, int head, int c) { return ((size_t)row * sh.max_chunks + c) * sh.n_q + head; }
 
 // Expert grouping of a projection (all fields zero: plain GEMM).  Group e has counts[e] rows;
