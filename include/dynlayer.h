@@ -82,8 +82,10 @@ typedef struct {
                                   work items to fill the chip; large ones write fewer partials and switch items less
                                   often (32 layers at batch 256, contexts 1024..8192: 256 -> 2048 positions takes 4.5 %
                                   off the layer; batch 128, contexts 512..4096: 1024 is 1 % faster, 2048 5 % slower).
-                                  Sequences of several tokens are cut by a rule of their own (1024 positions,
-                                  more behind 8192 cached ones) whatever this says */
+                                  Sequences of several tokens are cut by a rule of their own whatever this says (1024
+                                  positions; more behind 8192 cached ones, and for a sequence of more than 1024 tokens in the
+                                  step where its query blocks alone fill the chip), which reads that sequence's tokens and
+                                  positions and nothing else of the batch */
 } dyn_layer_config;
 
 /* One entry per layer (array of n_layers). */

@@ -4,7 +4,7 @@
 //
 // An 8-wave workgroup serves one query block - up to 16 * (16 / G) tokens (64 with G = 4 q heads per kv
 // head) of one sequence whose positions fall in one aligned block - against one chunk of cached positions (1024, more behind
-// a long prefix or for a long prompt: prompt_chunk) of one kv head.  K and V tiles of 64 positions (four pages each, 32 KB together) go from
+// a long prefix or for a long prompt: prompt_chunk_positions) of one kv head.  K and V tiles of 64 positions (four pages each, 32 KB together) go from
 // global memory straight into an LDS ring with direct loads, once per workgroup, and all eight waves read
 // their MFMA operands from there: a key is fetched once per query block and q-head
 // group, and the waves hold no K/V staging registers.  A wave owns two sets of 16 columns

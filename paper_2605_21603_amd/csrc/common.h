@@ -90,8 +90,7 @@ __device__ __forceinline__ void static_for(F &&f) {
 // sequence, from `reach` = the largest key count a token of its aligned position block can
 // attend.  1024 positions, doubled until the block has at most 8 chunks, up to 8192: behind a
 // long cached prefix fixed 1024-position chunks leave one fp32 partial set per 1024 keys and
-// token for the merge to read back.  A function of the block's positions alone, so a token's
-// chunks - and the order its partials are merged in - do not depend on the batch around it.
+// token for the merge to read back.  A function of the block's positions alone.
 __host__ __device__ inline int prefill_chunk_positions(int reach) {
     int ct = 1024;
     while (reach > 8 * ct && ct < 8192) ct *= 2;
@@ -108,6 +107,27 @@ __host__ __device__ inline int prefill_run_chunk_positions(int reach, int tg, in
     const long long cu = (long long)n_kv * rows * mean_keys / (256 * tg);
     while (ct < 8192 && ct < reach && 4 * ct <= cu) ct *= 2;
     return ct;
+}
+// The chunk size in use: that of the tokens in the aligned block of `tg` positions of a multi-token sequence that row t, at position p, lies in.
+// A function of that sequence's rows and positions in this step, and of nothing else in the dispatch (which holds whole
+// sequences): the length of its run of rows is read off the rows whole 1024s in front of the block and behind it, and a run that none of
+// them is part of - any of up to 1024 rows, wherever it begins in its blocks - has the plain rule.  (So in a dispatch of up to 1024 rows
+// there is nothing to read.)
+constexpr int kRunStep = 1024, kRunProbes = 4;
+__host__ __device__ inline int prompt_chunk_positions(const int32_t *seq_of_token, int t, int p, int rows, int tg, int n_kv) {
+    const int reach = (p / tg + 1) * tg, first = t - p % tg, last = first + tg - 1;
+    int before = 0, after = 0;
+    if (rows > kRunStep) {
+        const int s = seq_of_token[t];
+#pragma unroll
+        for (int i = 1; i <= kRunProbes; ++i) {
+            const int lo = first - i * kRunStep, hi = last + i * kRunStep;
+            if (lo >= 0) before += seq_of_token[lo] == s;
+            if (hi < rows) after += seq_of_token[hi] == s;
+        }
+    }
+    if (before + after == 0) return prefill_chunk_positions(reach);
+    return prefill_run_chunk_positions(reach, tg, n_kv, (before + after + 1) * kRunStep, reach + (after - before) * (kRunStep / 2));
 }
 // The most chunks a token with at most `positions` keys can have under that rule: a chunk size below 8192 is taken up to
 // eight chunks' reach only.

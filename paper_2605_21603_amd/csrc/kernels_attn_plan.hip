@@ -16,7 +16,7 @@ constexpr int PS = 16;
 // positions, all of them against one pass over the keys.  List 0 holds the tokens that are
 // alone in their sequence this step (decode: groups of one, 4 of 16 MFMA columns live), list 1
 // the tokens of multi-token sequences (prefill chunks) in query blocks of up to tg1 tokens, against
-// chunks of prefill_chunk_positions() positions (1024 unless the block reaches past 8192 keys; more for a long prompt).
+// chunks of prompt_chunk_positions() positions (1024 unless the block reaches past 8192 keys; more for a long prompt).
 // One entry per (group, chunk) that exists: list[0] = number of entries, entry i =
 // (first token row, chunk | tokens << 20) at list[2 + 2 i].
 // List 0 is ordered by work, largest first: its entries are bucketed by their size in quarters of
@@ -54,23 +54,6 @@ __device__ __forceinline__ int scan64(int x) {
 
 struct PlanRow { int which, nc, n_tok, b_full, b_last; };
 
-// Chunk size of the tokens in one aligned block of a multi-token sequence: row t at position p.  How long the sequence's run of
-// rows is, is read off the rows whole 1024s around the block's first position (a dispatch holds whole sequences).
-constexpr int kRunStep = 1024, kRunProbes = 4;
-__device__ __forceinline__ int prompt_chunk(const int32_t *__restrict__ seq_of_token, int t, int s, int p, int rows, int tg1, int n_kv) {
-    const int reach = (p / tg1 + 1) * tg1;
-    if (rows <= kRunStep) return prefill_chunk_positions(reach);
-    const int first = t - p % tg1;
-    int before = 0, after = 0;
-#pragma unroll
-    for (int i = 1; i <= kRunProbes; ++i) {
-        const int lo = first - i * kRunStep, hi = first + i * kRunStep;
-        if (lo >= 0) before += seq_of_token[lo] == s;
-        if (hi < rows) after += seq_of_token[hi] == s;
-    }
-    return prefill_run_chunk_positions(reach, tg1, n_kv, (before + after + 1) * kRunStep, reach + (after - before) * (kRunStep / 2));
-}
-
 __device__ __forceinline__ void attn_plan(const int32_t *__restrict__ seq_of_token, const int32_t *__restrict__ pos_of_token, int rows, int ct,
                                           int tg1, int n_kv, int32_t *__restrict__ plan0, int32_t *__restrict__ plan1,
                                           int32_t *__restrict__ ct_of_token) {
@@ -88,7 +71,7 @@ __device__ __forceinline__ void attn_plan(const int32_t *__restrict__ seq_of_tok
         const int s = seq_of_token[t], s_before = seq_of_token[before], s_after = seq_of_token[after], p = pos_of_token[t];
         const bool prev_same = t > 0 && s_before == s, next_same = t + 1 < rows && s_after == s;
         r.which = prev_same || next_same;
-        const int tg = r.which ? tg1 : 1, ctw = r.which ? prompt_chunk(seq_of_token, t, s, p, rows, tg1, n_kv) : ct;
+        const int tg = r.which ? tg1 : 1, ctw = r.which ? prompt_chunk_positions(seq_of_token, t, p, rows, tg1, n_kv) : ct;
         if (!prev_same || p % tg == 0) {                     // group leader
             const int cand = min(tg - p % tg, rows - t);     // positions left in the aligned block
             // rows t .. t + n_tok - 1 belong to the sequence: the matches form a prefix of the

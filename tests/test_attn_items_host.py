@@ -3,7 +3,8 @@
 The kernels ask column_end (csrc/common.h) what an item does with each of its columns.  Here the rule is compiled for
 the host and walked over every (block, chunk) item of a prompt: a token whose keys fit one chunk has its output written
 by exactly one item, any other token has exactly one partial per chunk it reaches, and nothing else is written.  The bound on a token's chunks that sizes the partials
-(prefill_max_chunks) is walked too."""
+(prefill_max_chunks) is walked too, and so is the rule that picks a block's chunk size (prompt_chunk_positions): it may read
+what its own sequence has in the step and nothing else of the dispatch."""
 import os
 import subprocess
 
@@ -66,11 +67,57 @@ int main() {
 """
 
 
-def test_every_token_is_written_once_whatever_the_block_and_chunk(tmp_path):
+RULE = r"""
+#include <cstdio>
+#include <vector>
+#include "common.h"
+using namespace dyn;
+// The chunk of every token of a prompt of `n` rows from position p0 on, with `before` and `after` rows of other sequences around it.
+static std::vector<int> chunks(int n, int p0, int before, int after, int tg, int n_kv) {
+    std::vector<int32_t> seq(before + n + after);
+    for (int i = 0; i < (int)seq.size(); ++i) seq[i] = i < before ? i : i < before + n ? before : i - n + 1;
+    std::vector<int> out(n);
+    for (int i = 0; i < n; ++i) out[i] = prompt_chunk_positions(seq.data(), before + i, p0 + i, (int)seq.size(), tg, n_kv);
+    return out;
+}
+int main() {
+    long other_rows = 0, in_block = 0, short_runs = 0, grown = 0;
+    const int heads[][2] = {{32, 8}, {64, 8}, {96, 8}, {128, 8}, {40, 8}, {40, 40}, {12, 12}, {15, 1}};
+    for (auto &h : heads) {
+        const int tg = 16 * (16 / (h[0] / h[1]));
+        for (int n : {2, 40, 600, 768, 960, 1000, 1023, 1024, 1025, 1500, 2048, 4096, 9000})
+            for (int p0 : {0, 7, 1500, 4096, 5003, 7900, 16300, 32700}) {
+                const std::vector<int> alone = chunks(n, p0, 0, 0, tg, h[1]);
+                for (int i = 0; i < n; ++i) {
+                    const int plain = prefill_chunk_positions(((p0 + i) / tg + 1) * tg);
+                    in_block += i && (p0 + i) % tg && alone[i] != alone[i - 1];
+                    short_runs += n <= kRunStep && alone[i] != plain;
+                    grown += alone[i] > plain;
+                }
+                for (int before : {0, 1, 64, 1024, 1100, 5000})
+                    for (int after : {0, 1, 64, 1024, 1100, 5000}) other_rows += chunks(n, p0, before, after, tg, h[1]) != alone;
+            }
+    }
+    printf("%ld %ld %ld %d\n", other_rows, in_block, short_runs, grown > 0);
+}
+"""
+
+
+def compiled(tmp_path, name, source):
     if not os.path.exists(HIPCC):
         pytest.skip("no ROCm toolchain")
-    src, exe = tmp_path / "walk.cpp", tmp_path / "walk"
-    src.write_text(WALK)
+    src, exe = tmp_path / (name + ".cpp"), tmp_path / name
+    src.write_text(source)
     subprocess.check_call([HIPCC, "-x", "hip", "--cuda-host-only", "-std=c++17", "-O1", "-I" + os.path.join(ROOT, "paper_2605_21603_amd", "csrc"),
                            str(src), "-o", str(exe)], stderr=subprocess.DEVNULL)
-    assert int(subprocess.check_output([str(exe)], text=True)) == 0
+    return subprocess.check_output([str(exe)], text=True)
+
+
+def test_a_prompts_chunks_do_not_depend_on_the_rows_around_it(tmp_path):
+    """Alone in its dispatch or with up to 10000 rows around it, on either side, a prompt is cut alike; the tokens of a block are; and a run of
+    at most 1024 rows, wherever it begins in its blocks, has the plain rule.  Long prompts' chunks do grow."""
+    assert compiled(tmp_path, "rule", RULE).split() == ["0", "0", "0", "1"]
+
+
+def test_every_token_is_written_once_whatever_the_block_and_chunk(tmp_path):
+    assert int(compiled(tmp_path, "walk", WALK)) == 0

@@ -237,6 +237,18 @@ def test_long_prompts_take_longer_chunks(prompt, cached):
     assert not torch.equal(y_end, y[-end:])                           # the cuts differ
 
 
+# Prompts of up to 1024 rows behind thousands of positions, each in a micro-batch of its own and all in one dispatch of more rows than that: the same
+# chunks, so the same bits - two prompts, one beside decodes, one across position 8192, and 1024 rows that begin inside a block of positions.
+@pytest.mark.parametrize("n_q,n_kv,prompts,cached,decodes", [(64, 8, 2, 5000, 0), (64, 8, 1, 4096, 64), (32, 8, 1, 7900, 400), (128, 8, 1, 2048, 40), (64, 8, 1, 5013, 1)])
+def test_short_prompts_are_cut_alike_in_dispatches_of_any_size(n_q, n_kv, prompts, cached, decodes):
+    rows = {5000: 600, 4096: 1000, 7900: 700, 2048: 1000, 5013: 1024}[cached]
+    seqs = [(rows, cached + rows)] * prompts + [(1, 1 + i % 90) for i in range(decodes)]
+    w = workload("short", "bf16", 128, n_q, n_kv, 128, 128, seqs, seed=cached)
+    assert w.nano_rows[1] <= 1024 < w.nano_rows[2]
+    data = gen.generate(w)
+    both_schedules(w, data)
+
+
 # The merge's forms: one and two chunks four groups of eight heads at a time, up to eight, more, and more than 64 in two levels; head counts that
 # leave groups of eight part-filled, dims of one and two loads a lane.
 @pytest.mark.parametrize("dtype,n_q,n_kv,hd", [("bf16", 12, 3, 128), ("bf16", 40, 8, 64), ("f32", 3, 1, 64), ("f32", 2, 2, 256), ("bf16", 36, 12, 32)])
