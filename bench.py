@@ -37,10 +37,10 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # instead of going stale silently.
 ATTN_SOURCE = tuple(os.path.join(ROOT, "paper_2605_21603_amd", "csrc", f) for f in ("kernels_attn_mfma.hip", "kernels_attn_plan.hip"))
 ROCPROF_TRAFFIC = {
-    "c2": {"bytes": 1273152307 + 20704870, "source_sha256_16": "3c4eaea37d73b9b5", "kv_chunk_positions": 256,
-           "source": "profiles/c2_sequential_attn_mfma_kernel.md (FETCH_SIZE 621,656.4 x 2.0 KiB + WRITE_SIZE 20,219.6 KiB)"},
-    "c5": {"bytes": 5050507059 + 21974630, "source_sha256_16": "3c4eaea37d73b9b5", "kv_chunk_positions": 1024,
-           "source": "profiles/c5_sequential_32_layer_decode.md (FETCH_SIZE 2,466,067.9 x 2.0 KiB + WRITE_SIZE 21,459.6 KiB)"},
+    "c2": {"bytes": 1273165414 + 20704973, "source_sha256_16": "f4780762182baf88", "kv_chunk_positions": 256,
+           "source": "profiles/c2_sequential_attn_mfma_kernel.md (FETCH_SIZE 621,662.8 x 2.0 KiB + WRITE_SIZE 20,219.7 KiB)"},
+    "c5": {"bytes": 5050693018 + 21975347, "source_sha256_16": "f4780762182baf88", "kv_chunk_positions": 1024,
+           "source": "profiles/c5_sequential_32_layer_decode.md (FETCH_SIZE 2,466,158.7 x 2.0 KiB + WRITE_SIZE 21,460.3 KiB)"},
 }
 
 

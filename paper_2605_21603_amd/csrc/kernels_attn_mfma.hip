@@ -279,13 +279,8 @@ __global__ __launch_bounds__(256, NQG == 1 ? 2 : 1) void attn_mfma_kernel(const 
     attn_decode_items<NQG, 4>(qkv, seq_of_token, pos_of_token, block_table, k_cache, v_cache, out, ld_out, part_o, part_ml, sh, plan, blockIdx.x, gridDim.x);
 }
 
-// Workgroups of a mixed launch that start on query blocks.  The share that would finish both lists together if each CU had its part of memory's
-// rate: memory is busy with fewer, so the decode list ends first, and its workgroups take query blocks after it; the other way round
-// there is no way back (2048 prompt tokens beside 128 decodes behind 4000 positions, half of the CUs on query blocks: a step of 1414 us as two
-// launches 1525).  Costs in us of one CU: a position of a decode item 512 bytes at 19.5 GB/s, a query block's tile of 64 positions 6 beside
-// decodes; the first, the middle and the last query block stand for all.  The share is rounded to whole rounds of query blocks, which are long beside the
-// launch (2048 tokens beside 64 decodes, 384 of them, on 88 / 112 / 128 workgroups: 154 / 172 / 148 us); up to a quarter of the workgroups each
-// takes one.
+// Workgroups of a mixed launch that start on query blocks (mixed_share).  Costs in us of one CU: a position of a decode item 512 bytes at
+// 19.5 GB/s, a query block's tile of 64 positions 6 beside decodes; the first, the middle and the last query block stand for all.
 __device__ __forceinline__ int mixed_prompt_groups(const int32_t *__restrict__ plan, const int32_t *__restrict__ plan_multi,
                                                    const int32_t *__restrict__ pos_of_token, const int32_t *__restrict__ ct_of_token, const AttnShape &sh,
                                                    int groups) {
@@ -295,10 +290,7 @@ __device__ __forceinline__ int mixed_prompt_groups(const int32_t *__restrict__ p
         return (min(ct, pos_of_token[t] + (packed >> 20) - (packed & 0xfffff) * ct) + 63) / 64;
     };
     const float prompts = 1.5f * (tiles(0) + 2 * tiles(entries / 2) + tiles(entries - 1)) * entries, decodes = 0.026f * PS * sh.chunk_pages * plan[0];
-    const int items = entries * sh.n_kv;
-    const float share = max(groups * prompts / (prompts + decodes), 1.0f);
-    const int rounds = items <= groups / 4 ? 1 : max((int)(items / share + 0.5f), 1);
-    return max(min(((items + rounds - 1) / rounds + 7) / 8 * 8, groups - 8), min(8, groups / 2));
+    return mixed_share(entries * sh.n_kv, prompts, decodes, groups);
 }
 
 // Decodes and prompts of one dispatch in one launch, a workgroup per CU: the first (an equal share of every XCD's) claim query blocks, the others

@@ -4,7 +4,7 @@ The kernels ask column_end (csrc/common.h) what an item does with each of its co
 the host and walked over every (block, chunk) item of a prompt: a token whose keys fit one chunk has its output written
 by exactly one item, any other token has exactly one partial per chunk it reaches, and nothing else is written.  The bound on a token's chunks that sizes the partials
 (prefill_max_chunks) is walked too, and so is the rule that picks a block's chunk size (prompt_chunk_positions): it may read
-what its own sequence has in the step and nothing else of the dispatch."""
+what its own sequence has in the step and nothing else of the dispatch.  Last, the share of a mixed launch (mixed_share)."""
 import os
 import subprocess
 
@@ -121,3 +121,29 @@ def test_a_prompts_chunks_do_not_depend_on_the_rows_around_it(tmp_path):
 
 def test_every_token_is_written_once_whatever_the_block_and_chunk(tmp_path):
     assert int(compiled(tmp_path, "walk", WALK)) == 0
+
+
+SHARE = r"""
+#include <cstdio>
+#include "common.h"
+using namespace dyn;
+int main() {
+    long over = 0, outside = 0, full = 0;
+    for (int groups : {1, 2, 7, 8, 9, 16, 64, 128, 256})
+        for (int items = 1; items < 3000; items += 1 + items / 40)
+            for (int parts = 0; parts <= 200; ++parts) {
+                const float prompts = items * 40.f, decodes = prompts * parts / 20.f, share = groups * prompts / (prompts + decodes);
+                const int n = mixed_share(items, prompts, decodes, groups), least = groups / 2 < 8 ? groups / 2 : 8;
+                outside += n < 0 || (groups > 1 && n >= groups);                                 // someone starts on the decodes
+                over += items > groups / 4 && n > least && n > (int)(share + 7.001f) / 8 * 8;    // no more than the share, in eights
+                full += groups == 256 && parts && items > 64 && n > 0.8f * groups && decodes > 0.3f * prompts;
+            }
+    printf("%ld %ld %ld %d %d\n", outside, over, full, mixed_share(288, 702.f, 213.f, 256), mixed_share(384, 3528.f, 3408.f, 256));
+}
+"""
+
+
+def test_a_mixed_launch_leaves_the_decodes_their_share(tmp_path):
+    """Prompts never start on more workgroups than their part of the estimated work, rounded up to eight (one for each XCD), whatever number of
+    rounds that makes; 288 blocks of a share of 196 workgroups go in two rounds of 144, 384 of one of 130 in three."""
+    assert compiled(tmp_path, "share", SHARE).split() == ["0", "0", "0", "144", "128"]
