@@ -154,15 +154,23 @@ __host__ __device__ inline ColumnEnd column_end(int nk, int first, int chunk) {
 // parts cost.  The share that would finish both together if each CU had its part of memory's rate: memory is busy with fewer, so the
 // decodes end first, and their workgroups take query blocks after them; the other way round there is no way back.  The share is
 // cut to whole rounds of query blocks, which are long beside the launch (2048 tokens beside 64 decodes, 384 of them, on 88 / 112 / 128
-// workgroups: 154 / 172 / 148 us); up to a quarter of the workgroups each takes one.
+// workgroups: 154 / 172 / 148 us).  Up to a quarter of the workgroups each takes one, where the decodes are not long beside it: else as many rounds as a
+// fifth of the decodes' time holds, since no workgroup that is through with its query blocks can help with them (attention, apart / one round /
+// this: 33 tokens beside 128 decodes of 500 to 4000 positions, 32 kv heads, 32 blocks, 862 / 921 / 867 us; 300 tokens, 64 blocks, 880 / 920 / 876).
 // Always down to them: what a workgroup too many takes from the decodes nobody gives back.  To the nearest number of rounds, prompts could
 // be left all workgroups but eight, which then had every decode to themselves (attention, launches apart / to the nearest / down, 16 to 40 q heads:
 // 300 tokens behind 4000 positions beside 2 decodes of 4000 104 / 406 / 98 us, beside 16 of up to 3000 104 / 353 / 97; 2500 tokens beside 16
 // 181 / 415 / 165).  Over 210 mixes (7 pairs of head counts, 33 to 2500 tokens, 2 to 200 decodes), against the best of 18 shares: 1.064 -> 1.028 on
-// average; 15 -> 3 of them are slower than apart, by up to 3.9x -> 2 %.
+// average.  Against launches apart on the same tensors, over 378 mixes of 9 pairs of head counts: 1.147x on average, the worst 16 and 32 kv heads beside
+// 128 decodes of up to 6000 positions, 0.954x (738 -> 773 us).
 __host__ __device__ inline int mixed_share(int items, float prompts, float decodes, int groups) {
     const float share = groups * prompts / (prompts + decodes);
-    const int whole = share > 1.0f ? (int)share : 1, rounds = items <= groups / 4 ? 1 : (items + whole - 1) / whole;
+    const int whole = share > 1.0f ? (int)share : 1;
+    int rounds = (items + whole - 1) / whole;
+    if (items <= groups / 4) {
+        const float beside = 0.2f * decodes * items / (prompts * groups);
+        rounds = beside < rounds ? (beside > 1.0f ? (int)beside : 1) : rounds;
+    }
     const int each = ((items + rounds - 1) / rounds + 7) / 8 * 8, most = groups > 8 ? groups - 8 : 0, least = groups / 2 < 8 ? groups / 2 : 8;
     return each < most ? (each > least ? each : least) : most > least ? most : least;
 }

@@ -128,7 +128,7 @@ SHARE = r"""
 #include "common.h"
 using namespace dyn;
 int main() {
-    long over = 0, outside = 0, full = 0;
+    long over = 0, outside = 0, full = 0, longer = 0;
     for (int groups : {1, 2, 7, 8, 9, 16, 64, 128, 256})
         for (int items = 1; items < 3000; items += 1 + items / 40)
             for (int parts = 0; parts <= 200; ++parts) {
@@ -136,14 +136,17 @@ int main() {
                 const int n = mixed_share(items, prompts, decodes, groups), least = groups / 2 < 8 ? groups / 2 : 8;
                 outside += n < 0 || (groups > 1 && n >= groups);                                 // someone starts on the decodes
                 over += items > groups / 4 && n > least && n > (int)(share + 7.001f) / 8 * 8;    // no more than the share, in eights
+                longer += items <= groups / 4 && n > 8 && n < items && (items + n - 1) / n > 0.2f * decodes * items / (prompts * groups) + 1;
                 full += groups == 256 && parts && items > 64 && n > 0.8f * groups && decodes > 0.3f * prompts;
             }
-    printf("%ld %ld %ld %d %d\n", outside, over, full, mixed_share(288, 702.f, 213.f, 256), mixed_share(384, 3528.f, 3408.f, 256));
+    printf("%ld %ld %ld %ld %d %d %d %d\n", outside, over, full, longer, mixed_share(288, 702.f, 213.f, 256), mixed_share(384, 3528.f, 3408.f, 256),
+           mixed_share(40, 90.f, 500.f, 256), mixed_share(32, 6.f, 8400.f, 256));
 }
 """
 
 
 def test_a_mixed_launch_leaves_the_decodes_their_share(tmp_path):
     """Prompts never start on more workgroups than their part of the estimated work, rounded up to eight (one for each XCD), whatever number of
-    rounds that makes; 288 blocks of a share of 196 workgroups go in two rounds of 144, 384 of one of 130 in three."""
-    assert compiled(tmp_path, "share", SHARE).split() == ["0", "0", "0", "144", "128"]
+    rounds that makes; 288 blocks of a share of 196 workgroups go in two rounds of 144, 384 of one of 130 in three.  A few blocks have a workgroup
+each, unless that takes workgroups for nothing from decodes that last much longer: 40 beside as much again, 32 beside a thousand times their time."""
+    assert compiled(tmp_path, "share", SHARE).split() == ["0", "0", "0", "0", "144", "128", "40", "8"]
