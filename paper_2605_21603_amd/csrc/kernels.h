@@ -137,7 +137,8 @@ hipError_t launch_gemm_gate_fold(hipStream_t s, const void *X, int ldx, const vo
 // Planes folded in registers, 128-wide tiles of several heights: tiles[i] m tiles of 96 + 32 i rows.  fold_cut: the heights for a launch, if they beat
 // p's one.
 struct FoldCut { int tiles[3]; };
-bool fold_cut(const GemmPath &p, int rows, int N, FoldCut *out);
+bool fold_cut(const GemmPath &p, int rows, int N, FoldCut *out);     // with weights that stay in the last-level cache
+bool gemm_fold_cut(const GemmPath &p, int rows, int N, int K, int n_cus, FoldCut *out);
 hipError_t launch_gemm_fold_cut(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int S,
                                 const FoldCut &cut);
 // Expert-grouped projection without planes on 256-wide tiles of a height chosen per expert (the grouped launchers

@@ -395,7 +395,7 @@ hipError_t launch_gemm(int dtype, const void *X, int ldx, const void *W, const v
     launch_gemm_bf16<BN, MT, INREG, NS, false, NW>(grid, s, X, ldx, W, R, Y, partial, plane_stride, rows, N, K, S)
     hipError_t e;
     FoldCut fold;
-    if ((n_cus <= 0 || n_cus >= 256) && fold_cut(p, rows, N, &fold)) e = launch_gemm_fold_cut(s, X, ldx, W, R, Y, rows, N, K, S, fold);
+    if (gemm_fold_cut(p, rows, N, K, n_cus, &fold)) e = launch_gemm_fold_cut(s, X, ldx, W, R, Y, rows, N, K, S, fold);
     else if (p.kind == GEMM_TALL) e = p.mt == 256 ? DYN_GEMM(128, 256, false, 3, 8) : p.mt == 384 ? DYN_GEMM(128, 384, false, 2, 8) : DYN_GEMM(128, 512, false, 2, 8);
     else if (p.kind == GEMM_WIDE) e = DYN_GEMM(256, 256, false, 2, 8);
     else if (p.kind == GEMM_MANY && p.bn == 256) e = launch_gemm_fold(grid, s, X, ldx, W, R, Y, rows, N, K, S);

@@ -261,7 +261,8 @@ float longest_share(const int *n, const float *cost, int kinds, float odd = 0.f)
 // The heights with the shortest longest share, tallest tiles first: 192-, 128- and 64-row tiles take 0.80, 0.60 and 0.40 of a 256-row one.  From two
 // rounds on and where 4.5 % are to be had: a height's tiles walk all of W once more.  28672 columns 4096 deep, one height (and the last rows' launch) ->
 // heights of their own, 800 / 1100 / 1300 / 1700 / 2112 rows 232 / 291 / 334 / 407 / 460 -> 207 / 264 / 301 / 386 / 439 us, steps 546 / 665 / 747 / 888 / 1048 -> 524 /
-// 642 / 731 / 869 / 1023; outside the lines 600 rows 186 -> 198, 3000 rows 623 -> 626.
+// 642 / 731 / 869 / 1023; outside the lines 600 rows 186 -> 198, 3000 rows 623 -> 626.  (44 launches of 8 layer widths, 1024 to 8192 deep: 1.07x on average,
+// the least 0.98x.)
 bool wide_cut(int rows, int N, float now, WideCut *out) {
     static const float cost[4] = {1.0f, 0.80f, 0.60f, 0.40f};             // 256, 192, 128, 64 rows
     const int nt = N / 256, units = (rows + 63) / 64;
@@ -322,8 +323,11 @@ hipError_t launch_gemm_fold_cut(hipStream_t s, const void *X, int ldx, const voi
 // tiles take 0.60, 0.50 and 0.43 (a pair's 99 / 83 / 71 us at 4096 x 4096), a CU's odd one 0.6 of its own more, a round of 256 x 128 tiles 0.975.
 // One height -> two, 1100 / 1300 / 1700 / 2112 / 2700 rows: qkv (6144 x 4096) 78 / 86 / 131 / 140 / 161 -> 70 / 76 / 121 / 125 / 141 us, o (4096 x 4096) 78 / 74 / 81 /
 // 98 / 141 -> 67 / 70 / 74 / 87 / 132, down (4096 x 14336) from 1300 rows 220 / 241 / 290 / 425 -> 213 / 225 / 249 / 412; 1900 and 4096 rows, which fill whole
-// rounds, 241 -> 247 and 469 -> 475 with two: left as they are.
-bool fold_cut(const GemmPath &p, int rows, int N, FoldCut *out) {
+// rounds, 241 -> 247 and 469 -> 475 with two: left as they are.  (416 launches of 13 layer widths, 1024 to 28672 deep: 1.036x on average; the same
+// launch measured in another process differs by up to 4 %.)
+// again: what a further height of less than a round costs beside its tiles, in rounds: they walk all of W once more (gemm_fold_cut; all tiles at once
+// walk it together).
+static bool fold_cut(const GemmPath &p, int rows, int N, float again, FoldCut *out) {
     static const float cost[3] = {0.60f, 0.50f, 0.43f};
     if (p.kind != GEMM_MANY || !p.folded) return false;
     const int nt = N / 128, units = (rows + 31) / 32;
@@ -340,11 +344,22 @@ bool fold_cut(const GemmPath &p, int rows, int N, FoldCut *out) {
         const FoldCut c = units <= 3 * k   ? FoldCut{{k, 0, 0}}
                           : units <= 4 * k ? FoldCut{{4 * k - units, units - 3 * k, 0}}
                                            : FoldCut{{0, 5 * k - units, units - 4 * k}};
-        const int n[3] = {c.tiles[2] * nt, c.tiles[1] * nt, c.tiles[0] * nt};
-        const float t = longest_share(n, cost, 3, 0.6f);
+        const int n[3] = {c.tiles[2] * nt, c.tiles[1] * nt, c.tiles[0] * nt}, all = n[0] + n[1] + n[2], last = n[2] ? n[2] : n[1] ? n[1] : n[0];
+        const float t = longest_share(n, cost, 3, 0.6f) + (all > 512 && last < all && last < 512 ? again : 0.f);
         if (t < best) { best = t; *out = c; found = true; }
     }
     return found;
+}
+
+bool fold_cut(const GemmPath &p, int rows, int N, FoldCut *out) { return fold_cut(p, rows, N, 0.f, out); }
+
+// For a launch of N x K weights on n_cus CUs (0: all).  Weights of more than 256 MiB do not stay in the last-level cache from one height's tiles to
+// the next ones', and less than a round of tiles is no longer than their way from HBM: 2 N K bytes at 4.8 TB/s, beside rounds of 20 us for 1024 of K
+// (8192 x 28672, one height / 8 x 128 and 3 x 96 rows / now, 2 x 128 and 11 x 96: 1300 rows 830 / 910 / 797 us, the step 2545 / 2489 / 2375; 1400
+// 864 / 895 / 813, 2607 / 2563 / 2468).
+bool gemm_fold_cut(const GemmPath &p, int rows, int N, int K, int n_cus, FoldCut *out) {
+    if (n_cus > 0 && n_cus < 256) return false;            // (shares of 256 CUs)
+    return fold_cut(p, rows, N, (size_t)N * K > (size_t)1 << 27 ? N * (2.f / 4.8e6f) / (20.f / 1024.f) : 0.f, out);
 }
 
 // Gate/up with planes, some hundred rows: 64 gate and the matching 64 up columns a workgroup, planes folded in registers and gated, where
