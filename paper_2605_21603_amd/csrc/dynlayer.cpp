@@ -55,6 +55,7 @@ struct Dispatch {
     bool any_multi;          // some sequence contributes more than one token to rows r0..r1
     bool any_single = true;  // attention: some sequence contributes exactly one
     int long_rows = 0;       // qkv: rows of sequences that contribute 16 tokens and more
+    int n_cus = 0;           // CUs of its partition, 0: the whole device
     bool noop;               // launches nothing: no rows, or the gate when the projection's epilogue applied it
     std::vector<int> deps;   // dispatches (indices into the plan) whose output rows this one reads
     bool plan = false;          // first norm: its launch also builds the attention work lists of its rows; attention: they have been built
@@ -278,7 +279,7 @@ bool plan_norm_in(const dyn_layer_config &c, const std::vector<Dispatch> &plan, 
     for (const Dispatch &d : plan) {
         const int rows = d.r1 - d.r0, N = op == DYN_OP_QKV ? qkv_width(c) : 2 * c.mlp_inter;
         if (d.op != op || rows <= 0) continue;
-        if (!dyn::gemm_norm_in_supported(c.dtype, rows, N, c.hidden)) return false;
+        if (!dyn::gemm_norm_in_supported(c.dtype, rows, N, c.hidden, d.n_cus)) return false;
         if (op == DYN_OP_QKV && !dyn::gemm_f32_rope_supported(nullptr, c.hidden, nullptr, rows, N, c.hidden, sh)) return false;
     }
     return true;
@@ -405,6 +406,8 @@ dyn_status build_plan(const dyn_layer *L, const dyn_batch *b, const dyn_schedule
             Dispatch d{};
             d.layer = l; d.op = sl.op; d.nano = sl.nano; d.n_nano = sl.n_nano; d.r0 = rows[sl.nano]; d.r1 = rows[sl.nano + sl.n_nano];
             d.stream = sl.stream; d.partition = sl.partition;
+            if (d.partition > 0 && s->mode == DYN_SCHED_EXPLICIT)
+                for (int w = 0; w < s->cu_mask_words; ++w) d.n_cus += __builtin_popcount(s->cu_masks[(d.partition - 1) * s->cu_mask_words + w]);
             // Operators that launch nothing of their own: the SiLU gate where the gate/up projection's dispatch
             // applies it (below); rotary + cache append, which the qkv projection's dispatch applies to the rows it
             // wrote; the second norm, applied by the o projection's dispatch; and from the second layer on
@@ -726,10 +729,7 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
     const char *x_in = d.layer == 0 ? (const char *)b->x : (d.layer % 2 ? base + ws.xa : base + ws.xb);
     char *x_out = d.layer == nl - 1 ? (char *)b->y : (d.layer % 2 ? base + ws.xb : base + ws.xa);
     auto rowp = [&](const char *p, int width) { return p + (size_t)d.r0 * width * e; };
-    dyn::AttnShape sh{c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, b->max_pages_per_seq, L->chunk_pages, ws.max_chunks, 0};
-    if (d.partition > 0 && s->mode == DYN_SCHED_EXPLICIT)
-        for (int i = 0; i < s->cu_mask_words; ++i)
-            sh.n_cus += __builtin_popcount(s->cu_masks[(d.partition - 1) * s->cu_mask_words + i]);
+    dyn::AttnShape sh{c.n_q_heads, c.n_kv_heads, c.head_dim, c.page_size, b->max_pages_per_seq, L->chunk_pages, ws.max_chunks, d.n_cus};
     char *kc = b->k_cache_layers ? (char *)b->k_cache_layers[d.layer] : (char *)b->k_cache + (size_t)d.layer * b->kv_layer_stride;
     char *vc = b->v_cache_layers ? (char *)b->v_cache_layers[d.layer] : (char *)b->v_cache + (size_t)d.layer * b->kv_layer_stride;
     int32_t *const plan = (int32_t *)(base + ws.plan) + (size_t)d.r0 * (ws.max_chunks + 2) * 4;   // attention work lists of these rows

@@ -95,7 +95,7 @@ struct GemmEpilogue {
 
 // The RMSNorm before a projection, applied to the X rows by the projection itself (g null: none); same bits as launch_rmsnorm's rows.
 struct GemmNorm { const void *g = nullptr; float eps = 0.f; };
-bool gemm_norm_in_supported(int dtype, int rows, int N, int K);
+bool gemm_norm_in_supported(int dtype, int rows, int N, int K, int n_cus);
 
 // Y[rows,N] = X[rows,K] W[N,K]^T (+ R[rows,N]); ldx = elements between rows of X (>= K).  partial: fp32 scratch for split-K planes,
 // plane p at partial + p * plane_stride (elements); unused when the split factor is 1.
@@ -113,7 +113,7 @@ bool gemm_f32_rope_supported(const void *X, int ldx, const void *W, int rows, in
 hipError_t launch_gemm_f32_rope(const void *X, int ldx, const void *W, void *Y, int rows, int N, int K, const GemmNorm &norm, const GemmEpilogue &rope,
                                 hipStream_t s);
 bool gemm_f32_gated_rows_supported(int rows, int N2, int K);         // with that many rows, or any
-bool gemm_f32_norm_supported(int rows, int N, int K);                // with rotary or gate, the norm of X in the same launch
+bool gemm_f32_norm_supported(int rows, int N, int K, int n_cus);     // with rotary or gate, the norm of X in the same launch
 hipError_t launch_gemm_f32_gated(const void *X, int ldx, const void *W, void *Y, int ldy, int rows, int N2, int K, const GemmNorm &norm, hipStream_t s);
 // A few rows (at most 16), planes summed in the workgroup (kernels_gemm_rows.hip; launch_gemm calls it).
 bool gemm_rows16_wide_supported(int rows, int N, int K, int S);       // on the whole chip

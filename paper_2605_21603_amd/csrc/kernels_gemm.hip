@@ -429,7 +429,7 @@ namespace {
 bool gemm_experts_on_wide(const GemmGroups &gr, int N, int S) { return S == 1 && N % 256 == 0 && gr.cap / std::max(gr.n_groups, 1) > 200; }
 }  // namespace
 
-bool gemm_norm_in_supported(int dtype, int rows, int N, int K) { return dtype == 0 && gemm_f32_norm_supported(rows, N, K); }
+bool gemm_norm_in_supported(int dtype, int rows, int N, int K, int n_cus) { return dtype == 0 && gemm_f32_norm_supported(rows, N, K, n_cus); }
 
 bool gemm_gated_supported(int dtype, int N2, int K, bool experts) {
     return dtype == 1 ? gemm_split_k(dtype, N2, K) == 1 : !experts && gemm_f32_gated_supported(N2, K);

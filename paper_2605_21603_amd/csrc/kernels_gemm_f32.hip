@@ -622,8 +622,14 @@ bool gemm_f32_gated_rows_supported(int rows, int N2, int K) {
 // 16 / 32 rows 36.1 / 42.3 / 43.4 / 43.8 -> 32.7 / 38.8 / 41.4 / 41.8 us; 512 wide 1 / 8 / 16 rows 41.1 / 47.4 / 48.6 -> 37.8 / 44.7 / 47.8; 1024
 // wide 1 / 4 / 8 rows 47.3 / 49.0 / 49.9 -> 45.3 / 46.8 / 49.3.  Beyond, a workgroup's own pass over X is longer than the launch: 512 wide 24
 // rows 48.4 -> 48.6, 1024 wide 16 rows 52.2 -> 54.4, 2048 wide 1 / 8 rows 84.6 / 91.5 -> 87.3 / 97.3, 4096 wide 8 rows 163 -> 166.
-bool gemm_f32_norm_supported(int rows, int N, int K) {
-    return K % 256 == 0 && K <= 1024 && (long)rows * K <= 8192 && f32_few(rows, N, f32_whole(N, K));
+// Every workgroup makes that pass, so it is one that each CU (n_cus of them, 0: 256) makes once, twice where a pass is short (any depth, up to 768 wide here).
+// Steps, norms of their own -> inside: 1024 wide, 8192 MLP (512 tiles) 1 / 4 / 8 rows 55.5 / 57.6 / 63.4 -> 57.5 / 59.8 / 66.1, 16384 MLP 82.1 / 86.7 / 93.6 -> 85.8 /
+// 91.0 / 100.5; 512 wide, 8192 MLP, 10 / 16 rows 57.6 / 58.5 -> 60.9 / 61.6; 1024 wide, 4096 MLP (256 tiles) on 64 CUs 1 / 8 rows 81.8 / 91.5 -> 89.3 / 101.4; but 256 and
+// 768 wide, 8192 MLP (512 tiles) 46.0 -> 42.3 and 56.4 -> 52.1 at 4 rows.
+bool gemm_f32_norm_supported(int rows, int N, int K, int n_cus) {
+    const bool whole = f32_whole(N, K);
+    const long tiles = (long)((rows + 15) / 16) * ((N + 31) / 32);
+    return K % 256 == 0 && K <= 1024 && (long)rows * K <= 8192 && f32_few(rows, N, whole) && tiles <= (whole ? 1 : 2) * (n_cus > 0 ? n_cus : 256);
 }
 
 hipError_t launch_gemm_f32_gated(const void *X, int ldx, const void *W, void *Y, int ldy, int rows, int N2, int K, const GemmNorm &norm, hipStream_t s) {

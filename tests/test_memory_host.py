@@ -187,3 +187,16 @@ def test_partials_and_lists_hold_every_chunk_of_every_token(seqs, chunk):
     assert layer.schedule_workspace_bytes(hb, B.sequential()) <= layer.workspace_bytes(T, -(-max(c for _, c in seqs) // 16))
     if all(q == 1 for q, _ in seqs):                             # decodes alone: the handle's chunk and nothing more
         assert by_kind["part_o"] == T * 4 * -(-max(c for _, c in seqs) // (chunk or 256)) * 128 * 4
+
+
+@pytest.mark.parametrize("hidden,inter,rows,n_cus,kinds", [
+    (1024, 4096, 8, 0, []), (1024, 8192, 1, 0, ["h"]), (1024, 8192, 8, 0, ["h"]), (512, 8192, 16, 0, ["h"]), (256, 8192, 16, 0, []), (768, 8192, 10, 0, []),
+    (1024, 4096, 1, 64, ["h"]), (1024, 4096, 8, 128, ["h"]), (1024, 1024, 8, 64, []), (256, 1024, 32, 64, [])])
+def test_projections_normalise_their_rows_where_a_cu_does_it_once(hidden, inter, rows, n_cus, kinds):
+    """fp32 steps of few rows hold no normalised rows where the projections apply the norms, which every workgroup of theirs does for itself:
+    not where gate/up has more workgroups than CUs (twice as many where rows are short), of the chip or of the partition it runs on."""
+    sh = gen.LayerShape("f32", hidden, 4, 4, 64, inter)
+    w = gen.Workload("norm_in", sh, ((1, 5),) * rows, 1, (0, rows))
+    layer = B.DynLayer(B.make_config(sh), [{n: 0x1000 for n in ("w_qkv", "w_o", "w_gate_up", "w_down", "g_norm1", "g_norm2")}])
+    sched = B.nano_schedule([0, rows], chain=B.DENSE_CHAIN, partitions=[1], cu_masks=[[(1 << n_cus // 8) - 1] * 8]) if n_cus else B.sequential()
+    assert [r["kind"] for r in layer.schedule_regions(host_batch(w), sched) if r["kind"] == "h"] == kinds
