@@ -814,7 +814,7 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
             }
             if (d.gated) {                                        // DYN_OP_SILU has nothing left to do
                 void *const act = (void *)rowp(base + ws.act, ws.ld_act);
-                if (dyn::gemm_uses_plane_buffer(c.dtype, rows, 2 * I, H) && !dyn::gate_fold_rows(rows, 2 * I, H)) {     // a launch that needs no planes after all leaves gate and up there
+                if (dyn::gemm_uses_plane_buffer(c.dtype, rows, 2 * I, H) && !dyn::gate_fold_taken(rows, 2 * I, H, d.n_cus)) {     // a launch that needs no planes after all leaves gate and up there
                     dyn::GemmEpilogue ep;
                     ep.kind = dyn::GemmEpilogue::GATE;
                     ep.h_out = act;

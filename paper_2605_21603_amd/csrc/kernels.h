@@ -133,6 +133,7 @@ hipError_t launch_gemm_cut(bool gated, hipStream_t s, const void *X, int ldx, co
                            const WideCut &cut);
 // Gate/up with planes folded in registers and the gate in the epilogue (bf16): the tile height for a launch, 0 where planes go over workgroups.
 int gate_fold_rows(int rows, int N2, int K);
+bool gate_fold_taken(int rows, int N2, int K, int n_cus);              // on n_cus CUs, 0: all
 hipError_t launch_gemm_gate_fold(hipStream_t s, const void *X, int ldx, const void *W, void *Y, int ldy, int rows, int N2, int K);
 // Planes folded in registers, 128-wide tiles of several heights: tiles[i] m tiles of 96 + 32 i rows.  fold_cut: the heights for a launch, if they beat
 // p's one.

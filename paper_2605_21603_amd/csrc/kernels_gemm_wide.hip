@@ -387,6 +387,14 @@ int gate_fold_rows(int rows, int N2, int K) {
     return mt <= 256 ? mt : 0;
 }
 
+// Its round is several on a partition, where lower tiles, filled less and with less of W behind each X row, cost more than the planes' way through memory:
+// below 128 CUs on 256-row tiles alone.  Gate/up, planes over workgroups -> folded, 170 / 360 / 500 rows (tiles of 128, 192, 256), 64 CUs: 2048 wide, 8192 MLP
+// 112 / 145 / 178 -> 117 / 150 / 171 us, 2560 wide, 6912 MLP 125 / 162 / 198 -> 131 / 170 / 195; 128 CUs: 78 / 96 / 113 -> 79 / 94 / 105, 84 / 104 / 125 -> 86 / 105 / 118.
+bool gate_fold_taken(int rows, int N2, int K, int n_cus) {
+    const int mt = gate_fold_rows(rows, N2, K);
+    return n_cus <= 0 || n_cus >= 128 ? mt > 0 : mt == 256;
+}
+
 hipError_t launch_gemm_gate_fold(hipStream_t s, const void *X, int ldx, const void *W, void *Y, int ldy, int rows, int N2, int K) {
     const int mt = gate_fold_rows(rows, N2, K), S = gemm_split_k(1, N2, K), grid = (N2 / 128 + 7) / 8 * 8 * ((rows + mt - 1) / mt);
 #define DYN_GATE_FOLD(MT, NS)                                                                                                                          \

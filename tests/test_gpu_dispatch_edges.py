@@ -357,6 +357,18 @@ def test_gate_with_planes_folded(hidden, inter, rows, cut, tile):
     say("%d rows: %.2e" % (rows, check_against_oracle(w, data, y, k, v)))
 
 
+# On a partition of 64 CUs the same planes go over the workgroups again (150 and 340 rows) or stay folded (480, on 256-row tiles), on one of 128 they stay folded: the
+# bits of the whole chip.
+@pytest.mark.parametrize("rows", [150, 340, 480])
+def test_gate_with_planes_on_a_partition(rows):
+    w = workload("gate_part", "bf16", 2048, 16, 4, 128, 8192, [(1, 1 + i % 5) for i in range(rows)], seed=rows)
+    run = GpuRun(w, gen.generate(w))
+    y = run.run(B.sequential())[0]
+    for cus in (8, 16):
+        sched = B.nano_schedule([0, rows], chain=B.DENSE_CHAIN, partitions=[1], cu_masks=[[(1 << cus) - 1] * 8])
+        assert torch.equal(y.view(torch.uint8), run.run(sched)[0].view(torch.uint8))
+
+
 # The same inside the fp32 projection: tiles of any depth (256, 68) and of whole blocks (512, 1024), 16 and 32 rows high, heads of 32, 64 and
 # 256, pages of 16 and 48.  Where the batch or one of its parts keeps the launch of its own - more rows (the first two, whose whole batch
 # takes 64 x 64 tiles and tiles of any depth), heads of 128 and 16 - it is the same bits.

@@ -50,3 +50,16 @@ def test_the_heights_of_a_cut_hold_its_rows():
                     cuts += 1
                     assert 0 <= 32 * sum((3 + i) * t for i, t in enumerate(tiles)) - rows < 96
     assert cuts > 200
+
+
+@pytest.mark.parametrize("hidden,inter", [(2048, 8192), (2560, 6912), (1024, 4096)])
+def test_gate_up_folds_its_planes_on_few_cus_on_the_tallest_tiles_alone(hidden, inter):
+    """One round of tiles on the whole chip is several on a partition: below 128 CUs planes stay spread over the workgroups, but for 256-row tiles."""
+    tile, taken = B.lib()._ZN3dyn14gate_fold_rowsEiii, B.lib()._ZN3dyn15gate_fold_takenEiiii
+    heights = set()
+    for rows in range(64, 600, 7):
+        mt = tile(rows, 2 * inter, hidden)
+        heights.add(mt)
+        assert (mt > 0) == (128 < rows <= 512)
+        assert [taken(rows, 2 * inter, hidden, n) & 0xff for n in (0, 256, 128, 120, 64)] == [mt > 0] * 3 + [mt == 256] * 2
+    assert len(heights) >= 3
