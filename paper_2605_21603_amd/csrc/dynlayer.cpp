@@ -1012,27 +1012,26 @@ void analyse_memory(const dyn_layer *L, const dyn_batch *b, const std::vector<Di
     const size_t e = esize(c);
     const Sizes ws = tensor_sizes(L, b->n_tokens, b->max_pages_per_seq, b->n_tokens > b->n_seqs);
     const int n_slots = (int)plan.size() / c.n_layers;
-    // (fp32 steps of so few rows that their projections normalise and gate at any depth hold less than this counts: the report is of what
-    // the operators exchange with any number of rows.)
-    const bool moe = c.n_experts > 0;
-    const bool gated = c.dtype == DYN_F32 ? dyn::gemm_gated_supported(c.dtype, 2 * c.mlp_inter, c.hidden, moe) : plan_gated(c, plan);
+    const bool moe = c.n_experts > 0, gated = plan_gated(c, plan);                        // as plan_layout
+    const bool norm1 = !norm_in(plan, DYN_OP_QKV), norm2 = !norm_in(plan, DYN_OP_GATE_UP);
+    const bool route = moe && !route_in(plan);                                                        // the router is a dispatch of its own
     const int pairs = moe ? c.top_k : 1, H = c.hidden, I = c.mlp_inter, NQKV = qkv_width(c), NQ = c.n_q_heads * c.head_dim;
     int slot_of[DYN_N_OPS][DYN_MAX_NANO];
     for (auto &r : slot_of) std::fill(r, r + DYN_MAX_NANO, -1);
     for (int i = 0; i < n_slots; ++i)
         for (int nb = plan[i].nano; nb < plan[i].nano + plan[i].n_nano; ++nb) slot_of[plan[i].op][nb] = i;
     // Who writes and who reads what (the projections' dispatches also run the operator that follows
-    // them: qkv rotates and appends, o and down write the next norm's output).
+    // them: qkv rotates and appends, o and down write the next norm's output, o its router's; or the one before them: its norm).
     struct Tensor { int producer; int consumers[2]; size_t row_bytes; bool from_previous_layer; bool present; bool first_layer_only; };
     const Tensor tensors[] = {
         {DYN_OP_DOWN, {DYN_OP_OPROJ, -1}, H * e, true, true, false},                          // layer input (not the caller's x): the residual
-        {DYN_OP_NORM1, {DYN_OP_QKV, -1}, ws.ld_h * e, false, true, true},                     // first norm, first layer
-        {DYN_OP_DOWN, {DYN_OP_QKV, -1}, ws.ld_h * e, true, true, false},                      // first norm, later layers
+        {DYN_OP_NORM1, {DYN_OP_QKV, -1}, ws.ld_h * e, false, norm1, true},                    // first norm, first layer
+        {DYN_OP_DOWN, {DYN_OP_QKV, -1}, ws.ld_h * e, true, norm1, false},                     // first norm, later layers
         {DYN_OP_QKV, {DYN_OP_ATTN, -1}, NQKV * e, false, true, false},                        // q rotated by the projection's dispatch
         {DYN_OP_ATTN, {DYN_OP_OPROJ, -1}, ws.ld_attn * e, false, true, false},
         {DYN_OP_OPROJ, {DYN_OP_DOWN, -1}, H * e, false, true, false},                         // x2: the residual of the MLP
-        {DYN_OP_OPROJ, {moe ? DYN_OP_ROUTE : DYN_OP_GATE_UP, moe ? DYN_OP_GATE_UP : -1}, ws.ld_h * e, false, true, false},   // second norm
-        {route_in(plan) ? DYN_OP_OPROJ : DYN_OP_ROUTE, {DYN_OP_GATE_UP, DYN_OP_DOWN}, (size_t)c.top_k * 8, false, moe, false},   // selected experts and their weights
+        {DYN_OP_OPROJ, {route ? DYN_OP_ROUTE : DYN_OP_GATE_UP, route ? DYN_OP_GATE_UP : -1}, ws.ld_h * e, false, norm2, false},   // second norm
+        {route ? DYN_OP_ROUTE : DYN_OP_OPROJ, {DYN_OP_GATE_UP, DYN_OP_DOWN}, (size_t)c.top_k * 8, false, moe, false},   // selected experts and their weights
         {DYN_OP_GATE_UP, {DYN_OP_SILU, -1}, (size_t)pairs * 2 * I * e, false, !gated, false},
         {gated ? DYN_OP_GATE_UP : DYN_OP_SILU, {DYN_OP_DOWN, -1}, (size_t)pairs * ws.ld_act * e, false, true, false},
     };
