@@ -170,12 +170,18 @@ Sizes tensor_sizes(const dyn_layer *L, int T, int max_pages, bool prompts) {
     return z;
 }
 
-// Scratch a dispatch over `rows` token rows holds while it runs (bytes; 0 = none).
+// Whether a gate/up dispatch of a dense layer folds its planes in registers and gates them, so that it needs no plane buffer.
+bool folds_gate(const dyn_layer_config &c, const Dispatch &d) {
+    return d.gated && c.dtype == DYN_BF16 && dyn::gate_fold_taken(d.r1 - d.r0, 2 * c.mlp_inter, c.hidden, d.n_cus);
+}
+
+// Scratch a dispatch holds while it runs (bytes; 0 = none).
 struct ScratchBytes { size_t planes, part_o, part_ml, lists, moe_planes; };
 
-ScratchBytes dispatch_scratch(const dyn_layer *L, const Sizes &z, int op, int rows) {
+ScratchBytes dispatch_scratch(const dyn_layer *L, const Sizes &z, const Dispatch &d) {
     const dyn_layer_config &c = L->cfg;
     ScratchBytes k{};
+    const int rows = d.r1 - d.r0;
     if (rows <= 0) return k;
     const size_t r = (size_t)rows;
     const int H = c.hidden, I = c.mlp_inter, NQKV = qkv_width(c), NQ = c.n_q_heads * c.head_dim;
@@ -183,7 +189,7 @@ ScratchBytes dispatch_scratch(const dyn_layer *L, const Sizes &z, int op, int ro
     auto planes = [&](int N, int K) {
         return dyn::gemm_uses_plane_buffer(c.dtype, rows, N, K) ? (size_t)dyn::gemm_split_k(c.dtype, N, K) * r * N * sizeof(float) : 0;
     };
-    switch (op) {
+    switch (d.op) {
         case DYN_OP_QKV: k.planes = planes(NQKV, H); break;
         case DYN_OP_OPROJ: k.planes = planes(H, NQ); break;
         case DYN_OP_ATTN:
@@ -195,7 +201,7 @@ ScratchBytes dispatch_scratch(const dyn_layer *L, const Sizes &z, int op, int ro
                 k.lists = r * c.top_k * 2 * c.n_experts * sizeof(int32_t);   // E counts + E lists of up to rows * top_k pairs
                 const int S = dyn::gemm_split_k(c.dtype, 2 * I, H, c.n_experts);
                 if (S > 1 && !dyn::gemm_gated_supported(c.dtype, 2 * I, H, true)) k.planes = (size_t)S * r * c.top_k * 2 * I * sizeof(float);
-            } else {
+            } else if (!folds_gate(c, d)) {
                 k.planes = planes(2 * I, H);
             }
             break;
@@ -588,7 +594,7 @@ WsLayout plan_layout(const dyn_layer *L, const dyn_batch *b, const std::vector<D
     for (int j = 0; j < n_slots; ++j) {
         const Dispatch &d = plan[j];
         if (d.noop) continue;
-        const ScratchBytes kb = dispatch_scratch(L, z, d.op, d.r1 - d.r0);
+        const ScratchBytes kb = dispatch_scratch(L, z, d);
         if (kb.planes) sr[j].planes = add(DYN_REGION_PLANES, j, kb.planes, false);
         if (kb.part_o) sr[j].part_o = add(DYN_REGION_PART_O, j, kb.part_o, false);
         if (kb.part_ml) sr[j].part_ml = add(DYN_REGION_PART_ML, j, kb.part_ml, false);
@@ -814,7 +820,7 @@ dyn_status launch_op(const dyn_layer *L, const dyn_batch *b, const dyn_schedule 
             }
             if (d.gated) {                                        // DYN_OP_SILU has nothing left to do
                 void *const act = (void *)rowp(base + ws.act, ws.ld_act);
-                if (dyn::gemm_uses_plane_buffer(c.dtype, rows, 2 * I, H) && !dyn::gate_fold_taken(rows, 2 * I, H, d.n_cus)) {     // a launch that needs no planes after all leaves gate and up there
+                if (dyn::gemm_uses_plane_buffer(c.dtype, rows, 2 * I, H) && !folds_gate(c, d)) {     // a launch that needs no planes after all leaves gate and up there
                     dyn::GemmEpilogue ep;
                     ep.kind = dyn::GemmEpilogue::GATE;
                     ep.h_out = act;
@@ -1077,7 +1083,7 @@ void analyse_memory(const dyn_layer *L, const dyn_batch *b, const std::vector<Di
             case DYN_OP_GATE_UP:
                 scratch[i] = moe ? lists + (gated ? 0 : (size_t)dyn::gemm_split_k(c.dtype, 2 * I, H, c.n_experts) > 1
                                                             ? (size_t)dyn::gemm_split_k(c.dtype, 2 * I, H, c.n_experts) * r * pairs * 2 * I * sizeof(float) : 0)
-                                 : planes(2 * I, H);
+                                 : folds_gate(c, d) ? 0 : planes(2 * I, H);
                 break;
             case DYN_OP_DOWN:
                 scratch[i] = moe ? lists + (size_t)dyn::gemm_split_k(c.dtype, H, I, c.n_experts) * r * c.top_k * H * sizeof(float) : planes(H, I);

@@ -213,3 +213,17 @@ def test_projections_normalise_their_rows_where_a_cu_does_it_once(hidden, inter,
     layer = B.DynLayer(B.make_config(sh), [{n: 0x1000 for n in ("w_qkv", "w_o", "w_gate_up", "w_down", "g_norm1", "g_norm2")}])
     sched = B.nano_schedule([0, rows], chain=B.DENSE_CHAIN, partitions=[1], cu_masks=[[(1 << n_cus // 8) - 1] * 8]) if n_cus else B.sequential()
     assert [r["kind"] for r in layer.schedule_regions(host_batch(w), sched) if r["kind"] == "h"] == kinds
+
+
+@pytest.mark.parametrize("rows,n_cus,planes", [(128, 0, True), (340, 0, False), (340, 128, False), (340, 64, True), (480, 64, False)])
+def test_gate_up_that_folds_its_planes_reserves_none(rows, n_cus, planes):
+    """2048 wide, 8192 MLP: two planes of gate/up are fp32 rows of 16384 columns each, 45 MB for 340 rows, where they go over the workgroups."""
+    sh = gen.LayerShape("bf16", 2048, 16, 4, 128, 8192)
+    w = gen.Workload("planes", sh, ((1, 5),) * rows, 1, (0, rows))
+    layer = B.DynLayer(B.make_config(sh), [{n: 0x1000 for n in ("w_qkv", "w_o", "w_gate_up", "w_down", "g_norm1", "g_norm2")}])
+    chain = list(B.DENSE_CHAIN)
+    sched = B.nano_schedule([0, rows], chain=chain, partitions=[1], cu_masks=[[(1 << n_cus // 8) - 1] * 8]) if n_cus else B.sequential()
+    mine = [r["bytes"] for r in layer.schedule_regions(host_batch(w), sched) if r["kind"] == "planes" and r["slot"] == chain.index(B.DYN_OP_GATE_UP)]
+    assert mine == ([2 * rows * 16384 * 4] if planes else [])
+    r = layer.memory(host_batch(w), sched)
+    assert r["peak_live_bytes"] <= r["workspace_bytes_schedule"]
