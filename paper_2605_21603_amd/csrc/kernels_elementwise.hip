@@ -80,9 +80,21 @@ __global__ __launch_bounds__(256) void gemm_reduce_norm_kernel(const float *__re
     const size_t row = blockIdx.x;
     const int nv = H / 8;
     vec_t kept[KEEP];
+    // f(i, n) for the thread's vectors i, n counting them.  With the router behind the norm the compiler does not unroll a loop over them, and kept[n] would
+    // lie in scratch memory (80 bytes a lane, 231 registers -> 179): there n is a constant, KEEP for all beyond.
+    auto vectors = [&](auto &&f) {
+        if constexpr (ROUTE) {
+            static_for<0, KEEP>([&](auto n) {
+                if ((int)threadIdx.x + n * 256 < nv) f((int)threadIdx.x + n * 256, n);
+            });
+            for (int i = (int)threadIdx.x + KEEP * 256; i < nv; i += 256) f(i, std::integral_constant<int, KEEP>());
+        } else {
+            int n = 0;
+            for (int i = threadIdx.x; i < nv; i += 256, ++n) f(i, n);
+        }
+    };
     float ss = 0.f;
-    int n = 0;
-    for (int i = threadIdx.x; i < nv; i += 256, ++n) {
+    vectors([&](int i, auto n) {
         const float *p = P + row * H + (size_t)i * 8;
         f32x4 a, b;
         vec_t rv{};
@@ -122,7 +134,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_norm_kernel(const float *__re
         if (n < KEEP) kept[n] = v;
 #pragma unroll
         for (int e = 0; e < 8; ++e) { const float f = bf2f(v[e]); ss = __builtin_fmaf(f, f, ss); }
-    }
+    });
     if constexpr (ROUTE) router.load();                     // beside the row's sum
     ss = wave_sum(ss);
     __shared__ float part[4];
@@ -130,8 +142,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_norm_kernel(const float *__re
     __syncthreads();
     const float total = ((part[0] + part[1]) + part[2]) + part[3];
     const float r = 1.0f / sqrtf(total / (float)H + eps);
-    n = 0;
-    for (int i = threadIdx.x; i < nv; i += 256, ++n) {
+    vectors([&](int i, auto n) {
         // beyond the kept vectors a thread reads back what it stored itself
         const vec_t v = n < KEEP ? kept[n] : *reinterpret_cast<const vec_t *>(Y + row * H + (size_t)i * 8);
         const vec_t gv = *reinterpret_cast<const vec_t *>(g + (size_t)i * 8);
@@ -140,7 +151,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_norm_kernel(const float *__re
         for (int e = 0; e < 8; ++e) o[e] = f2bf(bf2f(v[e]) * r * bf2f(gv[e]));
         *reinterpret_cast<vec_t *>(out + row * ld_out + (size_t)i * 8) = o;
         if constexpr (ROUTE) router(i, o);
-    }
+    });
     if constexpr (ROUTE) {
         __shared__ float slices[4][kMaxExperts];
         route_choose<8>(router.acc, slices, route.E, route.top_k, route.sel + row * route.top_k, route.wgt + row * route.top_k);

@@ -161,3 +161,17 @@ def test_prefill_attention_loop_touches_no_operand_before_its_wait(tmp_path_fact
     last_mfma = max(j for j, x in enumerate(body) if MFMA in x)
     violations, n = replay_lds_counter(body[head:last_mfma + 1])
     assert n == 48 and not violations, violations[:5]
+
+
+def test_the_norm_behind_summed_planes_keeps_its_row_in_registers(tmp_path):
+    """One workgroup a row, whose vectors a thread keeps from the sum to the scaling: indexed by a loop's counter they lie in scratch memory, as they did
+    with the router in the same launch (80 bytes a lane)."""
+    lines = compile_to_isa(tmp_path, "kernels_elementwise.hip")
+    scratch, name = {}, None
+    for l in lines:
+        if l.strip().startswith(".amdhsa_kernel "):
+            name = l.split()[1]
+        elif l.strip().startswith(".amdhsa_private_segment_fixed_size "):
+            scratch[name] = int(l.split()[1])
+    mine = {n: b for n, b in scratch.items() if "gemm_reduce_norm_kernel" in n or "rmsnorm" in n}
+    assert len(mine) >= 8 + 3 and not any(mine.values()), mine
