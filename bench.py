@@ -32,15 +32,15 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # HBM bytes per launch of the attention kernel, read with rocprofv3 counters (FETCH_SIZE and
 # WRITE_SIZE in runs of their own, scaled by a 1 GiB copy probe).  Counters cannot be read
 # from inside this process, so the figure of the committed counter summary is repeated here,
-# together with one hash of the sources it was measured on - the kernel, and the work lists whose order
-# decides which wave walks what: if one has changed since, the figure is withheld (traffic = null)
-# instead of going stale silently.
-ATTN_SOURCE = tuple(os.path.join(ROOT, "paper_2605_21603_amd", "csrc", f) for f in ("kernels_attn_mfma.hip", "kernels_attn_plan.hip"))
+# together with one hash of the sources it was measured on - the kernel, the work lists whose order
+# decides which wave walks what, and the layout of the partials it writes: if one has changed since, the figure is
+# withheld (traffic = null) instead of going stale silently.
+ATTN_SOURCE = tuple(os.path.join(ROOT, "paper_2605_21603_amd", "csrc", f) for f in ("attn_shape.h", "kernels_attn_mfma.hip", "kernels_attn_plan.hip"))
 ROCPROF_TRAFFIC = {
-    "c2": {"bytes": 1273165414 + 20704973, "source_sha256_16": "f4780762182baf88", "kv_chunk_positions": 256,
-           "source": "profiles/c2_sequential_attn_mfma_kernel.md (FETCH_SIZE 621,662.8 x 2.0 KiB + WRITE_SIZE 20,219.7 KiB)"},
-    "c5": {"bytes": 5050693018 + 21975347, "source_sha256_16": "f4780762182baf88", "kv_chunk_positions": 1024,
-           "source": "profiles/c5_sequential_32_layer_decode.md (FETCH_SIZE 2,466,158.7 x 2.0 KiB + WRITE_SIZE 21,460.3 KiB)"},
+    "c2": {"bytes": 1273186509 + 20703949, "source_sha256_16": "c209e9b72934455d", "kv_chunk_positions": 256,
+           "source": "profiles/c2_sequential_attn_mfma_kernel.md (FETCH_SIZE 621,673.1 x 2.0 KiB + WRITE_SIZE 20,218.7 KiB)"},
+    "c5": {"bytes": 5050641818 + 21974528, "source_sha256_16": "c209e9b72934455d", "kv_chunk_positions": 1024,
+           "source": "profiles/c5_sequential_32_layer_decode.md (FETCH_SIZE 2,466,133.7 x 2.0 KiB + WRITE_SIZE 21,459.5 KiB)"},
 }
 
 

@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "attn_shape.h"
+
 namespace dyn {
 
 constexpr int kMaxHalfDim = 128;   // rotary tables are passed by value: head_dim <= 256
@@ -13,19 +15,6 @@ constexpr int kMaxHalfDim = 128;   // rotary tables are passed by value: head_di
 struct RopeTable {                 // theta_i = base^(-2i/d), i < d/2, computed on the host in fp64
     double inv_freq[kMaxHalfDim];
 };
-
-struct AttnShape {
-    int n_q, n_kv, head_dim, page_size;
-    int max_pages_per_seq;         // block-table row length
-    int chunk_pages;               // pages per split-KV chunk (a constant of the layer)
-    int max_chunks;                // the most chunks a token of the batch can have
-    int n_cus;                     // CUs of the stream's partition (0: whole device); sizes the persistent launch
-};
-
-// Where chunk c of a row's q head lies in the split-KV partial arrays: a token's chunks behind one another, the heads of one side by side, so
-// what is written at one time - a few tokens' chunks - is one piece of memory.  (Chunk by chunk over all rows, a token's chunks lay a
-// whole number of MiB apart: 256 tokens of up to 32 chunks, attention 861 us where this takes 858, three layers' step 3198 -> 3176.)
-__host__ __device__ inline size_t part_index(const AttnShape &sh, int row, int head, int c) { return ((size_t)row * sh.max_chunks + c) * sh.n_q + head; }
 
 // Expert grouping of a projection (all fields zero: plain GEMM).  Group e has counts[e] rows;
 // row i of the group reads X row lists[e * cap + i] / x_div and writes output row
@@ -193,7 +182,7 @@ hipError_t launch_norm_plan(const void *x, const void *g, void *out, int ld_out,
                             const int32_t *pos_of_token, int32_t *plan, const AttnShape &sh, hipStream_t s);
 
 // Causal paged attention for token rows; part_o / part_ml are the split-KV partial arrays
-// ([max_chunks, rows, n_q, head_dim] and [max_chunks, rows, n_q, 2]); plan is scratch for the
+// ([rows, max_chunks, n_q, head_dim] and [rows, max_chunks, n_q, 2], part_index); plan is scratch for the
 // device-built work lists (AttnPlan); any_single / any_multi: some sequence has one / more
 // than one token in these rows (host knowledge; whether the decode / the prefill form is launched).
 hipError_t launch_attention(int dtype, const void *qkv, const int32_t *seq_of_token, const int32_t *pos_of_token,

@@ -45,9 +45,11 @@ def test_committed_counter_figures_belong_to_the_attention_kernel_as_it_is():
         assert 1.0 <= t["bytes"] / bench.attention_bytes(gen.config(wl)) < 1.06
 
 
-def test_the_counter_guard_covers_the_kernel_and_its_work_lists(tmp_path):
+def test_the_counter_guard_covers_the_kernel_its_work_lists_and_its_partials(tmp_path):
     names = [os.path.basename(p) for p in bench.ATTN_SOURCE]
-    assert sorted(names) == ["kernels_attn_mfma.hip", "kernels_attn_plan.hip"]
+    assert sorted(names) == ["attn_shape.h", "kernels_attn_mfma.hip", "kernels_attn_plan.hip"]
+    text = "".join(open(p).read() for p in bench.ATTN_SOURCE)
+    assert "inline size_t part_index(" in text and "__global__" in text         # the index of a partial is defined in what is hashed
     hashes = {bench.source_hash(bench.ATTN_SOURCE)}
     for changed in names:
         copies = []
@@ -56,7 +58,7 @@ def test_the_counter_guard_covers_the_kernel_and_its_work_lists(tmp_path):
             copy.write_bytes(open(p, "rb").read() + (b"\n" if os.path.basename(p) == changed else b""))
             copies.append(str(copy))
         hashes.add(bench.source_hash(copies))
-    assert len(hashes) == 3
+    assert len(hashes) == 1 + len(names)
 
 
 def test_more_than_one_gpu_is_refused_with_a_message():
