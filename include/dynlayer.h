@@ -83,7 +83,7 @@ typedef struct {
                                   often (32 layers at batch 256, contexts 1024..8192: 256 -> 2048 positions takes 4.5 %
                                   off the layer; batch 128, contexts 512..4096: 1024 is 1 % faster, 2048 5 % slower).
                                   Sequences of several tokens are cut by a rule of their own whatever this says (1024
-                                  positions; more behind 8192 cached ones, and for a sequence of more than 1024 tokens in the
+                                  positions; more behind 8192 cached ones, and for a sequence of more than 2560 tokens in the
                                   step where its query blocks alone fill the chip), which reads that sequence's tokens and
                                   positions and nothing else of the batch */
 } dyn_layer_config;

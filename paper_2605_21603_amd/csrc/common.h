@@ -99,35 +99,40 @@ __host__ __device__ inline int prefill_chunk_positions(int reach) {
 constexpr int kPrefillChunkPagesMax = 8192 / 16;     // in 16-position pages
 // The same for a block of a long prompt: its sequence has about `rows` tokens in this step with about `mean_keys` keys each, in blocks
 // of `tg`, for n_kv kv heads.  Such a prompt has work for all 256 CUs from its query blocks alone, and what a finer cut costs is a
-// partial set written and read back per chunk and token: chunks double (to 8192) while one is at most half of what a CU
-// gets.  4096 tokens behind 8192 positions,
-// chunks of 2048 -> 8192: merge 88 -> 33 us with the merge's own form, a step 2482 -> 2435; 4096 alone, 1024 -> 2048: chunk kernel 205 -> 188 us.
+// partial set written and read back per chunk and token: chunks double, to 4096, or to the one chunk of 8192 that holds a whole block,
+// while one is at most half of what a CU gets.  Attention,
+// chunks of 1024 or 2048 -> these: 4096 tokens alone 247 -> 209 us, behind 2000 positions 433 -> 395, behind 8000 846 -> 801; 6000 behind 2000 651 -> 531.  Beyond, or with
+// shorter prompts, what is left over of a CU's last chunk costs more: chunks of 8192 for 4096 tokens behind 8000 positions 812, for 2300 behind 16000
+// 712 -> 779, of 4096 for 1200 behind 8000 235 -> 275.  (450 prompts of 10 pairs of head counts, 600 to 10000 tokens behind 0 to 30000 positions: 0.977 of the time
+// on average, none longer.)
 __host__ __device__ inline int prefill_run_chunk_positions(int reach, int tg, int n_kv, int rows, int mean_keys) {
     int ct = prefill_chunk_positions(reach);
     const long long cu = (long long)n_kv * rows * mean_keys / (256 * tg);
-    while (ct < 8192 && ct < reach && 4 * ct <= cu) ct *= 2;
+    const int most = reach <= 8192 ? 8192 : 4096;
+    while (ct < most && ct < reach && 4 * ct <= cu) ct *= 2;
     return ct;
 }
-// The chunk size in use: that of the tokens in the aligned block of `tg` positions of a multi-token sequence that row t, at position p, lies in.
-// A function of that sequence's rows and positions in this step, and of nothing else in the dispatch (which holds whole
-// sequences): the length of its run of rows is read off the rows whole 1024s in front of the block and behind it, and a run that none of
-// them is part of - any of up to 1024 rows, wherever it begins in its blocks - has the plain rule.  (So in a dispatch of up to 1024 rows
-// there is nothing to read.)
-constexpr int kRunStep = 1024, kRunProbes = 4;
-__host__ __device__ inline int prompt_chunk_positions(const int32_t *seq_of_token, int t, int p, int rows, int tg, int n_kv) {
-    const int reach = (p / tg + 1) * tg, first = t - p % tg, last = first + tg - 1;
+// The chunk size in use: that of the tokens in the aligned block of `tg` positions of a multi-token sequence that row t, at position p, lies in,
+// where rows start .. end - 1 are the sequence's (a dispatch holds whole sequences).  A function of that sequence's rows and positions in this
+// step, and of nothing else in the dispatch; up to 2560 rows the plain rule.
+constexpr int kLongRun = 2560;
+__host__ __device__ inline int prompt_chunk_positions(int t, int p, int start, int end, int tg, int n_kv) {
+    const int reach = (p / tg + 1) * tg, rows = end - start;
+    if (rows <= kLongRun) return prefill_chunk_positions(reach);
+    return prefill_run_chunk_positions(reach, tg, n_kv, rows, p - (t - start) + (rows + 1) / 2);
+}
+// The run of rows, of one sequence, that row `at` of a dispatch of `rows` rows lies in.  count(row, step): how many of the rows row + step, row + 2 step, ..
+// row + 64 step are the sequence's, before the first that is not or is no row.  (Up to 64 x 4161 rows to either side.)
+struct Run { int start, end; };
+template <class Count>
+__host__ __device__ inline Run run_around(int at, int rows, Count &&count) {
     int before = 0, after = 0;
-    if (rows > kRunStep) {
-        const int s = seq_of_token[t];
-#pragma unroll
-        for (int i = 1; i <= kRunProbes; ++i) {
-            const int lo = first - i * kRunStep, hi = last + i * kRunStep;
-            if (lo >= 0) before += seq_of_token[lo] == s;
-            if (hi < rows) after += seq_of_token[hi] == s;
-        }
+    for (int step = rows > 4096 ? 4096 : 64; step >= 1; step /= 64) {
+        const int lo = count(at - before, -step), hi = count(at + after, step);
+        before += lo * step;
+        after += hi * step;
     }
-    if (before + after == 0) return prefill_chunk_positions(reach);
-    return prefill_run_chunk_positions(reach, tg, n_kv, (before + after + 1) * kRunStep, reach + (after - before) * (kRunStep / 2));
+    return Run{at - before, at + after + 1};
 }
 // The most chunks a token with at most `positions` keys can have under that rule: a chunk size below 8192 is taken up to
 // eight chunks' reach only.

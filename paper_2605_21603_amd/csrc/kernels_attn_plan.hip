@@ -63,15 +63,36 @@ __device__ __forceinline__ void attn_plan(const int32_t *__restrict__ seq_of_tok
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int chunk_pages = ct / PS, bucket_pages = max(1, (chunk_pages + kPlanBuckets - 1) / kPlanBuckets);
 
+    // The rows of the sequence that row t belongs to, as far as they matter: a sequence of more than kLongRun rows has the first or the last of a
+    // wave's 64 rows, so the wave looks for the ends of those two, 64 rows at a time, unless its last rows were of the same.  All lanes call this.
+    // (A lane for itself, in steps around its block: lists and norm of 4096 / 8192 rows 24 / 39 -> 29 / 53 us in 8 steps, 31 / 70 in 20; this 27 / 44.)
+    Run known{0, 0};
+    auto run_of = [&](int t) {
+        Run run{t, t + 1};
+        const int first = __builtin_amdgcn_readfirstlane(t);
+        if (rows <= kLongRun || first >= rows) return run;
+        for (int edge : {first, min(first + 63, rows - 1)}) {
+            if (edge < known.start || edge >= known.end) {
+                const int s = seq_of_token[edge];
+                known = run_around(edge, rows, [&](int row, int step) {
+                    const int r = row + step * (lane + 1);
+                    return (int)__popcll(__ballot(r >= 0 && r < rows && seq_of_token[min(max(r, 0), rows - 1)] == s));
+                });
+            }
+            if (t >= known.start && t < known.end) run = known;
+        }
+        return run;
+    };
+
     // What token row t contributes: which list, how many entries, and for list 0 the buckets of
     // its chunks (all but the last have the sequence's balanced chunk size, the last the rest).
-    auto classify = [&](int t) {
+    auto classify = [&](int t, const Run &run) {
         PlanRow r{0, 0, 0, 0, 0};
         const int before = max(t - 1, 0), after = min(t + 1, rows - 1);
         const int s = seq_of_token[t], s_before = seq_of_token[before], s_after = seq_of_token[after], p = pos_of_token[t];
         const bool prev_same = t > 0 && s_before == s, next_same = t + 1 < rows && s_after == s;
         r.which = prev_same || next_same;
-        const int tg = r.which ? tg1 : 1, ctw = r.which ? prompt_chunk_positions(seq_of_token, t, p, rows, tg1, n_kv) : ct;
+        const int tg = r.which ? tg1 : 1, ctw = r.which ? prompt_chunk_positions(t, p, run.start, run.end, tg1, n_kv) : ct;
         if (!prev_same || p % tg == 0) {                     // group leader
             const int cand = min(tg - p % tg, rows - t);     // positions left in the aligned block
             // rows t .. t + n_tok - 1 belong to the sequence: the matches form a prefix of the
@@ -110,11 +131,16 @@ __device__ __forceinline__ void attn_plan(const int32_t *__restrict__ seq_of_tok
     for (int b = 0; b < kBatches; ++b) {
         const int t = b * 1024 + (int)threadIdx.x;
         kept[b] = PlanRow{0, 0, 0, 0, 0};
-        if (t < rows) kept[b] = classify(t);
+        const Run run = run_of(t);
+        if (t < rows) kept[b] = classify(t, run);
     }
 #pragma unroll
     for (int b = 0; b < kBatches; ++b) count(kept[b]);
-    for (int t = kBatches * 1024 + (int)threadIdx.x; t < rows; t += 1024) count(classify(t));
+    for (int t0 = kBatches * 1024; t0 < rows; t0 += 1024) {
+        const int t = t0 + (int)threadIdx.x;
+        const Run run = run_of(t);
+        if (t < rows) count(classify(t, run));
+    }
     __syncthreads();
     int base[NL];                                             // next free entry of each bucket / of list 1
     base[0] = 0;
@@ -176,7 +202,8 @@ __device__ __forceinline__ void attn_plan(const int32_t *__restrict__ seq_of_tok
         if (b * 1024 < rows) place(b * 1024 + (int)threadIdx.x, kept[b]);
     for (int t0 = kBatches * 1024; t0 < rows; t0 += 1024) {
         const int t = t0 + (int)threadIdx.x;
-        place(t, t < rows ? classify(t) : PlanRow{0, 0, 0, 0, 0});
+        const Run run = run_of(t);
+        place(t, t < rows ? classify(t, run) : PlanRow{0, 0, 0, 0, 0});
     }
     if (threadIdx.x == 0) { plan0[0] = total0; plan1[0] = base[kPlanBuckets]; plan1[1] = 0; }   // list sizes; list 1's work counter
 }

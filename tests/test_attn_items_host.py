@@ -3,8 +3,8 @@
 The kernels ask column_end (csrc/common.h) what an item does with each of its columns.  Here the rule is compiled for
 the host and walked over every (block, chunk) item of a prompt: a token whose keys fit one chunk has its output written
 by exactly one item, any other token has exactly one partial per chunk it reaches, and nothing else is written.  The bound on a token's chunks that sizes the partials
-(prefill_max_chunks) is walked too, and so is the rule that picks a block's chunk size (prompt_chunk_positions): it may read
-what its own sequence has in the step and nothing else of the dispatch.  Last, the share of a mixed launch (mixed_share)."""
+(prefill_max_chunks) is walked too, and so is the rule that picks a block's chunk size (prompt_chunk_positions): it depends on
+what its own sequence has in the step and on nothing else of the dispatch.  Last, the share of a mixed launch (mixed_share)."""
 import os
 import subprocess
 
@@ -46,7 +46,7 @@ int main() {
         const int TG = 16 / G;
         for (int p0 : {0, 1, 959, 1000}) {
             bad += wrong(p0, 20000, 16 * TG, [](int reach) { return prefill_chunk_positions(reach); });
-            for (int rows : {1024, 5120}) bad += wrong(p0, 20000, 16 * TG, [=](int reach) { return prefill_run_chunk_positions(reach, 16 * TG, 8, rows, reach); });
+            for (int rows : {2624, 5120}) bad += wrong(p0, 20000, 16 * TG, [=](int reach) { return prefill_run_chunk_positions(reach, 16 * TG, 8, rows, reach); });
             for (int ct : {64, 240, 256, 1024}) bad += wrong(p0, 3000, 4 * TG, [ct](int) { return ct; });
         }
     }
@@ -72,33 +72,47 @@ RULE = r"""
 #include <vector>
 #include "common.h"
 using namespace dyn;
-// The chunk of every token of a prompt of `n` rows from position p0 on, with `before` and `after` rows of other sequences around it.
-static std::vector<int> chunks(int n, int p0, int before, int after, int tg, int n_kv) {
+// The chunk of every token of a prompt of `n` rows from position p0 on, with `before` and `after` rows of other sequences around it, the run's ends
+// looked for from each row as a wave does it from its first and last.
+static std::vector<int> chunks(int n, int p0, int before, int after, int tg, int n_kv, long &ends) {
     std::vector<int32_t> seq(before + n + after);
     for (int i = 0; i < (int)seq.size(); ++i) seq[i] = i < before ? i : i < before + n ? before : i - n + 1;
     std::vector<int> out(n);
-    for (int i = 0; i < n; ++i) out[i] = prompt_chunk_positions(seq.data(), before + i, p0 + i, (int)seq.size(), tg, n_kv);
+    for (int i = 0; i < n; ++i) {
+        auto count = [&](int row, int step) {
+            int k = 0;
+            for (int r = row + step; k < 64 && r >= 0 && r < (int)seq.size() && seq[r] == before; r += step) ++k;
+            return k;
+        };
+        const int t = before + i;
+        const Run run = run_around(t, (int)seq.size(), count);
+        ends += run.start != before || run.end != before + n;
+        out[i] = prompt_chunk_positions(t, p0 + i, run.start, run.end, tg, n_kv);
+    }
     return out;
 }
 int main() {
-    long other_rows = 0, in_block = 0, short_runs = 0, grown = 0;
+    long other_rows = 0, in_block = 0, short_runs = 0, grown = 0, ends = 0;
     const int heads[][2] = {{32, 8}, {64, 8}, {96, 8}, {128, 8}, {40, 8}, {40, 40}, {12, 12}, {15, 1}};
     for (auto &h : heads) {
         const int tg = 16 * (16 / (h[0] / h[1]));
-        for (int n : {2, 40, 600, 768, 960, 1000, 1023, 1024, 1025, 1500, 2048, 4096, 9000})
+        for (int n : {2, 40, 600, 1000, 1024, 1025, 2048, 2500, 2559, 2560, 2561, 2600, 2700, 3000, 4096, 9000})
             for (int p0 : {0, 7, 1500, 4096, 5003, 7900, 16300, 32700}) {
-                const std::vector<int> alone = chunks(n, p0, 0, 0, tg, h[1]);
+                const std::vector<int> alone = chunks(n, p0, 0, 0, tg, h[1], ends);
                 for (int i = 0; i < n; ++i) {
                     const int plain = prefill_chunk_positions(((p0 + i) / tg + 1) * tg);
                     in_block += i && (p0 + i) % tg && alone[i] != alone[i - 1];
-                    short_runs += n <= kRunStep && alone[i] != plain;
+                    short_runs += n <= kLongRun && alone[i] != plain;
                     grown += alone[i] > plain;
                 }
-                for (int before : {0, 1, 64, 1024, 1100, 5000})
-                    for (int after : {0, 1, 64, 1024, 1100, 5000}) other_rows += chunks(n, p0, before, after, tg, h[1]) != alone;
+                for (int before : {0, 1, 64, 1100, 2500, 5000})
+                    for (int after : {0, 1, 64, 1100, 2500, 5000}) other_rows += chunks(n, p0, before, after, tg, h[1], ends) != alone;
             }
     }
-    printf("%ld %ld %ld %d\n", other_rows, in_block, short_runs, grown > 0);
+    long uneven = 0;
+    for (int ct : chunks(4096, 8192, 1, 1, 64, 8, ends)) uneven += ct != 4096;
+    for (int n : {5000, 20000, 100000}) chunks(n, 0, 5, 9, 64, 8, ends);
+    printf("%ld %ld %ld %ld %d %ld\n", ends, other_rows, in_block, short_runs, grown > 0, uneven);
 }
 """
 
@@ -115,8 +129,9 @@ def compiled(tmp_path, name, source):
 
 def test_a_prompts_chunks_do_not_depend_on_the_rows_around_it(tmp_path):
     """Alone in its dispatch or with up to 10000 rows around it, on either side, a prompt is cut alike; the tokens of a block are; and a run of
-    at most 1024 rows, wherever it begins in its blocks, has the plain rule.  Long prompts' chunks do grow."""
-    assert compiled(tmp_path, "rule", RULE).split() == ["0", "0", "0", "1"]
+    at most 2560 rows, wherever it begins in its blocks, has the plain rule.  Long prompts' chunks do grow, alike over the whole of one of 4096 rows
+behind 8192 positions."""
+    assert compiled(tmp_path, "rule", RULE).split() == ["0", "0", "0", "0", "1", "0"]
 
 
 def test_every_token_is_written_once_whatever_the_block_and_chunk(tmp_path):

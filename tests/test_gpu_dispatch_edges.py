@@ -237,16 +237,16 @@ def test_long_prompts_take_longer_chunks(prompt, cached):
     assert not torch.equal(y_end, y[-end:])                           # the cuts differ
 
 
-# Prompts of up to 1024 rows behind thousands of positions, each in a micro-batch of its own and all in one dispatch of more rows than that: the same
-# chunks, so the same bits - two prompts, one beside decodes, one across position 8192, and 1024 rows that begin inside a block of positions.
-@pytest.mark.parametrize("n_q,n_kv,prompts,cached,decodes", [(64, 8, 2, 5000, 0), (64, 8, 1, 4096, 64), (32, 8, 1, 7900, 400), (128, 8, 1, 2048, 40), (64, 8, 1, 5013, 1)])
-def test_short_prompts_are_cut_alike_in_dispatches_of_any_size(n_q, n_kv, prompts, cached, decodes):
-    rows = {5000: 600, 4096: 1000, 7900: 700, 2048: 1000, 5013: 1024}[cached]
+# Prompts behind thousands of positions, each in a micro-batch of its own and all in one dispatch of more rows than that: the same chunks, so the same
+# bits - two prompts, one beside decodes, one across position 8192, 1024 rows that begin inside a block of positions; then runs at the 2560 rows
+# from which on their length is read off the rows around, and above.
+@pytest.mark.parametrize("n_q,n_kv,rows,prompts,cached,decodes", [
+    (64, 8, 600, 2, 5000, 0), (64, 8, 1000, 1, 4096, 64), (32, 8, 700, 1, 7900, 400), (128, 8, 1000, 1, 2048, 40), (64, 8, 1024, 1, 5013, 1),
+    (64, 8, 2550, 1, 5013, 20), (32, 8, 2560, 1, 7000, 3), (32, 8, 2600, 2, 4090, 0), (40, 8, 2700, 1, 3001, 70)])
+def test_prompts_are_cut_alike_in_dispatches_of_any_size(n_q, n_kv, rows, prompts, cached, decodes):
     seqs = [(rows, cached + rows)] * prompts + [(1, 1 + i % 90) for i in range(decodes)]
-    w = workload("short", "bf16", 128, n_q, n_kv, 128, 128, seqs, seed=cached)
-    assert w.nano_rows[1] <= 1024 < w.nano_rows[2]
-    data = gen.generate(w)
-    both_schedules(w, data)
+    w = workload("cuts", "bf16", 128, n_q, n_kv, 128, 128, seqs, seed=cached)
+    both_schedules(w, gen.generate(w))
 
 
 # The merge's forms: one and two chunks four groups of eight heads at a time, up to eight, more, and more than 64 in two levels; head counts that
