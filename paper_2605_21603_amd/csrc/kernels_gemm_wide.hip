@@ -378,13 +378,16 @@ __global__ __launch_bounds__(512, 1) void gemm_gate_fold_kernel(const bf16_t *__
 
 // Its tile height for a launch, 0: not taken.  Above 128 rows, while one round of tiles of up to 256 rows holds them; steps, planes over workgroups -> folded:
 // 2048 wide, 64-wide heads 130 / 200 / 250 / 340 / 480 rows 94 / 99 / 103 / 150 / 154 -> 90 / 93 / 97 / 143 / 142 us; 2560 wide 130 / 300 / 500 rows 104 / 139 / 172 ->
-// 97 / 135 / 163; 1024 wide 130 / 300 / 500 rows 60 / 82 / 89 -> 54 / 73 / 78.
+// 97 / 135 / 163; 1024 wide 130 / 300 / 500 rows 60 / 82 / 89 -> 54 / 73 / 78.  (Gate/up of 11 layer widths, 1024 to 5120 deep, 12 row counts each: 1.016x to 1.220x
+// on average.)  What it saves is the same at any depth, and below some height a tile's own time grows faster with it than that of planes on 128 rows: deeper than that
+// from 192 rows a tile on (8192 wide, 4096 MLP, tiles of 64 / 128 rows, 160 / 300 rows 78.5 / 100 -> 87.5 / 105 us; 8192 MLP, tiles of 128 / 192 / 256, 129 / 300 / 384 rows
+// 0.95x / 1.04x / 1.09x).
 int gate_fold_rows(int rows, int N2, int K) {
     if (gemm_split_k(1, N2, K) == 1 || N2 < 8192 || N2 % 512 || rows <= 128 || rows > 512) return 0;
     const int nt = N2 / 128, m_tiles = 256 / nt;           // m tiles of one round
     if (m_tiles < 1) return 0;
     const int mt = ((rows + m_tiles - 1) / m_tiles + 63) / 64 * 64;
-    return mt <= 256 ? mt : 0;
+    return mt <= 256 && (K <= 5120 || mt >= 192) ? mt : 0;
 }
 
 // Its round is several on a partition, where lower tiles, filled less and with less of W behind each X row, cost more than the planes' way through memory:

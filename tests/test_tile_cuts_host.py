@@ -63,3 +63,12 @@ def test_gate_up_folds_its_planes_on_few_cus_on_the_tallest_tiles_alone(hidden, 
         assert (mt > 0) == (128 < rows <= 512)
         assert [taken(rows, 2 * inter, hidden, n) & 0xff for n in (0, 256, 128, 120, 64)] == [mt > 0] * 3 + [mt == 256] * 2
     assert len(heights) >= 3
+
+
+@pytest.mark.parametrize("hidden,inter,low", [(4096, 4096, True), (5120, 8192, True), (8192, 4096, False), (8192, 8192, False)])
+def test_gate_up_of_deep_weights_folds_its_planes_on_tall_tiles_alone(hidden, inter, low):
+    """A low tile moves 128 W rows a stage for its 64 or 128 rows, and deeper than 5120 that is more than the planes' way through memory."""
+    tile = B.lib()._ZN3dyn14gate_fold_rowsEiii
+    heights = {tile(rows, 2 * inter, hidden) for rows in range(129, 513)} - {0}
+    assert (min(heights, default=256) < 192) == low
+    assert tile(513, 2 * inter, hidden) == tile(128, 2 * inter, hidden) == 0
