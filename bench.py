@@ -249,7 +249,7 @@ def policy_sweep(args):
     from workloads import gen
     rows, weights, layer = [], None, None
     stream = torch.cuda.Stream()
-    # "fit": the grid the policy's three overlap constants were fitted on; "holdout": points between and beside them
+    # "fit": the grid the policy's three overlap constants were first fitted on; "holdout": points between and beside them
     grid = {"fit": ((256, 512, 1024, 2048, 4096), ((64, 2048), (64, 8192), (256, 2048), (256, 8192))),
             "holdout": ((384, 768, 1536, 3072), ((32, 4096), (128, 1024), (128, 4096), (192, 8192)))}[args.sweep_grid]
     for P in grid[0]:

@@ -55,11 +55,13 @@ void reset_recording(dyn_scheduler *s, int k) {
 //   projections, few rows     weights stream at about 3.8 TB/s
 //   projections, more rows    the launcher's own tile and regime (dyn::gemm_path): a launch takes
 //                             ceil(workgroups / resident workgroups) rounds of one tile's duration,
-//                             a CU working at 1/256 of 0.95 PFLOP/s (1.25 with 256 x 256 tiles);
+//                             a CU working at 1/256 of 0.95 PFLOP/s (1.25 with 256 x 256 tiles); where the
+//                             launcher cuts its rows into tiles of several heights, the parts of a round that
+//                             its own rule counts (cut_rounds);
 //                             planes that are not folded in registers are read back at 5 TB/s
 //   decode attention          K/V stream at about 5.0 TB/s
-//   prefill attention         about 0.45 PFLOP/s (up to 0.94 since its waves work in two groups; not fitted again:
-//                             the order it leads to costs at most 2.3 % against the better one on 36 mixes)
+//   prefill attention         about 0.45 PFLOP/s (up to 0.94 since its waves work in two groups; not fitted again);
+//                             beside decodes in one launch, half of the shorter part is hidden
 //   element-wise operators    about 2 TB/s
 //   a dependent kernel in a replayed graph costs about 2 us before it does anything; the
 //   split-K reduce, the split-KV merge and the work-list kernel add their own launches.
@@ -97,7 +99,10 @@ OpCost estimate(const dyn_scheduler *s, const int32_t *ctx_len, int r0, int r1) 
             // the launcher's own choice of tile and regime: a launch takes ceil(workgroups / resident)
             // rounds, each as long as one workgroup's tile takes at the rate its regime reaches
             const dyn::GemmPath p = dyn::gemm_path(1, (int)T, (int)n, (int)k);
-            if (p.tail_rows) {   // the last rows as a launch of their own: at most 256 rows, tall or few-row tiles
+            dyn::WideCut wide;
+            dyn::FoldCut fold;
+            const bool wide_cut = dyn::gemm_cut(p, (int)T, (int)n, 0, &wide), fold_cut = dyn::gemm_fold_cut(p, (int)T, (int)n, (int)k, 0, &fold);
+            if (p.tail_rows && !wide_cut) {   // the last rows as a launch of their own: at most 256 rows, tall or few-row tiles
                 const dyn::GemmPath q = dyn::gemm_path(1, p.tail_rows, (int)n, (int)k);
                 const double q_rounds = std::ceil((double)q.workgroups / q.resident);
                 tail = std::max(n * k * e / R.w_stream, q_rounds * (5e-6 + 2.0 * q.bn * q.mt * (k / q.split) / (R.mfma / 256))) +
@@ -110,11 +115,12 @@ OpCost estimate(const dyn_scheduler *s, const int32_t *ctx_len, int r0, int r1) 
                 case dyn::GEMM_TALL:    // one workgroup per CU; planes (if any) are read back by the reduce kernel
                     compute = rounds * (5e-6 + wg_flops / (R.mfma / 256)) + (p.split > 1 ? p.split * T * n * 4 / 5e12 : 0);
                     break;
-                case dyn::GEMM_WIDE:
-                    compute = rounds * (3e-6 + wg_flops / (R.mfma_wide / 256));
+                case dyn::GEMM_WIDE:    // tiles of several heights: parts of a round
+                    compute = (wide_cut ? (double)dyn::cut_rounds(wide, (int)n) : rounds) * (3e-6 + wg_flops / (R.mfma_wide / 256));
                     break;
                 case dyn::GEMM_MANY:    // one or two workgroups share a CU
-                    compute = rounds * (p.resident / 256) * wg_flops / (R.mfma / 256);
+                    compute = fold_cut ? dyn::cut_rounds(fold, (int)n) * 2 * (2.0 * 128 * 128 * k) / (R.mfma / 256)
+                                       : rounds * (p.resident / 256) * wg_flops / (R.mfma / 256);
                     break;
                 default:
                     compute = 2.0 * std::ceil(T / 128) * 128 * n * k / R.mfma;
@@ -129,7 +135,7 @@ OpCost estimate(const dyn_scheduler *s, const int32_t *ctx_len, int r0, int r1) 
     const int32_t *q = s->q_start.data();
     const int s0 = (int)(std::lower_bound(q, q + s->n_seqs + 1, r0) - q);
     const int s1 = (int)(std::lower_bound(q, q + s->n_seqs + 1, r1) - q);
-    double kv_bytes = 0, prefill_flops = 0;
+    double kv_bytes = 0, prompt_kv_bytes = 0, prefill_flops = 0;
     for (int i = s0; i < s1; ++i) {
         const double ql = q[i + 1] - q[i], ctx = ctx_len[i];
         if (ql == 1) {
@@ -137,13 +143,15 @@ OpCost estimate(const dyn_scheduler *s, const int32_t *ctx_len, int r0, int r1) 
         } else {
             const double pairs = ql * (2 * ctx - ql + 1) / 2;     // (query, key) pairs of a causal chunk ending at ctx
             prefill_flops += 4.0 * NQ * D * pairs;
-            kv_bytes += ctx * 2 * NKV * D * e;
+            prompt_kv_bytes += ctx * 2 * NKV * D * e;
         }
     }
     c.us[DYN_OP_NORM1] = elementwise(2 * T * H * e);
     c.us[DYN_OP_QKV] = gemm((NQ + 2 * NKV) * D, H, 1);
     c.us[DYN_OP_ROPE_KV] = elementwise(2 * T * (NQ + 2 * NKV) * D * e);
-    c.us[DYN_OP_ATTN] = (kv_bytes / R.kv_stream + prefill_flops / R.prefill) * 1e6 + 3 * R.launch_us;
+    const double decodes = kv_bytes / R.kv_stream, prompts = prompt_kv_bytes / R.kv_stream + prefill_flops / R.prefill;
+    // both in one launch hide half of the shorter (2048 tokens beside 64 decodes: 117 and 67 us apart, 151 together)
+    c.us[DYN_OP_ATTN] = (std::max(decodes, prompts) + 0.5 * std::min(decodes, prompts)) * 1e6 + 3 * R.launch_us;
     c.us[DYN_OP_OPROJ] = gemm(H, NQ * D, 1);
     c.us[DYN_OP_NORM2] = elementwise(2 * T * H * e);
     if (g.n_experts > 0) {
@@ -171,9 +179,13 @@ OpCost estimate(const dyn_scheduler *s, const int32_t *ctx_len, int r0, int r1) 
 // round.  Fitted to prefill chunks of 256..4096 tokens beside 64..256 decodes at contexts
 // 2048..8192 (measured split time = longer + share x shorter, estimates scaled to the measured
 // sequential time): 0.58-0.76 at 256 tokens, 0.77-0.81 at 512, 0.71-0.88 at 1024, 0.90-0.99 at 2048.
+// The sequential order gained since (tiles of several heights, both attentions in one launch).  With that priced, and
+// 0.70 / 0.78 for 0.62 / 0.80, the choice is the faster order in 33 of 36 mixes of 256..4096 tokens beside 32..256 decodes, the others
+// within 1.1 % of it; priced as rounds of one height and attentions apart it was in 27, the others up to 5.3 % behind
+// (4096 tokens beside 256 decodes behind 8192 positions: split 3720 us, sequential 3533).
 double unhidden_share(int prefill_tokens) {
-    if (prefill_tokens <= 384) return 0.62;
-    if (prefill_tokens <= 1536) return 0.80;
+    if (prefill_tokens <= 384) return 0.70;
+    if (prefill_tokens <= 1536) return 0.78;
     return 0.93;
 }
 
@@ -336,8 +348,8 @@ dyn_status dyn_policy_auto(dyn_scheduler *s, const int32_t *ctx_len_host, int us
         const int multi_rows = s->q_start[1] - s->q_start[0] > 1 ? cut : T - cut;     // tokens of the multi-token side of the cut
         t_split = std::max(a, b) + unhidden_share(multi_rows) * std::min(a, b);
     }
-    // The model is good to about 5-8 % on mixes of 256..4096 prefill tokens and 64..256 decodes,
-    // but its errors on the two orders go the same way.  A predicted gain below 1 % is not worth
+    // The model is good to 5 % on mixes of up to 1024 prefill tokens beside 32..256 decodes and up to 19 % too long
+    // with 4096, but its errors on the two orders go the same way.  A predicted gain below 1 % is not worth
     // the extra streams.
     const bool split = cut > 0 && t_split < 0.99 * t_seq;
     if (choice) {

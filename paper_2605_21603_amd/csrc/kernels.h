@@ -118,6 +118,8 @@ hipError_t launch_gemm_fold(int grid, hipStream_t s, const void *X, int ldx, con
 // beat `now` (in rounds of 256 x 256 tiles); rows x N has to be GEMM_WIDE's.
 struct WideCut { int tiles[4]; };
 bool wide_cut(int rows, int N, float now, WideCut *out);
+bool gemm_cut(const GemmPath &p, int rows, int N, int n_cus, WideCut *cut);   // whether launch_gemm and launch_gemm_gated take them for p, on n_cus CUs (0: all)
+float cut_rounds(const WideCut &cut, int N);                                  // the longest CU's share, in rounds of 256 x 256 tiles
 hipError_t launch_gemm_cut(bool gated, hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int ldy, int rows, int N, int K,
                            const WideCut &cut);
 // Gate/up with planes folded in registers and the gate in the epilogue (bf16): the tile height for a launch, 0 where planes go over workgroups.
@@ -129,6 +131,7 @@ hipError_t launch_gemm_gate_fold(hipStream_t s, const void *X, int ldx, const vo
 struct FoldCut { int tiles[3]; };
 bool fold_cut(const GemmPath &p, int rows, int N, FoldCut *out);     // with weights that stay in the last-level cache
 bool gemm_fold_cut(const GemmPath &p, int rows, int N, int K, int n_cus, FoldCut *out);
+float cut_rounds(const FoldCut &cut, int N);                         // the longest CU's share, in rounds of two 128 x 128 tiles a CU
 hipError_t launch_gemm_fold_cut(hipStream_t s, const void *X, int ldx, const void *W, const void *R, void *Y, int rows, int N, int K, int S,
                                 const FoldCut &cut);
 // Expert-grouped projection without planes on 256-wide tiles of a height chosen per expert (the grouped launchers

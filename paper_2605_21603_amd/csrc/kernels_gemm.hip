@@ -312,7 +312,6 @@ GemmPath gemm_path(int dtype, int rows, int N, int K) {
     return p;
 }
 
-namespace {
 // A GEMM_WIDE launch on tiles of several heights, where that is the faster way; else p as it is: rounds of 256 tiles, and the last rows' launch
 // at what it takes beside a round (gate/up of 28672 columns, 64 / 128 / 256 rows: 48 / 60 / 76 us, a round 122).
 bool gemm_cut(const GemmPath &p, int rows, int N, int n_cus, WideCut *cut) {
@@ -320,7 +319,6 @@ bool gemm_cut(const GemmPath &p, int rows, int N, int n_cus, WideCut *cut) {
     const float tail = p.tail_rows == 0 ? 0.f : p.tail_rows <= 64 ? 0.40f : p.tail_rows <= 128 ? 0.49f : 0.62f;
     return wide_cut(rows, N, (p.workgroups + 255) / 256 + tail, cut);
 }
-}  // namespace
 
 bool gemm_uses_plane_buffer(int dtype, int rows, int N, int K) {
     if (dtype == 0 || rows <= 0) return false;

@@ -263,9 +263,13 @@ float longest_share(const int *n, const float *cost, int kinds, float odd = 0.f)
 // heights of their own, 800 / 1100 / 1300 / 1700 / 2112 rows 232 / 291 / 334 / 407 / 460 -> 207 / 264 / 301 / 386 / 439 us, steps 546 / 665 / 747 / 888 / 1048 -> 524 /
 // 642 / 731 / 869 / 1023; outside the lines 600 rows 186 -> 198, 3000 rows 623 -> 626.  (44 launches of 8 layer widths, 1024 to 8192 deep: 1.07x on average,
 // the least 0.98x.)
+static const float kWideCost[4] = {1.0f, 0.80f, 0.60f, 0.40f};            // 256, 192, 128, 64 rows
+float cut_rounds(const WideCut &cut, int N) {
+    const int nt = N / 256, n[4] = {cut.tiles[3] * nt, cut.tiles[2] * nt, cut.tiles[1] * nt, cut.tiles[0] * nt};
+    return longest_share(n, kWideCost, 4);
+}
 bool wide_cut(int rows, int N, float now, WideCut *out) {
-    static const float cost[4] = {1.0f, 0.80f, 0.60f, 0.40f};             // 256, 192, 128, 64 rows
-    const int nt = N / 256, units = (rows + 63) / 64;
+    const int units = (rows + 63) / 64;
     if (now < 2.0f) return false;
     float best = now * 0.955f;
     bool found = false;
@@ -273,9 +277,9 @@ bool wide_cut(int rows, int N, float now, WideCut *out) {
         for (int n2 = 0; n2 <= std::min((units - 3 * n3) / 2, 3); ++n2) {
             const int n1 = (units - 3 * n3 - 2 * n2) % 4, n4 = (units - 3 * n3 - 2 * n2) / 4;
             if (n1 > 1) continue;
-            const int n[4] = {n4 * nt, n3 * nt, n2 * nt, n1 * nt};
-            const float t = longest_share(n, cost, 4);
-            if (t < best) { best = t; *out = WideCut{{n1, n2, n3, n4}}; found = true; }
+            const WideCut c{{n1, n2, n3, n4}};
+            const float t = cut_rounds(c, N);
+            if (t < best) { best = t; *out = c; found = true; }
         }
     return found;
 }
@@ -327,8 +331,12 @@ hipError_t launch_gemm_fold_cut(hipStream_t s, const void *X, int ldx, const voi
 // launch measured in another process differs by up to 4 %.)
 // again: what a further height of less than a round costs beside its tiles, in rounds: they walk all of W once more (gemm_fold_cut; all tiles at once
 // walk it together).
+static const float kFoldCost[3] = {0.60f, 0.50f, 0.43f};
+float cut_rounds(const FoldCut &cut, int N) {
+    const int nt = N / 128, n[3] = {cut.tiles[2] * nt, cut.tiles[1] * nt, cut.tiles[0] * nt};
+    return longest_share(n, kFoldCost, 3, 0.6f);
+}
 static bool fold_cut(const GemmPath &p, int rows, int N, float again, FoldCut *out) {
-    static const float cost[3] = {0.60f, 0.50f, 0.43f};
     if (p.kind != GEMM_MANY || !p.folded) return false;
     const int nt = N / 128, units = (rows + 31) / 32;
     float best;
@@ -336,7 +344,7 @@ static bool fold_cut(const GemmPath &p, int rows, int N, float again, FoldCut *o
         best = 0.975f * ((p.workgroups + 255) / 256);
     } else {
         const int n[3] = {p.mt == 160 ? p.workgroups : 0, p.mt == 128 ? p.workgroups : 0, 0};
-        best = longest_share(n, cost, 3, 0.6f);
+        best = longest_share(n, kFoldCost, 3, 0.6f);
     }
     best *= 0.97f;
     bool found = false;
@@ -345,7 +353,7 @@ static bool fold_cut(const GemmPath &p, int rows, int N, float again, FoldCut *o
                           : units <= 4 * k ? FoldCut{{4 * k - units, units - 3 * k, 0}}
                                            : FoldCut{{0, 5 * k - units, units - 4 * k}};
         const int n[3] = {c.tiles[2] * nt, c.tiles[1] * nt, c.tiles[0] * nt}, all = n[0] + n[1] + n[2], last = n[2] ? n[2] : n[1] ? n[1] : n[0];
-        const float t = longest_share(n, cost, 3, 0.6f) + (all > 512 && last < all && last < 512 ? again : 0.f);
+        const float t = cut_rounds(c, N) + (all > 512 && last < all && last < 512 ? again : 0.f);
         if (t < best) { best = t; *out = c; found = true; }
     }
     return found;

@@ -222,6 +222,20 @@ def test_policy_estimates_follow_the_roofline():
     assert kv16 <= extra < kv16 + 5.0
 
 
+# (prompt tokens, decodes, their context) of the benchmark's dense layer, us of the sequential order and of the split, measured on one card
+@pytest.mark.parametrize("prompt,decodes,ctx,sequential,split", [
+    (256, 64, 2048, 380, 394), (512, 64, 2048, 549, 507), (512, 64, 8192, 876, 798), (512, 256, 8192, 2177, 2117), (384, 192, 8192, 1696, 1636),
+    (768, 32, 4096, 624, 652), (1024, 256, 8192, 2405, 2271), (1536, 128, 1024, 902, 927), (2048, 64, 2048, 1042, 1133), (2048, 256, 8192, 2674, 2735),
+    (3072, 128, 4096, 1895, 1942), (4096, 256, 2048, 2288, 2357), (4096, 256, 8192, 3533, 3720)])
+def test_policy_takes_the_order_that_is_clearly_faster(prompt, decodes, ctx, sequential, split):
+    """Where the two orders differ by more than 2 %: the model prices the launches as they run, tiles of several heights and both attentions in one."""
+    w = gen.mixed(prompt, decodes, ctx)
+    md = gen.metadata(w)
+    _, choice = B.Scheduler(B.make_config(w.shape), md["q_start"]).auto(md["ctx_len"])
+    assert abs(split / sequential - 1) > 0.02
+    assert bool(choice["split"]) == (split < sequential), choice
+
+
 def test_policy_considers_only_a_clean_prefill_decode_boundary():
     w = gen.config("c3")
     cfg = B.make_config(w.shape)
