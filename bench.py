@@ -592,14 +592,15 @@ def main():
     gu_avg_ms = sum(gu_ms) / len(gu_ms) if gu_ms else float("nan")
     if gu_ms and w.shape.dtype == "bf16" and gu_avg_ms > attn_avg_ms:
         gb, gf = gate_up_bytes_flops(w)
+        kernel = "%s projection (SiLU gate in the epilogue)" % ("gate/up" if not w.shape.n_experts else "expert-grouped gate/up")
         if gf / (MFMA_BF16_PEAK_TFLOPS * 1e12) > gb / (HBM_PEAK_GBS * 1e9):
             a = gf / 1e12 / (gu_avg_ms * 1e-3)
-            roofline = {"bound": "mfma", "kernel": "gemm_bf16_kernel (gate/up, SiLU gate in the epilogue)", "achieved": a,
+            roofline = {"bound": "mfma", "kernel": kernel, "achieved": a,
                         "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": a / MFMA_BF16_PEAK_TFLOPS,
                         "flops_per_launch": gf, "avg_launch_ms": gu_avg_ms}
         else:
             a = gb / 1e9 / (gu_avg_ms * 1e-3)
-            roofline = {"bound": "hbm", "kernel": "gemm_bf16_kernel (gate/up, SiLU gate in the epilogue)", "achieved": a,
+            roofline = {"bound": "hbm", "kernel": kernel, "achieved": a,
                         "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": a / HBM_PEAK_GBS, "bytes_per_launch": gb,
                         "avg_launch_ms": gu_avg_ms}
 
