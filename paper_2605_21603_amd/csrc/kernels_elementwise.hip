@@ -131,7 +131,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_norm_kernel(const float *__re
 #pragma unroll
         for (int e = 0; e < 4; ++e) { v[e] = f2bf(a[e]); v[e + 4] = f2bf(b[e]); }
         *reinterpret_cast<vec_t *>(Y + row * H + (size_t)i * 8) = v;
-        if (n < KEEP) kept[n] = v;
+        if (n < KEEP) kept[n < KEEP ? n : 0] = v;
 #pragma unroll
         for (int e = 0; e < 8; ++e) { const float f = bf2f(v[e]); ss = __builtin_fmaf(f, f, ss); }
     });
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_norm_kernel(const float *__re
     const float r = 1.0f / sqrtf(total / (float)H + eps);
     vectors([&](int i, auto n) {
         // beyond the kept vectors a thread reads back what it stored itself
-        const vec_t v = n < KEEP ? kept[n] : *reinterpret_cast<const vec_t *>(Y + row * H + (size_t)i * 8);
+        const vec_t v = n < KEEP ? kept[n < KEEP ? n : 0] : *reinterpret_cast<const vec_t *>(Y + row * H + (size_t)i * 8);
         const vec_t gv = *reinterpret_cast<const vec_t *>(g + (size_t)i * 8);
         vec_t o;
 #pragma unroll
