@@ -37,10 +37,10 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # withheld (traffic = null) instead of going stale silently.
 ATTN_SOURCE = tuple(os.path.join(ROOT, "paper_2605_21603_amd", "csrc", f) for f in ("attn_shape.h", "kernels_attn_mfma.hip", "kernels_attn_plan.hip"))
 ROCPROF_TRAFFIC = {
-    "c2": {"bytes": 1273169510 + 20705075, "source_sha256_16": "5d82f3e7965f6b64", "kv_chunk_positions": 256,
-           "source": "profiles/c2_sequential_attn_mfma_kernel.md (FETCH_SIZE 621,664.8 x 2.0 KiB + WRITE_SIZE 20,219.8 KiB)"},
-    "c5": {"bytes": 5050494566 + 21975040, "source_sha256_16": "5d82f3e7965f6b64", "kv_chunk_positions": 1024,
-           "source": "profiles/c5_sequential_32_layer_decode.md (FETCH_SIZE 2,466,061.8 x 2.0 KiB + WRITE_SIZE 21,460.0 KiB)"},
+    "c2": {"bytes": 1273196818 + 20705427, "source_sha256_16": "513ca5d8c9ef02d9", "kv_chunk_positions": 256,
+           "source": "profiles/c2_sequential_attn_mfma_kernel.md (FETCH_SIZE 621,678.1 x 2.0 KiB + WRITE_SIZE 20,220.1 KiB)"},
+    "c5": {"bytes": 5050729343 + 21974670, "source_sha256_16": "513ca5d8c9ef02d9", "kv_chunk_positions": 1024,
+           "source": "profiles/c5_sequential_32_layer_decode.md (FETCH_SIZE 2,466,176.4 x 2.0 KiB + WRITE_SIZE 21,459.6 KiB)"},
 }
 
 

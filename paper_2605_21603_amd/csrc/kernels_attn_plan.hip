@@ -54,6 +54,10 @@ __device__ __forceinline__ int scan64(int x) {
 
 struct PlanRow { int which, nc, n_tok, b_full, b_last; };
 
+// LONG: a dispatch that may hold a prompt of more than kLongRun rows.  Without the search for one, and the rows past kBatches, the launch is half as
+// long in code (norm and lists 34 -> 18 KB), which a kernel that runs once a step has to fetch first: one token's step 118.0 -> 116.5 us, 128 decodes
+// 401.3 -> 400.7.
+template <bool LONG>
 __device__ __forceinline__ void attn_plan(const int32_t *__restrict__ seq_of_token, const int32_t *__restrict__ pos_of_token, int rows, int ct,
                                           int tg1, int n_kv, int32_t *__restrict__ plan0, int32_t *__restrict__ plan1,
                                           int32_t *__restrict__ ct_of_token) {
@@ -69,17 +73,19 @@ __device__ __forceinline__ void attn_plan(const int32_t *__restrict__ seq_of_tok
     Run known{0, 0};
     auto run_of = [&](int t) {
         Run run{t, t + 1};
-        const int first = __builtin_amdgcn_readfirstlane(t);
-        if (rows <= kLongRun || first >= rows) return run;
-        for (int edge : {first, min(first + 63, rows - 1)}) {
-            if (edge < known.start || edge >= known.end) {
-                const int s = seq_of_token[edge];
-                known = run_around(edge, rows, [&](int row, int step) {
-                    const int r = row + step * (lane + 1);
-                    return (int)__popcll(__ballot(r >= 0 && r < rows && seq_of_token[min(max(r, 0), rows - 1)] == s));
-                });
+        if constexpr (LONG) {
+            const int first = __builtin_amdgcn_readfirstlane(t);
+            if (first >= rows) return run;
+            for (int edge : {first, min(first + 63, rows - 1)}) {
+                if (edge < known.start || edge >= known.end) {
+                    const int s = seq_of_token[edge];
+                    known = run_around(edge, rows, [&](int row, int step) {
+                        const int r = row + step * (lane + 1);
+                        return (int)__popcll(__ballot(r >= 0 && r < rows && seq_of_token[min(max(r, 0), rows - 1)] == s));
+                    });
+                }
+                if (t >= known.start && t < known.end) run = known;
             }
-            if (t >= known.start && t < known.end) run = known;
         }
         return run;
     };
@@ -136,7 +142,7 @@ __device__ __forceinline__ void attn_plan(const int32_t *__restrict__ seq_of_tok
     }
 #pragma unroll
     for (int b = 0; b < kBatches; ++b) count(kept[b]);
-    for (int t0 = kBatches * 1024; t0 < rows; t0 += 1024) {
+    for (int t0 = kBatches * 1024; LONG && t0 < rows; t0 += 1024) {
         const int t = t0 + (int)threadIdx.x;
         const Run run = run_of(t);
         if (t < rows) count(classify(t, run));
@@ -200,7 +206,7 @@ __device__ __forceinline__ void attn_plan(const int32_t *__restrict__ seq_of_tok
 #pragma unroll
     for (int b = 0; b < kBatches; ++b)
         if (b * 1024 < rows) place(b * 1024 + (int)threadIdx.x, kept[b]);
-    for (int t0 = kBatches * 1024; t0 < rows; t0 += 1024) {
+    for (int t0 = kBatches * 1024; LONG && t0 < rows; t0 += 1024) {
         const int t = t0 + (int)threadIdx.x;
         const Run run = run_of(t);
         place(t, t < rows ? classify(t, run) : PlanRow{0, 0, 0, 0, 0});
@@ -208,20 +214,24 @@ __device__ __forceinline__ void attn_plan(const int32_t *__restrict__ seq_of_tok
     if (threadIdx.x == 0) { plan0[0] = total0; plan1[0] = base[kPlanBuckets]; plan1[1] = 0; }   // list sizes; list 1's work counter
 }
 
+static_assert(kLongRun <= kBatches * 1024, "the short form keeps all its rows");
+
+template <bool LONG>
 __global__ __launch_bounds__(1024) void attn_plan_kernel(const int32_t *__restrict__ seq_of_token, const int32_t *__restrict__ pos_of_token, int rows,
                                                          int ct, int tg1, int n_kv, int32_t *__restrict__ plan0, int32_t *__restrict__ plan1,
                                                          int32_t *__restrict__ ct_of_token) {
-    attn_plan(seq_of_token, pos_of_token, rows, ct, tg1, n_kv, plan0, plan1, ct_of_token);
+    attn_plan<LONG>(seq_of_token, pos_of_token, rows, ct, tg1, n_kv, plan0, plan1, ct_of_token);
 }
 
 // Workgroup 0 builds the lists, each of the others normalises four rows.
+template <bool LONG>
 __global__ __launch_bounds__(1024) void norm_plan_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ g, bf16_t *__restrict__ out, int ld_out,
                                                          int H, float eps, const int32_t *__restrict__ seq_of_token,
                                                          const int32_t *__restrict__ pos_of_token, int rows, int ct, int tg1, int n_kv,
                                                          int32_t *__restrict__ plan0, int32_t *__restrict__ plan1,
                                                          int32_t *__restrict__ ct_of_token) {
     if (blockIdx.x == 0) {
-        attn_plan(seq_of_token, pos_of_token, rows, ct, tg1, n_kv, plan0, plan1, ct_of_token);
+        attn_plan<LONG>(seq_of_token, pos_of_token, rows, ct, tg1, n_kv, plan0, plan1, ct_of_token);
         return;
     }
     __shared__ float part[4][4];
@@ -236,7 +246,7 @@ AttnPlan attn_plan_lists(int32_t *plan, const AttnShape &sh, int rows) {
 
 hipError_t launch_attn_plan(const int32_t *seq_of_token, const int32_t *pos_of_token, int32_t *plan, const AttnShape &sh, int rows, hipStream_t s) {
     const AttnPlan l = attn_plan_lists(plan, sh, rows);
-    hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(1024), 0, s, seq_of_token, pos_of_token, rows, sh.chunk_pages * PS,
+    hipLaunchKernelGGL(rows > kLongRun ? attn_plan_kernel<true> : attn_plan_kernel<false>, dim3(1), dim3(1024), 0, s, seq_of_token, pos_of_token, rows, sh.chunk_pages * PS,
                        attn_prefill_block_tokens(sh), sh.n_kv, l.single, l.multi, l.ct_of_token);
     return hipGetLastError();
 }
@@ -245,7 +255,7 @@ hipError_t launch_norm_plan(const void *x, const void *g, void *out, int ld_out,
                             const int32_t *pos_of_token, int32_t *plan, const AttnShape &sh, hipStream_t s) {
     if (rows <= 0) return hipSuccess;
     const AttnPlan l = attn_plan_lists(plan, sh, rows);
-    hipLaunchKernelGGL(norm_plan_kernel, dim3(1 + (rows + 3) / 4), dim3(1024), 0, s, (const bf16_t *)x, (const bf16_t *)g, (bf16_t *)out, ld_out, H, eps,
+    hipLaunchKernelGGL(rows > kLongRun ? norm_plan_kernel<true> : norm_plan_kernel<false>, dim3(1 + (rows + 3) / 4), dim3(1024), 0, s, (const bf16_t *)x, (const bf16_t *)g, (bf16_t *)out, ld_out, H, eps,
                        seq_of_token, pos_of_token, rows, sh.chunk_pages * PS, attn_prefill_block_tokens(sh), sh.n_kv, l.single, l.multi, l.ct_of_token);
     return hipGetLastError();
 }
