@@ -122,7 +122,8 @@ __host__ __device__ inline int prompt_chunk_positions(int t, int p, int start, i
     return prefill_run_chunk_positions(reach, tg, n_kv, rows, p - (t - start) + (rows + 1) / 2);
 }
 // The run of rows, of one sequence, that row `at` of a dispatch of `rows` rows lies in.  count(row, step): how many of the rows row + step, row + 2 step, ..
-// row + 64 step are the sequence's, before the first that is not or is no row.  (Up to 64 x 4161 rows to either side.)
+// row + 64 step are the sequence's, before the first that is not or is no row.  (Up to 64 x 4161 rows to either side: a longer run
+// has the longest chunks wherever its ends are.)
 struct Run { int start, end; };
 template <class Count>
 __host__ __device__ inline Run run_around(int at, int rows, Count &&count) {
