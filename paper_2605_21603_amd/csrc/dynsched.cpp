@@ -180,12 +180,14 @@ OpCost estimate(const dyn_scheduler *s, const int32_t *ctx_len, int r0, int r1) 
 // 2048..8192 (measured split time = longer + share x shorter, estimates scaled to the measured
 // sequential time): 0.58-0.76 at 256 tokens, 0.77-0.81 at 512, 0.71-0.88 at 1024, 0.90-0.99 at 2048.
 // The sequential order gained since (tiles of several heights, both attentions in one launch).  With that priced, and
-// 0.70 / 0.78 for 0.62 / 0.80, the choice is the faster order in 33 of 36 mixes of 256..4096 tokens beside 32..256 decodes, the others
-// within 1.1 % of it; priced as rounds of one height and attentions apart it was in 27, the others up to 5.3 % behind
-// (4096 tokens beside 256 decodes behind 8192 positions: split 3720 us, sequential 3533).
+// 0.70 / 0.76 for 0.62 / 0.80 up to 384 / 640 tokens, the choice is the faster order in 90 of 103 mixes of 256..4096 tokens beside 16..256 decodes (36 of 4096 x
+// 14336 layers, the others 2048 to 8192 wide with 64- and 128-wide heads) and 0.16 % behind on average, 4.2 % at most (64-wide heads, 768 + 128);
+// priced as rounds of one height and attentions apart it was in 44, 2.05 % behind on average and up to 11 % (64-wide heads, 256 + 128: sequential 390, split
+// 435 us; 4096 wide, 4096 + 256 behind 8192 positions: 3533, 3720).
 double unhidden_share(int prefill_tokens) {
     if (prefill_tokens <= 384) return 0.70;
-    if (prefill_tokens <= 1536) return 0.78;
+    if (prefill_tokens <= 640) return 0.76;
+    if (prefill_tokens <= 1536) return 0.80;
     return 0.93;
 }
 
@@ -348,8 +350,8 @@ dyn_status dyn_policy_auto(dyn_scheduler *s, const int32_t *ctx_len_host, int us
         const int multi_rows = s->q_start[1] - s->q_start[0] > 1 ? cut : T - cut;     // tokens of the multi-token side of the cut
         t_split = std::max(a, b) + unhidden_share(multi_rows) * std::min(a, b);
     }
-    // The model is good to 5 % on mixes of up to 1024 prefill tokens beside 32..256 decodes and up to 19 % too long
-    // with 4096, but its errors on the two orders go the same way.  A predicted gain below 1 % is not worth
+    // For a 4096-wide layer the model is good to 5 % on mixes of up to 1024 prefill tokens beside 32..256 decodes and up to 19 % too long
+    // with 4096, for 64-wide heads up to half too short, but its errors on the two orders go the same way.  A predicted gain below 1 % is not worth
     // the extra streams.
     const bool split = cut > 0 && t_split < 0.99 * t_seq;
     if (choice) {

@@ -236,6 +236,19 @@ def test_policy_takes_the_order_that_is_clearly_faster(prompt, decodes, ctx, seq
     assert bool(choice["split"]) == (split < sequential), choice
 
 
+@pytest.mark.parametrize("hidden,n_q,hd,inter,prompt,decodes,ctx,sequential,split", [
+    (2048, 32, 64, 8192, 256, 128, 4096, 390, 435), (2048, 32, 64, 8192, 1536, 128, 4096, 848, 881), (2048, 16, 128, 8192, 4096, 256, 2048, 1158, 1199),
+    (5120, 40, 128, 13824, 512, 256, 2048, 1070, 1033), (5120, 40, 128, 13824, 1024, 128, 4096, 1270, 1230), (5120, 40, 128, 13824, 1536, 256, 8192, 2755, 2831),
+    (8192, 64, 128, 28672, 512, 64, 2048, 1432, 1383), (8192, 64, 128, 28672, 768, 128, 4096, 2041, 2243), (8192, 64, 128, 28672, 3072, 256, 8192, 7093, 7573)])
+def test_policy_takes_the_clearly_faster_order_of_other_layers(hidden, n_q, hd, inter, prompt, decodes, ctx, sequential, split):
+    """The same for layers of other widths and 64-wide heads."""
+    w = gen.mixed(prompt, decodes, ctx, shape=gen.LayerShape("bf16", hidden, n_q, 8, hd, inter))
+    md = gen.metadata(w)
+    _, choice = B.Scheduler(B.make_config(w.shape), md["q_start"]).auto(md["ctx_len"])
+    assert abs(split / sequential - 1) > 0.02
+    assert bool(choice["split"]) == (split < sequential), choice
+
+
 def test_policy_considers_only_a_clean_prefill_decode_boundary():
     w = gen.config("c3")
     cfg = B.make_config(w.shape)
